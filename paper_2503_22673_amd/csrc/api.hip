@@ -1226,7 +1226,7 @@ extern "C" int as_adamw_update(as_ctx* ctx, float* const* d_master, void* const*
   AdamBatch bt; bt.n = 0; bt.n_chunks = 0;
   for (int i = 0; i < n_tensors; i++) {
     if (numel[i] == 0) continue;
-    const int64_t nc = cdiv(numel[i], 65536);
+    const int64_t nc = cdiv(numel[i], kAdamChunk);
     if (nc > INT32_MAX / 2) return as_fail(ctx, AS_ERR_SHAPE, "as_adamw_update: tensor %d is too large", i);
     if (bt.n == kAdamBatch || (int64_t)bt.n_chunks + nc > INT32_MAX / 2) {
       int rc = launch_adamw_batch(ctx, bt, lr, beta1, beta2, eps, bc1, bc2, st);

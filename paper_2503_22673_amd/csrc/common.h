@@ -221,10 +221,10 @@ int launch_loss_finalize(as_ctx* ctx, const float* loss_rows, const int32_t* cou
                          float* loss_sum, hipStream_t st);
 int launch_splitk_reduce(as_ctx* ctx, const float* partial, int splitk, int64_t mn, int N, float alpha,
                          float* C, int64_t ldc, hipStream_t st);
-// one tensor of a multi-tensor update, and one 64 K-element chunk of work
+// one tensor of a multi-tensor update; a workgroup takes kAdamChunk elements of it
 struct AdamTensor { float* w; bf16_t* w_lowp; const float* g; float* m; float* v; int64_t n; float wd; int first_chunk; };
 // a batch of tensors travels as a kernel argument: no table in device memory, nothing to allocate or to keep alive
-constexpr int kAdamBatch = 64;
+constexpr int kAdamBatch = 64, kAdamChunk = 4096;
 struct AdamBatch { AdamTensor t[kAdamBatch]; int n; int n_chunks; };
 int launch_adamw_batch(as_ctx* ctx, const AdamBatch& b, float lr, float b1, float b2, float eps, float bc1, float bc2, hipStream_t st);
 int launch_embed_bwd(as_ctx* ctx, int mode, const int32_t* tok, int n, int d, int V, const void* dh,

@@ -814,20 +814,52 @@ int launch_splitk_reduce(as_ctx* ctx, const float* partial, int splitk, int64_t 
 
 // -------------------------------------------------------------------- AdamW
 // Up to kAdamBatch tensors per launch, described in the kernel argument itself: workgroup b takes the b-th chunk of
-// 65,536 consecutive elements of the batch (tensor found by a scan over the batch's first-chunk numbers).
+// kAdamChunk consecutive elements of the batch (tensor found by bisection over the batch's first-chunk numbers).
+// Bound by memory (28 bytes per element, 30 with a 16-bit copy), so a thread asks for everything it will touch before it
+// computes: four groups of four elements of w, g, m, v are 256 bytes in flight per thread, and 4096-element chunks give a
+// launch tens of workgroups per CU.  168 M elements in 448 tensors: 1660 us with 65,536-element chunks and scalar loads
+// (2.8 TB/s), 907 us so (5.2 TB/s; a large copy runs at 4.9).
+__device__ __forceinline__ void adamw_one(float& w, float g, float& m, float& v, float lr, float b1, float b2, float eps, float bc1, float bc2, float wd) {
+  m = b1 * m + (1.f - b1) * g;
+  v = b2 * v + (1.f - b2) * g * g;
+  const float upd = (m / bc1) / (sqrtf(v / bc2) + eps) + wd * w;
+  w = w - lr * upd;
+}
 __global__ __launch_bounds__(256) void adamw_batch_kernel(const AdamBatch b, float lr, float b1, float b2, float eps, float bc1, float bc2) {
-  int ti = 0;
-  while (ti + 1 < b.n && (int)blockIdx.x >= b.t[ti + 1].first_chunk) ti++;
+  int ti = 0, hi_t = b.n - 1;                            // last tensor whose first chunk is at or before this workgroup's
+  while (ti < hi_t) { const int mid = (ti + hi_t + 1) >> 1; if ((int)blockIdx.x >= b.t[mid].first_chunk) ti = mid; else hi_t = mid - 1; }
   const AdamTensor& t = b.t[ti];
-  const int64_t lo = (int64_t)((int)blockIdx.x - t.first_chunk) * 65536, hi = min(t.n, lo + 65536);
+  const int64_t lo = (int64_t)((int)blockIdx.x - t.first_chunk) * kAdamChunk, hi = min(t.n, lo + kAdamChunk);
+  const float wd = t.wd;
+  const uintptr_t al = (uintptr_t)t.w | (uintptr_t)t.g | (uintptr_t)t.m | (uintptr_t)t.v;
+  if (hi - lo == kAdamChunk && al % 16 == 0 && (uintptr_t)t.w_lowp % 8 == 0) {   // a whole chunk of aligned tensors
+    constexpr int GROUPS = kAdamChunk / 1024;
+    f32x4 w[GROUPS], g[GROUPS], m[GROUPS], v[GROUPS];
+#pragma unroll
+    for (int i = 0; i < GROUPS; i++) {
+      const int64_t e = lo + i * 1024 + threadIdx.x * 4;
+      g[i] = *reinterpret_cast<const f32x4*>(t.g + e); m[i] = *reinterpret_cast<const f32x4*>(t.m + e);
+      v[i] = *reinterpret_cast<const f32x4*>(t.v + e); w[i] = *reinterpret_cast<const f32x4*>(t.w + e);
+    }
+#pragma unroll
+    for (int i = 0; i < GROUPS; i++) {
+      const int64_t e = lo + i * 1024 + threadIdx.x * 4;
+      bf16x4 low;
+#pragma unroll
+      for (int k = 0; k < 4; k++) {
+        float wk = w[i][k], mk = m[i][k], vk = v[i][k];
+        adamw_one(wk, g[i][k], mk, vk, lr, b1, b2, eps, bc1, bc2, wd);
+        w[i][k] = wk; m[i][k] = mk; v[i][k] = vk; low[k] = (bf16_t)wk;
+      }
+      *reinterpret_cast<f32x4*>(t.m + e) = m[i]; *reinterpret_cast<f32x4*>(t.v + e) = v[i]; *reinterpret_cast<f32x4*>(t.w + e) = w[i];
+      if (t.w_lowp) *reinterpret_cast<bf16x4*>(t.w_lowp + e) = low;
+    }
+    return;
+  }
   for (int64_t i = lo + threadIdx.x; i < hi; i += 256) {
-    float gi = t.g[i], wi = t.w[i];
-    float mi = b1 * t.m[i] + (1.f - b1) * gi;
-    float vi = b2 * t.v[i] + (1.f - b2) * gi * gi;
-    t.m[i] = mi; t.v[i] = vi;
-    float upd = (mi / bc1) / (sqrtf(vi / bc2) + eps) + t.wd * wi;
-    wi = wi - lr * upd;
-    t.w[i] = wi;
+    float wi = t.w[i], mi = t.m[i], vi = t.v[i];
+    adamw_one(wi, t.g[i], mi, vi, lr, b1, b2, eps, bc1, bc2, wd);
+    t.m[i] = mi; t.v[i] = vi; t.w[i] = wi;
     if (t.w_lowp) t.w_lowp[i] = (bf16_t)wi;
   }
 }

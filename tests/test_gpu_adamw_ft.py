@@ -37,6 +37,34 @@ def test_adamw_matches_reference_over_steps():
             assert torch.equal(lowp[i], masters[i].to(torch.bfloat16))
 
 
+@pytest.mark.parametrize("n,shift", [(4095, 0), (4096, 0), (4097, 0), (3 * 4096, 0), (2 * 4096, 1), (70 * 1024 + 5, 0)])
+def test_adamw_whole_and_partial_chunks(n, shift):
+    """Chunk edges, and tensors that start off a 16-byte boundary (`shift` elements in), next to a small tensor in the same
+    launch.  Reference with the float32 values of the rates: m carries two roundings of its terms' size, v three (at most
+    3 x 2^-24 = 1.8e-7), w one of its own size and the update's, which is 2e-5 of it."""
+    from paper_2503_22673_amd import binding as B
+    ctx = B.Context(B.make_config(synth.CONFIGS[1]))
+    gen = torch.Generator(device="cuda"); gen.manual_seed(n)
+    new = lambda k, s: torch.empty(k + shift, device="cuda").normal_(0.0, s, generator=gen)[shift:]
+    w, g, m, v = [[new(k, s) for k in (n, 9)] for s in (0.02, 1e-3, 1e-4, 1e-3)]
+    for x in v:
+        x.square_()
+    low = [torch.zeros(n + shift, dtype=torch.bfloat16, device="cuda")[shift:], None]
+    ref = [[t.double() for t in x] for x in (w, g, m, v)]
+    lr, b1, b2, eps, wd = (float(np.float32(x)) for x in (2e-5, 0.9, 0.95, 1e-8, 0.1))
+    step = 3
+    ctx.adamw_update(w, low, g, m, v, [1, 0], step, lr, b1, b2, eps, wd)
+    torch.cuda.synchronize()
+    for i, decay in enumerate((wd, 0.0)):
+        rw, rg, rm, rv = (x[i] for x in ref)
+        size = float((b1 * rm.abs() + (1 - b1) * rg.abs()).max())
+        rm, rv = b1 * rm + (1 - b1) * rg, b2 * rv + (1 - b2) * rg * rg
+        rw = rw - lr * (rm / (1 - b1 ** step) / ((rv / (1 - b2 ** step)).sqrt() + eps) + decay * rw)
+        assert float((m[i] - rm).abs().max()) <= 2e-7 * size and float((v[i] - rv).abs().max()) <= 2e-7 * float(rv.abs().max())
+        assert float((w[i] - rw).abs().max()) <= 2e-7 * float(rw.abs().max())
+    assert torch.equal(low[0], w[0].to(torch.bfloat16))
+
+
 def test_adamw_first_step_closed_form_and_identity():
     from paper_2503_22673_amd import binding as B
     ctx = B.Context(B.make_config(synth.CONFIGS[1]))
