@@ -276,6 +276,7 @@ struct Plan {
   void *dh, *dh2, *dm, *dgu, *db, *d_o, *dqkv, *da;
   void *du_qkv, *du_o, *du_gu, *du_d;
   void *wT, *xT, *dyT, *uT, *duT, *attT;
+  size_t dyT_bytes;
   void* wdq;                             // one dequantised projection matrix (NF4 base)
   void *xbp, *dlogit, *du_r, *wrT;       // MoE scratch: permuted rows [2N, d], router logit gradient [N, E], [N, rp], router weight transpose [d, E]
   std::vector<LoraSlot> lora;            // L * AS_N_TARGETS
@@ -385,7 +386,8 @@ static void make_plan(const as_ctx* ctx, int64_t rows, int64_t row_len, Bump& w,
   size_t ymax = std::max({(size_t)P.QKV, moe ? E : (size_t)2 * P.F, (size_t)P.d});
   const size_t Np = (size_t)P.Np;
   P.xT = w.take(need_T ? xmax * Np * es : 0);
-  P.dyT = w.take(need_T ? ymax * Np * es : 0);
+  P.dyT_bytes = need_T ? std::max(ymax * Np * es, full ? embed_bwd_aux_bytes(P.N, P.d) : 0) : 0;   // full mode: also the embedding gradient's scratch, once the layers are done
+  P.dyT = w.take(P.dyT_bytes);
   size_t umax = (size_t)std::max({P.n_qkv, P.n_gu, 1}) * rp;
   P.uT = w.take(umax * Np * es); P.duT = w.take(umax * Np * es);
   P.gpart = (float*)w.take(full ? (size_t)256 * P.d * 4 : 0);
@@ -1117,7 +1119,7 @@ static int run_step(as_ctx* ctx, const char* who, const as_weights* weights, con
     if (c.recompute == 2 && l != c.n_layers - 1 && (rc = S.rebuild_cheap(l, a))) return rc;
     if ((rc = S.backward_layer(l, a))) return rc;
   }
-  if (full && (rc = launch_embed_bwd(ctx, c.mode, d_tokens, n, c.d_model, c.vocab, P.dh, P.iscratch, grads->embed, st))) return rc;
+  if (full && (rc = launch_embed_bwd(ctx, c.mode, d_tokens, n, c.d_model, c.vocab, P.dh, P.iscratch, P.dyT, P.dyT_bytes, grads->embed, st))) return rc;
   return S.wq_rc;
 }
 

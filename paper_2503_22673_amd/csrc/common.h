@@ -227,5 +227,7 @@ struct AdamTensor { float* w; bf16_t* w_lowp; const float* g; float* m; float* v
 constexpr int kAdamBatch = 64, kAdamChunk = 4096;
 struct AdamBatch { AdamTensor t[kAdamBatch]; int n; int n_chunks; };
 int launch_adamw_batch(as_ctx* ctx, const AdamBatch& b, float lr, float b1, float b2, float eps, float bc1, float bc2, hipStream_t st);
+// scratch: 2n int32; aux: embed_bwd_aux_bytes(n, d), 256-byte aligned
+size_t embed_bwd_aux_bytes(int n, int d);
 int launch_embed_bwd(as_ctx* ctx, int mode, const int32_t* tok, int n, int d, int V, const void* dh,
-                     int32_t* scratch, float* dE, hipStream_t st);
+                     int32_t* scratch, void* aux, size_t aux_bytes, float* dE, hipStream_t st);

@@ -871,66 +871,225 @@ int launch_adamw_batch(as_ctx* ctx, const AdamBatch& b, float lr, float b1, floa
 }
 
 // ------------------------------------------------- embedding gradient (full)
-// dE[v] = sum of dh[t] over the positions t holding token v, in ascending t.
-// rank[t] = number of earlier positions with the same token (brute force over
-// LDS-staged token tiles) gives each position a fixed slot in its token's list.
-__global__ void token_rank_kernel(const int32_t* __restrict__ tok, int n, int32_t* __restrict__ prev) {
-  // prev[t] = largest t' < t with tok[t'] == tok[t], or -1: a linked list per token
-  __shared__ int32_t tile[1024];
-  int t = blockIdx.x * blockDim.x + threadIdx.x;
-  int mine = t < n ? tok[t] : -1;
-  int best = -1;
-  int t_hi = min(n, (int)((blockIdx.x + 1) * blockDim.x));
-  for (int base = 0; base < t_hi; base += 1024) {
-    __syncthreads();
-    if (base + (int)threadIdx.x < n) tile[threadIdx.x] = tok[base + threadIdx.x];
-    __syncthreads();
-    int lim = min(1024, t - base);
-    for (int i = 0; i < lim; i++) if (tile[i] == mine) best = base + i;
+// dE[v] = sum of dh[t] over the positions t holding token v, in ascending t.  Token frequencies fall off like 1 / rank: one
+// token may hold an eighth of all positions, so neither a workgroup per token nor a walk along its positions balances.
+// The positions are sorted by token (stable, least significant 9 bits first: a histogram, a scan and a scatter per digit),
+// the sorted list is cut into pieces of EMB_PIECE positions, and a workgroup adds up the runs inside its piece.  A run that
+// lies inside one piece is written straight to dE; a run that crosses pieces leaves a float partial row per piece, which
+// the workgroup of the piece it starts in adds in order.  Bound by reading dh and writing dE once.
+// 15,700 positions, d 2048, vocabulary 32,000, Zipf(1.1): 121 us in all (sums 35, zero fill of dE 34, sort 42,
+// join 10) against 5950 us for a walk along each token's positions.
+constexpr int EMB_BITS = 9, EMB_BINS = 1 << EMB_BITS, EMB_TILE = 2048, EMB_PIECE = 32;
+
+// cnt[bin * n_tiles + tile] = positions of this tile whose token has `bin` as its current digit
+__global__ __launch_bounds__(256) void embed_hist_kernel(const int32_t* __restrict__ tok, const int32_t* __restrict__ pos, int n, int shift,
+                                                         int n_tiles, int32_t* __restrict__ cnt) {
+  __shared__ int32_t h[EMB_BINS];
+  for (int i = threadIdx.x; i < EMB_BINS; i += 256) h[i] = 0;
+  __syncthreads();
+  for (int i = threadIdx.x; i < EMB_TILE; i += 256) {
+    const int k = blockIdx.x * EMB_TILE + i;
+    if (k < n) atomicAdd(&h[((uint32_t)tok[pos ? pos[k] : k] >> shift) & (EMB_BINS - 1)], 1);
   }
-  if (t < n) prev[t] = best;
+  __syncthreads();
+  for (int i = threadIdx.x; i < EMB_BINS; i += 256) cnt[(int64_t)i * n_tiles + blockIdx.x] = h[i];
 }
-template <typename T>
-__global__ void embed_bwd_kernel(const int32_t* __restrict__ tok, const int32_t* __restrict__ prev,
-                                 const int32_t* __restrict__ is_last, int n, int d, const T* __restrict__ dh,
-                                 float* __restrict__ dE) {
-  // one block per position that is the LAST occurrence of its token: walk the list backwards
-  int t = blockIdx.x;
-  if (!is_last[t]) return;
-  int v = tok[t];
-  for (int j = threadIdx.x; j < d; j += blockDim.x) {
-    // collect in ascending order: first count, then the walk is reversed by recursion-free two passes
-    float acc = 0.f;
-    // ascending order needs the list reversed; addition order is fixed either way (descending t)
-    for (int u = t; u >= 0; u = prev[u]) acc += to_f<T>(dh[(int64_t)u * d + j]);
-    dE[(int64_t)v * d + j] = acc;
+// exclusive scan of m integers in place, one workgroup
+__global__ __launch_bounds__(1024) void embed_scan_kernel(int32_t* __restrict__ cnt, int m) {
+  __shared__ int32_t wsum[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int per = (m + 1023) / 1024, b = min(m, tid * per), e = min(m, b + per);
+  int s = 0;
+  for (int i = b; i < e; i++) s += cnt[i];
+  int incl = s;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o, 64); if (lane >= o) incl += v; }
+  if (lane == 63) wsum[wave] = incl;
+  __syncthreads();
+  int base = incl - s;
+  for (int w = 0; w < wave; w++) base += wsum[w];
+  for (int i = b; i < e; i++) { const int v = cnt[i]; cnt[i] = base; base += v; }
+}
+// stable scatter of the tile's positions in order, 256 at a time; the rank of a position among those with its digit is that
+// among the lower lanes of its wave (ballots over the digit's bits) plus the counts of the waves and rounds before
+__device__ __forceinline__ void embed_scatter_tile(const int32_t* __restrict__ tok, const int32_t* pos, int first, int n, int shift,
+                                                   int32_t* base, int32_t (*wcnt)[EMB_BINS], int32_t* out) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int r = 0; r < EMB_TILE / 256 && first + r * 256 < n; r++) {
+    for (int i = tid; i < 4 * EMB_BINS; i += 256) (&wcnt[0][0])[i] = 0;
+    __syncthreads();
+    const int k = first + r * 256 + tid;
+    const bool live = k < n;
+    const int p = live ? (pos ? pos[k] : k) : 0;
+    const int d = live ? (int)(((uint32_t)tok[p] >> shift) & (EMB_BINS - 1)) : 0;
+    uint64_t same = __ballot(live);
+#pragma unroll
+    for (int bit = 0; bit < EMB_BITS; bit++) { const uint64_t m = __ballot((d >> bit) & 1); same &= ((d >> bit) & 1) ? m : ~m; }
+    const int rank = __popcll(same & ((1ull << lane) - 1));
+    if (live && rank == 0) wcnt[wave][d] = __popcll(same);
+    __syncthreads();
+    if (live) {
+      int at = base[d] + rank;
+      for (int w = 0; w < wave; w++) at += wcnt[w][d];
+      out[at] = p;
+    }
+    __syncthreads();
+    for (int i = tid; i < EMB_BINS; i += 256) base[i] += wcnt[0][i] + wcnt[1][i] + wcnt[2][i] + wcnt[3][i];
+    __syncthreads();
   }
 }
-__global__ void mark_last_kernel(const int32_t* __restrict__ prev, int n, int32_t* __restrict__ is_last) {
-  int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n) return;
-  int p = prev[t];
-  if (p >= 0) is_last[p] = 0;      // plain stores of the same value: order does not matter
+__global__ __launch_bounds__(256) void embed_scatter_kernel(const int32_t* __restrict__ tok, const int32_t* __restrict__ pos, int n, int shift,
+                                                            int n_tiles, const int32_t* __restrict__ cnt, int32_t* __restrict__ out) {
+  __shared__ int32_t base[EMB_BINS], wcnt[4][EMB_BINS];
+  for (int i = threadIdx.x; i < EMB_BINS; i += 256) base[i] = cnt[(int64_t)i * n_tiles + blockIdx.x];
+  embed_scatter_tile(tok, pos, blockIdx.x * EMB_TILE, n, shift, base, wcnt, out);
 }
-__global__ void fill_int_kernel(int32_t* p, int n, int v) {
-  int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < n) p[t] = v;
+// at most one tile of positions: every digit in one launch, the positions in LDS
+__global__ __launch_bounds__(256) void embed_sort_tile_kernel(const int32_t* __restrict__ tok, int n, int V, int32_t* __restrict__ out) {
+  __shared__ int32_t base[EMB_BINS], wcnt[4][EMB_BINS], buf[2][EMB_TILE];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int32_t* in = nullptr;
+  int b = 0;
+  for (int shift = 0; shift == 0 || (shift < 31 && (V - 1) >> shift); shift += EMB_BITS, b ^= 1) {
+    for (int i = tid; i < EMB_BINS; i += 256) base[i] = 0;
+    __syncthreads();
+    for (int k = tid; k < n; k += 256) atomicAdd(&base[((uint32_t)tok[in ? in[k] : k] >> shift) & (EMB_BINS - 1)], 1);
+    __syncthreads();
+    if (tid < 64) {                                        // exclusive scan of the bins, eight per lane
+      int c[EMB_BINS / 64], s = 0;
+#pragma unroll
+      for (int i = 0; i < EMB_BINS / 64; i++) { c[i] = base[lane * (EMB_BINS / 64) + i]; s += c[i]; }
+      int incl = s;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) { const int v = __shfl_up(incl, o, 64); if (lane >= o) incl += v; }
+      int at = incl - s;
+#pragma unroll
+      for (int i = 0; i < EMB_BINS / 64; i++) { base[lane * (EMB_BINS / 64) + i] = at; at += c[i]; }
+    }
+    __syncthreads();
+    embed_scatter_tile(tok, in, 0, n, shift, base, wcnt, buf[b]);
+    in = buf[b];
+  }
+  for (int k = tid; k < n; k += 256) out[k] = in[k];
+}
+// piece blockIdx.x of the sorted positions, columns of blockIdx.y.  part[2 * piece]: the run that began in an earlier piece,
+// part[2 * piece + 1]: the run that begins here and goes on in the next piece (rows of d floats).
+template <typename T, int VN>
+__global__ __launch_bounds__(256) void embed_sum_kernel(const int32_t* __restrict__ tok, const int32_t* __restrict__ pos, int n, int d, int V,
+                                                        const T* __restrict__ dh, float* __restrict__ dE, float* __restrict__ part) {
+  __shared__ int32_t sp[EMB_PIECE], sv[EMB_PIECE + 2];     // sv[i + 1] = token of entry i; neighbours at both ends, -1 past the list
+  const int k0 = blockIdx.x * EMB_PIECE, cnt = min(EMB_PIECE, n - k0);
+  if (threadIdx.x < EMB_PIECE + 2) {
+    const int i = (int)threadIdx.x - 1, k = k0 + i;
+    const int p = k >= 0 && k < n ? pos[k] : -1;
+    if (i >= 0 && i < EMB_PIECE) sp[i] = p;
+    sv[threadIdx.x] = p >= 0 ? tok[p] : -1;
+  }
+  __syncthreads();
+  const int j = (blockIdx.y * 256 + threadIdx.x) * VN;
+  if (j >= d) return;
+  float acc[VN];
+#pragma unroll
+  for (int c = 0; c < VN; c++) acc[c] = 0.f;
+  auto put = [&](float* q) {
+    if constexpr (VN % 4 == 0) {
+#pragma unroll
+      for (int c = 0; c < VN; c += 4) *reinterpret_cast<f32x4*>(q + c) = (f32x4){acc[c], acc[c + 1], acc[c + 2], acc[c + 3]};
+    } else {
+#pragma unroll
+      for (int c = 0; c < VN; c++) q[c] = acc[c];
+    }
+  };
+  bool began_here = sv[0] != sv[1];
+  for (int i0 = 0; i0 < cnt; i0 += 8) {
+    float x[8][VN];
+#pragma unroll
+    for (int q = 0; q < 8; q++)                            // eight rows in flight
+      if (i0 + q < cnt) {
+        const T* row = dh + (int64_t)sp[i0 + q] * d + j;
+        if constexpr (VN == Vec<T>::N) load_vec<T>(row, x[q]); else x[q][0] = to_f<T>(row[0]);
+      }
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+      const int i = i0 + q;
+      if (i >= cnt) break;
+#pragma unroll
+      for (int c = 0; c < VN; c++) acc[c] += x[q][c];
+      const int v = sv[i + 1];
+      const bool run_ends = sv[i + 2] != v;
+      if (!run_ends && i + 1 < cnt) continue;
+      if (!began_here) put(part + (int64_t)(2 * blockIdx.x) * d + j);
+      else if (!run_ends) put(part + (int64_t)(2 * blockIdx.x + 1) * d + j);
+      else if ((uint32_t)v < (uint32_t)V) put(dE + (int64_t)v * d + j);
+      began_here = true;
+#pragma unroll
+      for (int c = 0; c < VN; c++) acc[c] = 0.f;
+    }
+  }
+}
+// the run that begins in piece blockIdx.x and goes on: its partial rows in order
+__global__ __launch_bounds__(256) void embed_join_kernel(const int32_t* __restrict__ tok, const int32_t* __restrict__ pos, int n, int d, int V,
+                                                         const float* __restrict__ part, float* __restrict__ dE) {
+  const int k0 = blockIdx.x * EMB_PIECE, last = k0 + EMB_PIECE - 1;
+  if (last + 1 >= n) return;
+  const int v = tok[pos[last]];
+  if (tok[pos[last + 1]] != v || (uint32_t)v >= (uint32_t)V) return;
+  if (tok[pos[k0]] == v && k0 > 0 && tok[pos[k0 - 1]] == v) return;                   // began in an earlier piece
+  int end = blockIdx.x + 1;                                                           // last piece that holds the token: bisection over the sorted list
+  { int lo = last + 1, hi = n - 1;                                                    // entry lo holds v; entries holding v are contiguous
+    const int t = v;
+    while (lo < hi) { const int mid = lo + (hi - lo + 1) / 2; if (tok[pos[mid]] == t) lo = mid; else hi = mid - 1; }
+    end = lo / EMB_PIECE; }
+  const int j = blockIdx.y * 256 + threadIdx.x;
+  if (j >= d) return;
+  float acc = part[(int64_t)(2 * blockIdx.x + 1) * d + j];
+  int q = blockIdx.x + 1;
+  for (; q + 8 <= end + 1; q += 8) {
+    float x[8];
+#pragma unroll
+    for (int i = 0; i < 8; i++) x[i] = part[(int64_t)(2 * (q + i)) * d + j];
+#pragma unroll
+    for (int i = 0; i < 8; i++) acc += x[i];
+  }
+  for (; q <= end; q++) acc += part[(int64_t)(2 * q) * d + j];
+  dE[(int64_t)v * d + j] = acc;
 }
 
+size_t embed_bwd_aux_bytes(int n, int d) {
+  const size_t cnt = ((size_t)EMB_BINS * cdiv(n, EMB_TILE) * 4 + 255) & ~(size_t)255;
+  return cnt + (size_t)2 * cdiv(n, EMB_PIECE) * d * 4;
+}
 int launch_embed_bwd(as_ctx* ctx, int mode, const int32_t* tok, int n, int d, int V, const void* dh,
-                     int32_t* scratch, float* dE, hipStream_t st) {
-  // scratch: 2n int32 (prev, is_last).  dE is zeroed first (rows of unused tokens stay zero).
+                     int32_t* scratch, void* aux, size_t aux_bytes, float* dE, hipStream_t st) {
+  // scratch: 2n int32 (the positions, sorted by one digit after the other); dE is zeroed first (rows of unused tokens stay zero)
   int rc = launch_fill_zero(ctx, dE, (size_t)V * d * sizeof(float), st);
   if (rc) return rc;
   if (n <= 0) return AS_OK;
-  int32_t* prev = scratch; int32_t* is_last = scratch + n;
-  token_rank_kernel<<<cdiv(n, 1024), 1024, 0, st>>>(tok, n, prev);
+  if (embed_bwd_aux_bytes(n, d) > aux_bytes) return as_fail(ctx, AS_ERR_WORKSPACE, "embedding gradient: scratch too small");
+  const int tiles = (int)cdiv(n, EMB_TILE), pieces = (int)cdiv(n, EMB_PIECE);
+  int32_t* cnt = (int32_t*)aux;
+  float* part = (float*)((char*)aux + (((size_t)EMB_BINS * tiles * 4 + 255) & ~(size_t)255));
+  const int32_t* in = nullptr; int32_t* out = scratch;
+  if (tiles == 1) {
+    embed_sort_tile_kernel<<<1, 256, 0, st>>>(tok, n, V, out);
+    AS_LAUNCH_CHECK(ctx);
+    in = out;
+  } else
+  for (int shift = 0; shift == 0 || (shift < 31 && (V - 1) >> shift); shift += EMB_BITS) {
+    embed_hist_kernel<<<tiles, 256, 0, st>>>(tok, in, n, shift, tiles, cnt);
+    embed_scan_kernel<<<1, 1024, 0, st>>>(cnt, EMB_BINS * tiles);
+    embed_scatter_kernel<<<tiles, 256, 0, st>>>(tok, in, n, shift, tiles, cnt, out);
+    AS_LAUNCH_CHECK(ctx);
+    in = out; out = out == scratch ? scratch + n : scratch;
+  }
+  DISPATCH_T(mode, {
+    constexpr int VN = Vec<T>::N;
+    if (vec_ok<T>(dh, d) && (uintptr_t)dE % 16 == 0 && d % 4 == 0)
+      embed_sum_kernel<T, VN><<<dim3(pieces, (unsigned)cdiv(d, 256 * VN)), 256, 0, st>>>(tok, in, n, d, V, (const T*)dh, dE, part);
+    else
+      embed_sum_kernel<T, 1><<<dim3(pieces, (unsigned)cdiv(d, 256)), 256, 0, st>>>(tok, in, n, d, V, (const T*)dh, dE, part); });
   AS_LAUNCH_CHECK(ctx);
-  fill_int_kernel<<<cdiv(n, 256), 256, 0, st>>>(is_last, n, 1);
-  AS_LAUNCH_CHECK(ctx);
-  mark_last_kernel<<<cdiv(n, 256), 256, 0, st>>>(prev, n, is_last);
-  AS_LAUNCH_CHECK(ctx);
-  DISPATCH_T(mode, (embed_bwd_kernel<T><<<n, 256, 0, st>>>(tok, prev, is_last, n, d, (const T*)dh, dE)));
+  embed_join_kernel<<<dim3(pieces, (unsigned)cdiv(d, 256)), 256, 0, st>>>(tok, in, n, d, V, part, dE);
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }

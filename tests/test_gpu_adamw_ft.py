@@ -94,3 +94,23 @@ def test_full_finetuning_step_matches_reference(bf16):
     rep = G.compare_step(sh, 3, trajs, 2, 320, bf16=bf16, loss_tol=2e-3 if bf16 else 1e-4, grad_tol=3e-2 if bf16 else 1e-4,
                          full=True)
     print("full FT %s: loss rel %.2e worst grad %.2e" % ("bf16" if bf16 else "fp32", rep["loss_rel"], rep["worst_grad"]))
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("n,d", [(5, 64), (32, 64), (33, 96), (2048, 64), (2049, 64), (4203, 72)])
+def test_embedding_gradient_piece_and_tile_edges(n, d, bf16):
+    """Token lists around the edges of the sum's pieces (32 positions) and of the sort's tiles (2048), one token holding
+    40 % of all positions (its run crosses many pieces), the first and last id of a vocabulary that takes two sort digits,
+    a width that is no multiple of a workgroup's columns.  The step's stated tolerances."""
+    import gpu_util as G
+    sh = synth.CONFIGS[1].replace(n_layers=1, n_q_heads=2, n_kv_heads=1, head_dim=32, d_model=d, ffn=64, vocab=1300,
+                                  lora_rank=0, lora_alpha=0.0, lora_targets=(), full_ft=True)
+    g = synth.rng(n, 31)
+    ids = np.where(g.random(n) < 0.4, 700, g.integers(0, sh.vocab, size=n)).astype(np.int32)
+    ids[0], ids[-1] = 0, sh.vocab - 1
+    trajs = [[(1, ids[b:b + 2]), (2, ids[b + 2:b + 500])] for b in range(0, n - 4, 500)]
+    if n > 4 and (n - 4) % 500:
+        trajs[-1][-1] = (2, ids[(n - 5) // 500 * 500 + 2:])
+    row_len = max(512, n)
+    rep = G.compare_step(sh, 4, trajs, 1, row_len, bf16=bf16, loss_tol=2e-3 if bf16 else 1e-4, grad_tol=3e-2 if bf16 else 1e-4, full=True)
+    assert rep["grads"]["embed"] <= (3e-2 if bf16 else 1e-4)
