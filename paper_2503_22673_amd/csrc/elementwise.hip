@@ -516,42 +516,47 @@ __global__ void transpose_kernel(int rows, int rows_pad, int cols, const T* __re
   }
 }
 
-// bf16, 16-byte accesses on both sides: a 64x64 tile is read as 8-element row chunks and written as
-// 8-element chunks of the output rows (gathered from an LDS tile column).  Needs cols, ldi, ldo, rows_pad
-// multiples of 8 (rows_pad of 64 in fact: whole output chunks) and 16-byte aligned bases.
+// bf16, 16-byte accesses on both sides, through registers: a lane reads eight rows of eight elements, turns the 8 x 8 block
+// with byte permutes (dword k of output row c is the pair of elements c of rows 2 k and 2 k + 1) and writes eight rows of
+// eight.  The lanes of a wave lie 8 x 8, so that every access of a wave is eight whole 128-byte lines, in and out; no LDS,
+// no barrier, eight loads in flight per lane.  Memory bound: one read and one write of the matrix.  Through an LDS tile
+// (eight 2-byte reads per output vector) the expert matrices of a sparse layer took 1693 us, 1407 us so (4.4 TB/s); the copies of a
+// 1B layer's weight gradients 1371 and 712 us (4.9 TB/s).
+// QS: the lane of an even output chunk takes source rows 0-3 and 8-11 of its 16, that of an odd one the others.
+// Needs cols, ldi, ldo and rows_pad multiples of 8 (QS: rows_pad of 16) and 16-byte aligned bases.
 template <bool QS>
-__global__ void transpose_vec_kernel(int rows, int rows_pad, int cols, const bf16_t* __restrict__ in, int64_t ldi,
-                                     bf16_t* __restrict__ out, int64_t ldo, const int* __restrict__ rows_dev, int row_off) {
-  __shared__ bf16_t tile[64][72];                          // [source row][source col], padded
+__global__ __launch_bounds__(256) void transpose_vec_kernel(int rows, int rows_pad, int cols, const bf16_t* __restrict__ in, int64_t ldi,
+                                                            bf16_t* __restrict__ out, int64_t ldo, const int* __restrict__ rows_dev, int row_off) {
+  typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
   const int live = rows_dev ? min(rows, *rows_dev - row_off) : rows;
-  const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-  for (int k = threadIdx.x; k < 512; k += 256) {           // 64 rows x 8 chunks
-    const int i = k >> 3, cc = (k & 7) * 8;
-    const int r = r0 + i, c = c0 + cc;
-    bf16x8 v;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int c0 = blockIdx.x * 64, r0 = (blockIdx.y * 4 + wave) * 64;
+  // reading, neighbouring lanes are neighbouring column blocks; the result is written in the same arrangement: lanes of equal
+  // column block write one output row each of eight, 16 bytes apart along it
+  const int cb = lane & 7, rbk = lane >> 3;
+  const int c = c0 + cb * 8, ro = r0 + rbk * 8;            // output rows c .. c + 7, positions ro .. ro + 7
+  if (c >= cols || ro >= rows_pad) return;
+  const int rs = QS ? r0 + (rbk >> 1) * 16 + (rbk & 1) * 4 : ro;                        // first source row; QS: rows rs .. + 3 and rs + 8 .. + 11
+  const bf16_t* src = in + (int64_t)rs * ldi + c;
+  u32x4 v[8];
 #pragma unroll
-    for (int e = 0; e < 8; e++) v[e] = (bf16_t)0.f;
-    if (r < live && c < cols) v = *reinterpret_cast<const bf16x8*>(in + (int64_t)r * ldi + c);   // cols % 8 == 0: whole chunks
-    *reinterpret_cast<bf16x8*>(&tile[i][cc]) = v;
+  for (int i = 0; i < 8; i++) {
+    const int o = QS ? (i & 3) + (i >> 2) * 8 : i;
+    v[i] = (u32x4){0u, 0u, 0u, 0u};
+    if (rs + o < live) v[i] = *reinterpret_cast<const u32x4*>(src + (int64_t)o * ldi);
   }
-  __syncthreads();
-  for (int k = threadIdx.x; k < 512; k += 256) {           // 64 output rows (source cols) x 8 chunks of 8 source rows
-    const int oc = k & 63, ch = k >> 6;                    // consecutive threads: consecutive output rows, same chunk
-    const int c = c0 + oc, rr = r0 + ch * 8;
-    if (c >= cols || rr >= rows_pad) continue;
-    bf16x8 v;
+  bf16_t* dst = out + (int64_t)c * ldo + ro;
 #pragma unroll
-    for (int e = 0; e < 8; e++) {
-      const int pos = ch * 8 + e;                          // output position inside the tile
-      const int src = QS ? ((pos & ~12) | ((pos & 4) << 1) | ((pos & 8) >> 1)) : pos;
-      v[e] = tile[src][oc];
-    }
-    *reinterpret_cast<bf16x8*>(out + (int64_t)c * ldo + rr) = v;
+  for (int q = 0; q < 8; q++) {
+    u32x4 w;
+#pragma unroll
+    for (int k = 0; k < 4; k++) w[k] = __builtin_amdgcn_perm(v[2 * k + 1][q >> 1], v[2 * k][q >> 1], (q & 1) ? 0x07060302u : 0x05040100u);
+    *reinterpret_cast<u32x4*>(dst + (int64_t)q * ldo) = w;
   }
 }
 
 static bool transpose_vec_ok(int mode, int rows_pad, int cols, const void* in, int64_t ldi, const void* out, int64_t ldo) {
-  return mode == AS_BF16 && rows_pad % 64 == 0 && cols % 8 == 0 && ldi % 8 == 0 && ldo % 8 == 0 &&
+  return mode == AS_BF16 && rows_pad % 8 == 0 && cols % 8 == 0 && ldi % 8 == 0 && ldo % 8 == 0 &&
          (uintptr_t)in % 16 == 0 && (uintptr_t)out % 16 == 0;
 }
 
@@ -561,7 +566,7 @@ int launch_transpose(as_ctx* ctx, int mode, int rows, int rows_pad, int cols, co
   dim3 grid(cdiv(cols, 64), cdiv(rows_pad, 64));
   prof_begin(ctx, st, AS_K_TRANSPOSE, 0.0);
   if (transpose_vec_ok(mode, rows_pad, cols, in, ldi, out, ldo))
-    transpose_vec_kernel<false><<<grid, 256, 0, st>>>(rows, rows_pad, cols, (const bf16_t*)in, ldi, (bf16_t*)out, ldo, rows_dev, row_off);
+    transpose_vec_kernel<false><<<dim3((unsigned)cdiv(cols, 64), (unsigned)cdiv(rows_pad, 256)), 256, 0, st>>>(rows, rows_pad, cols, (const bf16_t*)in, ldi, (bf16_t*)out, ldo, rows_dev, row_off);
   else
   DISPATCH_T(mode, (transpose_kernel<T, false><<<grid, 256, 0, st>>>(rows, rows_pad, cols, (const T*)in, ldi, (T*)out, ldo, rows_dev, row_off)));
   prof_end(ctx, st);
@@ -577,7 +582,7 @@ int launch_transpose_qs(as_ctx* ctx, int mode, int rows, int rows_pad, int cols,
   dim3 grid(cdiv(cols, 64), cdiv(rows_pad, 64));
   prof_begin(ctx, st, AS_K_TRANSPOSE, 0.0);
   if (transpose_vec_ok(mode, rows_pad, cols, in, ldi, out, ldo))
-    transpose_vec_kernel<true><<<grid, 256, 0, st>>>(rows, rows_pad, cols, (const bf16_t*)in, ldi, (bf16_t*)out, ldo, nullptr, 0);
+    transpose_vec_kernel<true><<<dim3((unsigned)cdiv(cols, 64), (unsigned)cdiv(rows_pad, 256)), 256, 0, st>>>(rows, rows_pad, cols, (const bf16_t*)in, ldi, (bf16_t*)out, ldo, nullptr, 0);
   else
   DISPATCH_T(mode, (transpose_kernel<T, true><<<grid, 256, 0, st>>>(rows, rows_pad, cols, (const T*)in, ldi, (T*)out, ldo, nullptr, 0)));
   prof_end(ctx, st);
