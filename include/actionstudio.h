@@ -165,7 +165,7 @@ int as_workspace_bytes(const as_ctx* ctx, int64_t max_rows, int64_t row_len, siz
  * and the sum of their algorithmic flops (2*M*N*K for GEMMs with a host-known
  * row count; 0 for classes where the host cannot know the work). */
 enum { AS_K_GEMM_MFMA_256 = 0,   /* bf16 MFMA GEMM, 256x256 tile                 */
-       AS_K_GEMM_MFMA_SKINNY,    /* bf16 MFMA GEMM, 256x64 / 64x256 / 128x128    */
+       AS_K_GEMM_MFMA_SKINNY,    /* bf16 MFMA GEMM, smaller tiles                 */
        AS_K_GEMM_FMA,            /* plain FMA GEMM                               */
        AS_K_GEMM_DEVROWS,        /* any GEMM whose row count lives on the device */
        AS_K_ATTN_FWD, AS_K_ATTN_BWD, AS_K_TRANSPOSE, AS_K_NORM, AS_K_SWIGLU, AS_K_ROPE, AS_K_CE,
@@ -335,9 +335,9 @@ int as_adamw_update(as_ctx* ctx, float* const* d_master, void* const* d_params_l
  * 128x128 / 128x64; 30 = direct-to-LDS 256x256 tiles (K in 64-wide steps, else 10);
  * 34 = hand-scheduled 256x256 kernel where it applies (else 30).
  * d_tail_scratch [device], may be NULL: AS_GEMM_TAIL_SCRATCH_BYTES of scratch, 256-byte aligned.  With it the
- * hand-scheduled kernel splits the contraction of the tiles of a last, at most half-full round of 256 workgroups
- * over two workgroups each (as as_train_step does inside its workspace): float partial sums per half, added in
- * order by a second small launch. */
+ * contraction may be split over several workgroups per tile (as as_train_step does inside its workspace): that of
+ * every tile where there are too few tiles for the chip, that of the last tiles of a large product where they would
+ * leave half of the chip idle.  Float partial sums per part, added in order by a second small launch. */
 #define AS_GEMM_TAIL_SCRATCH_BYTES (64u << 20)
 int as_op_gemm(as_ctx* ctx, int mode, int variant, int64_t M, int64_t N,
                const void* A1, int64_t lda1, const void* B1, int64_t ldb1, int64_t K1,

@@ -101,11 +101,11 @@ struct GemmParams {
   //    the sum of exp(value - maximum) go to epi_part[(row * (N / 128) + block) * 2 + {0, 1}];
   //  epi == GEMM_EPI_PROB:  C = w_row * (exp(value - epi_lse[row]) - [column == epi_lab[row]]), w_row = epi_w[row] when
   //    given, else 1 / *epi_cnt: the gradient of the masked loss with respect to the logits, straight from the accumulators.
-  // Last partial round of tiles (hand-scheduled kernel, plain rows): with tail_first >= 0 the tiles tail_first .. of the launch
-  // are each computed by TWO workgroups, one per half of the contraction, as float partials in tail_part
-  // [tile - tail_first][half][256 x 256]; a second small launch adds the halves in order and applies the epilogue.
-  // A launch of 3696 tiles on 256 CUs then ends after 14.5 rounds instead of 15.  Set by the launcher.
-  int tail_first; float* tail_part;
+  // Split tiles (hand-scheduled kernel, plain rows): with tail_first >= 0 the tiles tail_first .. of the launch are each
+  // computed by tail_parts workgroups, one per part of the contraction, as float partials in tail_part
+  // [tile - tail_first][part][256 x 256]; a second small launch adds the parts in order and applies the epilogue.
+  // Set by the launcher, which finds room for kGemmTailFloats floats at tail_part.
+  int tail_first, tail_parts; float* tail_part;
   int epi; const float* epi_lse; const int32_t* epi_lab; const float* epi_w; const int32_t* epi_cnt; float* epi_part;
 };
 enum { GEMM_EPI_NONE = 0, GEMM_EPI_STATS = 1, GEMM_EPI_PROB = 2 };

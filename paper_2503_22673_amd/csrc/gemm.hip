@@ -3,16 +3,14 @@
 // product (x A^T)(s B)^T, so the adapter costs one extra pass over r columns
 // inside the same accumulators instead of a second GEMM and an add.
 //
-// Two kernels:
-//  * gemm_fma_kernel   -- any type, any shape; 64x64 tile, fp32 FMAs.  The
-//    fp32 tier runs on it.
-//  * gemm_mfma_kernel  -- bf16 in, fp32 accumulate, v_mfma_f32_32x32x16_bf16.
-//    Tiles are staged global -> registers -> LDS (two LDS stages, one barrier
-//    per 64-wide K step), rows padded by 16 bytes so that the 16-byte fragment
-//    reads of 16 lanes hit 64 distinct banks.  Workgroup ids are first
-//    de-interleaved over the 8 XCDs (ids are dealt round-robin to XCDs, each
-//    with a private L2) and then walked in groups of 8 row-tiles so that the
-//    tiles resident on one XCD share A and B panels.
+// Kernels:
+//  * gemm_fma_kernel        -- any type, any shape; fp32 FMAs.  The fp32 tier runs on it.
+//  * gemm_mfma_rs_kernel    -- bf16, hand-scheduled 256x256 tiles: the large products.
+//  * gemm_mfma_ring_kernel  -- bf16, 128x128 and 64x64 tiles in a ring of LDS stages: few rows or narrow outputs.
+//  * gemm_mfma_dlds_kernel, gemm_mfma_kernel -- bf16: K that is no multiple of 64, rows counted on the device that the
+//    hand-scheduled kernel does not take, rows that are not 16-byte aligned.
+// In all of them workgroup ids are first de-interleaved over the 8 XCDs (ids are dealt round-robin to XCDs, each with a
+// private L2) and then walked in groups of row tiles, so that the tiles resident on one XCD share A and B panels.
 #include "common.h"
 
 // ------------------------------------------------------------------ helpers
@@ -414,6 +412,227 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_dlds_kernel(GemmParams
                         (row0 + BM <= M) && (col0 + BN <= p.N), rb);
 }
 
+// Ring of LDS stages, for products with too few 256 x 256 tiles for the chip and for narrow outputs.  Tiles of BM x BN, four
+// waves of (BM / 2) x (BN / 2), NST stages of one 64-wide K step each, filled straight from global memory (swizzled chunks, as
+// above); a step waits for its own stage only (`vmcnt` of the younger ones), passes one barrier and asks for the stage
+// NST - 1 ahead.  What bounds it: a CU's path into LDS carries about 40 bytes per clock, 800 clocks for the 32 KB of a
+// 128 x 128 step against 512 of matrix work, so a CU runs two workgroups (64 KB of LDS each) whose waits and barriers fall
+// at different times: 0.52 us per step and tile with two on a CU, 0.74 with one.  64 x 64 tiles read twice the operand
+// bytes per flop but give four times the workgroups: the adapters' 64-wide products, bound by reading A once, run
+// at 4.6 TB/s (15,500 rows, K 14336: 97 us; 128 x 64 register-staged tiles: 240).
+// The contraction may be split over `splitk` workgroups (grid.y): float partials, added in order by a second launch.
+// Results leave through LDS, 32 rows of a wave's block at a time, as whole 16-byte pieces; blocks are computed transposed, so
+// that a lane owns four consecutive columns of a row.
+// Needs: plain rows, K segments in 64-wide steps, 16-byte aligned rows of every operand (ring_ok).
+template <int N> __device__ __forceinline__ void wait_vm() {
+  // vmcnt(N), expcnt and lgkmcnt untouched: bits 3:0 and 15:14 vmcnt, 6:4 expcnt, 11:8 lgkmcnt
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
+}
+template <int L, int D> __device__ __forceinline__ void wait_stages(int younger) {   // all but the loads of the `younger` newest stages have landed
+  if constexpr (D <= 0) wait_vm<0>();
+  else { if (younger >= D) wait_vm<L * D>(); else wait_stages<L, D - 1>(younger); }
+}
+
+template <int BM, int BN, int NST>
+__global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(GemmParams p, int tiles_m, int tiles_n) {
+  constexpr int BK = 64, WM = 2, WN = 2, NW = WM * WN, TM = BM / WM / 32, TN = BN / WN / 32;
+  constexpr int LA = BM / 8 / NW, LB = BN / 8 / NW, L = LA + LB, ST_E = (BM + BN) * BK;
+  extern __shared__ __align__(16) unsigned char smem[];
+  bf16_t* sm = (bf16_t*)smem;
+  const int nblk = tiles_m * tiles_n, pid = blockIdx.x, z = blockIdx.y;
+  const int q8 = nblk / 8, rem = nblk % 8, xcd = pid % 8, loc = pid / 8;
+  const int logical = xcd * q8 + min(xcd, rem) + loc;
+  constexpr int GROUP = 8;
+  const int in_group = GROUP * tiles_n, grp = logical / in_group, first_m = grp * GROUP;
+  const int gsize = min(tiles_m - first_m, GROUP);
+  const int row0 = (first_m + (logical % in_group) % gsize) * BM, col0 = ((logical % in_group) / gsize) * BN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WN, wn = wave % WN;
+  // K steps of this split, over both segments one after the other
+  const int n0 = p.seg[0].K / BK, ntot = n0 + (p.nseg > 1 ? p.seg[1].K / BK : 0);
+  const int k_lo = (int)((int64_t)ntot * z / p.splitk), nt = (int)((int64_t)ntot * (z + 1) / p.splitk) - k_lo;
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; i++)
+#pragma unroll
+    for (int j = 0; j < TN; j++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
+  const int lrow = lane >> 3;
+  uint32_t offA[2][LA], offB[2][LB];                     // byte offsets of this lane's rows and chunk inside the panels
+#pragma unroll
+  for (int i = 0; i < LA; i++) {
+    const int rt = (wave * LA + i) * 8 + lrow, r = min(row0 + rt, p.M - 1) - row0, ch = ((lane & 7) ^ swz(rt)) * 8;
+    offA[0][i] = (uint32_t)((r * p.seg[0].lda + ch) * 2); offA[1][i] = (uint32_t)((r * p.seg[1].lda + ch) * 2);
+  }
+#pragma unroll
+  for (int i = 0; i < LB; i++) {
+    const int rt = (wave * LB + i) * 8 + lrow, r = min(col0 + rt, p.N - 1) - col0, ch = ((lane & 7) ^ swz(rt)) * 8;
+    offB[0][i] = (uint32_t)((r * p.seg[0].ldb + ch) * 2); offB[1][i] = (uint32_t)((r * p.seg[1].ldb + ch) * 2);
+  }
+  // which weight matrix this column tile belongs to (column groups are whole tiles wide)
+  const bf16_t* b0 = (const bf16_t*)p.seg[0].B; const bf16_t* b1 = (const bf16_t*)p.seg[1].B;
+  int colg = col0, a2 = 0;
+  if (p.ncg > 0) {
+    int g = 0;
+    while (g + 1 < p.ncg && col0 >= p.cg_end[g]) g++;
+    colg = col0 - (g ? p.cg_end[g - 1] : 0);
+    b0 = (const bf16_t*)p.cg_B1[g];
+    if (p.nseg > 1) { b1 = (const bf16_t*)p.cg_B2[g]; a2 = p.cg_a2[g]; }
+  }
+  const char* A0 = (const char*)p.seg[0].A + (int64_t)row0 * p.seg[0].lda * 2; const char* B0 = (const char*)(b0 + (int64_t)colg * p.seg[0].ldb);
+  const char* A1 = (const char*)((const bf16_t*)p.seg[1].A + a2 + (int64_t)row0 * p.seg[1].lda); const char* B1 = (const char*)(b1 + (int64_t)colg * p.seg[1].ldb);
+  auto fetch = [&](int it, int slot) {
+    const int ks = k_lo + it;
+    const bool first = ks < n0;
+    const char* a = first ? A0 + (int64_t)ks * (BK * 2) : A1 + (int64_t)(ks - n0) * (BK * 2);
+    const char* b = first ? B0 + (int64_t)ks * (BK * 2) : B1 + (int64_t)(ks - n0) * (BK * 2);
+    bf16_t* da = sm + slot * ST_E + wave * LA * 8 * BK; bf16_t* db = sm + slot * ST_E + BM * BK + wave * LB * 8 * BK;
+#pragma unroll
+    for (int i = 0; i < LA; i++)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(a + (first ? offA[0][i] : offA[1][i])),
+                                       (__attribute__((address_space(3))) void*)(da + i * 8 * BK), 16, 0, 0);
+#pragma unroll
+    for (int i = 0; i < LB; i++)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(b + (first ? offB[0][i] : offB[1][i])),
+                                       (__attribute__((address_space(3))) void*)(db + i * 8 * BK), 16, 0, 0);
+  };
+  const int x7 = swz(lane & 31), hh = lane >> 5, l31 = lane & 31;
+  int coff[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ks++) coff[ks] = ((2 * ks + hh) ^ x7) * 8;
+#pragma unroll
+  for (int s = 0; s < NST - 1; s++) if (s < nt) fetch(s, s);
+  int slot = 0;
+  for (int it = 0; it < nt; it++) {
+    wait_stages<L, NST - 2>(nt - 1 - it);
+    __builtin_amdgcn_s_barrier();                        // stage `it` is in LDS for every wave, and every wave has read stage it - 1
+    asm volatile("" ::: "memory");
+    const int nslot = slot == 0 ? NST - 1 : slot - 1;
+    if (it + NST - 1 < nt) fetch(it + NST - 1, nslot);
+    const bf16_t* a = sm + slot * ST_E + (wm * TM * 32 + l31) * BK; const bf16_t* b = sm + slot * ST_E + BM * BK + (wn * TN * 32 + l31) * BK;
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++) {
+      bf16x8 af[TM], bf[TN];
+#pragma unroll
+      for (int i = 0; i < TM; i++) af[i] = *reinterpret_cast<const bf16x8*>(a + i * 32 * BK + coff[ks]);
+#pragma unroll
+      for (int j = 0; j < TN; j++) bf[j] = *reinterpret_cast<const bf16x8*>(b + j * 32 * BK + coff[ks]);
+#pragma unroll
+      for (int i = 0; i < TM; i++)
+#pragma unroll
+        for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[j], af[i], acc[i][j], 0, 0, 0);   // transposed blocks
+    }
+    asm volatile("" ::: "memory");
+    slot = slot == NST - 1 ? 0 : slot + 1;
+  }
+  // epilogue through LDS, 32 rows of the wave's block at a time; a lane owns row l31 and columns 32 j + 8 b4 + 4 hh ..+3
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  constexpr int WC = TN * 32;                            // columns of the wave's block
+  const int rw = row0 + wm * TM * 32, cw = col0 + wn * WC;
+  if (p.splitk > 1 || p.c_f32) {
+    constexpr int PITCH = WC + 4;                        // floats
+    float* my = (float*)smem + wave * 32 * PITCH;
+    static_assert(NW * 32 * PITCH * 4 <= NST * ST_E * 2, "epilogue fits the stages");
+    constexpr int LPR = WC / 4, RPI = 64 / LPR;
+    float* C = p.splitk > 1 ? p.partial + (int64_t)z * p.M * p.N : (float*)p.C;
+    const int64_t ldc = p.splitk > 1 ? p.N : p.ldc;
+    const float alpha = p.splitk > 1 ? 1.f : p.alpha;
+#pragma unroll
+    for (int i = 0; i < TM; i++) {
+#pragma unroll
+      for (int j = 0; j < TN; j++)
+#pragma unroll
+        for (int b4 = 0; b4 < 4; b4++)
+          *reinterpret_cast<f32x4*>(my + l31 * PITCH + 32 * j + 8 * b4 + 4 * hh) =
+              (f32x4){alpha * acc[i][j][4 * b4], alpha * acc[i][j][4 * b4 + 1], alpha * acc[i][j][4 * b4 + 2], alpha * acc[i][j][4 * b4 + 3]};
+      __builtin_amdgcn_s_waitcnt(0xc07f);
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int r = 0; r < 32; r += RPI) {
+        const int rr = r + lane / LPR, cc = (lane % LPR) * 4, row = rw + i * 32 + rr, col = cw + cc;
+        if (row < p.M && col < p.N) {
+          f32x4 v = *reinterpret_cast<const f32x4*>(my + rr * PITCH + cc);
+          float* q = C + (int64_t)row * ldc + col;
+          if (p.splitk <= 1) {
+            if (p.R) { const bf16x4 x = *reinterpret_cast<const bf16x4*>((const bf16_t*)p.R + (int64_t)row * p.ldr + col);
+#pragma unroll
+              for (int k = 0; k < 4; k++) v[k] += (float)x[k]; }
+            if (p.accumulate) v += *reinterpret_cast<const f32x4*>(q);
+          }
+          *reinterpret_cast<f32x4*>(q) = v;
+        }
+      }
+      asm volatile("" ::: "memory");
+    }
+  } else {
+    constexpr int PITCH = WC + 8;                        // bf16
+    float alpha = p.alpha;
+    bf16_t* my = (bf16_t*)smem + wave * 32 * PITCH;
+    constexpr int LPR = WC / 8, RPI = 64 / LPR;
+#pragma unroll
+    for (int i = 0; i < TM; i++) {
+      if (p.R) {
+#pragma unroll
+        for (int r = 0; r < 32; r += RPI) {
+          const int rr = r + lane / LPR, cc = (lane % LPR) * 8, row = rw + i * 32 + rr, col = cw + cc;
+          if (row < p.M && col < p.N) *reinterpret_cast<u32x4*>(my + rr * PITCH + cc) = *reinterpret_cast<const u32x4*>((const bf16_t*)p.R + (int64_t)row * p.ldr + col);
+        }
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        asm volatile("" ::: "memory");
+      }
+#pragma unroll
+      for (int j = 0; j < TN; j++)
+#pragma unroll
+        for (int b4 = 0; b4 < 4; b4++) {
+          bf16x4* q = reinterpret_cast<bf16x4*>(my + l31 * PITCH + 32 * j + 8 * b4 + 4 * hh);
+          f32x4 v;
+#pragma unroll
+          for (int k = 0; k < 4; k++) v[k] = alpha * acc[i][j][4 * b4 + k];
+          if (p.R) { const bf16x4 x = *q;
+#pragma unroll
+            for (int k = 0; k < 4; k++) v[k] += (float)x[k]; }
+          bf16x4 w;
+#pragma unroll
+          for (int k = 0; k < 4; k++) w[k] = (bf16_t)v[k];
+          *q = w;
+        }
+      __builtin_amdgcn_s_waitcnt(0xc07f);
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int r = 0; r < 32; r += RPI) {
+        const int rr = r + lane / LPR, cc = (lane % LPR) * 8, row = rw + i * 32 + rr, col = cw + cc;
+        if (row < p.M && col < p.N) *reinterpret_cast<u32x4*>((bf16_t*)p.C + (int64_t)row * p.ldc + col) = *reinterpret_cast<const u32x4*>(my + rr * PITCH + cc);
+      }
+      asm volatile("" ::: "memory");
+    }
+  }
+}
+
+// sum of the splits in order, then the epilogue
+__global__ __launch_bounds__(256) void gemm_splitk_finish_kernel(GemmParams p) {
+  const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4, mn = (int64_t)p.M * p.N;
+  if (idx >= mn) return;
+  const int64_t row = idx / p.N; const int col = (int)(idx % p.N);
+  f32x4 v = *reinterpret_cast<const f32x4*>(p.partial + idx);
+  for (int s = 1; s < p.splitk; s++) v += *reinterpret_cast<const f32x4*>(p.partial + (int64_t)s * mn + idx);
+#pragma unroll
+  for (int k = 0; k < 4; k++) v[k] *= p.alpha;
+  if (p.R) { const bf16x4 x = *reinterpret_cast<const bf16x4*>((const bf16_t*)p.R + row * p.ldr + col);
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] += (float)x[k]; }
+  if (p.c_f32) {
+    f32x4* q = reinterpret_cast<f32x4*>((float*)p.C + row * p.ldc + col);
+    if (p.accumulate) v += *q;
+    *q = v;
+  } else {
+    bf16x4 w;
+#pragma unroll
+    for (int k = 0; k < 4; k++) w[k] = (bf16_t)v[k];
+    *reinterpret_cast<bf16x4*>((bf16_t*)p.C + row * p.ldc + col) = w;
+  }
+}
+
 // Epilogue for accumulator blocks that were computed transposed (B fragment as the first MFMA operand): a lane owns
 // row (lane % 32) of every 32 x 32 block and, per accumulator quad b4, the four consecutive columns
 // 8 b4 + 4 (lane / 32) .. + 3.  Whole tiles only, no split-K.  One row pointer per 32-row block and immediate column
@@ -580,6 +799,8 @@ __device__ __forceinline__ void gemm_epilogue_stats(const GemmParams& p, f32x16 
 // instruction by instruction (gen_gemm_rs_loop.py -> gemm_rs_loop.inc).  LDS layout and fragment order are those
 // of the direct-to-LDS kernel.  Covers whole 256 x 256 tiles, K segments that are multiples of 64, host-side
 // row counts, no split-K; the launcher sends everything else to the other kernels.
+// LIVE = 2: plain rows whose number is no multiple of 256; the last row tile is moved up to end with the last row and writes
+// only the rows that are its own.
 // LIVE = 1: the row count is a device-side value and / or the rows are those of one group (expert).  Tiles past the live
 // rows exit; a tile still computes 256 rows, moved up if need be so that they lie inside the `limit` rows the operands
 // are known to have (M for a plain row count, rows_cap for grouped rows), and writes the rows that are its own and live.
@@ -591,7 +812,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
   constexpr int BM = 256, BN = 256, BK = 64, TM = 4, TN = 4;
   extern __shared__ __align__(16) unsigned char smem[];
   int rb = 0, mlive = p.M;
-  if (LIVE) {
+  if (LIVE == 1) {
     if (p.grp_n > 0) {                                   // the live row tiles of all groups, one group after the other
       int total = 0;
       for (int e = 0; e < p.grp_n; e++) total += (p.grp_off[e + 1] - p.grp_off[e] + BM - 1) / BM;
@@ -603,8 +824,11 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
     }
   }
   int nblk = tiles_m * tiles_n, pid = blockIdx.x;
-  int khalf = -1;                                        // >= 0: this workgroup computes one half of the contraction of a tail tile
-  if (!LIVE && EPI == GEMM_EPI_NONE && p.tail_first >= 0 && pid >= p.tail_first) { khalf = (pid - p.tail_first) & 1; pid = p.tail_first + ((pid - p.tail_first) >> 1); }
+  int kpart = -1;                                        // >= 0: this workgroup computes one part of the contraction of a split tile
+  if (LIVE != 1 && EPI == GEMM_EPI_NONE && p.tail_first >= 0 && pid >= p.tail_first) {
+    const int i = pid - p.tail_first;
+    kpart = i % p.tail_parts; pid = p.tail_first + i / p.tail_parts;
+  }
   if (pid >= nblk) return;
   int q8 = nblk / 8, rem = nblk % 8, xcd = pid % 8, loc = pid / 8;
   int logical = xcd * q8 + min(xcd, rem) + loc;
@@ -616,7 +840,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
   int gsize = min(tiles_m - first_m, GROUP);
   int tile_m = first_m + (logical % in_group) % gsize, tile_n = (logical % in_group) / gsize;
   int b_group = 0;
-  if (LIVE && p.grp_n > 0) {                             // which group this row tile belongs to, and which of its tiles it is
+  if (LIVE == 1 && p.grp_n > 0) {                        // which group this row tile belongs to, and which of its tiles it is
     int e = 0, rows_e = p.grp_off[1] - p.grp_off[0], nt_e = (rows_e + BM - 1) / BM;
     while (tile_m >= nt_e && e + 1 < p.grp_n) {
       tile_m -= nt_e; e++;
@@ -625,7 +849,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
     rb = p.grp_off[e]; mlive = rows_e; b_group = e;
   }
   const int row_lo = rb + tile_m * BM, row_hi = rb + mlive;                  // LIVE: the rows this tile writes
-  const int row0 = LIVE ? min(row_lo, (p.grp_off ? p.rows_cap : p.M) - BM) : tile_m * BM, col0 = tile_n * BN;
+  const int row0 = LIVE ? min(row_lo, (LIVE == 1 && p.grp_off ? p.rows_cap : p.M) - BM) : tile_m * BM, col0 = tile_n * BN;
 
   const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, hh = lane >> 5, lrow = lane >> 3, lch = lane & 7;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -633,9 +857,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
   int nt0 = p.seg[0].K / BK, nt = nt0 + (p.nseg > 1 ? p.seg[1].K / BK : 0);
   const GemmSeg s0 = p.seg[0], s1 = p.nseg > 1 ? p.seg[1] : p.seg[0];
   int64_t k_skip = 0;                                    // elements of segment 0 this workgroup starts behind
-  if (khalf >= 0) {                                      // first half: steps [0, nt / 2) of segment 0; second half: the rest of it and segment 1
-    const int sp = nt / 2;                               // the launcher made sure that sp <= nt0
-    if (khalf == 0) { nt0 = sp; nt = sp; } else { k_skip = (int64_t)sp * BK; nt0 -= sp; nt -= sp; }
+  if (kpart >= 0) {                                      // steps [lo, hi) of the contraction; the launcher made sure that every part starts inside segment 0
+    const int lo = (int)((int64_t)nt * kpart / p.tail_parts), hi = (int)((int64_t)nt * (kpart + 1) / p.tail_parts);
+    k_skip = (int64_t)lo * BK; nt0 = min(nt0, hi) - lo; nt = hi - lo;
   }
 
   f32x16 acc[TM][TN];
@@ -689,9 +913,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
                  : GEMM_RS_LOOP_CLOBBERS);
   }
   // bf16 results with 16-byte rows leave through LDS (whole 256-byte row pieces per store), the rest row by row
-  if (!LIVE && EPI == GEMM_EPI_NONE && khalf >= 0) {     // raw float sums of this half into the tile's scratch
+  if (LIVE != 1 && EPI == GEMM_EPI_NONE && kpart >= 0) { // raw float sums of this part into the tile's scratch
     GemmParams q = p;
-    q.C = p.tail_part + ((int64_t)(pid - p.tail_first) * 2 + khalf) * (BM * BN); q.ldc = BN; q.c_f32 = 1; q.alpha = 1.f; q.R = nullptr; q.accumulate = 0;
+    q.C = p.tail_part + ((int64_t)(pid - p.tail_first) * p.tail_parts + kpart) * (BM * BN); q.ldc = BN; q.c_f32 = 1; q.alpha = 1.f; q.R = nullptr; q.accumulate = 0;
     gemm_epilogue_rows<TM, TN, false>(q, acc, wm * TM * 32 + l31, wn * TN * 32 + 4 * hh);
     return;
   }
@@ -714,9 +938,9 @@ static int launch_dlds_cfg(as_ctx* ctx, const GemmParams& p, int m_off, hipStrea
   return AS_OK;
 }
 
-// Second launch for the tiles of a split last round: sum of the two halves (first half first), then the usual epilogue.
-// Four workgroups per tile (64 rows each: a last round is at most 128 tiles), the same workgroup -> tile mapping as the
-// main kernel; a thread owns 4 consecutive columns.
+// Second launch for split tiles: sum of the parts in order, then the usual epilogue.
+// Four workgroups per tile (64 rows each), the same workgroup -> tile mapping as the main kernel; a thread owns 4
+// consecutive columns.
 __global__ __launch_bounds__(256) void gemm_tail_fixup_kernel(GemmParams p, int tiles_m, int tiles_n) {
   constexpr int BM = 256, BN = 256, GROUP = 4;
   const int tile = blockIdx.x >> 2, r_first = (blockIdx.x & 3) * (BM / 4);
@@ -727,14 +951,16 @@ __global__ __launch_bounds__(256) void gemm_tail_fixup_kernel(GemmParams p, int 
   const int in_group = GROUP * tiles_n, grp = logical / in_group, first_m = grp * GROUP;
   const int gsize = min(tiles_m - first_m, GROUP);
   const int tile_m = first_m + (logical % in_group) % gsize, tile_n = (logical % in_group) / gsize;
-  const float* h0 = p.tail_part + (int64_t)tile * 2 * (BM * BN); const float* h1 = h0 + BM * BN;
+  const float* h0 = p.tail_part + (int64_t)tile * p.tail_parts * (BM * BN);
   const int c = (threadIdx.x & 63) * 4;
+  const int row0 = p.rows_cap >= tiles_m * BM ? tile_m * BM : min(tile_m * BM, p.M - BM);   // as the main kernel: a ragged last tile was moved up
   for (int r = r_first + (threadIdx.x >> 6); r < r_first + BM / 4; r += 4) {
-    const f32x4 a = *reinterpret_cast<const f32x4*>(h0 + r * BN + c), b = *reinterpret_cast<const f32x4*>(h1 + r * BN + c);
-    const int64_t row = (int64_t)tile_m * BM + r; const int col = tile_n * BN + c;
-    f32x4 v;
+    const int64_t row = (int64_t)row0 + r; const int col = tile_n * BN + c;
+    if (row < (int64_t)tile_m * BM) continue;                                       // rows of the tile above
+    f32x4 v = *reinterpret_cast<const f32x4*>(h0 + r * BN + c);
+    for (int s = 1; s < p.tail_parts; s++) v += *reinterpret_cast<const f32x4*>(h0 + (int64_t)s * (BM * BN) + r * BN + c);
 #pragma unroll
-    for (int k = 0; k < 4; k++) v[k] = p.alpha * (a[k] + b[k]);
+    for (int k = 0; k < 4; k++) v[k] *= p.alpha;
     if (p.R) { const bf16x4_t x = *reinterpret_cast<const bf16x4_t*>((const bf16_t*)p.R + row * p.ldr + col);
 #pragma unroll
       for (int k = 0; k < 4; k++) v[k] += (float)x[k]; }
@@ -767,17 +993,37 @@ static bool rs_ok(const GemmParams& p) {
 }
 
 static bool rs_live(const GemmParams& p) { return p.m_dev || p.grp_off; }
+constexpr int kCus = 256;
+static int k_steps(const GemmParams& p) { return (int)(p.seg[0].K / 64) + (p.nseg > 1 ? (int)(p.seg[1].K / 64) : 0); }
+// The tiles of a last partial round are split in two when that round would leave at least half of the CUs idle, the launch
+// has full rounds before it and the contraction is long enough to be worth a second small launch: a launch of 3696 tiles
+// on 256 CUs then ends after 14.5 rounds instead of 15.
+static bool rs_tail_splits(const GemmParams& p, int T) {
+  const int rest = T % kCus, nt = k_steps(p);
+  return p.tail_part && p.epi == GEMM_EPI_NONE && T > kCus && rest > 0 && rest <= kCus / 2 && nt >= 32 && nt / 2 <= (int)(p.seg[0].K / 64);
+}
+// what the ring kernels need: plain rows, whole K steps, rows of C and R in 16-byte pieces, 32-bit offsets inside a tile
+static bool ring_ok(const GemmParams& p) {
+  if (rs_live(p) || p.splitk > 1 || p.epi != GEMM_EPI_NONE || p.N % 8 || p.ldc % 8 || ((uintptr_t)p.C % 16)) return false;
+  if (p.R && (p.ldr % 8 || ((uintptr_t)p.R % 16))) return false;
+  for (int s = 0; s < p.nseg; s++)
+    if (p.seg[s].K % 64 || p.seg[s].K < 64 || p.seg[s].lda > (1 << 22) || p.seg[s].ldb > (1 << 22)) return false;
+  return true;
+}
 static bool mfma_ok(const GemmParams& p);
 bool gemm_rs_applies(int mode, const GemmParams& p) { return mode == AS_BF16 && mfma_ok(p) && rs_ok(p); }
 
-static int launch_rs_cfg(as_ctx* ctx, const GemmParams& p_in, int m_off, hipStream_t st) {
+// parts > 1: the contraction of every tile is split over that many workgroups
+static int launch_rs_cfg(as_ctx* ctx, const GemmParams& p_in, int m_off, int parts, hipStream_t st) {
   GemmParams p = p_in;
   constexpr size_t smem = 131072 + 256 * 64;             // two stages of A and B tiles + a 64-byte line per lane (the staged epilogue: 4 x 128 rows of 272 bytes)
   AS_SET_SMEM(ctx, gemm_mfma_rs_kernel<0>, smem);
   AS_SET_SMEM(ctx, gemm_mfma_rs_kernel<1>, smem);
+  AS_SET_SMEM(ctx, gemm_mfma_rs_kernel<2>, smem);
   AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<1, GEMM_EPI_STATS>), smem);
   AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<1, GEMM_EPI_PROB>), smem);
   const int tn = p.N / 256;
+  p.tail_first = -1; p.tail_parts = 2;
   if (p.epi != GEMM_EPI_NONE && !p.m_dev) return as_fail(ctx, AS_ERR_SHAPE, "gemm: the head epilogues run over a device-side row count");
   if (rs_live(p)) {                                      // every row tile the live rows can reach; the kernel drops the rest
     const int tm = p.grp_n > 0 ? (int)cdiv(p.rows_cap, 256) + p.grp_n : (int)cdiv(p.M, 256);
@@ -785,20 +1031,36 @@ static int launch_rs_cfg(as_ctx* ctx, const GemmParams& p_in, int m_off, hipStre
     else if (p.epi == GEMM_EPI_PROB) gemm_mfma_rs_kernel<1, GEMM_EPI_PROB><<<dim3(tm * tn), 256, smem, st>>>(p, m_off, tm, tn);
     else gemm_mfma_rs_kernel<1><<<dim3(tm * tn), 256, smem, st>>>(p, m_off, tm, tn);
   } else {
-    // whole row tiles only: the ragged last one too when the operands have the rows, else the caller handles the rest
-    const int tm = p.rows_cap >= (int)cdiv(p.M, 256) * 256 ? (int)cdiv(p.M, 256) : p.M / 256;
-    // Split the contraction of the last partial round's tiles over two workgroups each when that round would leave at
-    // least half of the CUs idle, the launch has full rounds before it (short launches keep one summation order with the
-    // other kernels) and the contraction is long enough to be worth a second small launch.
-    const int T = tm * tn, cus = 256, full = T / cus * cus, rest = T - full;
-    const int nt0 = (int)(p.seg[0].K / 64), nt = nt0 + (p.nseg > 1 ? (int)(p.seg[1].K / 64) : 0);
-    p.tail_first = -1;
-    if (p.tail_part && p.epi == GEMM_EPI_NONE && full > 0 && rest > 0 && rest <= 128 && nt >= 32 && nt / 2 <= nt0) p.tail_first = full;
-    else p.tail_part = nullptr;
-    gemm_mfma_rs_kernel<0><<<dim3(p.tail_first >= 0 ? full + 2 * rest : T), 256, smem, st>>>(p, 0, tm, tn);
-    if (p.tail_first >= 0) { AS_LAUNCH_CHECK(ctx); gemm_tail_fixup_kernel<<<dim3(4 * rest), 256, 0, st>>>(p, tm, tn); }
+    // a ragged last row tile runs over rows past M when the operands have them, else it is moved up (instance 2)
+    const int tm = (int)cdiv(p.M, 256), T = tm * tn;
+    const bool whole = p.rows_cap >= tm * 256 || p.M % 256 == 0;
+    if (p.M % 256 == 0) p.rows_cap = p.M;
+    if (parts > 1) { p.tail_first = 0; p.tail_parts = parts; }
+    else if (rs_tail_splits(p, T)) p.tail_first = T / kCus * kCus;
+    const int split = p.tail_first >= 0 ? T - p.tail_first : 0;
+    const dim3 grid(T - split + split * p.tail_parts);
+    if (whole) gemm_mfma_rs_kernel<0><<<grid, 256, smem, st>>>(p, 0, tm, tn);
+    else gemm_mfma_rs_kernel<2><<<grid, 256, smem, st>>>(p, 0, tm, tn);
+    if (split) { AS_LAUNCH_CHECK(ctx); gemm_tail_fixup_kernel<<<dim3(4 * split), 256, 0, st>>>(p, tm, tn); }
   }
   AS_LAUNCH_CHECK(ctx);
+  return AS_OK;
+}
+
+template <int BM, int BN, int NST>
+static int launch_ring_cfg(as_ctx* ctx, const GemmParams& p_in, int splits, hipStream_t st) {
+  GemmParams p = p_in;
+  if (p.nseg < 2) p.seg[1] = p.seg[0];                   // the kernel forms the second segment's addresses in any case
+  p.splitk = splits; p.partial = p.tail_part;
+  constexpr size_t smem = (size_t)NST * (BM + BN) * 64 * sizeof(bf16_t);
+  AS_SET_SMEM(ctx, (gemm_mfma_ring_kernel<BM, BN, NST>), smem);
+  const int tm = (int)cdiv(p.M, BM), tn = (int)cdiv(p.N, BN);
+  gemm_mfma_ring_kernel<BM, BN, NST><<<dim3((unsigned)((int64_t)tm * tn), splits), 256, smem, st>>>(p, tm, tn);
+  AS_LAUNCH_CHECK(ctx);
+  if (splits > 1) {
+    gemm_splitk_finish_kernel<<<(unsigned)cdiv((int64_t)p.M * p.N, 1024), 256, 0, st>>>(p);
+    AS_LAUNCH_CHECK(ctx);
+  }
   return AS_OK;
 }
 
@@ -832,18 +1094,62 @@ static bool mfma_ok(const GemmParams& p) {
 
 // Tile configuration of the MFMA kernels.  Register-staged (any K that is a multiple of 8): 0 = 256x256 (8 waves,
 // 128x64 each), 1 = 256x64, 2 = 64x256, 3 = 128x128, 4 = 128x64.  20 = direct-to-LDS 256x256 with 8 waves (K in 64-wide steps);
-// 24 = the hand-scheduled register-staged 256x256 kernel with 4 waves.
-static int pick_cfg(const GemmParams& p) {
-  // narrow outputs (the adapters' rank-wide products) stream A once at HBM speed: 128 x 128 tiles measured 2-33 % ahead of
-  // 256 x 64 here (58,880 rows; N = 128: 121 against 181 us, where two 64-wide column tiles read A twice); up to 64
-  // columns a 128 x 64 tile loads half the B rows per step (a CU's load path carries A and B alike): 3-6 % ahead
-  if (p.N <= 64 && p.M > 128) return 4;
-  if (p.N <= 128 && p.M > 128) return 3;
-  if (p.M <= 128) return 2;
-  if ((int64_t)cdiv(p.M, 256) * cdiv(p.N, 256) * p.splitk < 128) return 3;
-  // The hand-scheduled register-staged kernel is ahead on every shape it covers (9-13 % on the shapes of an 8B model)
-  if (rs_ok(p)) return 24;
-  return 20;                                             // direct-to-LDS tiles when K allows, else staged (0)
+// 24 = the hand-scheduled register-staged 256x256 kernel with 4 waves; 25, 26 = ring of stages, 128x128 and 64x64 tiles.
+struct GemmPick { int cfg, parts; };                     // parts: workgroups that share a tile's contraction
+
+// Plain rows in whole K steps: the kernel and the split that the measured step times say is fastest (us; every pair of
+// 14 projections of the 1B and 8B shapes and 9 row counts from 300 to 16,000, and the adapters' widths 64 to 192 from 300 to
+// 59,000 rows: 2 % over the best of all candidates on average, 20 % at worst):
+//   256x256 hand-scheduled  1.04 per K step and 13.9 per round of 256 workgroups (start-up and epilogue of a tile)
+//   128x128 ring            1.05 per step with two workgroups on every CU, 0.74 with one, 1.3 per round
+//   64x64 ring              0.46 and 0.30, 3.6 per launch
+// and for a split the second launch, its partials written and read at about 4 TB/s, and its serial sum over the parts.
+// More than half a round of 256x256 tiles goes to the hand-scheduled kernel unsplit without looking further: from there on it
+// was at most 7 % behind (2560 x 8192 x 2112: 100 against 95) and mostly 15-40 % ahead.
+// Examples: 1531 x 4096 x 14400: 128x128 register-staged tiles 260, ring 226, 256x256 in two parts 173; 1003 x 2048 x 8256:
+// 136, 51 (four parts), 77; 512 x 2048 x 15744: 250, 53 (eight parts).
+static GemmPick pick_plain(const GemmParams& p) {
+  const int steps = k_steps(p);
+  const double mb = (double)p.M * p.N * 4e-6;
+  const bool can_split = p.tail_part != nullptr;
+  GemmPick best{24, 1}; double best_t = 1e30;
+  auto offer = [&](int cfg, int parts, double t) { if (t < best_t) { best_t = t; best = {cfg, parts}; } };
+  const int try_parts[] = {1, 2, 3, 4, 6, 8, 12};
+  const bool rs = rs_ok(p);
+  if (rs && cdiv(p.M, 256) * (p.N / 256) > kCus / 2) return best;
+  for (int parts : try_parts) {
+    if (parts > 1 && (!can_split || parts > steps / 2)) break;
+    const double per = (double)cdiv(steps, parts);
+    if (rs) {
+      const int64_t T = cdiv(p.M, 256) * (p.N / 256);      // at most half a round
+      if (parts == 1) offer(24, 1, per * 1.04 + 13.9);
+      else if (T * parts <= kCus && steps / parts >= 3 && (steps - cdiv(steps, parts)) < (int64_t)(p.seg[0].K / 64))
+        offer(24, parts, per * 1.04 + 13.9 + 4.1 + 2. * parts + 0.246 * (parts + 0.5) * mb);
+    }
+    if ((double)parts * p.M * p.N > (double)kGemmTailFloats && parts > 1) continue;
+    auto ring = [&](int cfg, int b, double launch, double one, double two, double round, double f0, double f_part, double f_mb) {
+      const int64_t T = cdiv(p.M, b) * cdiv(p.N, b) * parts, full = T / (2 * kCus), rest = T % (2 * kCus);
+      double t = launch + full * (per * two + round) + (rest ? per * (rest > kCus ? two : one) + round : 0.);
+      if (parts > 1) t += f0 + f_part * parts + f_mb * (parts + 0.5) * mb;
+      offer(cfg, parts, t);
+    };
+    ring(25, 128, 0., 0.74, 1.05, 1.3, 2.2, 0.54, 0.264);
+    ring(26, 64, 3.6, 0.30, 0.46, 0., 1.5, 0.28, 0.307);
+  }
+  return best;
+}
+
+static GemmPick pick_cfg(const GemmParams& p) {
+  if (ring_ok(p)) return pick_plain(p);
+  // narrow outputs stream A once: 128 x 128 tiles measured 2-33 % ahead of 256 x 64 here (58,880 rows; N = 128: 121 against
+  // 181 us, where two 64-wide column tiles read A twice); up to 64 columns a 128 x 64 tile loads half the B rows per step
+  if (p.N <= 64 && p.M > 128) return {4, 1};
+  if (p.N <= 128 && p.M > 128) return {3, 1};
+  if (p.M <= 128) return {2, 1};
+  if ((int64_t)cdiv(p.M, 256) * cdiv(p.N, 256) * p.splitk < 128) return {3, 1};
+  // The hand-scheduled register-staged kernel is ahead on every large shape it covers (9-13 % on the shapes of an 8B model)
+  if (rs_ok(p)) return {24, 1};
+  return {20, 1};                                        // direct-to-LDS tiles when K allows, else staged (0)
 }
 
 // m_dev semantics: the live row count is *m_dev - m_off (clamped to [0, M]).
@@ -858,7 +1164,7 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
   if (p.grp_off && p.splitk > 1) return as_fail(ctx, AS_ERR_SHAPE, "gemm: grouped rows and split-K do not combine");
   if (p.grp_n > 0) {
     if (!p.grp_off || p.nseg != 1 || p.m_dev || m_off) return as_fail(ctx, AS_ERR_SHAPE, "gemm: all groups in one launch need a group table and one K segment");
-    const int c0 = variant >= 10 ? variant - 10 : pick_cfg(p);
+    const int c0 = variant >= 10 ? variant - 10 : pick_cfg(p).cfg;
     if (!(mode == AS_BF16 && variant != 1 && mfma_ok(p) && c0 == 24 && rs_ok(p))) {       // one launch per group
       const size_t esz = mode == AS_BF16 ? 2 : 4;
       for (int e = 0; e < p.grp_n; e++) {
@@ -877,9 +1183,11 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
   }
   if (p.ncg > 0) {
     if (p.ncg > 3 || p.grp_off || p.m_dev || p.splitk > 1 || p.cg_end[p.ncg - 1] != p.N) return as_fail(ctx, AS_ERR_SHAPE, "gemm: column groups need plain rows and ends that add up to N");
-    bool fused = mode == AS_BF16 && variant != 1 && mfma_ok(p) && (variant >= 10 ? variant - 10 : pick_cfg(p)) == 24 && rs_ok(p) &&
-                 p.rows_cap >= (int)cdiv(p.M, 256) * 256;      // the hand-scheduled kernel over every row tile
-    for (int g = 0; g < p.ncg && fused; g++) fused = p.cg_end[g] % 256 == 0 && !((uintptr_t)p.cg_B1[g] % 16) && (p.nseg < 2 || !((uintptr_t)p.cg_B2[g] % 16));
+    // the hand-scheduled kernel and the ring kernels take all groups at once when every group is whole tiles wide
+    const int c = variant >= 10 ? variant - 10 : mode == AS_BF16 && variant != 1 ? pick_cfg(p).cfg : -1;
+    const int width = c == 24 ? 256 : c == 25 ? 128 : 64;
+    bool fused = mode == AS_BF16 && variant != 1 && mfma_ok(p) && ((c == 24 && rs_ok(p)) || c == 25 || c == 26);
+    for (int g = 0; g < p.ncg && fused; g++) fused = p.cg_end[g] % width == 0 && !((uintptr_t)p.cg_B1[g] % 16) && (p.nseg < 2 || !((uintptr_t)p.cg_B2[g] % 16));
     if (!fused) {                                        // one launch per group
       const size_t esz = mode == AS_BF16 ? 2 : 4;
       for (int g = 0, c0 = 0; g < p.ncg; c0 = p.cg_end[g], g++) {
@@ -899,10 +1207,11 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
   if (variant >= 2 && !use_mfma) return as_fail(ctx, AS_ERR_SHAPE, "gemm: MFMA kernel needs bf16 and 8-element alignment");
   int rc = AS_OK;
   double ksum = 0; for (int s = 0; s < p.nseg; s++) ksum += p.seg[s].K;
-  int cfg = variant >= 10 ? variant - 10 : pick_cfg(p);
+  const GemmPick pick = variant >= 10 ? GemmPick{variant - 10, 1} : use_mfma ? pick_cfg(p) : GemmPick{0, 1};
+  int cfg = pick.cfg;
   if (p.epi != GEMM_EPI_NONE) cfg = 24;                    // only the hand-scheduled kernel has those epilogues (checked above)
   if (cfg >= 20) for (int s = 0; s < p.nseg; s++) if (p.seg[s].K % 64) cfg = 0;     // direct-to-LDS tiles need whole 64-wide K steps
-  const bool big = use_mfma && (cfg == 0 || cfg >= 20);
+  const bool big = use_mfma && (cfg == 0 || cfg == 20 || cfg == 24);
   const bool rs = use_mfma && cfg == 24 && rs_ok(p) && !rs_live(p) && !m_off;     // live-row launches keep their own timing classes
   prof_begin(ctx, st, rs ? AS_K_GEMM_RS : p.grp_off ? AS_K_GEMM_GROUPED : p.m_dev ? AS_K_GEMM_DEVROWS : !use_mfma ? AS_K_GEMM_FMA : big ? AS_K_GEMM_MFMA_256 : AS_K_GEMM_MFMA_SKINNY,
              p.grp_off ? 2.0 * p.grp_rows * p.N * ksum : p.m_dev ? 0.0 : 2.0 * p.M * p.N * ksum);
@@ -913,20 +1222,12 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
       case 3: rc = launch_mfma_cfg<128, 128, 2, 2>(ctx, p, m_off, st); break;
       case 4: rc = launch_mfma_cfg<128, 64, 2, 2>(ctx, p, m_off, st); break;
       case 20: rc = launch_dlds_cfg<256, 256, 2, 4>(ctx, p, m_off, st); break;
-      case 24: {                                           // whole row tiles by the register-staged kernel, the ragged rest by the default one
+      case 24: {
         if (!rs_ok(p) || (m_off && !p.m_dev)) { rc = launch_dlds_cfg<256, 256, 2, 4>(ctx, p, m_off, st); break; }
-        rc = launch_rs_cfg(ctx, p, m_off, st);
-        if (rs_live(p)) break;                             // covers its ragged tiles itself
-        const int done = p.rows_cap >= (int)cdiv(p.M, 256) * 256 ? p.M : p.M / 256 * 256;
-        if (!rc && done < p.M) {
-          GemmParams t = p;
-          t.M = p.M - done;
-          for (int s = 0; s < t.nseg; s++) t.seg[s].A = (const bf16_t*)t.seg[s].A + (int64_t)done * t.seg[s].lda;
-          t.C = t.c_f32 ? (void*)((float*)t.C + (int64_t)done * t.ldc) : (void*)((bf16_t*)t.C + (int64_t)done * t.ldc);
-          if (t.R) t.R = (const bf16_t*)t.R + (int64_t)done * t.ldr;
-          rc = launch_dlds_cfg<256, 256, 2, 4>(ctx, t, 0, st);
-        }
+        rc = launch_rs_cfg(ctx, p, m_off, pick.parts, st);
         break; }
+      case 25: rc = launch_ring_cfg<128, 128, 2>(ctx, p, pick.parts, st); break;
+      case 26: rc = launch_ring_cfg<64, 64, 4>(ctx, p, pick.parts, st); break;
       default: rc = launch_mfma_cfg<256, 256, 2, 4>(ctx, p, m_off, st); break;
     }
   } else {

@@ -110,6 +110,37 @@ def test_hand_scheduled_gemm_split_last_round(out_f32, with_residual):
     assert np.abs(got - G.to_np(plain)).max() <= (1e-4 if out_f32 else 2.0 ** -7) * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("out_f32,with_residual,scratch", [(False, True, True), (True, False, True), (False, False, False), (True, True, False)])
+@pytest.mark.parametrize("M,N,K1,K2", [(1, 8, 64, 0), (63, 64, 192, 0), (65, 72, 128, 64), (129, 520, 576, 128), (1003, 64, 4096, 0), (1003, 512, 2048, 64),
+                                       (300, 4096, 4096, 64), (1003, 2048, 2048, 64), (257, 4096, 8192, 64), (1531, 4096, 14336, 64), (512, 2048, 15744, 0),
+                                       (4353, 4096, 2048, 64), (2560, 2048, 8192, 64)])
+def test_gemm_kernel_and_split_choice(M, N, K1, K2, out_f32, with_residual, scratch):
+    """The kernels the size rule picks (64x64 and 128x128 rings, 256x256; whole and split contractions; ragged last tiles, a
+    ragged last tile in a split last round) at the edges of their tiles, into a result whose rows are longer than N and which
+    has rows behind M: every entry against float64, nothing written outside.  Operands N(0, 1): a float sum of K exact
+    products, in any order, and one rounding to bf16."""
+    import ctypes as C
+    B, G, ctx, _ = _env()
+    gen = torch.Generator(device="cuda"); gen.manual_seed(M + N)
+    new = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    A1, B1 = new(M, K1), new(N, K1)
+    A2, B2 = (new(M, K2), new(N, K2)) if K2 else (None, None)
+    R = new(M, N) if with_residual else None
+    out = torch.full((M + 3, N + 8), 7.0, dtype=torch.float32 if out_f32 else torch.bfloat16, device="cuda")
+    ws = torch.empty(B.GEMM_TAIL_SCRATCH_BYTES, dtype=torch.uint8, device="cuda") if scratch else None
+    ctx.check(B.lib.as_op_gemm(ctx.handle, B.AS_BF16, 0, M, N, B._ptr(A1), K1, B._ptr(B1), K1, K1, B._ptr(A2), K2, B._ptr(B2), K2, K2, C.c_float(0.5),
+                               B._ptr(R), N, B._ptr(out), N + 8, int(out_f32), B._ptr(ws), B.GEMM_TAIL_SCRATCH_BYTES if scratch else 0, B._stream()))
+    torch.cuda.synchronize()
+    ref = A1.double() @ B1.double().T
+    if K2:
+        ref += A2.double() @ B2.double().T
+    ref = 0.5 * ref + (R.double() if with_residual else 0.0)
+    err, K = (out[:M, :N].double() - ref).abs(), K1 + K2
+    bound = 1e-5 * K ** 0.5 if out_f32 else 2.0 ** -8 * ref.abs() + 1e-4 * K ** 0.5
+    assert bool((err <= bound).all()), float((err / bound).max())
+    assert bool((out[M:] == 7.0).all()) and bool((out[:, N:] == 7.0).all())
+
+
 @pytest.mark.parametrize("out_f32", [False, True])
 @pytest.mark.parametrize("variant", [0, 30, 34])
 @pytest.mark.parametrize("row_off,live", [(0, 700), (128, 896), (0, 0), (256, 1)])
