@@ -401,7 +401,7 @@ int as_op_attention_bwd(as_ctx* ctx, int mode, int variant, int64_t n, const int
                         void* t_scratch, void* stream);
 
 /* The vocabulary head with the masked cross-entropy (Section 3.2.1: the loss covers assistant tokens only), as the
- * step runs it over the compacted target rows:
+ * step runs it over the compacted target rows (the step, which has scratch for it, may also split the last product's contraction):
  *   loss_rows[r] = logsumexp_v(hf[r] . head[v]) - hf[r] . head[labels[r]],
  *   dhf[r]       = factor_r * (softmax_v(hf[r] . head[v]) - onehot(labels[r])) head,   factor_r = row_w[r], or 1 / *d_count
  * for the rows r < *d_count (a device-side count, at most n_rows); other rows are neither read into a result nor written.

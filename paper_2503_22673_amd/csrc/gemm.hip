@@ -805,6 +805,12 @@ __device__ __forceinline__ void gemm_epilogue_stats(const GemmParams& p, f32x16 
 // rows exit; a tile still computes 256 rows, moved up if need be so that they lie inside the `limit` rows the operands
 // are known to have (M for a plain row count, rows_cap for grouped rows), and writes the rows that are its own and live.
 #include "gemm_rs_loop.inc"
+// Rows counted on the device, with scratch for partial sums: the contraction of every tile is split over as many workgroups as
+// fit one round, up to kLiveParts.  Host code cannot know the count, so both launches work the split out from it.
+constexpr int kLiveParts = 16;
+__device__ __forceinline__ int live_parts(const GemmParams& p, int tiles) {
+  return p.tail_part && tiles > 0 && tiles <= 128 ? min(kLiveParts, 256 / tiles) : 1;
+}
 // EPI: the epilogue is a compile-time choice (GEMM_EPI_*), so that the head's epilogues, which need registers of their own,
 // cost the projection GEMMs nothing.
 template <int LIVE, int EPI = GEMM_EPI_NONE>
@@ -824,10 +830,14 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
     }
   }
   int nblk = tiles_m * tiles_n, pid = blockIdx.x;
-  int kpart = -1;                                        // >= 0: this workgroup computes one part of the contraction of a split tile
+  int kpart = -1, parts = p.tail_parts;                  // >= 0: this workgroup computes one part of the contraction of a split tile
+  if (LIVE == 1 && EPI == GEMM_EPI_NONE && p.tail_part) {
+    parts = live_parts(p, nblk);
+    if (parts > 1) { kpart = pid % parts; pid /= parts; }
+  }
   if (LIVE != 1 && EPI == GEMM_EPI_NONE && p.tail_first >= 0 && pid >= p.tail_first) {
     const int i = pid - p.tail_first;
-    kpart = i % p.tail_parts; pid = p.tail_first + i / p.tail_parts;
+    kpart = i % parts; pid = p.tail_first + i / parts;
   }
   if (pid >= nblk) return;
   int q8 = nblk / 8, rem = nblk % 8, xcd = pid % 8, loc = pid / 8;
@@ -858,7 +868,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
   const GemmSeg s0 = p.seg[0], s1 = p.nseg > 1 ? p.seg[1] : p.seg[0];
   int64_t k_skip = 0;                                    // elements of segment 0 this workgroup starts behind
   if (kpart >= 0) {                                      // steps [lo, hi) of the contraction; the launcher made sure that every part starts inside segment 0
-    const int lo = (int)((int64_t)nt * kpart / p.tail_parts), hi = (int)((int64_t)nt * (kpart + 1) / p.tail_parts);
+    const int lo = (int)((int64_t)nt * kpart / parts), hi = (int)((int64_t)nt * (kpart + 1) / parts);
     k_skip = (int64_t)lo * BK; nt0 = min(nt0, hi) - lo; nt = hi - lo;
   }
 
@@ -913,9 +923,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
                  : GEMM_RS_LOOP_CLOBBERS);
   }
   // bf16 results with 16-byte rows leave through LDS (whole 256-byte row pieces per store), the rest row by row
-  if (LIVE != 1 && EPI == GEMM_EPI_NONE && kpart >= 0) { // raw float sums of this part into the tile's scratch
+  if (EPI == GEMM_EPI_NONE && kpart >= 0) {              // raw float sums of this part into the tile's scratch
     GemmParams q = p;
-    q.C = p.tail_part + ((int64_t)(pid - p.tail_first) * p.tail_parts + kpart) * (BM * BN); q.ldc = BN; q.c_f32 = 1; q.alpha = 1.f; q.R = nullptr; q.accumulate = 0;
+    q.C = p.tail_part + ((int64_t)(pid - (LIVE == 1 ? 0 : p.tail_first)) * parts + kpart) * (BM * BN); q.ldc = BN; q.c_f32 = 1; q.alpha = 1.f; q.R = nullptr; q.accumulate = 0;
     gemm_epilogue_rows<TM, TN, false>(q, acc, wm * TM * 32 + l31, wn * TN * 32 + 4 * hh);
     return;
   }
@@ -939,42 +949,61 @@ static int launch_dlds_cfg(as_ctx* ctx, const GemmParams& p, int m_off, hipStrea
 }
 
 // Second launch for split tiles: sum of the parts in order, then the usual epilogue.
-// Four workgroups per tile (64 rows each), the same workgroup -> tile mapping as the main kernel; a thread owns 4
+// Sixteen workgroups per tile (16 rows each), the same workgroup -> tile mapping as the main kernel; a thread owns 4
 // consecutive columns.
-__global__ __launch_bounds__(256) void gemm_tail_fixup_kernel(GemmParams p, int tiles_m, int tiles_n) {
-  constexpr int BM = 256, BN = 256, GROUP = 4;
-  const int tile = blockIdx.x >> 2, r_first = (blockIdx.x & 3) * (BM / 4);
-  const int nblk = tiles_m * tiles_n, pid = p.tail_first + tile;
+__global__ __launch_bounds__(256) void gemm_tail_fixup_kernel(GemmParams p, int m_off, int tiles_m, int tiles_n) {
+  constexpr int BM = 256, BN = 256, GROUP = 4, WPT = 16;
+  const int tile = blockIdx.x / WPT, r_first = (blockIdx.x % WPT) * (BM / WPT);
+  int live = p.M, parts = p.tail_parts, first = p.tail_first;
+  if (p.m_dev) {
+    int rb, mmax;
+    live = gemm_rows(p, m_off, rb, mmax);
+    tiles_m = min(tiles_m, (max(live, 0) + BM - 1) / BM);
+    parts = live_parts(p, tiles_m * tiles_n); first = 0;
+    if (parts <= 1) return;
+  }
+  const int nblk = tiles_m * tiles_n, pid = first + tile;
   if (pid >= nblk) return;
   const int q8 = nblk / 8, rem = nblk % 8, xcd = pid % 8, loc = pid / 8;
   const int logical = xcd * q8 + min(xcd, rem) + loc;
   const int in_group = GROUP * tiles_n, grp = logical / in_group, first_m = grp * GROUP;
   const int gsize = min(tiles_m - first_m, GROUP);
   const int tile_m = first_m + (logical % in_group) % gsize, tile_n = (logical % in_group) / gsize;
-  const float* h0 = p.tail_part + (int64_t)tile * p.tail_parts * (BM * BN);
+  const float* h0 = p.tail_part + (int64_t)tile * parts * (BM * BN);
   const int c = (threadIdx.x & 63) * 4;
-  const int row0 = p.rows_cap >= tiles_m * BM ? tile_m * BM : min(tile_m * BM, p.M - BM);   // as the main kernel: a ragged last tile was moved up
-  for (int r = r_first + (threadIdx.x >> 6); r < r_first + BM / 4; r += 4) {
-    const int64_t row = (int64_t)row0 + r; const int col = tile_n * BN + c;
-    if (row < (int64_t)tile_m * BM) continue;                                       // rows of the tile above
-    f32x4 v = *reinterpret_cast<const f32x4*>(h0 + r * BN + c);
-    for (int s = 1; s < p.tail_parts; s++) v += *reinterpret_cast<const f32x4*>(h0 + (int64_t)s * (BM * BN) + r * BN + c);
+  // as the main kernel: a ragged last tile was moved up; it writes its own rows (and rows past M where the operands have them)
+  const bool spare = !p.m_dev && p.rows_cap >= tiles_m * BM;
+  const int row0 = spare ? tile_m * BM : min(tile_m * BM, p.M - BM), row_hi = spare ? tiles_m * BM : live;
+  constexpr int RPT = BM / WPT / 4;                      // rows of a thread, four apart
+  f32x4 sum[RPT];
+  const float* h = h0 + (r_first + (threadIdx.x >> 6)) * BN + c;
 #pragma unroll
-    for (int k = 0; k < 4; k++) v[k] *= p.alpha;
-    if (p.R) { const bf16x4_t x = *reinterpret_cast<const bf16x4_t*>((const bf16_t*)p.R + row * p.ldr + col);
+  for (int i = 0; i < RPT; i++) sum[i] = *reinterpret_cast<const f32x4*>(h + i * 4 * BN);
+  for (int s = 1; s < parts; s++) {
+    h += BM * BN;
 #pragma unroll
-      for (int k = 0; k < 4; k++) v[k] += (float)x[k]; }
-    if (p.c_f32) {
-      f32x4* q = reinterpret_cast<f32x4*>((float*)p.C + row * p.ldc + col);
-      if (p.accumulate) { const f32x4 o = *q;
+    for (int i = 0; i < RPT; i++) sum[i] += *reinterpret_cast<const f32x4*>(h + i * 4 * BN);
+  }
 #pragma unroll
-        for (int k = 0; k < 4; k++) v[k] += o[k]; }
-      *q = v;
-    } else {
-      bf16x4_t w;
+  for (int i = 0; i < RPT; i++) {
+    const int64_t row = (int64_t)row0 + r_first + (threadIdx.x >> 6) + 4 * i; const int col = tile_n * BN + c;
+    if (row >= (int64_t)tile_m * BM && row < row_hi) {
+      f32x4 v = sum[i];
 #pragma unroll
-      for (int k = 0; k < 4; k++) w[k] = (bf16_t)v[k];
-      *reinterpret_cast<bf16x4_t*>((bf16_t*)p.C + row * p.ldc + col) = w;
+      for (int k = 0; k < 4; k++) v[k] *= p.alpha;
+      if (p.R) { const bf16x4_t x = *reinterpret_cast<const bf16x4_t*>((const bf16_t*)p.R + row * p.ldr + col);
+#pragma unroll
+        for (int k = 0; k < 4; k++) v[k] += (float)x[k]; }
+      if (p.c_f32) {
+        f32x4* q = reinterpret_cast<f32x4*>((float*)p.C + row * p.ldc + col);
+        if (p.accumulate) v += *q;
+        *q = v;
+      } else {
+        bf16x4_t w;
+#pragma unroll
+        for (int k = 0; k < 4; k++) w[k] = (bf16_t)v[k];
+        *reinterpret_cast<bf16x4_t*>((bf16_t*)p.C + row * p.ldc + col) = w;
+      }
     }
   }
 }
@@ -1001,6 +1030,10 @@ static int k_steps(const GemmParams& p) { return (int)(p.seg[0].K / 64) + (p.nse
 static bool rs_tail_splits(const GemmParams& p, int T) {
   const int rest = T % kCus, nt = k_steps(p);
   return p.tail_part && p.epi == GEMM_EPI_NONE && T > kCus && rest > 0 && rest <= kCus / 2 && nt >= 32 && nt / 2 <= (int)(p.seg[0].K / 64);
+}
+// rows counted on the device whose contraction is long enough (sixteen parts of eight steps) to be split by the live count
+static bool live_split_ok(const GemmParams& p) {
+  return p.m_dev && !p.grp_off && p.tail_part && p.nseg == 1 && p.epi == GEMM_EPI_NONE && k_steps(p) >= 8 * kLiveParts;
 }
 // what the ring kernels need: plain rows, whole K steps, rows of C and R in 16-byte pieces, 32-bit offsets inside a tile
 static bool ring_ok(const GemmParams& p) {
@@ -1029,7 +1062,11 @@ static int launch_rs_cfg(as_ctx* ctx, const GemmParams& p_in, int m_off, int par
     const int tm = p.grp_n > 0 ? (int)cdiv(p.rows_cap, 256) + p.grp_n : (int)cdiv(p.M, 256);
     if (p.epi == GEMM_EPI_STATS) gemm_mfma_rs_kernel<1, GEMM_EPI_STATS><<<dim3(tm * tn), 256, smem, st>>>(p, m_off, tm, tn);
     else if (p.epi == GEMM_EPI_PROB) gemm_mfma_rs_kernel<1, GEMM_EPI_PROB><<<dim3(tm * tn), 256, smem, st>>>(p, m_off, tm, tn);
-    else gemm_mfma_rs_kernel<1><<<dim3(tm * tn), 256, smem, st>>>(p, m_off, tm, tn);
+    else {
+      if (!live_split_ok(p)) p.tail_part = nullptr;
+      gemm_mfma_rs_kernel<1><<<dim3(p.tail_part ? std::max(tm * tn, kCus) : tm * tn), 256, smem, st>>>(p, m_off, tm, tn);
+      if (p.tail_part) { AS_LAUNCH_CHECK(ctx); gemm_tail_fixup_kernel<<<dim3(16 * std::min(tm * tn, 128)), 256, 0, st>>>(p, m_off, tm, tn); }
+    }
   } else {
     // a ragged last row tile runs over rows past M when the operands have them, else it is moved up (instance 2)
     const int tm = (int)cdiv(p.M, 256), T = tm * tn;
@@ -1041,7 +1078,7 @@ static int launch_rs_cfg(as_ctx* ctx, const GemmParams& p_in, int m_off, int par
     const dim3 grid(T - split + split * p.tail_parts);
     if (whole) gemm_mfma_rs_kernel<0><<<grid, 256, smem, st>>>(p, 0, tm, tn);
     else gemm_mfma_rs_kernel<2><<<grid, 256, smem, st>>>(p, 0, tm, tn);
-    if (split) { AS_LAUNCH_CHECK(ctx); gemm_tail_fixup_kernel<<<dim3(4 * split), 256, 0, st>>>(p, tm, tn); }
+    if (split) { AS_LAUNCH_CHECK(ctx); gemm_tail_fixup_kernel<<<dim3(16 * split), 256, 0, st>>>(p, 0, tm, tn); }
   }
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
@@ -1141,6 +1178,9 @@ static GemmPick pick_plain(const GemmParams& p) {
 
 static GemmPick pick_cfg(const GemmParams& p) {
   if (ring_ok(p)) return pick_plain(p);
+  // the head's gradient: few target rows against a contraction over the vocabulary (about 1900 rows x 2048 x 32000: 64 tiles,
+  // 565 us unsplit, 231 in four parts; 250 rows: 497 us on 128x128 tiles, 75 in sixteen parts)
+  if (rs_ok(p) && live_split_ok(p)) return {24, 1};
   // narrow outputs stream A once: 128 x 128 tiles measured 2-33 % ahead of 256 x 64 here (58,880 rows; N = 128: 121 against
   // 181 us, where two 64-wide column tiles read A twice); up to 64 columns a 128 x 64 tile loads half the B rows per step
   if (p.N <= 64 && p.M > 128) return {4, 1};

@@ -74,6 +74,18 @@ def test_preference_step_more_targets_than_one_head_pass(bf16):
     print("dpo, several head passes, %s: max dz %.2e worst grad %.2e" % ("bf16" if bf16 else "fp32", dz, worst))
 
 
+@pytest.mark.parametrize("d,row_len,share", [(256, 64, 0.3), (256, 640, 0.45), (1024, 1600, 0.8)])
+def test_head_gradient_split_over_the_vocabulary(d, row_len, share):
+    """Few target rows against a vocabulary of 8192: the last product of the head (contraction over the vocabulary) is split
+    over workgroups by the live row count, 16 parts for 1 and 2-3 tiles, fewer for 20; fewer rows than a tile, a ragged
+    second tile.  The step's stated bf16 tolerances."""
+    import gpu_util as G
+    sh = synth.CONFIGS[1].replace(**dict(NARROW, d_model=d, vocab=8192))
+    trajs = synth.trajectories_lognormal(5, 1, row_len, sh.vocab, row_len // 3, 0.3, 16, row_len, turns=(2, 5), assistant_share=share, token_dist="uniform")
+    rep = G.compare_step(sh, 6, trajs, 1, max(row_len, 512), bf16=True, loss_tol=2e-3, grad_tol=3e-2)
+    print("d %d, %d tokens: loss rel %.2e worst grad %.2e" % (d, row_len, rep["loss_rel"], rep["worst_grad"]))
+
+
 # ------------------------------------------------------------------ true widths, reduced depth
 
 def _one_row(cfg_id, seed, row_len):
