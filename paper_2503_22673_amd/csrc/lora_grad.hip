@@ -10,6 +10,7 @@
 // c0 + 8 m + q of X.  U comes from its small token-major copy ([j][token]), one 16-byte load per
 // lane and 16-column block.  Token ranges (splits) go to a partial buffer reduced in split order.
 #include "common.h"
+#include <cmath>
 
 namespace {
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
@@ -137,10 +138,13 @@ __global__ void tn_reduce_kernel(const float* __restrict__ partial, int splits, 
 
 // One workgroup fits a CU (the accumulators fill the register file): the token range is split so that the launch is one
 // round of at most 256 workgroups (14336 columns: 28 x 9 = 252 workgroups; with 28 x 10 the last 24 ran alone and the
-// launch took half as long again).
+// launch took half as long again).  Short token ranges: a split of `s` steps costs their latency, its partial sums are
+// written and read again, so the best split grows with the root of the range; with r 16, kernel and sum of the splits, at
+// 16 steps per split and so: 1003 tokens x 2048: 16.4 and 8.2 us; 4000 x 2048: 17.6 and 12.1; 7500 x 512: 19.2 and 11.7;
+// 15,500 x 2048: 24.3 and 21.3.  (Not trimmed to the steps that are used: the bound on partial sums must grow with n.)
 static int tn_splits(int n, int M) {
   const int steps = (int)cdiv(n, 32), wg_cols = (int)cdiv(cdiv(M, 128), 4);
-  return (int)std::max<int64_t>(1, std::min<int64_t>(256 / wg_cols, cdiv(steps, 16)));
+  return (int)std::max<int64_t>(1, std::min<int64_t>(256 / wg_cols, (int64_t)std::sqrt(8.0 * steps)));
 }
 
 size_t lora_grad_tn_partial_floats(int n, int M, int r) { return (size_t)tn_splits(n, M) * M * r; }
@@ -152,9 +156,9 @@ int launch_lora_grad_tn(as_ctx* ctx, const void* X, int64_t ldx, const void* UT,
   if (r > 64 || (M % 8) || (ldx % 8) || (ldu % 8) || ((uintptr_t)X % 16) || ((uintptr_t)UT % 16) || ((uintptr_t)partial % 16))
     return as_fail(ctx, AS_ERR_SHAPE, "lora_grad_tn: rank <= 64 and 8-element alignment needed");
   const int steps = (int)cdiv(n, 32), slabs = (int)cdiv(M, 128);
-  const int splits = tn_splits(n, M);
+  const int per = (int)cdiv(steps, tn_splits(n, M)), splits = (int)cdiv(steps, per);
   if ((size_t)splits * M * r > partial_floats) return as_fail(ctx, AS_ERR_WORKSPACE, "lora_grad_tn: partial buffer too small");
-  TnParams p{(const bf16_t*)X, ldx, (const bf16_t*)UT, ldu, n, M, r, partial, (int)cdiv(steps, splits), steps};
+  TnParams p{(const bf16_t*)X, ldx, (const bf16_t*)UT, ldu, n, M, r, partial, per, steps};
   const int nb = (int)cdiv(r, 16);
   dim3 grid((unsigned)cdiv(slabs, 4), splits);
   prof_begin(ctx, st, AS_K_LORA_GRAD, 2.0 * n * (double)M * r);
