@@ -702,6 +702,12 @@ struct Step {
   int transpose(int rows, int cols, const void* in, int64_t ldi, void* out, int64_t ldo) {
     return launch_transpose(ctx, mode, rows, rows, cols, in, ldi, out, ldo, nullptr, 0, st);
   }
+  // the transpose [cols, rows] of a frozen projection, dense or NF4, for the product that contracts over its rows
+  int weight_transposed(int rows, int cols, const void* w, const float* absmax, void* out, int64_t ldo) {
+    if (c.weight_format == AS_W_NF4 && nf4_transposed_ok(mode, (const uint8_t*)w, rows, cols, out, ldo))
+      return launch_nf4_dequantize_transposed(ctx, (const uint8_t*)w, absmax, rows, cols, out, ldo, st);
+    return transpose(rows, cols, dense(w, absmax, rows, cols), cols, out, ldo);
+  }
   // [N tokens, cols] -> [cols, Np]: token-major copy whose rows are padded with zeros to Np
   int transpose_tok(int cols, const void* in, int64_t ldi, void* out) {
     return launch_transpose(ctx, mode, P.N, P.Np, cols, in, ldi, out, P.Np, nullptr, 0, st);
@@ -743,7 +749,7 @@ struct Step {
     else {
     // ---- down projection
     { LoraSlot& s = slot(l, AS_T_DOWN);
-      if ((rc = transpose(d, F, dense(w.wdown, w.adown, d, F), F, P.wT, d))) return rc;                       // [F, d]
+      if ((rc = weight_transposed(d, F, w.wdown, w.adown, P.wT, d))) return rc;                       // [F, d]
       if (s.on && (rc = gemm(N, rp, P.dh, d, s.Bst, d, d, nullptr, 0, nullptr, 0, 0, nullptr, 0, P.du_d, rp))) return rc;
       rows_cap_once = P.cap;
       if ((rc = gemm(N, F, P.dh, d, P.wT, d, d, s.on ? P.du_d : nullptr, rp, s.At, rp, s.on ? rp : 0, nullptr, 0, P.dm, F))) return rc;
@@ -765,7 +771,7 @@ struct Step {
       const void* wg[2] = {w.wgate, w.wup}; const float* ag[2] = {w.agate, w.aup};
       for (int i = 0; i < 2; i++) {
         LoraSlot& s = slot(l, AS_T_GATE + i);
-        if ((rc = transpose(F, d, dense(wg[i], ag[i], F, d), d, off(P.wT, (size_t)i * F), 2 * F))) return rc;        // [d, 2F]
+        if ((rc = weight_transposed(F, d, wg[i], ag[i], off(P.wT, (size_t)i * F), 2 * F))) return rc;        // [d, 2F]
         if (s.on && (rc = gemm(N, rp, off(P.dgu, (size_t)i * F), 2 * F, s.Bst, F, F, nullptr, 0, nullptr, 0, 0, nullptr, 0,
                                off(P.du_gu, (size_t)s.slot * rp), ldg))) return rc;
       }
@@ -825,7 +831,7 @@ struct Step {
       const bool need_da = full || l > 0;
       for (int i = 0; i < 3; i++) {
         LoraSlot& s = slot(l, i);
-        if (need_da && (rc = transpose(nout[i], d, dense(wq[i], aq[i], nout[i], d), d, off(P.wT, coff[i]), QKV))) return rc;          // [d, QKV]
+        if (need_da && (rc = weight_transposed(nout[i], d, wq[i], aq[i], off(P.wT, coff[i]), QKV))) return rc;          // [d, QKV]
         if (s.on && (rc = gemm(N, rp, off(P.dqkv, coff[i]), QKV, s.Bst, nout[i], nout[i], nullptr, 0, nullptr, 0, 0, nullptr, 0,
                                off(P.du_qkv, (size_t)s.slot * rp), ldu))) return rc;
       }

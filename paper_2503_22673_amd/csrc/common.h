@@ -176,6 +176,9 @@ int launch_rope(as_ctx* ctx, int mode, int n, int n_heads, int dh, void* x, int6
 // NF4 block quantisation (quant.hip)
 int launch_nf4_quantize(as_ctx* ctx, int mode, const void* w, int64_t numel, uint8_t* codes, float* absmax, hipStream_t st);
 int launch_nf4_dequantize(as_ctx* ctx, int mode, const uint8_t* codes, const float* absmax, int64_t numel, void* out, hipStream_t st);
+// out[c, r] = the dequantised element (r, c) of a [rows, cols] matrix (bf16), where nf4_transposed_ok
+bool nf4_transposed_ok(int mode, const uint8_t* codes, int rows, int cols, const void* out, int64_t ldo);
+int launch_nf4_dequantize_transposed(as_ctx* ctx, const uint8_t* codes, const float* absmax, int rows, int cols, void* out, int64_t ldo, hipStream_t st);
 // mixture-of-experts routing and row grouping (moe.hip)
 int launch_moe_route(as_ctx* ctx, const float* logit, int n, int E, int32_t* sel, float* w, hipStream_t st);
 int launch_moe_permute(as_ctx* ctx, const int32_t* sel, int n, int E, int32_t* eoff, int32_t* pos, int32_t* perm, hipStream_t st);
