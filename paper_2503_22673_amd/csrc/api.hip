@@ -739,6 +739,12 @@ struct Step {
     return gemm(dout, din, dyT_rows, N, xT, N, N, nullptr, 0, nullptr, 0, 0, nullptr, 0, dW, din, 1);
   }
 
+  // backward of a norm over the tokens; dg: its gain gradient too (full fine-tuning)
+  int norm_bwd(const void* dy, const int32_t* src_pos, const void* x, const void* g, const float* rstd, const void* add, void* dx, float* dg) {
+    if (dg) return launch_rmsnorm_bwd_gain(ctx, mode, P.N, P.d, dy, src_pos, x, g, rstd, add, dx, P.gpart, 256, dg, st);
+    return launch_rmsnorm_bwd(ctx, mode, P.N, P.d, dy, src_pos, x, g, rstd, add, dx, st);
+  }
+
   // dh_out in P.dh -> dh_in in P.dh (P.dh2 holds the mid-layer gradient)
   int backward_layer(int l, Acts& a) {
     const as_layer_weights& w = W->layers[l];
@@ -794,11 +800,10 @@ struct Step {
       } }
     }
     // ---- second norm
-    if (full && (rc = launch_rmsnorm_dgain(ctx, mode, N, d, P.db, nullptr, a.h_mid, a.rstd2, P.gpart, 256, G->w_layers[l].g2, st))) return rc;
-    if ((rc = launch_rmsnorm_bwd(ctx, mode, N, d, P.db, nullptr, a.h_mid, w.g2, a.rstd2, P.dh, P.dh2, st))) return rc;
+    if ((rc = norm_bwd(P.db, nullptr, a.h_mid, w.g2, a.rstd2, P.dh, P.dh2, full ? G->w_layers[l].g2 : nullptr))) return rc;
     // ---- output projection
     { LoraSlot& s = slot(l, AS_T_O);
-      if ((rc = transpose(d, D, dense(w.wo, w.ao, d, D), D, P.wT, d))) return rc;                          // [D, d]
+      if ((rc = weight_transposed(d, D, w.wo, w.ao, P.wT, d))) return rc;                          // [D, d]
       if (s.on && (rc = gemm(N, rp, P.dh2, d, s.Bst, d, d, nullptr, 0, nullptr, 0, 0, nullptr, 0, P.du_o, rp))) return rc;
       rows_cap_once = P.cap;
       if ((rc = gemm(N, D, P.dh2, d, P.wT, d, d, s.on ? P.du_o : nullptr, rp, s.At, rp, s.on ? rp : 0, nullptr, 0, P.d_o, D))) return rc;
@@ -854,8 +859,7 @@ struct Step {
       } }
     // ---- first norm
     if (!full && l == 0) return AS_OK;
-    if (full && (rc = launch_rmsnorm_dgain(ctx, mode, N, d, P.da, nullptr, P.h[l], a.rstd1, P.gpart, 256, G->w_layers[l].g1, st))) return rc;
-    return launch_rmsnorm_bwd(ctx, mode, N, d, P.da, nullptr, P.h[l], w.g1, a.rstd1, P.dh2, P.dh, st);
+    return norm_bwd(P.da, nullptr, P.h[l], w.g1, a.rstd1, P.dh2, P.dh, full ? G->w_layers[l].g1 : nullptr);
   }
 
   // one product of the head over the target rows r0 .. r0 + rows - 1 (their number lives on the device), with one of the
@@ -946,8 +950,7 @@ struct Step {
     if ((rc = head_grad_rows(row_w, LS.kind == LOSS_MEAN, full ? G->head : nullptr))) return rc;
     if (LS.kind == LOSS_MEAN && (rc = launch_loss_finalize(ctx, P.loss_rows, P.count, d_loss, d_loss_sum, st))) return rc;
     // back through the final norm, scattered to all rows (zero where a row is no target)
-    if (full && (rc = launch_rmsnorm_dgain(ctx, mode, N, d, P.dhf, P.tgt_pos, P.h[P.L], P.rstd_f, P.gpart, 256, G->g_final, st))) return rc;
-    return launch_rmsnorm_bwd(ctx, mode, N, d, P.dhf, P.tgt_pos, P.h[P.L], W->g_final, P.rstd_f, nullptr, P.dh, st);
+    return norm_bwd(P.dhf, P.tgt_pos, P.h[P.L], W->g_final, P.rstd_f, nullptr, P.dh, full ? G->g_final : nullptr);
   }
 };
 

@@ -168,9 +168,9 @@ int launch_rmsnorm_fwd(as_ctx* ctx, int mode, int n, int d, const void* x, const
 int launch_rmsnorm_bwd(as_ctx* ctx, int mode, int n, int d, const void* dy, const int32_t* src_pos,
                        const void* x, const void* g, const float* rstd, const void* add, void* dx,
                        hipStream_t st);
-int launch_rmsnorm_dgain(as_ctx* ctx, int mode, int n, int d, const void* dy, const int32_t* src_pos,
-                         const void* x, const float* rstd, float* partial, int n_part, float* dg,
-                         hipStream_t st);
+// the same, and dg = sum_t dy[t] x[t] rstd[t] (partial: n_part rows of d floats)
+int launch_rmsnorm_bwd_gain(as_ctx* ctx, int mode, int n, int d, const void* dy, const int32_t* src_pos, const void* x, const void* g,
+                            const float* rstd, const void* add, void* dx, float* partial, int n_part, float* dg, hipStream_t st);
 int launch_rope(as_ctx* ctx, int mode, int n, int n_heads, int dh, void* x, int64_t ldx,
                 const int32_t* seg_start, const float* cosb, const float* sinb, int inverse, hipStream_t st);
 // NF4 block quantisation (quant.hip)

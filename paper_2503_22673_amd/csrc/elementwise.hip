@@ -373,8 +373,97 @@ int launch_rmsnorm_bwd(as_ctx* ctx, int mode, int n, int d, const void* dy, cons
   return AS_OK;
 }
 
-// Gain gradient dg_j = sum_t dy[t,j] x[t,j] rstd[t]: each block sums a slab of
-// rows into partial[block, :], a second pass adds the slabs in block order.
+// The same with the gain gradient dg_j = sum_t dy[t,j] x[t,j] rstd[t] out of the same pass over dy and x (full fine-tuning):
+// up to 256 workgroups walk the rows, a lane adds up the columns it holds of every row it sees, the waves of a workgroup are
+// added in order through LDS into partial[workgroup, :], and a second launch adds the workgroups in order.  Bound by memory
+// (dy, x, add in, dx out), so by the rows in flight: KEEP = 4 (2048 16-bit columns) leaves registers for 16 waves of a
+// workgroup, KEEP = 8 for 8.  15,700 rows of 2048, bf16: 77 us with the sum; as three launches
+// (backward, a second pass over dy and x, a sum of 256 slabs by one thread per column) 130 us.
+template <typename T, int KEEP>
+__global__ __launch_bounds__(4096 / KEEP) void rmsnorm_bwd_gain_kernel(int n, int d, const T* __restrict__ dy, const int32_t* __restrict__ src_pos,
+                                                               const T* __restrict__ x, const T* __restrict__ g, const float* __restrict__ rstd,
+                                                               const T* __restrict__ add, T* __restrict__ dx, float* __restrict__ partial) {
+  constexpr int VN = Vec<T>::N, STEP = AS_WAVE * VN, NW = 64 / KEEP;
+  typedef typename Vec<T>::type VT;
+  extern __shared__ __align__(16) float gsum[];          // [d]
+  const int lane = threadIdx.x % AS_WAVE, wave = threadIdx.x / AS_WAVE;
+  float acc[KEEP][VN];
+#pragma unroll
+  for (int q = 0; q < KEEP; q++)
+#pragma unroll
+    for (int i = 0; i < VN; i++) acc[q][i] = 0.f;
+  for (int64_t row = (int64_t)blockIdx.x * NW + wave; row < n; row += (int64_t)gridDim.x * NW) {
+    const int64_t src = src_pos ? src_pos[row] : row;
+    T* dxr = dx + row * d;
+    const T* ar = add ? add + row * d : nullptr;
+    if (src < 0) {                                       // no upstream gradient for this row
+#pragma unroll
+      for (int q = 0; q < KEEP; q++) {
+        const int j = q * STEP + lane * VN;
+        if (j < d) {
+          float o[VN];
+#pragma unroll
+          for (int i = 0; i < VN; i++) o[i] = 0.f;
+          if (ar) load_vec<T>(ar + j, o);
+          store_vec<T>(dxr + j, o);
+        }
+      }
+      continue;
+    }
+    const T* dyr = dy + src * d; const T* xr = x + row * d;
+    const float r = rstd[src_pos ? src : row];
+    VT kdy[KEEP], kx[KEEP], ka[KEEP];
+#pragma unroll
+    for (int q = 0; q < KEEP; q++) {
+      const int j = q * STEP + lane * VN;
+      if (j < d) {
+        kdy[q] = *reinterpret_cast<const VT*>(dyr + j); kx[q] = *reinterpret_cast<const VT*>(xr + j);
+        if (ar) ka[q] = *reinterpret_cast<const VT*>(ar + j);
+      }
+    }
+    float dot = 0.f;
+#pragma unroll
+    for (int q = 0; q < KEEP; q++) {
+      const int j = q * STEP + lane * VN;
+      if (j < d) {
+        float c[VN]; load_vec<T>(g + j, c);
+#pragma unroll
+        for (int i = 0; i < VN; i++) {
+          const float p = to_f<T>(kdy[q][i]) * to_f<T>(kx[q][i]);
+          dot += p * c[i]; acc[q][i] += p * r;
+        }
+      }
+    }
+    dot = wave_sum(dot);
+    const float k = r * r * r * dot / (float)d;
+#pragma unroll
+    for (int q = 0; q < KEEP; q++) {
+      const int j = q * STEP + lane * VN;
+      if (j < d) {
+        float c[VN], o[VN]; load_vec<T>(g + j, c);
+#pragma unroll
+        for (int i = 0; i < VN; i++) o[i] = (ar ? to_f<T>(ka[q][i]) : 0.f) + (r * c[i] * to_f<T>(kdy[q][i]) - to_f<T>(kx[q][i]) * k);
+        store_vec<T>(dxr + j, o);
+      }
+    }
+  }
+  for (int w = 0; w < NW; w++) {
+    if (wave == w) {
+#pragma unroll
+      for (int q = 0; q < KEEP; q++) {
+        const int j = q * STEP + lane * VN;
+        if (j < d) {
+#pragma unroll
+          for (int i = 0; i < VN; i++) gsum[j + i] = (w ? gsum[j + i] : 0.f) + acc[q][i];
+        }
+      }
+    }
+    __syncthreads();
+  }
+  for (int j = threadIdx.x; j < d; j += NW * AS_WAVE) partial[(int64_t)blockIdx.x * d + j] = gsum[j];
+}
+
+// Gain gradient alone (rows the kernel above does not take): each block sums a slab of rows into partial[block, :].
 template <typename T>
 __global__ void rmsnorm_dgain_part(int n, int d, const T* __restrict__ dy, const int32_t* __restrict__ src_pos,
                                    const T* __restrict__ x, const float* __restrict__ rstd,
@@ -390,25 +479,44 @@ __global__ void rmsnorm_dgain_part(int n, int d, const T* __restrict__ dy, const
   }
   partial[(int64_t)blockIdx.y * d + j] = acc;
 }
-__global__ void sum_partials_kernel(const float* __restrict__ partial, int n_part, int64_t len,
-                                    float alpha, float* __restrict__ out) {
-  int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= len) return;
+// out[j] = sum over the slabs: 32 columns per workgroup, eight threads per column with every eighth slab each, added in order
+__global__ __launch_bounds__(256) void sum_partials_kernel(const float* __restrict__ partial, int n_part, int64_t len, float* __restrict__ out) {
+  __shared__ float sh[8][32];
+  const int c = threadIdx.x & 31, k = threadIdx.x >> 5;
+  const int64_t j = (int64_t)blockIdx.x * 32 + c;
   float acc = 0.f;
-  for (int p = 0; p < n_part; p++) acc += partial[(int64_t)p * len + j];
-  out[j] = alpha * acc;
+  if (j < len) {
+#pragma unroll 8
+    for (int p = k; p < n_part; p += 8) acc += partial[(int64_t)p * len + j];
+  }
+  sh[k][c] = acc;
+  __syncthreads();
+  if (k == 0 && j < len) {
+    for (int i = 1; i < 8; i++) acc += sh[i][c];
+    out[j] = acc;
+  }
 }
 
-int launch_rmsnorm_dgain(as_ctx* ctx, int mode, int n, int d, const void* dy, const int32_t* src_pos,
-                         const void* x, const float* rstd, float* partial, int n_part, float* dg,
-                         hipStream_t st) {
+int launch_rmsnorm_bwd_gain(as_ctx* ctx, int mode, int n, int d, const void* dy, const int32_t* src_pos, const void* x, const void* g,
+                            const float* rstd, const void* add, void* dx, float* partial, int n_part, float* dg, hipStream_t st) {
   if (n <= 0 || n_part <= 0) return AS_OK;
-  int rows_per = (int)cdiv(n, n_part);
-  dim3 grid(cdiv(d, 256), n_part);
-  DISPATCH_T(mode, (rmsnorm_dgain_part<T><<<grid, 256, 0, st>>>(n, d, (const T*)dy, src_pos, (const T*)x, rstd,
-                                                                 partial, rows_per)));
+  bool fused = false;
+  DISPATCH_T(mode, fused = d <= 8 * AS_WAVE * Vec<T>::N && vec_ok<T>(dy, d) && vec_ok<T>(x, d) && vec_ok<T>(g, d) && vec_ok<T>(dx, d) && (!add || vec_ok<T>(add, d)););
+  prof_begin(ctx, st, AS_K_NORM, 0.0);
+  if (fused) {
+    DISPATCH_T(mode, {
+      const bool small = d <= 4 * AS_WAVE * Vec<T>::N;
+      n_part = (int)std::min<int64_t>(n_part, cdiv(n, small ? 16 : 8));
+      if (small) rmsnorm_bwd_gain_kernel<T, 4><<<n_part, 1024, (size_t)d * 4, st>>>(n, d, (const T*)dy, src_pos, (const T*)x, (const T*)g, rstd, (const T*)add, (T*)dx, partial);
+      else rmsnorm_bwd_gain_kernel<T, 8><<<n_part, 512, (size_t)d * 4, st>>>(n, d, (const T*)dy, src_pos, (const T*)x, (const T*)g, rstd, (const T*)add, (T*)dx, partial); });
+  } else {
+    int rc = launch_rmsnorm_bwd(ctx, mode, n, d, dy, src_pos, x, g, rstd, add, dx, st);
+    if (rc) return rc;
+    DISPATCH_T(mode, (rmsnorm_dgain_part<T><<<dim3(cdiv(d, 256), n_part), 256, 0, st>>>(n, d, (const T*)dy, src_pos, (const T*)x, rstd, partial, (int)cdiv(n, n_part))));
+  }
   AS_LAUNCH_CHECK(ctx);
-  sum_partials_kernel<<<cdiv(d, 256), 256, 0, st>>>(partial, n_part, d, 1.f, dg);
+  sum_partials_kernel<<<(unsigned)cdiv(d, 32), 256, 0, st>>>(partial, n_part, d, dg);
+  prof_end(ctx, st);
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }

@@ -114,3 +114,15 @@ def test_embedding_gradient_piece_and_tile_edges(n, d, bf16):
     row_len = max(512, n)
     rep = G.compare_step(sh, 4, trajs, 1, row_len, bf16=bf16, loss_tol=2e-3 if bf16 else 1e-4, grad_tol=3e-2 if bf16 else 1e-4, full=True)
     assert rep["grads"]["embed"] <= (3e-2 if bf16 else 1e-4)
+
+
+@pytest.mark.parametrize("d,bf16", [(72, False), (1032, False), (100, True), (2048, True), (2304, True), (4104, True)])
+def test_gain_gradients_over_row_widths(d, bf16):
+    """Gain gradients that come out of the norm's backward pass (up to 1024 / 2048 float, 2048 / 4096 bf16 columns in registers)
+    and those of wider rows and of rows that are no whole vectors (a pass of their own); the final norm's rows are a subset."""
+    import gpu_util as G
+    sh = synth.CONFIGS[1].replace(n_layers=1, n_q_heads=2, n_kv_heads=1, head_dim=32, d_model=d, ffn=64, vocab=96,
+                                  lora_rank=0, lora_alpha=0.0, lora_targets=(), full_ft=True)
+    trajs = random_trajs(d, 6, sh.vocab, turn_lo=10, turn_hi=30, turns=(2, 4))
+    rep = G.compare_step(sh, 3, trajs, 1, 512, bf16=bf16, loss_tol=2e-3 if bf16 else 1e-4, grad_tol=3e-2 if bf16 else 1e-4, full=True)
+    assert max(rep["grads"][k] for k in ("g_final", "L0.g1", "L0.g2")) <= (3e-2 if bf16 else 1e-4)
