@@ -518,25 +518,32 @@ struct Step {
     return launch_gemm_off(ctx, mode, gv, g, 0, st);
   }
 
-  int prep_lora(int l) {
-    const as_layer_lora& Lr = lora->layers[l];
+  // type T copies of every adapter and their transposes, as many matrices per launch as a kernel argument holds
+  int prep_lora() {
     const float s = c.lora_alpha / (float)c.lora_rank;
     const int r = c.lora_rank, rp = P.rp;
-    for (int t = 0; t < AS_N_TARGETS; t++) {
-      LoraSlot& sl = slot(l, t);
-      if (!sl.on) continue;
-      int64_t ld_at = (t <= AS_T_V) ? (int64_t)P.n_qkv * rp : (t == AS_T_GATE || t == AS_T_UP) ? (int64_t)P.n_gu * rp : rp;
-      // A [r, din] -> A copy [rp, din] and its transpose block [din, rp] inside a [din, group] matrix
-      int rc = launch_lora_prep_ex(Lr.a[t], r, sl.din, rp, sl.din, 1.f, sl.A, sl.din, sl.At, ld_at);
-      if (rc) return rc;
-      // B [dout, r] -> s*B [dout, rp] and transpose [rp, dout]
-      rc = launch_lora_prep_ex(Lr.b[t], sl.dout, r, sl.dout, rp, s, sl.Bs, rp, sl.Bst, sl.dout);
-      if (rc) return rc;
+    PrepBatch b; b.n = 0; b.n_tiles = 0;
+    int rc = AS_OK;
+    auto add = [&](const float* in, int rows, int cols, int rows_pad, int cols_pad, float scale, void* out, int64_t ldo, void* out_t, int64_t ldo_t) {
+      const int64_t tiles = cdiv(rows_pad, 64) * cdiv(cols_pad, 64);
+      if (!rc && (b.n == kPrepBatch || b.n_tiles + tiles > (1 << 22))) { rc = launch_lora_prep_batch(ctx, mode, b, st); b.n = 0; b.n_tiles = 0; }
+      b.m[b.n++] = {in, out, out_t, ldo, ldo_t, rows, cols, rows_pad, cols_pad, scale, b.n_tiles};
+      b.n_tiles += (int)tiles;
+    };
+    for (int l = 0; l < c.n_layers; l++) {
+      const as_layer_lora& Lr = lora->layers[l];
+      for (int t = 0; t < AS_N_TARGETS; t++) {
+        LoraSlot& sl = slot(l, t);
+        if (!sl.on) continue;
+        int64_t ld_at = (t <= AS_T_V) ? (int64_t)P.n_qkv * rp : (t == AS_T_GATE || t == AS_T_UP) ? (int64_t)P.n_gu * rp : rp;
+        // A [r, din] -> A copy [rp, din] and its transpose block [din, rp] inside a [din, group] matrix
+        add(Lr.a[t], r, sl.din, rp, sl.din, 1.f, sl.A, sl.din, sl.At, ld_at);
+        // B [dout, r] -> s*B [dout, rp] and transpose [rp, dout]
+        add(Lr.b[t], sl.dout, r, sl.dout, rp, s, sl.Bs, rp, sl.Bst, sl.dout);
+      }
     }
-    return AS_OK;
+    return rc ? rc : launch_lora_prep_batch(ctx, mode, b, st);
   }
-  int launch_lora_prep_ex(const float* in, int rows, int cols, int rows_pad, int cols_pad, float scale,
-                          void* out, int64_t ldo, void* out_t, int64_t ldo_t);
 
   int forward_layer(int l, Acts& a) {
     const as_layer_weights& w = W->layers[l];
@@ -653,8 +660,7 @@ struct Step {
         if ((rc = transpose_tok(E, P.dlogit, E, P.dyT))) return rc;
         if ((rc = transpose_tok(d, a.b, d, P.xT))) return rc;
       }
-      if ((rc = transpose_tok(rp, a.u_r, rp, P.uT))) return rc;
-      if ((rc = transpose_tok(rp, P.du_r, rp, P.duT))) return rc;
+      if ((rc = transpose_pair(rp, a.u_r, P.du_r, P.uT, P.duT))) return rc;
       if ((rc = lora_grads(l, AS_T_ROUTER, P.dlogit, E, a.b, d, P.dyT, P.xT))) return rc;
     }
     return AS_OK;
@@ -713,6 +719,11 @@ struct Step {
     return launch_transpose(ctx, mode, P.N, P.Np, cols, in, ldi, out, P.Np, nullptr, 0, st);
   }
 
+  // the same for the adapter activations u and their gradients du, which have one shape
+  int transpose_pair(int cols, const void* u, const void* du, void* uT, void* duT) {
+    return launch_transpose_pair(ctx, mode, P.N, P.Np, cols, u, du, cols, uT, duT, P.Np, st);
+  }
+
   // adapter gradients of one projection: dB = s dy^T u, dA = du^T x.  bf16 with rank <= 64: one
   // streaming pass over dy and over x (row-major, as they are) against the token-major copies of u
   // and du.  Otherwise: GEMMs on the token-major copies dyT [dout, Np], xT [din, Np].
@@ -767,8 +778,7 @@ struct Step {
         if ((rc = transpose_tok(F, a.m, F, P.xT))) return rc;
       }
       if (s.on) {
-        if ((rc = transpose_tok(rp, a.u_d, rp, P.uT))) return rc;
-        if ((rc = transpose_tok(rp, P.du_d, rp, P.duT))) return rc;
+        if ((rc = transpose_pair(rp, a.u_d, P.du_d, P.uT, P.duT))) return rc;
         if ((rc = lora_grads(l, AS_T_DOWN, P.dh, d, a.m, F, P.dyT, P.xT))) return rc;
       }
       if (full && (rc = weight_grad(G->w_layers[l].wdown, d, F, P.dyT, P.xT))) return rc; }
@@ -789,8 +799,7 @@ struct Step {
         if ((rc = transpose_tok(d, a.b, d, P.xT))) return rc;
       }
       if (P.n_gu) {
-        if ((rc = transpose_tok(ldg, a.u_gu, ldg, P.uT))) return rc;
-        if ((rc = transpose_tok(ldg, P.du_gu, ldg, P.duT))) return rc;
+        if ((rc = transpose_pair(ldg, a.u_gu, P.du_gu, P.uT, P.duT))) return rc;
         for (int i = 0; i < 2; i++)
           if ((rc = lora_grads(l, AS_T_GATE + i, off(P.dgu, (size_t)i * F), 2 * F, a.b, d, off(P.dyT, (size_t)i * F * P.Np), P.xT))) return rc;
       }
@@ -812,8 +821,7 @@ struct Step {
         if ((rc = transpose_tok(D, a.o, D, P.xT))) return rc;
       }
       if (s.on) {
-        if ((rc = transpose_tok(rp, a.u_o, rp, P.uT))) return rc;
-        if ((rc = transpose_tok(rp, P.du_o, rp, P.duT))) return rc;
+        if ((rc = transpose_pair(rp, a.u_o, P.du_o, P.uT, P.duT))) return rc;
         if ((rc = lora_grads(l, AS_T_O, P.dh2, d, a.o, D, P.dyT, P.xT))) return rc;
       }
       if (full && (rc = weight_grad(G->w_layers[l].wo, d, D, P.dyT, P.xT))) return rc; }
@@ -848,8 +856,7 @@ struct Step {
         if ((rc = transpose_tok(d, a.a, d, P.xT))) return rc;
       }
       if (P.n_qkv) {
-        if ((rc = transpose_tok(ldu, a.u_qkv, ldu, P.uT))) return rc;
-        if ((rc = transpose_tok(ldu, P.du_qkv, ldu, P.duT))) return rc;
+        if ((rc = transpose_pair(ldu, a.u_qkv, P.du_qkv, P.uT, P.duT))) return rc;
         for (int i = 0; i < 3; i++)
           if ((rc = lora_grads(l, i, off(P.dqkv, coff[i]), QKV, a.a, d, off(P.dyT, (size_t)coff[i] * P.Np), P.xT))) return rc;
       }
@@ -954,10 +961,6 @@ struct Step {
   }
 };
 
-int Step::launch_lora_prep_ex(const float* in, int rows, int cols, int rows_pad, int cols_pad, float scale,
-                              void* out, int64_t ldo, void* out_t, int64_t ldo_t) {
-  return launch_lora_prep2(ctx, mode, in, rows, cols, rows_pad, cols_pad, scale, out, ldo, out_t, ldo_t, st);
-}
 }  // namespace
 
 // Small per-step table (compacted segment boundaries, launch orders, pair list) host -> device into the caller's
@@ -1116,7 +1119,7 @@ static int run_step(as_ctx* ctx, const char* who, const as_weights* weights, con
   if ((rc = launch_rope_table(ctx, max_seg, c.head_dim, c.rope_base, P.rope_cos, P.rope_sin, st))) return rc;
   if ((rc = launch_select_targets(ctx, P.seg_start, d_loss_mask, d_tokens, n, P.tgt_idx, P.tgt_pos, P.labels, d_count, st))) return rc;
   P.count = d_count;
-  if (!full && !adapters_off) for (int l = 0; l < c.n_layers; l++) if ((rc = S.prep_lora(l))) return rc;
+  if (!full && !adapters_off && (rc = S.prep_lora())) return rc;
   if ((rc = launch_embed(ctx, c.mode, d_tokens, n, c.d_model, weights->embed, P.h[0], st))) return rc;
   for (int l = 0; l < c.n_layers; l++)
     if ((rc = S.forward_layer(l, P.acts[c.recompute == 1 ? 0 : l]))) return rc;

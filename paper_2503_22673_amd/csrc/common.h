@@ -195,10 +195,15 @@ int launch_transpose(as_ctx* ctx, int mode, int rows, int rows_pad, int cols, co
                      int64_t ldo, const int* rows_dev, int row_off, hipStream_t st);
 int launch_transpose_qs(as_ctx* ctx, int mode, int rows, int rows_pad, int cols, const void* in, int64_t ldi, void* out,
                         int64_t ldo, hipStream_t st);
+// two matrices of one shape and layout in one launch where the 16-bit kernel takes them
+int launch_transpose_pair(as_ctx* ctx, int mode, int rows, int rows_pad, int cols, const void* in, const void* in2, int64_t ldi,
+                          void* out, void* out2, int64_t ldo, hipStream_t st);
 // out[rows_pad, cols_pad] (type T, row stride ldo) = scale * in[rows, cols] (float), zero in the
-// padding; out_t (row stride ldo_t) receives the transpose.  Either output may be NULL.
-int launch_lora_prep2(as_ctx* ctx, int mode, const float* in, int rows, int cols, int rows_pad, int cols_pad,
-                      float scale, void* out, int64_t ldo, void* out_t, int64_t ldo_t, hipStream_t st);
+// padding; out_t (row stride ldo_t) receives the transpose.
+struct PrepMatrix { const float* in; void *out, *out_t; int64_t ldo, ldo_t; int rows, cols, rows_pad, cols_pad; float scale; int first_tile; };
+constexpr int kPrepBatch = 48;                             // a batch is a kernel argument (3.1 KB)
+struct PrepBatch { PrepMatrix m[kPrepBatch]; int n, n_tiles; };
+int launch_lora_prep_batch(as_ctx* ctx, int mode, const PrepBatch& b, hipStream_t st);
 int launch_fill_zero(as_ctx* ctx, void* p, size_t bytes, hipStream_t st);
 int launch_select_targets(as_ctx* ctx, const int32_t* seg_start, const uint8_t* mask, const int32_t* tok,
                           int n, int32_t* tgt_idx, int32_t* tgt_pos, int32_t* labels, int32_t* count,

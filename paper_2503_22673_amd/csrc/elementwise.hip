@@ -632,9 +632,12 @@ __global__ void transpose_kernel(int rows, int rows_pad, int cols, const T* __re
 // 1B layer's weight gradients 1371 and 712 us (4.9 TB/s).
 // QS: the lane of an even output chunk takes source rows 0-3 and 8-11 of its 16, that of an odd one the others.
 // Needs cols, ldi, ldo and rows_pad multiples of 8 (QS: rows_pad of 16) and 16-byte aligned bases.
+// grid.z = 2: a second matrix of the same shape and strides (in2 -> out2).
 template <bool QS>
 __global__ __launch_bounds__(256) void transpose_vec_kernel(int rows, int rows_pad, int cols, const bf16_t* __restrict__ in, int64_t ldi,
-                                                            bf16_t* __restrict__ out, int64_t ldo, const int* __restrict__ rows_dev, int row_off) {
+                                                            bf16_t* __restrict__ out, int64_t ldo, const int* __restrict__ rows_dev, int row_off,
+                                                            const bf16_t* __restrict__ in2, bf16_t* __restrict__ out2) {
+  if (blockIdx.z) { in = in2; out = out2; }
   typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
   const int live = rows_dev ? min(rows, *rows_dev - row_off) : rows;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -674,12 +677,27 @@ int launch_transpose(as_ctx* ctx, int mode, int rows, int rows_pad, int cols, co
   dim3 grid(cdiv(cols, 64), cdiv(rows_pad, 64));
   prof_begin(ctx, st, AS_K_TRANSPOSE, 0.0);
   if (transpose_vec_ok(mode, rows_pad, cols, in, ldi, out, ldo))
-    transpose_vec_kernel<false><<<dim3((unsigned)cdiv(cols, 64), (unsigned)cdiv(rows_pad, 256)), 256, 0, st>>>(rows, rows_pad, cols, (const bf16_t*)in, ldi, (bf16_t*)out, ldo, rows_dev, row_off);
+    transpose_vec_kernel<false><<<dim3((unsigned)cdiv(cols, 64), (unsigned)cdiv(rows_pad, 256)), 256, 0, st>>>(rows, rows_pad, cols, (const bf16_t*)in, ldi, (bf16_t*)out, ldo, rows_dev, row_off, nullptr, nullptr);
   else
   DISPATCH_T(mode, (transpose_kernel<T, false><<<grid, 256, 0, st>>>(rows, rows_pad, cols, (const T*)in, ldi, (T*)out, ldo, rows_dev, row_off)));
   prof_end(ctx, st);
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
+}
+
+int launch_transpose_pair(as_ctx* ctx, int mode, int rows, int rows_pad, int cols, const void* in, const void* in2, int64_t ldi,
+                          void* out, void* out2, int64_t ldo, hipStream_t st) {
+  if (rows <= 0 || cols <= 0) return AS_OK;
+  if (transpose_vec_ok(mode, rows_pad, cols, in, ldi, out, ldo) && transpose_vec_ok(mode, rows_pad, cols, in2, ldi, out2, ldo)) {
+    prof_begin(ctx, st, AS_K_TRANSPOSE, 0.0);
+    transpose_vec_kernel<false><<<dim3((unsigned)cdiv(cols, 64), (unsigned)cdiv(rows_pad, 256), 2), 256, 0, st>>>(
+        rows, rows_pad, cols, (const bf16_t*)in, ldi, (bf16_t*)out, ldo, nullptr, 0, (const bf16_t*)in2, (bf16_t*)out2);
+    prof_end(ctx, st);
+    AS_LAUNCH_CHECK(ctx);
+    return AS_OK;
+  }
+  const int rc = launch_transpose(ctx, mode, rows, rows_pad, cols, in, ldi, out, ldo, nullptr, 0, st);
+  return rc ? rc : launch_transpose(ctx, mode, rows, rows_pad, cols, in2, ldi, out2, ldo, nullptr, 0, st);
 }
 
 // the quad-swapped variant (rows_pad must be a multiple of 16)
@@ -690,7 +708,7 @@ int launch_transpose_qs(as_ctx* ctx, int mode, int rows, int rows_pad, int cols,
   dim3 grid(cdiv(cols, 64), cdiv(rows_pad, 64));
   prof_begin(ctx, st, AS_K_TRANSPOSE, 0.0);
   if (transpose_vec_ok(mode, rows_pad, cols, in, ldi, out, ldo))
-    transpose_vec_kernel<true><<<dim3((unsigned)cdiv(cols, 64), (unsigned)cdiv(rows_pad, 256)), 256, 0, st>>>(rows, rows_pad, cols, (const bf16_t*)in, ldi, (bf16_t*)out, ldo, nullptr, 0);
+    transpose_vec_kernel<true><<<dim3((unsigned)cdiv(cols, 64), (unsigned)cdiv(rows_pad, 256)), 256, 0, st>>>(rows, rows_pad, cols, (const bf16_t*)in, ldi, (bf16_t*)out, ldo, nullptr, 0, nullptr, nullptr);
   else
   DISPATCH_T(mode, (transpose_kernel<T, true><<<grid, 256, 0, st>>>(rows, rows_pad, cols, (const T*)in, ldi, (T*)out, ldo, nullptr, 0)));
   prof_end(ctx, st);
@@ -699,24 +717,42 @@ int launch_transpose_qs(as_ctx* ctx, int mode, int rows, int rows_pad, int cols,
 }
 
 // ------------------------------------------------------ LoRA operand copies
-// out[rp, cp] = scale * in[r, c] inside, 0 in the padding; out_t is its transpose.
+// out[rp, cp] = scale * in[r, c] inside, 0 in the padding; out_t is its transpose.  Up to kPrepBatch matrices per launch,
+// described in the kernel argument; a workgroup takes one 64 x 64 tile of one of them (found by bisection over the
+// matrices' first tiles), writes it and, through LDS, its transpose, both in whole row pieces.  One launch per matrix wrote the
+// transposes two bytes at a time and took 102 us
+// for the 28 matrices of two 1B layers; 17 us so.
 template <typename T>
-__global__ void lora_prep_kernel(const float* __restrict__ in, int rows, int cols, int rows_pad, int cols_pad,
-                                 float scale, T* __restrict__ out, int64_t ldo, T* __restrict__ out_t, int64_t ldo_t) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)rows_pad * cols_pad) return;
-  int r = idx / cols_pad, c = idx % cols_pad;
-  float v = (r < rows && c < cols) ? scale * in[(int64_t)r * cols + c] : 0.f;
-  if (out) out[(int64_t)r * ldo + c] = from_f<T>(v);
-  if (out_t) out_t[(int64_t)c * ldo_t + r] = from_f<T>(v);
+__global__ __launch_bounds__(256) void lora_prep_kernel(const PrepBatch b) {
+  __shared__ float tile[64][65];
+  int mi = 0, hi = b.n - 1;
+  while (mi < hi) { const int mid = (mi + hi + 1) >> 1; if ((int)blockIdx.x >= b.m[mid].first_tile) mi = mid; else hi = mid - 1; }
+  const PrepMatrix& m = b.m[mi];
+  const int tiles_c = (m.cols_pad + 63) / 64, t = (int)blockIdx.x - m.first_tile;
+  const int r0 = (t / tiles_c) * 64, c0 = (t % tiles_c) * 64;
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  T* out = (T*)m.out; T* out_t = (T*)m.out_t;
+#pragma unroll
+  for (int i = 0; i < 16; i++) {
+    const int r = r0 + ty + 4 * i, c = c0 + tx;
+    tile[ty + 4 * i][tx] = (r < m.rows && c < m.cols) ? m.scale * m.in[(int64_t)r * m.cols + c] : 0.f;
+  }
+#pragma unroll
+  for (int i = 0; i < 16; i++) {
+    const int r = r0 + ty + 4 * i, c = c0 + tx;
+    if (r < m.rows_pad && c < m.cols_pad) out[(int64_t)r * m.ldo + c] = from_f<T>(tile[ty + 4 * i][tx]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 16; i++) {
+    const int c = c0 + ty + 4 * i, r = r0 + tx;
+    if (r < m.rows_pad && c < m.cols_pad) out_t[(int64_t)c * m.ldo_t + r] = from_f<T>(tile[tx][ty + 4 * i]);
+  }
 }
 
-int launch_lora_prep2(as_ctx* ctx, int mode, const float* in, int rows, int cols, int rows_pad, int cols_pad,
-                      float scale, void* out, int64_t ldo, void* out_t, int64_t ldo_t, hipStream_t st) {
-  int64_t tot = (int64_t)rows_pad * cols_pad;
-  if (tot <= 0) return AS_OK;
-  DISPATCH_T(mode, (lora_prep_kernel<T><<<cdiv(tot, 256), 256, 0, st>>>(in, rows, cols, rows_pad, cols_pad, scale,
-                                                                        (T*)out, ldo, (T*)out_t, ldo_t)));
+int launch_lora_prep_batch(as_ctx* ctx, int mode, const PrepBatch& b, hipStream_t st) {
+  if (b.n <= 0 || b.n_tiles <= 0) return AS_OK;
+  DISPATCH_T(mode, (lora_prep_kernel<T><<<b.n_tiles, 256, 0, st>>>(b)));
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }

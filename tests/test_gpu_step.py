@@ -201,3 +201,13 @@ def test_wide_ffn_step_runs_the_hand_scheduled_gemm(row_len):
     ctx.profile(False)
     assert float(out["loss"].item()) == a["loss"] == rep["loss"]
     assert prof["gemm_mfma_rs"][0] >= 4, prof["gemm_mfma_rs"]                 # 2 layers x (gate | up in one launch, dX of down)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_more_adapter_matrices_than_one_preparation_launch(bf16):
+    """4 layers x 7 adapters are 56 matrices, prepared 48 per launch; widths that are no multiple of the 64 x 64 tiles."""
+    import gpu_util as G
+    sh = synth.CONFIGS[1].replace(n_layers=4, n_q_heads=2, n_kv_heads=1, head_dim=32, d_model=72, ffn=136, vocab=128,
+                                  lora_targets=synth.DENSE_TARGETS7, lora_rank=5, lora_alpha=10.0)
+    trajs = random_trajs(12, 4, sh.vocab, turn_lo=8, turn_hi=20, turns=(2, 4))
+    G.compare_step(sh, 8, trajs, 1, 256, bf16=bf16, loss_tol=2e-3 if bf16 else 1e-4, grad_tol=3e-2 if bf16 else 1e-4)
