@@ -50,50 +50,81 @@ __device__ __forceinline__ void store_out(const GemmParams& p, int z, int row, i
 }
 
 // ------------------------------------------------------------- plain kernel
-template <typename T>
+// float FMAs, every product of an output in ascending order of k.  Tiles of BT x BT with 16 x 16 threads, rows in LDS with k
+// contiguous, so that a thread reads four k of a row at a time; the next K step's elements are on their way from memory
+// while this one is multiplied.  The fp32 tier's products are small and bound by latency, by the length of the chain load ->
+// LDS -> multiply per K step: 64-wide steps and 32 x 32 tiles while those do not fill the chip, 64 x 64 tiles beyond that.
+// The products of a 2-layer model of width 128 at 469 tokens: 28 us each with 64 x 64 tiles, 16-wide steps and nothing in
+// flight, 9.4 us so.
+template <typename T, int BT, int BK>
 __global__ __launch_bounds__(256) void gemm_fma_kernel(GemmParams p, int m_off) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float As[BK][BM + 4];
-  __shared__ float Bs[BK][BN + 4];
+  constexpr int TT = BT / 16, LS = BK + 4, PER = BT * BK / 4 / 256;      // outputs per thread and side; groups of four elements a thread loads
+  static_assert(BT * BK / 4 % 256 == 0 && BK % 4 == 0, "whole groups per thread");
+  __shared__ __align__(16) float As[BT][LS];
+  __shared__ __align__(16) float Bs[BT][LS];
   int rb, mmax;
-  int M = gemm_rows(p, m_off, rb, mmax);
-  int row0 = blockIdx.y * BM, col0 = blockIdx.x * BN, z = blockIdx.z;
+  const int M = gemm_rows(p, m_off, rb, mmax);
+  const int row0 = blockIdx.y * BT, col0 = blockIdx.x * BT, z = blockIdx.z;
   if (row0 >= M) return;
-  int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-  float acc[4][4] = {};
-  int lr = tid / 4, lk = (tid % 4) * 4;                 // loader: one row, 4 consecutive k
+  const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
+  float acc[TT][TT] = {};
+  f32x4 ra[PER], rbv[PER];
   for (int s = 0; s < p.nseg; s++) {
     const T* A = (const T*)p.seg[s].A; const T* B = (const T*)p.seg[s].B;
-    int64_t lda = p.seg[s].lda, ldb = p.seg[s].ldb; int K = p.seg[s].K;
-    KRange kr = split_range(K, BK, p.splitk, z);
+    const int64_t lda = p.seg[s].lda, ldb = p.seg[s].ldb; const int K = p.seg[s].K;
+    if (p.ncg > 0) {                                     // which weight matrix this column tile belongs to (column groups are whole tiles wide)
+      int g = 0;
+      while (g + 1 < p.ncg && col0 >= p.cg_end[g]) g++;
+      B = (const T*)(s ? p.cg_B2[g] : p.cg_B1[g]) - (g ? (int64_t)p.cg_end[g - 1] * ldb : 0);
+      if (s) A += p.cg_a2[g];
+    }
+    const bool va = sizeof(T) == 4 && lda % 4 == 0 && (uintptr_t)A % 16 == 0, vb = sizeof(T) == 4 && ldb % 4 == 0 && (uintptr_t)B % 16 == 0;
+    const KRange kr = split_range(K, BK, p.splitk, z);
+    auto four = [&](const T* row, bool row_in, int k, bool vec) {
+      f32x4 v = {0.f, 0.f, 0.f, 0.f};
+      if (!row_in || k >= K) return v;
+      if (vec && k + 4 <= K) return *reinterpret_cast<const f32x4*>((const float*)row + k);
+#pragma unroll
+      for (int q = 0; q < 4; q++) if (k + q < K) v[q] = to_f<T>(row[k + q]);
+      return v;
+    };
+    auto fetch = [&](int kt) {
+#pragma unroll
+      for (int i = 0; i < PER; i++) {
+        const int g = tid + i * 256, r = g / (BK / 4), k = kt * BK + (g % (BK / 4)) * 4;
+        ra[i] = four(A + (int64_t)(rb + row0 + r) * lda, row0 + r < M, k, va);
+        rbv[i] = four(B + (int64_t)(col0 + r) * ldb, col0 + r < p.N, k, vb);
+      }
+    };
+    if (kr.beg < kr.end) fetch(kr.beg);
     for (int kt = kr.beg; kt < kr.end; kt++) {
-      int k0 = kt * BK;
+      __syncthreads();                                   // the step before has been read
 #pragma unroll
-      for (int q = 0; q < 4; q++) {
-        int k = k0 + lk + q;
-        int ar = row0 + lr, br = col0 + lr;
-        As[lk + q][lr] = (ar < M && k < K) ? to_f<T>(A[(int64_t)(rb + ar) * lda + k]) : 0.f;
-        Bs[lk + q][lr] = (br < p.N && k < K) ? to_f<T>(B[(int64_t)br * ldb + k]) : 0.f;
+      for (int i = 0; i < PER; i++) {
+        const int g = tid + i * 256, r = g / (BK / 4), k = (g % (BK / 4)) * 4;
+        *reinterpret_cast<f32x4*>(&As[r][k]) = ra[i]; *reinterpret_cast<f32x4*>(&Bs[r][k]) = rbv[i];
       }
       __syncthreads();
+      if (kt + 1 < kr.end) fetch(kt + 1);
+#pragma unroll 4
+      for (int k = 0; k < BK; k += 4) {
+        f32x4 a[TT], b[TT];
 #pragma unroll
-      for (int k = 0; k < BK; k++) {
-        float a[4], b[4];
+        for (int i = 0; i < TT; i++) { a[i] = *reinterpret_cast<const f32x4*>(&As[ty + 16 * i][k]); b[i] = *reinterpret_cast<const f32x4*>(&Bs[tx + 16 * i][k]); }
 #pragma unroll
-        for (int i = 0; i < 4; i++) { a[i] = As[k][ty * 4 + i]; b[i] = Bs[k][tx * 4 + i]; }
+        for (int q = 0; q < 4; q++)
 #pragma unroll
-        for (int i = 0; i < 4; i++)
+          for (int i = 0; i < TT; i++)
 #pragma unroll
-          for (int j = 0; j < 4; j++) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+            for (int j = 0; j < TT; j++) acc[i][j] = fmaf(a[i][q], b[j][q], acc[i][j]);
       }
-      __syncthreads();
     }
   }
 #pragma unroll
-  for (int i = 0; i < 4; i++)
+  for (int i = 0; i < TT; i++)
 #pragma unroll
-    for (int j = 0; j < 4; j++) {
-      int r = row0 + ty * 4 + i, c = col0 + tx * 4 + j;
+    for (int j = 0; j < TT; j++) {
+      const int r = row0 + ty + 16 * i, c = col0 + tx + 16 * j;
       if (r < M && c < p.N) store_out<T>(p, z, r, c, acc[i][j], rb);
     }
 }
@@ -1023,6 +1054,7 @@ static bool rs_ok(const GemmParams& p) {
 
 static bool rs_live(const GemmParams& p) { return p.m_dev || p.grp_off; }
 constexpr int kCus = 256;
+static int fma_tile(const GemmParams& p) { return cdiv(p.N, 64) * cdiv(p.M, 64) * p.splitk >= kCus ? 64 : 32; }
 static int k_steps(const GemmParams& p) { return (int)(p.seg[0].K / 64) + (p.nseg > 1 ? (int)(p.seg[1].K / 64) : 0); }
 // The tiles of a last partial round are split in two when that round would leave at least half of the CUs idle, the launch
 // has full rounds before it and the contraction is long enough to be worth a second small launch: a launch of 3696 tiles
@@ -1228,6 +1260,10 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
     const int width = c == 24 ? 256 : c == 25 ? 128 : 64;
     bool fused = mode == AS_BF16 && variant != 1 && mfma_ok(p) && ((c == 24 && rs_ok(p)) || c == 25 || c == 26);
     for (int g = 0; g < p.ncg && fused; g++) fused = p.cg_end[g] % width == 0 && !((uintptr_t)p.cg_B1[g] % 16) && (p.nseg < 2 || !((uintptr_t)p.cg_B2[g] % 16));
+    if (mode == AS_FP32) {
+      fused = true;
+      for (int g = 0; g < p.ncg; g++) fused = fused && p.cg_end[g] % fma_tile(p) == 0;
+    }
     if (!fused) {                                        // one launch per group
       const size_t esz = mode == AS_BF16 ? 2 : 4;
       for (int g = 0, c0 = 0; g < p.ncg; c0 = p.cg_end[g], g++) {
@@ -1271,9 +1307,12 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
       default: rc = launch_mfma_cfg<256, 256, 2, 4>(ctx, p, m_off, st); break;
     }
   } else {
-    dim3 grid((unsigned)cdiv(p.N, 64), (unsigned)cdiv(p.M, 64), (unsigned)p.splitk);
-    if (mode == AS_FP32) gemm_fma_kernel<float><<<grid, 256, 0, st>>>(p, m_off);
-    else gemm_fma_kernel<bf16_t><<<grid, 256, 0, st>>>(p, m_off);
+    const int bt = fma_tile(p);
+    const bool big = bt == 64;
+    dim3 grid((unsigned)cdiv(p.N, bt), (unsigned)cdiv(p.M, bt), (unsigned)p.splitk);
+    if (mode == AS_FP32) { if (big) gemm_fma_kernel<float, 64, 32><<<grid, 256, 0, st>>>(p, m_off); else gemm_fma_kernel<float, 32, 64><<<grid, 256, 0, st>>>(p, m_off); }
+    else if (big) gemm_fma_kernel<bf16_t, 64, 32><<<grid, 256, 0, st>>>(p, m_off);
+    else gemm_fma_kernel<bf16_t, 32, 64><<<grid, 256, 0, st>>>(p, m_off);
     AS_LAUNCH_CHECK(ctx);
   }
   prof_end(ctx, st);
