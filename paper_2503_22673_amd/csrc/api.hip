@@ -417,6 +417,7 @@ static void make_plan(const as_ctx* ctx, int64_t rows, int64_t row_len, Bump& w,
         int r = c.lora_rank;
         part = std::max(part, (size_t)pick_splitk(c.mode, s.dout, r, P.N) * s.dout * r);
         part = std::max(part, (size_t)pick_splitk(c.mode, r, s.din, P.N) * r * s.din);
+        if (c.mode == AS_FP32) part = std::max(part, plain_grad_partial_floats(P.N, (int64_t)2 * (P.QKV + 3 * P.d) + 2 * (2 * P.F + 2 * P.d), r));   // no group of products has more columns
         if (c.mode == AS_BF16 && r <= 64) {
           part = std::max(part, lora_grad_tn_partial_floats(P.N, s.dout, r));
           part = std::max(part, lora_grad_tn_partial_floats(P.N, s.din, r));
@@ -660,8 +661,8 @@ struct Step {
         if ((rc = transpose_tok(E, P.dlogit, E, P.dyT))) return rc;
         if ((rc = transpose_tok(d, a.b, d, P.xT))) return rc;
       }
-      if ((rc = transpose_pair(rp, a.u_r, P.du_r, P.uT, P.duT))) return rc;
-      if ((rc = lora_grads(l, AS_T_ROUTER, P.dlogit, E, a.b, d, P.dyT, P.xT))) return rc;
+      if ((rc = lora_tok(rp, a.u_r, P.du_r))) return rc;
+      if ((rc = lora_grads(l, AS_T_ROUTER, P.dlogit, E, a.b, d, a.u_r, P.du_r, rp, P.dyT, P.xT)) || (rc = lora_flush())) return rc;
     }
     return AS_OK;
   }
@@ -719,21 +720,34 @@ struct Step {
     return launch_transpose(ctx, mode, P.N, P.Np, cols, in, ldi, out, P.Np, nullptr, 0, st);
   }
 
-  // the same for the adapter activations u and their gradients du, which have one shape
-  int transpose_pair(int cols, const void* u, const void* du, void* uT, void* duT) {
-    return launch_transpose_pair(ctx, mode, P.N, P.Np, cols, u, du, cols, uT, duT, P.Np, st);
-  }
-
   // adapter gradients of one projection: dB = s dy^T u, dA = du^T x.  bf16 with rank <= 64: one
   // streaming pass over dy and over x (row-major, as they are) against the token-major copies of u
-  // and du.  Otherwise: GEMMs on the token-major copies dyT [dout, Np], xT [din, Np].
-  bool tn_path() const { return mode == AS_BF16 && c.lora_rank <= 64; }
-  int lora_grads(int l, int t, const void* dy, int64_t lddy, const void* x, int64_t ldx, const void* dyT_rows, const void* xT) {
+  // and du (uT, duT: lora_tok).  fp32: gathered, and launched for the whole group by lora_flush.  Otherwise: GEMMs on the
+  // token-major copies dyT [dout, Np], xT [din, Np].
+  bool tn_path() const { return mode == AS_FP32 || c.lora_rank <= 64; }
+  // token-major copies of a group's u and du (bf16)
+  int lora_tok(int cols, const void* u, const void* du) {
+    if (mode == AS_FP32) return AS_OK;
+    return launch_transpose_pair(ctx, mode, P.N, P.Np, cols, u, du, cols, P.uT, P.duT, P.Np, st);
+  }
+  PlainGradBatch pg{};
+  int lora_flush() {
+    const int rc = launch_plain_grads(ctx, pg, P.N, c.lora_rank, P.partial, P.partial_floats, st);
+    pg.n = 0;
+    return rc;
+  }
+  int lora_grads(int l, int t, const void* dy, int64_t lddy, const void* x, int64_t ldx, const void* u, const void* du, int64_t ldu,
+                 const void* dyT_rows, const void* xT) {
     LoraSlot& s = slot(l, t);
     if (!s.on) return AS_OK;
     const int Np = P.Np, r = c.lora_rank, rp = P.rp;
     const float sc = c.lora_alpha / (float)c.lora_rank;
     const as_layer_lora_grads& g = G->lora_layers[l];
+    if (mode == AS_FP32) {
+      pg.m[pg.n++] = {(const float*)dy, (const float*)u + (size_t)s.slot * rp, lddy, ldu, g.b[t], r, 1, 0, s.dout, 0, sc};
+      pg.m[pg.n++] = {(const float*)x, (const float*)du + (size_t)s.slot * rp, ldx, ldu, g.a[t], 1, s.din, 0, s.din, 0, 1.f};
+      return AS_OK;
+    }
     const void* uT = off(P.uT, (size_t)s.slot * rp * Np);
     const void* duT = off(P.duT, (size_t)s.slot * rp * Np);
     if (tn_path()) {
@@ -778,8 +792,8 @@ struct Step {
         if ((rc = transpose_tok(F, a.m, F, P.xT))) return rc;
       }
       if (s.on) {
-        if ((rc = transpose_pair(rp, a.u_d, P.du_d, P.uT, P.duT))) return rc;
-        if ((rc = lora_grads(l, AS_T_DOWN, P.dh, d, a.m, F, P.dyT, P.xT))) return rc;
+        if ((rc = lora_tok(rp, a.u_d, P.du_d))) return rc;
+        if ((rc = lora_grads(l, AS_T_DOWN, P.dh, d, a.m, F, a.u_d, P.du_d, rp, P.dyT, P.xT)) || (rc = lora_flush())) return rc;
       }
       if (full && (rc = weight_grad(G->w_layers[l].wdown, d, F, P.dyT, P.xT))) return rc; }
     // ---- gate / up projections
@@ -799,9 +813,10 @@ struct Step {
         if ((rc = transpose_tok(d, a.b, d, P.xT))) return rc;
       }
       if (P.n_gu) {
-        if ((rc = transpose_pair(ldg, a.u_gu, P.du_gu, P.uT, P.duT))) return rc;
+        if ((rc = lora_tok(ldg, a.u_gu, P.du_gu))) return rc;
         for (int i = 0; i < 2; i++)
-          if ((rc = lora_grads(l, AS_T_GATE + i, off(P.dgu, (size_t)i * F), 2 * F, a.b, d, off(P.dyT, (size_t)i * F * P.Np), P.xT))) return rc;
+          if ((rc = lora_grads(l, AS_T_GATE + i, off(P.dgu, (size_t)i * F), 2 * F, a.b, d, a.u_gu, P.du_gu, ldg, off(P.dyT, (size_t)i * F * P.Np), P.xT))) return rc;
+        if ((rc = lora_flush())) return rc;
       }
       if (full) {
         if ((rc = weight_grad(G->w_layers[l].wgate, F, d, P.dyT, P.xT))) return rc;
@@ -821,8 +836,8 @@ struct Step {
         if ((rc = transpose_tok(D, a.o, D, P.xT))) return rc;
       }
       if (s.on) {
-        if ((rc = transpose_pair(rp, a.u_o, P.du_o, P.uT, P.duT))) return rc;
-        if ((rc = lora_grads(l, AS_T_O, P.dh2, d, a.o, D, P.dyT, P.xT))) return rc;
+        if ((rc = lora_tok(rp, a.u_o, P.du_o))) return rc;
+        if ((rc = lora_grads(l, AS_T_O, P.dh2, d, a.o, D, a.u_o, P.du_o, rp, P.dyT, P.xT)) || (rc = lora_flush())) return rc;
       }
       if (full && (rc = weight_grad(G->w_layers[l].wo, d, D, P.dyT, P.xT))) return rc; }
     // ---- attention
@@ -856,9 +871,10 @@ struct Step {
         if ((rc = transpose_tok(d, a.a, d, P.xT))) return rc;
       }
       if (P.n_qkv) {
-        if ((rc = transpose_pair(ldu, a.u_qkv, P.du_qkv, P.uT, P.duT))) return rc;
+        if ((rc = lora_tok(ldu, a.u_qkv, P.du_qkv))) return rc;
         for (int i = 0; i < 3; i++)
-          if ((rc = lora_grads(l, i, off(P.dqkv, coff[i]), QKV, a.a, d, off(P.dyT, (size_t)coff[i] * P.Np), P.xT))) return rc;
+          if ((rc = lora_grads(l, i, off(P.dqkv, coff[i]), QKV, a.a, d, a.u_qkv, P.du_qkv, ldu, off(P.dyT, (size_t)coff[i] * P.Np), P.xT))) return rc;
+        if ((rc = lora_flush())) return rc;
       }
       if (full) {
         float* gw[3] = {G->w_layers[l].wq, G->w_layers[l].wk, G->w_layers[l].wv};

@@ -126,6 +126,13 @@ size_t lora_grad_tn_partial_floats(int n, int M, int r);
 int launch_lora_grad_tn(as_ctx* ctx, const void* X, int64_t ldx, const void* UT, int64_t ldu, int n, int M, int r,
                         float alpha, float* C, int64_t sm, int64_t sj, float* partial, size_t partial_floats, hipStream_t st);
 
+// fp32 tier: C[m*sm + j*sj] = alpha * sum_t X[t, m] * U[t, j] for up to eight products of one rank r over the same n tokens; U
+// rows hold r rounded up to 16 columns
+struct PlainGrad { const float *X, *U; int64_t ldx, ldu; float* C; int64_t sm, sj, first_out; int M, first_block; float alpha; };
+struct PlainGradBatch { PlainGrad m[8]; int n; int64_t total; };
+size_t plain_grad_partial_floats(int n, int64_t cols, int r);      // cols: sum of M over the batch
+int launch_plain_grads(as_ctx* ctx, PlainGradBatch b, int n, int r, float* partial, size_t partial_floats, hipStream_t st);
+
 // ---- attention (attention.hip) -----------------------------------------------
 struct AttnParams {
   int n, Hq, Hkv, dh;

@@ -171,3 +171,84 @@ int launch_lora_grad_tn(as_ctx* ctx, const void* X, int64_t ldx, const void* UT,
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }
+
+// ---- fp32 tier -------------------------------------------------------------------------------------------------------
+// The same products with float operands, all those of one input group in one launch (a projection's dB and dA; the six of
+// q, k, v), X and U read as they are.  A workgroup owns 64 columns of one X and 16 columns of its U; its 16 waves take every
+// 16th token each, a lane one column of X (coalesced), U's values are the same for the whole wave (scalar loads), and the waves
+// are added in order through LDS.  More than 1024 tokens are split over grid.y, partial sums added in order by a second launch.
+// Bound by latency at the tier's sizes: as token-major copies of both operands, split-K products and their sums, two
+// layers of four adapters at 469 tokens took about 630 us in 56 launches; 44 us in 4 so.
+constexpr int PG_WAVES = 16, PG_J = 16;
+__global__ __launch_bounds__(PG_WAVES * 64) void plain_grad_kernel(const PlainGradBatch b, int n, int r, int splits, float* __restrict__ partial) {
+  __shared__ float sh[PG_WAVES][64][PG_J / 4 + 1];         // four of the sixteen columns at a time
+  int it = 0;
+  while (it + 1 < b.n && (int)blockIdx.x >= b.m[it + 1].first_block) it++;
+  const PlainGrad& m = b.m[it];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nj = (r + PG_J - 1) / PG_J, blk = (int)blockIdx.x - m.first_block, col = (blk / nj) * 64 + lane, j0 = (blk % nj) * PG_J;
+  const int per = (n + splits - 1) / splits, t_lo = blockIdx.y * per, t_hi = min(n, t_lo + per);
+  const float* X = m.X + (col < m.M ? col : 0); const float* U = m.U + j0;
+  float acc[PG_J];
+#pragma unroll
+  for (int j = 0; j < PG_J; j++) acc[j] = 0.f;
+#pragma unroll 4
+  for (int t = t_lo + wave; t < t_hi; t += PG_WAVES) {
+    const float x = X[(int64_t)t * m.ldx];
+    const float* u = U + (int64_t)t * m.ldu;
+#pragma unroll
+    for (int j = 0; j < PG_J; j++) acc[j] = fmaf(x, u[j], acc[j]);
+  }
+  // wave w adds column quad q = w (four quads) over the waves; element (column, j) leaves through the thread that added it
+#pragma unroll
+  for (int q = 0; q < PG_J / 4; q++) {
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; k++) sh[wave][lane][k] = acc[4 * q + k];
+    __syncthreads();
+    if (wave < 4) {                                        // wave k of four: column j0 + 4 q + k
+      float s = 0.f;
+#pragma unroll
+      for (int w = 0; w < PG_WAVES; w++) s += sh[w][lane][wave];
+      const int j = j0 + 4 * q + wave;
+      if (col < m.M && j < r) {
+        if (splits > 1) partial[(int64_t)blockIdx.y * b.total + m.first_out + (int64_t)col * r + j] = s;
+        else m.C[(int64_t)col * m.sm + (int64_t)j * m.sj] = m.alpha * s;
+      }
+    }
+  }
+}
+__global__ __launch_bounds__(256) void plain_grad_sum_kernel(const PlainGradBatch b, int r, int splits, const float* __restrict__ partial) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= b.total) return;
+  int it = 0;
+  while (it + 1 < b.n && i >= b.m[it + 1].first_out) it++;
+  const PlainGrad& m = b.m[it];
+  float s = 0.f;
+#pragma unroll 8
+  for (int k = 0; k < splits; k++) s += partial[(int64_t)k * b.total + i];
+  const int64_t e = i - m.first_out;
+  m.C[(e / r) * m.sm + (e % r) * m.sj] = m.alpha * s;
+}
+
+static int plain_grad_splits(int n) { return (int)std::min<int64_t>(32, cdiv(std::max(n, 1), 1024)); }
+size_t plain_grad_partial_floats(int n, int64_t cols, int r) { return n > 1024 ? (size_t)plain_grad_splits(n) * cols * r : 0; }
+
+int launch_plain_grads(as_ctx* ctx, PlainGradBatch b, int n, int r, float* partial, size_t partial_floats, hipStream_t st) {
+  if (n <= 0 || b.n <= 0 || r <= 0) return AS_OK;
+  const int nj = (int)cdiv(r, PG_J);
+  int64_t blocks = 0; b.total = 0;
+  for (int i = 0; i < b.n; i++) {
+    b.m[i].first_block = (int)blocks; b.m[i].first_out = b.total;
+    blocks += cdiv(b.m[i].M, 64) * nj; b.total += (int64_t)b.m[i].M * r;
+  }
+  const int splits = plain_grad_splits(n);
+  if (splits > 1 && (size_t)splits * b.total > partial_floats) return as_fail(ctx, AS_ERR_WORKSPACE, "adapter gradients: partial buffer too small");
+  prof_begin(ctx, st, AS_K_LORA_GRAD, 2.0 * n * (double)b.total);
+  plain_grad_kernel<<<dim3((unsigned)blocks, splits), PG_WAVES * 64, 0, st>>>(b, n, r, splits, partial);
+  AS_LAUNCH_CHECK(ctx);
+  if (splits > 1) plain_grad_sum_kernel<<<(unsigned)cdiv(b.total, 256), 256, 0, st>>>(b, r, splits, partial);
+  prof_end(ctx, st);
+  AS_LAUNCH_CHECK(ctx);
+  return AS_OK;
+}
