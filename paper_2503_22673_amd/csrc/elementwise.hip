@@ -600,27 +600,32 @@ int launch_swiglu_bwd(as_ctx* ctx, int mode, int64_t n, int F, const void* dm, c
 }
 
 // --------------------------------------------------------------- transpose
-// out[c, r] = in[r, c] through a padded 64x64 LDS tile; rows past the
+// out[c, r] = in[r, c] through a padded LDS tile; rows past the
 // device-side row count (if given) read as zero.
 // QS: inside every group of 16 output positions the two middle quads are exchanged (position order
 // 0-3, 8-11, 4-7, 12-15 of the source rows), which is the order one lane half of a 32x32x16 MFMA
 // holds its 8 contraction indices in: such a fragment is then one 16-byte read.
+// 32 x 32 tiles, four elements per thread in flight: what comes here is small (fp32 tier) or oddly shaped.
 template <typename T, bool QS>
-__global__ void transpose_kernel(int rows, int rows_pad, int cols, const T* __restrict__ in, int64_t ldi,
-                                 T* __restrict__ out, int64_t ldo, const int* __restrict__ rows_dev, int row_off) {
-  __shared__ T tile[64][65];
-  int live = rows_dev ? min(rows, *rows_dev - row_off) : rows;
-  int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-  int tx = threadIdx.x % 64, ty = threadIdx.x / 64;       // 256 threads: 4 rows at a time
-  for (int i = ty; i < 64; i += 4) {
-    int r = r0 + i, c = c0 + tx;
-    tile[i][tx] = (r < live && c < cols) ? in[(int64_t)r * ldi + c] : from_f<T>(0.f);
+__global__ __launch_bounds__(256) void transpose_kernel(int rows, int rows_pad, int cols, const T* __restrict__ in, int64_t ldi,
+                                                        T* __restrict__ out, int64_t ldo, const int* __restrict__ rows_dev, int row_off) {
+  __shared__ T tile[32][33];
+  const int live = rows_dev ? min(rows, *rows_dev - row_off) : rows;
+  const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32, tx = threadIdx.x % 32, ty = threadIdx.x / 32;
+  T v[4];
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    const int r = r0 + ty + 8 * i, c = c0 + tx;
+    v[i] = (r < live && c < cols) ? in[(int64_t)r * ldi + c] : from_f<T>(0.f);
   }
+#pragma unroll
+  for (int i = 0; i < 4; i++) tile[ty + 8 * i][tx] = v[i];
   __syncthreads();
-  for (int i = ty; i < 64; i += 4) {
-    int c = c0 + i, r = r0 + tx;
-    const int src = QS ? ((tx & ~12) | ((tx & 4) << 1) | ((tx & 8) >> 1)) : tx;
-    if (c < cols && r < rows_pad) out[(int64_t)c * ldo + r] = tile[src][i];
+  const int src = QS ? ((tx & ~12) | ((tx & 4) << 1) | ((tx & 8) >> 1)) : tx;
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    const int c = c0 + ty + 8 * i, r = r0 + tx;
+    if (c < cols && r < rows_pad) out[(int64_t)c * ldo + r] = tile[src][ty + 8 * i];
   }
 }
 
@@ -674,7 +679,7 @@ static bool transpose_vec_ok(int mode, int rows_pad, int cols, const void* in, i
 int launch_transpose(as_ctx* ctx, int mode, int rows, int rows_pad, int cols, const void* in, int64_t ldi, void* out,
                      int64_t ldo, const int* rows_dev, int row_off, hipStream_t st) {
   if (rows <= 0 || cols <= 0) return AS_OK;
-  dim3 grid(cdiv(cols, 64), cdiv(rows_pad, 64));
+  dim3 grid(cdiv(cols, 32), cdiv(rows_pad, 32));
   prof_begin(ctx, st, AS_K_TRANSPOSE, 0.0);
   if (transpose_vec_ok(mode, rows_pad, cols, in, ldi, out, ldo))
     transpose_vec_kernel<false><<<dim3((unsigned)cdiv(cols, 64), (unsigned)cdiv(rows_pad, 256)), 256, 0, st>>>(rows, rows_pad, cols, (const bf16_t*)in, ldi, (bf16_t*)out, ldo, rows_dev, row_off, nullptr, nullptr);
@@ -705,7 +710,7 @@ int launch_transpose_qs(as_ctx* ctx, int mode, int rows, int rows_pad, int cols,
                         int64_t ldo, hipStream_t st) {
   if (rows <= 0 || cols <= 0) return AS_OK;
   if (rows_pad % 16) return as_fail(ctx, AS_ERR_SHAPE, "transpose: the quad-swapped layout needs a row count padded to 16");
-  dim3 grid(cdiv(cols, 64), cdiv(rows_pad, 64));
+  dim3 grid(cdiv(cols, 32), cdiv(rows_pad, 32));
   prof_begin(ctx, st, AS_K_TRANSPOSE, 0.0);
   if (transpose_vec_ok(mode, rows_pad, cols, in, ldi, out, ldo))
     transpose_vec_kernel<true><<<dim3((unsigned)cdiv(cols, 64), (unsigned)cdiv(rows_pad, 256)), 256, 0, st>>>(rows, rows_pad, cols, (const bf16_t*)in, ldi, (bf16_t*)out, ldo, nullptr, 0, nullptr, nullptr);
