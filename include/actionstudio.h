@@ -383,12 +383,13 @@ int as_op_rmsnorm_bwd(as_ctx* ctx, int mode, int64_t n, int64_t d, const void* d
  * dense, lse float [n,Hq].  seg_start [n] int32: first token of each token's
  * segment.  variant: 0 = pick, 1 = plain kernel, 2 = MFMA kernels (bf16, head_dim 64 or 128); backward only:
  * 4 = the MFMA kernels that work from token-major copies, dK and dV in two launches with float partials per query
- * head.  Otherwise head_dim 64 takes the same kernels with dK and dV from one launch, and head_dim 128 with row
- * strides that are multiples of 128 elements the one-pass kernels that read their operands as they are.
+ * head.  Otherwise head_dim 64, and head_dim 128 with row strides that are multiples of 128 elements, take one-pass
+ * kernels that read their operands as they are.
  * t_scratch: type T, only read by the MFMA kernels (may be NULL otherwise):
  * room for Hkv*dh * n64 elements in forward and (6*Hq + Hkv)*dh * n64 in
  * backward, n64 = n rounded up to 64 (token-major copies of V, resp. K, Q, dO,
- * followed in backward by float dK / dV partials per query head; the one-pass kernels leave it untouched). */
+ * followed in backward by float dK / dV partials per query head; the one-pass kernels of head_dim 128 leave it
+ * untouched, those of head_dim 64 keep row statistics and the partials in it). */
 int as_op_attention_fwd(as_ctx* ctx, int mode, int variant, int64_t n, const int32_t* seg_start,
                         const void* q, int64_t ldq, const void* k, const void* v, int64_t ldkv,
                         void* o, float* lse, void* t_scratch, void* stream);

@@ -111,9 +111,14 @@ __device__ __forceinline__ void tile_to_lds(const bf16_t* base, int64_t ld, int 
 // group stream the same operand tiles, so a whole group is kept on one XCD: XCD x takes the groups x, x + 8, ...
 // one after the other, each in the order given (longest first).  Without a multiple of eight groups the
 // mapping falls back to group-major order.
+// INTERLEAVE: the groups of an XCD take turns instead, item by item, so that the longest items of all of them come first: one
+// order table serves every group, and with group after group the last groups' long items would start late.
+template <bool INTERLEAVE = false>
 __device__ inline void xcd_group_map(int wg, int per, int ngrp, int& group, int& item) {
-  if (ngrp % 8 == 0) { const int slot = wg >> 3; group = (slot / per) * 8 + (wg & 7); item = slot % per; }
-  else { group = wg / per; item = wg % per; }
+  if (ngrp % 8 == 0) {
+    const int slot = wg >> 3, mine = ngrp / 8;
+    group = (INTERLEAVE ? slot % mine : slot / per) * 8 + (wg & 7); item = INTERLEAVE ? slot / mine : slot % per;
+  } else { group = INTERLEAVE ? wg % ngrp : wg / per; item = INTERLEAVE ? wg / ngrp : wg % per; }
 }
 
 template <int DH, int HPW, int QB, int NWV>
@@ -461,8 +466,8 @@ template <int DH, int WHICH>
 __global__ __launch_bounds__(512) void attn_bwd_dkv2_mfma(AttnParams p, float scale, float sl2, float* __restrict__ part) {
   constexpr int KS = DH / 16, CB = DH / 32, NWV = 8, KPB = 32 * NWV;
   constexpr int KT_E = BKEY * DH;
-  constexpr bool DO_K = WHICH != 1, DO_V = WHICH != 0;    // WHICH 2: both gradients from one S (head_dim 64: the registers allow it)
-  constexpr int NT = (DO_K ? 3 : 1) + (DO_V ? 1 : 0);     // dK: Q, dO, Q^T tiles; dV: Q, dO^T tiles; both: Q, dO, Q^T, dO^T
+  constexpr bool DO_K = WHICH == 0;
+  constexpr int NT = DO_K ? 3 : 2;                         // dK: Q, dO, Q^T tiles; dV: Q, dO^T tiles
   constexpr int ST_E = NT * KT_E + 4 * BKEY;              // + 64 lse and 64 delta floats (2 bf16 slots each)
   extern __shared__ __align__(16) unsigned char dyn_smem[];
   bf16_t* sm = (bf16_t*)dyn_smem;
@@ -483,13 +488,9 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv2_mfma(AttnParams p, float sc
     kf[ks] = *reinterpret_cast<const bf16x8*>(K + (int64_t)uc * p.ldkv + g * DH + ks * 16 + h * 8);
     if constexpr (DO_K) vf[ks] = *reinterpret_cast<const bf16x8*>(V + (int64_t)uc * p.ldkv + g * DH + ks * 16 + h * 8);
   }
-  f32x16 acc[CB], acc2[WHICH == 2 ? CB : 1];                    // dK^T or dV^T, [dh rows, key lane]; both: dK^T and dV^T
+  f32x16 acc[CB];                                               // dK^T or dV^T, [dh rows, key lane]
 #pragma unroll
   for (int cb = 0; cb < CB; cb++) acc[cb] = zero16();
-  if constexpr (WHICH == 2) {
-#pragma unroll
-    for (int cb = 0; cb < CB; cb++) acc2[cb] = zero16();
-  }
   const int q_first = u_wg / BKEY;
   const int q_last = __builtin_amdgcn_readfirstlane((p.seg_end[min(u_wg + KPB - 1, n - 1)] - 1) / BKEY);
   // this wave's keys are visible from queries in [u_base, w_end); all of them from queries in [u_base + 31, w_end_min)
@@ -508,8 +509,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv2_mfma(AttnParams p, float sc
     if constexpr (DO_K) {
       tile_to_lds<BKEY, DH, NWV>(dO + jj * DH, (int64_t)p.Hq * DH, t0, n - 1, offD, d + KT_E, wave, lane);
       tile_to_lds_fast<DH, BKEY, NWV>(QTm + (int64_t)jj * DH * p.ldT + t0, offT, d + 2 * KT_E, wave);
-    }
-    if constexpr (DO_V) tile_to_lds_fast<DH, BKEY, NWV>(DOT + (int64_t)jj * DH * p.ldT + t0, offT, d + (NT - 1) * KT_E, wave);
+    } else tile_to_lds_fast<DH, BKEY, NWV>(DOT + (int64_t)jj * DH * p.ldT + t0, offT, d + (NT - 1) * KT_E, wave);
     if (wave < (DO_K ? 2 : 1)) {                           // 64 lse (wave 0) and 64 delta (wave 1) values, 4 bytes a lane
       const float* src = (wave == 0 ? p.lse : p.delta) + (int64_t)min(t0 + lane, n - 1) * p.Hq + jj;
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
@@ -528,7 +528,6 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv2_mfma(AttnParams p, float sc
     const bf16_t* sQ = sm + b * ST_E;
     const bf16_t* sdO = sQ + KT_E;                              // with dK only
     const bf16_t* sT = sQ + (DO_K ? 2 : 1) * KT_E;              // Q^T (dK) or dO^T (dV)
-    const bf16_t* sT2 = sQ + (NT - 1) * KT_E;                   // dO^T when both
     const float* sLse = (const float*)(sQ + NT * KT_E); const float* sDel = sLse + BKEY;
     f32x16 s[2], dp[DO_K ? 2 : 1];
     s[0] = zero16(); s[1] = zero16();
@@ -554,7 +553,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv2_mfma(AttnParams p, float sc
           s[qb][e] = (t >= u && t < uend) ? s[qb][e] : -INFINITY;
         }
     }
-    bf16x8 bop[4], bop2[WHICH == 2 ? 4 : 1];                    // dS (dK) or P (dV) as B operands; both: dS and P
+    bf16x8 bop[4];                                              // dS (dK) or P (dV) as B operands
 #pragma unroll
     for (int qb = 0; qb < 2; qb++) {
 #pragma unroll
@@ -567,14 +566,10 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv2_mfma(AttnParams p, float sc
         for (int i = 0; i < 4; i++) {
           const int e = b4 * 4 + i;
           const float pr = fast_exp2(fmaf(s[qb][e], sl2, -1.4426950408889634f * ls[i]));
-          if constexpr (WHICH == 2) { dp[qb][e] = pr * (dp[qb][e] - dl[i]); s[qb][e] = pr; }
-          else if constexpr (WHICH == 0) s[qb][e] = pr * (dp[qb][e] - dl[i]); else s[qb][e] = pr;
+          if constexpr (DO_K) s[qb][e] = pr * (dp[qb][e] - dl[i]); else s[qb][e] = pr;
         }
       }
-      if constexpr (WHICH == 2) {
-        bop[qb * 2] = pack8(dp[qb], 0); bop[qb * 2 + 1] = pack8(dp[qb], 1);
-        bop2[qb * 2] = pack8(s[qb], 0); bop2[qb * 2 + 1] = pack8(s[qb], 1);
-      } else { bop[qb * 2] = pack8(s[qb], 0); bop[qb * 2 + 1] = pack8(s[qb], 1); }
+      bop[qb * 2] = pack8(s[qb], 0); bop[qb * 2 + 1] = pack8(s[qb], 1);
     }
 #pragma unroll
     for (int x = 0; x < 4; x++)
@@ -582,32 +577,24 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv2_mfma(AttnParams p, float sc
       for (int cb = 0; cb < CB; cb++) {
         const bf16x8 a = *reinterpret_cast<const bf16x8*>(sT + (cb * 32 + l31) * BKEY + (((2 * x + h) ^ swT) * 8));
         acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bop[x], acc[cb], 0, 0, 0);
-        if constexpr (WHICH == 2) {
-          const bf16x8 a2 = *reinterpret_cast<const bf16x8*>(sT2 + (cb * 32 + l31) * BKEY + (((2 * x + h) ^ swT) * 8));
-          acc2[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, bop2[x], acc2[cb], 0, 0, 0);
-        }
       }
   }
   if (u >= n) return;
-  auto put = [&](const f32x16 (&r)[CB], int which) {
-    if (grp > 1) {
-      float* row = part + (((int64_t)which * p.Hq + jj) * n + u) * DH;
+  if (grp > 1) {
+    float* row = part + (((int64_t)WHICH * p.Hq + jj) * n + u) * DH;
 #pragma unroll
-      for (int cb = 0; cb < CB; cb++)
+    for (int cb = 0; cb < CB; cb++)
 #pragma unroll
-        for (int b4 = 0; b4 < 4; b4++) {
-          f32x4 w;
+      for (int b4 = 0; b4 < 4; b4++) {
+        f32x4 w;
 #pragma unroll
-          for (int i = 0; i < 4; i++) w[i] = r[cb][b4 * 4 + i];
-          *reinterpret_cast<f32x4*>(row + cb * 32 + 8 * b4 + 4 * h) = w;
-        }
-    } else {
-      bf16_t* row = (bf16_t*)(which == 0 ? p.dk : p.dv) + (int64_t)u * p.ldkv + g * DH;
-      store_grad_row<DH>(r, which == 0 ? scale : 1.f, row, h, which == 0 ? p.rope_cos : nullptr, p.rope_sin, u - p.seg_start[u]);
-    }
-  };
-  put(acc, WHICH == 1 ? 1 : 0);
-  if constexpr (WHICH == 2) put(acc2, 1);
+        for (int i = 0; i < 4; i++) w[i] = acc[cb][b4 * 4 + i];
+        *reinterpret_cast<f32x4*>(row + cb * 32 + 8 * b4 + 4 * h) = w;
+      }
+  } else {
+    bf16_t* row = (bf16_t*)(DO_K ? p.dk : p.dv) + (int64_t)u * p.ldkv + g * DH;
+    store_grad_row<DH>(acc, DO_K ? scale : 1.f, row, h, DO_K ? p.rope_cos : nullptr, p.rope_sin, u - p.seg_start[u]);
+  }
 }
 
 // dQ with one wave per SIMD (head_dim 128, four query heads per KV head): wave = 64 queries of one head (a lane owns two
@@ -840,6 +827,406 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv3_mfma(AttnParams p, float sc
   store_grad_row<DH>(accV, 1.f, (bf16_t*)p.dv + (int64_t)u * p.ldkv + g * DH, h, nullptr, p.rope_sin, pos);
 }
 
+// ------------------------------------------------------------------ head_dim 64
+// Tiles of 64 tokens x 64 columns sit in LDS once, row major (8 KB, 128-byte rows); the products that contract over tokens
+// read them through the transposing LDS loads, so there are no token-major copies.  LDS position of chunk c (16 bytes) of row r:
+// c ^ f(r), f = bits 1..3 of the row in reverse order: the 16 rows of a row read then hit every bank once, and so do the four
+// rows x 32 bytes of a transposing read (rows r and r + 2, which share their half of the banks, differ in the chunk pair).
+// At this head size the matrix work per exponential is half that of head_dim 128 (matrix pipes 48 %, vector pipes 44 % of the time
+// busy in dK / dV), and what eight-wave workgroups lose is time in which all their waves are in the same phase: behind the barrier all
+// issue the next tiles' loads, then all multiply, then all exponentiate.  Workgroups of four waves, three (dK / dV) or four to a
+// CU by their registers, overlap their phases; reading fragments ahead into registers costs a workgroup per CU and was slower
+// (dK / dV: 230 registers, 575 against 545 us of backward), and so was a third stage.  32 query heads on 8 KV heads, this and the
+// eight-wave kernels with token-major copies: forward 186 and 200 us (8191 tokens, longest segment 4096), 271 and 309
+// (30000, 2500), 22 and 26 (1003, 700); backward 523 and 694, 926 and 1217, 60 and 77 us.
+__device__ __forceinline__ int swz64(int row) { return ((row & 2) << 1) | ((row >> 1) & 2) | ((row >> 3) & 1); }
+constexpr int T64_E = 64 * 64;                            // elements of a tile
+
+// One wave of four: its quarter (16 rows) of a tile, two 1 KB loads.  voff: this lane's byte offsets of the two loads (tile64_offsets)
+__device__ __forceinline__ void tile64_offsets(int64_t ld, int wave, int lane, uint32_t (&voff)[2]) {
+#pragma unroll
+  for (int i = 0; i < 2; i++) { const int row = wave * 16 + i * 8 + (lane >> 3); voff[i] = (uint32_t)((row * ld + (((lane & 7) ^ swz64(row)) * 8)) * 2); }
+}
+__device__ __forceinline__ void tile64_to_lds(const bf16_t* base, int64_t ld, int row0, int row_max, const uint32_t (&voff)[2], bf16_t* s, int wave, int lane) {
+  if (row0 + 63 <= row_max) {
+    const char* b = (const char*)uniform_ptr(base + (int64_t)row0 * ld);
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(b + voff[i]),
+                                       (__attribute__((address_space(3))) void*)(s + (wave * 2 + i) * 512), 16, 0, 0);
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; i++) {                           // the last tile of the stream: rows past the end repeat the last one
+    const int row = wave * 16 + i * 8 + (lane >> 3);
+    const bf16_t* src = base + (int64_t)min(row0 + row, row_max) * ld + ((lane & 7) ^ swz64(row)) * 8;
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)(s + (wave * 2 + i) * 512), 16, 0, 0);
+  }
+}
+// row fragment: row 32 blk + lane % 32, columns 16 ks + 8 h .. + 7 (f(row) = f(lane % 32): 32 blk does not touch bits 1..3)
+__device__ __forceinline__ bf16x8 row64(const bf16_t* tile, int blk, int ks, int l31, int h, int f) {
+  return *reinterpret_cast<const bf16x8*>(tile + (blk * 32 + l31) * 64 + (((2 * ks + h) ^ f) * 8));
+}
+// column fragment: column 32 cb + lane % 32, rows 16 x + 4 h + 0..3 and 16 x + 8 + 4 h + 0..3 (the order in which a lane half
+// holds 16 accumulator rows).  A group of 16 lanes addresses a patch of 4 rows x 16 columns, 8 bytes per lane, and receives it
+// transposed.  corner: this lane's address for x = 0, cb = 0 (elements).
+struct Corner64 { int lo[2], hi[2]; };                    // per column block: rows .. + 3, rows + 8 .. + 11
+__device__ __forceinline__ Corner64 corner64(int lane) {
+  const int sl = lane & 15, mh = (lane >> 4) & 1, h = lane >> 5, row = 4 * h + (sl >> 2);
+  Corner64 c;
+#pragma unroll
+  for (int cb = 0; cb < 2; cb++) {
+    const int ch = cb * 4 + 2 * mh + ((sl & 3) >> 1);
+    c.lo[cb] = row * 64 + ((ch ^ swz64(row)) * 8) + (sl & 1) * 4;
+    c.hi[cb] = (row + 8) * 64 + ((ch ^ swz64(row + 8)) * 8) + (sl & 1) * 4;
+  }
+  return c;
+}
+__device__ __forceinline__ bf16x8 col64(const bf16_t* tile, const Corner64& c, int x, int cb) {
+  const bf16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4*)(tile + c.lo[cb] + x * 1024));
+  const bf16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4*)(tile + c.hi[cb] + x * 1024));
+  return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+// every lane of the wave has its part of the stage's loads in LDS, and then every wave has (and has read the stage before)
+__device__ __forceinline__ void stage_barrier() {
+  __builtin_amdgcn_s_waitcnt(0x0f70);
+  __syncthreads();
+}
+
+template <int HPW>
+__global__ __launch_bounds__(256, 4) void attn_fwd64_mfma(AttnParams p, float sl2) {
+  constexpr int DH = 64, KS = 4, CB = 2, QT = 32 * (4 / HPW);
+  extern __shared__ __align__(256) unsigned char dyn_smem[];
+  bf16_t* sm = (bf16_t*)dyn_smem;                         // [2 stages][K, V]
+  const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = p.n, grp = p.Hq / p.Hkv;
+  int hg, qi;
+  const int nqt = (n + 2 * QT - 1) / (2 * QT) * 2;         // the order table names tiles of 2 QT
+  xcd_group_map(blockIdx.x, nqt, p.Hq / HPW, hg, qi);
+  const int j = hg * HPW + (wave % HPW), g = j / grp;      // HPW divides the group: one KV head per workgroup
+  const int t_wg = (p.order_q ? p.order_q[qi >> 1] * 2 + 1 - (qi & 1) : nqt - 1 - qi) * QT;   // long rows first
+  if (t_wg >= n) return;
+  const int t_base = t_wg + (wave / HPW) * 32;
+  const bf16_t* Q = (const bf16_t*)p.q; const bf16_t* K = (const bf16_t*)p.k + g * DH; const bf16_t* V = (const bf16_t*)p.v + g * DH;
+  const int kv_first = __builtin_amdgcn_readfirstlane(p.seg_start[t_wg] / BKEY);
+  const int kv_last = min(t_wg + QT - 1, n - 1) / BKEY;
+  uint32_t voff[2];
+  tile64_offsets(p.ldkv, wave, lane, voff);
+  auto stage_k = [&](int kt, int b) { tile64_to_lds(K, p.ldkv, kt * BKEY, n - 1, voff, sm + b * 2 * T64_E, wave, lane); };
+  auto stage_v = [&](int kt, int b) { tile64_to_lds(V, p.ldkv, kt * BKEY, n - 1, voff, sm + b * 2 * T64_E + T64_E, wave, lane); };
+  stage_k(kv_first, 0); stage_v(kv_first, 0);              // the first tiles travel while the wave fetches its own rows
+  const int tq = t_base + l31, tc = min(tq, n - 1), ss = p.seg_start[tc];
+  bf16x8 qf[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ks++) qf[ks] = *reinterpret_cast<const bf16x8*>(Q + (int64_t)tc * p.ldq + j * DH + ks * 16 + h * 8);
+  const int ss_hi = __builtin_amdgcn_readfirstlane(p.seg_start[min(t_base + 31, n - 1)]);   // the latest segment start any query of this wave has
+  f32x16 o[CB];
+  float mref = -INFINITY, l = 0.f;
+#pragma unroll
+  for (int cb = 0; cb < CB; cb++) o[cb] = zero16();
+  const int f = swz64(l31);
+  const Corner64 cn = corner64(lane);
+  for (int kt = kv_first; kt <= kv_last; kt++) {
+    const int b = (kt - kv_first) & 1, k0 = kt * BKEY;
+    stage_barrier();
+    if (kt < kv_last) stage_k(kt + 1, b ^ 1);
+    const bool mine = !(k0 > t_base + 31 || t_base >= n);  // else the tile lies after every query of this wave
+    const bf16_t* sK = sm + b * 2 * T64_E; const bf16_t* sV = sK + T64_E;
+    f32x16 s[2];
+    if (mine) {
+#pragma unroll
+      for (int kb = 0; kb < 2; kb++) {
+        s[kb] = zero16();
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row64(sK, kb, ks, l31, h, f), qf[ks], s[kb], 0, 0, 0);
+      }
+    }
+    if (kt < kv_last) stage_v(kt + 1, b ^ 1);
+    if (!mine) continue;
+    if (!((k0 + 63 <= t_base) && (k0 >= ss_hi))) {          // the tile touches the diagonal or a segment start
+#pragma unroll
+      for (int kb = 0; kb < 2; kb++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+          const int key = k0 + kb * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
+          s[kb][e] = (key >= ss && key <= tq) ? s[kb][e] : -INFINITY;
+        }
+    }
+    float mx = s[0][0];
+#pragma unroll
+    for (int kb = 0; kb < 2; kb++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) mx = fmaxf(mx, s[kb][e]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * sl2;
+    const bool raise = mx > mref + 8.f;
+    if (__builtin_amdgcn_ballot_w64(raise) != 0) {
+      const float m_new = raise ? mx : mref;
+      const float alpha = raise ? fast_exp2(mref - m_new) : 1.f;
+      mref = m_new;
+      l *= alpha;
+#pragma unroll
+      for (int cb = 0; cb < CB; cb++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) o[cb][e] *= alpha;
+    }
+    const float neg_m = (mref == -INFINITY) ? 0.f : -mref;
+    float rs = 0.f;
+    bf16x8 pb[4];
+#pragma unroll
+    for (int kb = 0; kb < 2; kb++) {
+#pragma unroll
+      for (int e = 0; e < 16; e++) { const float pv = fast_exp2(fmaf(s[kb][e], sl2, neg_m)); s[kb][e] = pv; rs += pv; }
+      pb[kb * 2] = pack8(s[kb], 0); pb[kb * 2 + 1] = pack8(s[kb], 1);
+    }
+    rs += __shfl_xor(rs, 32, 64);
+    l += rs;
+#pragma unroll
+    for (int x = 0; x < 4; x++)
+#pragma unroll
+      for (int cb = 0; cb < CB; cb++) o[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col64(sV, cn, x, cb), pb[x], o[cb], 0, 0, 0);
+  }
+  if (tq >= n) return;
+  const float inv = 1.f / l;
+  bf16_t* orow = (bf16_t*)p.o + ((int64_t)tq * p.Hq + j) * DH;
+#pragma unroll
+  for (int cb = 0; cb < CB; cb++)
+#pragma unroll
+    for (int b4 = 0; b4 < 4; b4++) {
+      bf16x4 w;
+#pragma unroll
+      for (int i = 0; i < 4; i++) w[i] = (bf16_t)(o[cb][b4 * 4 + i] * inv);
+      *reinterpret_cast<bf16x4*>(orow + cb * 32 + 8 * b4 + 4 * h) = w;
+    }
+  if (h == 0) p.lse[(int64_t)tq * p.Hq + j] = (mref + log2f(l)) * 0.6931471805599453f;
+}
+
+template <int HPW>
+__global__ __launch_bounds__(256, 4) void attn_bwd_dq64_mfma(AttnParams p, float scale, float sl2) {
+  constexpr int DH = 64, KS = 4, CB = 2, QT = 32 * (4 / HPW);
+  extern __shared__ __align__(256) unsigned char dyn_smem[];
+  bf16_t* sm = (bf16_t*)dyn_smem;                         // [2 stages][K, V]
+  const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = p.n, grp = p.Hq / p.Hkv;
+  int hg, qi;
+  const int nqt = (n + 2 * QT - 1) / (2 * QT) * 2;
+  xcd_group_map(blockIdx.x, nqt, p.Hq / HPW, hg, qi);
+  const int j = hg * HPW + (wave % HPW), g = j / grp;
+  const int t_wg = (p.order_q ? p.order_q[qi >> 1] * 2 + 1 - (qi & 1) : nqt - 1 - qi) * QT;
+  if (t_wg >= n) return;
+  const int t_base = t_wg + (wave / HPW) * 32;
+  const bf16_t* Q = (const bf16_t*)p.q; const bf16_t* K = (const bf16_t*)p.k + g * DH; const bf16_t* V = (const bf16_t*)p.v + g * DH;
+  const bf16_t* dO = (const bf16_t*)p.d_o;
+  const int kv_first = __builtin_amdgcn_readfirstlane(p.seg_start[t_wg] / BKEY);
+  const int kv_last = min(t_wg + QT - 1, n - 1) / BKEY;
+  uint32_t voff[2];
+  tile64_offsets(p.ldkv, wave, lane, voff);
+  auto stage_k = [&](int kt, int b) { tile64_to_lds(K, p.ldkv, kt * BKEY, n - 1, voff, sm + b * 2 * T64_E, wave, lane); };
+  auto stage_v = [&](int kt, int b) { tile64_to_lds(V, p.ldkv, kt * BKEY, n - 1, voff, sm + b * 2 * T64_E + T64_E, wave, lane); };
+  stage_k(kv_first, 0); stage_v(kv_first, 0);
+  const int tq = t_base + l31, tc = min(tq, n - 1), ss = p.seg_start[tc];
+  bf16x8 qf[KS], dof[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ks++) {
+    qf[ks] = *reinterpret_cast<const bf16x8*>(Q + (int64_t)tc * p.ldq + j * DH + ks * 16 + h * 8);
+    dof[ks] = *reinterpret_cast<const bf16x8*>(dO + ((int64_t)tc * p.Hq + j) * DH + ks * 16 + h * 8);
+  }
+  const float neg_lse2 = -p.lse[(int64_t)tc * p.Hq + j] * 1.4426950408889634f;
+  const float dl = p.delta[(int64_t)tc * p.Hq + j];
+  const int ss_hi = __builtin_amdgcn_readfirstlane(p.seg_start[min(t_base + 31, n - 1)]);
+  f32x16 dq[CB];
+#pragma unroll
+  for (int cb = 0; cb < CB; cb++) dq[cb] = zero16();
+  const int f = swz64(l31);
+  const Corner64 cn = corner64(lane);
+  for (int kt = kv_first; kt <= kv_last; kt++) {
+    const int b = (kt - kv_first) & 1, k0 = kt * BKEY;
+    stage_barrier();
+    if (kt < kv_last) stage_k(kt + 1, b ^ 1);
+    const bool mine = !(k0 > t_base + 31 || t_base >= n);
+    const bf16_t* sK = sm + b * 2 * T64_E; const bf16_t* sV = sK + T64_E;
+    const bool full = (k0 + 63 <= t_base) && (k0 >= ss_hi);
+#pragma unroll
+    for (int kb = 0; kb < 2; kb++) {
+      if (kb == 1 && kt < kv_last) stage_v(kt + 1, b ^ 1);
+      if (!mine) continue;
+      f32x16 s = zero16(), dp = zero16();
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++) {
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row64(sK, kb, ks, l31, h, f), qf[ks], s, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row64(sV, kb, ks, l31, h, f), dof[ks], dp, 0, 0, 0);
+      }
+      if (!full) {
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+          const int key = k0 + kb * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
+          s[e] = (key >= ss && key <= tq) ? s[e] : -INFINITY;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 16; e++) s[e] = fast_exp2(fmaf(s[e], sl2, neg_lse2)) * (dp[e] - dl);
+#pragma unroll
+      for (int x = 0; x < 2; x++) {
+        const bf16x8 ds = pack8(s, x);
+#pragma unroll
+        for (int cb = 0; cb < CB; cb++) dq[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col64(sK, cn, 2 * kb + x, cb), ds, dq[cb], 0, 0, 0);
+      }
+    }
+  }
+  if (tq < n) store_grad_row<DH>(dq, scale, (bf16_t*)p.dq + (int64_t)tq * p.ldq + j * DH, h, p.rope_cos, p.rope_sin, tq - ss);
+}
+
+// delta = rowsum(dO * O) as the other kernels take it, and for the dK / dV kernel, head by head ([head][token], token count
+// rounded up to 64), -lse / scale and -delta: the start values of its accumulators of S and dP, so that neither costs a vector
+// instruction per element there.
+// Launch order of the blocks of 256 keys of a call that brings none, one workgroup: most query tiles first (ties: the earlier block).
+constexpr int kOrderBlocks = 1024;                        // counting ranks is quadratic; 262144 tokens
+__device__ void order_blocks(int n, const int32_t* __restrict__ seg_end, int32_t* __restrict__ order) {
+  __shared__ int len[kOrderBlocks];
+  const int nb = (n + 255) / 256;
+  for (int i = threadIdx.x; i < nb; i += 256) len[i] = seg_end[min(i * 256 + 255, n - 1)] - i * 256;
+  __syncthreads();
+  for (int i = threadIdx.x; i < nb; i += 256) {
+    int rank = 0;
+    for (int j = 0; j < nb; j++) rank += len[j] > len[i] || (len[j] == len[i] && j < i);
+    order[rank] = i;
+  }
+}
+
+__global__ __launch_bounds__(256) void attn_stat64_kernel(const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, int n, int Hq,
+                                                          int n64, float inv_scale, float* __restrict__ delta, float* __restrict__ nls, float* __restrict__ nd,
+                                                          const int32_t* __restrict__ seg_end, int32_t* __restrict__ order) {
+  if (order && blockIdx.x == gridDim.x - 1) { order_blocks(n, seg_end, order); return; }
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, r = t >> 3;                 // eight lanes per (token, head)
+  float acc = 0.f;
+  if (r < (int64_t)n * Hq) {
+    const u32x4 a = *reinterpret_cast<const u32x4*>(o + t * 8), b = *reinterpret_cast<const u32x4*>(d_o + t * 8);
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+      acc += __uint_as_float(a[k] << 16) * __uint_as_float(b[k] << 16) + __uint_as_float(a[k] & 0xffff0000u) * __uint_as_float(b[k] & 0xffff0000u);
+  }
+#pragma unroll
+  for (int off = 1; off < 8; off <<= 1) acc += __shfl_xor(acc, off);
+  if (r < (int64_t)n64 * Hq && (threadIdx.x & 7) == 0) {   // tokens n .. n64 - 1: zeros, their products are masked and must be finite
+    const int tok = (int)(r / Hq), hd = (int)(r % Hq);
+    if (tok < n) delta[r] = acc;
+    nls[(int64_t)hd * n64 + tok] = tok < n ? -lse[r] * inv_scale : 0.f;
+    nd[(int64_t)hd * n64 + tok] = -acc;
+  }
+}
+
+// dK and dV of 128 keys of one KV head from ONE query head: a wave owns 32 keys (a lane one key).  With several query heads per KV
+// head float partials [dK, dV][query head][token][dh], summed in head order by a second pass: a workgroup that takes the heads of a
+// group one after the other saves that pass (95 us of 555 at 15.5k tokens, 32 heads) but is four times as long, and the launch then
+// waits for its longest ones (600 against 460 + 95 us).
+__global__ __launch_bounds__(256, 3) void attn_bwd_dkv64_mfma(AttnParams p, float scale, float sl2, const float* __restrict__ nls, const float* __restrict__ nd, int n64,
+                                                              const int32_t* __restrict__ order, float* __restrict__ part) {
+  constexpr int DH = 64, KS = 4, CB = 2, KPB = 128;
+  constexpr int ST_E = 2 * T64_E + 256;                    // Q, dO, 64 -lse / scale and 64 -delta floats (2 elements each)
+  extern __shared__ __align__(256) unsigned char dyn_smem[];
+  bf16_t* sm = (bf16_t*)dyn_smem;
+  const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = p.n, grp = p.Hq / p.Hkv;
+  int jj, ki;
+  xcd_group_map<true>(blockIdx.x, 2 * ((n + 255) / 256), p.Hq, jj, ki);
+  const int g = jj / grp;
+  const int u_wg = (order ? order[ki >> 1] * 2 + (ki & 1) : ki) * KPB, u_base = u_wg + wave * 32;
+  if (u_wg >= n) return;
+  const bf16_t* Q = (const bf16_t*)p.q + jj * DH; const bf16_t* dO = (const bf16_t*)p.d_o + jj * DH;
+  const bf16_t* K = (const bf16_t*)p.k + g * DH; const bf16_t* V = (const bf16_t*)p.v + g * DH;
+  const int64_t ldo = (int64_t)p.Hq * DH;
+  const int q_first = u_wg / BKEY;
+  const int q_last = __builtin_amdgcn_readfirstlane((p.seg_end[min(u_wg + KPB - 1, n - 1)] - 1) / BKEY);
+  // this wave's keys are visible from queries in [u_base, w_end); all of them from queries in [u_base + 31, w_end_min)
+  const int w_end = (u_base < n) ? __builtin_amdgcn_readfirstlane(p.seg_end[min(u_base + 31, n - 1)]) : 0;
+  const int w_end_min = (u_base < n) ? __builtin_amdgcn_readfirstlane(p.seg_end[min(u_base, n - 1)]) : 0;
+  uint32_t voffQ[2], voffD[2];
+  tile64_offsets(p.ldq, wave, lane, voffQ); tile64_offsets(ldo, wave, lane, voffD);
+  // query tiles from the segment's end downwards: the workgroups of a head and segment that run together read the same tiles
+  auto stage_q = [&](int t0, int b) { tile64_to_lds(Q, p.ldq, t0, n - 1, voffQ, sm + b * ST_E, wave, lane); };
+  auto stage_d = [&](int t0, int b) {
+    tile64_to_lds(dO, ldo, t0, n - 1, voffD, sm + b * ST_E + T64_E, wave, lane);
+    if (wave < 2)                                          // rows past n of a last tile are inside the n64 entries and masked
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((wave ? nd : nls) + (int64_t)jj * n64 + t0 + lane),
+                                       (__attribute__((address_space(3))) void*)(sm + b * ST_E + 2 * T64_E + wave * 128), 4, 0, 0);
+  };
+  stage_q(q_last * BKEY, 0); stage_d(q_last * BKEY, 0);
+  const int u = u_base + l31, uc = min(u, n - 1);
+  const int uend = (u < n) ? p.seg_end[uc] : 0;            // queries u <= t < uend see this key
+  bf16x8 kf[KS], vf[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ks++) {
+    kf[ks] = *reinterpret_cast<const bf16x8*>(K + (int64_t)uc * p.ldkv + ks * 16 + h * 8);
+    vf[ks] = *reinterpret_cast<const bf16x8*>(V + (int64_t)uc * p.ldkv + ks * 16 + h * 8);
+  }
+  f32x16 accK[CB], accV[CB];                               // dK^T and dV^T, [dh rows, key lane]
+#pragma unroll
+  for (int cb = 0; cb < CB; cb++) { accK[cb] = zero16(); accV[cb] = zero16(); }
+  const int f = swz64(l31);
+  const Corner64 cn = corner64(lane);
+  for (int qt = q_last; qt >= q_first; qt--) {
+    const int b = (q_last - qt) & 1, t0 = qt * BKEY;
+    stage_barrier();
+    if (qt > q_first) stage_q(t0 - BKEY, b ^ 1);
+    const bf16_t* sQ = sm + b * ST_E; const bf16_t* sD = sQ + T64_E;
+    const float* sN = (const float*)(sQ + 2 * T64_E);
+    const bool mine = !(t0 + 63 < u_base || t0 >= w_end);   // else no query of the tile sees a key of this wave
+    const bool full = (t0 >= u_base + 31) && (t0 + 63 < w_end_min);
+#pragma unroll
+    for (int qb = 0; qb < 2; qb++) {
+      if (qb == 1 && qt > q_first) stage_d(t0 - BKEY, b ^ 1);
+      if (!mine) continue;
+      f32x16 s, dp;
+#pragma unroll
+      for (int b4 = 0; b4 < 4; b4++) {
+        const f32x4 a = *reinterpret_cast<const f32x4*>(sN + qb * 32 + 8 * b4 + 4 * h), c = *reinterpret_cast<const f32x4*>(sN + 64 + qb * 32 + 8 * b4 + 4 * h);
+#pragma unroll
+        for (int i = 0; i < 4; i++) { s[4 * b4 + i] = a[i]; dp[4 * b4 + i] = c[i]; }
+      }
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++) {
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row64(sQ, qb, ks, l31, h, f), kf[ks], s, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row64(sD, qb, ks, l31, h, f), vf[ks], dp, 0, 0, 0);
+      }
+      if (!full) {                                         // the tile touches the diagonal or a segment end
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+          const int t = t0 + qb * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
+          s[e] = (t >= u && t < uend) ? s[e] : -INFINITY;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 16; e++) { const float pr = fast_exp2(s[e] * sl2); s[e] = pr; dp[e] = pr * dp[e]; }
+#pragma unroll
+      for (int x = 0; x < 2; x++) {
+        const bf16x8 pv = pack8(s, x), ds = pack8(dp, x);
+#pragma unroll
+        for (int cb = 0; cb < CB; cb++) {
+          accV[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col64(sD, cn, 2 * qb + x, cb), pv, accV[cb], 0, 0, 0);
+          accK[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col64(sQ, cn, 2 * qb + x, cb), ds, accK[cb], 0, 0, 0);
+        }
+      }
+    }
+  }
+  if (u >= n) return;
+  if (grp > 1) {
+    auto put = [&](const f32x16 (&r)[CB], int which) {
+      float* row = part + (((int64_t)which * p.Hq + jj) * n + u) * DH;
+#pragma unroll
+      for (int cb = 0; cb < CB; cb++)
+#pragma unroll
+        for (int b4 = 0; b4 < 4; b4++) *reinterpret_cast<f32x4*>(row + cb * 32 + 8 * b4 + 4 * h) = (f32x4){r[cb][b4 * 4], r[cb][b4 * 4 + 1], r[cb][b4 * 4 + 2], r[cb][b4 * 4 + 3]};
+    };
+    put(accK, 0); put(accV, 1);
+    return;
+  }
+  const int pos = u - p.seg_start[u];
+  store_grad_row<DH>(accK, scale, (bf16_t*)p.dk + (int64_t)u * p.ldkv + g * DH, h, p.rope_cos, p.rope_sin, pos);
+  store_grad_row<DH>(accV, 1.f, (bf16_t*)p.dv + (int64_t)u * p.ldkv + g * DH, h, nullptr, p.rope_sin, pos);
+}
+
 // dk[u, g, :] = scale * sum over the query heads of group g, in head order, of the dK partials; dv likewise (scale 1).
 // With rotary tables dk is rotated back by the token's position before its one rounding: a thread then owns 4 columns
 // i .. i + 3 of the lower half and their partners i + dh / 2.
@@ -898,17 +1285,50 @@ int launch_fwd2(as_ctx* ctx, const AttnParams& p_in, float sl2, hipStream_t st) 
   return AS_OK;
 }
 
-template <int DH>
-int fwd_dh(as_ctx* ctx, const AttnParams& p_in, int variant, hipStream_t st) {
+constexpr size_t kSmem64 = (size_t)2 * 2 * T64_E * sizeof(bf16_t);          // two stages of a K and a V tile
+template <int HPW>
+int launch_fwd64(as_ctx* ctx, const AttnParams& p, float sl2, hipStream_t st) {
+  AS_SET_SMEM(ctx, attn_fwd64_mfma<HPW>, kSmem64);
+  attn_fwd64_mfma<HPW><<<(unsigned)(cdiv(p.n, 64 * (4 / HPW)) * 2 * (p.Hq / HPW)), 256, kSmem64, st>>>(p, sl2);
+  AS_LAUNCH_CHECK(ctx);
+  return AS_OK;
+}
+template <int HPW>
+int launch_dq64(as_ctx* ctx, const AttnParams& p, float scale, float sl2, hipStream_t st) {
+  AS_SET_SMEM(ctx, attn_bwd_dq64_mfma<HPW>, kSmem64);
+  attn_bwd_dq64_mfma<HPW><<<(unsigned)(cdiv(p.n, 64 * (4 / HPW)) * 2 * (p.Hq / HPW)), 256, kSmem64, st>>>(p, scale, sl2);
+  AS_LAUNCH_CHECK(ctx);
+  return AS_OK;
+}
+
+// Scratch of t_scratch: -lse / scale, -delta and an order of the key blocks where the token-major copy of Q would be, partials behind it all.
+int bwd64(as_ctx* ctx, const AttnParams& p, float scale, float sl2, int Np, float* stat, float* part, hipStream_t st) {
+  float* nls = stat; float* nd = nls + (size_t)p.Hq * Np;
+  int32_t* order = !p.order_k && cdiv(p.n, 256) <= kOrderBlocks ? (int32_t*)(nd + (size_t)p.Hq * Np) : nullptr;
+  attn_stat64_kernel<<<(unsigned)(cdiv((int64_t)Np * p.Hq * 8, 256) + (order ? 1 : 0)), 256, 0, st>>>((const bf16_t*)p.o, (const bf16_t*)p.d_o, p.lse, p.n, p.Hq, Np,
+                                                                                                     sqrtf(64.f), p.delta, nls, nd, p.seg_end, order);
+  AS_LAUNCH_CHECK(ctx);
+  const int hpw = heads_per_wg(p);
+  const int rc = hpw == 4 ? launch_dq64<4>(ctx, p, scale, sl2, st) : hpw == 2 ? launch_dq64<2>(ctx, p, scale, sl2, st) : launch_dq64<1>(ctx, p, scale, sl2, st);
+  if (rc) return rc;
+  constexpr size_t smem = (size_t)2 * (2 * T64_E + 256) * sizeof(bf16_t);   // two stages of Q, dO, -lse / scale, -delta
+  AS_SET_SMEM(ctx, attn_bwd_dkv64_mfma, smem);
+  attn_bwd_dkv64_mfma<<<(unsigned)(2 * cdiv(p.n, 256) * p.Hq), 256, smem, st>>>(p, scale, sl2, nls, nd, Np, order ? order : p.order_k, part);
+  AS_LAUNCH_CHECK(ctx);
+  return AS_OK;
+}
+
+int fwd_dh(as_ctx* ctx, const AttnParams& p_in, hipStream_t st) {
   AttnParams p = p_in;
-  const int Np = (int)cdiv(p.n, 64) * 64, Dkv = p.Hkv * DH;
+  const int Np = (int)cdiv(p.n, 64) * 64, Dkv = p.Hkv * p.dh;
   if (!p.t_scratch) return as_fail(ctx, AS_ERR_WORKSPACE, "attention: the MFMA kernels need the token-major scratch buffer");
+  const float sl2 = 1.4426950408889634f / sqrtf((float)p.dh);
+  const int hpw = heads_per_wg(p);
+  if (p.dh == 64) return hpw == 4 ? launch_fwd64<4>(ctx, p, sl2, st) : hpw == 2 ? launch_fwd64<2>(ctx, p, sl2, st) : launch_fwd64<1>(ctx, p, sl2, st);
   p.ldT = Np; p.vT = p.t_scratch;
   int rc = launch_transpose_qs(ctx, AS_BF16, p.n, Np, Dkv, p.v, p.ldkv, p.t_scratch, Np, st);   // V^T [Dkv, Np]
   if (rc) return rc;
-  const float sl2 = 1.4426950408889634f / sqrtf((float)DH);
-  const int hpw = heads_per_wg(p);
-  return hpw == 4 ? launch_fwd2<DH, 4, 1>(ctx, p, sl2, st) : hpw == 2 ? launch_fwd2<DH, 2, 1>(ctx, p, sl2, st) : launch_fwd2<DH, 1, 1>(ctx, p, sl2, st);
+  return hpw == 4 ? launch_fwd2<128, 4, 1>(ctx, p, sl2, st) : hpw == 2 ? launch_fwd2<128, 2, 1>(ctx, p, sl2, st) : launch_fwd2<128, 1, 1>(ctx, p, sl2, st);
 }
 
 template <int DH, int HPW>
@@ -922,7 +1342,7 @@ int launch_dq2(as_ctx* ctx, const AttnParams& p, float scale, float sl2, hipStre
 
 template <int DH, int WHICH>
 int launch_dkv2(as_ctx* ctx, const AttnParams& p, float scale, float sl2, float* part, hipStream_t st) {
-  constexpr size_t smem = (size_t)2 * ((WHICH == 0 ? 3 : WHICH == 1 ? 2 : 4) * BKEY * DH + 4 * BKEY) * sizeof(bf16_t);
+  constexpr size_t smem = (size_t)2 * ((WHICH == 0 ? 3 : 2) * BKEY * DH + 4 * BKEY) * sizeof(bf16_t);
   AS_SET_SMEM(ctx, (attn_bwd_dkv2_mfma<DH, WHICH>), smem);
   attn_bwd_dkv2_mfma<DH, WHICH><<<(unsigned)(cdiv(p.n, 256) * p.Hq), 512, smem, st>>>(p, scale, sl2, part);
   AS_LAUNCH_CHECK(ctx);
@@ -955,7 +1375,10 @@ int bwd_dh(as_ctx* ctx, const AttnParams& p_in, int variant, hipStream_t st) {
   int rc;
   const float scale = 1.f / sqrtf((float)DH), sl2 = 1.4426950408889634f * scale;
   const int64_t rows = (int64_t)p.n * p.Hq;
-  {
+  float* part = (float*)(ts + (size_t)(Dkv + 2 * D) * Np);         // [2][Hq][n][dh] floats behind the token-major copies
+  if (DH == 64 && variant != 4) {
+    if ((rc = bwd64(ctx, p, scale, sl2, Np, (float*)(ts + (size_t)Dkv * Np), part, st))) return rc;
+  } else {
     // one pass for dK and dV (head_dim 128, row strides a multiple of 256 bytes): reads Q and dO as they are
     const bool one_pass = DH == 128 && variant != 4 && p.ldq % 128 == 0;
     const int hpw = heads_per_wg(p);
@@ -972,20 +1395,14 @@ int bwd_dh(as_ctx* ctx, const AttnParams& p_in, int variant, hipStream_t st) {
     else if (hpw == 4) rc = launch_dq2<DH, 4>(ctx, p, scale, sl2, st); else if (hpw == 2) rc = launch_dq2<DH, 2>(ctx, p, scale, sl2, st);
     else rc = launch_dq2<DH, 1>(ctx, p, scale, sl2, st);
     if (rc) return rc;
-    float* part = (float*)(ts + (size_t)(Dkv + 2 * D) * Np);       // [2][Hq][n][dh] floats behind the token-major copies
     if (one_pass) return launch_dkv3(ctx, p, scale, sl2, st);     // sums over the query heads itself
-    // head_dim 64: both gradients in one launch (S and the exponentials once); at head_dim 128 two waves per SIMD do not have the registers for it
-    if constexpr (DH == 64) {
-      if (variant != 4) { if ((rc = launch_dkv2<DH, 2>(ctx, p, scale, sl2, part, st))) return rc; }
-      else if ((rc = launch_dkv2<DH, 0>(ctx, p, scale, sl2, part, st)) || (rc = launch_dkv2<DH, 1>(ctx, p, scale, sl2, part, st))) return rc;
-    } else if ((rc = launch_dkv2<DH, 0>(ctx, p, scale, sl2, part, st)) || (rc = launch_dkv2<DH, 1>(ctx, p, scale, sl2, part, st))) return rc;
-    if (p.Hq > p.Hkv) {
-      const int64_t threads = 2 * (int64_t)p.n * p.Hkv * (DH / 4);
-      attn_dkv_reduce_kernel<<<(unsigned)cdiv(threads, 256), 256, 0, st>>>(part, p.n, p.Hq, p.Hkv, DH, scale, (bf16_t*)p.dk, (bf16_t*)p.dv, p.ldkv,
-                                                                             p.seg_start, p.rope_cos, p.rope_sin);
-      AS_LAUNCH_CHECK(ctx);
-    }
-    return AS_OK;
+    if ((rc = launch_dkv2<DH, 0>(ctx, p, scale, sl2, part, st)) || (rc = launch_dkv2<DH, 1>(ctx, p, scale, sl2, part, st))) return rc;
+  }
+  if (p.Hq > p.Hkv) {
+    const int64_t threads = 2 * (int64_t)p.n * p.Hkv * (DH / 4);
+    attn_dkv_reduce_kernel<<<(unsigned)cdiv(threads, 256), 256, 0, st>>>(part, p.n, p.Hq, p.Hkv, DH, scale, (bf16_t*)p.dk, (bf16_t*)p.dv, p.ldkv,
+                                                                           p.seg_start, p.rope_cos, p.rope_sin);
+    AS_LAUNCH_CHECK(ctx);
   }
   return AS_OK;
 }
@@ -1004,7 +1421,8 @@ bool attention_mfma_ok(const AttnParams& p) {
 }
 
 int launch_attention_fwd_mfma(as_ctx* ctx, const AttnParams& p, int variant, hipStream_t st) {
-  return p.dh == 128 ? fwd_dh<128>(ctx, p, variant, st) : fwd_dh<64>(ctx, p, variant, st);
+  (void)variant;
+  return fwd_dh(ctx, p, st);
 }
 
 int launch_attention_bwd_mfma(as_ctx* ctx, const AttnParams& p, int variant, hipStream_t st) {

@@ -299,3 +299,32 @@ def test_attention_forward_and_backward(tier, Hq, Hkv, dh, lens, late_gain):
         sc = (k[s0:t + 1, 0] @ q[t, 0]) / np.sqrt(dh)
         ref = sc.max() + np.log(np.exp(sc - sc.max()).sum())
         assert abs(float(lse[t, 0]) - ref) < (2e-2 if bf16 else 1e-4)
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(2, 2), (4, 2), (8, 2), (16, 8)])
+@pytest.mark.parametrize("lens", [[2], [63], [1, 63], [64, 1], [65, 62, 1], [127, 129], [31, 97, 128], [1, 3, 253, 64, 130, 5], [200, 700, 100, 11]])
+def test_attention_head_dim_64_at_tile_edges(Hq, Hkv, lens):
+    """Workgroups of one, two and four heads, groups that do and do not divide among eight, token counts around the tiles of 64, the
+    128 keys of a workgroup and the blocks of 256 that are put in order, segments shorter than a tile.  Four bf16 roundings lie between the operands
+    and a result (o as the backward reads it, P, dS, the result itself), each at most 2^-9 of its value, and o's enters through
+    a difference with dP of its own size: 8 * 2^-9."""
+    B, G, ctx, sh = _env(n_q_heads=Hq, n_kv_heads=Hkv, head_dim=64)
+    dh, tol = 64, 2.0 ** -6
+    g, cu, n = _attn_case(9, len(lens), Hq, Hkv, dh, lens)
+    q = G.quantise(g.standard_normal((n, Hq, dh)), True)
+    k = G.quantise(g.standard_normal((n, Hkv, dh)), True)
+    v = G.quantise(g.standard_normal((n, Hkv, dh)), True)
+    do = G.quantise(g.standard_normal((n, Hq, dh)), True)
+    o_ref, probs = om.attention(q, k, v, cu, Hq // Hkv)
+    refs = (o_ref,) + tuple(om.attention_bwd(do, q, k, v, o_ref, probs, cu, Hq // Hkv))
+    seg = om.segment_ids(cu, n)
+    seg_start = torch.from_numpy(cu[seg].astype(np.int32)).cuda()
+    seg_end = torch.from_numpy(cu[seg + 1].astype(np.int32)).cuda()
+    qkv_d = G.to_dev(np.concatenate([x.reshape(n, -1) for x in (q, k, v)], axis=1), torch.bfloat16)
+    o, lse = ctx.op_attention_fwd(qkv_d, seg_start, variant=2, mode=B.AS_BF16)
+    o_in = G.to_dev(o_ref.reshape(n, -1), torch.bfloat16)
+    dqkv = ctx.op_attention_bwd(qkv_d, seg_start, seg_end, o_in, lse, G.to_dev(do.reshape(n, -1), torch.bfloat16), variant=2, mode=B.AS_BF16)
+    D, Dkv = Hq * dh, Hkv * dh
+    got = G.to_np(dqkv)
+    for x, r in zip((G.to_np(o), got[:, :D], got[:, D:D + Dkv], got[:, D + Dkv:]), refs):
+        assert grad_norm_err(x, r.reshape(n, -1)) < tol
