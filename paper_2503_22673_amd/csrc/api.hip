@@ -603,12 +603,61 @@ struct Step {
 
   // every expert's product over its own rows: rows eoff[e] .. eoff[e+1] of A and C times the e-th of the stacked
   // matrices at B (b_stride elements apart); one launch where the kernel allows, else one per expert
-  int gemm_experts(const int32_t* eoff, int N, const void* A, int64_t lda, const void* B, int64_t b_stride, int64_t ldb, int K, void* C, int64_t ldc) {
+  // A product with a gradient contracts over the rows of a weight matrix.  The hand-scheduled GEMM reads the matrices as they
+  // are ([K, N] rows), the others want the transposed copy: 8192 tokens on eight experts of 4096 x 14336 each spent
+  // 1400 us of 15.0 ms in those copies, and the products take the same time either way.
+  struct Piece { const void* w; const float* absmax; int rows; };
+  // C [M, N] = dY [w1; w2; ..] (+ du A): the pieces' rows below one another; A [K2, N], At its transpose
+  int gemm_dx(int M, int N, const void* dY, int64_t ldy, std::initializer_list<Piece> ws, const void* du, int64_t ldu, const void* A, const void* At,
+              int64_t ldat, int K2, void* C, int64_t ldc) {
     GemmParams g; memset(&g, 0, sizeof g);
-    g.seg[0] = {A, B, lda, ldb, K}; g.nseg = 1;
-    g.M = P.N; g.N = N; g.C = C; g.ldc = ldc; g.alpha = 1.f; g.splitk = 1;
+    int K = 0, rc;
+    for (const Piece& w : ws) {
+      if (!g.nn) g.seg[0].B = w.w; else { g.nb[g.nn - 1] = w.w; g.nb_row[g.nn - 1] = K; }
+      g.nn++; K += w.rows;
+    }
+    g.seg[0] = {dY, g.seg[0].B, ldy, N, K}; g.nseg = 1;
+    if (du && K2 > 0) { g.seg[1] = {du, A, ldu, N, K2}; g.nseg = 2; }
+    g.M = M; g.N = N; g.C = C; g.ldc = ldc; g.alpha = 1.f; g.splitk = 1; g.tail_part = P.gemm_tail; g.rows_cap = rows_cap_once;
+    if (c.weight_format != AS_W_NF4 && gemm_nn_applies(mode, gv, g)) { rows_cap_once = 0; return launch_gemm(ctx, mode, gv, g, st); }
+    int k0 = 0;
+    for (const Piece& w : ws) {
+      if ((rc = weight_transposed(w.rows, N, w.w, w.absmax, off(P.wT, (size_t)k0), K))) return rc;
+      k0 += w.rows;
+    }
+    return gemm(M, N, dY, ldy, P.wT, K, K, du, ldu, At, ldat, K2, nullptr, 0, C, ldc);
+  }
+  // the same over the experts' rows: pieces [E][rows][N]
+  int gemm_experts_dx(const int32_t* eoff, int N, const void* dY, std::initializer_list<Piece> ws, void* C) {
+    GemmParams g; memset(&g, 0, sizeof g);
+    int K = 0, rc;
+    for (const Piece& w : ws) {
+      if (!g.nn) g.seg[0].B = w.w; else { g.nb[g.nn - 1] = w.w; g.nb_row[g.nn - 1] = K; }
+      g.nn++; K += w.rows;
+    }
+    const int64_t stride = (int64_t)ws.begin()->rows * N;   // between the experts' matrices: one value, all pieces have as many rows
+    g.seg[0] = {dY, g.seg[0].B, K, N, K};
+    experts_args(g, eoff, N, stride, C, N);
+    if (gemm_nn_applies(mode, gv, g)) return launch_gemm(ctx, mode, gv, g, st);
+    // the transposed matrices of all experts side by side (the workspace slot holds E of them), then one product each
+    for (int e = 0; e < c.n_experts; e++) {
+      int k0 = 0;
+      for (const Piece& w : ws) {
+        if ((rc = transpose(w.rows, N, off(const_cast<void*>(w.w), (size_t)e * w.rows * N), N, off(P.wT, (size_t)e * K * N + k0), K))) return rc;
+        k0 += w.rows;
+      }
+    }
+    return gemm_experts(eoff, N, dY, K, P.wT, (int64_t)K * N, K, K, C, N);
+  }
+  void experts_args(GemmParams& g, const int32_t* eoff, int N, int64_t b_stride, void* C, int64_t ldc) {
+    g.nseg = 1; g.M = P.N; g.N = N; g.C = C; g.ldc = ldc; g.alpha = 1.f; g.splitk = 1;
     g.grp_off = eoff; g.grp_n = c.n_experts; g.grp_b_stride = b_stride; g.grp_rows = 2.0 * P.N;
     g.rows_cap = 2 * P.N;                                  // A and C are (token, slot) buffers: 2 N rows
+  }
+  int gemm_experts(const int32_t* eoff, int N, const void* A, int64_t lda, const void* B, int64_t b_stride, int64_t ldb, int K, void* C, int64_t ldc) {
+    GemmParams g; memset(&g, 0, sizeof g);
+    g.seg[0] = {A, B, lda, ldb, K};
+    experts_args(g, eoff, N, b_stride, C, ldc);
     return launch_gemm_off(ctx, mode, gv, g, 0, st);
   }
 
@@ -639,17 +688,9 @@ struct Step {
     int rc;
     if ((rc = launch_moe_dlogit(ctx, mode, P.dh, a.y_perm, a.pos, a.sel, a.wsel, N, d, E, P.dlogit, st))) return rc;
     if ((rc = launch_moe_gather(ctx, mode, P.dh, a.perm, a.wsel, 2 * N, d, P.xbp, st))) return rc;        // w * dy, grouped
-    // the transposed matrices of all experts side by side (the workspace slot holds E of them), then one product each
-    for (int e = 0; e < E; e++)
-      if ((rc = transpose(d, F, off(w.wdown, (size_t)e * d * F), F, off(P.wT, (size_t)e * F * d), d))) return rc;      // [F, d]
-    if ((rc = gemm_experts(a.eoff, F, P.xbp, d, P.wT, (int64_t)F * d, d, d, P.dm, F))) return rc;
+    if ((rc = gemm_experts_dx(a.eoff, F, P.xbp, {{w.wdown, nullptr, d}}, P.dm))) return rc;
     if ((rc = launch_swiglu_bwd(ctx, mode, 2 * N, F, P.dm, a.gu, P.dgu, nullptr, st))) return rc;
-    for (int e = 0; e < E; e++) {
-      void* wt = off(P.wT, (size_t)e * 2 * F * d);
-      if ((rc = transpose(F, d, off(w.wgate, (size_t)e * F * d), d, wt, 2 * F))) return rc;               // [d, 2F]
-      if ((rc = transpose(F, d, off(w.wup, (size_t)e * F * d), d, off(wt, (size_t)F), 2 * F))) return rc;
-    }
-    if ((rc = gemm_experts(a.eoff, d, P.dgu, 2 * F, P.wT, (int64_t)2 * F * d, 2 * F, 2 * F, P.xbp, d))) return rc;     // grouped gradient of the expert inputs
+    if ((rc = gemm_experts_dx(a.eoff, d, P.dgu, {{w.wgate, nullptr, F}, {w.wup, nullptr, F}}, P.xbp))) return rc;   // grouped gradient of the expert inputs
     if ((rc = launch_moe_combine(ctx, mode, nullptr, P.xbp, a.pos, nullptr, N, d, P.da, st))) return rc;  // back to token order
     // router: db = (expert part) + dlogit Wr + du_r A
     LoraSlot& s = slot(l, AS_T_ROUTER);
@@ -780,10 +821,9 @@ struct Step {
     else {
     // ---- down projection
     { LoraSlot& s = slot(l, AS_T_DOWN);
-      if ((rc = weight_transposed(d, F, w.wdown, w.adown, P.wT, d))) return rc;                       // [F, d]
       if (s.on && (rc = gemm(N, rp, P.dh, d, s.Bst, d, d, nullptr, 0, nullptr, 0, 0, nullptr, 0, P.du_d, rp))) return rc;
       rows_cap_once = P.cap;
-      if ((rc = gemm(N, F, P.dh, d, P.wT, d, d, s.on ? P.du_d : nullptr, rp, s.At, rp, s.on ? rp : 0, nullptr, 0, P.dm, F))) return rc;
+      if ((rc = gemm_dx(N, F, P.dh, d, {{w.wdown, w.adown, d}}, s.on ? P.du_d : nullptr, rp, s.A, s.At, rp, s.on ? rp : 0, P.dm, F))) return rc;
       // ---- SwiGLU (in recompute mode 2 it also rewrites the forward product, which the gradients below need)
       const bool rewrite_m = c.recompute == 2 && l != c.n_layers - 1 && (full || s.on);
       if ((rc = launch_swiglu_bwd(ctx, mode, N, F, P.dm, a.gu, P.dgu, rewrite_m ? a.m : nullptr, st))) return rc;
@@ -798,16 +838,13 @@ struct Step {
       if (full && (rc = weight_grad(G->w_layers[l].wdown, d, F, P.dyT, P.xT))) return rc; }
     // ---- gate / up projections
     { const int ldg = P.n_gu * rp;
-      const void* wg[2] = {w.wgate, w.wup}; const float* ag[2] = {w.agate, w.aup};
       for (int i = 0; i < 2; i++) {
         LoraSlot& s = slot(l, AS_T_GATE + i);
-        if ((rc = weight_transposed(F, d, wg[i], ag[i], off(P.wT, (size_t)i * F), 2 * F))) return rc;        // [d, 2F]
         if (s.on && (rc = gemm(N, rp, off(P.dgu, (size_t)i * F), 2 * F, s.Bst, F, F, nullptr, 0, nullptr, 0, 0, nullptr, 0,
                                off(P.du_gu, (size_t)s.slot * rp), ldg))) return rc;
       }
       rows_cap_once = P.cap;
-      if ((rc = gemm(N, d, P.dgu, 2 * F, P.wT, 2 * F, 2 * F, P.n_gu ? P.du_gu : nullptr, ldg, P.At_gu[l], ldg, ldg,
-                     nullptr, 0, P.db, d))) return rc;
+      if ((rc = gemm_dx(N, d, P.dgu, 2 * F, {{w.wgate, w.agate, F}, {w.wup, w.aup, F}}, P.n_gu ? P.du_gu : nullptr, ldg, P.A_gu[l], P.At_gu[l], ldg, ldg, P.db, d))) return rc;
       if (full || (P.n_gu && !tn_path())) {
         if ((rc = transpose_tok(2 * F, P.dgu, 2 * F, P.dyT))) return rc;
         if ((rc = transpose_tok(d, a.b, d, P.xT))) return rc;
@@ -827,10 +864,9 @@ struct Step {
     if ((rc = norm_bwd(P.db, nullptr, a.h_mid, w.g2, a.rstd2, P.dh, P.dh2, full ? G->w_layers[l].g2 : nullptr))) return rc;
     // ---- output projection
     { LoraSlot& s = slot(l, AS_T_O);
-      if ((rc = weight_transposed(d, D, w.wo, w.ao, P.wT, d))) return rc;                          // [D, d]
       if (s.on && (rc = gemm(N, rp, P.dh2, d, s.Bst, d, d, nullptr, 0, nullptr, 0, 0, nullptr, 0, P.du_o, rp))) return rc;
       rows_cap_once = P.cap;
-      if ((rc = gemm(N, D, P.dh2, d, P.wT, d, d, s.on ? P.du_o : nullptr, rp, s.At, rp, s.on ? rp : 0, nullptr, 0, P.d_o, D))) return rc;
+      if ((rc = gemm_dx(N, D, P.dh2, d, {{w.wo, w.ao, d}}, s.on ? P.du_o : nullptr, rp, s.A, s.At, rp, s.on ? rp : 0, P.d_o, D))) return rc;
       if (full || (s.on && !tn_path())) {
         if ((rc = transpose_tok(d, P.dh2, d, P.dyT))) return rc;
         if ((rc = transpose_tok(D, a.o, D, P.xT))) return rc;
@@ -853,19 +889,17 @@ struct Step {
       if (!fused_rope && (rc = launch_rope(ctx, mode, N, c.n_q_heads + c.n_kv_heads, c.head_dim, P.dqkv, QKV, P.seg_start, P.rope_cos, P.rope_sin, 1, st))) return rc; }
     // ---- q / k / v projections
     { const int ldu = P.n_qkv * rp;
-      const void* wq[3] = {w.wq, w.wk, w.wv}; const float* aq[3] = {w.aq, w.ak, w.av};
       const int nout[3] = {D, Dkv, Dkv}; const int coff[3] = {0, D, D + Dkv};
       // with frozen embeddings nothing below the first layer's first norm takes a gradient
       const bool need_da = full || l > 0;
       for (int i = 0; i < 3; i++) {
         LoraSlot& s = slot(l, i);
-        if (need_da && (rc = weight_transposed(nout[i], d, wq[i], aq[i], off(P.wT, coff[i]), QKV))) return rc;          // [d, QKV]
         if (s.on && (rc = gemm(N, rp, off(P.dqkv, coff[i]), QKV, s.Bst, nout[i], nout[i], nullptr, 0, nullptr, 0, 0, nullptr, 0,
                                off(P.du_qkv, (size_t)s.slot * rp), ldu))) return rc;
       }
       rows_cap_once = P.cap;
-      if (need_da && (rc = gemm(N, d, P.dqkv, QKV, P.wT, QKV, QKV, P.n_qkv ? P.du_qkv : nullptr, ldu, P.At_qkv[l], ldu, ldu,
-                                nullptr, 0, P.da, d))) return rc;
+      if (need_da && (rc = gemm_dx(N, d, P.dqkv, QKV, {{w.wq, w.aq, D}, {w.wk, w.ak, Dkv}, {w.wv, w.av, Dkv}}, P.n_qkv ? P.du_qkv : nullptr, ldu,
+                                   P.A_qkv[l], P.At_qkv[l], ldu, ldu, P.da, d))) return rc;
       if (full || (P.n_qkv && !tn_path())) {
         if ((rc = transpose_tok(QKV, P.dqkv, QKV, P.dyT))) return rc;
         if ((rc = transpose_tok(d, a.a, d, P.xT))) return rc;
@@ -903,10 +937,21 @@ struct Step {
   // Otherwise (fp32 tier, odd sizes): a float logits chunk, a row pass, the same second product.
   bool head_fused = false;
   int head_chunk_rows(int r0) const { return head_fused ? std::min(P.Mc, (int)cdiv(P.N - r0, 256) * 256) : std::min(P.Mc, P.N - r0); }
+  bool head_nn = false;
+  GemmParams head_dh_args(int r0, int rows) const {
+    GemmParams g; memset(&g, 0, sizeof g);
+    g.seg[0] = {P.P, W->head, P.V, P.d, P.V}; g.nseg = 1; g.nn = 1;
+    g.M = rows; g.N = P.d; g.m_dev = P.count; g.C = off(P.dhf, (size_t)r0 * P.d); g.ldc = P.d; g.alpha = 1.f; g.splitk = 1; g.tail_part = P.gemm_tail;
+    return g;
+  }
   int head_begin(bool grads) {
     int rc;
-    if (grads && (rc = transpose(P.V, P.d, W->head, P.d, P.headT, P.V))) return rc;                     // [d, V]
     head_fused = P.head_fused;
+    if (grads) {
+      head_nn = true;                                      // every chunk's product reads the head as it is, or all its transposed copy
+      for (int r0 = 0; r0 < P.N; r0 += P.Mc) { const GemmParams g = head_dh_args(r0, head_chunk_rows(r0)); head_nn = head_nn && gemm_nn_applies(mode, gv, g); }
+      if (!head_nn && (rc = transpose(P.V, P.d, W->head, P.d, P.headT, P.V))) return rc;                // [d, V]
+    }
     if (!head_fused) return AS_OK;
     GemmParams g; memset(&g, 0, sizeof g);
     g.seg[0] = {P.hf, W->head, P.d, P.d, P.d}; g.nseg = 1; g.M = std::min(P.Mc, (int)cdiv(P.N, 256) * 256); g.N = P.V; g.m_dev = P.count;
@@ -938,7 +983,9 @@ struct Step {
         if ((rc = gemm(rows, V, hf_c, d, W->head, d, d, nullptr, 0, nullptr, 0, 0, nullptr, 0, P.logits, V, 1, 1.f, 0, P.count, r0))) return rc;
         if ((rc = launch_ce_rows(ctx, mode, P.logits, rows, V, r0, P.labels, P.count, P.loss_rows, row_w, P.P, st))) return rc;
       }
-      if ((rc = gemm(rows, d, P.P, V, P.headT, V, V, nullptr, 0, nullptr, 0, 0, nullptr, 0, off(P.dhf, (size_t)r0 * d), d, 0, 1.f, 0, P.count, r0))) return rc;
+      if (head_nn) rc = launch_gemm_off(ctx, mode, gv, head_dh_args(r0, rows), r0, st);
+      else rc = gemm(rows, d, P.P, V, P.headT, V, V, nullptr, 0, nullptr, 0, 0, nullptr, 0, off(P.dhf, (size_t)r0 * d), d, 0, 1.f, 0, P.count, r0);
+      if (rc) return rc;
       if (dw_head) {
         // dW_head += P_c^T hf_c  (rows past the live count are read as zero)
         // the contraction length is padded to whole 64-token steps (zero rows past the chunk), so that the MFMA kernel takes it

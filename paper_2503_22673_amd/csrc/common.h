@@ -106,11 +106,17 @@ struct GemmParams {
   // [tile - tail_first][part][256 x 256]; a second small launch adds the parts in order and applies the epilogue.
   // Set by the launcher, which finds room for kGemmTailFloats floats at tail_part.
   int tail_first, tail_parts; float* tail_part;
+  // nn > 0: B of both segments is [K, N], rows of N elements with ONE row stride (seg[0].ldb == seg[1].ldb); segment 0's rows are those of
+  // nn <= 3 matrices below one another: seg[0].B, and from row nb_row[i] (a multiple of 64) on nb[i].  Hand-scheduled kernel only: ask
+  // gemm_nn_applies first.
+  int nn; const void* nb[2]; int nb_row[2];
   int epi; const float* epi_lse; const int32_t* epi_lab; const float* epi_w; const int32_t* epi_cnt; float* epi_part;
 };
 enum { GEMM_EPI_NONE = 0, GEMM_EPI_STATS = 1, GEMM_EPI_PROB = 2 };
 // the hand-scheduled kernel would take this product (whole 256 x 256 tiles, K in 64-wide steps, alignment)
 bool gemm_rs_applies(int mode, const GemmParams& p);
+// the launch (p.nn set) would go to the hand-scheduled kernel, which alone reads B as [K, N]
+bool gemm_nn_applies(int mode, int variant, const GemmParams& p);
 // floats of scratch (GemmParams::tail_part given by the caller through `tail_ws`) that let the launcher split the last round
 constexpr size_t kGemmTailFloats = (size_t)128 * 2 * 256 * 256;
 int launch_gemm(as_ctx* ctx, int mode, int variant, const GemmParams& p, hipStream_t st);

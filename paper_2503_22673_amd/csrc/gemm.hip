@@ -835,7 +835,12 @@ __device__ __forceinline__ void gemm_epilogue_stats(const GemmParams& p, f32x16 
 // LIVE = 1: the row count is a device-side value and / or the rows are those of one group (expert).  Tiles past the live
 // rows exit; a tile still computes 256 rows, moved up if need be so that they lie inside the `limit` rows the operands
 // are known to have (M for a plain row count, rows_cap for grouped rows), and writes the rows that are its own and live.
+// NN: B is taken as [K, N] rows (gemm_rs_nn_loop.inc), the layout of a weight matrix in the product with its output
+// gradient: the matrix does not have to be transposed first.  The loop is the same but for half-width, transposing reads of B, and so
+// is its rate: steps of 16384 tokens on a dense 8B model and of 8192 tokens on a sparse 8x7B one lost 700 us of 33.1 ms and 1150 us
+// of 15.0 ms, the time of the copies, and nothing else changed.
 #include "gemm_rs_loop.inc"
+#include "gemm_rs_nn_loop.inc"
 // Rows counted on the device, with scratch for partial sums: the contraction of every tile is split over as many workgroups as
 // fit one round, up to kLiveParts.  Host code cannot know the count, so both launches work the split out from it.
 constexpr int kLiveParts = 16;
@@ -844,7 +849,7 @@ __device__ __forceinline__ int live_parts(const GemmParams& p, int tiles) {
 }
 // EPI: the epilogue is a compile-time choice (GEMM_EPI_*), so that the head's epilogues, which need registers of their own,
 // cost the projection GEMMs nothing.
-template <int LIVE, int EPI = GEMM_EPI_NONE>
+template <int LIVE, int EPI = GEMM_EPI_NONE, bool NN = false>
 __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_off, int tiles_m, int tiles_n) {
   constexpr int BM = 256, BN = 256, BK = 64, TM = 4, TN = 4;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -920,13 +925,20 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
       const unsigned c = (unsigned)(((2 * ks + hh) ^ x7) * 16);
       line[0][ks] = (unsigned)((wm * 128 + l31) * 128) + c;                    // fragment reads of A
       line[1][ks] = 65536u + (unsigned)((wn * 128 + l31) * 128) + c;           // ... of B
+      // NN: by column block ks; this lane's 8 bytes of the 4 x 16 patch, 64-byte unit u of row r at u ^ (r & 3)
+      if (NN) line[1][ks] = 65536u + (unsigned)((8 * hh + ((lane >> 2) & 3)) * 512 + wn * 256 + ((ks ^ ((lane >> 2) & 3)) * 64) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8);
     }
     const unsigned wrow = (unsigned)((wave * 64 + lrow) * 128);
     line[2][0] = wrow + (unsigned)((lch ^ (lrow >> 1)) * 16);                  // LDS stores, even / odd load
     line[2][1] = wrow + (unsigned)((lch ^ ((lrow >> 1) | 4)) * 16);
     line[2][2] = line[2][0] + 65536u; line[2][3] = line[2][1] + 65536u;
+    if (NN) {                                            // rows 2 i, 2 i + 1 of the wave's sixteen, half a wave each
+      const unsigned r = (unsigned)(wave * 16 + hh) * 512u + 65536u, in = (unsigned)((l31 & 3) * 16), u = (unsigned)(l31 >> 2);
+      line[2][2] = r + ((u ^ (unsigned)hh) * 64u) + in; line[2][3] = r + ((u ^ (unsigned)(hh + 2)) * 64u) + in;
+    }
     line[3][0] = (unsigned)((lrow * s0.lda + lch * 8) * 2); line[3][1] = (unsigned)((lrow * s0.ldb + lch * 8) * 2);
     line[3][2] = (unsigned)((lrow * s1.lda + lch * 8) * 2); line[3][3] = (unsigned)((lrow * s1.ldb + lch * 8) * 2);
+    if (NN) line[3][1] = line[3][3] = (unsigned)((hh * s0.ldb + l31 * 8) * 2);
     u32x4* scratch = reinterpret_cast<u32x4*>(smem + 131072 + tid * 64);
 #pragma unroll
     for (int i = 0; i < 4; i++) scratch[i] = line[i];
@@ -945,6 +957,25 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
     const uint64_t A1 = (uint64_t)((const bf16_t*)s1.A + a2off + (int64_t)(row0 + wave * 64) * s1.lda);
     const uint64_t B1 = (uint64_t)(b1p + (int64_t)(colg + wave * 64) * s1.ldb);
     const int sA0 = (int)(16 * s0.lda), sB0 = (int)(16 * s0.ldb), sA1 = (int)(16 * s1.lda), sB1 = (int)(16 * s1.ldb);   // 8 rows, bytes
+    if constexpr (NN) {
+      const int64_t ldb = s0.ldb, row_w = (int64_t)(wave * 16) * ldb + col0, lo = k_skip / BK;
+      // base of a matrix minus its first row: step t of this workgroup reads rows 64 t .. of it
+      auto base = [&](const void* m, int64_t first_row) {
+        return (uint64_t)m + (uint64_t)(2 * ((int64_t)b_group * p.grp_b_stride + row_w + (k_skip - first_row) * ldb));
+      };
+      const int n1 = p.nn > 1 ? (int)(p.nb_row[0] / BK - lo) : nt0, n2 = p.nn > 2 ? (int)(p.nb_row[1] / BK - lo) : nt0;
+      const uint64_t P0 = base(s0.B, 0), P1 = base(p.nb[0], p.nb_row[0]), P2 = base(p.nb[1], p.nb_row[1]);
+      const uint64_t P3 = (uint64_t)s1.B + (uint64_t)(2 * (row_w - (int64_t)nt0 * BK * ldb));
+      const int sB = (int)(4 * ldb), sK = (int)(128 * ldb);   // two rows, 64 rows, bytes
+      asm volatile(GEMM_RS_NN_LOOP_ASM
+                   : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[0][2]), "+a"(acc[0][3]),
+                     "+a"(acc[1][0]), "+a"(acc[1][1]), "+a"(acc[1][2]), "+a"(acc[1][3]),
+                     "+a"(acc[2][0]), "+a"(acc[2][1]), "+a"(acc[2][2]), "+a"(acc[2][3]),
+                     "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][2]), "+a"(acc[3][3])
+                   : "v"(scratch_addr), "s"(A0), "s"(P0), "s"(A1), "s"(P3), "s"(sA0), "s"(sB), "s"(sA1), "s"(sB), "s"(nt0), "s"(nt),
+                     "s"(P1), "s"(P2), "s"(n1), "s"(n2), "s"(sK)
+                   : GEMM_RS_NN_LOOP_CLOBBERS);
+    } else
     asm volatile(GEMM_RS_LOOP_ASM
                  : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[0][2]), "+a"(acc[0][3]),
                    "+a"(acc[1][0]), "+a"(acc[1][1]), "+a"(acc[1][2]), "+a"(acc[1][3]),
@@ -1085,6 +1116,9 @@ static int launch_rs_cfg(as_ctx* ctx, const GemmParams& p_in, int m_off, int par
   AS_SET_SMEM(ctx, gemm_mfma_rs_kernel<0>, smem);
   AS_SET_SMEM(ctx, gemm_mfma_rs_kernel<1>, smem);
   AS_SET_SMEM(ctx, gemm_mfma_rs_kernel<2>, smem);
+  AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<0, GEMM_EPI_NONE, true>), smem);
+  AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<1, GEMM_EPI_NONE, true>), smem);
+  AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<2, GEMM_EPI_NONE, true>), smem);
   AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<1, GEMM_EPI_STATS>), smem);
   AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<1, GEMM_EPI_PROB>), smem);
   const int tn = p.N / 256;
@@ -1096,7 +1130,9 @@ static int launch_rs_cfg(as_ctx* ctx, const GemmParams& p_in, int m_off, int par
     else if (p.epi == GEMM_EPI_PROB) gemm_mfma_rs_kernel<1, GEMM_EPI_PROB><<<dim3(tm * tn), 256, smem, st>>>(p, m_off, tm, tn);
     else {
       if (!live_split_ok(p)) p.tail_part = nullptr;
-      gemm_mfma_rs_kernel<1><<<dim3(p.tail_part ? std::max(tm * tn, kCus) : tm * tn), 256, smem, st>>>(p, m_off, tm, tn);
+      const dim3 grid(p.tail_part ? std::max(tm * tn, kCus) : tm * tn);
+      if (p.nn) gemm_mfma_rs_kernel<1, GEMM_EPI_NONE, true><<<grid, 256, smem, st>>>(p, m_off, tm, tn);
+      else gemm_mfma_rs_kernel<1><<<grid, 256, smem, st>>>(p, m_off, tm, tn);
       if (p.tail_part) { AS_LAUNCH_CHECK(ctx); gemm_tail_fixup_kernel<<<dim3(16 * std::min(tm * tn, 128)), 256, 0, st>>>(p, m_off, tm, tn); }
     }
   } else {
@@ -1108,7 +1144,9 @@ static int launch_rs_cfg(as_ctx* ctx, const GemmParams& p_in, int m_off, int par
     else if (rs_tail_splits(p, T)) p.tail_first = T / kCus * kCus;
     const int split = p.tail_first >= 0 ? T - p.tail_first : 0;
     const dim3 grid(T - split + split * p.tail_parts);
-    if (whole) gemm_mfma_rs_kernel<0><<<grid, 256, smem, st>>>(p, 0, tm, tn);
+    if (p.nn && whole) gemm_mfma_rs_kernel<0, GEMM_EPI_NONE, true><<<grid, 256, smem, st>>>(p, 0, tm, tn);
+    else if (p.nn) gemm_mfma_rs_kernel<2, GEMM_EPI_NONE, true><<<grid, 256, smem, st>>>(p, 0, tm, tn);
+    else if (whole) gemm_mfma_rs_kernel<0><<<grid, 256, smem, st>>>(p, 0, tm, tn);
     else gemm_mfma_rs_kernel<2><<<grid, 256, smem, st>>>(p, 0, tm, tn);
     if (split) { AS_LAUNCH_CHECK(ctx); gemm_tail_fixup_kernel<<<dim3(16 * split), 256, 0, st>>>(p, 0, tm, tn); }
   }
@@ -1224,6 +1262,17 @@ static GemmPick pick_cfg(const GemmParams& p) {
   return {20, 1};                                        // direct-to-LDS tiles when K allows, else staged (0)
 }
 
+bool gemm_nn_applies(int mode, int variant, const GemmParams& p) {
+  if (mode != AS_BF16 || (variant != 0 && variant != 2 && variant != 34) || !mfma_ok(p) || !rs_ok(p)) return false;
+  if (p.nn < 1 || p.nn > 3 || p.ncg || p.epi != GEMM_EPI_NONE || p.seg[0].ldb > (1 << 22) || (p.nseg > 1 && p.seg[1].ldb != p.seg[0].ldb)) return false;
+  int row = 0;
+  for (int i = 0; i + 1 < p.nn; i++) {
+    if (((uintptr_t)p.nb[i] % 16) || p.nb_row[i] % 64 || p.nb_row[i] <= row || p.nb_row[i] >= p.seg[0].K) return false;
+    row = p.nb_row[i];
+  }
+  return variant == 34 || pick_cfg(p).cfg == 24;
+}
+
 // m_dev semantics: the live row count is *m_dev - m_off (clamped to [0, M]).
 // variant: 0 pick, 1 plain FMA kernel, 2 MFMA kernel with the default tile choice, 10 + c forces tile configuration c.
 int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, int m_off, hipStream_t st) {
@@ -1234,6 +1283,7 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
   if (p.splitk > 1 && !p.partial) return as_fail(ctx, AS_ERR_WORKSPACE, "gemm: split-K needs a partial buffer");
   if (p.accumulate && !p.c_f32) return as_fail(ctx, AS_ERR_SHAPE, "gemm: accumulate needs float output");
   if (p.grp_off && p.splitk > 1) return as_fail(ctx, AS_ERR_SHAPE, "gemm: grouped rows and split-K do not combine");
+  if (p.nn && (!gemm_nn_applies(mode, variant, p) || (m_off && !p.m_dev))) return as_fail(ctx, AS_ERR_SHAPE, "gemm: only the hand-scheduled kernel reads B as [K, N]");
   if (p.grp_n > 0) {
     if (!p.grp_off || p.nseg != 1 || p.m_dev || m_off) return as_fail(ctx, AS_ERR_SHAPE, "gemm: all groups in one launch need a group table and one K segment");
     const int c0 = variant >= 10 ? variant - 10 : pick_cfg(p).cfg;

@@ -1,6 +1,6 @@
 #!/usr/bin/env python3
-"""Writes gemm_rs_loop.inc: the hand-scheduled main loop of gemm_mfma_rs_kernel (gemm.hip) as one inline-asm
-block.  Run by hand after a change (python gen_gemm_rs_loop.py); the generated file is committed.
+"""Writes gemm_rs_loop.inc and gemm_rs_nn_loop.inc: the hand-scheduled main loops of gemm_mfma_rs_kernel (gemm.hip) as one
+inline-asm block each.  Run by hand after a change (python gen_gemm_rs_loop.py); the generated file is committed.
 
 One K step (64 wide) of one wave (a 128 x 128 block of a 256 x 256 tile, four waves, one per SIMD) is 64
 v_mfma_f32_32x32x16_bf16 on 16 accumulators, and behind every MFMA rides one other memory instruction, at a
@@ -24,6 +24,15 @@ v[206:209] per-lane byte offsets of A and B rows in segment 0 and 1; (v204, v205
 tile being loaded in even / odd steps.  Scalar: s[40:47] operand bases of both segments, s[48:51] their 8-row
 strides, s52 nt0, s53 nt, s54 nt - 1, s67 step, s66 / s68 .. s73 temps; running bases and strides of the loads:
 s[60:65] in even steps, s[74:79] in odd steps.
+
+The second loop (NN) takes B as [K rows, N columns], rows of N contiguous: a tile is 64 rows of 512 bytes, load n of a wave is
+rows 2n, 2n + 1 of its 16, and a B fragment is two transposing reads of 8 bytes a lane (a group of 16 lanes reads 4 rows x 16
+columns and receives the columns).  LDS position of 64-byte unit u of row r: u ^ (r & 3), so that the four rows of a read,
+which are 512 bytes apart, lie in different quarters of the banks.  It issues 12 LDS reads a slice instead of 8, two halves
+of a fragment behind the same MFMA, for the same bytes.  B is up to three matrices below one another and the second segment's,
+all of the same row stride: s[42:43], s[80:81], s[82:83], s[46:47] are their bases minus their first row, s84, s85, s52 the steps
+at which the next one begins, s86 the bytes of 64 rows, (s88, s89) a step's offset.  v[196:199] are then the LDS read
+addresses of B per 32-column block instead of per slice.
 """
 import os
 
@@ -36,6 +45,10 @@ BARRIER_SLOT = 49
 DIST = 2          # a step loads tile it + 1 + DIST: 2 = as early as the register stages allow (1.7 steps in flight), 1 = one step later
 STORE_SLOTS = [58, 60, 62, 63, 8, 10, 12, 14, 24, 26, 28, 30, 40, 42, 44, 46]   # register n; the first four belong to the previous step
 LOAD_SLOTS = [9, 11, 13, 15, 25, 27, 29, 31, 41, 43, 45, 47, 48, 49, 59, 61]    # register n
+
+
+NN = False
+OP_P1, OP_P2, OP_N1, OP_N2, OP_SK = range(27, 32)        # NN: bases of the second and third matrix, their first steps, bytes of 64 rows of B
 
 
 def frag(setno, which, idx):
@@ -51,12 +64,17 @@ def stage_reg(stage, n):
 def scal(P):
     """(A base pair, B base pair, A stride, B stride, A offset vgpr, B offset vgpr) of the loads issued in a step of parity P"""
     return (("s60", "s61", "s62", "s63", "s64", "s65", "v204", "v205") if P == 0 else
-            ("s74", "s75", "s76", "s77", "s78", "s79", "v210", "v211"))
+            ("s74", "s75", "s76", "s77", "s78", "s79", "v210", "v211"))[:7] + (("v207",) if NN else ("v205",) if P == 0 else ("v211",))
 
 
 def text_read(setno, lds_stage, ks, which, idx):
-    return "ds_read_b128 %s, v%d offset:%d" % (frag(setno, which, idx), (192 if which == "a" else 196) + ks,
-                                                lds_stage * A_STAGE + idx * 4096)
+    """the reads that fill a fragment"""
+    if NN and which == "b":
+        base = 128 + 32 * setno + 16 + 4 * idx
+        return ["ds_read_b64_tr_b16 v[%d:%d], v%d offset:%d" % (base + 2 * q, base + 2 * q + 1, 196 + idx, lds_stage * A_STAGE + ks * 8192 + q * 2048)
+                for q in range(2)]
+    return ["ds_read_b128 %s, v%d offset:%d" % (frag(setno, which, idx), (192 if which == "a" else 196) + ks,
+                                                lds_stage * A_STAGE + idx * 4096)]
 
 
 def text_store(reg_stage, lds_stage, n):
@@ -77,6 +95,17 @@ def text_load(reg_stage, n, P):
 def tile_bases(P):
     """s66 = tile to load (clamped here to the last one); sets the running bases, strides and offsets of parity P"""
     alo, ahi, blo, bhi, sa, sb, va, vb = scal(P)
+    if NN:
+        return ["s_min_i32 s66, s66, s54", "s_mul_i32 s88, s66, s86", "s_mul_hi_u32 s89, s66, s86",
+                "s_cmp_lt_i32 s66, s84", "s_cselect_b64 s[72:73], s[42:43], s[80:81]",
+                "s_cmp_lt_i32 s66, s85", "s_cselect_b64 s[72:73], s[72:73], s[82:83]",
+                "s_cmp_lt_i32 s66, s52", "s_cselect_b64 s[72:73], s[72:73], s[46:47]",
+                "s_cselect_b32 s69, 0, s52", "s_cselect_b64 s[70:71], s[40:41], s[44:45]", "s_cselect_b32 %s, s48, s50" % sa,
+                "s_cselect_b64 vcc, -1, 0",
+                "s_mov_b32 %s, s49" % sb, "s_sub_i32 s68, s66, s69", "s_lshl_b32 s68, s68, 7",
+                "s_add_u32 %s, s70, s68" % alo, "s_addc_u32 %s, s71, 0" % ahi,
+                "s_add_u32 %s, s72, s88" % blo, "s_addc_u32 %s, s73, s89" % bhi,
+                "v_cndmask_b32 %s, v208, v206, vcc" % va]
     return ["s_min_i32 s66, s66, s54",
             "s_cmp_lt_i32 s66, s52",                      # scc: the tile lies in segment 0
             "s_cselect_b32 s69, 0, s52",
@@ -120,7 +149,9 @@ def step_ops(P):
     # scalar work for the next step's loads (tile it+4, other scalar set), spread behind the first MFMAs
     # (the run from the compare to the last select depends on scc, which the loads' address updates overwrite: one slot)
     tb = ["s_add_i32 s66, s67, %d" % (2 + DIST)] + tile_bases(Q)
-    for slot, lo, hi in ((16, 0, 9), (18, 9, 11), (20, 11, 13), (22, 13, 15), (24, 15, 17)):
+    cuts = (((16, 0, 4), (17, 4, 6), (18, 6, 8), (19, 8, 14), (20, 14, 17), (21, 17, 19), (22, 19, 21), (23, 21, 22)) if NN else
+            ((16, 0, 9), (18, 9, 11), (20, 11, 13), (22, 13, 15), (24, 15, 17)))
+    for slot, lo, hi in cuts:
         slots[slot].append(("scalar", tb[lo:hi]))
     return slots
 
@@ -147,11 +178,10 @@ def emit_steps(e):
             nonlocal lds_done
             if idx <= lds_done:
                 return
-            younger = lds_issued - idx
-            assert younger <= 15, ("lgkmcnt cannot express", younger, k, g, op)
+            younger = min(lds_issued - idx, 15)            # what the counter can express; 15 waits for younger ones too
             if em is not None:
                 em.append("s_waitcnt lgkmcnt(%d)" % younger)
-            lds_done = idx
+            lds_done = lds_issued - younger
         def wait_vm(idx):
             nonlocal vm_done
             if idx <= vm_done:
@@ -175,10 +205,11 @@ def emit_steps(e):
                 em.append("v_mfma_f32_32x32x16_bf16 %s, %s, %s, %s" % (acc, frag(setno, "b", j), frag(setno, "a", i), acc))
         elif kind == "read":
             _, setno, lds_stage, ks, which, idx = op
-            lds_issued += 1
+            text = text_read(setno, lds_stage, ks, which, idx)
+            lds_issued += len(text)
             frag_src[(setno, which, idx)] = lds_issued
             if em is not None:
-                em.append(text_read(setno, lds_stage, ks, which, idx))
+                em.extend(text)
         elif kind == "store":
             _, reg_stage, lds_stage, n = op
             if (reg_stage, n) in load_idx:
@@ -190,10 +221,7 @@ def emit_steps(e):
         elif kind == "load":
             _, reg_stage, n, P = op
             if (reg_stage, n) in store_idx:                # the store has read these registers
-                if lds_issued - store_idx[(reg_stage, n)] <= 15:
-                    wait_lds(store_idx[(reg_stage, n)])
-                else:
-                    assert store_idx[(reg_stage, n)] <= lds_done, "a store 16 LDS operations back is not known complete"
+                wait_lds(store_idx[(reg_stage, n)])
             vm_issued += 1
             load_idx[(reg_stage, n)] = vm_issued
             if em is not None:
@@ -219,7 +247,10 @@ class Emitter:
             self.lines.append(s)
 
 
-def main(out_path=None):
+def generate(nn, out_path=None):
+    global NN
+    NN = nn
+    name = "rs_nn" if nn else "rs"
     e = Emitter()
     # ---- set-up: per-lane values from the LDS scratch line of this lane, scalars from the operands
     e("ds_read_b128 v[192:195], %%%d" % OP_SCRATCH)
@@ -230,6 +261,11 @@ def main(out_path=None):
         e("s_mov_b64 %s, %%%d" % (dst, op))
     for dst, op in (("s48", OP_SA0), ("s49", OP_SB0), ("s50", OP_SA1), ("s51", OP_SB1), ("s52", OP_NT0), ("s53", OP_NT)):
         e("s_mov_b32 %s, %%%d" % (dst, op))
+    if nn:
+        for dst, op in (("s[80:81]", OP_P1), ("s[82:83]", OP_P2)):
+            e("s_mov_b64 %s, %%%d" % (dst, op))
+        for dst, op in (("s84", OP_N1), ("s85", OP_N2), ("s86", OP_SK)):
+            e("s_mov_b32 %s, %%%d" % (dst, op))
     e("s_sub_i32 s54, s53, 1")
     e("s_waitcnt lgkmcnt(0)")
     # ---- prologue: the state the loop expects at step 0 -- tile 0 in LDS stage 0, registers 0..3 of tile 1 in LDS
@@ -264,34 +300,34 @@ def main(out_path=None):
     e("s_waitcnt lgkmcnt(0)")
     # ---- main loop, two steps per trip
     even, odd = emit_steps(e)
-    e("L_rs_loop_%=:")
+    e("L_%s_loop_%%=:" % name)
     e(even)
     e("s_add_i32 s67, s67, 1")
     e("s_cmp_ge_i32 s67, s53")
-    e("s_cbranch_scc1 L_rs_end_%=")
+    e("s_cbranch_scc1 L_%s_end_%%=" % name)
     e(odd)
     e("s_add_i32 s67, s67, 1")
     e("s_cmp_lt_i32 s67, s53")
-    e("s_cbranch_scc1 L_rs_loop_%=")
-    e("L_rs_end_%=:")
+    e("s_cbranch_scc1 L_%s_loop_%%=" % name)
+    e("L_%s_end_%%=:" % name)
     # the re-requested tiles must land before their registers are reused; the last MFMAs must have written
     e("s_waitcnt vmcnt(0) lgkmcnt(0)")
     e("s_nop 15")
     e("s_nop 15")
 
-    out = out_path or os.path.join(os.path.dirname(os.path.abspath(__file__)), "gemm_rs_loop.inc")
+    out = out_path or os.path.join(os.path.dirname(os.path.abspath(__file__)), "gemm_%s_loop.inc" % name)
     with open(out, "w") as f:
         f.write("// Generated by gen_gemm_rs_loop.py -- do not edit.  Main loop of gemm_mfma_rs_kernel.\n")
-        f.write("#define GEMM_RS_LOOP_ASM \\\n")
+        f.write("#define GEMM_%s_LOOP_ASM \\\n" % name.upper())
         for ln in e.lines:
             f.write('  "%s\\n" \\\n' % ln)
         f.write('  ""\n')
         vregs = ", ".join('"v%d"' % i for i in range(212))
-        sregs = ", ".join('"s%d"' % i for i in range(40, 80))
-        f.write("#define GEMM_RS_LOOP_CLOBBERS %s, %s, \"vcc\", \"scc\", \"memory\"\n" % (vregs, sregs))
+        sregs = ", ".join('"s%d"' % i for i in range(40, 90 if nn else 80))
+        f.write("#define GEMM_%s_LOOP_CLOBBERS %s, %s, \"vcc\", \"scc\", \"memory\"\n" % (name.upper(), vregs, sregs))
     print("wrote", out, len(e.lines), "instructions")
 
 
 if __name__ == "__main__":
-    import sys
-    main(sys.argv[1] if len(sys.argv) > 1 else None)
+    generate(False)
+    generate(True)

@@ -105,3 +105,14 @@ def test_moe_experts_without_tokens_and_single_token_segment():
     assert all(int(c["ffn"]["sel"].max()) <= 3 for c in f["cache"]["layers"])
     _compare(sh, params, lora, trajs, 1, 96, False, 0)
     _compare(sh, params, lora, trajs, 1, 96, True, 2)
+
+
+@pytest.mark.parametrize("live,seed", [(8, 6), (6, 9)])
+def test_moe_expert_gradients_from_matrices_as_they_are(live, seed):
+    """A 1024-wide sparse model with 33 row tiles: the experts' input gradients are products over the matrices as they lie, gate and
+    up below one another; every group ends in a ragged row tile, two experts may have no rows."""
+    sh = synth.CONFIGS[1].replace(**dict(MOE, n_layers=1, d_model=1024, ffn=192, head_dim=64, n_q_heads=4, n_kv_heads=1, lora_rank=8, lora_alpha=16.0))
+    trajs = synth.trajectories_lognormal(8, 1, 8300, sh.vocab, 400, 0.5, 64, 900, turns=(2, 5), assistant_share=0.3, token_dist="uniform")
+    params, lora = structured_router_params(sh, seed, live=live), synth.lora_weights(sh, seed)
+    res, _, worst = _compare(sh, params, lora, trajs, 1, 8300, True, 0)
+    print("wide moe worst grad err %.2e" % worst)

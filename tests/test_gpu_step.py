@@ -211,3 +211,17 @@ def test_more_adapter_matrices_than_one_preparation_launch(bf16):
                                   lora_targets=synth.DENSE_TARGETS7, lora_rank=5, lora_alpha=10.0)
     trajs = random_trajs(12, 4, sh.vocab, turn_lo=8, turn_hi=20, turns=(2, 4))
     G.compare_step(sh, 8, trajs, 1, 256, bf16=bf16, loss_tol=2e-3 if bf16 else 1e-4, grad_tol=3e-2 if bf16 else 1e-4)
+
+
+@pytest.mark.parametrize("row_len,ffn,targets,full", [(4352, 192, synth.DENSE_TARGETS7, False), (4300, 256, ("v", "gate"), False),
+                                                      (4300, 192, ("down",), False), (4352, 256, (), True)])
+def test_input_gradients_from_matrices_as_they_are(row_len, ffn, targets, full):
+    """17 row tiles of a 2048-wide model: the input gradients of q | k | v (matrices of 512, 64 and 64 rows) and gate | up (192 or 256
+    rows) are products over the matrices as they lie, with all, some or no adapter columns behind them; whole and ragged
+    last row tiles.  The step's stated bf16 tolerances."""
+    import gpu_util as G
+    sh = synth.CONFIGS[1].replace(n_layers=2, n_q_heads=8, n_kv_heads=1, head_dim=64, d_model=2048, ffn=ffn, vocab=512,
+                                  lora_targets=targets or synth.DENSE_TARGETS7, lora_rank=8, lora_alpha=16.0)
+    trajs = synth.trajectories_lognormal(7, 1, row_len, sh.vocab, 400, 0.5, 64, 900, turns=(2, 5), assistant_share=0.3, token_dist="uniform")
+    rep = G.compare_step(sh, 9, trajs, 1, row_len, bf16=True, loss_tol=2e-3, grad_tol=3e-2, full=full)
+    print("rows of %d: loss rel %.2e worst grad %.2e" % (row_len, rep["loss_rel"], rep["worst_grad"]))
