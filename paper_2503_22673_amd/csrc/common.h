@@ -110,6 +110,10 @@ struct GemmParams {
   // nn <= 3 matrices below one another: seg[0].B, and from row nb_row[i] (a multiple of 64) on nb[i].  Hand-scheduled kernel only: ask
   // gemm_nn_applies first.
   int nn; const void* nb[2]; int nb_row[2];
+  // tn: A of the one segment is [K, M] and B [K, N] (hand-scheduled kernel only: gemm_tn_applies), float result.  Its rows may be those of
+  // several matrices: from row rg_row[i] (a multiple of 256) on they go to rg_C[i], all with row stride ldc.  k_dev: the
+  // contraction ends with row *k_dev - k_off (rows up to the next multiple of 64 must be zero in both operands).
+  int tn; const int* k_dev; int k_off; int nrg; void* rg_C[2]; int rg_row[2];
   int epi; const float* epi_lse; const int32_t* epi_lab; const float* epi_w; const int32_t* epi_cnt; float* epi_part;
 };
 enum { GEMM_EPI_NONE = 0, GEMM_EPI_STATS = 1, GEMM_EPI_PROB = 2 };
@@ -117,6 +121,7 @@ enum { GEMM_EPI_NONE = 0, GEMM_EPI_STATS = 1, GEMM_EPI_PROB = 2 };
 bool gemm_rs_applies(int mode, const GemmParams& p);
 // the launch (p.nn set) would go to the hand-scheduled kernel, which alone reads B as [K, N]
 bool gemm_nn_applies(int mode, int variant, const GemmParams& p);
+bool gemm_tn_applies(int mode, int variant, const GemmParams& p);
 // floats of scratch (GemmParams::tail_part given by the caller through `tail_ws`) that let the launcher split the last round
 constexpr size_t kGemmTailFloats = (size_t)128 * 2 * 256 * 256;
 int launch_gemm(as_ctx* ctx, int mode, int variant, const GemmParams& p, hipStream_t st);
@@ -218,6 +223,7 @@ constexpr int kPrepBatch = 48;                             // a batch is a kerne
 struct PrepBatch { PrepMatrix m[kPrepBatch]; int n, n_tiles; };
 int launch_lora_prep_batch(as_ctx* ctx, int mode, const PrepBatch& b, hipStream_t st);
 int launch_fill_zero(as_ctx* ctx, void* p, size_t bytes, hipStream_t st);
+int launch_zero_tail_rows(as_ctx* ctx, int rows, const int* n_dev, int off, void* a, int64_t lda, int ca, void* b, int64_t ldb, int cb, hipStream_t st);
 int launch_select_targets(as_ctx* ctx, const int32_t* seg_start, const uint8_t* mask, const int32_t* tok,
                           int n, int32_t* tgt_idx, int32_t* tgt_pos, int32_t* labels, int32_t* count,
                           hipStream_t st);

@@ -776,6 +776,22 @@ int launch_fill_zero(as_ctx* ctx, void* p, size_t bytes, hipStream_t st) {
   return AS_OK;
 }
 
+// Rows live .. of two bf16 matrices up to the next multiple of 64 become zero (a contraction over rows runs in steps of 64); live = rows, or
+// *n_dev - off within [0, rows].  Column counts are multiples of 8.
+__global__ __launch_bounds__(256) void zero_tail_rows_kernel(int rows, const int* n_dev, int off, bf16_t* a, int64_t lda, int ca, bf16_t* b, int64_t ldb, int cb) {
+  const int live = n_dev ? min(max(*n_dev - off, 0), rows) : rows, r = live + blockIdx.x;
+  if (r >= (live + 63) / 64 * 64) return;
+  const uint4 z = make_uint4(0u, 0u, 0u, 0u);
+  for (int c = (blockIdx.y * 256 + threadIdx.x) * 8; c < ca; c += gridDim.y * 2048) *reinterpret_cast<uint4*>(a + (int64_t)r * lda + c) = z;
+  for (int c = (blockIdx.y * 256 + threadIdx.x) * 8; c < cb; c += gridDim.y * 2048) *reinterpret_cast<uint4*>(b + (int64_t)r * ldb + c) = z;
+}
+int launch_zero_tail_rows(as_ctx* ctx, int rows, const int* n_dev, int off, void* a, int64_t lda, int ca, void* b, int64_t ldb, int cb, hipStream_t st) {
+  if (!n_dev && rows % 64 == 0) return AS_OK;
+  zero_tail_rows_kernel<<<dim3(63, (unsigned)std::min<int64_t>(16, cdiv(std::max(ca, cb), 2048))), 256, 0, st>>>(rows, n_dev, off, (bf16_t*)a, lda, ca, (bf16_t*)b, ldb, cb);
+  AS_LAUNCH_CHECK(ctx);
+  return AS_OK;
+}
+
 // ---------------------------------------------------------- target selection
 // Position t is a target when t+1 exists, starts no segment, and carries the
 // mask.  One block scans the whole stream so the order is fixed.

@@ -5,7 +5,7 @@
 //
 // Kernels:
 //  * gemm_fma_kernel        -- any type, any shape; fp32 FMAs.  The fp32 tier runs on it.
-//  * gemm_mfma_rs_kernel    -- bf16, hand-scheduled 256x256 tiles: the large products.
+//  * gemm_mfma_rs_kernel    -- bf16, hand-scheduled 256x256 tiles: the large products; also with B, or A and B, given by rows of K.
 //  * gemm_mfma_ring_kernel  -- bf16, 128x128 and 64x64 tiles in a ring of LDS stages: few rows or narrow outputs.
 //  * gemm_mfma_dlds_kernel, gemm_mfma_kernel -- bf16: K that is no multiple of 64, rows counted on the device that the
 //    hand-scheduled kernel does not take, rows that are not 16-byte aligned.
@@ -835,23 +835,35 @@ __device__ __forceinline__ void gemm_epilogue_stats(const GemmParams& p, f32x16 
 // LIVE = 1: the row count is a device-side value and / or the rows are those of one group (expert).  Tiles past the live
 // rows exit; a tile still computes 256 rows, moved up if need be so that they lie inside the `limit` rows the operands
 // are known to have (M for a plain row count, rows_cap for grouped rows), and writes the rows that are its own and live.
-// NN: B is taken as [K, N] rows (gemm_rs_nn_loop.inc), the layout of a weight matrix in the product with its output
+// LAYOUT 1, NN: B is taken as [K, N] rows (gemm_rs_nn_loop.inc), the layout of a weight matrix in the product with its output
 // gradient: the matrix does not have to be transposed first.  The loop is the same but for half-width, transposing reads of B, and so
 // is its rate: steps of 16384 tokens on a dense 8B model and of 8192 tokens on a sparse 8x7B one lost 700 us of 33.1 ms and 1150 us
 // of 15.0 ms, the time of the copies, and nothing else changed.
 #include "gemm_rs_loop.inc"
+// LAYOUT 2, TN: A as [K, M] too (gemm_rs_tn_loop.inc): the gradient of a weight matrix, tokens contracted, from the output gradient and
+// the input as they are.  Full step of one 1B layer at 16384 tokens, 4350 of them targets: 8.00 ms with token-major copies (600 us),
+// one launch per matrix and the head's gradient contracted over whole chunks; 6.28 ms so, the head over its live rows.
 #include "gemm_rs_nn_loop.inc"
+#include "gemm_rs_tn_loop.inc"
+enum { RS_NT = 0, RS_NN = 1, RS_TN = 2 };
 // Rows counted on the device, with scratch for partial sums: the contraction of every tile is split over as many workgroups as
 // fit one round, up to kLiveParts.  Host code cannot know the count, so both launches work the split out from it.
 constexpr int kLiveParts = 16;
 __device__ __forceinline__ int live_parts(const GemmParams& p, int tiles) {
   return p.tail_part && tiles > 0 && tiles <= 128 ? min(kLiveParts, 256 / tiles) : 1;
 }
+// the matrix that a result row lies in, minus the rows above it (float results, whole tiles per group)
+__device__ __forceinline__ void* row_group_base(const GemmParams& p, int row) {
+  int g = 0;
+  while (g < p.nrg && row >= p.rg_row[g]) g++;
+  return g ? (float*)p.rg_C[g - 1] - (int64_t)p.rg_row[g - 1] * p.ldc : (float*)p.C;
+}
 // EPI: the epilogue is a compile-time choice (GEMM_EPI_*), so that the head's epilogues, which need registers of their own,
 // cost the projection GEMMs nothing.
-template <int LIVE, int EPI = GEMM_EPI_NONE, bool NN = false>
+template <int LIVE, int EPI = GEMM_EPI_NONE, int LAYOUT = RS_NT>
 __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_off, int tiles_m, int tiles_n) {
   constexpr int BM = 256, BN = 256, BK = 64, TM = 4, TN = 4;
+  constexpr bool NN = LAYOUT != RS_NT, AK = LAYOUT == RS_TN;      // B is [K, N]; A is [K, M]
   extern __shared__ __align__(16) unsigned char smem[];
   int rb = 0, mlive = p.M;
   if (LIVE == 1) {
@@ -902,6 +914,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
   const int wm = wave >> 1, wn = wave & 1;
   int nt0 = p.seg[0].K / BK, nt = nt0 + (p.nseg > 1 ? p.seg[1].K / BK : 0);
   const GemmSeg s0 = p.seg[0], s1 = p.nseg > 1 ? p.seg[1] : p.seg[0];
+  if (AK && p.k_dev) nt0 = nt = min(nt, (max(*p.k_dev - p.k_off, 0) + BK - 1) / BK);
+  if (AK && nt == 0 && p.accumulate && kpart < 0) return;
   int64_t k_skip = 0;                                    // elements of segment 0 this workgroup starts behind
   if (kpart >= 0) {                                      // steps [lo, hi) of the contraction; the launcher made sure that every part starts inside segment 0
     const int lo = (int)((int64_t)nt * kpart / parts), hi = (int)((int64_t)nt * (kpart + 1) / parts);
@@ -926,7 +940,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
       line[0][ks] = (unsigned)((wm * 128 + l31) * 128) + c;                    // fragment reads of A
       line[1][ks] = 65536u + (unsigned)((wn * 128 + l31) * 128) + c;           // ... of B
       // NN: by column block ks; this lane's 8 bytes of the 4 x 16 patch, 64-byte unit u of row r at u ^ (r & 3)
-      if (NN) line[1][ks] = 65536u + (unsigned)((8 * hh + ((lane >> 2) & 3)) * 512 + wn * 256 + ((ks ^ ((lane >> 2) & 3)) * 64) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8);
+      const unsigned tr = (unsigned)((8 * hh + ((lane >> 2) & 3)) * 512 + ((ks ^ ((lane >> 2) & 3)) * 64) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8);
+      if (NN) line[1][ks] = 65536u + tr + (unsigned)(wn * 256);
+      if (AK) line[0][ks] = tr + (unsigned)(wm * 256);
     }
     const unsigned wrow = (unsigned)((wave * 64 + lrow) * 128);
     line[2][0] = wrow + (unsigned)((lch ^ (lrow >> 1)) * 16);                  // LDS stores, even / odd load
@@ -935,9 +951,11 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
     if (NN) {                                            // rows 2 i, 2 i + 1 of the wave's sixteen, half a wave each
       const unsigned r = (unsigned)(wave * 16 + hh) * 512u + 65536u, in = (unsigned)((l31 & 3) * 16), u = (unsigned)(l31 >> 2);
       line[2][2] = r + ((u ^ (unsigned)hh) * 64u) + in; line[2][3] = r + ((u ^ (unsigned)(hh + 2)) * 64u) + in;
+      if (AK) { line[2][0] = line[2][2] - 65536u; line[2][1] = line[2][3] - 65536u; }
     }
     line[3][0] = (unsigned)((lrow * s0.lda + lch * 8) * 2); line[3][1] = (unsigned)((lrow * s0.ldb + lch * 8) * 2);
     line[3][2] = (unsigned)((lrow * s1.lda + lch * 8) * 2); line[3][3] = (unsigned)((lrow * s1.ldb + lch * 8) * 2);
+    if (AK) line[3][0] = line[3][2] = (unsigned)((hh * s0.lda + l31 * 8) * 2);
     if (NN) line[3][1] = line[3][3] = (unsigned)((hh * s0.ldb + l31 * 8) * 2);
     u32x4* scratch = reinterpret_cast<u32x4*>(smem + 131072 + tid * 64);
 #pragma unroll
@@ -957,7 +975,17 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
     const uint64_t A1 = (uint64_t)((const bf16_t*)s1.A + a2off + (int64_t)(row0 + wave * 64) * s1.lda);
     const uint64_t B1 = (uint64_t)(b1p + (int64_t)(colg + wave * 64) * s1.ldb);
     const int sA0 = (int)(16 * s0.lda), sB0 = (int)(16 * s0.ldb), sA1 = (int)(16 * s1.lda), sB1 = (int)(16 * s1.ldb);   // 8 rows, bytes
-    if constexpr (NN) {
+    if constexpr (AK) {
+      const uint64_t At = (uint64_t)((const bf16_t*)s0.A + (k_skip + wave * 16) * s0.lda + row0), Bt = (uint64_t)(b0p + (k_skip + wave * 16) * s0.ldb + col0);
+      const int sA = (int)(4 * s0.lda), sB = (int)(4 * s0.ldb), kA = (int)(128 * s0.lda), kB = (int)(128 * s0.ldb);   // two rows, 64 rows, bytes
+      asm volatile(GEMM_RS_TN_LOOP_ASM
+                   : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[0][2]), "+a"(acc[0][3]),
+                     "+a"(acc[1][0]), "+a"(acc[1][1]), "+a"(acc[1][2]), "+a"(acc[1][3]),
+                     "+a"(acc[2][0]), "+a"(acc[2][1]), "+a"(acc[2][2]), "+a"(acc[2][3]),
+                     "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][2]), "+a"(acc[3][3])
+                   : "v"(scratch_addr), "s"(At), "s"(Bt), "s"(At), "s"(Bt), "s"(sA), "s"(sB), "s"(sA), "s"(sB), "s"(nt), "s"(nt), "s"(kA), "s"(kB)
+                   : GEMM_RS_TN_LOOP_CLOBBERS);
+    } else if constexpr (NN) {
       const int64_t ldb = s0.ldb, row_w = (int64_t)(wave * 16) * ldb + col0, lo = k_skip / BK;
       // base of a matrix minus its first row: step t of this workgroup reads rows 64 t .. of it
       auto base = [&](const void* m, int64_t first_row) {
@@ -993,6 +1021,11 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
   }
   if constexpr (EPI == GEMM_EPI_STATS) { gemm_epilogue_stats<TM, TN, LIVE != 0>(p, acc, row0 + wm * TM * 32 + l31, (col0 + wn * TN * 32) / 128, hh, row_lo, row_hi); return; }
   if constexpr (EPI == GEMM_EPI_PROB) { gemm_epilogue_staged<TM, TN, LIVE != 0, true>(p, acc, smem, wave, lane, row0 + wm * TM * 32, col0 + wn * TN * 32, row_lo, row_hi); return; }
+  if constexpr (AK) {
+    GemmParams q = p; q.C = row_group_base(p, row0);
+    gemm_epilogue_rows<TM, TN, false>(q, acc, row0 + wm * TM * 32 + l31, col0 + wn * TN * 32 + 4 * hh);
+    return;
+  }
   const bool staged = !p.c_f32 && !(p.ldc % 8) && (!p.R || (!(p.ldr % 8) && !((uintptr_t)p.R % 16)));
   if (staged) gemm_epilogue_staged<TM, TN, LIVE != 0>(p, acc, smem, wave, lane, row0 + wm * TM * 32, col0 + wn * TN * 32, row_lo, row_hi);
   else gemm_epilogue_rows<TM, TN, LIVE != 0>(p, acc, row0 + wm * TM * 32 + l31, col0 + wn * TN * 32 + 4 * hh, row_lo, row_hi);
@@ -1057,7 +1090,7 @@ __global__ __launch_bounds__(256) void gemm_tail_fixup_kernel(GemmParams p, int 
 #pragma unroll
         for (int k = 0; k < 4; k++) v[k] += (float)x[k]; }
       if (p.c_f32) {
-        f32x4* q = reinterpret_cast<f32x4*>((float*)p.C + row * p.ldc + col);
+        f32x4* q = reinterpret_cast<f32x4*>((float*)(p.nrg ? row_group_base(p, row0) : p.C) + row * p.ldc + col);
         if (p.accumulate) v += *q;
         *q = v;
       } else {
@@ -1116,9 +1149,10 @@ static int launch_rs_cfg(as_ctx* ctx, const GemmParams& p_in, int m_off, int par
   AS_SET_SMEM(ctx, gemm_mfma_rs_kernel<0>, smem);
   AS_SET_SMEM(ctx, gemm_mfma_rs_kernel<1>, smem);
   AS_SET_SMEM(ctx, gemm_mfma_rs_kernel<2>, smem);
-  AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<0, GEMM_EPI_NONE, true>), smem);
-  AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<1, GEMM_EPI_NONE, true>), smem);
-  AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<2, GEMM_EPI_NONE, true>), smem);
+  AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<0, GEMM_EPI_NONE, RS_NN>), smem);
+  AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<1, GEMM_EPI_NONE, RS_NN>), smem);
+  AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<0, GEMM_EPI_NONE, RS_TN>), smem);
+  AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<2, GEMM_EPI_NONE, RS_NN>), smem);
   AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<1, GEMM_EPI_STATS>), smem);
   AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<1, GEMM_EPI_PROB>), smem);
   const int tn = p.N / 256;
@@ -1131,7 +1165,7 @@ static int launch_rs_cfg(as_ctx* ctx, const GemmParams& p_in, int m_off, int par
     else {
       if (!live_split_ok(p)) p.tail_part = nullptr;
       const dim3 grid(p.tail_part ? std::max(tm * tn, kCus) : tm * tn);
-      if (p.nn) gemm_mfma_rs_kernel<1, GEMM_EPI_NONE, true><<<grid, 256, smem, st>>>(p, m_off, tm, tn);
+      if (p.nn) gemm_mfma_rs_kernel<1, GEMM_EPI_NONE, RS_NN><<<grid, 256, smem, st>>>(p, m_off, tm, tn);
       else gemm_mfma_rs_kernel<1><<<grid, 256, smem, st>>>(p, m_off, tm, tn);
       if (p.tail_part) { AS_LAUNCH_CHECK(ctx); gemm_tail_fixup_kernel<<<dim3(16 * std::min(tm * tn, 128)), 256, 0, st>>>(p, m_off, tm, tn); }
     }
@@ -1144,8 +1178,9 @@ static int launch_rs_cfg(as_ctx* ctx, const GemmParams& p_in, int m_off, int par
     else if (rs_tail_splits(p, T)) p.tail_first = T / kCus * kCus;
     const int split = p.tail_first >= 0 ? T - p.tail_first : 0;
     const dim3 grid(T - split + split * p.tail_parts);
-    if (p.nn && whole) gemm_mfma_rs_kernel<0, GEMM_EPI_NONE, true><<<grid, 256, smem, st>>>(p, 0, tm, tn);
-    else if (p.nn) gemm_mfma_rs_kernel<2, GEMM_EPI_NONE, true><<<grid, 256, smem, st>>>(p, 0, tm, tn);
+    if (p.tn) gemm_mfma_rs_kernel<0, GEMM_EPI_NONE, RS_TN><<<grid, 256, smem, st>>>(p, 0, tm, tn);
+    else if (p.nn && whole) gemm_mfma_rs_kernel<0, GEMM_EPI_NONE, RS_NN><<<grid, 256, smem, st>>>(p, 0, tm, tn);
+    else if (p.nn) gemm_mfma_rs_kernel<2, GEMM_EPI_NONE, RS_NN><<<grid, 256, smem, st>>>(p, 0, tm, tn);
     else if (whole) gemm_mfma_rs_kernel<0><<<grid, 256, smem, st>>>(p, 0, tm, tn);
     else gemm_mfma_rs_kernel<2><<<grid, 256, smem, st>>>(p, 0, tm, tn);
     if (split) { AS_LAUNCH_CHECK(ctx); gemm_tail_fixup_kernel<<<dim3(16 * split), 256, 0, st>>>(p, 0, tm, tn); }
@@ -1233,7 +1268,7 @@ static GemmPick pick_plain(const GemmParams& p) {
       else if (T * parts <= kCus && steps / parts >= 3 && (steps - cdiv(steps, parts)) < (int64_t)(p.seg[0].K / 64))
         offer(24, parts, per * 1.04 + 13.9 + 4.1 + 2. * parts + 0.246 * (parts + 0.5) * mb);
     }
-    if ((double)parts * p.M * p.N > (double)kGemmTailFloats && parts > 1) continue;
+    if (p.tn || ((double)parts * p.M * p.N > (double)kGemmTailFloats && parts > 1)) continue;   // tn: the hand-scheduled kernel only
     auto ring = [&](int cfg, int b, double launch, double one, double two, double round, double f0, double f_part, double f_mb) {
       const int64_t T = cdiv(p.M, b) * cdiv(p.N, b) * parts, full = T / (2 * kCus), rest = T % (2 * kCus);
       double t = launch + full * (per * two + round) + (rest ? per * (rest > kCus ? two : one) + round : 0.);
@@ -1273,6 +1308,14 @@ bool gemm_nn_applies(int mode, int variant, const GemmParams& p) {
   return variant == 34 || pick_cfg(p).cfg == 24;
 }
 
+// Splits as pick_plain says.  Under half a chip of workgroups even then (small weight matrices), copies and a kernel of smaller tiles are as fast.
+bool gemm_tn_applies(int mode, int variant, const GemmParams& p) {
+  if (mode != AS_BF16 || (variant != 0 && variant != 2 && variant != 34) || !p.tn || p.nseg != 1 || !p.c_f32 || p.R) return false;
+  if (!mfma_ok(p) || !rs_ok(p) || rs_live(p) || p.ncg || p.nn || p.M % 256 || p.seg[0].lda > (1 << 22) || p.seg[0].ldb > (1 << 22)) return false;
+  for (int i = 0; i < p.nrg; i++) if (p.rg_row[i] % 256 || ((uintptr_t)p.rg_C[i] % 16)) return false;
+  return p.M / 256 * (p.N / 256) * pick_plain(p).parts >= kCus / 2;
+}
+
 // m_dev semantics: the live row count is *m_dev - m_off (clamped to [0, M]).
 // variant: 0 pick, 1 plain FMA kernel, 2 MFMA kernel with the default tile choice, 10 + c forces tile configuration c.
 int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, int m_off, hipStream_t st) {
@@ -1284,6 +1327,13 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
   if (p.accumulate && !p.c_f32) return as_fail(ctx, AS_ERR_SHAPE, "gemm: accumulate needs float output");
   if (p.grp_off && p.splitk > 1) return as_fail(ctx, AS_ERR_SHAPE, "gemm: grouped rows and split-K do not combine");
   if (p.nn && (!gemm_nn_applies(mode, variant, p) || (m_off && !p.m_dev))) return as_fail(ctx, AS_ERR_SHAPE, "gemm: only the hand-scheduled kernel reads B as [K, N]");
+  if (p.tn) {
+    if (!gemm_tn_applies(mode, variant, p) || m_off) return as_fail(ctx, AS_ERR_SHAPE, "gemm: only the hand-scheduled kernel reads A as [K, M]");
+    prof_begin(ctx, st, AS_K_GEMM_RS, p.k_dev ? 0.0 : 2.0 * p.M * p.N * p.seg[0].K);
+    const int rc = launch_rs_cfg(ctx, p, 0, pick_plain(p).parts, st);
+    prof_end(ctx, st);
+    return rc;
+  }
   if (p.grp_n > 0) {
     if (!p.grp_off || p.nseg != 1 || p.m_dev || m_off) return as_fail(ctx, AS_ERR_SHAPE, "gemm: all groups in one launch need a group table and one K segment");
     const int c0 = variant >= 10 ? variant - 10 : pick_cfg(p).cfg;

@@ -1,5 +1,5 @@
 #!/usr/bin/env python3
-"""Writes gemm_rs_loop.inc and gemm_rs_nn_loop.inc: the hand-scheduled main loops of gemm_mfma_rs_kernel (gemm.hip) as one
+"""Writes gemm_rs_loop.inc, gemm_rs_nn_loop.inc and gemm_rs_tn_loop.inc: the hand-scheduled main loops of gemm_mfma_rs_kernel (gemm.hip) as one
 inline-asm block each.  Run by hand after a change (python gen_gemm_rs_loop.py); the generated file is committed.
 
 One K step (64 wide) of one wave (a 128 x 128 block of a 256 x 256 tile, four waves, one per SIMD) is 64
@@ -33,6 +33,9 @@ of a fragment behind the same MFMA, for the same bytes.  B is up to three matric
 all of the same row stride: s[42:43], s[80:81], s[82:83], s[46:47] are their bases minus their first row, s84, s85, s52 the steps
 at which the next one begins, s86 the bytes of 64 rows, (s88, s89) a step's offset.  v[196:199] are then the LDS read
 addresses of B per 32-column block instead of per slice.
+
+The third loop (TN) takes A that way too, [K, M]: 16 LDS reads a slice.  One segment, one matrix each: s84, s86 are the bytes of 64 rows
+of A and B, (s68, s69) and (s88, s89) a step's offsets.
 """
 import os
 
@@ -47,8 +50,10 @@ STORE_SLOTS = [58, 60, 62, 63, 8, 10, 12, 14, 24, 26, 28, 30, 40, 42, 44, 46]   
 LOAD_SLOTS = [9, 11, 13, 15, 25, 27, 29, 31, 41, 43, 45, 47, 48, 49, 59, 61]    # register n
 
 
-NN = False
+NN = False        # B is [K, N]
+TN = False        # A is [K, M] too
 OP_P1, OP_P2, OP_N1, OP_N2, OP_SK = range(27, 32)        # NN: bases of the second and third matrix, their first steps, bytes of 64 rows of B
+OP_KA, OP_KB = 27, 28                                    # TN: bytes of 64 rows of A, of B
 
 
 def frag(setno, which, idx):
@@ -64,14 +69,14 @@ def stage_reg(stage, n):
 def scal(P):
     """(A base pair, B base pair, A stride, B stride, A offset vgpr, B offset vgpr) of the loads issued in a step of parity P"""
     return (("s60", "s61", "s62", "s63", "s64", "s65", "v204", "v205") if P == 0 else
-            ("s74", "s75", "s76", "s77", "s78", "s79", "v210", "v211"))[:7] + (("v207",) if NN else ("v205",) if P == 0 else ("v211",))
+            ("s74", "s75", "s76", "s77", "s78", "s79", "v210", "v211"))[:6 if TN else 7] + (("v206", "v207") if TN else ("v207",) if NN else ("v205",) if P == 0 else ("v211",))
 
 
 def text_read(setno, lds_stage, ks, which, idx):
     """the reads that fill a fragment"""
-    if NN and which == "b":
-        base = 128 + 32 * setno + 16 + 4 * idx
-        return ["ds_read_b64_tr_b16 v[%d:%d], v%d offset:%d" % (base + 2 * q, base + 2 * q + 1, 196 + idx, lds_stage * A_STAGE + ks * 8192 + q * 2048)
+    if TN or NN and which == "b":
+        base, addr = 128 + 32 * setno + (0 if which == "a" else 16) + 4 * idx, (192 if which == "a" else 196) + idx
+        return ["ds_read_b64_tr_b16 v[%d:%d], v%d offset:%d" % (base + 2 * q, base + 2 * q + 1, addr, lds_stage * A_STAGE + ks * 8192 + q * 2048)
                 for q in range(2)]
     return ["ds_read_b128 %s, v%d offset:%d" % (frag(setno, which, idx), (192 if which == "a" else 196) + ks,
                                                 lds_stage * A_STAGE + idx * 4096)]
@@ -95,6 +100,11 @@ def text_load(reg_stage, n, P):
 def tile_bases(P):
     """s66 = tile to load (clamped here to the last one); sets the running bases, strides and offsets of parity P"""
     alo, ahi, blo, bhi, sa, sb, va, vb = scal(P)
+    if TN:
+        return ["s_min_i32 s66, s66, s54", "s_mul_i32 s68, s66, s84", "s_mul_hi_u32 s69, s66, s84",
+                "s_mul_i32 s88, s66, s86", "s_mul_hi_u32 s89, s66, s86", "s_mov_b32 %s, s48" % sa, "s_mov_b32 %s, s49" % sb,
+                "s_add_u32 %s, s40, s68" % alo, "s_addc_u32 %s, s41, s69" % ahi,
+                "s_add_u32 %s, s42, s88" % blo, "s_addc_u32 %s, s43, s89" % bhi]
     if NN:
         return ["s_min_i32 s66, s66, s54", "s_mul_i32 s88, s66, s86", "s_mul_hi_u32 s89, s66, s86",
                 "s_cmp_lt_i32 s66, s84", "s_cselect_b64 s[72:73], s[42:43], s[80:81]",
@@ -149,7 +159,8 @@ def step_ops(P):
     # scalar work for the next step's loads (tile it+4, other scalar set), spread behind the first MFMAs
     # (the run from the compare to the last select depends on scc, which the loads' address updates overwrite: one slot)
     tb = ["s_add_i32 s66, s67, %d" % (2 + DIST)] + tile_bases(Q)
-    cuts = (((16, 0, 4), (17, 4, 6), (18, 6, 8), (19, 8, 14), (20, 14, 17), (21, 17, 19), (22, 19, 21), (23, 21, 22)) if NN else
+    cuts = (((16, 0, 4), (17, 4, 6), (18, 6, 8), (20, 8, 10), (22, 10, 12)) if TN else
+            ((16, 0, 4), (17, 4, 6), (18, 6, 8), (19, 8, 14), (20, 14, 17), (21, 17, 19), (22, 19, 21), (23, 21, 22)) if NN else
             ((16, 0, 9), (18, 9, 11), (20, 11, 13), (22, 13, 15), (24, 15, 17)))
     for slot, lo, hi in cuts:
         slots[slot].append(("scalar", tb[lo:hi]))
@@ -247,10 +258,10 @@ class Emitter:
             self.lines.append(s)
 
 
-def generate(nn, out_path=None):
-    global NN
-    NN = nn
-    name = "rs_nn" if nn else "rs"
+def generate(layout, out_path=None):
+    global NN, TN
+    NN, TN = layout == "nn", layout == "tn"
+    nn, name = NN, "rs" if layout == "nt" else "rs_" + layout
     e = Emitter()
     # ---- set-up: per-lane values from the LDS scratch line of this lane, scalars from the operands
     e("ds_read_b128 v[192:195], %%%d" % OP_SCRATCH)
@@ -266,6 +277,9 @@ def generate(nn, out_path=None):
             e("s_mov_b64 %s, %%%d" % (dst, op))
         for dst, op in (("s84", OP_N1), ("s85", OP_N2), ("s86", OP_SK)):
             e("s_mov_b32 %s, %%%d" % (dst, op))
+    if TN:
+        e("s_mov_b32 s84, %%%d" % OP_KA)
+        e("s_mov_b32 s86, %%%d" % OP_KB)
     e("s_sub_i32 s54, s53, 1")
     e("s_waitcnt lgkmcnt(0)")
     # ---- prologue: the state the loop expects at step 0 -- tile 0 in LDS stage 0, registers 0..3 of tile 1 in LDS
@@ -323,11 +337,11 @@ def generate(nn, out_path=None):
             f.write('  "%s\\n" \\\n' % ln)
         f.write('  ""\n')
         vregs = ", ".join('"v%d"' % i for i in range(212))
-        sregs = ", ".join('"s%d"' % i for i in range(40, 90 if nn else 80))
+        sregs = ", ".join('"s%d"' % i for i in range(40, 80 if layout == "nt" else 90))
         f.write("#define GEMM_%s_LOOP_CLOBBERS %s, %s, \"vcc\", \"scc\", \"memory\"\n" % (name.upper(), vregs, sregs))
     print("wrote", out, len(e.lines), "instructions")
 
 
 if __name__ == "__main__":
-    generate(False)
-    generate(True)
+    for layout in ("nt", "nn", "tn"):
+        generate(layout)

@@ -126,3 +126,15 @@ def test_gain_gradients_over_row_widths(d, bf16):
     trajs = random_trajs(d, 6, sh.vocab, turn_lo=10, turn_hi=30, turns=(2, 4))
     rep = G.compare_step(sh, 3, trajs, 1, 512, bf16=bf16, loss_tol=2e-3 if bf16 else 1e-4, grad_tol=3e-2 if bf16 else 1e-4, full=True)
     assert max(rep["grads"][k] for k in ("g_final", "L0.g1", "L0.g2")) <= (3e-2 if bf16 else 1e-4)
+
+
+@pytest.mark.parametrize("row_len,Hkv,ffn,share", [(4352, 4, 256, 0.3), (11000, 4, 512, 0.9), (9000, 4, 256, 0.3), (4301, 1, 320, 0.3)])
+def test_weight_gradients_from_rows_as_they_are(row_len, Hkv, ffn, share):
+    """Contractions over the tokens of a 1024-wide model: q | k | v and gate | up as rows of one product, the head over its live target rows (one
+    chunk, two, a second one without targets), token counts that are no multiple of a 64-token step; the last
+    case has matrices of 64 and 320 rows, which go through token-major copies.  The step's stated bf16 tolerances."""
+    import gpu_util as G
+    sh = synth.CONFIGS[1].replace(n_layers=2, n_q_heads=8, n_kv_heads=Hkv, head_dim=64, d_model=1024, ffn=ffn, vocab=1024)
+    trajs = synth.trajectories_lognormal(3, 1, row_len, sh.vocab, 400, 0.5, 64, 900, turns=(2, 5), assistant_share=share, token_dist="uniform")
+    rep = G.compare_step(sh, 5, trajs, 1, row_len, bf16=True, loss_tol=2e-3, grad_tol=3e-2, full=True)
+    print("rows of %d: loss rel %.2e worst grad %.2e" % (row_len, rep["loss_rel"], rep["worst_grad"]))
