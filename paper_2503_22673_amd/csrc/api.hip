@@ -401,7 +401,7 @@ static void make_plan(const as_ctx* ctx, int64_t rows, int64_t row_len, Bump& w,
   for (int l = 0; l < P.L && !full; l++) {
     P.A_qkv[l] = w.take((size_t)P.n_qkv * rp * P.d * es); P.At_qkv[l] = w.take((size_t)P.d * P.n_qkv * rp * es);
     P.A_gu[l] = w.take((size_t)P.n_gu * rp * P.d * es); P.At_gu[l] = w.take((size_t)P.d * P.n_gu * rp * es);
-    int sq = 0, sg = 0;
+    int sq = 0, sg = 0, items = 0, grp_of = -1, Ms[6];
     for (int t = 0; t < AS_N_TARGETS; t++) {
       LoraSlot& s = P.lora[(size_t)l * AS_N_TARGETS + t];
       s.on = on(t);
@@ -418,9 +418,11 @@ static void make_plan(const as_ctx* ctx, int64_t rows, int64_t row_len, Bump& w,
         part = std::max(part, (size_t)pick_splitk(c.mode, s.dout, r, P.N) * s.dout * r);
         part = std::max(part, (size_t)pick_splitk(c.mode, r, s.din, P.N) * r * s.din);
         if (c.mode == AS_FP32) part = std::max(part, plain_grad_partial_floats(P.N, (int64_t)2 * (P.QKV + 3 * P.d) + 2 * (2 * P.F + 2 * P.d), r));   // no group of products has more columns
-        if (c.mode == AS_BF16 && r <= 64) {
-          part = std::max(part, lora_grad_tn_partial_floats(P.N, s.dout, r));
-          part = std::max(part, lora_grad_tn_partial_floats(P.N, s.din, r));
+        if (c.mode == AS_BF16 && r <= 64) {                // this target's group so far: q | k | v, gate | up, or the target alone
+          const int gid = t <= AS_T_V ? 0 : t == AS_T_UP ? AS_T_GATE : t;
+          if (gid != grp_of) { grp_of = gid; items = 0; }
+          Ms[items++] = s.dout; Ms[items++] = s.din;
+          part = std::max(part, tn_grad_partial_floats(P.N, Ms, items, r));
         }
       }
     }
@@ -763,7 +765,7 @@ struct Step {
 
   // adapter gradients of one projection: dB = s dy^T u, dA = du^T x.  bf16 with rank <= 64: one
   // streaming pass over dy and over x (row-major, as they are) against the token-major copies of u
-  // and du (uT, duT: lora_tok).  fp32: gathered, and launched for the whole group by lora_flush.  Otherwise: GEMMs on the
+  // and du (uT, duT: lora_tok).  fp32: x and dy against u and du as they are.  Both are launched for the whole group by lora_flush.  Otherwise: GEMMs on the
   // token-major copies dyT [dout, Np], xT [din, Np].
   bool tn_path() const { return mode == AS_FP32 || c.lora_rank <= 64; }
   // token-major copies of a group's u and du (bf16)
@@ -772,9 +774,11 @@ struct Step {
     return launch_transpose_pair(ctx, mode, P.N, P.Np, cols, u, du, cols, P.uT, P.duT, P.Np, st);
   }
   PlainGradBatch pg{};
+  TnGradBatch tg{};
   int lora_flush() {
-    const int rc = launch_plain_grads(ctx, pg, P.N, c.lora_rank, P.partial, P.partial_floats, st);
-    pg.n = 0;
+    const int rc = mode == AS_FP32 ? launch_plain_grads(ctx, pg, P.N, c.lora_rank, P.partial, P.partial_floats, st)
+                                   : launch_tn_grads(ctx, tg, P.N, c.lora_rank, P.partial, P.partial_floats, st);
+    pg.n = tg.n = 0;
     return rc;
   }
   int lora_grads(int l, int t, const void* dy, int64_t lddy, const void* x, int64_t ldx, const void* u, const void* du, int64_t ldu,
@@ -792,9 +796,10 @@ struct Step {
     const void* uT = off(P.uT, (size_t)s.slot * rp * Np);
     const void* duT = off(P.duT, (size_t)s.slot * rp * Np);
     if (tn_path()) {
-      int rc = launch_lora_grad_tn(ctx, dy, lddy, uT, Np, P.N, s.dout, r, sc, g.b[t], r, 1, P.partial, P.partial_floats, st);
-      if (rc) return rc;
-      return launch_lora_grad_tn(ctx, x, ldx, duT, Np, P.N, s.din, r, 1.f, g.a[t], 1, s.din, P.partial, P.partial_floats, st);
+      tg.ldu = Np;
+      tg.m[tg.n++] = {dy, lddy, uT, s.dout, sc, g.b[t], r, 1, 0, 0};
+      tg.m[tg.n++] = {x, ldx, duT, s.din, 1.f, g.a[t], 1, s.din, 0, 0};
+      return AS_OK;
     }
     int rc = gemm(s.dout, r, dyT_rows, Np, uT, Np, Np, nullptr, 0, nullptr, 0, 0, nullptr, 0, g.b[t], r, 1, sc, 0, nullptr, 0, true);
     if (rc) return rc;

@@ -133,9 +133,10 @@ int launch_mfma_peak(as_ctx* ctx, int iters, int blocks, float* sink, hipStream_
 
 // ---- adapter gradients (lora_grad.hip) ---------------------------------------
 // C[m*sm + j*sj] = alpha * sum_t X[t, m] * UT[j, t]  (bf16 X row-major, UT token-major, float C)
-size_t lora_grad_tn_partial_floats(int n, int M, int r);
-int launch_lora_grad_tn(as_ctx* ctx, const void* X, int64_t ldx, const void* UT, int64_t ldu, int n, int M, int r,
-                        float alpha, float* C, int64_t sm, int64_t sj, float* partial, size_t partial_floats, hipStream_t st);
+struct TnGrad { const void* X; int64_t ldx; const void* UT; int M; float alpha; float* C; int64_t sm, sj; int first_block; int64_t first_out; };
+struct TnGradBatch { TnGrad m[6]; int n; int64_t ldu, total; };
+size_t tn_grad_partial_floats(int n, const int* M, int items, int r);
+int launch_tn_grads(as_ctx* ctx, TnGradBatch b, int n, int r, float* partial, size_t partial_floats, hipStream_t st);
 
 // fp32 tier: C[m*sm + j*sj] = alpha * sum_t X[t, m] * U[t, j] for up to eight products of one rank r over the same n tokens; U
 // rows hold r rounded up to 16 columns

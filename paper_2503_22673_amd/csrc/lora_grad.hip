@@ -9,6 +9,9 @@
 // v_mfma_f32_16x16x32_bf16 -- one per column of the block; MFMA row m then stands for column
 // c0 + 8 m + q of X.  U comes from its small token-major copy ([j][token]), one 16-byte load per
 // lane and 16-column block.  Token ranges (splits) go to a partial buffer reduced in split order.
+// The products of an input group (dB and dA of q, k, v) are one launch and one sum: each of them alone is a ramp of a few
+// microseconds around little work when tokens are few: steps of two 1B layers with seven adapters at 1003 tokens 1708 -> 1555 us,
+// at 32768 tokens 18.19 -> 17.68 ms.
 #include "common.h"
 #include <cmath>
 
@@ -16,21 +19,28 @@ namespace {
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 struct TnParams {
-  const bf16_t* X; int64_t ldx;      // [n, M] row-major
-  const bf16_t* UT; int64_t ldu;     // [>= 16*NB rows, tokens rounded up to 64] token-major, zero past n and past r
-  int n, M, r;
-  float* partial;                    // [splits, M, r]
+  TnGradBatch b;
+  int n, r;
+  float* partial;                    // [splits][every product's M x r behind one another]
   int steps_per_split, total_steps;  // 32-token steps
 };
 
 #include "lora_grad_loop.inc"
 template <int NB>
-__global__ __launch_bounds__(256) void lora_grad_tn_kernel(TnParams p) {
+__global__ __launch_bounds__(256) void lora_grad_tn_kernel(TnParams batch) {
+  int it = 0;
+  while (it + 1 < batch.b.n && (int)blockIdx.x >= batch.b.m[it + 1].first_block) it++;
+  struct { const bf16_t* X; int64_t ldx; const bf16_t* UT; int64_t ldu; int n, M, r, steps_per_split, total_steps; float* partial; int64_t split_stride; } p;
+  {
+    const TnGrad& m = batch.b.m[it];
+    p.X = (const bf16_t*)m.X; p.ldx = m.ldx; p.UT = (const bf16_t*)m.UT; p.ldu = batch.b.ldu; p.n = batch.n; p.M = m.M; p.r = batch.r;
+    p.steps_per_split = batch.steps_per_split; p.total_steps = batch.total_steps; p.partial = batch.partial + m.first_out; p.split_stride = batch.b.total;
+  }
   const int tid = threadIdx.x, lane = tid & 63, lm = lane & 15, lg = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // the four waves of a workgroup take four neighbouring 128-column slabs and the same tokens, so that
   // the workgroup reads 1 KB of every token row at a time
-  const int slab = blockIdx.x * 4 + wave, split = blockIdx.y;
+  const int slab = ((int)blockIdx.x - batch.b.m[it].first_block) * 4 + wave, split = blockIdx.y;
   if (slab * 128 >= p.M) return;
   const int col = slab * 128 + 8 * lm;
   const bool col_ok = col < p.M;
@@ -102,7 +112,7 @@ __global__ __launch_bounds__(256) void lora_grad_tn_kernel(TnParams p) {
     compute(xb, bb);
   }
   // accumulator row 4*lg + i of MFMA q is column c0 + 8*(4*lg + i) + q; its column is j = nb*16 + lm
-  float* out = p.partial + (int64_t)split * p.M * p.r;
+  float* out = p.partial + (int64_t)split * p.split_stride;
 #pragma unroll
   for (int q = 0; q < 8; q++)
 #pragma unroll
@@ -116,11 +126,13 @@ __global__ __launch_bounds__(256) void lora_grad_tn_kernel(TnParams p) {
     }
 }
 
-__global__ void tn_reduce_kernel(const float* __restrict__ partial, int splits, int M, int r, float alpha,
-                                 float* __restrict__ C, int64_t sm, int64_t sj) {
+__global__ void tn_reduce_kernel(const TnGradBatch b, const float* __restrict__ partial, int splits, int r) {
   // a thread owns four consecutive elements (M is a multiple of 8) and adds the splits in order; eight loads in flight
-  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4, total = (int64_t)M * r;
+  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4, total = b.total;
   if (i >= total) return;
+  int it = 0;
+  while (it + 1 < b.n && i >= b.m[it + 1].first_out) it++;
+  const TnGrad& m = b.m[it];
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   int s = 0;
   for (; s + 8 <= splits; s += 8) {
@@ -132,41 +144,51 @@ __global__ void tn_reduce_kernel(const float* __restrict__ partial, int splits, 
   }
   for (; s < splits; s++) acc += *reinterpret_cast<const f32x4*>(partial + (int64_t)s * total + i);
 #pragma unroll
-  for (int k = 0; k < 4; k++) C[((i + k) / r) * sm + ((i + k) % r) * sj] = alpha * acc[k];
+  for (int k = 0; k < 4; k++) { const int64_t e = i - m.first_out + k; m.C[(e / r) * m.sm + (e % r) * m.sj] = m.alpha * acc[k]; }
 }
 }  // namespace
 
-// One workgroup fits a CU (the accumulators fill the register file): the token range is split so that the launch is one
-// round of at most 256 workgroups (14336 columns: 28 x 9 = 252 workgroups; with 28 x 10 the last 24 ran alone and the
-// launch took half as long again).  Short token ranges: a split of `s` steps costs their latency, its partial sums are
-// written and read again, so the best split grows with the root of the range; with r 16, kernel and sum of the splits, at
-// 16 steps per split and so: 1003 tokens x 2048: 16.4 and 8.2 us; 4000 x 2048: 17.6 and 12.1; 7500 x 512: 19.2 and 11.7;
-// 15,500 x 2048: 24.3 and 21.3.  (Not trimmed to the steps that are used: the bound on partial sums must grow with n.)
-static int tn_splits(int n, int M) {
-  const int steps = (int)cdiv(n, 32), wg_cols = (int)cdiv(cdiv(M, 128), 4);
-  return (int)std::max<int64_t>(1, std::min<int64_t>(256 / wg_cols, (int64_t)std::sqrt(8.0 * steps)));
+// One workgroup of four column blocks fits a CU (the accumulators fill the register file): the token range is split so that the
+// launch is whole rounds of 256 workgroups, one per product (14336 columns alone: 28 x 9 = 252 workgroups; with 28 x 10 the last
+// 24 ran alone and the launch took half as long again).  Short token ranges: a split of `s` steps costs their latency, its
+// partial sums are written and read again, so the best split grows with the root of the range; with r 16, kernel and sum of the
+// splits, at 16 steps per split and so: 1003 tokens x 2048: 16.4 and 8.2 us; 4000 x 2048: 17.6 and 12.1; 7500 x 512: 19.2 and
+// 11.7; 15,500 x 2048: 24.3 and 21.3.  (Not trimmed to the steps that are used: the bound on partial sums must grow with n.)
+static int tn_blocks(int M) { return (int)cdiv(cdiv(M, 128), 4); }
+static int tn_splits(int n, int blocks, int items) {
+  const int steps = (int)cdiv(n, 32);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(256 * items / blocks, (int64_t)std::sqrt(8.0 * steps)));
 }
 
-size_t lora_grad_tn_partial_floats(int n, int M, int r) { return (size_t)tn_splits(n, M) * M * r; }
+size_t tn_grad_partial_floats(int n, const int* M, int items, int r) {
+  int blocks = 0; int64_t cols = 0;
+  for (int i = 0; i < items; i++) { blocks += tn_blocks(M[i]); cols += M[i]; }
+  return items ? (size_t)tn_splits(n, blocks, items) * cols * r : 0;
+}
 
-// C[m * sm + j * sj] = alpha * sum_t X[t, m] * UT[j, t];  r <= 64, M a multiple of 8, ldx a multiple of 8.
-int launch_lora_grad_tn(as_ctx* ctx, const void* X, int64_t ldx, const void* UT, int64_t ldu, int n, int M, int r,
-                        float alpha, float* C, int64_t sm, int64_t sj, float* partial, size_t partial_floats, hipStream_t st) {
-  if (n <= 0 || M <= 0 || r <= 0) return AS_OK;
-  if (r > 64 || (M % 8) || (ldx % 8) || (ldu % 8) || ((uintptr_t)X % 16) || ((uintptr_t)UT % 16) || ((uintptr_t)partial % 16))
-    return as_fail(ctx, AS_ERR_SHAPE, "lora_grad_tn: rank <= 64 and 8-element alignment needed");
-  const int steps = (int)cdiv(n, 32), slabs = (int)cdiv(M, 128);
-  const int per = (int)cdiv(steps, tn_splits(n, M)), splits = (int)cdiv(steps, per);
-  if ((size_t)splits * M * r > partial_floats) return as_fail(ctx, AS_ERR_WORKSPACE, "lora_grad_tn: partial buffer too small");
-  TnParams p{(const bf16_t*)X, ldx, (const bf16_t*)UT, ldu, n, M, r, partial, per, steps};
+// C[m * sm + j * sj] = alpha * sum_t X[t, m] * UT[j, t] for every product of the batch;  r <= 64, M a multiple of 8, ldx a multiple of 8.
+int launch_tn_grads(as_ctx* ctx, TnGradBatch b, int n, int r, float* partial, size_t partial_floats, hipStream_t st) {
+  if (n <= 0 || b.n <= 0 || r <= 0) return AS_OK;
+  if (r > 64 || (b.ldu % 8) || ((uintptr_t)partial % 16)) return as_fail(ctx, AS_ERR_SHAPE, "lora_grad_tn: rank <= 64 and 8-element alignment needed");
+  int blocks = 0; b.total = 0;
+  for (int i = 0; i < b.n; i++) {
+    TnGrad& m = b.m[i];
+    if ((m.M % 8) || (m.ldx % 8) || ((uintptr_t)m.X % 16) || ((uintptr_t)m.UT % 16)) return as_fail(ctx, AS_ERR_SHAPE, "lora_grad_tn: rank <= 64 and 8-element alignment needed");
+    m.first_block = blocks; m.first_out = b.total;
+    blocks += tn_blocks(m.M); b.total += (int64_t)m.M * r;
+  }
+  const int steps = (int)cdiv(n, 32);
+  const int per = (int)cdiv(steps, tn_splits(n, blocks, b.n)), splits = (int)cdiv(steps, per);
+  if ((size_t)splits * b.total > partial_floats) return as_fail(ctx, AS_ERR_WORKSPACE, "lora_grad_tn: partial buffer too small");
+  TnParams p{b, n, r, partial, per, steps};
   const int nb = (int)cdiv(r, 16);
-  dim3 grid((unsigned)cdiv(slabs, 4), splits);
-  prof_begin(ctx, st, AS_K_LORA_GRAD, 2.0 * n * (double)M * r);
+  dim3 grid(blocks, splits);
+  prof_begin(ctx, st, AS_K_LORA_GRAD, 2.0 * n * (double)b.total);
 #define TN_LAUNCH(NB) { lora_grad_tn_kernel<NB><<<grid, 256, 0, st>>>(p); }
   switch (nb) { case 1: TN_LAUNCH(1) break; case 2: TN_LAUNCH(2) break; case 3: TN_LAUNCH(3) break; default: TN_LAUNCH(4) break; }
 #undef TN_LAUNCH
   AS_LAUNCH_CHECK(ctx);
-  tn_reduce_kernel<<<(unsigned)cdiv((int64_t)M * r, 1024), 256, 0, st>>>(partial, splits, M, r, alpha, C, sm, sj);
+  tn_reduce_kernel<<<(unsigned)cdiv(b.total, 1024), 256, 0, st>>>(b, partial, splits, r);
   prof_end(ctx, st);
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;

@@ -225,3 +225,15 @@ def test_input_gradients_from_matrices_as_they_are(row_len, ffn, targets, full):
     trajs = synth.trajectories_lognormal(7, 1, row_len, sh.vocab, 400, 0.5, 64, 900, turns=(2, 5), assistant_share=0.3, token_dist="uniform")
     rep = G.compare_step(sh, 9, trajs, 1, row_len, bf16=True, loss_tol=2e-3, grad_tol=3e-2, full=full)
     print("rows of %d: loss rel %.2e worst grad %.2e" % (row_len, rep["loss_rel"], rep["worst_grad"]))
+
+
+@pytest.mark.parametrize("targets,rank", [(("v",), 16), (("k", "v", "up"), 3), (("q", "v", "gate", "up", "down"), 33), (synth.DENSE_TARGETS7, 64)])
+@pytest.mark.parametrize("turns", [(2, 3), (20, 30)])
+def test_adapter_gradients_of_a_group_in_one_launch(targets, rank, turns):
+    """Groups of one to six products of unequal, ragged widths, one and several splits of the tokens, ranks of one to four column blocks.
+    The step's stated bf16 tolerances."""
+    import gpu_util as G
+    sh = synth.CONFIGS[1].replace(n_layers=1, n_q_heads=2, n_kv_heads=1, head_dim=64, d_model=136, ffn=712, vocab=128,
+                                  lora_targets=targets, lora_rank=rank, lora_alpha=2.0 * rank)
+    trajs = random_trajs(13, 3, sh.vocab, turn_lo=8, turn_hi=20, turns=turns)
+    G.compare_step(sh, 8, trajs, 2, 640, bf16=True, loss_tol=2e-3, grad_tol=3e-2)
