@@ -342,6 +342,12 @@ def generate(layout, out_path=None):
     print("wrote", out, len(e.lines), "instructions")
 
 
+def main(out_path=None, layout="nt"):
+    """one loop to a file, or all of them to their places"""
+    for name in [layout] if out_path else ["nt", "nn", "tn"]:
+        generate(name, out_path)
+
+
 if __name__ == "__main__":
-    for layout in ("nt", "nn", "tn"):
-        generate(layout)
+    import sys
+    main(*sys.argv[1:])

@@ -553,3 +553,18 @@ def test_gemm_rs_loop_replay():
                     without(lambda ln: ln == "s_barrier")):                          # a stage rewritten while it is read
         with pytest.raises(AssertionError):
             _replay_gemm_loop(planted)
+
+
+@pytest.mark.parametrize("layout", ["nn", "tn"])
+def test_gemm_loops_over_rows_of_the_contraction_replay(layout, tmp_path):
+    """The loops that read B, or A and B, by rows of the contraction: the committed file is the generator's output, and the same replay
+    holds (their 8-byte transposing reads fill half a fragment each, otherwise they are reads like the others)."""
+    import subprocess
+    import sys
+    committed = os.path.join(CSRC, "gemm_rs_%s_loop.inc" % layout)
+    out = tmp_path / "loop.inc"
+    subprocess.run([sys.executable, os.path.join(CSRC, "gen_gemm_rs_loop.py"), str(out), layout], check=True, capture_output=True)
+    assert out.read_text() == open(committed).read()
+    lines = [ln.replace("L_rs_%s_" % layout, "L_rs_").replace("ds_read_b64_tr_b16", "ds_read_b128")
+             for ln in _macro(committed, "GEMM_RS_%s_LOOP_ASM" % layout.upper())]
+    assert _replay_gemm_loop(lines) == 3 * 2 * 64
