@@ -23,11 +23,11 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
 # HBM-side bytes per launch of the dominant kernel at config 3: FETCH_SIZE and WRITE_SIZE of two counter runs over one
 # bench step, each scaled by what the counter reads for a 1 GiB copy (profiles/bench_config3_counters.md).  The figure
 # belongs to the kernel sources those runs saw: the digest below names them, and the line reports null when they differ.
-TRAFFIC_BYTES_PER_LAUNCH = {(3, "gemm_mfma_rs_kernel<0, 0>"): 13.15e9}
-TRAFFIC_SOURCES = ("gemm.hip", "gemm_rs_loop.inc", "common.h")
-TRAFFIC_SOURCE_DIGEST = "c18174f2a2f31f2f"
-DOMINANT_KERNEL = "gemm_mfma_rs_kernel<0, 0>"                  # dense models; expert GEMMs: the same kernel with live-row limits, <1>
-GROUPED_KERNEL = "gemm_mfma_rs_kernel<1, 0>"
+TRAFFIC_BYTES_PER_LAUNCH = {(3, "gemm_mfma_rs_kernel<0, 0, *>"): 13.15e9}
+TRAFFIC_SOURCES = ("gemm.hip", "gemm_rs_loop.inc", "gemm_rs_nn_loop.inc", "common.h")
+TRAFFIC_SOURCE_DIGEST = "0549bae264a40f09"
+DOMINANT_KERNEL = "gemm_mfma_rs_kernel<0, 0, *>"               # dense models; expert GEMMs: the same kernel with live-row limits, <1>
+GROUPED_KERNEL = "gemm_mfma_rs_kernel<1, 0, *>"
 
 
 def kernel_sources_digest():

@@ -1329,7 +1329,7 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
   if (p.nn && (!gemm_nn_applies(mode, variant, p) || (m_off && !p.m_dev))) return as_fail(ctx, AS_ERR_SHAPE, "gemm: only the hand-scheduled kernel reads B as [K, N]");
   if (p.tn) {
     if (!gemm_tn_applies(mode, variant, p) || m_off) return as_fail(ctx, AS_ERR_SHAPE, "gemm: only the hand-scheduled kernel reads A as [K, M]");
-    prof_begin(ctx, st, AS_K_GEMM_RS, p.k_dev ? 0.0 : 2.0 * p.M * p.N * p.seg[0].K);
+    prof_begin(ctx, st, p.k_dev ? AS_K_GEMM_DEVROWS : AS_K_GEMM_RS, p.k_dev ? 0.0 : 2.0 * p.M * p.N * p.seg[0].K);
     const int rc = launch_rs_cfg(ctx, p, 0, pick_plain(p).parts, st);
     prof_end(ctx, st);
     return rc;
