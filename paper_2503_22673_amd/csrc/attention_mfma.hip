@@ -8,9 +8,10 @@
 // and the probabilities, rounded to bf16, are already laid out as the B
 // operand of the next product O^T = V^T P^T (contraction over the keys a lane
 // holds).  The same holds in the backward kernels for dS.  The operand that is
-// contracted over its row index (V in forward; K, Q, dO in backward) is taken
-// from a token-major copy ([column][token], made by a transpose pass right
-// before the launch) so that its fragments are two 8-byte LDS reads.
+// contracted over its row index (V in forward; K, Q, dO in backward) is read
+// through the transposing LDS loads (head_dim 64; backward at head_dim 128),
+// or taken from a token-major copy ([column][token], made by a transpose pass
+// right before the launch: forward at head_dim 128, the eight-wave backward).
 //
 // Tiles are cut on the flat token stream (64 keys per step); a query t sees
 // key u iff seg_start[t] <= u <= t, equivalently u <= t < seg_end[u], so no
