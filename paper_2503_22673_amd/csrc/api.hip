@@ -525,13 +525,10 @@ struct Step {
   int prep_lora() {
     const float s = c.lora_alpha / (float)c.lora_rank;
     const int r = c.lora_rank, rp = P.rp;
-    PrepBatch b; b.n = 0; b.n_tiles = 0;
-    int rc = AS_OK;
+    auto launch = [&](const PrepBatch& b) { return launch_lora_prep_batch(ctx, mode, b, st); };
+    BatchedLaunches<PrepBatch, kPrepBatch, decltype(launch)> batches(1 << 22, launch);
     auto add = [&](const float* in, int rows, int cols, int rows_pad, int cols_pad, float scale, void* out, int64_t ldo, void* out_t, int64_t ldo_t) {
-      const int64_t tiles = cdiv(rows_pad, 64) * cdiv(cols_pad, 64);
-      if (!rc && (b.n == kPrepBatch || b.n_tiles + tiles > (1 << 22))) { rc = launch_lora_prep_batch(ctx, mode, b, st); b.n = 0; b.n_tiles = 0; }
-      b.m[b.n++] = {in, out, out_t, ldo, ldo_t, rows, cols, rows_pad, cols_pad, scale, b.n_tiles};
-      b.n_tiles += (int)tiles;
+      batches.add(PrepMatrix{in, out, out_t, ldo, ldo_t, rows, cols, rows_pad, cols_pad, scale, 0}, cdiv(rows_pad, 64) * cdiv(cols_pad, 64));
     };
     for (int l = 0; l < c.n_layers; l++) {
       const as_layer_lora& Lr = lora->layers[l];
@@ -545,7 +542,7 @@ struct Step {
         add(Lr.b[t], sl.dout, r, sl.dout, rp, s, sl.Bs, rp, sl.Bst, sl.dout);
       }
     }
-    return rc ? rc : launch_lora_prep_batch(ctx, mode, b, st);
+    return batches.finish();
   }
 
   int forward_layer(int l, Acts& a) {

@@ -18,3 +18,21 @@ int pack_plan(int vocab, const int32_t* turn_tokens, const int32_t* turn_offsets
               int32_t* traj_row, std::string* err);
 // cu[0..S] is a partition of [0, N) into segments none of which crosses a multiple of T; *max_seg = longest segment
 int check_cu(const int32_t* cu, int32_t S, int64_t N, int32_t T, int* max_seg, std::string* err);
+
+// Launches over many items, as many at a time as a kernel argument holds (Batch: m[CAP], n, n_tiles; an item's first_tile is set here).
+// add() launches the collected items first when one more would exceed CAP or max_tiles.  Once a launch has failed nothing is
+// collected any more; finish() launches the rest and returns the first status that was not AS_OK.
+template <typename Batch, int CAP, typename Launch> class BatchedLaunches {
+ public:
+  BatchedLaunches(int64_t max_tiles, Launch launch) : max_tiles_(max_tiles), launch_(launch) { b_.n = 0; b_.n_tiles = 0; }
+  template <typename Item> void add(const Item& item, int64_t tiles) {
+    if (!rc_ && b_.n > 0 && (b_.n == CAP || b_.n_tiles + tiles > max_tiles_)) send();
+    if (rc_) return;
+    b_.m[b_.n] = item; b_.m[b_.n].first_tile = b_.n_tiles;
+    b_.n++; b_.n_tiles += (int)tiles;
+  }
+  int finish() { if (!rc_ && b_.n > 0) send(); return rc_; }
+ private:
+  void send() { rc_ = launch_(b_); b_.n = 0; b_.n_tiles = 0; }
+  Batch b_; int64_t max_tiles_; Launch launch_; int rc_ = AS_OK;
+};

@@ -70,6 +70,23 @@ int main() {
       c.lora_alpha = f[2]; c.lora_targets = (uint32_t)v[11]; c.mode = v[12]; c.train_mode = v[13]; c.recompute = v[14]; c.weight_format = v[15];
       if (c.struct_size == 0) c.struct_size = sizeof(as_model_config);
       printf("rc %d\n", check_config(&c, &err));
+    } else if (!strcmp(kind, "batches")) {                 // items of `tiles` tiles each, in batches of at most 4 items; launch `fail` (from 0) fails
+      int items, tiles, max_tiles, fail;
+      if (scanf("%d %d %d %d", &items, &tiles, &max_tiles, &fail) != 4) return 3;
+      struct Item { int id, first_tile; };
+      struct Batch { std::unique_ptr<Item[]> m{new Item[4]}; int n, n_tiles; };      // a heap block of exactly the batch's length
+      int n_launch = 0;
+      auto launch = [&](const Batch& b) {
+        printf(" [");
+        for (int i = 0; i < b.n; i++) printf("%s%d@%d", i ? " " : "", b.m[i].id, b.m[i].first_tile);
+        printf("]");
+        return n_launch++ == fail ? -7 : 0;
+      };
+      BatchedLaunches<Batch, 4, decltype(launch)> batches(max_tiles, launch);
+      printf("launches");
+      for (int i = 0; i < items; i++) batches.add(Item{i, -1}, tiles);
+      const int rc = batches.finish();
+      printf(" rc %d\n", rc);
     } else {
       return 3;
     }

@@ -123,3 +123,19 @@ def test_configuration_check(driver):
            cfg(train_mode=1), cfg(recompute=3), cfg(weight_format=2), cfg(weight_format=1, ffn=344)]
     out = driver("".join(good) + "".join(bad))
     assert out == ["rc 0"] * len(good) + ["rc %d" % ERR["CONFIG"]] * len(bad), out
+
+
+def test_batched_launches_stop_after_a_failure(driver):
+    """Items go out in batches of at most four; once a launch has failed no item is stored and nothing more is launched, however many follow."""
+    def case(items, tiles, max_tiles, fail):
+        return "batches %d %d %d %d\n" % (items, tiles, max_tiles, fail)
+    out = driver(case(0, 1, 100, -1) + case(4, 3, 100, -1) + case(9, 3, 100, -1) + case(5, 3, 6, -1) + case(2, 7, 6, -1) +
+                 case(40, 1, 100, 0) + case(40, 1, 100, 1) + case(3, 1, 100, 0))
+    assert out == ["launches rc 0",
+                   "launches [0@0 1@3 2@6 3@9] rc 0",
+                   "launches [0@0 1@3 2@6 3@9] [4@0 5@3 6@6 7@9] [8@0] rc 0",
+                   "launches [0@0 1@3] [2@0 3@3] [4@0] rc 0",                # the grid's limit
+                   "launches [0@0] [1@0] rc 0",                              # an item above it goes alone
+                   "launches [0@0 1@1 2@2 3@3] rc -7",
+                   "launches [0@0 1@1 2@2 3@3] [4@0 5@1 6@2 7@3] rc -7",
+                   "launches [0@0 1@1 2@2] rc -7"], out
