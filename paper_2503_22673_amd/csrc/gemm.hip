@@ -456,8 +456,9 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_dlds_kernel(GemmParams
 // that a lane owns four consecutive columns of a row.
 // Needs: plain rows, K segments in 64-wide steps, 16-byte aligned rows of every operand (ring_ok).
 template <int N> __device__ __forceinline__ void wait_vm() {
-  // vmcnt(N), expcnt and lgkmcnt untouched: bits 3:0 and 15:14 vmcnt, 6:4 expcnt, 11:8 lgkmcnt
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
+  // vmcnt(N) and lgkmcnt(0): bits 3:0 and 15:14 vmcnt, 6:4 expcnt (untouched), 11:8 lgkmcnt.  The barrier behind it lets other waves
+  // overwrite the stage this wave has read, so its reads must have returned (their MFMAs have waited for them already)
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);
 }
 template <int L, int D> __device__ __forceinline__ void wait_stages(int younger) {   // all but the loads of the `younger` newest stages have landed
   if constexpr (D <= 0) wait_vm<0>();
@@ -557,6 +558,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(GemmParams p, int t
     slot = slot == NST - 1 ? 0 : slot + 1;
   }
   // epilogue through LDS, 32 rows of the wave's block at a time; a lane owns row l31 and columns 32 j + 8 b4 + 4 hh ..+3
+  wait_vm<0>();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   constexpr int WC = TN * 32;                            // columns of the wave's block
