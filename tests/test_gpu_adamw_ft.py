@@ -138,3 +138,36 @@ def test_weight_gradients_from_rows_as_they_are(row_len, Hkv, ffn, share):
     trajs = synth.trajectories_lognormal(3, 1, row_len, sh.vocab, 400, 0.5, 64, 900, turns=(2, 5), assistant_share=share, token_dist="uniform")
     rep = G.compare_step(sh, 5, trajs, 1, row_len, bf16=True, loss_tol=2e-3, grad_tol=3e-2, full=True)
     print("rows of %d: loss rel %.2e worst grad %.2e" % (row_len, rep["loss_rel"], rep["worst_grad"]))
+
+
+@pytest.mark.parametrize("vocab", [1024, 8448])
+@pytest.mark.parametrize("targets", [0, 40])
+def test_head_gradient_over_few_or_no_target_rows(vocab, targets):
+    """The head's weight gradient contracts over as many target rows as the device counts.  16 tiles: every tile is split into parts,
+    all or all but one of them empty; 132 tiles: unsplit.  Without targets every gradient is exactly zero, the head's over what the
+    buffer held before; with 40 (one partial step of 64 rows) the step's stated bf16 tolerances hold."""
+    import gpu_util as G
+    from paper_2503_22673_amd import binding as B
+    sh = synth.CONFIGS[1].replace(n_layers=1, n_q_heads=8, n_kv_heads=4, head_dim=64, d_model=1024, ffn=256, vocab=vocab,
+                                  lora_rank=0, lora_alpha=0.0, lora_targets=(), full_ft=True)
+    g = synth.rng(vocab + targets, 32)
+    ids = g.integers(0, vocab, size=4352).astype(np.int32)
+    trajs = [[(1, ids[b:b + 544])] for b in range(0, 4352, 544)]
+    if targets:
+        trajs[3] = [(1, trajs[3][0][1][:300]), (2, trajs[3][0][1][300:300 + targets]), (1, trajs[3][0][1][300 + targets:])]
+        rep = G.compare_step(sh, 5, trajs, 1, 4352, bf16=True, loss_tol=2e-3, grad_tol=3e-2, full=True, skip=False)
+        assert rep["grads"]["head"] <= 3e-2
+        return
+    params = G.quantise_params(synth.weights(sh, 5), True)
+    ctx = B.Context(B.make_config(sh, mode=B.AS_BF16, train_mode=B.AS_FULL))
+    pk = ctx.pack(*synth.flatten_trajectories(trajs), 4352, 1)
+    model = B.DeviceModel(ctx, params)
+    grads = [t for k in ("embed", "head", "g_final") for t in [model.w_grads[k]]] + [t for L in model.w_grads["layers"] for t in L.values()]
+    for t in grads:
+        t.fill_(7.0)
+    ws = torch.zeros(ctx.workspace_bytes(1, 4352), dtype=torch.uint8, device="cuda")
+    out = ctx.train_step(model, pk["tokens"], pk["cu_seqlens"], pk["cu_seqlens"].cpu().numpy(), pk["loss_mask"], 1, 4352, ws)
+    torch.cuda.synchronize()
+    assert int(out["count"].item()) == 0 and float(out["loss_sum"].item()) == 0.0
+    for t in grads:
+        assert int(torch.count_nonzero(t)) == 0

@@ -328,3 +328,27 @@ def test_attention_head_dim_64_at_tile_edges(Hq, Hkv, lens):
     got = G.to_np(dqkv)
     for x, r in zip((G.to_np(o), got[:, :D], got[:, D:D + Dkv], got[:, D + Dkv:]), refs):
         assert grad_norm_err(x, r.reshape(n, -1)) < tol
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("Hq,Hkv,dh", [(2, 2, 32), (8, 2, 32), (2, 1, 64), (4, 1, 128)])
+def test_plain_attention_around_one_wave_and_one_workgroup_of_rows(Hq, Hkv, dh, bf16):
+    """Ranges of one row up to more than a workgroup's 256, around a wave's 64 and the row groups of each head size, in one call.
+    fp32: sums of at most 300 products, as in the test above; bf16: as at the tile edges above."""
+    B, G, ctx, sh = _env(n_q_heads=Hq, n_kv_heads=Hkv, head_dim=dh)
+    dt, tol, mode = (torch.bfloat16, 2.0 ** -6, B.AS_BF16) if bf16 else (torch.float32, 1e-5, B.AS_FP32)
+    lens = [1, 2, 31, 32, 33, 16, 63, 64, 65, 255, 256, 257, 300, 3]
+    g, cu, n = _attn_case(11, len(lens), Hq, Hkv, dh, lens)
+    q, k, v, do = (G.quantise(g.standard_normal((n, h, dh)), bf16) for h in (Hq, Hkv, Hkv, Hq))
+    o_ref, probs = om.attention(q, k, v, cu, Hq // Hkv)
+    refs = (o_ref,) + tuple(om.attention_bwd(do, q, k, v, o_ref, probs, cu, Hq // Hkv))
+    seg = om.segment_ids(cu, n)
+    seg_start = torch.from_numpy(cu[seg].astype(np.int32)).cuda()
+    seg_end = torch.from_numpy(cu[seg + 1].astype(np.int32)).cuda()
+    qkv_d = G.to_dev(np.concatenate([x.reshape(n, -1) for x in (q, k, v)], axis=1), dt)
+    o, lse = ctx.op_attention_fwd(qkv_d, seg_start, variant=1, mode=mode)
+    dqkv = ctx.op_attention_bwd(qkv_d, seg_start, seg_end, G.to_dev(o_ref.reshape(n, -1), dt), lse, G.to_dev(do.reshape(n, -1), dt), variant=1, mode=mode)
+    D, Dkv = Hq * dh, Hkv * dh
+    got = G.to_np(dqkv)
+    for x, r in zip((G.to_np(o), got[:, :D], got[:, D:D + Dkv], got[:, D + Dkv:]), refs):
+        assert grad_norm_err(x, r.reshape(n, -1)) < tol
