@@ -600,8 +600,6 @@ struct Step {
     return AS_OK;
   }
 
-  // every expert's product over its own rows: rows eoff[e] .. eoff[e+1] of A and C times the e-th of the stacked
-  // matrices at B (b_stride elements apart); one launch where the kernel allows, else one per expert
   // A product with a gradient contracts over the rows of a weight matrix.  The hand-scheduled GEMM reads the matrices as they
   // are ([K, N] rows), the others want the transposed copy: 8192 tokens on eight experts of 4096 x 14336 each spent
   // 1400 us of 15.0 ms in those copies, and the products take the same time either way.
@@ -653,6 +651,8 @@ struct Step {
     g.grp_off = eoff; g.grp_n = c.n_experts; g.grp_b_stride = b_stride; g.grp_rows = 2.0 * P.N;
     g.rows_cap = 2 * P.N;                                  // A and C are (token, slot) buffers: 2 N rows
   }
+  // every expert's product over its own rows: rows eoff[e] .. eoff[e+1] of A and C times the e-th of the stacked
+  // matrices at B (b_stride elements apart); one launch where the kernel allows, else one per expert
   int gemm_experts(const int32_t* eoff, int N, const void* A, int64_t lda, const void* B, int64_t b_stride, int64_t ldb, int K, void* C, int64_t ldc) {
     GemmParams g; memset(&g, 0, sizeof g);
     g.seg[0] = {A, B, lda, ldb, K};

@@ -7,6 +7,9 @@
 // visible rows take 256 / dh row groups side by side (their sums are added in order at the end), so that neither loop is a
 // long chain of dependent loads.  469 tokens, 4 heads of 32: forward 24 us, dQ 21, dK and dV 103 with one wave per token;
 // 12, 15 and 19 us so.
+// The one shape that lost by it is the forward of many segments of 8 to 48 tokens (4096 tokens in segments of 16, 8 heads of 32: 51 us
+// against 44 with one wave per token), where three of the four waves have no row; its backward takes 137 us against 243.
+// Leaving short ranges to the first wave gave the 44 back and cost long segments 3 to 7 %; 128 threads cost them 7 %.
 #include "common.h"
 
 constexpr int kPlainThreads = 256;

@@ -837,7 +837,12 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv3_mfma(AttnParams p, float sc
 // busy in dK / dV), and what eight-wave workgroups lose is time in which all their waves are in the same phase: behind the barrier all
 // issue the next tiles' loads, then all multiply, then all exponentiate.  Workgroups of four waves, three (dK / dV) or four to a
 // CU by their registers, overlap their phases; reading fragments ahead into registers costs a workgroup per CU and was slower
-// (dK / dV: 230 registers, 575 against 545 us of backward), and so was a third stage.  32 query heads on 8 KV heads, this and the
+// (dK / dV: 230 registers, 575 against 545 us of backward).
+// What is left of it: the compiler cannot tell the transposing reads (col64) from the direct-to-LDS loads issued just before and waits
+// for those (vmcnt(0)) in front of the first transposing read of a tile step (forward) or of each half of one (dQ, dK / dV).
+// The next tile therefore lands in the middle of a step and not at its end, and the barrier's own wait finds little left.  A
+// third stage was level with two under that wait, which says nothing about three stages without it.  The forward and dQ spill
+// seven and three registers; their reloads are on the path of the stream's last tile only.  32 query heads on 8 KV heads, this and the
 // eight-wave kernels with token-major copies: forward 186 and 200 us (8191 tokens, longest segment 4096), 271 and 309
 // (30000, 2500), 22 and 26 (1003, 700); backward 523 and 694, 926 and 1217, 60 and 77 us.
 __device__ __forceinline__ int swz64(int row) { return ((row & 2) << 1) | ((row >> 1) & 2) | ((row >> 3) & 1); }
@@ -1078,9 +1083,6 @@ __global__ __launch_bounds__(256, 4) void attn_bwd_dq64_mfma(AttnParams p, float
   if (tq < n) store_grad_row<DH>(dq, scale, (bf16_t*)p.dq + (int64_t)tq * p.ldq + j * DH, h, p.rope_cos, p.rope_sin, tq - ss);
 }
 
-// delta = rowsum(dO * O) as the other kernels take it, and for the dK / dV kernel, head by head ([head][token], token count
-// rounded up to 64), -lse / scale and -delta: the start values of its accumulators of S and dP, so that neither costs a vector
-// instruction per element there.
 // Launch order of the blocks of 256 keys of a call that brings none, one workgroup: most query tiles first (ties: the earlier block).
 constexpr int kOrderBlocks = 1024;                        // counting ranks is quadratic; 262144 tokens
 __device__ void order_blocks(int n, const int32_t* __restrict__ seg_end, int32_t* __restrict__ order) {
@@ -1095,6 +1097,9 @@ __device__ void order_blocks(int n, const int32_t* __restrict__ seg_end, int32_t
   }
 }
 
+// delta = rowsum(dO * O) as the other kernels take it, and for the dK / dV kernel, head by head ([head][token], token count
+// rounded up to 64), -lse / scale and -delta: the start values of its accumulators of S and dP, so that neither costs a vector
+// instruction per element there.
 __global__ __launch_bounds__(256) void attn_stat64_kernel(const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o, const float* __restrict__ lse, int n, int Hq,
                                                           int n64, float inv_scale, float* __restrict__ delta, float* __restrict__ nls, float* __restrict__ nd,
                                                           const int32_t* __restrict__ seg_end, int32_t* __restrict__ order) {

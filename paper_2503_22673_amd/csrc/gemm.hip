@@ -446,11 +446,14 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_dlds_kernel(GemmParams
 // Ring of LDS stages, for products with too few 256 x 256 tiles for the chip and for narrow outputs.  Tiles of BM x BN, four
 // waves of (BM / 2) x (BN / 2), NST stages of one 64-wide K step each, filled straight from global memory (swizzled chunks, as
 // above); a step waits for its own stage only (`vmcnt` of the younger ones), passes one barrier and asks for the stage
-// NST - 1 ahead.  What bounds it: a CU's path into LDS carries about 40 bytes per clock, 800 clocks for the 32 KB of a
+// NST - 1 ahead.  What bounds it: a CU's path into LDS carries about 40 bytes per clock, 800 clocks (0.33 us) for the 32 KB of a
 // 128 x 128 step against 512 of matrix work, so a CU runs two workgroups (64 KB of LDS each) whose waits and barriers fall
-// at different times: 0.52 us per step and tile with two on a CU, 0.74 with one.  64 x 64 tiles read twice the operand
+// at different times: 0.52 us per step and tile with two on a CU, 0.74 with one.  What is above 0.33 is LDS latency: the
+// compiled step reads the fragments of one 16-wide slice, waits for all of them (lgkmcnt(0)) and multiplies, four times, always
+// into the same registers, so no read is under way behind an MFMA.  64 x 64 tiles read twice the operand
 // bytes per flop but give four times the workgroups: the adapters' 64-wide products, bound by reading A once, run
-// at 4.6 TB/s (15,500 rows, K 14336: 97 us; 128 x 64 register-staged tiles: 240).
+// at 4.6 TB/s (15,500 rows, K 14336: 97 us; 128 x 64 register-staged tiles: 240; at 59,000 rows, where those fill the chip
+// too, the two are level).
 // The contraction may be split over `splitk` workgroups (grid.y): float partials, added in order by a second launch.
 // Results leave through LDS, 32 rows of a wave's block at a time, as whole 16-byte pieces; blocks are computed transposed, so
 // that a lane owns four consecutive columns of a row.
@@ -830,8 +833,10 @@ __device__ __forceinline__ void gemm_epilogue_stats(const GemmParams& p, f32x16 
 // Here a tile travels global -> registers -> LDS and its loads are issued 1.75 K steps before its LDS store.
 // With one wave per SIMD every wait in the instruction stream idles the matrix pipe, so the loop is written out
 // instruction by instruction (gen_gemm_rs_loop.py -> gemm_rs_loop.inc).  LDS layout and fragment order are those
-// of the direct-to-LDS kernel.  Covers whole 256 x 256 tiles, K segments that are multiples of 64, host-side
-// row counts, no split-K; the launcher sends everything else to the other kernels.
+// of the direct-to-LDS kernel.  Covers N in whole 256-column tiles, at least 256 rows and K segments that are multiples of 64
+// (rs_ok); the launcher sends everything else to the other kernels.  The contraction of a tile may be shared by several
+// workgroups (tail_first, tail_parts; rows counted on the device: live_parts), each with its part of the K steps.
+// LIVE = 0: plain rows in whole row tiles, or a ragged last one whose spare rows the operands have.
 // LIVE = 2: plain rows whose number is no multiple of 256; the last row tile is moved up to end with the last row and writes
 // only the rows that are its own.
 // LIVE = 1: the row count is a device-side value and / or the rows are those of one group (expert).  Tiles past the live
