@@ -122,9 +122,10 @@ __device__ inline void xcd_group_map(int wg, int per, int ngrp, int& group, int&
   } else { group = INTERLEAVE ? wg % ngrp : wg / per; item = INTERLEAVE ? wg / ngrp : wg % per; }
 }
 
-template <int DH, int HPW, int QB, int NWV>
-__global__ __launch_bounds__(NWV * 64, QB == 1 ? 2 : 1) void attn_fwd2_mfma(AttnParams p, float sl2) {
-  constexpr int KS = DH / 16, CB = DH / 32, WQ = 32 * QB, QT = WQ * (NWV / HPW);
+// Forward, head_dim 128: HPW heads of a group per workgroup of eight waves, 32 queries per wave.
+template <int HPW>
+__global__ __launch_bounds__(512, 2) void attn_fwd2_mfma(AttnParams p, float sl2) {
+  constexpr int DH = 128, QB = 1, NWV = 8, KS = DH / 16, CB = DH / 32, WQ = 32 * QB, QT = WQ * (NWV / HPW);   // QB: blocks of 32 queries per wave
   constexpr int KT_E = BKEY * DH, ST_E = 2 * KT_E;        // elements of one tile / of one stage (K tile + V^T tile)
   extern __shared__ __align__(16) unsigned char dyn_smem[];
   bf16_t* sm = (bf16_t*)dyn_smem;
@@ -1279,14 +1280,11 @@ int heads_per_wg(const AttnParams& p) {
   return grp % 4 == 0 ? 4 : (grp % 2 == 0 ? 2 : 1);
 }
 
-template <int DH, int HPW, int QB, int NWV = 8 / QB>
-int launch_fwd2(as_ctx* ctx, const AttnParams& p_in, float sl2, hipStream_t st) {
-  AttnParams p = p_in;
-  if (32 * QB * (NWV / HPW) != attention_query_tile(p.Hq, p.Hkv)) p.order_q = nullptr;   // the order table is cut for another tile size
-  constexpr size_t smem = (size_t)2 * 2 * BKEY * DH * sizeof(bf16_t);       // two stages of a K tile and a V^T tile
-  AS_SET_SMEM(ctx, (attn_fwd2_mfma<DH, HPW, QB, NWV>), smem);
-  constexpr int QT = 32 * QB * (NWV / HPW);
-  attn_fwd2_mfma<DH, HPW, QB, NWV><<<(unsigned)(cdiv(p.n, QT) * (p.Hq / HPW)), NWV * 64, smem, st>>>(p, sl2);
+template <int HPW>
+int launch_fwd2(as_ctx* ctx, const AttnParams& p, float sl2, hipStream_t st) {
+  constexpr size_t smem = (size_t)2 * 2 * BKEY * 128 * sizeof(bf16_t);       // two stages of a K tile and a V^T tile
+  AS_SET_SMEM(ctx, attn_fwd2_mfma<HPW>, smem);
+  attn_fwd2_mfma<HPW><<<(unsigned)(cdiv(p.n, 32 * (8 / HPW)) * (p.Hq / HPW)), 512, smem, st>>>(p, sl2);       // tiles of attention_query_tile() tokens
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }
@@ -1334,7 +1332,7 @@ int fwd_dh(as_ctx* ctx, const AttnParams& p_in, hipStream_t st) {
   p.ldT = Np; p.vT = p.t_scratch;
   int rc = launch_transpose_qs(ctx, AS_BF16, p.n, Np, Dkv, p.v, p.ldkv, p.t_scratch, Np, st);   // V^T [Dkv, Np]
   if (rc) return rc;
-  return hpw == 4 ? launch_fwd2<128, 4, 1>(ctx, p, sl2, st) : hpw == 2 ? launch_fwd2<128, 2, 1>(ctx, p, sl2, st) : launch_fwd2<128, 1, 1>(ctx, p, sl2, st);
+  return hpw == 4 ? launch_fwd2<4>(ctx, p, sl2, st) : hpw == 2 ? launch_fwd2<2>(ctx, p, sl2, st) : launch_fwd2<1>(ctx, p, sl2, st);
 }
 
 template <int DH, int HPW>
