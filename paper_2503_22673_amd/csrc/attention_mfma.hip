@@ -834,9 +834,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv3_mfma(AttnParams p, float sc
 // read them through the transposing LDS loads, so there are no token-major copies.  LDS position of chunk c (16 bytes) of row r:
 // c ^ f(r), f = bits 1..3 of the row in reverse order: the 16 rows of a row read then hit every bank once, and so do the four
 // rows x 32 bytes of a transposing read (rows r and r + 2, which share their half of the banks, differ in the chunk pair).
-// At this head size the matrix work per exponential is half that of head_dim 128 (matrix pipes 48 %, vector pipes 44 % of the time
-// busy in dK / dV), and what eight-wave workgroups lose is time in which all their waves are in the same phase: behind the barrier all
-// issue the next tiles' loads, then all multiply, then all exponentiate.  Workgroups of four waves, three (dK / dV) or four to a
+// At this head size the matrix work per exponential is half that of head_dim 128 (matrix and vector pipes busy 45 and 44 % of the time
+// in dK / dV, 45 and 62 % in dQ, 37 and 70 % in the forward), and what eight-wave workgroups lose is time in which all their waves are in
+// the same phase: behind the barrier all issue the next tiles' loads, then all multiply, then all exponentiate.  Workgroups of four waves, three (dK / dV) or four to a
 // CU by their registers, overlap their phases; reading fragments ahead into registers costs a workgroup per CU and was slower
 // (dK / dV: 230 registers, 575 against 545 us of backward).
 // What is left of it: the compiler cannot tell the transposing reads (col64) from the direct-to-LDS loads issued just before and waits

@@ -375,12 +375,12 @@ int launch_rmsnorm_bwd(as_ctx* ctx, int mode, int n, int d, const void* dy, cons
 
 // The same with the gain gradient dg_j = sum_t dy[t,j] x[t,j] rstd[t] out of the same pass over dy and x (full fine-tuning):
 // up to 256 workgroups walk the rows, a lane adds up the columns it holds of every row it sees, the waves of a workgroup are
-// added in order through LDS into partial[workgroup, :], and a second launch adds the workgroups in order.  Its least work is
-// memory (dy, x, add in, dx out); 16 waves of a workgroup with KEEP = 4 (2048 16-bit columns), 8 with KEEP = 8.  The 16-bit
-// instances need more registers than that leaves: 40 (KEEP 4) and 92 (KEEP 8) spill, and the column sums among them go through
-// scratch for every row.  That, not memory, bounds it: 15,700 rows of 2048, bf16: 77 us with the sum, 3.3 TB/s, where the
-// backward pass alone runs at 5.8; as three launches (backward, a second pass over dy and x, a sum of 256 slabs by one
-// thread per column) 130 us.
+// added in order through LDS into partial[workgroup, :], and a second launch adds the workgroups in order.  Bound by memory (dy, x,
+// add in, dx out), by more of it than that: 16 waves of a workgroup with KEEP = 4 (2048 16-bit columns), 8 with KEEP = 8,
+// leave too few registers for the 16-bit instances.  40 and 92 spill, and the column sums among them go through scratch memory for
+// every row: 48,564 rows of 2048, bf16: 204 us for 832 MB in and 464 MB out by the counters, where the operands are 597 and
+// 199 MB (3.9 TB/s of them; the backward pass without gains runs at 5.8).  15,700 rows: 77 us with the sum; as three launches
+// (backward, a second pass over dy and x, a sum of 256 slabs by one thread per column) 130 us.
 template <typename T, int KEEP>
 __global__ __launch_bounds__(4096 / KEEP) void rmsnorm_bwd_gain_kernel(int n, int d, const T* __restrict__ dy, const int32_t* __restrict__ src_pos,
                                                                const T* __restrict__ x, const T* __restrict__ g, const float* __restrict__ rstd,
