@@ -402,6 +402,7 @@ static void make_plan(const as_ctx* ctx, int64_t rows, int64_t row_len, Bump& w,
     P.A_qkv[l] = w.take((size_t)P.n_qkv * rp * P.d * es); P.At_qkv[l] = w.take((size_t)P.d * P.n_qkv * rp * es);
     P.A_gu[l] = w.take((size_t)P.n_gu * rp * P.d * es); P.At_gu[l] = w.take((size_t)P.d * P.n_gu * rp * es);
     int sq = 0, sg = 0, items = 0, grp_of = -1, Ms[6];
+    int64_t cols = 0;
     for (int t = 0; t < AS_N_TARGETS; t++) {
       LoraSlot& s = P.lora[(size_t)l * AS_N_TARGETS + t];
       s.on = on(t);
@@ -417,13 +418,12 @@ static void make_plan(const as_ctx* ctx, int64_t rows, int64_t row_len, Bump& w,
         int r = c.lora_rank;
         part = std::max(part, (size_t)pick_splitk(c.mode, s.dout, r, P.N) * s.dout * r);
         part = std::max(part, (size_t)pick_splitk(c.mode, r, s.din, P.N) * r * s.din);
-        if (c.mode == AS_FP32) part = std::max(part, plain_grad_partial_floats(P.N, (int64_t)2 * (P.QKV + 3 * P.d) + 2 * (2 * P.F + 2 * P.d), r));   // no group of products has more columns
-        if (c.mode == AS_BF16 && r <= 64) {                // this target's group so far: q | k | v, gate | up, or the target alone
-          const int gid = t <= AS_T_V ? 0 : t == AS_T_UP ? AS_T_GATE : t;
-          if (gid != grp_of) { grp_of = gid; items = 0; }
-          Ms[items++] = s.dout; Ms[items++] = s.din;
-          part = std::max(part, tn_grad_partial_floats(P.N, Ms, items, r));
-        }
+        // this target's group so far: q | k | v, gate | up, or the target alone
+        const int gid = t <= AS_T_V ? 0 : t == AS_T_UP ? AS_T_GATE : t;
+        if (gid != grp_of) { grp_of = gid; items = 0; cols = 0; }
+        Ms[items++] = s.dout; Ms[items++] = s.din; cols += s.dout + s.din;
+        if (c.mode == AS_FP32) part = std::max(part, plain_grad_partial_floats(P.N, cols, r));
+        else if (r <= 64) part = std::max(part, tn_grad_partial_floats(P.N, Ms, items, r));
       }
     }
   }

@@ -67,6 +67,21 @@ def test_workspace_query(B):
     assert gb5 < 170, gb5
 
 
+def test_workspace_of_fp32_adapter_gradients_follows_their_groups(B):
+    """Partial sums of the float adapter gradients are kept for one input group at a time: with an adapter on q alone they do not
+    depend on the FFN width.  Per token the width costs nine floats a column: gate | up (2) and their product, their gradients
+    (2 + 1), and the token-major copies of an input (1) and of gate | up's gradient (2)."""
+    n, size = 32768, {}
+    for ffn in (4096, 8192):
+        sh = synth.CONFIGS[1].replace(n_layers=1, ffn=ffn, lora_rank=256, lora_targets=("q",))
+        ctx = B.Context(B.make_config(sh, mode=B.AS_FP32))
+        size[ffn] = ctx.workspace_bytes(1, n)
+        ctx.close()
+    d = synth.CONFIGS[1].d_model
+    weights = 2 * 4096 * d * 4                              # transposed gate | up
+    assert size[8192] - size[4096] <= 9 * 4 * 4096 * n + weights + 4096, size
+
+
 def _pack_args(trajs):
     return synth.flatten_trajectories(trajs)
 
