@@ -5,7 +5,9 @@
 //
 // Kernels:
 //  * gemm_fma_kernel        -- any type, any shape; fp32 FMAs.  The fp32 tier runs on it.
-//  * gemm_mfma_rs_kernel    -- bf16, hand-scheduled 256x256 tiles: the large products; also with B, or A and B, given by rows of K.
+//  * gemm_mfma_rd_kernel    -- bf16, hand-scheduled 256x256 tiles, persistent: the large products; also with B, or A and B, given by rows of K.
+//  * gemm_mfma_rs_kernel    -- the same tiles staged through registers and one workgroup per tile (variant 34 of as_op_gemm only: its sums are
+//    those of the direct-to-LDS kernel, in the same order).
 //  * gemm_mfma_ring_kernel  -- bf16, 128x128 and 64x64 tiles in a ring of LDS stages: few rows or narrow outputs.
 //  * gemm_mfma_dlds_kernel, gemm_mfma_kernel -- bf16: K that is no multiple of 64, rows counted on the device that the
 //    hand-scheduled kernel does not take, rows that are not 16-byte aligned.
@@ -730,9 +732,7 @@ __device__ __forceinline__ void gemm_epilogue_rows(const GemmParams& p, f32x16 (
 // the tile memory, which is free once every wave has left the loop, and reads it back 16 bytes per lane, so that a store
 // instruction writes four whole 256-byte row pieces.  Rows are 272 bytes apart in LDS.  The residual takes the same way
 // in: loaded 16 bytes per lane, parked at the place of the result, picked up by the lane that owns the element.
-// PROB: the values are turned into w_row * (exp(value - lse_row) - [column is the row's label]) before they are rounded
-// (the gradient of the masked cross-entropy with respect to the logits, written instead of the logits themselves).
-template <int TM, int TN, bool MASK = false, bool PROB = false>
+template <int TM, int TN, bool MASK = false>
 __device__ __forceinline__ void gemm_epilogue_staged(const GemmParams& p, f32x16 (&acc)[TM][TN], unsigned char* smem, int wave, int lane,
                                                      int row_w0, int col_w0, int row_lo = 0, int row_hi = 0) {
   constexpr int LROW = 272, ROWS = TM * 32;
@@ -754,13 +754,6 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmParams& p, f32x16
   }
 #pragma unroll
   for (int i = 0; i < TM; i++) {
-    float neg_lse2 = 0.f, wrow = 0.f; int clab = -1;
-    if (PROB) {                                          // rows outside the live range compute with the last live row's values and are not written
-      const int r = MASK ? min(max(row_w0 + 32 * i + l31, row_lo), row_hi - 1) : row_w0 + 32 * i + l31;
-      neg_lse2 = -1.4426950408889634f * p.epi_lse[r];
-      wrow = p.epi_w ? p.epi_w[r] : 1.f / (float)*p.epi_cnt;
-      clab = p.epi_lab[r] - col_w0 - 4 * hh;               // position of the label among this lane's columns of the block, if any
-    }
 #pragma unroll
     for (int j = 0; j < TN; j++)
 #pragma unroll
@@ -769,11 +762,6 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmParams& p, f32x16
         f32x4 v;
 #pragma unroll
         for (int k = 0; k < 4; k++) v[k] = alpha * acc[i][j][4 * b4 + k];
-        if (PROB) {
-#pragma unroll
-          for (int k = 0; k < 4; k++)
-            v[k] = wrow * (__builtin_amdgcn_exp2f(fmaf(v[k], 1.4426950408889634f, neg_lse2)) - (clab == 32 * j + 8 * b4 + k ? 1.f : 0.f));
-        }
         if (p.R) { const bf16x4_t x = *q;
 #pragma unroll
           for (int k = 0; k < 4; k++) v[k] += (float)x[k]; }
@@ -791,37 +779,6 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmParams& p, f32x16
     const int r = row_w0 + 4 * it + r4;
     if (!MASK || (r >= row_lo && r < row_hi))
       *reinterpret_cast<u32x4*>(c + (int64_t)(4 * it) * p.ldc) = *reinterpret_cast<const u32x4*>(my + (4 * it + r4) * LROW + c16 * 16);
-  }
-}
-
-// Softmax statistics of a wave's 128 x 128 block of logits, straight from the accumulators (same lane layout as above: a lane
-// owns row lane % 32 of every 32-row block and half of the block's 128 columns, the other half sits in lane ^ 32): per row the
-// maximum and the sum of exp(value - maximum) over the 128 columns.  Nothing of the logits is written.
-template <int TM, int TN, bool MASK>
-__device__ __forceinline__ void gemm_epilogue_stats(const GemmParams& p, f32x16 (&acc)[TM][TN], int row_lane, int blk, int hh, int row_lo, int row_hi) {
-  const float alpha = p.alpha;
-  const int nblk = p.N / 128;
-#pragma unroll
-  for (int i = 0; i < TM; i++) {
-    float m = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < TN; j++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) m = fmaxf(m, alpha * acc[i][j][e]);
-    const float mo = __shfl_xor(m, 32, 64);
-    const float mx = fmaxf(m, mo);
-    const float nm2 = -1.4426950408889634f * mx;
-    float s = 0.f;
-#pragma unroll
-    for (int j = 0; j < TN; j++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) s += __builtin_amdgcn_exp2f(fmaf(alpha * acc[i][j][e], 1.4426950408889634f, nm2));
-    s += __shfl_xor(s, 32, 64);
-    const int r = row_lane + 32 * i;
-    if (hh == 0 && (!MASK || (r >= row_lo && r < row_hi))) {
-      float2* q = reinterpret_cast<float2*>(p.epi_part) + (int64_t)r * nblk + blk;
-      *q = make_float2(mx, s);
-    }
   }
 }
 
@@ -865,9 +822,7 @@ __device__ __forceinline__ void* row_group_base(const GemmParams& p, int row) {
   while (g < p.nrg && row >= p.rg_row[g]) g++;
   return g ? (float*)p.rg_C[g - 1] - (int64_t)p.rg_row[g - 1] * p.ldc : (float*)p.C;
 }
-// EPI: the epilogue is a compile-time choice (GEMM_EPI_*), so that the head's epilogues, which need registers of their own,
-// cost the projection GEMMs nothing.
-template <int LIVE, int EPI = GEMM_EPI_NONE, int LAYOUT = RS_NT>
+template <int LIVE, int LAYOUT = RS_NT>
 __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_off, int tiles_m, int tiles_n) {
   constexpr int BM = 256, BN = 256, BK = 64, TM = 4, TN = 4;
   constexpr bool NN = LAYOUT != RS_NT, AK = LAYOUT == RS_TN;      // B is [K, N]; A is [K, M]
@@ -886,11 +841,11 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
   }
   int nblk = tiles_m * tiles_n, pid = blockIdx.x;
   int kpart = -1, parts = p.tail_parts;                  // >= 0: this workgroup computes one part of the contraction of a split tile
-  if (LIVE == 1 && EPI == GEMM_EPI_NONE && p.tail_part) {
+  if (LIVE == 1 && p.tail_part) {
     parts = live_parts(p, nblk);
     if (parts > 1) { kpart = pid % parts; pid /= parts; }
   }
-  if (LIVE != 1 && EPI == GEMM_EPI_NONE && p.tail_first >= 0 && pid >= p.tail_first) {
+  if (LIVE != 1 && p.tail_first >= 0 && pid >= p.tail_first) {
     const int i = pid - p.tail_first;
     kpart = i % parts; pid = p.tail_first + i / parts;
   }
@@ -1020,14 +975,12 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
                  : GEMM_RS_LOOP_CLOBBERS);
   }
   // bf16 results with 16-byte rows leave through LDS (whole 256-byte row pieces per store), the rest row by row
-  if (EPI == GEMM_EPI_NONE && kpart >= 0) {              // raw float sums of this part into the tile's scratch
+  if (kpart >= 0) {              // raw float sums of this part into the tile's scratch
     GemmParams q = p;
     q.C = p.tail_part + ((int64_t)(pid - (LIVE == 1 ? 0 : p.tail_first)) * parts + kpart) * (BM * BN); q.ldc = BN; q.c_f32 = 1; q.alpha = 1.f; q.R = nullptr; q.accumulate = 0;
     gemm_epilogue_rows<TM, TN, false>(q, acc, wm * TM * 32 + l31, wn * TN * 32 + 4 * hh);
     return;
   }
-  if constexpr (EPI == GEMM_EPI_STATS) { gemm_epilogue_stats<TM, TN, LIVE != 0>(p, acc, row0 + wm * TM * 32 + l31, (col0 + wn * TN * 32) / 128, hh, row_lo, row_hi); return; }
-  if constexpr (EPI == GEMM_EPI_PROB) { gemm_epilogue_staged<TM, TN, LIVE != 0, true>(p, acc, smem, wave, lane, row0 + wm * TM * 32, col0 + wn * TN * 32, row_lo, row_hi); return; }
   if constexpr (AK) {
     GemmParams q = p; q.C = row_group_base(p, row0);
     gemm_epilogue_rows<TM, TN, false>(q, acc, row0 + wm * TM * 32 + l31, col0 + wn * TN * 32 + 4 * hh);
@@ -1036,6 +989,374 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
   const bool staged = !p.c_f32 && !(p.ldc % 8) && (!p.R || (!(p.ldr % 8) && !((uintptr_t)p.R % 16)));
   if (staged) gemm_epilogue_staged<TM, TN, LIVE != 0>(p, acc, smem, wave, lane, row0 + wm * TM * 32, col0 + wn * TN * 32, row_lo, row_hi);
   else gemm_epilogue_rows<TM, TN, LIVE != 0>(p, acc, row0 + wm * TM * 32 + l31, col0 + wn * TN * 32 + 4 * hh, row_lo, row_hi);
+}
+
+// ------------------------------------------------------------- persistent 256 x 256 tiles
+// The large products.  Same tiles, layouts (NT, NN, TN), live rows, groups and split tiles as the kernel above; what differs:
+// * Under the chip's power limit the clock follows the energy of an operation, and a 16x16x32 product costs less of it than a 32x32x16
+//   one (register-resident loops on random operands: 2025 against 1788 TFLOP/s).  A slot of 16 clocks has no room for LDS stores (the
+//   kernel above with 16x16x32 products: 2510 clocks a step instead of 2170 and 2 % in all), so tiles go straight to LDS, through a
+//   ring of five 32 KB half stages that keeps the loads one to 1.7 steps ahead (gen_gemm_rd_loop.py): 2190 clocks a step of 2048 of
+//   matrix work, at 1.65 to 1.75 GHz where the kernel above holds 1.5 to 1.57.
+// * The workgroups are persistent, one per CU: the first two steps of the next tile are on their way while the last ones of a tile are
+//   multiplied and while its result is written.  A tile costs its steps, an epilogue of 7,400 clocks and 2,100 between tiles; the kernel
+//   above loses 21,000 (epilogue 10,500, first loads, launch).  The epilogue takes 64 accumulators at a time: with all 256 in the
+//   compiler's hands it spilled a hundred registers.
+// TFLOP/s before and now, random operands, launches back to back: 16384 x 14336 x 4096 1333 and 1525, 16384 x 4096 x 14336 1365 and 1558,
+// 32768 x 8192 x 2048 1234 and 1407, 32768 x 2048 x 8192 1346 and 1535.
+#include "gemm_rd_loop.inc"
+#include "gemm_rd_nn_loop.inc"
+#include "gemm_rd_tn_loop.inc"
+constexpr size_t kRdSmem = 5 * 32768;
+
+// A wave's block leaves in four pieces of 32 rows, whose 64 accumulators are taken to vector registers first: t[j] is the 32 x 32 block of
+// column j, its 16 x 16 block (a, b) elements 4 (2 a + b) .. + 3; a lane owns row 16 a + lane % 16 and the four columns from 16 b + 4 (lane / 16).
+struct RdOut { int row0, col0, row_lo, row_hi; };          // the wave's block; with MASK only rows row_lo .. row_hi - 1 are read and written
+__device__ __forceinline__ f32x4 quad(const f32x16& v, int a, int b, float alpha) {
+  f32x4 r;
+#pragma unroll
+  for (int k = 0; k < 4; k++) r[k] = alpha * v[4 * (2 * a + b) + k];
+  return r;
+}
+
+// float results, or bf16 ones whose rows are no whole 16-byte pieces: straight from the registers.  EXTRA: a residual, or a sum with what is there.
+template <bool MASK, bool F32, bool EXTRA>
+__device__ __forceinline__ void rd_rows(const GemmParams& p, const f32x16 (&t)[4], const RdOut& o, int i, int lane) {
+#pragma unroll
+  for (int a = 0; a < 2; a++) {
+    const int64_t r = o.row0 + 32 * i + 16 * a + (lane & 15);
+    const int c0 = o.col0 + 4 * (lane >> 4);
+    if (MASK && (r < o.row_lo || r >= o.row_hi)) continue;
+    const bf16_t* rr = (const bf16_t*)p.R + r * p.ldr + c0;
+    float* cf = (float*)p.C + r * p.ldc + c0;
+    bf16_t* cb = (bf16_t*)p.C + r * p.ldc + c0;
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+#pragma unroll
+      for (int b = 0; b < 2; b++) {
+        f32x4 v = quad(t[j], a, b, p.alpha);
+        if (EXTRA && p.R) { const bf16x4_t x = *reinterpret_cast<const bf16x4_t*>(rr + 32 * j + 16 * b);
+#pragma unroll
+          for (int k = 0; k < 4; k++) v[k] += (float)x[k]; }
+        if (F32) {
+          f32x4* q = reinterpret_cast<f32x4*>(cf + 32 * j + 16 * b);
+          if (EXTRA && p.accumulate) { const f32x4 x = *q;
+#pragma unroll
+            for (int k = 0; k < 4; k++) v[k] += x[k]; }
+          *q = v;
+        } else {
+          bf16x4_t w;
+#pragma unroll
+          for (int k = 0; k < 4; k++) w[k] = (bf16_t)v[k];
+          *reinterpret_cast<bf16x4_t*>(cb + 32 * j + 16 * b) = w;
+        }
+      }
+  }
+}
+
+// bf16 results through the wave's 8 KB of the free half stage, so that a store instruction writes four whole 256-byte row pieces; 16-byte
+// chunk c of row r lies at c ^ (r % 16).  A residual takes the same way in: loaded 16 bytes per lane, parked at the place of the result,
+// picked up by the lane that owns the element and rounded once with the sum.
+// PROB: the values are turned into w_row * (exp(value - lse_row) - [column is the row's label]) before they are rounded.
+template <bool MASK>
+__device__ __forceinline__ void rd_load_residual(const GemmParams& p, u32x4 (&res)[8], const RdOut& o, int i, int lane) {
+  const int r4 = lane >> 4, c16 = lane & 15;
+  if (MASK) {
+#pragma unroll
+    for (int it = 0; it < 8; it++)
+      res[it] = *reinterpret_cast<const u32x4*>((const bf16_t*)p.R + (int64_t)min(max(o.row0 + 32 * i + 4 * it + r4, o.row_lo), o.row_hi - 1) * p.ldr + o.col0 + c16 * 8);
+    return;
+  }
+  const uint32_t at = (uint32_t)((r4 * p.ldr + c16 * 8) * 2);
+  const int64_t step = 8 * p.ldr;                          // bytes of four rows
+  const char* src = (const char*)((const bf16_t*)p.R + (int64_t)(o.row0 + 32 * i) * p.ldr + o.col0);
+#pragma unroll
+  for (int it = 0; it < 8; it++, src += step) res[it] = *reinterpret_cast<const u32x4*>(src + at);
+}
+template <bool MASK, bool PROB, bool RES>
+__device__ __forceinline__ void rd_staged(const GemmParams& p, f32x16 (&t)[4], u32x4 (&res)[8], unsigned char* my, const RdOut& o, int i, int lane) {
+  const int l15 = lane & 15, q = lane >> 4, r4 = lane >> 4, c16 = lane & 15;
+  unsigned char* mine = my + l15 * 256 + (q & 1) * 8;      // this lane's row of 16 and its half of a chunk
+  const int ch = ((q >> 1) ^ l15) * 16;
+  // whole rows: row 4 it + r4, chunk c16 ^ (row % 16), that is (c16 ^ r4) ^ 4 (it % 4)
+  unsigned char* rows = my + r4 * 256;
+  const int cr = (c16 ^ r4) * 16;
+  if (RES) {
+#pragma unroll
+    for (int it = 0; it < 8; it++) *reinterpret_cast<u32x4*>(rows + it * 1024 + (cr ^ ((it & 3) * 64))) = res[it];
+    asm volatile("" ::: "memory");
+    if (i < 3) rd_load_residual<MASK>(p, res, o, i + 1, lane);
+  }
+  if (p.alpha != 1.f) {
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) t[j][e] *= p.alpha;
+  }
+#pragma unroll
+  for (int a = 0; a < 2; a++) {
+    float neg_lse2 = 0.f, wrow = 0.f; int clab = -1;
+    if (PROB) {                                            // rows outside the live range compute with the last live row's values and are not written
+      const int rr = o.row0 + 32 * i + 16 * a + l15, r = MASK ? min(max(rr, o.row_lo), o.row_hi - 1) : rr;
+      neg_lse2 = -1.4426950408889634f * p.epi_lse[r];
+      wrow = p.epi_w ? p.epi_w[r] : 1.f / (float)*p.epi_cnt;
+      clab = p.epi_lab[r] - o.col0 - 4 * q;                // position of the label among this lane's columns of the block, if any
+    }
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+#pragma unroll
+      for (int b = 0; b < 2; b++) {
+        bf16x4_t* at = reinterpret_cast<bf16x4_t*>(mine + a * 4096 + (ch ^ ((4 * j + 2 * b) * 16)));
+        f32x4 v = quad(t[j], a, b, 1.f);
+        if (PROB) {
+#pragma unroll
+          for (int k = 0; k < 4; k++)
+            v[k] = wrow * (__builtin_amdgcn_exp2f(fmaf(v[k], 1.4426950408889634f, neg_lse2)) - (clab == 32 * j + 16 * b + k ? 1.f : 0.f));
+        }
+        if (RES) { const bf16x4_t x = *at;
+#pragma unroll
+          for (int k = 0; k < 4; k++) v[k] += (float)x[k]; }
+        bf16x4_t w;
+#pragma unroll
+        for (int k = 0; k < 4; k++) w[k] = (bf16_t)v[k];
+        *at = w;
+      }
+  }
+  asm volatile("" ::: "memory");                           // LDS operations of a wave complete in order
+  u32x4 out[8];
+#pragma unroll
+  for (int it = 0; it < 8; it++) out[it] = *reinterpret_cast<const u32x4*>(rows + it * 1024 + (cr ^ ((it & 3) * 64)));
+  const uint32_t at = (uint32_t)((r4 * p.ldc + c16 * 8) * 2);
+  const int64_t step = 8 * p.ldc;                          // bytes of four rows
+  char* c = (char*)((bf16_t*)p.C + (int64_t)(o.row0 + 32 * i) * p.ldc + o.col0);
+#pragma unroll
+  for (int it = 0; it < 8; it++, c += step) {
+    const int r = o.row0 + 32 * i + 4 * it + r4;
+    if (!MASK || (r >= o.row_lo && r < o.row_hi)) *reinterpret_cast<u32x4*>(c + at) = out[it];
+  }
+  asm volatile("" ::: "memory");
+}
+
+// Softmax statistics of the logits, nothing of which is written (a lane owns 32 of a row's 128 columns, the others sit in lane ^ 16,
+// lane ^ 32): per row the maximum and the sum of exp(value - maximum).
+template <bool MASK>
+__device__ __forceinline__ void rd_stats(const GemmParams& p, const f32x16 (&t)[4], const RdOut& o, int i, int lane) {
+  const float alpha = p.alpha;
+#pragma unroll
+  for (int a = 0; a < 2; a++) {
+    float m = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+#pragma unroll
+      for (int e = 0; e < 8; e++) m = fmaxf(m, alpha * t[j][8 * a + e]);
+    m = fmaxf(m, __shfl_xor(m, 32, 64));
+    m = fmaxf(m, __shfl_xor(m, 16, 64));
+    const float nm2 = -1.4426950408889634f * m;
+    float s = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+#pragma unroll
+      for (int e = 0; e < 8; e++) s += __builtin_amdgcn_exp2f(fmaf(alpha * t[j][8 * a + e], 1.4426950408889634f, nm2));
+    s += __shfl_xor(s, 32, 64);
+    s += __shfl_xor(s, 16, 64);
+    const int r = o.row0 + 32 * i + 16 * a + (lane & 15);
+    if (lane < 16 && (!MASK || (r >= o.row_lo && r < o.row_hi))) *(reinterpret_cast<float2*>(p.epi_part) + (int64_t)r * (p.N / 128) + o.col0 / 128) = make_float2(m, s);
+  }
+}
+
+// A piece of work of the kernel below: one tile, or one part of a split tile's contraction.  Pointers are those of this wave.
+struct RdItem {
+  int row0, col0, row_lo, row_hi, pid, kpart, nt0, nt, n1, n2;
+  uint64_t a0, a1, b0, b1, b2, b3;                         // bases of both segments (NN: of the matrices below one another), for a step counted from this item's first
+  uint64_t bf; bool two;                                   // base of B in the first step; whether the second step has the same bases
+};
+
+// wave-uniform values the compiler does not know to be so, into scalar registers
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ uint64_t uni(uint64_t x) { return (uint64_t)(uint32_t)uni((int)(x >> 32)) << 32 | (uint32_t)uni((int)x); }
+
+template <int LIVE, int EPI = GEMM_EPI_NONE, int LAYOUT = RS_NT>
+__global__ __launch_bounds__(256) void gemm_mfma_rd_kernel(GemmParams p, int m_off, int tiles_m, int tiles_n) {
+  constexpr int BM = 256, BN = 256, BK = 64;
+  constexpr bool NN = LAYOUT == RS_NN, AK = LAYOUT == RS_TN;      // B is [K, N]; A is [K, M] and B [K, N]
+  extern __shared__ __align__(16) unsigned char smem[];
+  int rb_all = 0, mlive_all = p.M;
+  if (LIVE == 1) {
+    if (p.grp_n > 0) {                                   // the live row tiles of all groups, one group after the other
+      int total = 0;
+      for (int e = 0; e < p.grp_n; e++) total += (p.grp_off[e + 1] - p.grp_off[e] + BM - 1) / BM;
+      tiles_m = min(tiles_m, total);
+    } else {
+      int mmax;
+      mlive_all = gemm_rows(p, m_off, rb_all, mmax);
+      tiles_m = min(tiles_m, (max(mlive_all, 0) + BM - 1) / BM);
+    }
+  }
+  const int nblk = tiles_m * tiles_n;
+  int parts = p.tail_parts, first_split = nblk;            // tiles from first_split on are split into parts
+  if (LIVE == 1 && EPI == GEMM_EPI_NONE && p.tail_part) { parts = live_parts(p, nblk); if (parts > 1) first_split = 0; }
+  if (LIVE != 1 && EPI == GEMM_EPI_NONE && p.tail_first >= 0) first_split = p.tail_first;
+  const int items = first_split + (nblk - first_split) * parts;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+  const GemmSeg s0 = p.seg[0], s1 = p.nseg > 1 ? p.seg[1] : p.seg[0];
+  int nt0_all = p.seg[0].K / BK, nt_all = nt0_all + (p.nseg > 1 ? p.seg[1].K / BK : 0);
+  if (AK && p.k_dev) nt0_all = nt_all = min(nt_all, (max(*p.k_dev - p.k_off, 0) + BK - 1) / BK);
+
+  auto decode = [&](int item) {
+    RdItem w;
+    w.kpart = -1; w.pid = item;
+    if (item >= first_split) { const int i = item - first_split; w.kpart = i % parts; w.pid = first_split + i / parts; }
+    const int q8 = nblk / 8, rem = nblk % 8, xcd = w.pid % 8, loc = w.pid / 8;
+    const int logical = xcd * q8 + min(xcd, rem) + loc;
+    constexpr int GROUP = 4;                               // the 32 workgroups of an XCD cover 4 row tiles x 8 column tiles at a time, as above
+    const int in_group = GROUP * tiles_n, grp = logical / in_group, first_m = grp * GROUP;
+    const int gsize = min(tiles_m - first_m, GROUP);
+    int tile_m = first_m + (logical % in_group) % gsize;
+    const int tile_n = (logical % in_group) / gsize;
+    int b_group = 0, rb = rb_all, mlive = mlive_all;
+    if (LIVE == 1 && p.grp_n > 0) {                        // which group this row tile belongs to, and which of its tiles it is
+      int e = 0, rows_e = p.grp_off[1] - p.grp_off[0], nt_e = (rows_e + BM - 1) / BM;
+      while (tile_m >= nt_e && e + 1 < p.grp_n) {
+        tile_m -= nt_e; e++;
+        rows_e = p.grp_off[e + 1] - p.grp_off[e]; nt_e = (rows_e + BM - 1) / BM;
+      }
+      rb = p.grp_off[e]; mlive = rows_e; b_group = e;
+    }
+    w.row_lo = rb + tile_m * BM; w.row_hi = rb + mlive;
+    w.row0 = LIVE ? min(w.row_lo, (LIVE == 1 && p.grp_off ? p.rows_cap : p.M) - BM) : tile_m * BM;
+    w.col0 = tile_n * BN;
+    w.nt0 = nt0_all; w.nt = nt_all;
+    int64_t lo = 0;
+    if (w.kpart >= 0) {                                    // steps [lo, hi) of the contraction; the launcher made sure that every part starts inside segment 0
+      lo = (int64_t)nt_all * w.kpart / parts;
+      const int hi = (int)((int64_t)nt_all * (w.kpart + 1) / parts);
+      w.nt0 = min(nt0_all, hi) - (int)lo; w.nt = hi - (int)lo;
+    }
+    const int64_t k_skip = lo * BK;
+    const bf16_t* b0p = (const bf16_t*)s0.B + (int64_t)b_group * p.grp_b_stride; const bf16_t* b1p = (const bf16_t*)s1.B;
+    int colg = w.col0, a2off = 0;
+    if (p.ncg > 0) {                                       // which weight matrix this column tile belongs to
+      int g = 0;
+      while (g + 1 < p.ncg && w.col0 >= p.cg_end[g]) g++;
+      colg = w.col0 - (g ? p.cg_end[g - 1] : 0);
+      b0p = (const bf16_t*)p.cg_B1[g]; b1p = (const bf16_t*)(p.nseg > 1 ? p.cg_B2[g] : p.cg_B1[g]); a2off = p.nseg > 1 ? p.cg_a2[g] : 0;
+    }
+    w.n1 = w.n2 = w.nt0; w.b2 = w.b3 = 0; w.two = w.nt0 >= 2;
+    if (AK) {
+      w.a0 = w.a1 = (uint64_t)((const bf16_t*)s0.A + (k_skip + wave * 16) * s0.lda + w.row0);
+      w.b0 = w.b1 = (uint64_t)(b0p + (k_skip + wave * 16) * s0.ldb + w.col0);
+      w.bf = w.b0;
+      return w;
+    }
+    w.a0 = (uint64_t)((const bf16_t*)s0.A + (int64_t)(w.row0 + wave * 64) * s0.lda + k_skip);
+    w.a1 = (uint64_t)((const bf16_t*)s1.A + a2off + (int64_t)(w.row0 + wave * 64) * s1.lda - (int64_t)w.nt0 * BK);
+    if (NN) {
+      const int64_t ldb = s0.ldb, row_w = (int64_t)(wave * 16) * ldb + w.col0;
+      // base of a matrix minus its first row: step t of this item reads rows 64 t .. of it
+      auto base = [&](const void* m, int64_t first_row) {
+        return (uint64_t)m + (uint64_t)(2 * ((int64_t)b_group * p.grp_b_stride + row_w + (k_skip - first_row) * ldb));
+      };
+      w.b0 = base(s0.B, 0); w.b2 = base(p.nb[0], p.nb_row[0]); w.b3 = base(p.nb[1], p.nb_row[1]);
+      w.b1 = (uint64_t)s1.B + (uint64_t)(2 * (row_w - (int64_t)w.nt0 * BK * ldb));
+      if (p.nn > 1) w.n1 = (int)(p.nb_row[0] / BK - lo);
+      if (p.nn > 2) w.n2 = (int)(p.nb_row[1] / BK - lo);
+    } else {
+      w.b0 = (uint64_t)(b0p + (int64_t)(colg + wave * 64) * s0.ldb + k_skip);
+      w.b1 = (uint64_t)(b1p + (int64_t)(colg + wave * 64) * s1.ldb - (int64_t)w.nt0 * BK);
+    }
+    const int end = w.n1 > 0 ? w.n1 : w.n2 > 0 ? w.n2 : w.nt0;
+    w.bf = w.n1 > 0 ? w.b0 : w.n2 > 0 ? w.b2 : w.b3; w.two = w.two && end >= 2;
+    return w;
+  };
+
+  if ((int)blockIdx.x >= items) return;
+  // per-lane LDS read addresses, by slice or (transposing reads) by pair of column blocks, and global offsets of even and odd loads
+  unsigned ar[4], br[4], oa0[2], ob0[2], oa1[2], ob1[2];
+  {
+    const int l15 = lane & 15, q = lane >> 4, r = (lane >> 2) & 3, lrow = lane >> 3, lch = lane & 7, l31 = lane & 31, hh = lane >> 5;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+      const unsigned c = (unsigned)(l15 * 128 + (((4 * (k & 1) + q) ^ (l15 >> 1)) * 16)), t = (unsigned)((8 * q + r) * 512 + ((k ^ r) * 64) + (lane & 3) * 8);
+      ar[k] = AK ? t + (unsigned)(wm * 256) : c + (unsigned)(wm * 128 * 128);
+      br[k] = LAYOUT != RS_NT ? t + (unsigned)(wn * 256) : c + (unsigned)(wn * 128 * 128);
+    }
+#pragma unroll
+    for (int o = 0; o < 2; o++) {
+      const int ch = (lch ^ ((lrow >> 1) | (o * 4))) * 8, cu = ((l31 >> 2) ^ (2 * o + hh)) * 32 + (l31 & 3) * 8;
+      oa0[o] = (unsigned)((AK ? hh * s0.lda + cu : lrow * s0.lda + ch) * 2); oa1[o] = (unsigned)((lrow * s1.lda + ch) * 2);
+      ob0[o] = (unsigned)((LAYOUT != RS_NT ? hh * s0.ldb + cu : lrow * s0.ldb + ch) * 2); ob1[o] = (unsigned)((lrow * s1.ldb + ch) * 2);
+    }
+  }
+  // bytes between two loads: eight rows, or two rows of the contraction; bytes of a step of the contraction
+  const int sa0 = (int)((AK ? 4 : 16) * s0.lda), sa1 = (int)(16 * s1.lda), sb0 = (int)((LAYOUT != RS_NT ? 4 : 16) * s0.ldb), sb1 = (int)(16 * s1.ldb);
+  const int ka = (int)(128 * s0.lda), kb = (int)(128 * s0.ldb);
+  const int64_t step_a = AK ? ka : 2 * BK, step_b = LAYOUT != RS_NT ? kb : 2 * BK;
+  int half = 0, fresh = 1;                                 // LDS half stage of the next item's first step; nothing of it under way
+  for (int item = blockIdx.x; item < items; item += (int)gridDim.x) {
+    const RdItem w = decode(item);
+    bool chain = false;
+    uint64_t an = w.a0, bn = w.bf;                         // past this item's end the loads take its own first steps again (nobody reads them) ...
+    if (item + (int)gridDim.x < items) {
+      const RdItem nx = decode(item + (int)gridDim.x);
+      if (nx.two) { chain = true; an = nx.a0; bn = nx.bf; }  // ... or those of the next item
+    }
+    an -= (uint64_t)(w.nt * step_a); bn -= (uint64_t)(w.nt * step_b);
+    if (AK && w.nt == 0) {                                 // no live rows to contract (the same for every item): the result is zero
+      if (!p.accumulate || w.kpart >= 0) {
+        float* c = w.kpart >= 0 ? p.tail_part + ((int64_t)(w.pid - first_split) * parts + w.kpart) * (BM * BN) : (float*)row_group_base(p, w.row0) + (int64_t)w.row0 * p.ldc + w.col0;
+        const int64_t ld = w.kpart >= 0 ? BN : p.ldc;
+        for (int r = tid >> 6; r < BM; r += 4) *reinterpret_cast<f32x4*>(c + r * ld + lane * 4) = (f32x4){0.f, 0.f, 0.f, 0.f};
+      }
+    } else {
+      f32x16 acc[4][4];
+      const int lim = w.nt + (chain || w.two ? 1 : 0), off = half * 32768, lw = wave * 8192;
+#define RD_LOOP(name) \
+      asm volatile(GEMM_##name##_LOOP_ASM \
+                   : "={a[0:15]}"(acc[0][0]), "={a[16:31]}"(acc[0][1]), "={a[32:47]}"(acc[0][2]), "={a[48:63]}"(acc[0][3]), \
+                     "={a[64:79]}"(acc[1][0]), "={a[80:95]}"(acc[1][1]), "={a[96:111]}"(acc[1][2]), "={a[112:127]}"(acc[1][3]), \
+                     "={a[128:143]}"(acc[2][0]), "={a[144:159]}"(acc[2][1]), "={a[160:175]}"(acc[2][2]), "={a[176:191]}"(acc[2][3]), \
+                     "={a[192:207]}"(acc[3][0]), "={a[208:223]}"(acc[3][1]), "={a[224:239]}"(acc[3][2]), "={a[240:255]}"(acc[3][3]) \
+                   : "v"(ar[0]), "v"(ar[1]), "v"(ar[2]), "v"(ar[3]), "v"(br[0]), "v"(br[1]), "v"(br[2]), "v"(br[3]), \
+                     "v"(oa0[0]), "v"(oa0[1]), "v"(ob0[0]), "v"(ob0[1]), "v"(oa1[0]), "v"(oa1[1]), "v"(ob1[0]), "v"(ob1[1]), \
+                     "s"(uni(w.a0)), "s"(uni(w.b0)), "s"(uni(w.a1)), "s"(uni(w.b1)), "s"(uni(an)), "s"(uni(bn)), "s"(sa0), "s"(sb0), "s"(sa1), "s"(sb1), \
+                     "s"(uni(w.nt0)), "s"(uni(w.nt)), "s"(uni(lim)), "s"(uni(off)), "s"(lw), "s"(uni(fresh)), "s"(uni(w.b2)), "s"(uni(w.b3)), "s"(uni(w.n1)), "s"(uni(w.n2)), "s"(kb), "s"(ka) \
+                   : GEMM_##name##_LOOP_CLOBBERS)
+      if constexpr (AK) RD_LOOP(RD_TN);
+      else if constexpr (NN) RD_LOOP(RD_NN);
+      else RD_LOOP(RD);
+#undef RD_LOOP
+      half = (half + 2 * (w.nt % 5)) % 5; fresh = !chain;
+      unsigned char* my = smem + ((half + 4) % 5) * 32768 + wave * 8192;
+      GemmParams q = p;
+      RdOut o = {w.row0 + wm * 128, w.col0 + wn * 128, w.row_lo, w.row_hi};
+      const bool part = EPI == GEMM_EPI_NONE && w.kpart >= 0;
+      if (part) {                                          // raw float sums of this part into the tile's scratch
+        q.C = p.tail_part + ((int64_t)(w.pid - first_split) * parts + w.kpart) * (BM * BN); q.ldc = BN; q.c_f32 = 1; q.alpha = 1.f; q.R = nullptr; q.accumulate = 0;
+        o = {wm * 128, wn * 128, 0, BM};
+      } else if (AK) q.C = row_group_base(p, w.row0);
+      const bool staged = EPI == GEMM_EPI_PROB || (!AK && EPI == GEMM_EPI_NONE && !q.c_f32 && !(q.ldc % 8) && (!q.R || (!(q.ldr % 8) && !((uintptr_t)q.R % 16))));
+      constexpr bool MASK = LIVE != 0;
+      u32x4 res[8];
+      if (staged && q.R) rd_load_residual<MASK>(q, res, o, 0, lane);
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        f32x16 t[4] = {acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
+        int el = lane;                                     // the piece's per-lane addresses are formed here, not kept across the loop
+        asm volatile("" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]), "+v"(el));
+        if constexpr (EPI == GEMM_EPI_STATS) rd_stats<MASK>(q, t, o, i, el);
+        else if constexpr (EPI == GEMM_EPI_PROB) rd_staged<MASK, true, false>(q, t, res, my, o, i, el);
+        else if constexpr (AK) {
+          if (q.accumulate) rd_rows<false, true, true>(q, t, o, i, el); else rd_rows<false, true, false>(q, t, o, i, el);
+        } else if (staged && q.R) rd_staged<MASK, false, true>(q, t, res, my, o, i, el);
+        else if (staged) rd_staged<MASK, false, false>(q, t, res, my, o, i, el);
+        else if (q.c_f32 && !q.R && !q.accumulate) rd_rows<MASK, true, false>(q, t, o, i, el);
+        else if (q.c_f32) rd_rows<MASK, true, true>(q, t, o, i, el);
+        else rd_rows<MASK, false, true>(q, t, o, i, el);
+      }
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0x0f70);                    // loads that nobody reads must land before the workgroup's LDS is released
 }
 
 template <int BM, int BN, int WM, int WN>
@@ -1149,51 +1470,54 @@ static bool ring_ok(const GemmParams& p) {
 static bool mfma_ok(const GemmParams& p);
 bool gemm_rs_applies(int mode, const GemmParams& p) { return mode == AS_BF16 && mfma_ok(p) && rs_ok(p); }
 
-// parts > 1: the contraction of every tile is split over that many workgroups
-static int launch_rs_cfg(as_ctx* ctx, const GemmParams& p_in, int m_off, int parts, hipStream_t st) {
+// parts > 1: the contraction of every tile is split over that many workgroups.  DIRECT: the persistent kernel, else the register-staged one
+// (no head epilogues).
+template <bool DIRECT, int LIVE, int LAYOUT, int EPI = GEMM_EPI_NONE>
+static int launch_tiles(as_ctx* ctx, const GemmParams& p, int m_off, int wgs, int tm, int tn, hipStream_t st) {
+  if constexpr (DIRECT) {
+    AS_SET_SMEM(ctx, (gemm_mfma_rd_kernel<LIVE, EPI, LAYOUT>), kRdSmem);
+    gemm_mfma_rd_kernel<LIVE, EPI, LAYOUT><<<dim3(std::min(wgs, kCus)), 256, kRdSmem, st>>>(p, m_off, tm, tn);
+  } else {
+    constexpr size_t smem = 131072 + 256 * 64;           // two stages of A and B tiles + a 64-byte line per lane (the staged epilogue: 4 x 128 rows of 272 bytes)
+    AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<LIVE, LAYOUT>), smem);
+    gemm_mfma_rs_kernel<LIVE, LAYOUT><<<dim3(wgs), 256, smem, st>>>(p, m_off, tm, tn);
+  }
+  AS_LAUNCH_CHECK(ctx);
+  return AS_OK;
+}
+
+template <bool DIRECT>
+static int launch_256(as_ctx* ctx, const GemmParams& p_in, int m_off, int parts, hipStream_t st) {
   GemmParams p = p_in;
-  constexpr size_t smem = 131072 + 256 * 64;             // two stages of A and B tiles + a 64-byte line per lane (the staged epilogue: 4 x 128 rows of 272 bytes)
-  AS_SET_SMEM(ctx, gemm_mfma_rs_kernel<0>, smem);
-  AS_SET_SMEM(ctx, gemm_mfma_rs_kernel<1>, smem);
-  AS_SET_SMEM(ctx, gemm_mfma_rs_kernel<2>, smem);
-  AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<0, GEMM_EPI_NONE, RS_NN>), smem);
-  AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<1, GEMM_EPI_NONE, RS_NN>), smem);
-  AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<0, GEMM_EPI_NONE, RS_TN>), smem);
-  AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<2, GEMM_EPI_NONE, RS_NN>), smem);
-  AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<1, GEMM_EPI_STATS>), smem);
-  AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<1, GEMM_EPI_PROB>), smem);
   const int tn = p.N / 256;
+  int rc;
   p.tail_first = -1; p.tail_parts = 2;
   if (p.epi != GEMM_EPI_NONE && !p.m_dev) return as_fail(ctx, AS_ERR_SHAPE, "gemm: the head epilogues run over a device-side row count");
   if (rs_live(p)) {                                      // every row tile the live rows can reach; the kernel drops the rest
     const int tm = p.grp_n > 0 ? (int)cdiv(p.rows_cap, 256) + p.grp_n : (int)cdiv(p.M, 256);
-    if (p.epi == GEMM_EPI_STATS) gemm_mfma_rs_kernel<1, GEMM_EPI_STATS><<<dim3(tm * tn), 256, smem, st>>>(p, m_off, tm, tn);
-    else if (p.epi == GEMM_EPI_PROB) gemm_mfma_rs_kernel<1, GEMM_EPI_PROB><<<dim3(tm * tn), 256, smem, st>>>(p, m_off, tm, tn);
-    else {
-      if (!live_split_ok(p)) p.tail_part = nullptr;
-      const dim3 grid(p.tail_part ? std::max(tm * tn, kCus) : tm * tn);
-      if (p.nn) gemm_mfma_rs_kernel<1, GEMM_EPI_NONE, RS_NN><<<grid, 256, smem, st>>>(p, m_off, tm, tn);
-      else gemm_mfma_rs_kernel<1><<<grid, 256, smem, st>>>(p, m_off, tm, tn);
-      if (p.tail_part) { AS_LAUNCH_CHECK(ctx); gemm_tail_fixup_kernel<<<dim3(16 * std::min(tm * tn, 128)), 256, 0, st>>>(p, m_off, tm, tn); }
-    }
-  } else {
-    // a ragged last row tile runs over rows past M when the operands have them, else it is moved up (instance 2)
-    const int tm = (int)cdiv(p.M, 256), T = tm * tn;
-    const bool whole = p.rows_cap >= tm * 256 || p.M % 256 == 0;
-    if (p.M % 256 == 0) p.rows_cap = p.M;
-    if (parts > 1) { p.tail_first = 0; p.tail_parts = parts; }
-    else if (rs_tail_splits(p, T)) p.tail_first = T / kCus * kCus;
-    const int split = p.tail_first >= 0 ? T - p.tail_first : 0;
-    const dim3 grid(T - split + split * p.tail_parts);
-    if (p.tn) gemm_mfma_rs_kernel<0, GEMM_EPI_NONE, RS_TN><<<grid, 256, smem, st>>>(p, 0, tm, tn);
-    else if (p.nn && whole) gemm_mfma_rs_kernel<0, GEMM_EPI_NONE, RS_NN><<<grid, 256, smem, st>>>(p, 0, tm, tn);
-    else if (p.nn) gemm_mfma_rs_kernel<2, GEMM_EPI_NONE, RS_NN><<<grid, 256, smem, st>>>(p, 0, tm, tn);
-    else if (whole) gemm_mfma_rs_kernel<0><<<grid, 256, smem, st>>>(p, 0, tm, tn);
-    else gemm_mfma_rs_kernel<2><<<grid, 256, smem, st>>>(p, 0, tm, tn);
-    if (split) { AS_LAUNCH_CHECK(ctx); gemm_tail_fixup_kernel<<<dim3(16 * split), 256, 0, st>>>(p, 0, tm, tn); }
+    if (p.epi == GEMM_EPI_STATS) return launch_tiles<true, 1, RS_NT, GEMM_EPI_STATS>(ctx, p, m_off, tm * tn, tm, tn, st);
+    if (p.epi == GEMM_EPI_PROB) return launch_tiles<true, 1, RS_NT, GEMM_EPI_PROB>(ctx, p, m_off, tm * tn, tm, tn, st);
+    if (!live_split_ok(p)) p.tail_part = nullptr;
+    const int wgs = p.tail_part ? std::max(tm * tn, kCus) : tm * tn;
+    rc = p.nn ? launch_tiles<DIRECT, 1, RS_NN>(ctx, p, m_off, wgs, tm, tn, st) : launch_tiles<DIRECT, 1, RS_NT>(ctx, p, m_off, wgs, tm, tn, st);
+    if (!rc && p.tail_part) { gemm_tail_fixup_kernel<<<dim3(16 * std::min(tm * tn, 128)), 256, 0, st>>>(p, m_off, tm, tn); AS_LAUNCH_CHECK(ctx); }
+    return rc;
   }
-  AS_LAUNCH_CHECK(ctx);
-  return AS_OK;
+  // a ragged last row tile runs over rows past M when the operands have them, else it is moved up (instance 2)
+  const int tm = (int)cdiv(p.M, 256), T = tm * tn;
+  const bool whole = p.rows_cap >= tm * 256 || p.M % 256 == 0;
+  if (p.M % 256 == 0) p.rows_cap = p.M;
+  if (parts > 1) { p.tail_first = 0; p.tail_parts = parts; }
+  else if (rs_tail_splits(p, T)) p.tail_first = T / kCus * kCus;
+  const int split = p.tail_first >= 0 ? T - p.tail_first : 0;
+  const int wgs = T - split + split * p.tail_parts;
+  if (p.tn) rc = launch_tiles<DIRECT, 0, RS_TN>(ctx, p, 0, wgs, tm, tn, st);
+  else if (p.nn && whole) rc = launch_tiles<DIRECT, 0, RS_NN>(ctx, p, 0, wgs, tm, tn, st);
+  else if (p.nn) rc = launch_tiles<DIRECT, 2, RS_NN>(ctx, p, 0, wgs, tm, tn, st);
+  else if (whole) rc = launch_tiles<DIRECT, 0, RS_NT>(ctx, p, 0, wgs, tm, tn, st);
+  else rc = launch_tiles<DIRECT, 2, RS_NT>(ctx, p, 0, wgs, tm, tn, st);
+  if (!rc && split) { gemm_tail_fixup_kernel<<<dim3(16 * split), 256, 0, st>>>(p, 0, tm, tn); AS_LAUNCH_CHECK(ctx); }
+  return rc;
 }
 
 template <int BM, int BN, int NST>
@@ -1337,7 +1661,7 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
   if (p.tn) {
     if (!gemm_tn_applies(mode, variant, p) || m_off) return as_fail(ctx, AS_ERR_SHAPE, "gemm: only the hand-scheduled kernel reads A as [K, M]");
     prof_begin(ctx, st, p.k_dev ? AS_K_GEMM_DEVROWS : AS_K_GEMM_RS, p.k_dev ? 0.0 : 2.0 * p.M * p.N * p.seg[0].K);
-    const int rc = launch_rs_cfg(ctx, p, 0, pick_plain(p).parts, st);
+    const int rc = variant == 34 ? launch_256<false>(ctx, p, 0, pick_plain(p).parts, st) : launch_256<true>(ctx, p, 0, pick_plain(p).parts, st);
     prof_end(ctx, st);
     return rc;
   }
@@ -1407,7 +1731,7 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
       case 20: rc = launch_dlds_cfg<256, 256, 2, 4>(ctx, p, m_off, st); break;
       case 24: {
         if (!rs_ok(p) || (m_off && !p.m_dev)) { rc = launch_dlds_cfg<256, 256, 2, 4>(ctx, p, m_off, st); break; }
-        rc = launch_rs_cfg(ctx, p, m_off, pick.parts, st);
+        rc = variant == 34 ? launch_256<false>(ctx, p, m_off, pick.parts, st) : launch_256<true>(ctx, p, m_off, pick.parts, st);
         break; }
       case 25: rc = launch_ring_cfg<128, 128, 2>(ctx, p, pick.parts, st); break;
       case 26: rc = launch_ring_cfg<64, 64, 4>(ctx, p, pick.parts, st); break;
