@@ -107,7 +107,7 @@ struct GemmParams {
   // Set by the launcher, which finds room for kGemmTailFloats floats at tail_part.
   int tail_first, tail_parts; float* tail_part;
   // nn > 0: B of both segments is [K, N], rows of N elements with ONE row stride (seg[0].ldb == seg[1].ldb); segment 0's rows are those of
-  // nn <= 3 matrices below one another: seg[0].B, and from row nb_row[i] (a multiple of 64) on nb[i].  Hand-scheduled kernel only: ask
+  // nn <= 3 matrices below one another: seg[0].B, and from row nb_row[i] (bf16: a multiple of 64) on nb[i].  Not all kernels: ask
   // gemm_nn_applies first.
   int nn; const void* nb[2]; int nb_row[2];
   // tn: A of the one segment is [K, M] and B [K, N] (hand-scheduled kernel only: gemm_tn_applies), float result.  Its rows may be those of

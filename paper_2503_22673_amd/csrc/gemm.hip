@@ -54,10 +54,7 @@ __device__ __forceinline__ void store_out(const GemmParams& p, int z, int row, i
 // ------------------------------------------------------------- plain kernel
 // float FMAs, every product of an output in ascending order of k.  Tiles of BT x BT with 16 x 16 threads, rows in LDS with k
 // contiguous, so that a thread reads four k of a row at a time; the next K step's elements are on their way from memory
-// while this one is multiplied.  The fp32 tier's products are small and bound by latency, by the length of the chain load ->
-// LDS -> multiply per K step: 64-wide steps and 32 x 32 tiles while those do not fill the chip, 64 x 64 tiles beyond that.
-// The products of a 2-layer model of width 128 at 469 tokens: 28 us each with 64 x 64 tiles, 16-wide steps and nothing in
-// flight, 9.4 us so.
+// while this one is multiplied.  64-wide steps and 32 x 32 tiles (bf16 only) while those do not fill the chip, 64 x 64 tiles beyond.
 template <typename T, int BT, int BK>
 __global__ __launch_bounds__(256) void gemm_fma_kernel(GemmParams p, int m_off) {
   constexpr int TT = BT / 16, LS = BK + 4, PER = BT * BK / 4 / 256;      // outputs per thread and side; groups of four elements a thread loads
@@ -129,6 +126,131 @@ __global__ __launch_bounds__(256) void gemm_fma_kernel(GemmParams p, int m_off) 
       const int r = row0 + ty + 16 * i, c = col0 + tx + 16 * j;
       if (r < M && c < p.N) store_out<T>(p, z, r, c, acc[i][j], rb);
     }
+}
+
+// ------------------------------------------------------------- small float products
+// The fp32 tier's products on the matrix cores (v_mfma_f32_16x16x4f32: float products and sums, as FMAs), for models small enough
+// that a product is one chain load -> multiply -> store and little else.  So: a workgroup owns 16 T x 16 T results, its four waves take
+// every fourth 16-wide chunk of the contraction each, operands come from memory into the fragments without LDS (a lane loads four
+// consecutive k of its row, 16 bytes; the four k of one matrix instruction are then 4 apart, in both operands alike), the next four
+// chunks' loads are in flight behind the products of these, and one sum over the four waves ends it.  T = 1 until its 16 x 16 tiles are
+// eight workgroups per CU, T = 2 beyond, as half the operand reads per product count then.
+// NN: B is [K, N], rows of up to three matrices below one another (p.nn): the layout of a weight matrix in the product with its output
+// gradient, so that no matrix is transposed first.  A lane then loads its column of four rows, 4 bytes each.
+template <int T, bool NN>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p, int m_off) {
+  constexpr int U = 4;                                     // chunks in flight
+  __shared__ __align__(16) f32x4 red[4][T * T][64];
+  int rb, mmax;
+  const int M = gemm_rows(p, m_off, rb, mmax);
+  const int row0 = blockIdx.y * (16 * T), col0 = blockIdx.x * (16 * T), z = blockIdx.z;
+  if (row0 >= M) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, q = lane >> 4;
+  // which weight matrix this lane's columns belong to (groups that end inside a tile: one segment only, so that A is the same for all)
+  const float* bp[2][T]; int64_t a2 = 0;
+#pragma unroll
+  for (int t = 0; t < T; t++) {
+    const int n = min(col0 + 16 * t + l15, p.N - 1);
+    int g = 0;
+    if (!NN && p.ncg > 0) while (g + 1 < p.ncg && n >= p.cg_end[g]) g++;
+    const int nb = n - (g ? p.cg_end[g - 1] : 0);
+#pragma unroll
+    for (int s = 0; s < 2; s++) {
+      const float* B = (const float*)(p.ncg > 0 ? (s ? p.cg_B2[g] : p.cg_B1[g]) : p.seg[s].B);
+      bp[s][t] = NN ? B + n : B + (int64_t)nb * p.seg[s].ldb;
+    }
+    if (p.ncg > 0 && p.nseg > 1) a2 = p.cg_a2[g];
+  }
+  const float* ap[2][T];
+#pragma unroll
+  for (int t = 0; t < T; t++) {
+    const int64_t r = rb + min(row0 + 16 * t + l15, max(M, 1) - 1);
+    ap[0][t] = (const float*)p.seg[0].A + r * p.seg[0].lda; ap[1][t] = (const float*)p.seg[1].A + r * p.seg[1].lda + a2;
+  }
+  const int K0 = p.seg[0].K, K1 = p.nseg > 1 ? p.seg[1].K : 0;
+  bool va[2], vb[2];                                       // rows in whole 16-byte pieces
+#pragma unroll
+  for (int s = 0; s < 2; s++) {
+    const int K = s ? K1 : K0;
+    va[s] = K % 4 == 0 && p.seg[s].lda % 4 == 0 && (uintptr_t)ap[s][0] % 16 == 0;
+    vb[s] = K % 4 == 0 && p.seg[s].ldb % 4 == 0 && (uintptr_t)bp[s][0] % 16 == 0 && (p.ncg == 0 || (((uintptr_t)(s ? p.cg_B2[0] : p.cg_B1[0]) | (uintptr_t)(s ? p.cg_B2[p.ncg - 1] : p.cg_B1[p.ncg - 1]) | (uintptr_t)(s ? p.cg_B2[p.ncg / 2] : p.cg_B1[p.ncg / 2])) % 16 == 0));
+  }
+  const int n0 = (K0 + 15) / 16, nall = n0 + (K1 + 15) / 16;
+  const int c_lo = (int)((int64_t)nall * z / p.splitk), c_hi = (int)((int64_t)nall * (z + 1) / p.splitk);
+  auto four = [&](const float* row, int k, int K, bool vec) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (k >= K) return v;
+    if (vec) return *reinterpret_cast<const f32x4*>(row + k);
+#pragma unroll
+    for (int e = 0; e < 4; e++) if (k + e < K) v[e] = row[k + e];
+    return v;
+  };
+  auto fetch = [&](int c, f32x4 (&a)[T], f32x4 (&b)[T]) {
+    const int s = c < n0 ? 0 : 1, k = (s ? c - n0 : c) * 16 + 4 * q, K = c >= c_hi ? 0 : s ? K1 : K0;       // past the end: zeros
+#pragma unroll
+    for (int t = 0; t < T; t++) {
+      a[t] = four(s ? ap[1][t] : ap[0][t], k, K, s ? va[1] : va[0]);
+      if (!NN) { b[t] = four(s ? bp[1][t] : bp[0][t], k, K, s ? vb[1] : vb[0]); continue; }
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        const float* col = s ? bp[1][t] : bp[0][t];
+        int64_t kk = k + e;
+        if (!s && p.nn > 1) {
+          const int n = min(col0 + 16 * t + l15, p.N - 1);
+          if (p.nn > 2 && kk >= p.nb_row[1]) { col = (const float*)p.nb[1] + n; kk -= p.nb_row[1]; }
+          else if (kk >= p.nb_row[0]) { col = (const float*)p.nb[0] + n; kk -= p.nb_row[0]; }
+        }
+        b[t][e] = k + e < K ? col[kk * p.seg[0].ldb] : 0.f;
+      }
+    }
+  };
+  f32x4 acc[T][T];
+#pragma unroll
+  for (int i = 0; i < T; i++)
+#pragma unroll
+    for (int j = 0; j < T; j++) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  f32x4 a[U][T], b[U][T];
+  int c = c_lo + wave;
+#pragma unroll
+  for (int u = 0; u < U; u++) fetch(c + 4 * u, a[u], b[u]);
+  while (c < c_hi) {
+    f32x4 na[U][T], nb[U][T];
+    const bool more = c + 4 * U < c_hi;
+    if (more) {
+#pragma unroll
+      for (int u = 0; u < U; u++) fetch(c + 4 * (U + u), na[u], nb[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++)
+      if (c + 4 * u < c_hi) {
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+#pragma unroll
+          for (int i = 0; i < T; i++)
+#pragma unroll
+            for (int j = 0; j < T; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[u][j][e], a[u][i][e], acc[i][j], 0, 0, 0);   // transposed: a lane owns a row
+      }
+    if (more) {
+#pragma unroll
+      for (int u = 0; u < U; u++)
+#pragma unroll
+        for (int t = 0; t < T; t++) { a[u][t] = na[u][t]; b[u][t] = nb[u][t]; }
+    }
+    c += 4 * U;
+  }
+#pragma unroll
+  for (int i = 0; i < T; i++)
+#pragma unroll
+    for (int j = 0; j < T; j++) red[wave][i * T + j][lane] = acc[i][j];
+  __syncthreads();
+  if (wave >= T * T) return;
+  const int i = wave / T, j = wave % T, r = row0 + 16 * i + l15, n = col0 + 16 * j + 4 * q;
+  f32x4 v = red[0][wave][lane];
+#pragma unroll
+  for (int w = 1; w < 4; w++) v += red[w][wave][lane];
+  if (r >= M) return;
+#pragma unroll
+  for (int e = 0; e < 4; e++) if (n + e < p.N) store_out<float>(p, z, r, n + e, v[e], rb);
 }
 
 // -------------------------------------------------------------- MFMA kernel
@@ -1447,6 +1569,11 @@ static bool rs_ok(const GemmParams& p) {
 static bool rs_live(const GemmParams& p) { return p.m_dev || p.grp_off; }
 constexpr int kCus = 256;
 static int fma_tile(const GemmParams& p) { return cdiv(p.N, 64) * cdiv(p.M, 64) * p.splitk >= kCus ? 64 : 32; }
+// float products: 16 x 16 results per workgroup, 32 x 32 (gemm_f32_kernel), or 4: 64 x 64 (gemm_fma_kernel)
+static int f32_tile(const GemmParams& p) {
+  if (cdiv(p.N, 16) * cdiv(p.M, 16) * p.splitk <= 8 * kCus) return 1;
+  return p.nn || cdiv(p.N, 64) * cdiv(p.M, 64) * p.splitk < 4 * kCus ? 2 : 4;
+}
 static int k_steps(const GemmParams& p) { return (int)(p.seg[0].K / 64) + (p.nseg > 1 ? (int)(p.seg[1].K / 64) : 0); }
 // The tiles of a last partial round are split in two when that round would leave at least half of the CUs idle, the launch
 // has full rounds before it and the contraction is long enough to be worth a second small launch: a launch of 3696 tiles
@@ -1629,6 +1756,7 @@ static GemmPick pick_cfg(const GemmParams& p) {
 }
 
 bool gemm_nn_applies(int mode, int variant, const GemmParams& p) {
+  if (mode == AS_FP32) return variant <= 1 && p.nn >= 1 && p.nn <= 3 && !p.ncg && (p.nseg < 2 || p.seg[1].ldb == p.seg[0].ldb);
   if (mode != AS_BF16 || (variant != 0 && variant != 2 && variant != 34) || !mfma_ok(p) || !rs_ok(p)) return false;
   if (p.nn < 1 || p.nn > 3 || p.ncg || p.epi != GEMM_EPI_NONE || p.seg[0].ldb > (1 << 22) || (p.nseg > 1 && p.seg[1].ldb != p.seg[0].ldb)) return false;
   int row = 0;
@@ -1657,7 +1785,7 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
   if (p.splitk > 1 && !p.partial) return as_fail(ctx, AS_ERR_WORKSPACE, "gemm: split-K needs a partial buffer");
   if (p.accumulate && !p.c_f32) return as_fail(ctx, AS_ERR_SHAPE, "gemm: accumulate needs float output");
   if (p.grp_off && p.splitk > 1) return as_fail(ctx, AS_ERR_SHAPE, "gemm: grouped rows and split-K do not combine");
-  if (p.nn && (!gemm_nn_applies(mode, variant, p) || (m_off && !p.m_dev))) return as_fail(ctx, AS_ERR_SHAPE, "gemm: only the hand-scheduled kernel reads B as [K, N]");
+  if (p.nn && (!gemm_nn_applies(mode, variant, p) || (m_off && !p.m_dev))) return as_fail(ctx, AS_ERR_SHAPE, "gemm: B as [K, N] needs the hand-scheduled kernel or the float one");
   if (p.tn) {
     if (!gemm_tn_applies(mode, variant, p) || m_off) return as_fail(ctx, AS_ERR_SHAPE, "gemm: only the hand-scheduled kernel reads A as [K, M]");
     prof_begin(ctx, st, p.k_dev ? AS_K_GEMM_DEVROWS : AS_K_GEMM_RS, p.k_dev ? 0.0 : 2.0 * p.M * p.N * p.seg[0].K);
@@ -1673,6 +1801,7 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
       for (int e = 0; e < p.grp_n; e++) {
         GemmParams q = p; q.grp_n = 0; q.grp = e; q.grp_rows = p.grp_rows / p.grp_n;
         q.seg[0].B = (const char*)p.seg[0].B + (size_t)e * p.grp_b_stride * esz;
+        for (int i = 0; i + 1 < p.nn; i++) q.nb[i] = (const char*)p.nb[i] + (size_t)e * p.grp_b_stride * esz;
         const int rc1 = launch_gemm_off(ctx, mode, variant, q, 0, st);
         if (rc1) return rc1;
       }
@@ -1692,8 +1821,9 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
     bool fused = mode == AS_BF16 && variant != 1 && mfma_ok(p) && ((c == 24 && rs_ok(p)) || c == 25 || c == 26);
     for (int g = 0; g < p.ncg && fused; g++) fused = p.cg_end[g] % width == 0 && !((uintptr_t)p.cg_B1[g] % 16) && (p.nseg < 2 || !((uintptr_t)p.cg_B2[g] % 16));
     if (mode == AS_FP32) {
+      const int t = f32_tile(p);                         // the small kernel takes groups that end inside a tile if A is the same for all
       fused = true;
-      for (int g = 0; g < p.ncg; g++) fused = fused && p.cg_end[g] % fma_tile(p) == 0;
+      for (int g = 0; g < p.ncg; g++) fused = fused && ((t < 4 && p.nseg == 1) || p.cg_end[g] % (16 * t) == 0);
     }
     if (!fused) {                                        // one launch per group
       const size_t esz = mode == AS_BF16 ? 2 : 4;
@@ -1741,8 +1871,15 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
     const int bt = fma_tile(p);
     const bool big = bt == 64;
     dim3 grid((unsigned)cdiv(p.N, bt), (unsigned)cdiv(p.M, bt), (unsigned)p.splitk);
-    if (mode == AS_FP32) { if (big) gemm_fma_kernel<float, 64, 32><<<grid, 256, 0, st>>>(p, m_off); else gemm_fma_kernel<float, 32, 64><<<grid, 256, 0, st>>>(p, m_off); }
-    else if (big) gemm_fma_kernel<bf16_t, 64, 32><<<grid, 256, 0, st>>>(p, m_off);
+    if (mode == AS_FP32) {
+      const int t = f32_tile(p);
+      const dim3 g((unsigned)cdiv(p.N, 16 * t), (unsigned)cdiv(p.M, 16 * t), (unsigned)p.splitk);
+      if (t == 1 && p.nn) gemm_f32_kernel<1, true><<<g, 256, 0, st>>>(p, m_off);
+      else if (t == 1) gemm_f32_kernel<1, false><<<g, 256, 0, st>>>(p, m_off);
+      else if (t == 2 && p.nn) gemm_f32_kernel<2, true><<<g, 256, 0, st>>>(p, m_off);
+      else if (t == 2) gemm_f32_kernel<2, false><<<g, 256, 0, st>>>(p, m_off);
+      else gemm_fma_kernel<float, 64, 32><<<dim3((unsigned)cdiv(p.N, 64), (unsigned)cdiv(p.M, 64), (unsigned)p.splitk), 256, 0, st>>>(p, m_off);
+    } else if (big) gemm_fma_kernel<bf16_t, 64, 32><<<grid, 256, 0, st>>>(p, m_off);
     else gemm_fma_kernel<bf16_t, 32, 64><<<grid, 256, 0, st>>>(p, m_off);
     AS_LAUNCH_CHECK(ctx);
   }
