@@ -14,6 +14,7 @@
 // In all of them workgroup ids are first de-interleaved over the 8 XCDs (ids are dealt round-robin to XCDs, each with a
 // private L2) and then walked in groups of row tiles, so that the tiles resident on one XCD share A and B panels.
 #include "common.h"
+#include <type_traits>
 
 // ------------------------------------------------------------------ helpers
 struct KRange { int beg, end; };   // k-tile range of one segment for this split
@@ -130,17 +131,19 @@ __global__ __launch_bounds__(256) void gemm_fma_kernel(GemmParams p, int m_off) 
 
 // ------------------------------------------------------------- small float products
 // The fp32 tier's products on the matrix cores (v_mfma_f32_16x16x4f32: float products and sums, as FMAs), for models small enough
-// that a product is one chain load -> multiply -> store and little else.  So: a workgroup owns 16 T x 16 T results, its four waves take
-// every fourth 16-wide chunk of the contraction each, operands come from memory into the fragments without LDS (a lane loads four
+// that a product is one chain load -> multiply -> store and little else.  So: a workgroup owns 16 T x 16 T results, its NW waves take
+// every NW-th 16-wide chunk of the contraction each, operands come from memory into the fragments without LDS (a lane loads four
 // consecutive k of its row, 16 bytes; the four k of one matrix instruction are then 4 apart, in both operands alike), the next four
-// chunks' loads are in flight behind the products of these, and one sum over the four waves ends it.  T = 1 until its 16 x 16 tiles are
+// chunks' loads are in flight behind the products of these, and one sum over the waves ends it.  Four waves up to 16
+// chunks, eight up to 32, else sixteen (T = 1): up to 64 chunks every load of the product is then under way at once.  T = 1 until its 16 x 16 tiles are
 // eight workgroups per CU, T = 2 beyond, as half the operand reads per product count then.
 // NN: B is [K, N], rows of up to three matrices below one another (p.nn): the layout of a weight matrix in the product with its output
 // gradient, so that no matrix is transposed first.  A lane then loads its column of four rows, 4 bytes each.
-template <int T, bool NN>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p, int m_off) {
+// 2-layer model of width 128, 478 tokens, a product: 9.4 us with 32x32 tiles through LDS and FMAs, 5.6 so (K 688 and 1024: 20 and 28, now 8).
+template <int T, bool NN, int NW>
+__global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(GemmParams p, int m_off) {
   constexpr int U = 4;                                     // chunks in flight
-  __shared__ __align__(16) f32x4 red[4][T * T][64];
+  __shared__ __align__(16) f32x4 red[NW][T * T][64];
   int rb, mmax;
   const int M = gemm_rows(p, m_off, rb, mmax);
   const int row0 = blockIdx.y * (16 * T), col0 = blockIdx.x * (16 * T), z = blockIdx.z;
@@ -212,17 +215,17 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p, int m_off) 
   f32x4 a[U][T], b[U][T];
   int c = c_lo + wave;
 #pragma unroll
-  for (int u = 0; u < U; u++) fetch(c + 4 * u, a[u], b[u]);
+  for (int u = 0; u < U; u++) fetch(c + NW * u, a[u], b[u]);
   while (c < c_hi) {
     f32x4 na[U][T], nb[U][T];
-    const bool more = c + 4 * U < c_hi;
+    const bool more = c + NW * U < c_hi;
     if (more) {
 #pragma unroll
-      for (int u = 0; u < U; u++) fetch(c + 4 * (U + u), na[u], nb[u]);
+      for (int u = 0; u < U; u++) fetch(c + NW * (U + u), na[u], nb[u]);
     }
 #pragma unroll
     for (int u = 0; u < U; u++)
-      if (c + 4 * u < c_hi) {
+      if (c + NW * u < c_hi) {
 #pragma unroll
         for (int e = 0; e < 4; e++)
 #pragma unroll
@@ -236,7 +239,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p, int m_off) 
 #pragma unroll
         for (int t = 0; t < T; t++) { a[u][t] = na[u][t]; b[u][t] = nb[u][t]; }
     }
-    c += 4 * U;
+    c += NW * U;
   }
 #pragma unroll
   for (int i = 0; i < T; i++)
@@ -247,7 +250,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p, int m_off) 
   const int i = wave / T, j = wave % T, r = row0 + 16 * i + l15, n = col0 + 16 * j + 4 * q;
   f32x4 v = red[0][wave][lane];
 #pragma unroll
-  for (int w = 1; w < 4; w++) v += red[w][wave][lane];
+  for (int w = 1; w < NW; w++) v += red[w][wave][lane];
   if (r >= M) return;
 #pragma unroll
   for (int e = 0; e < 4; e++) if (n + e < p.N) store_out<float>(p, z, r, n + e, v[e], rb);
@@ -1874,10 +1877,16 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
     if (mode == AS_FP32) {
       const int t = f32_tile(p);
       const dim3 g((unsigned)cdiv(p.N, 16 * t), (unsigned)cdiv(p.M, 16 * t), (unsigned)p.splitk);
-      if (t == 1 && p.nn) gemm_f32_kernel<1, true><<<g, 256, 0, st>>>(p, m_off);
-      else if (t == 1) gemm_f32_kernel<1, false><<<g, 256, 0, st>>>(p, m_off);
-      else if (t == 2 && p.nn) gemm_f32_kernel<2, true><<<g, 256, 0, st>>>(p, m_off);
-      else if (t == 2) gemm_f32_kernel<2, false><<<g, 256, 0, st>>>(p, m_off);
+      auto run = [&](auto nn) {
+        constexpr bool NN = decltype(nn)::value;
+        const int chunks = (int)(cdiv(p.seg[0].K, 16) + (p.nseg > 1 ? cdiv(p.seg[1].K, 16) : 0)) / p.splitk;
+        if (t == 2) gemm_f32_kernel<2, NN, 4><<<g, 256, 0, st>>>(p, m_off);
+        else if (chunks <= 16) gemm_f32_kernel<1, NN, 4><<<g, 256, 0, st>>>(p, m_off);
+        else if (chunks <= 32) gemm_f32_kernel<1, NN, 8><<<g, 512, 0, st>>>(p, m_off);
+        else gemm_f32_kernel<1, NN, 16><<<g, 1024, 0, st>>>(p, m_off);
+      };
+      if (t < 4 && p.nn) run(std::true_type{});
+      else if (t < 4) run(std::false_type{});
       else gemm_fma_kernel<float, 64, 32><<<dim3((unsigned)cdiv(p.N, 64), (unsigned)cdiv(p.M, 64), (unsigned)p.splitk), 256, 0, st>>>(p, m_off);
     } else if (big) gemm_fma_kernel<bf16_t, 64, 32><<<grid, 256, 0, st>>>(p, m_off);
     else gemm_fma_kernel<bf16_t, 32, 64><<<grid, 256, 0, st>>>(p, m_off);
