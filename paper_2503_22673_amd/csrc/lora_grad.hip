@@ -196,48 +196,45 @@ int launch_tn_grads(as_ctx* ctx, TnGradBatch b, int n, int r, float* partial, si
 
 // ---- fp32 tier -------------------------------------------------------------------------------------------------------
 // The same products with float operands, all those of one input group in one launch (a projection's dB and dA; the six of
-// q, k, v), X and U read as they are.  A workgroup owns 64 columns of one X and 16 columns of its U; its 16 waves take every
-// 16th token each, a lane one column of X (coalesced), U's values are the same for the whole wave (scalar loads), and the waves
-// are added in order through LDS.  More than 1024 tokens are split over grid.y, partial sums added in order by a second launch.
-// Bound by latency at the tier's sizes: as token-major copies of both operands, split-K products and their sums, two
-// layers of four adapters at 469 tokens took about 630 us in 56 launches; 44 us in 4 so.
-constexpr int PG_WAVES = 16, PG_J = 16;
+// q, k, v), X and U read as they are.  A workgroup owns 16 columns of one X and 16 of its U; its 16 waves take every 16th group of
+// four tokens each (v_mfma_f32_16x16x4f32: float products and sums; a lane loads its column of one token, 64 bytes a row), the loads of
+// eight groups in flight, and are added in order through LDS.  More than 1024 tokens are split over grid.y, partial sums added in order by
+// a second launch.  Bound by latency at the tier's sizes: two layers of four adapters at 478 tokens, four launches: 44 us with
+// 64 columns per workgroup, FMAs and a chain of 30 tokens per wave (4 to 12 workgroups a launch), 21 us so.
+constexpr int PG_WAVES = 16, PG_B = 16, PG_U = 8;
 __global__ __launch_bounds__(PG_WAVES * 64) void plain_grad_kernel(const PlainGradBatch b, int n, int r, int splits, float* __restrict__ partial) {
-  __shared__ float sh[PG_WAVES][64][PG_J / 4 + 1];         // four of the sixteen columns at a time
+  __shared__ __align__(16) f32x4 sh[PG_WAVES][64];
   int it = 0;
   while (it + 1 < b.n && (int)blockIdx.x >= b.m[it + 1].first_block) it++;
   const PlainGrad& m = b.m[it];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nj = (r + PG_J - 1) / PG_J, blk = (int)blockIdx.x - m.first_block, col = (blk / nj) * 64 + lane, j0 = (blk % nj) * PG_J;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, q = lane >> 4;
+  const int nj = (r + PG_B - 1) / PG_B, blk = (int)blockIdx.x - m.first_block, col0 = (blk / nj) * PG_B, j0 = (blk % nj) * PG_B;
   const int per = (n + splits - 1) / splits, t_lo = blockIdx.y * per, t_hi = min(n, t_lo + per);
-  const float* X = m.X + (col < m.M ? col : 0); const float* U = m.U + j0;
-  float acc[PG_J];
+  const bool in_x = col0 + l15 < m.M, in_u = j0 + l15 < r;
+  const float* X = m.X + (in_x ? col0 + l15 : 0); const float* U = m.U + (in_u ? j0 + l15 : 0);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int t = t_lo + 4 * wave; t < t_hi; t += 4 * PG_WAVES * PG_U) {
+    float x[PG_U], u[PG_U];
 #pragma unroll
-  for (int j = 0; j < PG_J; j++) acc[j] = 0.f;
-#pragma unroll 4
-  for (int t = t_lo + wave; t < t_hi; t += PG_WAVES) {
-    const float x = X[(int64_t)t * m.ldx];
-    const float* u = U + (int64_t)t * m.ldu;
-#pragma unroll
-    for (int j = 0; j < PG_J; j++) acc[j] = fmaf(x, u[j], acc[j]);
-  }
-  // wave w adds column quad q = w (four quads) over the waves; element (column, j) leaves through the thread that added it
-#pragma unroll
-  for (int q = 0; q < PG_J / 4; q++) {
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 4; k++) sh[wave][lane][k] = acc[4 * q + k];
-    __syncthreads();
-    if (wave < 4) {                                        // wave k of four: column j0 + 4 q + k
-      float s = 0.f;
-#pragma unroll
-      for (int w = 0; w < PG_WAVES; w++) s += sh[w][lane][wave];
-      const int j = j0 + 4 * q + wave;
-      if (col < m.M && j < r) {
-        if (splits > 1) partial[(int64_t)blockIdx.y * b.total + m.first_out + (int64_t)col * r + j] = s;
-        else m.C[(int64_t)col * m.sm + (int64_t)j * m.sj] = m.alpha * s;
-      }
+    for (int k = 0; k < PG_U; k++) {
+      const int tt = t + 4 * PG_WAVES * k + q;             // past the end: zeros in both operands
+      x[k] = in_x && tt < t_hi ? X[(int64_t)tt * m.ldx] : 0.f;
+      u[k] = in_u && tt < t_hi ? U[(int64_t)tt * m.ldu] : 0.f;
     }
+#pragma unroll
+    for (int k = 0; k < PG_U; k++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(u[k], x[k], acc, 0, 0, 0);   // lane: column l15 of X, columns 4 q .. + 3 of U
+  }
+  sh[wave][lane] = acc;
+  __syncthreads();
+  if (threadIdx.x >= 256) return;
+  const int src = threadIdx.x >> 2, e = threadIdx.x & 3;   // one element each
+  float s = 0.f;
+#pragma unroll
+  for (int w = 0; w < PG_WAVES; w++) s += reinterpret_cast<const float*>(&sh[w][src])[e];
+  const int col = col0 + (src & 15), j = j0 + 4 * (src >> 4) + e;
+  if (col < m.M && j < r) {
+    if (splits > 1) partial[(int64_t)blockIdx.y * b.total + m.first_out + (int64_t)col * r + j] = s;
+    else m.C[(int64_t)col * m.sm + (int64_t)j * m.sj] = m.alpha * s;
   }
 }
 __global__ __launch_bounds__(256) void plain_grad_sum_kernel(const PlainGradBatch b, int r, int splits, const float* __restrict__ partial) {
@@ -258,11 +255,11 @@ size_t plain_grad_partial_floats(int n, int64_t cols, int r) { return n > 1024 ?
 
 int launch_plain_grads(as_ctx* ctx, PlainGradBatch b, int n, int r, float* partial, size_t partial_floats, hipStream_t st) {
   if (n <= 0 || b.n <= 0 || r <= 0) return AS_OK;
-  const int nj = (int)cdiv(r, PG_J);
+  const int nj = (int)cdiv(r, PG_B);
   int64_t blocks = 0; b.total = 0;
   for (int i = 0; i < b.n; i++) {
     b.m[i].first_block = (int)blocks; b.m[i].first_out = b.total;
-    blocks += cdiv(b.m[i].M, 64) * nj; b.total += (int64_t)b.m[i].M * r;
+    blocks += cdiv(b.m[i].M, PG_B) * nj; b.total += (int64_t)b.m[i].M * r;
   }
   const int splits = plain_grad_splits(n);
   if (splits > 1 && (size_t)splits * b.total > partial_floats) return as_fail(ctx, AS_ERR_WORKSPACE, "adapter gradients: partial buffer too small");
