@@ -25,7 +25,6 @@ struct as_ctx {
   int device;
   std::string err;
   // staging owned by the context (as_pack only)
-  void* d_stage = nullptr; size_t d_stage_bytes = 0;
   void* h_stage = nullptr; size_t h_stage_bytes = 0;
   // optional per-launch timing (as_profile): event pairs around kernels of the tracked classes
   struct ProfRec { hipEvent_t a, b; double flops; int cls; };
@@ -171,9 +170,7 @@ int attention_query_tile(int n_q_heads, int n_kv_heads);   // tokens per workgro
 int launch_attention_bwd(as_ctx* ctx, int mode, int variant, const AttnParams& p, hipStream_t st);
 
 // ---- element-wise and friends (elementwise.hip) ---------------------------------
-int launch_pack(as_ctx* ctx, const int32_t* d_src_tokens, const int32_t* d_piece_dst,
-                const int32_t* d_piece_src, const uint8_t* d_piece_mask, int n_pieces, int n_out,
-                int pad_id, int32_t* d_tokens, uint8_t* d_mask, hipStream_t st);
+int launch_pack(as_ctx* ctx, const int32_t* h_tokens, const int32_t* h_cu, const uint8_t* h_mask, int n_out, int n_cu, int32_t* d_tokens, int32_t* d_cu, uint8_t* d_mask, hipStream_t st);
 // tok_c[i], mask_c[i] = tok[src], mask[src] with src = src_start[s] + (i - cu_c[s]) for the kept segment s holding i
 int launch_compact(as_ctx* ctx, const int32_t* tok, const uint8_t* mask, const int32_t* cu_c, const int32_t* src_start,
                    int n_seg, int n, int32_t* tok_c, uint8_t* mask_c, hipStream_t st);

@@ -28,30 +28,26 @@ template <typename T> static bool vec_ok(const void* p, int64_t ld) {
 }
 
 // ------------------------------------------------------------------ pack
-// The host has cut the batch into pieces (a kept part of a turn, or a pad
-// tail); piece_dst holds their start offsets in the output, ascending.
-__global__ void pack_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ piece_dst,
-                            const int32_t* __restrict__ piece_src, const uint8_t* __restrict__ piece_mask,
-                            int n_pieces, int n_out, int pad_id, int32_t* __restrict__ tok,
-                            uint8_t* __restrict__ mask) {
-  int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_out) return;
-  int lo = 0, hi = n_pieces - 1;            // last piece with piece_dst[p] <= t
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (piece_dst[mid] <= t) lo = mid; else hi = mid - 1;
+// The packed stream lies in pinned host memory, put together there: one pass over the bus.  Four tokens a thread, so that a wave asks
+// for a kilobyte of tokens at a time and the whole stream is under way at once.
+template <bool VEC>
+__global__ __launch_bounds__(256) void pack_kernel(const int32_t* __restrict__ h_tok, const int32_t* __restrict__ h_cu, const uint8_t* __restrict__ h_mask, int n_out, int n_cu,
+                                                   int32_t* __restrict__ tok, int32_t* __restrict__ cu, uint8_t* __restrict__ mask) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  for (int k = i; k < n_cu; k += gridDim.x * 256) cu[k] = h_cu[k];
+  if (VEC && 4 * i + 4 <= n_out) {                         // i < 2^29: n_out is an int
+    const int4 t = reinterpret_cast<const int4*>(h_tok)[i];
+    const uint32_t m = reinterpret_cast<const uint32_t*>(h_mask)[i];
+    reinterpret_cast<int4*>(tok)[i] = t; reinterpret_cast<uint32_t*>(mask)[i] = m;
+    return;
   }
-  int s = piece_src[lo];
-  tok[t] = s < 0 ? pad_id : src[s + (t - piece_dst[lo])];
-  mask[t] = piece_mask[lo];
+  for (int k = 4 * i; k < n_out && k < 4 * i + 4; k++) { tok[k] = h_tok[k]; mask[k] = h_mask[k]; }
 }
 
-int launch_pack(as_ctx* ctx, const int32_t* d_src_tokens, const int32_t* d_piece_dst,
-                const int32_t* d_piece_src, const uint8_t* d_piece_mask, int n_pieces, int n_out,
-                int pad_id, int32_t* d_tokens, uint8_t* d_mask, hipStream_t st) {
-  if (n_out <= 0) return AS_OK;
-  pack_kernel<<<cdiv(n_out, 256), 256, 0, st>>>(d_src_tokens, d_piece_dst, d_piece_src, d_piece_mask,
-                                                n_pieces, n_out, pad_id, d_tokens, d_mask);
+int launch_pack(as_ctx* ctx, const int32_t* h_tokens, const int32_t* h_cu, const uint8_t* h_mask, int n_out, int n_cu, int32_t* d_tokens, int32_t* d_cu, uint8_t* d_mask, hipStream_t st) {
+  const unsigned grid = (unsigned)std::max<int64_t>(1, cdiv(n_out, 1024));
+  if (!((uintptr_t)d_tokens % 16) && !((uintptr_t)d_mask % 4)) pack_kernel<true><<<grid, 256, 0, st>>>(h_tokens, h_cu, h_mask, n_out, n_cu, d_tokens, d_cu, d_mask);
+  else pack_kernel<false><<<grid, 256, 0, st>>>(h_tokens, h_cu, h_mask, n_out, n_cu, d_tokens, d_cu, d_mask);
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }

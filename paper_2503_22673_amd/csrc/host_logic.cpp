@@ -71,7 +71,10 @@ int pack_plan(int vocab, const int32_t* turn_tokens, const int32_t* turn_offsets
     int64_t L = 0;
     for (int32_t t = traj_offsets[i]; t < traj_offsets[i + 1]; t++) {
       if (turn_roles[t] > AS_ROLE_TOOL) return host_fail(err, AS_ERR_ROLE, "as_pack: role code %d of turn %d is outside 0..3", (int)turn_roles[t], t);
-      for (int32_t k = turn_offsets[t]; k < turn_offsets[t + 1]; k++)
+      // all of a turn at once, without a branch per token: the sign bit of t | (vocab - 1 - t) says t < 0 or t >= vocab
+      uint32_t outside = 0;
+      for (int32_t k = turn_offsets[t]; k < turn_offsets[t + 1]; k++) outside |= (uint32_t)turn_tokens[k] | ((uint32_t)vocab - 1u - (uint32_t)turn_tokens[k]);
+      for (int32_t k = turn_offsets[t]; (outside >> 31) && k < turn_offsets[t + 1]; k++)
         if (turn_tokens[k] < 0 || turn_tokens[k] >= vocab)
           return host_fail(err, AS_ERR_TOKEN_RANGE, "as_pack: token %d at offset %d is outside [0, %d)", turn_tokens[k], k, vocab);
       L += turn_offsets[t + 1] - turn_offsets[t];
