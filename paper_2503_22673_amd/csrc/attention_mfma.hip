@@ -839,13 +839,11 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv3_mfma(AttnParams p, float sc
 // the same phase: behind the barrier all issue the next tiles' loads, then all multiply, then all exponentiate.  Workgroups of four waves, three (dK / dV) or four to a
 // CU by their registers, overlap their phases; reading fragments ahead into registers costs a workgroup per CU and was slower
 // (dK / dV: 230 registers, 575 against 545 us of backward).
-// What is left of it: the compiler cannot tell the transposing reads (col64) from the direct-to-LDS loads issued just before and waits
-// for those (vmcnt(0)) in front of the first transposing read of a tile step (forward) or of each half of one (dQ, dK / dV).
-// The next tile therefore lands in the middle of a step and not at its end, and the barrier's own wait finds little left.  A
-// third stage was level with two under that wait, which says nothing about three stages without it.  The forward and dQ spill
-// seven and three registers; their reloads are on the path of the stream's last tile only.  32 query heads on 8 KV heads, this and the
-// eight-wave kernels with token-major copies: forward 186 and 200 us (8191 tokens, longest segment 4096), 271 and 309
-// (30000, 2500), 22 and 26 (1003, 700); backward 523 and 694, 926 and 1217, 60 and 77 us.
+// The tiles' loads are issued from assembly (tile64_to_lds): known to the compiler they cost a wait for all of them in front of the
+// first transposing read of a step (forward) or half step (dQ, dK / dV).  Without it, and with priority for the wave that has products
+// to issue: forward 2 to 5 % faster, backward 3 %.  32 query heads on 8 KV heads, this and the eight-wave kernels with token-major
+// copies: forward 172 and 200 us (8191 tokens, longest segment 4096), 257 and 309 (30000, 2500), 22 and 26 (1003, 700); backward 500
+// and 694, 900 and 1217, 58 and 77 us.
 __device__ __forceinline__ int swz64(int row) { return ((row & 2) << 1) | ((row >> 1) & 2) | ((row >> 3) & 1); }
 constexpr int T64_E = 64 * 64;                            // elements of a tile
 
@@ -854,21 +852,30 @@ __device__ __forceinline__ void tile64_offsets(int64_t ld, int wave, int lane, u
 #pragma unroll
   for (int i = 0; i < 2; i++) { const int row = wave * 16 + i * 8 + (lane >> 3); voff[i] = (uint32_t)((row * ld + (((lane & 7) ^ swz64(row)) * 8)) * 2); }
 }
+// The loads are written in assembly: issued through the builtin they are LDS writes the compiler knows of, and as it cannot tell the
+// transposing reads from them it waits for all of them (vmcnt(0)) in front of the first such read of a step.  They have no register
+// results; their arrival is what stage_barrier waits for.
+__device__ __forceinline__ uint32_t lds_addr(const void* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p; }
 __device__ __forceinline__ void tile64_to_lds(const bf16_t* base, int64_t ld, int row0, int row_max, const uint32_t (&voff)[2], bf16_t* s, int wave, int lane) {
+  const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_addr(s)) + wave * 2048;
   if (row0 + 63 <= row_max) {
     const char* b = (const char*)uniform_ptr(base + (int64_t)row0 * ld);
-#pragma unroll
-    for (int i = 0; i < 2; i++)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(b + voff[i]),
-                                       (__attribute__((address_space(3))) void*)(s + (wave * 2 + i) * 512), 16, 0, 0);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\ts_add_u32 m0, %0, 1024\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3"
+                 :: "s"(dst), "v"(voff[0]), "v"(voff[1]), "s"(b) : "memory", "m0", "scc");
     return;
   }
+  const bf16_t* src[2];                                   // the last tile of the stream: rows past the end repeat the last one
 #pragma unroll
-  for (int i = 0; i < 2; i++) {                           // the last tile of the stream: rows past the end repeat the last one
+  for (int i = 0; i < 2; i++) {
     const int row = wave * 16 + i * 8 + (lane >> 3);
-    const bf16_t* src = base + (int64_t)min(row0 + row, row_max) * ld + ((lane & 7) ^ swz64(row)) * 8;
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)(s + (wave * 2 + i) * 512), 16, 0, 0);
+    src[i] = base + (int64_t)min(row0 + row, row_max) * ld + ((lane & 7) ^ swz64(row)) * 8;
   }
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_add_u32 m0, %0, 1024\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off"
+               :: "s"(dst), "v"(src[0]), "v"(src[1]) : "memory", "m0", "scc");
+}
+// 64 floats, one per lane
+__device__ __forceinline__ void floats64_to_lds(const float* src, bf16_t* s) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" :: "s"(__builtin_amdgcn_readfirstlane(lds_addr(s))), "v"(src) : "memory", "m0");
 }
 // row fragment: row 32 blk + lane % 32, columns 16 ks + 8 h .. + 7 (f(row) = f(lane % 32): 32 blk does not touch bits 1..3)
 __device__ __forceinline__ bf16x8 row64(const bf16_t* tile, int blk, int ks, int l31, int h, int f) {
@@ -899,6 +906,9 @@ __device__ __forceinline__ void stage_barrier() {
   __builtin_amdgcn_s_waitcnt(0x0f70);
   __syncthreads();
 }
+
+// Of the waves of a SIMD the one with products to issue goes first (backward, 8191 to 30000 tokens: 1.5 to 2 % faster; the forward is level).
+__device__ __forceinline__ void matrix_phase(bool on) { if (on) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0); }
 
 template <int HPW>
 __global__ __launch_bounds__(256, 4) void attn_fwd64_mfma(AttnParams p, float sl2) {
@@ -1061,9 +1071,11 @@ __global__ __launch_bounds__(256, 4) void attn_bwd_dq64_mfma(AttnParams p, float
       f32x16 s = zero16(), dp = zero16();
 #pragma unroll
       for (int ks = 0; ks < KS; ks++) {
+        if (ks == 0) matrix_phase(true);
         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row64(sK, kb, ks, l31, h, f), qf[ks], s, 0, 0, 0);
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row64(sV, kb, ks, l31, h, f), dof[ks], dp, 0, 0, 0);
       }
+      matrix_phase(false);
       if (!full) {
 #pragma unroll
         for (int e = 0; e < 16; e++) {
@@ -1156,8 +1168,7 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dkv64_mfma(AttnParams p, floa
   auto stage_d = [&](int t0, int b) {
     tile64_to_lds(dO, ldo, t0, n - 1, voffD, sm + b * ST_E + T64_E, wave, lane);
     if (wave < 2)                                          // rows past n of a last tile are inside the n64 entries and masked
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((wave ? nd : nls) + (int64_t)jj * n64 + t0 + lane),
-                                       (__attribute__((address_space(3))) void*)(sm + b * ST_E + 2 * T64_E + wave * 128), 4, 0, 0);
+      floats64_to_lds((wave ? nd : nls) + (int64_t)jj * n64 + t0 + lane, sm + b * ST_E + 2 * T64_E + wave * 128);
   };
   stage_q(q_last * BKEY, 0); stage_d(q_last * BKEY, 0);
   const int u = u_base + l31, uc = min(u, n - 1);
@@ -1194,9 +1205,11 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dkv64_mfma(AttnParams p, floa
       }
 #pragma unroll
       for (int ks = 0; ks < KS; ks++) {
+        if (ks == 0) matrix_phase(true);
         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row64(sQ, qb, ks, l31, h, f), kf[ks], s, 0, 0, 0);
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row64(sD, qb, ks, l31, h, f), vf[ks], dp, 0, 0, 0);
       }
+      matrix_phase(false);
       if (!full) {                                         // the tile touches the diagonal or a segment end
 #pragma unroll
         for (int e = 0; e < 16; e++) {
@@ -1209,12 +1222,14 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dkv64_mfma(AttnParams p, floa
 #pragma unroll
       for (int x = 0; x < 2; x++) {
         const bf16x8 pv = pack8(s, x), ds = pack8(dp, x);
+        matrix_phase(true);
 #pragma unroll
         for (int cb = 0; cb < CB; cb++) {
           accV[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col64(sD, cn, 2 * qb + x, cb), pv, accV[cb], 0, 0, 0);
           accK[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col64(sQ, cn, 2 * qb + x, cb), ds, accK[cb], 0, 0, 0);
         }
       }
+      matrix_phase(false);
     }
   }
   if (u >= n) return;
