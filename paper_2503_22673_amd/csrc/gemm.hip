@@ -575,9 +575,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_dlds_kernel(GemmParams
 // above); a step waits for its own stage only (`vmcnt` of the younger ones), passes one barrier and asks for the stage
 // NST - 1 ahead.  What bounds it: a CU's path into LDS carries about 40 bytes per clock, 800 clocks (0.33 us) for the 32 KB of a
 // 128 x 128 step against 512 of matrix work, so a CU runs two workgroups (64 KB of LDS each) whose waits and barriers fall
-// at different times: 0.52 us per step and tile with two on a CU, 0.74 with one.  What is above 0.33 is LDS latency: the
-// compiled step reads the fragments of one 16-wide slice, waits for all of them (lgkmcnt(0)) and multiplies, four times, always
-// into the same registers, so no read is under way behind an MFMA.  64 x 64 tiles read twice the operand
+// at different times: 0.51 us per step and tile with two on a CU, 0.74 with one.  Three and four stages are level: 32 KB a step of every
+// CU at once is 25 bytes per clock and CU, what the 256x256 kernel draws from the L2s too (64 KB in 2200 clocks).  64 x 64 tiles read twice the operand
 // bytes per flop but give four times the workgroups: the adapters' 64-wide products, bound by reading A once, run
 // at 4.6 TB/s (15,500 rows, K 14336: 97 us; 128 x 64 register-staged tiles: 240; at 59,000 rows, where those fill the chip
 // too, the two are level).
@@ -672,17 +671,29 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(GemmParams p, int t
     const int nslot = slot == 0 ? NST - 1 : slot - 1;
     if (it + NST - 1 < nt) fetch(it + NST - 1, nslot);
     const bf16_t* a = sm + slot * ST_E + (wm * TM * 32 + l31) * BK; const bf16_t* b = sm + slot * ST_E + BM * BK + (wn * TN * 32 + l31) * BK;
+    // 128 x 128: all of the step's fragments are asked for before the first product, so that LDS latency is paid once and not once per
+    // slice (with two workgroups on a CU 1 % on average, up to 16; 64 x 64 tiles lose 1.5 % by it)
+    constexpr int AHEAD = TM * TN > 1 ? 4 : 1;             // slices read together
 #pragma unroll
-    for (int ks = 0; ks < 4; ks++) {
-      bf16x8 af[TM], bf[TN];
+    for (int k0 = 0; k0 < 4; k0 += AHEAD) {
+      bf16x8 af[AHEAD][TM], bf[AHEAD][TN];
 #pragma unroll
-      for (int i = 0; i < TM; i++) af[i] = *reinterpret_cast<const bf16x8*>(a + i * 32 * BK + coff[ks]);
+      for (int ks = 0; ks < AHEAD; ks++) {
 #pragma unroll
-      for (int j = 0; j < TN; j++) bf[j] = *reinterpret_cast<const bf16x8*>(b + j * 32 * BK + coff[ks]);
+        for (int i = 0; i < TM; i++) af[ks][i] = *reinterpret_cast<const bf16x8*>(a + i * 32 * BK + coff[k0 + ks]);
 #pragma unroll
-      for (int i = 0; i < TM; i++)
+        for (int j = 0; j < TN; j++) bf[ks][j] = *reinterpret_cast<const bf16x8*>(b + j * 32 * BK + coff[k0 + ks]);
+      }
 #pragma unroll
-        for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[j], af[i], acc[i][j], 0, 0, 0);   // transposed blocks
+      for (int ks = 0; ks < AHEAD; ks++)
+#pragma unroll
+        for (int i = 0; i < TM; i++)
+#pragma unroll
+          for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ks][j], af[ks][i], acc[i][j], 0, 0, 0);   // transposed blocks
+    }
+    if constexpr (AHEAD > 1) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 4 * (TM + TN), 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 4 * TM * TN, 0);
     }
     asm volatile("" ::: "memory");
     slot = slot == NST - 1 ? 0 : slot + 1;
@@ -1703,14 +1714,16 @@ struct GemmPick { int cfg, parts; };                     // parts: workgroups th
 // Plain rows in whole K steps: the kernel and the split that the measured step times say is fastest (us; every pair of
 // 14 projections of the 1B and 8B shapes and 9 row counts from 300 to 16,000, and the adapters' widths 64 to 192 from 300 to
 // 59,000 rows: 2 % over the best of all candidates on average, 20 % at worst):
-//   256x256 hand-scheduled  1.04 per K step and 13.9 per round of 256 workgroups (start-up and epilogue of a tile)
-//   128x128 ring            1.05 per step with two workgroups on every CU, 0.74 with one, 1.3 per round
-//   64x64 ring              0.46 and 0.30, 3.6 per launch
+//   256x256 hand-scheduled  0.87 per K step and 14.4 per round of 256 workgroups (start-up and epilogue of a tile)
+//   128x128 ring            1.02 per step with two workgroups on every CU, 0.74 with one, 1.3 per round
+//   64x64 ring              0.46 and 0.24, 3.1 per launch
 // and for a split the second launch, its partials written and read at about 4 TB/s, and its serial sum over the parts.
 // More than half a round of 256x256 tiles goes to the hand-scheduled kernel unsplit without looking further: from there on it
-// was at most 7 % behind (2560 x 8192 x 2112: 100 against 95) and mostly 15-40 % ahead.
-// Examples: 1531 x 4096 x 14400: 128x128 register-staged tiles 260, ring 226, 256x256 in two parts 173; 1003 x 2048 x 8256:
-// 136, 51 (four parts), 77; 512 x 2048 x 15744: 250, 53 (eight parts).
+// is at most 3 % behind and mostly 15-40 % ahead.  Constants fitted to every candidate of 12 projections of the 1B and 8B shapes at seven
+// row counts from 300 to 7000 and of the adapters' widths 64 and 192 from 300 to 30,000 rows: the pick is 0.3 % over the best on
+// average, 11 % at worst (with the constants of the register-staged 256x256 kernel 1.4 and 31 %).
+// Examples (us): 1531 x 4096 x 14400: 64x64 ring 330, 128x128 218, 256x256 in two parts 158; 1003 x 2048 x 8256: 72, 49 (four parts), 51 (six);
+// 1003 x 2048 x 16512: 128x128 in four parts 86, 256x256 in eight 73.
 static GemmPick pick_plain(const GemmParams& p) {
   const int steps = k_steps(p);
   const double mb = (double)p.M * p.N * 4e-6;
@@ -1725,9 +1738,9 @@ static GemmPick pick_plain(const GemmParams& p) {
     const double per = (double)cdiv(steps, parts);
     if (rs) {
       const int64_t T = cdiv(p.M, 256) * (p.N / 256);      // at most half a round
-      if (parts == 1) offer(24, 1, per * 1.04 + 13.9);
+      if (parts == 1) offer(24, 1, per * 0.87 + 14.4);
       else if (T * parts <= kCus && steps / parts >= 3 && (steps - cdiv(steps, parts)) < (int64_t)(p.seg[0].K / 64))
-        offer(24, parts, per * 1.04 + 13.9 + 4.1 + 2. * parts + 0.246 * (parts + 0.5) * mb);
+        offer(24, parts, per * 0.87 + 14.4 + 6.2 + 2. * parts + 0.208 * (parts + 0.5) * mb);
     }
     if (p.tn || ((double)parts * p.M * p.N > (double)kGemmTailFloats && parts > 1)) continue;   // tn: the hand-scheduled kernel only
     auto ring = [&](int cfg, int b, double launch, double one, double two, double round, double f0, double f_part, double f_mb) {
@@ -1736,8 +1749,8 @@ static GemmPick pick_plain(const GemmParams& p) {
       if (parts > 1) t += f0 + f_part * parts + f_mb * (parts + 0.5) * mb;
       offer(cfg, parts, t);
     };
-    ring(25, 128, 0., 0.74, 1.05, 1.3, 2.2, 0.54, 0.264);
-    ring(26, 64, 3.6, 0.30, 0.46, 0., 1.5, 0.28, 0.307);
+    ring(25, 128, 0., 0.74, 1.02, 1.3, 2.2, 0.65, 0.248);
+    ring(26, 64, 3.1, 0.243, 0.455, 0., 0.8, 0.19, 0.53);
   }
   return best;
 }
