@@ -194,7 +194,11 @@ int launch_nf4_quantize(as_ctx* ctx, int mode, const void* w, int64_t numel, uin
 int launch_nf4_dequantize(as_ctx* ctx, int mode, const uint8_t* codes, const float* absmax, int64_t numel, void* out, hipStream_t st);
 // out[c, r] = the dequantised element (r, c) of a [rows, cols] matrix (bf16), where nf4_transposed_ok
 bool nf4_transposed_ok(int mode, const uint8_t* codes, int rows, int cols, const void* out, int64_t ldo);
-int launch_nf4_dequantize_transposed(as_ctx* ctx, const uint8_t* codes, const float* absmax, int rows, int cols, void* out, int64_t ldo, hipStream_t st);
+// up to three quantised matrices [rows, cols] and where their values go; first: set by the launcher
+struct Nf4Piece { const uint8_t* codes; const float* absmax; void* out; int rows, cols, first; };
+struct Nf4Batch { Nf4Piece m[3]; int n; };
+int launch_nf4_dequantize_batch(as_ctx* ctx, int mode, Nf4Batch b, hipStream_t st);
+int launch_nf4_dequantize_transposed(as_ctx* ctx, Nf4Batch b, int64_t ldo, hipStream_t st);   // all with the same cols, each nf4_transposed_ok;
 // mixture-of-experts routing and row grouping (moe.hip)
 int launch_moe_route(as_ctx* ctx, const float* logit, int n, int E, int32_t* sel, float* w, hipStream_t st);
 int launch_moe_permute(as_ctx* ctx, const int32_t* sel, int n, int E, int32_t* eoff, int32_t* pos, int32_t* perm, hipStream_t st);

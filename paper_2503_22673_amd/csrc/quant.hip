@@ -45,14 +45,24 @@ __global__ void nf4_dequantize_kernel(const uint8_t* __restrict__ codes, const f
   for (int e = 0; e < 8; e++) o[e] = from_f<T>(lut[(c >> (4 * e)) & 15] * a);
 }
 
-// bf16, 16 elements per thread: eight code bytes in, two 16-byte stores (`out` 16-byte, `codes` 8-byte aligned).
+// the matrix of a batch that a block works on
+__device__ __forceinline__ int piece_of(const Nf4Batch& b, int block) {
+  int k = 0;
+  while (k + 1 < b.n && block >= b.m[k + 1].first) k++;
+  return k;
+}
+
+// bf16, 16 elements per thread: eight code bytes in, two 16-byte stores (`out` 16-byte, `codes` 8-byte aligned), the matrices of one
+// input group (q, k, v; gate, up) in one launch.
 // Memory bound: 0.5 bytes in, 2 out per weight.
-__global__ __launch_bounds__(256) void nf4_dequantize_vec_kernel(const uint8_t* __restrict__ codes, const float* __restrict__ absmax, int64_t n16, bf16_t* __restrict__ out) {
+__global__ __launch_bounds__(256) void nf4_dequantize_vec_kernel(const Nf4Batch b) {
   __shared__ float lut[16];
   if (threadIdx.x < 16) lut[threadIdx.x] = kLevel[threadIdx.x];
   __syncthreads();
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n16) return;
+  const Nf4Piece& m = b.m[piece_of(b, blockIdx.x)];
+  const uint8_t* codes = m.codes; const float* absmax = m.absmax; bf16_t* out = (bf16_t*)m.out;
+  const int64_t i = (int64_t)((int)blockIdx.x - m.first) * 256 + threadIdx.x;
+  if (i >= (int64_t)m.rows * m.cols / 16) return;
   const uint2 c = *reinterpret_cast<const uint2*>(codes + i * 8);
   const float a = absmax[i >> 2];
   bf16x8 v, w;
@@ -65,14 +75,17 @@ __global__ __launch_bounds__(256) void nf4_dequantize_vec_kernel(const uint8_t* 
 // backward products, which contract over the rows.  A workgroup takes 64 rows x 256 columns (whole 128-byte lines of codes),
 // a wave 64 x 64 of them, a lane an 8 x 8 block: eight 4-byte code reads, eight 16-byte output rows; no dense copy in between.
 // Needs rows a multiple of 8, cols of 64 (a block of 64 codes lies in one row), ldo of 8, aligned bases.
-// The 11 matrices of two 1B layers that the backward needs: 203 us as a dense copy and its transpose, 96 us so.
-__global__ __launch_bounds__(256) void nf4_dequantize_transposed_kernel(const uint8_t* __restrict__ codes, const float* __restrict__ absmax,
-                                                                        int rows, int cols, bf16_t* __restrict__ out, int64_t ldo) {
+// The 11 matrices of two 1B layers that the backward needs: 203 us as a dense copy and its transpose, 96 us so, and those of one product
+// (gate over up, q over k over v: their outputs side by side) in one launch.
+__global__ __launch_bounds__(256) void nf4_dequantize_transposed_kernel(const Nf4Batch b, int64_t ldo) {
   __shared__ float lut[16];
   if (threadIdx.x < 16) lut[threadIdx.x] = kLevel[threadIdx.x];
   __syncthreads();
+  const Nf4Piece& m = b.m[piece_of(b, blockIdx.y)];
+  const uint8_t* codes = m.codes; const float* absmax = m.absmax; bf16_t* out = (bf16_t*)m.out;
+  const int rows = m.rows, cols = m.cols;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int c = blockIdx.x * 256 + wave * 64 + (lane & 7) * 8, r = blockIdx.y * 64 + (lane >> 3) * 8;
+  const int c = blockIdx.x * 256 + wave * 64 + (lane & 7) * 8, r = ((int)blockIdx.y - m.first) * 64 + (lane >> 3) * 8;
   if (c >= cols || r >= rows) return;
   uint32_t code[8]; float a[8];
 #pragma unroll
@@ -107,8 +120,29 @@ int launch_nf4_dequantize(as_ctx* ctx, int mode, const uint8_t* codes, const flo
   if ((uintptr_t)codes % 4) return as_fail(ctx, AS_ERR_SHAPE, "nf4: the code array must be 4-byte aligned");
   const int64_t n8 = numel / 8;
   if (mode == AS_FP32) nf4_dequantize_kernel<float><<<(unsigned)cdiv(n8, 256), 256, 0, st>>>(codes, absmax, n8, (float*)out);
-  else if ((uintptr_t)out % 16 == 0 && (uintptr_t)codes % 8 == 0) nf4_dequantize_vec_kernel<<<(unsigned)cdiv(n8 / 2, 256), 256, 0, st>>>(codes, absmax, n8 / 2, (bf16_t*)out);
-  else nf4_dequantize_kernel<bf16_t><<<(unsigned)cdiv(n8, 256), 256, 0, st>>>(codes, absmax, n8, (bf16_t*)out);
+  else if (numel / 64 <= INT32_MAX && (uintptr_t)out % 16 == 0 && (uintptr_t)codes % 8 == 0) {
+    Nf4Batch b{}; b.n = 1; b.m[0] = {codes, absmax, out, (int)(numel / 64), 64, 0};
+    return launch_nf4_dequantize_batch(ctx, mode, b, st);
+  } else nf4_dequantize_kernel<bf16_t><<<(unsigned)cdiv(n8, 256), 256, 0, st>>>(codes, absmax, n8, (bf16_t*)out);
+  AS_LAUNCH_CHECK(ctx);
+  return AS_OK;
+}
+
+int launch_nf4_dequantize_batch(as_ctx* ctx, int mode, Nf4Batch b, hipStream_t st) {
+  bool vec = mode == AS_BF16;
+  for (int k = 0; k < b.n; k++) vec = vec && b.m[k].cols % 64 == 0 && !((uintptr_t)b.m[k].out % 16) && !((uintptr_t)b.m[k].codes % 8);
+  if (!vec) {
+    for (int k = 0; k < b.n; k++) {
+      const int rc = launch_nf4_dequantize(ctx, mode, b.m[k].codes, b.m[k].absmax, (int64_t)b.m[k].rows * b.m[k].cols, b.m[k].out, st);
+      if (rc) return rc;
+    }
+    return AS_OK;
+  }
+  int64_t blocks = 0;
+  for (int k = 0; k < b.n; k++) { b.m[k].first = (int)blocks; blocks += cdiv((int64_t)b.m[k].rows * b.m[k].cols, 16 * 256); }
+  if (blocks <= 0) return AS_OK;
+  if (blocks > INT32_MAX) return as_fail(ctx, AS_ERR_SHAPE, "nf4: too many elements for one launch");
+  nf4_dequantize_vec_kernel<<<(unsigned)blocks, 256, 0, st>>>(b);
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }
@@ -116,9 +150,11 @@ int launch_nf4_dequantize(as_ctx* ctx, int mode, const uint8_t* codes, const flo
 bool nf4_transposed_ok(int mode, const uint8_t* codes, int rows, int cols, const void* out, int64_t ldo) {
   return mode == AS_BF16 && rows % 8 == 0 && cols % 64 == 0 && ldo % 8 == 0 && (uintptr_t)out % 16 == 0 && (uintptr_t)codes % 4 == 0;
 }
-int launch_nf4_dequantize_transposed(as_ctx* ctx, const uint8_t* codes, const float* absmax, int rows, int cols, void* out, int64_t ldo, hipStream_t st) {
-  if (rows <= 0 || cols <= 0) return AS_OK;
-  nf4_dequantize_transposed_kernel<<<dim3((unsigned)cdiv(cols, 256), (unsigned)cdiv(rows, 64)), 256, 0, st>>>(codes, absmax, rows, cols, (bf16_t*)out, ldo);
+int launch_nf4_dequantize_transposed(as_ctx* ctx, Nf4Batch b, int64_t ldo, hipStream_t st) {
+  int64_t blocks = 0;
+  for (int k = 0; k < b.n; k++) { b.m[k].first = (int)blocks; blocks += cdiv(b.m[k].rows, 64); }
+  if (blocks <= 0 || b.m[0].cols <= 0) return AS_OK;
+  nf4_dequantize_transposed_kernel<<<dim3((unsigned)cdiv(b.m[0].cols, 256), (unsigned)blocks), 256, 0, st>>>(b, ldo);
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }
