@@ -842,7 +842,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv3_mfma(AttnParams p, float sc
 // The tiles' loads are issued from assembly (tile64_to_lds): known to the compiler they cost a wait for all of them in front of the
 // first transposing read of a step (forward) or half step (dQ, dK / dV).  Without it, and with priority for the wave that has products
 // to issue: forward 2 to 5 % faster, backward 3 %.  32 query heads on 8 KV heads, this and the eight-wave kernels with token-major
-// copies: forward 172 and 200 us (8191 tokens, longest segment 4096), 257 and 309 (30000, 2500), 22 and 26 (1003, 700); backward 500
+// copies: forward 160 and 200 us (8191 tokens, longest segment 4096), 257 and 309 (30000, 2500), 22 and 26 (1003, 700); backward 500
 // and 694, 900 and 1217, 58 and 77 us.
 __device__ __forceinline__ int swz64(int row) { return ((row & 2) << 1) | ((row >> 1) & 2) | ((row >> 3) & 1); }
 constexpr int T64_E = 64 * 64;                            // elements of a tile
@@ -907,7 +907,8 @@ __device__ __forceinline__ void stage_barrier() {
   __syncthreads();
 }
 
-// Of the waves of a SIMD the one with products to issue goes first (backward, 8191 to 30000 tokens: 1.5 to 2 % faster; the forward is level).
+// Of the waves of a SIMD the one with products to issue goes first (backward, 8191 to 30000 tokens: 1.5 to 2 % faster; forward 169 -> 160 us
+// at 8191 tokens, level at 30000; no gain for the eight-wave forward of head_dim 128).
 __device__ __forceinline__ void matrix_phase(bool on) { if (on) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0); }
 
 template <int HPW>
@@ -952,6 +953,7 @@ __global__ __launch_bounds__(256, 4) void attn_fwd64_mfma(AttnParams p, float sl
     const bf16_t* sK = sm + b * 2 * T64_E; const bf16_t* sV = sK + T64_E;
     f32x16 s[2];
     if (mine) {
+      matrix_phase(true);
 #pragma unroll
       for (int kb = 0; kb < 2; kb++) {
         s[kb] = zero16();
@@ -959,6 +961,7 @@ __global__ __launch_bounds__(256, 4) void attn_fwd64_mfma(AttnParams p, float sl
         for (int ks = 0; ks < KS; ks++) s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row64(sK, kb, ks, l31, h, f), qf[ks], s[kb], 0, 0, 0);
       }
     }
+    matrix_phase(false);
     if (kt < kv_last) stage_v(kt + 1, b ^ 1);
     if (!mine) continue;
     if (!((k0 + 63 <= t_base) && (k0 >= ss_hi))) {          // the tile touches the diagonal or a segment start
@@ -998,10 +1001,12 @@ __global__ __launch_bounds__(256, 4) void attn_fwd64_mfma(AttnParams p, float sl
     }
     rs += __shfl_xor(rs, 32, 64);
     l += rs;
+    matrix_phase(true);
 #pragma unroll
     for (int x = 0; x < 4; x++)
 #pragma unroll
       for (int cb = 0; cb < CB; cb++) o[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col64(sV, cn, x, cb), pb[x], o[cb], 0, 0, 0);
+    matrix_phase(false);
   }
   if (tq >= n) return;
   const float inv = 1.f / l;
