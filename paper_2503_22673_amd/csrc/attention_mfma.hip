@@ -4,7 +4,8 @@
 // Orientation.  Scores are produced transposed, S^T = K Q^T, so that in the
 // accumulator layout of v_mfma_f32_32x32x16_bf16 a lane owns ONE query (its
 // column) and 16 keys (its registers): the running max / sum of the online
-// softmax are per-lane scalars plus one exchange between the two lane halves,
+// softmax are per-lane scalars, the maximum exchanged between the two lane
+// halves only where it is raised and the sum once at the end,
 // and the probabilities, rounded to bf16, are already laid out as the B
 // operand of the next product O^T = V^T P^T (contraction over the keys a lane
 // holds).  The same holds in the backward kernels for dS.  The operand that is
@@ -53,7 +54,12 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& a, int sl) {
 //  * the 1/sqrt(d) log2(e) factor is folded into the exponent's fused multiply-add;
 //  * the running maximum is only raised when a tile exceeds it by more than 2^8 (the accumulators are
 //    float, the probabilities stay below 256), so rescaling the output accumulators is rare and sits
-//    behind a wave-uniform branch.
+//    behind a wave-uniform branch.  The two lanes of a query hold the same reference, so each tests its own
+//    half of the keys; halves are exchanged only in that branch, and the two partial sums at the end.  The
+//    exchange through LDS on every tile sat in the serial chain between the products (24576 tokens, longest
+//    16384, 32 heads of 128: 2087 -> 2044 us; 8191, 4096: 263 -> 258; 32 heads of 64: 153.7 -> 149.8).
+//    Head_dim 128 is held by the card's power (1.7 GHz in this kernel): 16x16x32 products (level), half of the
+//    waves one phase behind the other half (level; 6 % slower on short segments) bring nothing.
 template <int ROWBYTES> __device__ __forceinline__ int swz_row(int row) { return ROWBYTES == 256 ? (row & 15) : ((row >> 1) & 7); }
 
 // [ROWS][COLS] bf16 tile -> LDS, 1 KB per wave instruction.  The per-lane part of the addresses (row inside the tile,
@@ -226,9 +232,10 @@ __global__ __launch_bounds__(512, 2) void attn_fwd2_mfma(AttnParams p, float sl2
       for (int kb = 0; kb < 2; kb++)
 #pragma unroll
         for (int e = 0; e < 16; e++) mx = fmaxf(mx, s[qb][kb][e]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * sl2;
-      const bool raise = mx > mref[qb] + 8.f;
-      if (__builtin_amdgcn_ballot_w64(raise) != 0) {
+      mx *= sl2;                                           // this lane's half of the keys; the other half's lane has the same reference
+      if (__builtin_amdgcn_ballot_w64(mx > mref[qb] + 8.f) != 0) {
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const bool raise = mx > mref[qb] + 8.f;
         const float m_new = raise ? mx : mref[qb];
         const float alpha = raise ? fast_exp2(mref[qb] - m_new) : 1.f;
         mref[qb] = m_new;
@@ -244,7 +251,6 @@ __global__ __launch_bounds__(512, 2) void attn_fwd2_mfma(AttnParams p, float sl2
       for (int kb = 0; kb < 2; kb++)
 #pragma unroll
         for (int e = 0; e < 16; e++) { float pv = fast_exp2(fmaf(s[qb][kb][e], sl2, neg_m)); s[qb][kb][e] = pv; rs += pv; }
-      rs += __shfl_xor(rs, 32, 64);
       l[qb] += rs;
 #pragma unroll
       for (int kb = 0; kb < 2; kb++) { pb[qb][kb * 2] = pack8(s[qb][kb], 0); pb[qb][kb * 2 + 1] = pack8(s[qb][kb], 1); }
@@ -266,6 +272,7 @@ __global__ __launch_bounds__(512, 2) void attn_fwd2_mfma(AttnParams p, float sl2
   bf16_t* O = (bf16_t*)p.o;
 #pragma unroll
   for (int qb = 0; qb < QB; qb++) {
+    l[qb] += __shfl_xor(l[qb], 32, 64);                    // the halves of the keys
     if (tq[qb] >= n) continue;
     float inv = 1.f / l[qb];
     bf16_t* orow = O + ((int64_t)tq[qb] * p.Hq + j) * DH;
@@ -842,7 +849,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv3_mfma(AttnParams p, float sc
 // The tiles' loads are issued from assembly (tile64_to_lds): known to the compiler they cost a wait for all of them in front of the
 // first transposing read of a step (forward) or half step (dQ, dK / dV).  Without it, and with priority for the wave that has products
 // to issue: forward 2 to 5 % faster, backward 3 %.  32 query heads on 8 KV heads, this and the eight-wave kernels with token-major
-// copies: forward 160 and 200 us (8191 tokens, longest segment 4096), 257 and 309 (30000, 2500), 22 and 26 (1003, 700); backward 500
+// copies: forward 150 and 200 us (8191 tokens, longest segment 4096), 246 and 309 (30000, 2500), 22 and 26 (1003, 700); backward 500
 // and 694, 900 and 1217, 58 and 77 us.
 __device__ __forceinline__ int swz64(int row) { return ((row & 2) << 1) | ((row >> 1) & 2) | ((row >> 3) & 1); }
 constexpr int T64_E = 64 * 64;                            // elements of a tile
@@ -978,9 +985,10 @@ __global__ __launch_bounds__(256, 4) void attn_fwd64_mfma(AttnParams p, float sl
     for (int kb = 0; kb < 2; kb++)
 #pragma unroll
       for (int e = 0; e < 16; e++) mx = fmaxf(mx, s[kb][e]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * sl2;
-    const bool raise = mx > mref + 8.f;
-    if (__builtin_amdgcn_ballot_w64(raise) != 0) {
+    mx *= sl2;                                             // this lane's half of the keys; the other half's lane has the same reference
+    if (__builtin_amdgcn_ballot_w64(mx > mref + 8.f) != 0) {
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const bool raise = mx > mref + 8.f;
       const float m_new = raise ? mx : mref;
       const float alpha = raise ? fast_exp2(mref - m_new) : 1.f;
       mref = m_new;
@@ -999,7 +1007,6 @@ __global__ __launch_bounds__(256, 4) void attn_fwd64_mfma(AttnParams p, float sl
       for (int e = 0; e < 16; e++) { const float pv = fast_exp2(fmaf(s[kb][e], sl2, neg_m)); s[kb][e] = pv; rs += pv; }
       pb[kb * 2] = pack8(s[kb], 0); pb[kb * 2 + 1] = pack8(s[kb], 1);
     }
-    rs += __shfl_xor(rs, 32, 64);
     l += rs;
     matrix_phase(true);
 #pragma unroll
@@ -1008,6 +1015,7 @@ __global__ __launch_bounds__(256, 4) void attn_fwd64_mfma(AttnParams p, float sl
       for (int cb = 0; cb < CB; cb++) o[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col64(sV, cn, x, cb), pb[x], o[cb], 0, 0, 0);
     matrix_phase(false);
   }
+  l += __shfl_xor(l, 32, 64);                              // the halves of the keys
   if (tq >= n) return;
   const float inv = 1.f / l;
   bf16_t* orow = (bf16_t*)p.o + ((int64_t)tq * p.Hq + j) * DH;
