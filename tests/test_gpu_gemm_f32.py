@@ -32,3 +32,16 @@ def test_float_products(M, N, K1, K2, pad):
     # a float sum of K products in any order is off by at most K roundings of the sum of their magnitudes; alpha and R are two more
     assert ((out[:M, :N].double() - ref).abs() <= (K1 + K2 + 3) * 2.0 ** -24 * size).all()
     assert (out[M:] == 7.0).all() and (out[:, N:] == 7.0).all()
+
+
+@pytest.mark.parametrize("full", [False, True])
+@pytest.mark.parametrize("d,hq,hkv,ffn,vocab,rank", [(128, 4, 2, 328, 301, 5), (96, 3, 1, 200, 1003, 12)])
+def test_float_step_at_odd_widths(d, hq, hkv, ffn, vocab, rank, full):
+    """gate | up and q | k | v side by side, input gradients over the weights as they lie, adapter gradients 16 columns at a time, where no
+    width is a whole tile"""
+    import gpu_util as G
+    import synth
+    from helpers import random_trajs
+    sh = synth.CONFIGS[1].replace(n_layers=2, n_q_heads=hq, n_kv_heads=hkv, head_dim=32, d_model=d, ffn=ffn, vocab=vocab, lora_targets=synth.DENSE_TARGETS7, lora_rank=rank)
+    trajs = random_trajs(8, 7, sh.vocab, turn_lo=8, turn_hi=30, turns=(2, 5))
+    G.compare_step(sh, 8, trajs, 2, 253, bf16=False, loss_tol=1e-4, grad_tol=1e-4, full=full)

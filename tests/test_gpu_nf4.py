@@ -102,6 +102,34 @@ def test_lora_step_on_nf4_base(bf16):
             assert torch.equal(model.lora_grads[l][name][0], outs[1][2].lora_grads[l][name][0])
 
 
+@pytest.mark.parametrize("targets", [("q",), ("k", "up"), ("gate", "down"), ("q", "k", "v", "o", "gate", "up", "down")])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_lora_step_on_nf4_base_with_some_matrices_adapted(bf16, targets):
+    """q | k | v and gate | up are dequantised and multiplied as one group whatever part of it carries adapters; widths that are no
+    whole tiles"""
+    from paper_2503_22673_amd import binding as B
+    import gpu_util as G
+    sh = synth.CONFIGS[1].replace(n_layers=2, n_q_heads=6, n_kv_heads=2, head_dim=32, d_model=192, ffn=320, lora_targets=targets, lora_rank=8, lora_alpha=16.0)
+    dev, ref = _quantised_model(sh, 7, bf16)
+    lora = G.quantise_lora(synth.lora_weights(sh, 7))
+    trajs = random_trajs(7, 7, sh.vocab, turn_lo=8, turn_hi=30, turns=(2, 5))
+    rows, row_len = 2, 256
+    ctx = B.Context(B.make_config(sh, mode=B.AS_BF16 if bf16 else B.AS_FP32, recompute=0, weight_format=B.AS_W_NF4))
+    pk = ctx.pack(*synth.flatten_trajectories(trajs), row_len, rows)
+    model = B.DeviceModel(ctx, dev, lora)
+    ws = torch.empty(ctx.workspace_bytes(pk["n_rows"], row_len), dtype=torch.uint8, device="cuda")
+    out = ctx.train_step(model, pk["tokens"], pk["cu_seqlens"], pk["cu_seqlens"].cpu().numpy(), pk["loss_mask"], pk["n_rows"], row_len, ws, seg_skip=pk["seg_skip"])
+    torch.cuda.synchronize()
+    ref_pk = oracle.pack(trajs, row_len, rows)
+    f, g = oracle.train_step(oracle.config_from_shape(sh), ref, lora, ref_pk["tokens"], ref_pk["cu_seqlens"], ref_pk["loss_mask"])
+    loss_tol, grad_tol = (2e-3, 3e-2) if bf16 else (1e-4, 1e-4)                            # as for the full set of adapters above
+    assert int(out["count"].item()) == f["count"] and rel_err(float(out["loss"].item()), f["loss"]) <= loss_tol
+    for l in range(sh.n_layers):
+        for name, (dA, dB) in model.lora_grads[l].items():
+            assert grad_norm_err(G.to_np(dA), g["lora"][l][name][0]) <= grad_tol, (l, name)
+            assert grad_norm_err(G.to_np(dB), g["lora"][l][name][1]) <= grad_tol, (l, name)
+
+
 def test_nf4_config_checks():
     from paper_2503_22673_amd import binding as B
     sh = synth.CONFIGS[1]

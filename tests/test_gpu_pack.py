@@ -51,6 +51,24 @@ def test_benchmark_workloads_full_size(cfg_id, rows):
     assert ref["n_rows"] == rows
 
 
+@pytest.mark.parametrize("shift", [0, 1, 2])
+@pytest.mark.parametrize("T,rows", [(1, 5), (37, 9), (64, 8)])
+def test_outputs_at_any_address(T, rows, shift):
+    """The stream is stored in 16-byte pieces where both buffers allow it, else value by value; nothing outside it is touched"""
+    B, ctx = _ctx(50)
+    trajs = random_trajs(11, 60, 50, turn_lo=0, turn_hi=9)
+    ref = oracle.pack(trajs, T, rows, pad_id=49)
+    n = rows * T
+    tok = torch.full((n + 8,), -7, dtype=torch.int32, device="cuda"); msk = torch.full((n + 8,), 9, dtype=torch.uint8, device="cuda")
+    cu = torch.empty(len(trajs) + rows + 1, dtype=torch.int32, device="cuda")
+    got = ctx.pack(*synth.flatten_trajectories(trajs), T, rows, pad_id=49, outputs=(tok[shift:shift + n], cu, msk[shift:shift + n]))
+    torch.cuda.synchronize()
+    live = ref["n_rows"] * T
+    assert got["n_rows"] == ref["n_rows"]
+    assert np.array_equal(tok[shift:shift + live].cpu().numpy(), ref["tokens"]) and np.array_equal(msk[shift:shift + live].cpu().numpy(), ref["loss_mask"])
+    assert (tok[:shift] == -7).all() and (tok[shift + live:] == -7).all() and (msk[:shift] == 9).all() and (msk[shift + live:] == 9).all()
+
+
 # ------------------------------------------------- best fit decreasing (as_pack_policy)
 
 def _same_policy(B, ctx, trajs, T, rows, policy, pad_id=0, truncate=True):
