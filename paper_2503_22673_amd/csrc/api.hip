@@ -656,6 +656,7 @@ struct Step {
     g.nseg = 1; g.M = P.N; g.N = N; g.C = C; g.ldc = ldc; g.alpha = 1.f; g.splitk = 1;
     g.grp_off = eoff; g.grp_n = c.n_experts; g.grp_b_stride = b_stride; g.grp_rows = 2.0 * P.N;
     g.rows_cap = 2 * P.N;                                  // A and C are (token, slot) buffers: 2 N rows
+    g.tail_part = P.gemm_tail;
   }
   // every expert's product over its own rows: rows eoff[e] .. eoff[e+1] of A and C times the e-th of the stacked
   // matrices at B (b_stride elements apart); one launch where the kernel allows, else one per expert

@@ -4,7 +4,8 @@
 // inside the same accumulators instead of a second GEMM and an add.
 //
 // Kernels:
-//  * gemm_fma_kernel        -- any type, any shape; fp32 FMAs.  The fp32 tier runs on it.
+//  * gemm_f32_kernel        -- float operands on the matrix cores, 16x16 and 32x32 results per workgroup: the fp32 tier's small products.
+//  * gemm_fma_kernel        -- any type, any shape; fp32 FMAs: the fp32 tier's large products, bf16 rows that are not 16-byte aligned.
 //  * gemm_mfma_rd_kernel    -- bf16, hand-scheduled 256x256 tiles, persistent: the large products; also with B, or A and B, given by rows of K.
 //  * gemm_mfma_rs_kernel    -- the same tiles staged through registers and one workgroup per tile (variant 34 of as_op_gemm only: its sums are
 //    those of the direct-to-LDS kernel, in the same order).
@@ -928,7 +929,7 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmParams& p, f32x16
 // instruction by instruction (gen_gemm_rs_loop.py -> gemm_rs_loop.inc).  LDS layout and fragment order are those
 // of the direct-to-LDS kernel.  Covers N in whole 256-column tiles, at least 256 rows and K segments that are multiples of 64
 // (rs_ok); the launcher sends everything else to the other kernels.  The contraction of a tile may be shared by several
-// workgroups (tail_first, tail_parts; rows counted on the device: live_parts), each with its part of the K steps.
+// workgroups (tail_first, tail_parts), each with its part of the K steps.
 // LIVE = 0: plain rows in whole row tiles, or a ragged last one whose spare rows the operands have.
 // LIVE = 2: plain rows whose number is no multiple of 256; the last row tile is moved up to end with the last row and writes
 // only the rows that are its own.
@@ -946,11 +947,22 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmParams& p, f32x16
 #include "gemm_rs_nn_loop.inc"
 #include "gemm_rs_tn_loop.inc"
 enum { RS_NT = 0, RS_NN = 1, RS_TN = 2 };
-// Rows counted on the device, with scratch for partial sums: the contraction of every tile is split over as many workgroups as
-// fit one round, up to kLiveParts.  Host code cannot know the count, so both launches work the split out from it.
+// Rows counted on the device, with scratch for partial sums: when the last round of tiles is at most half full, the contraction of each
+// of its tiles is split over as many workgroups as fit the round, up to kLiveParts.  Host code cannot know the count, so both launches
+// work the split out from it.  Experts of 8x7B widths over 8192 tokens in their two slots each, 4.1 rounds of tiles: down 1652 -> 1410 us,
+// input gradients of gate and up 2736 -> 2377, and 15 each for the sum of the parts (they had unsplit last rounds).
 constexpr int kLiveParts = 16;
-__device__ __forceinline__ int live_parts(const GemmParams& p, int tiles) {
-  return p.tail_part && tiles > 0 && tiles <= 128 ? min(kLiveParts, 256 / tiles) : 1;
+struct LiveSplit { int first, parts; };                  // tiles from `first` on, in that many parts
+__device__ __forceinline__ LiveSplit live_split(const GemmParams& p, int tiles) {
+  const int rest = tiles % 256;
+  if (!p.tail_part || rest == 0 || rest > 128) return {tiles, 1};
+  return {tiles - rest, min(kLiveParts, 256 / rest)};
+}
+// row tiles that the groups' rows fill, one group after the other
+__device__ __forceinline__ int group_row_tiles(const GemmParams& p) {
+  int total = 0;
+  for (int e = 0; e < p.grp_n; e++) total += (p.grp_off[e + 1] - p.grp_off[e] + 255) / 256;
+  return total;
 }
 // the matrix that a result row lies in, minus the rows above it (float results, whole tiles per group)
 __device__ __forceinline__ void* row_group_base(const GemmParams& p, int row) {
@@ -977,10 +989,6 @@ __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_o
   }
   int nblk = tiles_m * tiles_n, pid = blockIdx.x;
   int kpart = -1, parts = p.tail_parts;                  // >= 0: this workgroup computes one part of the contraction of a split tile
-  if (LIVE == 1 && p.tail_part) {
-    parts = live_parts(p, nblk);
-    if (parts > 1) { kpart = pid % parts; pid /= parts; }
-  }
   if (LIVE != 1 && p.tail_first >= 0 && pid >= p.tail_first) {
     const int i = pid - p.tail_first;
     kpart = i % parts; pid = p.tail_first + i / parts;
@@ -1318,11 +1326,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_rd_kernel(GemmParams p, int m_o
   extern __shared__ __align__(16) unsigned char smem[];
   int rb_all = 0, mlive_all = p.M;
   if (LIVE == 1) {
-    if (p.grp_n > 0) {                                   // the live row tiles of all groups, one group after the other
-      int total = 0;
-      for (int e = 0; e < p.grp_n; e++) total += (p.grp_off[e + 1] - p.grp_off[e] + BM - 1) / BM;
-      tiles_m = min(tiles_m, total);
-    } else {
+    if (p.grp_n > 0) tiles_m = min(tiles_m, group_row_tiles(p));
+    else {
       int mmax;
       mlive_all = gemm_rows(p, m_off, rb_all, mmax);
       tiles_m = min(tiles_m, (max(mlive_all, 0) + BM - 1) / BM);
@@ -1330,7 +1335,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_rd_kernel(GemmParams p, int m_o
   }
   const int nblk = tiles_m * tiles_n;
   int parts = p.tail_parts, first_split = nblk;            // tiles from first_split on are split into parts
-  if (LIVE == 1 && EPI == GEMM_EPI_NONE && p.tail_part) { parts = live_parts(p, nblk); if (parts > 1) first_split = 0; }
+  if (LIVE == 1 && EPI == GEMM_EPI_NONE) { const LiveSplit v = live_split(p, nblk); first_split = v.first; parts = v.parts; }
   if (LIVE != 1 && EPI == GEMM_EPI_NONE && p.tail_first >= 0) first_split = p.tail_first;
   const int items = first_split + (nblk - first_split) * parts;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1513,13 +1518,15 @@ static int launch_dlds_cfg(as_ctx* ctx, const GemmParams& p, int m_off, hipStrea
 __global__ __launch_bounds__(256) void gemm_tail_fixup_kernel(GemmParams p, int m_off, int tiles_m, int tiles_n) {
   constexpr int BM = 256, BN = 256, GROUP = 4, WPT = 16;
   const int tile = blockIdx.x / WPT, r_first = (blockIdx.x % WPT) * (BM / WPT);
-  int live = p.M, parts = p.tail_parts, first = p.tail_first;
-  if (p.m_dev) {
-    int rb, mmax;
-    live = gemm_rows(p, m_off, rb, mmax);
-    tiles_m = min(tiles_m, (max(live, 0) + BM - 1) / BM);
-    parts = live_parts(p, tiles_m * tiles_n); first = 0;
-    if (parts <= 1) return;
+  int live = p.M, parts = p.tail_parts, first = p.tail_first, rb = 0;
+  const bool counted = p.m_dev || p.grp_n > 0;
+  if (counted) {
+    int mmax;
+    if (p.grp_n > 0) tiles_m = min(tiles_m, group_row_tiles(p));
+    else { live = gemm_rows(p, m_off, rb, mmax); tiles_m = min(tiles_m, (max(live, 0) + BM - 1) / BM); }
+    const LiveSplit v = live_split(p, tiles_m * tiles_n);
+    if (v.parts <= 1) return;
+    first = v.first; parts = v.parts;
   }
   const int nblk = tiles_m * tiles_n, pid = first + tile;
   if (pid >= nblk) return;
@@ -1527,12 +1534,22 @@ __global__ __launch_bounds__(256) void gemm_tail_fixup_kernel(GemmParams p, int 
   const int logical = xcd * q8 + min(xcd, rem) + loc;
   const int in_group = GROUP * tiles_n, grp = logical / in_group, first_m = grp * GROUP;
   const int gsize = min(tiles_m - first_m, GROUP);
-  const int tile_m = first_m + (logical % in_group) % gsize, tile_n = (logical % in_group) / gsize;
+  int tile_m = first_m + (logical % in_group) % gsize;
+  const int tile_n = (logical % in_group) / gsize;
+  if (p.grp_n > 0) {                                     // the tile's group and which of its tiles it is
+    int e = 0;
+    live = p.grp_off[1] - p.grp_off[0];
+    while (tile_m >= (live + BM - 1) / BM && e + 1 < p.grp_n) {
+      tile_m -= (live + BM - 1) / BM; e++;
+      live = p.grp_off[e + 1] - p.grp_off[e];
+    }
+    rb = p.grp_off[e];
+  }
   const float* h0 = p.tail_part + (int64_t)tile * parts * (BM * BN);
   const int c = (threadIdx.x & 63) * 4;
   // as the main kernel: a ragged last tile was moved up; it writes its own rows (and rows past M where the operands have them)
-  const bool spare = !p.m_dev && p.rows_cap >= tiles_m * BM;
-  const int row0 = spare ? tile_m * BM : min(tile_m * BM, p.M - BM), row_hi = spare ? tiles_m * BM : live;
+  const bool spare = !counted && p.rows_cap >= tiles_m * BM;
+  const int row_lo = rb + tile_m * BM, row0 = spare ? row_lo : min(row_lo, (p.grp_off ? p.rows_cap : p.M) - BM), row_hi = spare ? tiles_m * BM : rb + live;
   constexpr int RPT = BM / WPT / 4;                      // rows of a thread, four apart
   f32x4 sum[RPT];
   const float* h = h0 + (r_first + (threadIdx.x >> 6)) * BN + c;
@@ -1546,7 +1563,7 @@ __global__ __launch_bounds__(256) void gemm_tail_fixup_kernel(GemmParams p, int 
 #pragma unroll
   for (int i = 0; i < RPT; i++) {
     const int64_t row = (int64_t)row0 + r_first + (threadIdx.x >> 6) + 4 * i; const int col = tile_n * BN + c;
-    if (row >= (int64_t)tile_m * BM && row < row_hi) {
+    if (row >= row_lo && row < row_hi) {
       f32x4 v = sum[i];
 #pragma unroll
       for (int k = 0; k < 4; k++) v[k] *= p.alpha;
@@ -1598,7 +1615,7 @@ static bool rs_tail_splits(const GemmParams& p, int T) {
 }
 // rows counted on the device whose contraction is long enough (sixteen parts of eight steps) to be split by the live count
 static bool live_split_ok(const GemmParams& p) {
-  return p.m_dev && !p.grp_off && p.tail_part && p.nseg == 1 && p.epi == GEMM_EPI_NONE && k_steps(p) >= 8 * kLiveParts;
+  return (p.grp_off ? p.grp_n > 0 : p.m_dev != nullptr) && p.tail_part && p.nseg == 1 && p.epi == GEMM_EPI_NONE && k_steps(p) >= 8 * kLiveParts;
 }
 // what the ring kernels need: plain rows, whole K steps, rows of C and R in 16-byte pieces, 32-bit offsets inside a tile
 static bool ring_ok(const GemmParams& p) {
@@ -1638,7 +1655,7 @@ static int launch_256(as_ctx* ctx, const GemmParams& p_in, int m_off, int parts,
     const int tm = p.grp_n > 0 ? (int)cdiv(p.rows_cap, 256) + p.grp_n : (int)cdiv(p.M, 256);
     if (p.epi == GEMM_EPI_STATS) return launch_tiles<true, 1, RS_NT, GEMM_EPI_STATS>(ctx, p, m_off, tm * tn, tm, tn, st);
     if (p.epi == GEMM_EPI_PROB) return launch_tiles<true, 1, RS_NT, GEMM_EPI_PROB>(ctx, p, m_off, tm * tn, tm, tn, st);
-    if (!live_split_ok(p)) p.tail_part = nullptr;
+    if (!DIRECT || !live_split_ok(p)) p.tail_part = nullptr;
     const int wgs = p.tail_part ? std::max(tm * tn, kCus) : tm * tn;
     rc = p.nn ? launch_tiles<DIRECT, 1, RS_NN>(ctx, p, m_off, wgs, tm, tn, st) : launch_tiles<DIRECT, 1, RS_NT>(ctx, p, m_off, wgs, tm, tn, st);
     if (!rc && p.tail_part) { gemm_tail_fixup_kernel<<<dim3(16 * std::min(tm * tn, 128)), 256, 0, st>>>(p, m_off, tm, tn); AS_LAUNCH_CHECK(ctx); }
@@ -1708,7 +1725,7 @@ static bool mfma_ok(const GemmParams& p) {
 
 // Tile configuration of the MFMA kernels.  Register-staged (any K that is a multiple of 8): 0 = 256x256 (8 waves,
 // 128x64 each), 1 = 256x64, 2 = 64x256, 3 = 128x128, 4 = 128x64.  20 = direct-to-LDS 256x256 with 8 waves (K in 64-wide steps);
-// 24 = the hand-scheduled register-staged 256x256 kernel with 4 waves; 25, 26 = ring of stages, 128x128 and 64x64 tiles.
+// 24 = the hand-scheduled persistent 256x256 kernel with 4 waves (variant 34: the register-staged one); 25, 26 = ring of stages, 128x128 and 64x64 tiles.
 struct GemmPick { int cfg, parts; };                     // parts: workgroups that share a tile's contraction
 
 // Plain rows in whole K steps: the kernel and the split that the measured step times say is fastest (us; every pair of
@@ -1759,7 +1776,7 @@ static GemmPick pick_cfg(const GemmParams& p) {
   if (ring_ok(p)) return pick_plain(p);
   // the head's gradient: few target rows against a contraction over the vocabulary (about 1900 rows x 2048 x 32000: 64 tiles,
   // 565 us unsplit, 231 in four parts; 250 rows: 497 us on 128x128 tiles, 75 in sixteen parts)
-  if (rs_ok(p) && live_split_ok(p)) return {24, 1};
+  if (rs_ok(p) && live_split_ok(p) && !p.grp_off) return {24, 1};
   // narrow outputs stream A once: 128 x 128 tiles measured 2-33 % ahead of 256 x 64 here (58,880 rows; N = 128: 121 against
   // 181 us, where two 64-wide column tiles read A twice); up to 64 columns a 128 x 64 tile loads half the B rows per step
   if (p.N <= 64 && p.M > 128) return {4, 1};

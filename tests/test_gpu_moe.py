@@ -116,3 +116,21 @@ def test_moe_expert_gradients_from_matrices_as_they_are(live, seed):
     params, lora = structured_router_params(sh, seed, live=live), synth.lora_weights(sh, seed)
     res, _, worst = _compare(sh, params, lora, trajs, 1, 8300, True, 0)
     print("wide moe worst grad err %.2e" % worst)
+
+
+@pytest.mark.parametrize("row_len", [300, 2000, 4096])
+def test_moe_expert_products_whose_last_round_is_split(row_len):
+    """A layer of 8x7B widths: down and the input gradients of gate and up contract over 14336 and 28672, and the tiles of their last,
+    at most half full round are shared out (under half a round of tiles in all; one round and some; two and some).  A tile summed wrongly
+    would be off by all of itself, which is a tenth of the result or more."""
+    import torch
+    import perf.cases as cases
+    case = dict(name="experts", kind="step", arch="8x7b", layers=1, rows=1, row_len=row_len, train="lora", recompute=0, fp32=False)
+    got = cases.run(cases.prepare(dict(case), 3))
+    torch.cuda.synchronize()
+    ref = cases.exact(dict(case), 3)
+    assert abs(float(got["loss"]) - float(ref["loss"])) <= 2e-3 * abs(float(ref["loss"]))
+    for t, g in ref["grads"][0].items():
+        for k in ("a", "b"):
+            err = ((got["grads"][0][t][k].double() - g[k]).norm() / g[k].norm()).item()
+            assert err <= 0.03, (t, k, err)                # the step's tolerance on its gradients
