@@ -118,10 +118,11 @@ def test_moe_expert_gradients_from_matrices_as_they_are(live, seed):
     print("wide moe worst grad err %.2e" % worst)
 
 
-@pytest.mark.parametrize("row_len", [300, 2000, 4096])
+@pytest.mark.parametrize("row_len", [300, 2000, 4096, 18000])
 def test_moe_expert_products_whose_last_round_is_split(row_len):
     """A layer of 8x7B widths: down and the input gradients of gate and up contract over 14336 and 28672, and the tiles of their last,
-    at most half full round are shared out (under half a round of tiles in all; one round and some; two and some).  A tile summed wrongly
+    at most half full round are shared out (under half a round of tiles in all; one round and some; two and some).  At 18000 tokens the head's
+    gradient has 304 tiles, 48 of them behind a full round, in five parts.  A tile summed wrongly
     would be off by all of itself, which is a tenth of the result or more."""
     import torch
     import perf.cases as cases
