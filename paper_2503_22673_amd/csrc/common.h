@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <atomic>
 #include "actionstudio.h"
+#include "gemm_items.h"
 
 typedef __bf16 bf16_t;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -67,55 +68,7 @@ __device__ __forceinline__ float wave_max(float v) {
 }
 
 // ---- GEMM (gemm.hip) ------------------------------------------------------
-// C[M,N] = alpha * sum_s A_s[M,K_s] B_s[N,K_s]^T (+ R), optional split over K.
-struct GemmSeg { const void* A; const void* B; int64_t lda, ldb; int K; };
-struct GemmParams {
-  GemmSeg seg[2]; int nseg;
-  int M, N;
-  const int* m_dev;        // if set, the row count is read from the device (<= M)
-  void* C; int64_t ldc; int c_f32;
-  float alpha;
-  const void* R; int64_t ldr;
-  int accumulate;          // C += result (float output only)
-  int splitk; float* partial;   // splitk > 1: partial [splitk, M, N] float, reduced afterwards
-  // grouped rows (mixture of experts): with grp_off set, the product covers rows
-  // [grp_off[grp], grp_off[grp+1]) of A, R and C (device-side table), at most M of them
-  const int* grp_off; int grp;
-  double grp_rows;            // expected live rows of the launch (timing records only)
-  // grp_n > 0: ALL groups 0 .. grp_n - 1 in one launch (grp is ignored); group e multiplies with the matrix that
-  // starts grp_b_stride elements after that of group e - 1 (B of segment 0; one segment only)
-  int grp_n; int64_t grp_b_stride;
-  // rows that every row operand (A of each segment, R, C) really has allocated, or 0: lets a kernel that works in
-  // whole 256-row tiles run over the ragged last tile too (rows past M are computed from whatever is there and
-  // written to rows past M of C; no row of the result depends on another row)
-  int rows_cap;
-  // Column groups: several weight matrices whose outputs sit side by side in C (q | k | v, gate | up) as ONE launch: fewer,
-  // larger grids (every launch ends on a partial round of tiles) and the shared row panel of A is read once per tile row.
-  // Group g covers columns [cg_end[g-1], cg_end[g]) (multiples of 256); its rows of B come from cg_B1[g] (segment 0) and
-  // cg_B2[g] (segment 1), both indexed from the group's first column, and segment 1 reads A at column offset cg_a2[g]
-  // (each projection has its own adapter activations).  ncg == 0: seg[].B as usual.
-  int ncg; int cg_end[3]; const void* cg_B1[3]; const void* cg_B2[3]; int cg_a2[3];
-  // Vocabulary head without stored logits (hand-scheduled kernel only; rows and row arrays are those of A):
-  //  epi == GEMM_EPI_STATS: nothing is written to C; for every row and every 128-column block of the result the maximum and
-  //    the sum of exp(value - maximum) go to epi_part[(row * (N / 128) + block) * 2 + {0, 1}];
-  //  epi == GEMM_EPI_PROB:  C = w_row * (exp(value - epi_lse[row]) - [column == epi_lab[row]]), w_row = epi_w[row] when
-  //    given, else 1 / *epi_cnt: the gradient of the masked loss with respect to the logits, straight from the accumulators.
-  // Split tiles (hand-scheduled kernel, plain rows): with tail_first >= 0 the tiles tail_first .. of the launch are each
-  // computed by tail_parts workgroups, one per part of the contraction, as float partials in tail_part
-  // [tile - tail_first][part][256 x 256]; a second small launch adds the parts in order and applies the epilogue.
-  // Set by the launcher, which finds room for kGemmTailFloats floats at tail_part.
-  int tail_first, tail_parts; float* tail_part;
-  // nn > 0: B of both segments is [K, N], rows of N elements with ONE row stride (seg[0].ldb == seg[1].ldb); segment 0's rows are those of
-  // nn <= 3 matrices below one another: seg[0].B, and from row nb_row[i] (bf16: a multiple of 64) on nb[i].  Not all kernels: ask
-  // gemm_nn_applies first.
-  int nn; const void* nb[2]; int nb_row[2];
-  // tn: A of the one segment is [K, M] and B [K, N] (hand-scheduled kernel only: gemm_tn_applies), float result.  Its rows may be those of
-  // several matrices: from row rg_row[i] (a multiple of 256) on they go to rg_C[i], all with row stride ldc.  k_dev: the
-  // contraction ends with row *k_dev - k_off (rows up to the next multiple of 64 must be zero in both operands).
-  int tn; const int* k_dev; int k_off; int nrg; void* rg_C[2]; int rg_row[2];
-  int epi; const float* epi_lse; const int32_t* epi_lab; const float* epi_w; const int32_t* epi_cnt; float* epi_part;
-};
-enum { GEMM_EPI_NONE = 0, GEMM_EPI_STATS = 1, GEMM_EPI_PROB = 2 };
+// GemmParams, what one product is, lies in gemm_items.h
 // the hand-scheduled kernel would take this product (whole 256 x 256 tiles, K in 64-wide steps, alignment)
 bool gemm_rs_applies(int mode, const GemmParams& p);
 // the launch (p.nn set) would go to the hand-scheduled kernel, which alone reads B as [K, N]

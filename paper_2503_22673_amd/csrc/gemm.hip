@@ -26,19 +26,6 @@ __device__ __forceinline__ KRange split_range(int K, int BK, int splitk, int z) 
   return r;
 }
 
-// Live row count of this launch and, for grouped rows, the first row of the group (rb): rows of A, R
-// and C are then rb + (0 .. M-1).  mmax is the largest row index a clamped load may touch.
-__device__ __forceinline__ int gemm_rows(const GemmParams& p, int m_off, int& rb, int& mmax) {
-  int M = p.m_dev ? min(p.M, *p.m_dev - m_off) : p.M;
-  rb = 0; mmax = p.M - 1;
-  if (p.grp_off) {
-    rb = p.grp_off[p.grp];
-    M = min(M, p.grp_off[p.grp + 1] - rb);
-    mmax = max(M, 1) - 1;
-  }
-  return M;
-}
-
 template <typename T>
 __device__ __forceinline__ void store_out(const GemmParams& p, int z, int row, int col, float v, int rb) {
   if (p.splitk > 1) { p.partial[((int64_t)z * p.M + row) * p.N + col] = v; return; }
@@ -946,34 +933,16 @@ __device__ __forceinline__ void gemm_epilogue_staged(const GemmParams& p, f32x16
 // one launch per matrix and the head's gradient contracted over whole chunks; 6.28 ms so, the head over its live rows.
 #include "gemm_rs_nn_loop.inc"
 #include "gemm_rs_tn_loop.inc"
-enum { RS_NT = 0, RS_NN = 1, RS_TN = 2 };
-// Rows counted on the device, with scratch for partial sums: when the last round of tiles is at most half full, the contraction of each
-// of its tiles is split over as many workgroups as fit the round, up to kLiveParts.  Host code cannot know the count, so both launches
-// work the split out from it.  Experts of 8x7B widths over 8192 tokens in their two slots each, 4.1 rounds of tiles: down 1652 -> 1410 us,
-// input gradients of gate and up 2736 -> 2377, and 15 each for the sum of the parts (they had unsplit last rounds).
-constexpr int kLiveParts = 16;
-struct LiveSplit { int first, parts; };                  // tiles from `first` on, in that many parts
-__device__ __forceinline__ LiveSplit live_split(const GemmParams& p, int tiles) {
-  const int rest = tiles % 256;
-  if (!p.tail_part || rest == 0 || rest > 128) return {tiles, 1};
-  return {tiles - rest, min(kLiveParts, 256 / rest)};
-}
-// row tiles that the groups' rows fill, one group after the other
-__device__ __forceinline__ int group_row_tiles(const GemmParams& p) {
-  int total = 0;
-  for (int e = 0; e < p.grp_n; e++) total += (p.grp_off[e + 1] - p.grp_off[e] + 255) / 256;
-  return total;
-}
 // the matrix that a result row lies in, minus the rows above it (float results, whole tiles per group)
 __device__ __forceinline__ void* row_group_base(const GemmParams& p, int row) {
   int g = 0;
   while (g < p.nrg && row >= p.rg_row[g]) g++;
   return g ? (float*)p.rg_C[g - 1] - (int64_t)p.rg_row[g - 1] * p.ldc : (float*)p.C;
 }
-template <int LIVE, int LAYOUT = RS_NT>
+template <int LIVE, int LAYOUT = RD_NT>
 __global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_off, int tiles_m, int tiles_n) {
   constexpr int BM = 256, BN = 256, BK = 64, TM = 4, TN = 4;
-  constexpr bool NN = LAYOUT != RS_NT, AK = LAYOUT == RS_TN;      // B is [K, N]; A is [K, M]
+  constexpr bool NN = LAYOUT != RD_NT, AK = LAYOUT == RD_TN;      // B is [K, N]; A is [K, M]
   extern __shared__ __align__(16) unsigned char smem[];
   int rb = 0, mlive = p.M;
   if (LIVE == 1) {
@@ -1308,108 +1277,20 @@ __device__ __forceinline__ void rd_stats(const GemmParams& p, const f32x16 (&t)[
   }
 }
 
-// A piece of work of the kernel below: one tile, or one part of a split tile's contraction.  Pointers are those of this wave.
-struct RdItem {
-  int row0, col0, row_lo, row_hi, pid, kpart, nt0, nt, n1, n2;
-  uint64_t a0, a1, b0, b1, b2, b3;                         // bases of both segments (NN: of the matrices below one another), for a step counted from this item's first
-  uint64_t bf; bool two;                                   // base of B in the first step; whether the second step has the same bases
-};
-
 // wave-uniform values the compiler does not know to be so, into scalar registers
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ __forceinline__ uint64_t uni(uint64_t x) { return (uint64_t)(uint32_t)uni((int)(x >> 32)) << 32 | (uint32_t)uni((int)x); }
 
-template <int LIVE, int EPI = GEMM_EPI_NONE, int LAYOUT = RS_NT>
+template <int LIVE, int EPI = GEMM_EPI_NONE, int LAYOUT = RD_NT>
 __global__ __launch_bounds__(256) void gemm_mfma_rd_kernel(GemmParams p, int m_off, int tiles_m, int tiles_n) {
-  constexpr int BM = 256, BN = 256, BK = 64;
-  constexpr bool NN = LAYOUT == RS_NN, AK = LAYOUT == RS_TN;      // B is [K, N]; A is [K, M] and B [K, N]
+  constexpr int BM = 256, BN = 256;
+  constexpr bool NN = LAYOUT == RD_NN, AK = LAYOUT == RD_TN;      // B is [K, N]; A is [K, M] and B [K, N]
   extern __shared__ __align__(16) unsigned char smem[];
-  int rb_all = 0, mlive_all = p.M;
-  if (LIVE == 1) {
-    if (p.grp_n > 0) tiles_m = min(tiles_m, group_row_tiles(p));
-    else {
-      int mmax;
-      mlive_all = gemm_rows(p, m_off, rb_all, mmax);
-      tiles_m = min(tiles_m, (max(mlive_all, 0) + BM - 1) / BM);
-    }
-  }
-  const int nblk = tiles_m * tiles_n;
-  int parts = p.tail_parts, first_split = nblk;            // tiles from first_split on are split into parts
-  if (LIVE == 1 && EPI == GEMM_EPI_NONE) { const LiveSplit v = live_split(p, nblk); first_split = v.first; parts = v.parts; }
-  if (LIVE != 1 && EPI == GEMM_EPI_NONE && p.tail_first >= 0) first_split = p.tail_first;
-  const int items = first_split + (nblk - first_split) * parts;
+  const RdLaunch g = rd_launch<LIVE, LAYOUT, EPI == GEMM_EPI_NONE>(p, m_off, tiles_m, tiles_n);
+  const int items = g.items, first_split = g.first_split, parts = g.parts;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
   const GemmSeg s0 = p.seg[0], s1 = p.nseg > 1 ? p.seg[1] : p.seg[0];
-  int nt0_all = p.seg[0].K / BK, nt_all = nt0_all + (p.nseg > 1 ? p.seg[1].K / BK : 0);
-  if (AK && p.k_dev) nt0_all = nt_all = min(nt_all, (max(*p.k_dev - p.k_off, 0) + BK - 1) / BK);
-
-  auto decode = [&](int item) {
-    RdItem w;
-    w.kpart = -1; w.pid = item;
-    if (item >= first_split) { const int i = item - first_split; w.kpart = i % parts; w.pid = first_split + i / parts; }
-    const int q8 = nblk / 8, rem = nblk % 8, xcd = w.pid % 8, loc = w.pid / 8;
-    const int logical = xcd * q8 + min(xcd, rem) + loc;
-    constexpr int GROUP = 4;                               // the 32 workgroups of an XCD cover 4 row tiles x 8 column tiles at a time, as above
-    const int in_group = GROUP * tiles_n, grp = logical / in_group, first_m = grp * GROUP;
-    const int gsize = min(tiles_m - first_m, GROUP);
-    int tile_m = first_m + (logical % in_group) % gsize;
-    const int tile_n = (logical % in_group) / gsize;
-    int b_group = 0, rb = rb_all, mlive = mlive_all;
-    if (LIVE == 1 && p.grp_n > 0) {                        // which group this row tile belongs to, and which of its tiles it is
-      int e = 0, rows_e = p.grp_off[1] - p.grp_off[0], nt_e = (rows_e + BM - 1) / BM;
-      while (tile_m >= nt_e && e + 1 < p.grp_n) {
-        tile_m -= nt_e; e++;
-        rows_e = p.grp_off[e + 1] - p.grp_off[e]; nt_e = (rows_e + BM - 1) / BM;
-      }
-      rb = p.grp_off[e]; mlive = rows_e; b_group = e;
-    }
-    w.row_lo = rb + tile_m * BM; w.row_hi = rb + mlive;
-    w.row0 = LIVE ? min(w.row_lo, (LIVE == 1 && p.grp_off ? p.rows_cap : p.M) - BM) : tile_m * BM;
-    w.col0 = tile_n * BN;
-    w.nt0 = nt0_all; w.nt = nt_all;
-    int64_t lo = 0;
-    if (w.kpart >= 0) {                                    // steps [lo, hi) of the contraction; the launcher made sure that every part starts inside segment 0
-      lo = (int64_t)nt_all * w.kpart / parts;
-      const int hi = (int)((int64_t)nt_all * (w.kpart + 1) / parts);
-      w.nt0 = min(nt0_all, hi) - (int)lo; w.nt = hi - (int)lo;
-    }
-    const int64_t k_skip = lo * BK;
-    const bf16_t* b0p = (const bf16_t*)s0.B + (int64_t)b_group * p.grp_b_stride; const bf16_t* b1p = (const bf16_t*)s1.B;
-    int colg = w.col0, a2off = 0;
-    if (p.ncg > 0) {                                       // which weight matrix this column tile belongs to
-      int g = 0;
-      while (g + 1 < p.ncg && w.col0 >= p.cg_end[g]) g++;
-      colg = w.col0 - (g ? p.cg_end[g - 1] : 0);
-      b0p = (const bf16_t*)p.cg_B1[g]; b1p = (const bf16_t*)(p.nseg > 1 ? p.cg_B2[g] : p.cg_B1[g]); a2off = p.nseg > 1 ? p.cg_a2[g] : 0;
-    }
-    w.n1 = w.n2 = w.nt0; w.b2 = w.b3 = 0; w.two = w.nt0 >= 2;
-    if (AK) {
-      w.a0 = w.a1 = (uint64_t)((const bf16_t*)s0.A + (k_skip + wave * 16) * s0.lda + w.row0);
-      w.b0 = w.b1 = (uint64_t)(b0p + (k_skip + wave * 16) * s0.ldb + w.col0);
-      w.bf = w.b0;
-      return w;
-    }
-    w.a0 = (uint64_t)((const bf16_t*)s0.A + (int64_t)(w.row0 + wave * 64) * s0.lda + k_skip);
-    w.a1 = (uint64_t)((const bf16_t*)s1.A + a2off + (int64_t)(w.row0 + wave * 64) * s1.lda - (int64_t)w.nt0 * BK);
-    if (NN) {
-      const int64_t ldb = s0.ldb, row_w = (int64_t)(wave * 16) * ldb + w.col0;
-      // base of a matrix minus its first row: step t of this item reads rows 64 t .. of it
-      auto base = [&](const void* m, int64_t first_row) {
-        return (uint64_t)m + (uint64_t)(2 * ((int64_t)b_group * p.grp_b_stride + row_w + (k_skip - first_row) * ldb));
-      };
-      w.b0 = base(s0.B, 0); w.b2 = base(p.nb[0], p.nb_row[0]); w.b3 = base(p.nb[1], p.nb_row[1]);
-      w.b1 = (uint64_t)s1.B + (uint64_t)(2 * (row_w - (int64_t)w.nt0 * BK * ldb));
-      if (p.nn > 1) w.n1 = (int)(p.nb_row[0] / BK - lo);
-      if (p.nn > 2) w.n2 = (int)(p.nb_row[1] / BK - lo);
-    } else {
-      w.b0 = (uint64_t)(b0p + (int64_t)(colg + wave * 64) * s0.ldb + k_skip);
-      w.b1 = (uint64_t)(b1p + (int64_t)(colg + wave * 64) * s1.ldb - (int64_t)w.nt0 * BK);
-    }
-    const int end = w.n1 > 0 ? w.n1 : w.n2 > 0 ? w.n2 : w.nt0;
-    w.bf = w.n1 > 0 ? w.b0 : w.n2 > 0 ? w.b2 : w.b3; w.two = w.two && end >= 2;
-    return w;
-  };
 
   if ((int)blockIdx.x >= items) return;
   // per-lane LDS read addresses, by slice or (transposing reads) by pair of column blocks, and global offsets of even and odd loads
@@ -1420,30 +1301,23 @@ __global__ __launch_bounds__(256) void gemm_mfma_rd_kernel(GemmParams p, int m_o
     for (int k = 0; k < 4; k++) {
       const unsigned c = (unsigned)(l15 * 128 + (((4 * (k & 1) + q) ^ (l15 >> 1)) * 16)), t = (unsigned)((8 * q + r) * 512 + ((k ^ r) * 64) + (lane & 3) * 8);
       ar[k] = AK ? t + (unsigned)(wm * 256) : c + (unsigned)(wm * 128 * 128);
-      br[k] = LAYOUT != RS_NT ? t + (unsigned)(wn * 256) : c + (unsigned)(wn * 128 * 128);
+      br[k] = LAYOUT != RD_NT ? t + (unsigned)(wn * 256) : c + (unsigned)(wn * 128 * 128);
     }
 #pragma unroll
     for (int o = 0; o < 2; o++) {
       const int ch = (lch ^ ((lrow >> 1) | (o * 4))) * 8, cu = ((l31 >> 2) ^ (2 * o + hh)) * 32 + (l31 & 3) * 8;
       oa0[o] = (unsigned)((AK ? hh * s0.lda + cu : lrow * s0.lda + ch) * 2); oa1[o] = (unsigned)((lrow * s1.lda + ch) * 2);
-      ob0[o] = (unsigned)((LAYOUT != RS_NT ? hh * s0.ldb + cu : lrow * s0.ldb + ch) * 2); ob1[o] = (unsigned)((lrow * s1.ldb + ch) * 2);
+      ob0[o] = (unsigned)((LAYOUT != RD_NT ? hh * s0.ldb + cu : lrow * s0.ldb + ch) * 2); ob1[o] = (unsigned)((lrow * s1.ldb + ch) * 2);
     }
   }
   // bytes between two loads: eight rows, or two rows of the contraction; bytes of a step of the contraction
-  const int sa0 = (int)((AK ? 4 : 16) * s0.lda), sa1 = (int)(16 * s1.lda), sb0 = (int)((LAYOUT != RS_NT ? 4 : 16) * s0.ldb), sb1 = (int)(16 * s1.ldb);
+  const int sa0 = (int)((AK ? 4 : 16) * s0.lda), sa1 = (int)(16 * s1.lda), sb0 = (int)((LAYOUT != RD_NT ? 4 : 16) * s0.ldb), sb1 = (int)(16 * s1.ldb);
   const int ka = (int)(128 * s0.lda), kb = (int)(128 * s0.ldb);
-  const int64_t step_a = AK ? ka : 2 * BK, step_b = LAYOUT != RS_NT ? kb : 2 * BK;
   int half = 0, fresh = 1;                                 // LDS half stage of the next item's first step; nothing of it under way
   for (int item = blockIdx.x; item < items; item += (int)gridDim.x) {
-    const RdItem w = decode(item);
-    bool chain = false;
-    uint64_t an = w.a0, bn = w.bf;                         // past this item's end the loads take its own first steps again (nobody reads them) ...
-    if (item + (int)gridDim.x < items) {
-      const RdItem nx = decode(item + (int)gridDim.x);
-      if (nx.two) { chain = true; an = nx.a0; bn = nx.bf; }  // ... or those of the next item
-    }
-    an -= (uint64_t)(w.nt * step_a); bn -= (uint64_t)(w.nt * step_b);
-    if (AK && w.nt == 0) {                                 // no live rows to contract (the same for every item): the result is zero
+    const RdItem w = rd_item<LIVE, LAYOUT>(p, g, item, wave);
+    const RdNext nx = rd_next<LIVE, LAYOUT>(p, g, w, item, (int)gridDim.x, wave);
+    if (AK && w.nt == 0) {                                 // no live rows to contract (in any item, or in this part): the sum is zero
       if (!p.accumulate || w.kpart >= 0) {
         float* c = w.kpart >= 0 ? p.tail_part + ((int64_t)(w.pid - first_split) * parts + w.kpart) * (BM * BN) : (float*)row_group_base(p, w.row0) + (int64_t)w.row0 * p.ldc + w.col0;
         const int64_t ld = w.kpart >= 0 ? BN : p.ldc;
@@ -1451,7 +1325,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_rd_kernel(GemmParams p, int m_o
       }
     } else {
       f32x16 acc[4][4];
-      const int lim = w.nt + (chain || w.two ? 1 : 0), off = half * 32768, lw = wave * 8192;
+      const int off = half * 32768, lw = wave * 8192;
 #define RD_LOOP(name) \
       asm volatile(GEMM_##name##_LOOP_ASM \
                    : "={a[0:15]}"(acc[0][0]), "={a[16:31]}"(acc[0][1]), "={a[32:47]}"(acc[0][2]), "={a[48:63]}"(acc[0][3]), \
@@ -1460,14 +1334,14 @@ __global__ __launch_bounds__(256) void gemm_mfma_rd_kernel(GemmParams p, int m_o
                      "={a[192:207]}"(acc[3][0]), "={a[208:223]}"(acc[3][1]), "={a[224:239]}"(acc[3][2]), "={a[240:255]}"(acc[3][3]) \
                    : "v"(ar[0]), "v"(ar[1]), "v"(ar[2]), "v"(ar[3]), "v"(br[0]), "v"(br[1]), "v"(br[2]), "v"(br[3]), \
                      "v"(oa0[0]), "v"(oa0[1]), "v"(ob0[0]), "v"(ob0[1]), "v"(oa1[0]), "v"(oa1[1]), "v"(ob1[0]), "v"(ob1[1]), \
-                     "s"(uni(w.a0)), "s"(uni(w.b0)), "s"(uni(w.a1)), "s"(uni(w.b1)), "s"(uni(an)), "s"(uni(bn)), "s"(sa0), "s"(sb0), "s"(sa1), "s"(sb1), \
-                     "s"(uni(w.nt0)), "s"(uni(w.nt)), "s"(uni(lim)), "s"(uni(off)), "s"(lw), "s"(uni(fresh)), "s"(uni(w.b2)), "s"(uni(w.b3)), "s"(uni(w.n1)), "s"(uni(w.n2)), "s"(kb), "s"(ka) \
+                     "s"(uni(w.a0)), "s"(uni(w.b0)), "s"(uni(w.a1)), "s"(uni(w.b1)), "s"(uni(nx.an)), "s"(uni(nx.bn)), "s"(sa0), "s"(sb0), "s"(sa1), "s"(sb1), \
+                     "s"(uni(w.nt0)), "s"(uni(w.nt)), "s"(uni(nx.lim)), "s"(uni(off)), "s"(lw), "s"(uni(fresh)), "s"(uni(w.b2)), "s"(uni(w.b3)), "s"(uni(w.n1)), "s"(uni(w.n2)), "s"(kb), "s"(ka) \
                    : GEMM_##name##_LOOP_CLOBBERS)
       if constexpr (AK) RD_LOOP(RD_TN);
       else if constexpr (NN) RD_LOOP(RD_NN);
       else RD_LOOP(RD);
 #undef RD_LOOP
-      half = (half + 2 * (w.nt % 5)) % 5; fresh = !chain;
+      half = (half + 2 * (w.nt % 5)) % 5; fresh = !nx.chain;
       unsigned char* my = smem + ((half + 4) % 5) * 32768 + wave * 8192;
       GemmParams q = p;
       RdOut o = {w.row0 + wm * 128, w.col0 + wn * 128, w.row_lo, w.row_hi};
@@ -1598,29 +1472,11 @@ static bool rs_ok(const GemmParams& p) {
 }
 
 static bool rs_live(const GemmParams& p) { return p.m_dev || p.grp_off; }
-constexpr int kCus = 256;
 static int fma_tile(const GemmParams& p) { return cdiv(p.N, 64) * cdiv(p.M, 64) * p.splitk >= kCus ? 64 : 32; }
 // float products: 16 x 16 results per workgroup, 32 x 32 (gemm_f32_kernel), or 4: 64 x 64 (gemm_fma_kernel)
 static int f32_tile(const GemmParams& p) {
   if (cdiv(p.N, 16) * cdiv(p.M, 16) * p.splitk <= 8 * kCus) return 1;
   return p.nn || cdiv(p.N, 64) * cdiv(p.M, 64) * p.splitk < 4 * kCus ? 2 : 4;
-}
-static int k_steps(const GemmParams& p) { return (int)(p.seg[0].K / 64) + (p.nseg > 1 ? (int)(p.seg[1].K / 64) : 0); }
-// The tiles of a last partial round are split when that round would leave at least half of the CUs idle, the launch
-// has full rounds before it and the contraction is long enough to be worth a second small launch: a launch of 3696 tiles
-// on 256 CUs then ends after 14.5 rounds instead of 15.
-static bool rs_tail_splits(const GemmParams& p, int T) {
-  const int rest = T % kCus, nt = k_steps(p);
-  return p.tail_part && p.epi == GEMM_EPI_NONE && T > kCus && rest > 0 && rest <= kCus / 2 && nt >= 32 && nt / 2 <= (int)(p.seg[0].K / 64);
-}
-// As many parts as fill the round, of at least eight steps each, the last one starting inside segment 0.  24,710 tokens on matrices of
-// 2048 x 8192 leave eight tiles behind three rounds: in two parts they took half a tile's time, in sixteen a sixteenth (step of two 1B
-// layers 16.64 -> 16.46 ms; 13,429 tokens on an 8B model, 80 tiles in three parts: 29.8 -> 29.6).
-static int tail_parts(const GemmParams& p, int rest) {
-  const int nt = k_steps(p), nt0 = (int)(p.seg[0].K / 64);
-  int parts = std::min({kLiveParts, kCus / rest, nt / 8});
-  while (parts > 2 && nt - (int)cdiv(nt, parts) >= nt0) parts--;
-  return std::max(parts, 2);
 }
 // rows counted on the device whose contraction is long enough (sixteen parts of eight steps) to be split by the live count
 static bool live_split_ok(const GemmParams& p) {
@@ -1662,11 +1518,11 @@ static int launch_256(as_ctx* ctx, const GemmParams& p_in, int m_off, int parts,
   if (p.epi != GEMM_EPI_NONE && !p.m_dev) return as_fail(ctx, AS_ERR_SHAPE, "gemm: the head epilogues run over a device-side row count");
   if (rs_live(p)) {                                      // every row tile the live rows can reach; the kernel drops the rest
     const int tm = p.grp_n > 0 ? (int)cdiv(p.rows_cap, 256) + p.grp_n : (int)cdiv(p.M, 256);
-    if (p.epi == GEMM_EPI_STATS) return launch_tiles<true, 1, RS_NT, GEMM_EPI_STATS>(ctx, p, m_off, tm * tn, tm, tn, st);
-    if (p.epi == GEMM_EPI_PROB) return launch_tiles<true, 1, RS_NT, GEMM_EPI_PROB>(ctx, p, m_off, tm * tn, tm, tn, st);
+    if (p.epi == GEMM_EPI_STATS) return launch_tiles<true, 1, RD_NT, GEMM_EPI_STATS>(ctx, p, m_off, tm * tn, tm, tn, st);
+    if (p.epi == GEMM_EPI_PROB) return launch_tiles<true, 1, RD_NT, GEMM_EPI_PROB>(ctx, p, m_off, tm * tn, tm, tn, st);
     if (!DIRECT || !live_split_ok(p)) p.tail_part = nullptr;
     const int wgs = p.tail_part ? std::max(tm * tn, kCus) : tm * tn;
-    rc = p.nn ? launch_tiles<DIRECT, 1, RS_NN>(ctx, p, m_off, wgs, tm, tn, st) : launch_tiles<DIRECT, 1, RS_NT>(ctx, p, m_off, wgs, tm, tn, st);
+    rc = p.nn ? launch_tiles<DIRECT, 1, RD_NN>(ctx, p, m_off, wgs, tm, tn, st) : launch_tiles<DIRECT, 1, RD_NT>(ctx, p, m_off, wgs, tm, tn, st);
     if (!rc && p.tail_part) { gemm_tail_fixup_kernel<<<dim3(16 * std::min(tm * tn, 128)), 256, 0, st>>>(p, m_off, tm, tn); AS_LAUNCH_CHECK(ctx); }
     return rc;
   }
@@ -1675,14 +1531,14 @@ static int launch_256(as_ctx* ctx, const GemmParams& p_in, int m_off, int parts,
   const bool whole = p.rows_cap >= tm * 256 || p.M % 256 == 0;
   if (p.M % 256 == 0) p.rows_cap = p.M;
   if (parts > 1) { p.tail_first = 0; p.tail_parts = parts; }
-  else if (rs_tail_splits(p, T)) { p.tail_first = T / kCus * kCus; p.tail_parts = tail_parts(p, T % kCus); }
+  else if (tail_splits(p, T)) { p.tail_first = T / kCus * kCus; p.tail_parts = tail_parts(p, T % kCus); }
   const int split = p.tail_first >= 0 ? T - p.tail_first : 0;
   const int wgs = T - split + split * p.tail_parts;
-  if (p.tn) rc = launch_tiles<DIRECT, 0, RS_TN>(ctx, p, 0, wgs, tm, tn, st);
-  else if (p.nn && whole) rc = launch_tiles<DIRECT, 0, RS_NN>(ctx, p, 0, wgs, tm, tn, st);
-  else if (p.nn) rc = launch_tiles<DIRECT, 2, RS_NN>(ctx, p, 0, wgs, tm, tn, st);
-  else if (whole) rc = launch_tiles<DIRECT, 0, RS_NT>(ctx, p, 0, wgs, tm, tn, st);
-  else rc = launch_tiles<DIRECT, 2, RS_NT>(ctx, p, 0, wgs, tm, tn, st);
+  if (p.tn) rc = launch_tiles<DIRECT, 0, RD_TN>(ctx, p, 0, wgs, tm, tn, st);
+  else if (p.nn && whole) rc = launch_tiles<DIRECT, 0, RD_NN>(ctx, p, 0, wgs, tm, tn, st);
+  else if (p.nn) rc = launch_tiles<DIRECT, 2, RD_NN>(ctx, p, 0, wgs, tm, tn, st);
+  else if (whole) rc = launch_tiles<DIRECT, 0, RD_NT>(ctx, p, 0, wgs, tm, tn, st);
+  else rc = launch_tiles<DIRECT, 2, RD_NT>(ctx, p, 0, wgs, tm, tn, st);
   if (!rc && split) { gemm_tail_fixup_kernel<<<dim3(16 * split), 256, 0, st>>>(p, 0, tm, tn); AS_LAUNCH_CHECK(ctx); }
   return rc;
 }

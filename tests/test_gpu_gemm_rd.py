@@ -9,10 +9,12 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("out_f32,with_residual", [(False, False), (False, True), (True, True)])
 @pytest.mark.parametrize("M,N,K1,K2,split", [(2817, 2816, 192, 0, False), (4353, 4096, 64, 0, False), (4353, 4096, 64, 64, False), (9001, 8192, 128, 0, False),
                                              (12289, 4352, 256, 128, False), (4353, 4096, 1024, 64, True),
-                                             (4300, 4096, 8192, 64, True), (4300, 4096, 2048, 128, True), (3900, 4352, 2240, 0, True)])
+                                             (4300, 4096, 8192, 64, True), (4300, 4096, 2048, 128, True), (3900, 4352, 2240, 0, True),
+                                             (4353, 4096, 1024, 1024, True), (4300, 4096, 1024, 1088, True), (4353, 4096, 1088, 1024, True)])
 def test_large_products(M, N, K1, K2, split, out_f32, with_residual):
     # more than half a round of tiles with whole 64-wide steps: always this kernel; split: not below 32 steps, then 16 tiles behind a full
-    # round, their contraction in 16, 4 and 4 parts
+    # round, their contraction in 16, 4 and 4 parts; segments of one length, or one step apart: in two, the second one beginning where
+    # segment 1 does, or with the last step before it
     from paper_2503_22673_amd import binding as B
     import perf.cases as cases
     ctx = B.Context(cases._config(dict(arch="1b", layers=1, train="lora")))
