@@ -172,7 +172,7 @@ enum { AS_K_GEMM_MFMA_256 = 0,   /* bf16 MFMA GEMM, 256x256 tile                
        AS_K_LORA_GRAD,           /* adapter-gradient kernel (contraction over tokens) */
        AS_K_GEMM_GROUPED,        /* expert GEMMs over grouped rows (flops: expected share) */
        AS_K_MOE,                 /* routing, grouping, gather and combine kernels */
-       AS_K_GEMM_RS,             /* 256x256 MFMA GEMMs of the hand-scheduled register-staged kernel (long contractions) */
+       AS_K_GEMM_RS,             /* 256x256 MFMA GEMMs of the persistent hand-scheduled kernel */
        AS_K_N_CLASSES };
 int as_profile(as_ctx* ctx, int enable);
 /* Restricts the brackets to one kernel class (kernel_class < 0: every class again): the events cost about 3 us of
@@ -333,7 +333,7 @@ int as_adamw_update(as_ctx* ctx, float* const* d_master, void* const* d_params_l
  * 2 = MFMA kernel (bf16 only; K1, K2, lda, ldb multiples of 8) with the tile
  * shape picked; 10..14 = register-staged tiles 256x256 / 256x64 / 64x256 /
  * 128x128 / 128x64; 30 = direct-to-LDS 256x256 tiles (K in 64-wide steps, else 10);
- * 34 = hand-scheduled 256x256 kernel where it applies (else 30).
+ * 34 = the persistent hand-scheduled 256x256 kernel, which 0 picks for large products, where it applies (else 30).
  * d_tail_scratch [device], may be NULL: AS_GEMM_TAIL_SCRATCH_BYTES of scratch, 256-byte aligned.  With it the
  * contraction may be split over several workgroups per tile (as as_train_step does inside its workspace): that of
  * every tile where there are too few tiles for the chip, that of the last tiles of a large product where they would

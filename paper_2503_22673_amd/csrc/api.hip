@@ -974,7 +974,7 @@ struct Step {
     GemmParams g; memset(&g, 0, sizeof g);
     g.seg[0] = {P.hf, W->head, P.d, P.d, P.d}; g.nseg = 1; g.M = std::min(P.Mc, (int)cdiv(P.N, 256) * 256); g.N = P.V; g.m_dev = P.count;
     g.C = P.P; g.ldc = P.V; g.splitk = 1;
-    if (!gemm_rs_applies(mode, g)) return as_fail(ctx, AS_ERR_SHAPE, "the head matrix must be 16-byte aligned");
+    if (!gemm_rd_applies(mode, g)) return as_fail(ctx, AS_ERR_SHAPE, "the head matrix must be 16-byte aligned");
     return launch_label_logit(ctx, P.hf, W->head, P.d, P.labels, P.count, P.N, P.zlab, st);
   }
   int head_losses(int r0, int rows) {                        // per-target losses of one chunk

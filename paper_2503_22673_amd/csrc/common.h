@@ -70,7 +70,7 @@ __device__ __forceinline__ float wave_max(float v) {
 // ---- GEMM (gemm.hip) ------------------------------------------------------
 // GemmParams, what one product is, lies in gemm_items.h
 // the hand-scheduled kernel would take this product (whole 256 x 256 tiles, K in 64-wide steps, alignment)
-bool gemm_rs_applies(int mode, const GemmParams& p);
+bool gemm_rd_applies(int mode, const GemmParams& p);
 // the launch (p.nn set) would go to the hand-scheduled kernel, which alone reads B as [K, N]
 bool gemm_nn_applies(int mode, int variant, const GemmParams& p);
 bool gemm_tn_applies(int mode, int variant, const GemmParams& p);

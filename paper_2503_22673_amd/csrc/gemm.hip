@@ -7,8 +7,6 @@
 //  * gemm_f32_kernel        -- float operands on the matrix cores, 16x16 and 32x32 results per workgroup: the fp32 tier's small products.
 //  * gemm_fma_kernel        -- any type, any shape; fp32 FMAs: the fp32 tier's large products, bf16 rows that are not 16-byte aligned.
 //  * gemm_mfma_rd_kernel    -- bf16, hand-scheduled 256x256 tiles, persistent: the large products; also with B, or A and B, given by rows of K.
-//  * gemm_mfma_rs_kernel    -- the same tiles staged through registers and one workgroup per tile (variant 34 of as_op_gemm only: its sums are
-//    those of the direct-to-LDS kernel, in the same order).
 //  * gemm_mfma_ring_kernel  -- bf16, 128x128 and 64x64 tiles in a ring of LDS stages: few rows or narrow outputs.
 //  * gemm_mfma_dlds_kernel, gemm_mfma_kernel -- bf16: K that is no multiple of 64, rows counted on the device that the
 //    hand-scheduled kernel does not take, rows that are not 16-byte aligned.
@@ -795,326 +793,33 @@ __global__ __launch_bounds__(256) void gemm_splitk_finish_kernel(GemmParams p) {
   }
 }
 
-// Epilogue for accumulator blocks that were computed transposed (B fragment as the first MFMA operand): a lane owns
-// row (lane % 32) of every 32 x 32 block and, per accumulator quad b4, the four consecutive columns
-// 8 b4 + 4 (lane / 32) .. + 3.  Whole tiles only, no split-K.  One row pointer per 32-row block and immediate column
-// offsets: nothing to keep in registers besides the accumulators (the element-wise epilogue above, unrolled over
-// 256 accumulators per lane, spills, and on this chip a spill reload waits for every store in flight).
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
-template <int TM, int TN, bool MASK = false>
-__device__ __forceinline__ void gemm_epilogue_rows(const GemmParams& p, f32x16 (&acc)[TM][TN], int row_lane, int col_lane,
-                                                   int row_lo = 0, int row_hi = 0) {
-  const float alpha = p.alpha;
-#pragma unroll
-  for (int i = 0; i < TM; i++) {
-    const int64_t r = row_lane + 32 * i;
-    if (MASK && (r < row_lo || r >= row_hi)) continue;   // with MASK only rows row_lo .. row_hi - 1 are written (and read)
-    if (p.c_f32) {
-      float* c = (float*)p.C + r * p.ldc + col_lane;
-      const bf16_t* rr = p.R ? (const bf16_t*)p.R + r * p.ldr + col_lane : nullptr;
-#pragma unroll
-      for (int j = 0; j < TN; j++)
-#pragma unroll
-        for (int b4 = 0; b4 < 4; b4++) {
-          f32x4 v;
-#pragma unroll
-          for (int k = 0; k < 4; k++) v[k] = alpha * acc[i][j][4 * b4 + k];
-          if (rr) { const bf16x4_t x = *reinterpret_cast<const bf16x4_t*>(rr + 32 * j + 8 * b4);
-#pragma unroll
-            for (int k = 0; k < 4; k++) v[k] += (float)x[k]; }
-          f32x4* q = reinterpret_cast<f32x4*>(c + 32 * j + 8 * b4);
-          if (p.accumulate) { const f32x4 o = *q;
-#pragma unroll
-            for (int k = 0; k < 4; k++) v[k] += o[k]; }
-          *q = v;
-        }
-    } else {
-      bf16_t* c = (bf16_t*)p.C + r * p.ldc + col_lane;
-      const bf16_t* rr = p.R ? (const bf16_t*)p.R + r * p.ldr + col_lane : nullptr;
-#pragma unroll
-      for (int j = 0; j < TN; j++)
-#pragma unroll
-        for (int b4 = 0; b4 < 4; b4++) {
-          f32x4 v;
-#pragma unroll
-          for (int k = 0; k < 4; k++) v[k] = alpha * acc[i][j][4 * b4 + k];
-          if (rr) { const bf16x4_t x = *reinterpret_cast<const bf16x4_t*>(rr + 32 * j + 8 * b4);
-#pragma unroll
-            for (int k = 0; k < 4; k++) v[k] += (float)x[k]; }
-          bf16x4_t w;
-#pragma unroll
-          for (int k = 0; k < 4; k++) w[k] = (bf16_t)v[k];
-          *reinterpret_cast<bf16x4_t*>(c + 32 * j + 8 * b4) = w;
-        }
-    }
-  }
-}
-
-// The same accumulator layout, bf16 output, through LDS: stored 8 bytes per lane as above, a store instruction touches
-// 32 rows with 16 bytes each, and the epilogue of a 256 x 256 tile costs 8-10 % of a tile with a contraction of 4096.
-// Here every wave writes its 128 x 128 block (with the residual added and rounded once, as above) into its own part of
-// the tile memory, which is free once every wave has left the loop, and reads it back 16 bytes per lane, so that a store
-// instruction writes four whole 256-byte row pieces.  Rows are 272 bytes apart in LDS.  The residual takes the same way
-// in: loaded 16 bytes per lane, parked at the place of the result, picked up by the lane that owns the element.
-template <int TM, int TN, bool MASK = false>
-__device__ __forceinline__ void gemm_epilogue_staged(const GemmParams& p, f32x16 (&acc)[TM][TN], unsigned char* smem, int wave, int lane,
-                                                     int row_w0, int col_w0, int row_lo = 0, int row_hi = 0) {
-  constexpr int LROW = 272, ROWS = TM * 32;
-  static_assert(TN * 32 == 128, "a block row is 256 bytes: 16 lanes of 16 bytes");
-  unsigned char* my = smem + wave * (ROWS * LROW);
-  const int l31 = lane & 31, hh = lane >> 5, r4 = lane >> 4, c16 = lane & 15;
-  const float alpha = p.alpha;
-  __syncthreads();                                       // the other waves have read their last fragments
-  if (p.R) {
-    const bf16_t* rr = (const bf16_t*)p.R + (int64_t)(row_w0 + r4) * p.ldr + col_w0 + c16 * 8;
-#pragma unroll 8
-    for (int it = 0; it < ROWS / 4; it++) {
-      const int r = row_w0 + 4 * it + r4;
-      if (!MASK || (r >= row_lo && r < row_hi))          // with MASK only rows row_lo .. row_hi - 1 are read and written
-        *reinterpret_cast<u32x4*>(my + (4 * it + r4) * LROW + c16 * 16) = *reinterpret_cast<const u32x4*>(rr + (int64_t)(4 * it) * p.ldr);
-    }
-    __builtin_amdgcn_s_waitcnt(0xc07f);                  // lgkmcnt(0): LDS operations of a wave complete in order; this is for the compiler's sake
-    asm volatile("" ::: "memory");
-  }
-#pragma unroll
-  for (int i = 0; i < TM; i++) {
-#pragma unroll
-    for (int j = 0; j < TN; j++)
-#pragma unroll
-      for (int b4 = 0; b4 < 4; b4++) {
-        bf16x4_t* q = reinterpret_cast<bf16x4_t*>(my + (32 * i + l31) * LROW + (32 * j + 8 * b4 + 4 * hh) * 2);
-        f32x4 v;
-#pragma unroll
-        for (int k = 0; k < 4; k++) v[k] = alpha * acc[i][j][4 * b4 + k];
-        if (p.R) { const bf16x4_t x = *q;
-#pragma unroll
-          for (int k = 0; k < 4; k++) v[k] += (float)x[k]; }
-        bf16x4_t w;
-#pragma unroll
-        for (int k = 0; k < 4; k++) w[k] = (bf16_t)v[k];
-        *q = w;
-      }
-  }
-  __builtin_amdgcn_s_waitcnt(0xc07f);
-  asm volatile("" ::: "memory");
-  bf16_t* c = (bf16_t*)p.C + (int64_t)(row_w0 + r4) * p.ldc + col_w0 + c16 * 8;
-#pragma unroll 8
-  for (int it = 0; it < ROWS / 4; it++) {
-    const int r = row_w0 + 4 * it + r4;
-    if (!MASK || (r >= row_lo && r < row_hi))
-      *reinterpret_cast<u32x4*>(c + (int64_t)(4 * it) * p.ldc) = *reinterpret_cast<const u32x4*>(my + (4 * it + r4) * LROW + c16 * 16);
-  }
-}
-
-// Register-staged pipeline with a hand-scheduled loop, four waves of 128 x 128 (one per SIMD: the 256 accumulator
-// registers of a wave live in the accumulation half of the register file, the vector half holds two register
-// stages of tile data and two fragment sets).  In the kernels above a tile's loads are issued one K step before
-// the tile is needed, because LDS holds two stages and the landing stage is the only place a direct-to-LDS load
-// can go; a load that misses the L2 comes back later than that, and the workgroup waits for it at the barrier.
-// Here a tile travels global -> registers -> LDS and its loads are issued 1.75 K steps before its LDS store.
-// With one wave per SIMD every wait in the instruction stream idles the matrix pipe, so the loop is written out
-// instruction by instruction (gen_gemm_rs_loop.py -> gemm_rs_loop.inc).  LDS layout and fragment order are those
-// of the direct-to-LDS kernel.  Covers N in whole 256-column tiles, at least 256 rows and K segments that are multiples of 64
-// (rs_ok); the launcher sends everything else to the other kernels.  The contraction of a tile may be shared by several
-// workgroups (tail_first, tail_parts), each with its part of the K steps.
-// LIVE = 0: plain rows in whole row tiles, or a ragged last one whose spare rows the operands have.
-// LIVE = 2: plain rows whose number is no multiple of 256; the last row tile is moved up to end with the last row and writes
-// only the rows that are its own.
-// LIVE = 1: the row count is a device-side value and / or the rows are those of one group (expert).  Tiles past the live
-// rows exit; a tile still computes 256 rows, moved up if need be so that they lie inside the `limit` rows the operands
-// are known to have (M for a plain row count, rows_cap for grouped rows), and writes the rows that are its own and live.
-// LAYOUT 1, NN: B is taken as [K, N] rows (gemm_rs_nn_loop.inc), the layout of a weight matrix in the product with its output
-// gradient: the matrix does not have to be transposed first.  The loop is the same but for half-width, transposing reads of B, and so
-// is its rate: steps of 16384 tokens on a dense 8B model and of 8192 tokens on a sparse 8x7B one lost 700 us of 33.1 ms and 1150 us
-// of 15.0 ms, the time of the copies, and nothing else changed.
-#include "gemm_rs_loop.inc"
-// LAYOUT 2, TN: A as [K, M] too (gemm_rs_tn_loop.inc): the gradient of a weight matrix, tokens contracted, from the output gradient and
-// the input as they are.  Full step of one 1B layer at 16384 tokens, 4350 of them targets: 8.00 ms with token-major copies (600 us),
-// one launch per matrix and the head's gradient contracted over whole chunks; 6.28 ms so, the head over its live rows.
-#include "gemm_rs_nn_loop.inc"
-#include "gemm_rs_tn_loop.inc"
 // the matrix that a result row lies in, minus the rows above it (float results, whole tiles per group)
 __device__ __forceinline__ void* row_group_base(const GemmParams& p, int row) {
   int g = 0;
   while (g < p.nrg && row >= p.rg_row[g]) g++;
   return g ? (float*)p.rg_C[g - 1] - (int64_t)p.rg_row[g - 1] * p.ldc : (float*)p.C;
 }
-template <int LIVE, int LAYOUT = RD_NT>
-__global__ __launch_bounds__(256) void gemm_mfma_rs_kernel(GemmParams p, int m_off, int tiles_m, int tiles_n) {
-  constexpr int BM = 256, BN = 256, BK = 64, TM = 4, TN = 4;
-  constexpr bool NN = LAYOUT != RD_NT, AK = LAYOUT == RD_TN;      // B is [K, N]; A is [K, M]
-  extern __shared__ __align__(16) unsigned char smem[];
-  int rb = 0, mlive = p.M;
-  if (LIVE == 1) {
-    if (p.grp_n > 0) {                                   // the live row tiles of all groups, one group after the other
-      int total = 0;
-      for (int e = 0; e < p.grp_n; e++) total += (p.grp_off[e + 1] - p.grp_off[e] + BM - 1) / BM;
-      tiles_m = min(tiles_m, total);
-    } else {
-      int mmax;
-      mlive = gemm_rows(p, m_off, rb, mmax);
-      tiles_m = min(tiles_m, (max(mlive, 0) + BM - 1) / BM);
-    }
-  }
-  int nblk = tiles_m * tiles_n, pid = blockIdx.x;
-  int kpart = -1, parts = p.tail_parts;                  // >= 0: this workgroup computes one part of the contraction of a split tile
-  if (LIVE != 1 && p.tail_first >= 0 && pid >= p.tail_first) {
-    const int i = pid - p.tail_first;
-    kpart = i % parts; pid = p.tail_first + i / parts;
-  }
-  if (pid >= nblk) return;
-  int q8 = nblk / 8, rem = nblk % 8, xcd = pid % 8, loc = pid / 8;
-  int logical = xcd * q8 + min(xcd, rem) + loc;
-  // the 32 workgroups an XCD runs at a time cover 4 row tiles x 8 column tiles: the row panels (activations, read from
-  // HBM the first time) are the expensive L2 misses, the column panels (weights, hot in the memory-side cache because
-  // every XCD reads them) the cheap ones; measured against 8 x 4: +2..6 %, against 16 x 2: +14 %
-  constexpr int GROUP = 4;
-  int in_group = GROUP * tiles_n, grp = logical / in_group, first_m = grp * GROUP;
-  int gsize = min(tiles_m - first_m, GROUP);
-  int tile_m = first_m + (logical % in_group) % gsize, tile_n = (logical % in_group) / gsize;
-  int b_group = 0;
-  if (LIVE == 1 && p.grp_n > 0) {                        // which group this row tile belongs to, and which of its tiles it is
-    int e = 0, rows_e = p.grp_off[1] - p.grp_off[0], nt_e = (rows_e + BM - 1) / BM;
-    while (tile_m >= nt_e && e + 1 < p.grp_n) {
-      tile_m -= nt_e; e++;
-      rows_e = p.grp_off[e + 1] - p.grp_off[e]; nt_e = (rows_e + BM - 1) / BM;
-    }
-    rb = p.grp_off[e]; mlive = rows_e; b_group = e;
-  }
-  const int row_lo = rb + tile_m * BM, row_hi = rb + mlive;                  // LIVE: the rows this tile writes
-  const int row0 = LIVE ? min(row_lo, (LIVE == 1 && p.grp_off ? p.rows_cap : p.M) - BM) : tile_m * BM, col0 = tile_n * BN;
-
-  const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, hh = lane >> 5, lrow = lane >> 3, lch = lane & 7;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
-  int nt0 = p.seg[0].K / BK, nt = nt0 + (p.nseg > 1 ? p.seg[1].K / BK : 0);
-  const GemmSeg s0 = p.seg[0], s1 = p.nseg > 1 ? p.seg[1] : p.seg[0];
-  if (AK && p.k_dev) nt0 = nt = min(nt, (max(*p.k_dev - p.k_off, 0) + BK - 1) / BK);
-  if (AK && nt == 0 && p.accumulate && kpart < 0) return;
-  int64_t k_skip = 0;                                    // elements of segment 0 this workgroup starts behind
-  if (kpart >= 0) {                                      // steps [lo, hi) of the contraction; the launcher made sure that every part starts inside segment 0
-    const int lo = (int)((int64_t)nt * kpart / parts), hi = (int)((int64_t)nt * (kpart + 1) / parts);
-    k_skip = (int64_t)lo * BK; nt0 = min(nt0, hi) - lo; nt = hi - lo;
-  }
-
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; i++)
-#pragma unroll
-    for (int j = 0; j < TN; j++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
-
-  if (nt > 0) {
-    // per-lane addresses of the loop, handed over through this lane's 64-byte line of LDS scratch
-    const int x7 = (l31 >> 1) & 7;
-    u32x4 line[4];
-#pragma unroll
-    for (int ks = 0; ks < 4; ks++) {
-      const unsigned c = (unsigned)(((2 * ks + hh) ^ x7) * 16);
-      line[0][ks] = (unsigned)((wm * 128 + l31) * 128) + c;                    // fragment reads of A
-      line[1][ks] = 65536u + (unsigned)((wn * 128 + l31) * 128) + c;           // ... of B
-      // NN: by column block ks; this lane's 8 bytes of the 4 x 16 patch, 64-byte unit u of row r at u ^ (r & 3)
-      const unsigned tr = (unsigned)((8 * hh + ((lane >> 2) & 3)) * 512 + ((ks ^ ((lane >> 2) & 3)) * 64) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8);
-      if (NN) line[1][ks] = 65536u + tr + (unsigned)(wn * 256);
-      if (AK) line[0][ks] = tr + (unsigned)(wm * 256);
-    }
-    const unsigned wrow = (unsigned)((wave * 64 + lrow) * 128);
-    line[2][0] = wrow + (unsigned)((lch ^ (lrow >> 1)) * 16);                  // LDS stores, even / odd load
-    line[2][1] = wrow + (unsigned)((lch ^ ((lrow >> 1) | 4)) * 16);
-    line[2][2] = line[2][0] + 65536u; line[2][3] = line[2][1] + 65536u;
-    if (NN) {                                            // rows 2 i, 2 i + 1 of the wave's sixteen, half a wave each
-      const unsigned r = (unsigned)(wave * 16 + hh) * 512u + 65536u, in = (unsigned)((l31 & 3) * 16), u = (unsigned)(l31 >> 2);
-      line[2][2] = r + ((u ^ (unsigned)hh) * 64u) + in; line[2][3] = r + ((u ^ (unsigned)(hh + 2)) * 64u) + in;
-      if (AK) { line[2][0] = line[2][2] - 65536u; line[2][1] = line[2][3] - 65536u; }
-    }
-    line[3][0] = (unsigned)((lrow * s0.lda + lch * 8) * 2); line[3][1] = (unsigned)((lrow * s0.ldb + lch * 8) * 2);
-    line[3][2] = (unsigned)((lrow * s1.lda + lch * 8) * 2); line[3][3] = (unsigned)((lrow * s1.ldb + lch * 8) * 2);
-    if (AK) line[3][0] = line[3][2] = (unsigned)((hh * s0.lda + l31 * 8) * 2);
-    if (NN) line[3][1] = line[3][3] = (unsigned)((hh * s0.ldb + l31 * 8) * 2);
-    u32x4* scratch = reinterpret_cast<u32x4*>(smem + 131072 + tid * 64);
-#pragma unroll
-    for (int i = 0; i < 4; i++) scratch[i] = line[i];
-    const unsigned scratch_addr = 131072u + (unsigned)tid * 64u;
-    // wave-uniform operand bases: first of the wave's 64 rows of the tile, first K step
-    const bf16_t* b0p = (const bf16_t*)s0.B + (int64_t)b_group * p.grp_b_stride; const bf16_t* b1p = (const bf16_t*)s1.B;
-    int colg = col0, a2off = 0;
-    if (p.ncg > 0) {                                     // which weight matrix this column tile belongs to
-      int cgi = 0;
-      while (cgi + 1 < p.ncg && col0 >= p.cg_end[cgi]) cgi++;
-      colg = col0 - (cgi ? p.cg_end[cgi - 1] : 0);
-      b0p = (const bf16_t*)p.cg_B1[cgi]; b1p = (const bf16_t*)(p.nseg > 1 ? p.cg_B2[cgi] : p.cg_B1[cgi]); a2off = p.nseg > 1 ? p.cg_a2[cgi] : 0;
-    }
-    const uint64_t A0 = (uint64_t)((const bf16_t*)s0.A + (int64_t)(row0 + wave * 64) * s0.lda + k_skip);
-    const uint64_t B0 = (uint64_t)(b0p + (int64_t)(colg + wave * 64) * s0.ldb + k_skip);
-    const uint64_t A1 = (uint64_t)((const bf16_t*)s1.A + a2off + (int64_t)(row0 + wave * 64) * s1.lda);
-    const uint64_t B1 = (uint64_t)(b1p + (int64_t)(colg + wave * 64) * s1.ldb);
-    const int sA0 = (int)(16 * s0.lda), sB0 = (int)(16 * s0.ldb), sA1 = (int)(16 * s1.lda), sB1 = (int)(16 * s1.ldb);   // 8 rows, bytes
-    if constexpr (AK) {
-      const uint64_t At = (uint64_t)((const bf16_t*)s0.A + (k_skip + wave * 16) * s0.lda + row0), Bt = (uint64_t)(b0p + (k_skip + wave * 16) * s0.ldb + col0);
-      const int sA = (int)(4 * s0.lda), sB = (int)(4 * s0.ldb), kA = (int)(128 * s0.lda), kB = (int)(128 * s0.ldb);   // two rows, 64 rows, bytes
-      asm volatile(GEMM_RS_TN_LOOP_ASM
-                   : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[0][2]), "+a"(acc[0][3]),
-                     "+a"(acc[1][0]), "+a"(acc[1][1]), "+a"(acc[1][2]), "+a"(acc[1][3]),
-                     "+a"(acc[2][0]), "+a"(acc[2][1]), "+a"(acc[2][2]), "+a"(acc[2][3]),
-                     "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][2]), "+a"(acc[3][3])
-                   : "v"(scratch_addr), "s"(At), "s"(Bt), "s"(At), "s"(Bt), "s"(sA), "s"(sB), "s"(sA), "s"(sB), "s"(nt), "s"(nt), "s"(kA), "s"(kB)
-                   : GEMM_RS_TN_LOOP_CLOBBERS);
-    } else if constexpr (NN) {
-      const int64_t ldb = s0.ldb, row_w = (int64_t)(wave * 16) * ldb + col0, lo = k_skip / BK;
-      // base of a matrix minus its first row: step t of this workgroup reads rows 64 t .. of it
-      auto base = [&](const void* m, int64_t first_row) {
-        return (uint64_t)m + (uint64_t)(2 * ((int64_t)b_group * p.grp_b_stride + row_w + (k_skip - first_row) * ldb));
-      };
-      const int n1 = p.nn > 1 ? (int)(p.nb_row[0] / BK - lo) : nt0, n2 = p.nn > 2 ? (int)(p.nb_row[1] / BK - lo) : nt0;
-      const uint64_t P0 = base(s0.B, 0), P1 = base(p.nb[0], p.nb_row[0]), P2 = base(p.nb[1], p.nb_row[1]);
-      const uint64_t P3 = (uint64_t)s1.B + (uint64_t)(2 * (row_w - (int64_t)nt0 * BK * ldb));
-      const int sB = (int)(4 * ldb), sK = (int)(128 * ldb);   // two rows, 64 rows, bytes
-      asm volatile(GEMM_RS_NN_LOOP_ASM
-                   : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[0][2]), "+a"(acc[0][3]),
-                     "+a"(acc[1][0]), "+a"(acc[1][1]), "+a"(acc[1][2]), "+a"(acc[1][3]),
-                     "+a"(acc[2][0]), "+a"(acc[2][1]), "+a"(acc[2][2]), "+a"(acc[2][3]),
-                     "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][2]), "+a"(acc[3][3])
-                   : "v"(scratch_addr), "s"(A0), "s"(P0), "s"(A1), "s"(P3), "s"(sA0), "s"(sB), "s"(sA1), "s"(sB), "s"(nt0), "s"(nt),
-                     "s"(P1), "s"(P2), "s"(n1), "s"(n2), "s"(sK)
-                   : GEMM_RS_NN_LOOP_CLOBBERS);
-    } else
-    asm volatile(GEMM_RS_LOOP_ASM
-                 : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[0][2]), "+a"(acc[0][3]),
-                   "+a"(acc[1][0]), "+a"(acc[1][1]), "+a"(acc[1][2]), "+a"(acc[1][3]),
-                   "+a"(acc[2][0]), "+a"(acc[2][1]), "+a"(acc[2][2]), "+a"(acc[2][3]),
-                   "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][2]), "+a"(acc[3][3])
-                 : "v"(scratch_addr), "s"(A0), "s"(B0), "s"(A1), "s"(B1), "s"(sA0), "s"(sB0), "s"(sA1), "s"(sB1), "s"(nt0), "s"(nt)
-                 : GEMM_RS_LOOP_CLOBBERS);
-  }
-  // bf16 results with 16-byte rows leave through LDS (whole 256-byte row pieces per store), the rest row by row
-  if (kpart >= 0) {              // raw float sums of this part into the tile's scratch
-    GemmParams q = p;
-    q.C = p.tail_part + ((int64_t)(pid - (LIVE == 1 ? 0 : p.tail_first)) * parts + kpart) * (BM * BN); q.ldc = BN; q.c_f32 = 1; q.alpha = 1.f; q.R = nullptr; q.accumulate = 0;
-    gemm_epilogue_rows<TM, TN, false>(q, acc, wm * TM * 32 + l31, wn * TN * 32 + 4 * hh);
-    return;
-  }
-  if constexpr (AK) {
-    GemmParams q = p; q.C = row_group_base(p, row0);
-    gemm_epilogue_rows<TM, TN, false>(q, acc, row0 + wm * TM * 32 + l31, col0 + wn * TN * 32 + 4 * hh);
-    return;
-  }
-  const bool staged = !p.c_f32 && !(p.ldc % 8) && (!p.R || (!(p.ldr % 8) && !((uintptr_t)p.R % 16)));
-  if (staged) gemm_epilogue_staged<TM, TN, LIVE != 0>(p, acc, smem, wave, lane, row0 + wm * TM * 32, col0 + wn * TN * 32, row_lo, row_hi);
-  else gemm_epilogue_rows<TM, TN, LIVE != 0>(p, acc, row0 + wm * TM * 32 + l31, col0 + wn * TN * 32 + 4 * hh, row_lo, row_hi);
-}
-
 // ------------------------------------------------------------- persistent 256 x 256 tiles
-// The large products.  Same tiles, layouts (NT, NN, TN), live rows, groups and split tiles as the kernel above; what differs:
+// The large products: N in whole 256-column tiles, at least 256 rows, K segments that are multiples of 64 (rd_ok); the launcher sends
+// everything else to the other kernels.  Four waves of 128 x 128, one per SIMD, whose 256 accumulators live in the accumulation half of
+// the register file.  With one wave per SIMD every wait in the instruction stream idles the matrix pipe, so the loop over a tile's
+// contraction is written out instruction by instruction (gen_gemm_rd_loop.py).  What it is built on, each against a kernel with 32x32x16
+// products, tiles staged through registers and one workgroup per tile:
 // * Under the chip's power limit the clock follows the energy of an operation, and a 16x16x32 product costs less of it than a 32x32x16
-//   one (register-resident loops on random operands: 2025 against 1788 TFLOP/s).  A slot of 16 clocks has no room for LDS stores (the
-//   kernel above with 16x16x32 products: 2510 clocks a step instead of 2170 and 2 % in all), so tiles go straight to LDS, through a
-//   ring of five 32 KB half stages that keeps the loads one to 1.7 steps ahead (gen_gemm_rd_loop.py): 2190 clocks a step of 2048 of
-//   matrix work, at 1.65 to 1.75 GHz where the kernel above holds 1.5 to 1.57.
+//   one (register-resident loops on random operands: 2025 against 1788 TFLOP/s).  A slot of 16 clocks has no room for LDS stores
+//   (staged through registers with 16x16x32 products: 2510 clocks a step instead of 2170 and 2 % in all), so tiles go straight to LDS,
+//   through a ring of five 32 KB half stages that keeps the loads one to 1.7 steps ahead: 2190 clocks a step of 2048 of matrix work, at
+//   1.65 to 1.75 GHz where the staged kernel held 1.5 to 1.57.
 // * The workgroups are persistent, one per CU: the first two steps of the next tile are on their way while the last ones of a tile are
-//   multiplied and while its result is written.  A tile costs its steps, an epilogue of 7,400 clocks and 2,100 between tiles; the kernel
-//   above loses 21,000 (epilogue 10,500, first loads, launch).  The epilogue takes 64 accumulators at a time: with all 256 in the
+//   multiplied and while its result is written.  A tile costs its steps, an epilogue of 7,400 clocks and 2,100 between tiles; the staged
+//   kernel lost 21,000 (epilogue 10,500, first loads, launch).  The epilogue takes 64 accumulators at a time: with all 256 in the
 //   compiler's hands it spilled a hundred registers.
+// * LAYOUT NN: B as [K, N] rows, the layout of a weight matrix in the product with its output gradient: no transposed copy first (16384
+//   tokens on a dense 8B model spent 700 us of 33.1 ms in those copies, 8192 tokens on a sparse 8x7B one 1150 us of 15.0 ms; the
+//   products take as long either way).  TN: A as [K, M] too, the gradient of a weight matrix, tokens contracted, from the output gradient
+//   and the input as they are: a full step of one 1B layer at 16384 tokens, 4350 of them targets, 8.00 ms with token-major copies, 6.28 so.
+// * The contraction of a tile may be shared by several workgroups, as parts with float sums (gemm_items.h: which tiles, where parts begin).
 // TFLOP/s before and now, random operands, launches back to back: 16384 x 14336 x 4096 1333 and 1525, 16384 x 4096 x 14336 1365 and 1558,
 // 32768 x 8192 x 2048 1234 and 1407, 32768 x 2048 x 8192 1346 and 1535.
 #include "gemm_rd_loop.inc"
@@ -1459,7 +1164,7 @@ __global__ __launch_bounds__(256) void gemm_tail_fixup_kernel(GemmParams p, int 
 }
 
 // whole 256 x 256 tiles of a plain launch (host-side row count, no split-K, K segments in 64-wide steps, 16-byte rows)
-static bool rs_ok(const GemmParams& p) {
+static bool rd_ok(const GemmParams& p) {
   if (p.splitk > 1 || p.M < 256 || (p.N % 256)) return false;
   if (p.grp_off && p.rows_cap < 256) return false;       // grouped rows: the caller states how many rows the operands have
   if (p.grp_n > 0 && (p.nseg != 1 || p.m_dev)) return false;
@@ -1471,7 +1176,7 @@ static bool rs_ok(const GemmParams& p) {
   return nt >= 1;
 }
 
-static bool rs_live(const GemmParams& p) { return p.m_dev || p.grp_off; }
+static bool rd_live(const GemmParams& p) { return p.m_dev || p.grp_off; }
 static int fma_tile(const GemmParams& p) { return cdiv(p.N, 64) * cdiv(p.M, 64) * p.splitk >= kCus ? 64 : 32; }
 // float products: 16 x 16 results per workgroup, 32 x 32 (gemm_f32_kernel), or 4: 64 x 64 (gemm_fma_kernel)
 static int f32_tile(const GemmParams& p) {
@@ -1484,45 +1189,37 @@ static bool live_split_ok(const GemmParams& p) {
 }
 // what the ring kernels need: plain rows, whole K steps, rows of C and R in 16-byte pieces, 32-bit offsets inside a tile
 static bool ring_ok(const GemmParams& p) {
-  if (rs_live(p) || p.splitk > 1 || p.epi != GEMM_EPI_NONE || p.N % 8 || p.ldc % 8 || ((uintptr_t)p.C % 16)) return false;
+  if (rd_live(p) || p.splitk > 1 || p.epi != GEMM_EPI_NONE || p.N % 8 || p.ldc % 8 || ((uintptr_t)p.C % 16)) return false;
   if (p.R && (p.ldr % 8 || ((uintptr_t)p.R % 16))) return false;
   for (int s = 0; s < p.nseg; s++)
     if (p.seg[s].K % 64 || p.seg[s].K < 64 || p.seg[s].lda > (1 << 22) || p.seg[s].ldb > (1 << 22)) return false;
   return true;
 }
 static bool mfma_ok(const GemmParams& p);
-bool gemm_rs_applies(int mode, const GemmParams& p) { return mode == AS_BF16 && mfma_ok(p) && rs_ok(p); }
+bool gemm_rd_applies(int mode, const GemmParams& p) { return mode == AS_BF16 && mfma_ok(p) && rd_ok(p); }
 
-// parts > 1: the contraction of every tile is split over that many workgroups.  DIRECT: the persistent kernel, else the register-staged one
-// (no head epilogues).
-template <bool DIRECT, int LIVE, int LAYOUT, int EPI = GEMM_EPI_NONE>
+template <int LIVE, int LAYOUT, int EPI = GEMM_EPI_NONE>
 static int launch_tiles(as_ctx* ctx, const GemmParams& p, int m_off, int wgs, int tm, int tn, hipStream_t st) {
-  if constexpr (DIRECT) {
-    AS_SET_SMEM(ctx, (gemm_mfma_rd_kernel<LIVE, EPI, LAYOUT>), kRdSmem);
-    gemm_mfma_rd_kernel<LIVE, EPI, LAYOUT><<<dim3(std::min(wgs, kCus)), 256, kRdSmem, st>>>(p, m_off, tm, tn);
-  } else {
-    constexpr size_t smem = 131072 + 256 * 64;           // two stages of A and B tiles + a 64-byte line per lane (the staged epilogue: 4 x 128 rows of 272 bytes)
-    AS_SET_SMEM(ctx, (gemm_mfma_rs_kernel<LIVE, LAYOUT>), smem);
-    gemm_mfma_rs_kernel<LIVE, LAYOUT><<<dim3(wgs), 256, smem, st>>>(p, m_off, tm, tn);
-  }
+  AS_SET_SMEM(ctx, (gemm_mfma_rd_kernel<LIVE, EPI, LAYOUT>), kRdSmem);
+  gemm_mfma_rd_kernel<LIVE, EPI, LAYOUT><<<dim3(std::min(wgs, kCus)), 256, kRdSmem, st>>>(p, m_off, tm, tn);
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }
 
-template <bool DIRECT>
+// parts > 1: the contraction of every tile is split over that many workgroups.
 static int launch_256(as_ctx* ctx, const GemmParams& p_in, int m_off, int parts, hipStream_t st) {
   GemmParams p = p_in;
   const int tn = p.N / 256;
   int rc;
   p.tail_first = -1; p.tail_parts = 2;
   if (p.epi != GEMM_EPI_NONE && !p.m_dev) return as_fail(ctx, AS_ERR_SHAPE, "gemm: the head epilogues run over a device-side row count");
-  if (rs_live(p)) {                                      // every row tile the live rows can reach; the kernel drops the rest
+  if (rd_live(p)) {                                      // every row tile the live rows can reach; the kernel drops the rest
     const int tm = p.grp_n > 0 ? (int)cdiv(p.rows_cap, 256) + p.grp_n : (int)cdiv(p.M, 256);
-    if (p.epi == GEMM_EPI_STATS) return launch_tiles<true, 1, RD_NT, GEMM_EPI_STATS>(ctx, p, m_off, tm * tn, tm, tn, st);
-    if (p.epi == GEMM_EPI_PROB) return launch_tiles<true, 1, RD_NT, GEMM_EPI_PROB>(ctx, p, m_off, tm * tn, tm, tn, st);
-    if (!DIRECT || !live_split_ok(p)) p.tail_part = nullptr;
+    if (p.epi == GEMM_EPI_STATS) return launch_tiles<1, RD_NT, GEMM_EPI_STATS>(ctx, p, m_off, tm * tn, tm, tn, st);
+    if (p.epi == GEMM_EPI_PROB) return launch_tiles<1, RD_NT, GEMM_EPI_PROB>(ctx, p, m_off, tm * tn, tm, tn, st);
+    if (!live_split_ok(p)) p.tail_part = nullptr;
     const int wgs = p.tail_part ? std::max(tm * tn, kCus) : tm * tn;
-    rc = p.nn ? launch_tiles<DIRECT, 1, RD_NN>(ctx, p, m_off, wgs, tm, tn, st) : launch_tiles<DIRECT, 1, RD_NT>(ctx, p, m_off, wgs, tm, tn, st);
+    rc = p.nn ? launch_tiles<1, RD_NN>(ctx, p, m_off, wgs, tm, tn, st) : launch_tiles<1, RD_NT>(ctx, p, m_off, wgs, tm, tn, st);
     if (!rc && p.tail_part) { gemm_tail_fixup_kernel<<<dim3(16 * std::min(tm * tn, 128)), 256, 0, st>>>(p, m_off, tm, tn); AS_LAUNCH_CHECK(ctx); }
     return rc;
   }
@@ -1534,11 +1231,11 @@ static int launch_256(as_ctx* ctx, const GemmParams& p_in, int m_off, int parts,
   else if (tail_splits(p, T)) { p.tail_first = T / kCus * kCus; p.tail_parts = tail_parts(p, T % kCus); }
   const int split = p.tail_first >= 0 ? T - p.tail_first : 0;
   const int wgs = T - split + split * p.tail_parts;
-  if (p.tn) rc = launch_tiles<DIRECT, 0, RD_TN>(ctx, p, 0, wgs, tm, tn, st);
-  else if (p.nn && whole) rc = launch_tiles<DIRECT, 0, RD_NN>(ctx, p, 0, wgs, tm, tn, st);
-  else if (p.nn) rc = launch_tiles<DIRECT, 2, RD_NN>(ctx, p, 0, wgs, tm, tn, st);
-  else if (whole) rc = launch_tiles<DIRECT, 0, RD_NT>(ctx, p, 0, wgs, tm, tn, st);
-  else rc = launch_tiles<DIRECT, 2, RD_NT>(ctx, p, 0, wgs, tm, tn, st);
+  if (p.tn) rc = launch_tiles<0, RD_TN>(ctx, p, 0, wgs, tm, tn, st);
+  else if (p.nn && whole) rc = launch_tiles<0, RD_NN>(ctx, p, 0, wgs, tm, tn, st);
+  else if (p.nn) rc = launch_tiles<2, RD_NN>(ctx, p, 0, wgs, tm, tn, st);
+  else if (whole) rc = launch_tiles<0, RD_NT>(ctx, p, 0, wgs, tm, tn, st);
+  else rc = launch_tiles<2, RD_NT>(ctx, p, 0, wgs, tm, tn, st);
   if (!rc && split) { gemm_tail_fixup_kernel<<<dim3(16 * split), 256, 0, st>>>(p, 0, tm, tn); AS_LAUNCH_CHECK(ctx); }
   return rc;
 }
@@ -1590,7 +1287,7 @@ static bool mfma_ok(const GemmParams& p) {
 
 // Tile configuration of the MFMA kernels.  Register-staged (any K that is a multiple of 8): 0 = 256x256 (8 waves,
 // 128x64 each), 1 = 256x64, 2 = 64x256, 3 = 128x128, 4 = 128x64.  20 = direct-to-LDS 256x256 with 8 waves (K in 64-wide steps);
-// 24 = the hand-scheduled persistent 256x256 kernel with 4 waves (variant 34: the register-staged one); 25, 26 = ring of stages, 128x128 and 64x64 tiles.
+// 24 = the hand-scheduled persistent 256x256 kernel with 4 waves; 25, 26 = ring of stages, 128x128 and 64x64 tiles.
 struct GemmPick { int cfg, parts; };                     // parts: workgroups that share a tile's contraction
 
 // Plain rows in whole K steps: the kernel and the split that the measured step times say is fastest (us; every pair of
@@ -1613,7 +1310,7 @@ static GemmPick pick_plain(const GemmParams& p) {
   GemmPick best{24, 1}; double best_t = 1e30;
   auto offer = [&](int cfg, int parts, double t) { if (t < best_t) { best_t = t; best = {cfg, parts}; } };
   const int try_parts[] = {1, 2, 3, 4, 6, 8, 12};
-  const bool rs = rs_ok(p);
+  const bool rs = rd_ok(p);
   if (rs && cdiv(p.M, 256) * (p.N / 256) > kCus / 2) return best;
   for (int parts : try_parts) {
     if (parts > 1 && (!can_split || parts > steps / 2)) break;
@@ -1641,21 +1338,21 @@ static GemmPick pick_cfg(const GemmParams& p) {
   if (ring_ok(p)) return pick_plain(p);
   // the head's gradient: few target rows against a contraction over the vocabulary (about 1900 rows x 2048 x 32000: 64 tiles,
   // 565 us unsplit, 231 in four parts; 250 rows: 497 us on 128x128 tiles, 75 in sixteen parts)
-  if (rs_ok(p) && live_split_ok(p) && !p.grp_off) return {24, 1};
+  if (rd_ok(p) && live_split_ok(p) && !p.grp_off) return {24, 1};
   // narrow outputs stream A once: 128 x 128 tiles measured 2-33 % ahead of 256 x 64 here (58,880 rows; N = 128: 121 against
   // 181 us, where two 64-wide column tiles read A twice); up to 64 columns a 128 x 64 tile loads half the B rows per step
   if (p.N <= 64 && p.M > 128) return {4, 1};
   if (p.N <= 128 && p.M > 128) return {3, 1};
   if (p.M <= 128) return {2, 1};
   if ((int64_t)cdiv(p.M, 256) * cdiv(p.N, 256) * p.splitk < 128) return {3, 1};
-  // The hand-scheduled register-staged kernel is ahead on every large shape it covers (9-13 % on the shapes of an 8B model)
-  if (rs_ok(p)) return {24, 1};
+  // The hand-scheduled kernel is ahead on every large shape it covers (a fifth and more on the shapes of an 8B model)
+  if (rd_ok(p)) return {24, 1};
   return {20, 1};                                        // direct-to-LDS tiles when K allows, else staged (0)
 }
 
 bool gemm_nn_applies(int mode, int variant, const GemmParams& p) {
   if (mode == AS_FP32) return variant <= 1 && p.nn >= 1 && p.nn <= 3 && !p.ncg && (p.nseg < 2 || p.seg[1].ldb == p.seg[0].ldb);
-  if (mode != AS_BF16 || (variant != 0 && variant != 2 && variant != 34) || !mfma_ok(p) || !rs_ok(p)) return false;
+  if (mode != AS_BF16 || (variant != 0 && variant != 2 && variant != 34) || !mfma_ok(p) || !rd_ok(p)) return false;
   if (p.nn < 1 || p.nn > 3 || p.ncg || p.epi != GEMM_EPI_NONE || p.seg[0].ldb > (1 << 22) || (p.nseg > 1 && p.seg[1].ldb != p.seg[0].ldb)) return false;
   int row = 0;
   for (int i = 0; i + 1 < p.nn; i++) {
@@ -1668,7 +1365,7 @@ bool gemm_nn_applies(int mode, int variant, const GemmParams& p) {
 // Splits as pick_plain says.  Under half a chip of workgroups even then (small weight matrices), copies and a kernel of smaller tiles are as fast.
 bool gemm_tn_applies(int mode, int variant, const GemmParams& p) {
   if (mode != AS_BF16 || (variant != 0 && variant != 2 && variant != 34) || !p.tn || p.nseg != 1 || !p.c_f32 || p.R) return false;
-  if (!mfma_ok(p) || !rs_ok(p) || rs_live(p) || p.ncg || p.nn || p.M % 256 || p.seg[0].lda > (1 << 22) || p.seg[0].ldb > (1 << 22)) return false;
+  if (!mfma_ok(p) || !rd_ok(p) || rd_live(p) || p.ncg || p.nn || p.M % 256 || p.seg[0].lda > (1 << 22) || p.seg[0].ldb > (1 << 22)) return false;
   for (int i = 0; i < p.nrg; i++) if (p.rg_row[i] % 256 || ((uintptr_t)p.rg_C[i] % 16)) return false;
   return p.M / 256 * (p.N / 256) * pick_plain(p).parts >= kCus / 2;
 }
@@ -1687,14 +1384,14 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
   if (p.tn) {
     if (!gemm_tn_applies(mode, variant, p) || m_off) return as_fail(ctx, AS_ERR_SHAPE, "gemm: only the hand-scheduled kernel reads A as [K, M]");
     prof_begin(ctx, st, p.k_dev ? AS_K_GEMM_DEVROWS : AS_K_GEMM_RS, p.k_dev ? 0.0 : 2.0 * p.M * p.N * p.seg[0].K);
-    const int rc = variant == 34 ? launch_256<false>(ctx, p, 0, pick_plain(p).parts, st) : launch_256<true>(ctx, p, 0, pick_plain(p).parts, st);
+    const int rc = launch_256(ctx, p, 0, pick_plain(p).parts, st);
     prof_end(ctx, st);
     return rc;
   }
   if (p.grp_n > 0) {
     if (!p.grp_off || p.nseg != 1 || p.m_dev || m_off) return as_fail(ctx, AS_ERR_SHAPE, "gemm: all groups in one launch need a group table and one K segment");
     const int c0 = variant >= 10 ? variant - 10 : pick_cfg(p).cfg;
-    if (!(mode == AS_BF16 && variant != 1 && mfma_ok(p) && c0 == 24 && rs_ok(p))) {       // one launch per group
+    if (!(mode == AS_BF16 && variant != 1 && mfma_ok(p) && c0 == 24 && rd_ok(p))) {       // one launch per group
       const size_t esz = mode == AS_BF16 ? 2 : 4;
       for (int e = 0; e < p.grp_n; e++) {
         GemmParams q = p; q.grp_n = 0; q.grp = e; q.grp_rows = p.grp_rows / p.grp_n;
@@ -1707,7 +1404,7 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
     }
   }
   if (p.epi != GEMM_EPI_NONE) {
-    if (!gemm_rs_applies(mode, p) || variant == 1 || (variant >= 10 && variant != 34)) return as_fail(ctx, AS_ERR_SHAPE, "gemm: the head epilogues need the hand-scheduled kernel (bf16, N a multiple of 256, K in 64-wide steps)");
+    if (!gemm_rd_applies(mode, p) || variant == 1 || (variant >= 10 && variant != 34)) return as_fail(ctx, AS_ERR_SHAPE, "gemm: the head epilogues need the hand-scheduled kernel (bf16, N a multiple of 256, K in 64-wide steps)");
     if (p.epi == GEMM_EPI_STATS && !p.epi_part) return as_fail(ctx, AS_ERR_NULL, "gemm: statistics epilogue without a buffer");
     if (p.epi == GEMM_EPI_PROB && (!p.epi_lse || !p.epi_lab || (!p.epi_w && !p.epi_cnt) || p.c_f32 || p.R || (p.ldc % 8))) return as_fail(ctx, AS_ERR_SHAPE, "gemm: probability epilogue needs lse, labels, a row factor and bf16 output");
   }
@@ -1716,7 +1413,7 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
     // the hand-scheduled kernel and the ring kernels take all groups at once when every group is whole tiles wide
     const int c = variant >= 10 ? variant - 10 : mode == AS_BF16 && variant != 1 ? pick_cfg(p).cfg : -1;
     const int width = c == 24 ? 256 : c == 25 ? 128 : 64;
-    bool fused = mode == AS_BF16 && variant != 1 && mfma_ok(p) && ((c == 24 && rs_ok(p)) || c == 25 || c == 26);
+    bool fused = mode == AS_BF16 && variant != 1 && mfma_ok(p) && ((c == 24 && rd_ok(p)) || c == 25 || c == 26);
     for (int g = 0; g < p.ncg && fused; g++) fused = p.cg_end[g] % width == 0 && !((uintptr_t)p.cg_B1[g] % 16) && (p.nseg < 2 || !((uintptr_t)p.cg_B2[g] % 16));
     if (mode == AS_FP32) {
       const int t = f32_tile(p);                         // the small kernel takes groups that end inside a tile if A is the same for all
@@ -1747,7 +1444,7 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
   if (p.epi != GEMM_EPI_NONE) cfg = 24;                    // only the hand-scheduled kernel has those epilogues (checked above)
   if (cfg >= 20) for (int s = 0; s < p.nseg; s++) if (p.seg[s].K % 64) cfg = 0;     // direct-to-LDS tiles need whole 64-wide K steps
   const bool big = use_mfma && (cfg == 0 || cfg == 20 || cfg == 24);
-  const bool rs = use_mfma && cfg == 24 && rs_ok(p) && !rs_live(p) && !m_off;     // live-row launches keep their own timing classes
+  const bool rs = use_mfma && cfg == 24 && rd_ok(p) && !rd_live(p) && !m_off;     // live-row launches keep their own timing classes
   prof_begin(ctx, st, rs ? AS_K_GEMM_RS : p.grp_off ? AS_K_GEMM_GROUPED : p.m_dev ? AS_K_GEMM_DEVROWS : !use_mfma ? AS_K_GEMM_FMA : big ? AS_K_GEMM_MFMA_256 : AS_K_GEMM_MFMA_SKINNY,
              p.grp_off ? 2.0 * p.grp_rows * p.N * ksum : p.m_dev ? 0.0 : 2.0 * p.M * p.N * ksum);
   if (use_mfma) {
@@ -1758,8 +1455,8 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
       case 4: rc = launch_mfma_cfg<128, 64, 2, 2>(ctx, p, m_off, st); break;
       case 20: rc = launch_dlds_cfg<256, 256, 2, 4>(ctx, p, m_off, st); break;
       case 24: {
-        if (!rs_ok(p) || (m_off && !p.m_dev)) { rc = launch_dlds_cfg<256, 256, 2, 4>(ctx, p, m_off, st); break; }
-        rc = variant == 34 ? launch_256<false>(ctx, p, m_off, pick.parts, st) : launch_256<true>(ctx, p, m_off, pick.parts, st);
+        if (!rd_ok(p) || (m_off && !p.m_dev)) { rc = launch_dlds_cfg<256, 256, 2, 4>(ctx, p, m_off, st); break; }
+        rc = launch_256(ctx, p, m_off, pick.parts, st);
         break; }
       case 25: rc = launch_ring_cfg<128, 128, 2>(ctx, p, pick.parts, st); break;
       case 26: rc = launch_ring_cfg<64, 64, 4>(ctx, p, pick.parts, st); break;

@@ -27,7 +27,7 @@ offsets of A_t, B_t, s48 step, s70, s71 LDS offsets the loads of A, B go to, s72
 a[0:255]: the 32 x 32 block (i, j) of the kernel's array is a[16 (4 i + j) ..], its 16 x 16 block (a, b) four registers at 4 (2 a + b) of
 those.  The blocks come out transposed (B fragment first): a lane owns row lane % 16 and four consecutive columns, 4 (lane / 16) ...
 
-LDS layouts are those of gen_gemm_rs_loop.py: rows of 64 of the contraction (128 bytes) with 16-byte chunk c of row r at c ^ (r / 2 % 8);
+LDS layouts: rows of 64 of the contraction (128 bytes) with 16-byte chunk c of row r at c ^ (r / 2 % 8);
 NN: B as [K rows, N columns], 64 rows of 512 bytes, 64-byte unit u of row r at u ^ (r % 4), fragments through two transposing reads of
 8 bytes a lane; TN: A that way too.  A load instruction fills 1 KB in lane order, so the permutation is in the addresses it reads.
 Bases of B in NN: up to three matrices below one another, the second segment's and the next tile's, each minus its first row.
