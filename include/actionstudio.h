@@ -371,6 +371,22 @@ int as_op_gemm_rows(as_ctx* ctx, int mode, int variant, int64_t M, int64_t N,
                     const int32_t* d_rows, int64_t row_off, const int32_t* d_group_off, int group, int n_groups,
                     int64_t group_b_stride, int64_t rows_cap, void* stream);
 
+/* The persistent 256x256 kernel alone (AS_BF16), in the layouts and over the rows that the step has it work with, split tiles
+ * included:
+ *   layout 0:  C[M,N] = alpha A[M,K] B[N,K]^T (+ R), n_b = 1;
+ *   layout 1:  C[M,N] = alpha A[M,K] B[K,N] (+ R): the K rows of B are those of n_b (1 to 3) matrices, one below the other in the
+ *              sum; h_b [host] points at them, h_b_rows [host] says how many rows each has (multiples of 64), all with row stride ldb;
+ *   layout 2:  C[M,N] float = alpha A[K,M]^T B[K,N] (+ C when accumulate), n_b = 1, over the first min(K, *d_k) rows when
+ *              d_k [device] is given; rows behind it up to a multiple of 64 must be zero.
+ * Layouts 0 and 1 take d_rows, row_off, or d_group_off, n_groups > 0, group_b_stride and rows_cap as as_op_gemm_rows does (all NULL and 0:
+ * M rows).  d_tail_scratch as in as_op_gemm.  AS_ERR_SHAPE where the kernel does not apply (N, M and K not in whole tiles and steps,
+ * operands not aligned, layout 2: too few tiles). */
+int as_op_gemm_layout(as_ctx* ctx, int layout, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
+                      const void* const* h_b, const int64_t* h_b_rows, int n_b, int64_t ldb,
+                      float alpha, const void* R, int64_t ldr, void* C, int64_t ldc, int c_is_f32, int accumulate,
+                      const int32_t* d_rows, int64_t row_off, const int32_t* d_group_off, int n_groups, int64_t group_b_stride, int64_t rows_cap,
+                      const int32_t* d_k, void* d_tail_scratch, size_t tail_scratch_bytes, void* stream);
+
 /* y = x * rstd * g with rstd = (mean x^2 + eps)^-1/2 per row; rstd float[n]. */
 int as_op_rmsnorm_fwd(as_ctx* ctx, int mode, int64_t n, int64_t d, const void* x, const void* g,
                       float eps, void* y, float* rstd, void* stream);

@@ -1412,6 +1412,43 @@ extern "C" int as_op_gemm_rows(as_ctx* ctx, int mode, int variant, int64_t M, in
   return launch_gemm_off(ctx, mode, variant, g, (int)row_off, (hipStream_t)stream);
 }
 
+extern "C" int as_op_gemm_layout(as_ctx* ctx, int layout, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
+                                 const void* const* h_b, const int64_t* h_b_rows, int n_b, int64_t ldb,
+                                 float alpha, const void* R, int64_t ldr, void* C, int64_t ldc, int c_is_f32, int accumulate,
+                                 const int32_t* d_rows, int64_t row_off, const int32_t* d_group_off, int n_groups, int64_t group_b_stride, int64_t rows_cap,
+                                 const int32_t* d_k, void* d_tail_scratch, size_t tail_scratch_bytes, void* stream) {
+  if (!ctx) return as_fail(nullptr, AS_ERR_NULL, "as_op_gemm_layout: NULL context");
+  if (!A || !h_b || !C) return as_fail(ctx, AS_ERR_NULL, "as_op_gemm_layout: NULL operand");
+  if (layout < 0 || layout > 2 || n_b < 1 || n_b > (layout == 1 ? 3 : 1) || (layout == 1 && !h_b_rows)) return as_fail(ctx, AS_ERR_SHAPE, "as_op_gemm_layout: layout 0, 1 (one to three matrices) or 2");
+  for (int i = 0; i < n_b; i++) if (!h_b[i]) return as_fail(ctx, AS_ERR_NULL, "as_op_gemm_layout: NULL operand");
+  if (M < 0 || N < 0 || K < 0 || M > INT32_MAX || N > INT32_MAX || K > INT32_MAX || row_off < 0 || row_off > INT32_MAX || rows_cap < 0 || rows_cap > INT32_MAX || n_groups < 0 || group_b_stride < 0)
+    return as_fail(ctx, AS_ERR_SHAPE, "as_op_gemm_layout: sizes must be in [0, 2^31)");
+  if (d_tail_scratch && (tail_scratch_bytes < (size_t)AS_GEMM_TAIL_SCRATCH_BYTES || ((uintptr_t)d_tail_scratch & 255)))
+    return as_fail(ctx, AS_ERR_WORKSPACE, "as_op_gemm_layout: tail scratch must be 256-byte aligned and hold AS_GEMM_TAIL_SCRATCH_BYTES");
+  if (lda < (layout == 2 ? M : K) || ldb < (layout == 0 ? K : N) || ldc < N || (R && ldr < N)) return as_fail(ctx, AS_ERR_SHAPE, "as_op_gemm_layout: leading dimension smaller than the row length");
+  if ((d_group_off != nullptr) != (n_groups > 0) || (d_group_off && (d_rows || row_off)) || (row_off && !d_rows) || (layout == 2 && (d_rows || d_group_off || R || !c_is_f32)) || (layout != 2 && (d_k || accumulate)))
+    return as_fail(ctx, AS_ERR_SHAPE, "as_op_gemm_layout: arguments of another layout");
+  GemmParams g; memset(&g, 0, sizeof g);
+  g.seg[0] = {A, h_b[0], lda, ldb, (int)K}; g.nseg = 1;
+  if (layout == 1) {
+    int64_t row = 0;
+    for (int i = 0; i < n_b; i++) {
+      if (h_b_rows[i] <= 0 || h_b_rows[i] % 64) return as_fail(ctx, AS_ERR_SHAPE, "as_op_gemm_layout: rows of a matrix must be a positive multiple of 64");
+      if (i) { g.nb[i - 1] = h_b[i]; g.nb_row[i - 1] = (int)row; }
+      row += h_b_rows[i];
+    }
+    if (row != K) return as_fail(ctx, AS_ERR_SHAPE, "as_op_gemm_layout: the matrices' rows must add up to K");
+    g.nn = n_b;
+  }
+  g.tn = layout == 2; g.k_dev = d_k; g.accumulate = accumulate;
+  g.M = (int)M; g.N = (int)N; g.C = C; g.ldc = ldc; g.c_f32 = c_is_f32; g.alpha = alpha; g.R = R; g.ldr = ldr; g.splitk = 1;
+  g.m_dev = d_rows; g.grp_off = d_group_off; g.grp_n = n_groups; g.grp_b_stride = group_b_stride;
+  g.tail_part = (float*)d_tail_scratch; g.rows_cap = d_group_off ? (int)rows_cap : d_tail_scratch ? (int)M : 0;
+  if (!gemm_rd_applies(AS_BF16, g)) return as_fail(ctx, AS_ERR_SHAPE, "as_op_gemm_layout: not in whole tiles and steps, or not aligned");
+  AS_HIP(ctx, hipSetDevice(ctx->device));
+  return launch_gemm_off(ctx, AS_BF16, 34, g, (int)row_off, (hipStream_t)stream);
+}
+
 extern "C" int as_op_rmsnorm_fwd(as_ctx* ctx, int mode, int64_t n, int64_t d, const void* x, const void* g,
                                  float eps, void* y, float* rstd, void* stream) {
   if (!ctx) return as_fail(nullptr, AS_ERR_NULL, "as_op_rmsnorm_fwd: NULL context");

@@ -199,3 +199,20 @@ def test_row_counted_gemm_and_timing_filter_reject_bad_arguments(B):
     assert B.lib.as_profile_only(ctx.handle, -1) == 0
     assert B.lib.as_profile_only(None, 0) == B.ERR["NULL"]
     ctx.close()
+
+
+def test_layout_gemm_rejects_bad_arguments(B):
+    """Host-side checks only: none of these reaches a HIP call."""
+    ctx = B.Context(B.make_config(synth.CONFIGS[1]))
+    p = C.c_void_p(4096)
+
+    def call(layout=0, M=512, N=256, K=128, A=p, lda=128, b=(4096,), rows=None, ldb=128, Cm=p, ldc=256, f32=0, acc=0, R=None, d_rows=None, row_off=0, off=None, groups=0, cap=0, d_k=None, ws=None, n=0):
+        hb, hr = (C.c_void_p * len(b))(*b), (C.c_int64 * len(b))(*(rows or [0] * len(b)))
+        return B.lib.as_op_gemm_layout(ctx.handle, layout, M, N, K, A, lda, hb, hr, len(b), ldb, 1.0, R, 256, Cm, ldc, f32, acc, d_rows, row_off, off, groups, 0, cap, d_k, ws, n, None)
+    assert call(A=None) == B.ERR["NULL"] and call(Cm=None) == B.ERR["NULL"] and call(b=(None,)) == B.ERR["NULL"]
+    for kw in (dict(layout=3), dict(b=(4096, 4096)), dict(M=-1), dict(lda=64), dict(ldb=64), dict(ldc=128), dict(N=128, ldc=128), dict(M=128), dict(K=96), dict(row_off=8), dict(groups=2), dict(off=p),
+               dict(d_rows=p, off=p, groups=1), dict(d_k=p), dict(acc=1), dict(layout=1, ldb=256, rows=[64]), dict(layout=1, ldb=256, b=(4096, 4096), rows=[96, 32]), dict(layout=2, lda=512, ldb=256, d_rows=p),
+               dict(layout=2, lda=512, ldb=256, f32=0), dict(A=C.c_void_p(4104))):
+        assert call(**kw) == B.ERR["SHAPE"], kw
+    assert call(ws=p, n=64) == B.ERR["WORKSPACE"] and call(ws=C.c_void_p(4100), n=64 << 20) == B.ERR["WORKSPACE"]
+    ctx.close()

@@ -31,6 +31,7 @@ def test_large_products(M, N, K1, K2, split, out_f32, with_residual):
     ref, size = 0.5 * ref, 0.5 * size
     if with_residual:
         ref += R.double(); size += R.double().abs()
-    # exact products, at most K additions in float that may each lose the bits below the last place; one rounding to the result's type
-    bound = (K1 + K2 + 3) * 2.0 ** -23 * size + (0.0 if out_f32 else 2.0 ** -8) * ref.abs()
+    # exact products of N(0, 1) values: K additions in float whose roundings, of sums of size sqrt(K), add up like a random walk, 2^-24 K, and
+    # at worst one after the other, K + 3 times the last place of the magnitudes' sum; one rounding to the result's type
+    bound = ((K1 + K2 + 3) * 2.0 ** -23 * size).clamp_max(1e-5 * (K1 + K2) ** 0.5) + (0.0 if out_f32 else 2.0 ** -8) * ref.abs()
     assert ((out.double() - ref).abs() <= bound).all()
