@@ -861,14 +861,16 @@ __device__ __forceinline__ void tile64_offsets(int64_t ld, int wave, int lane, u
 }
 // The loads are written in assembly: issued through the builtin they are LDS writes the compiler knows of, and as it cannot tell the
 // transposing reads from them it waits for all of them (vmcnt(0)) in front of the first such read of a step.  They have no register
-// results; their arrival is what stage_barrier waits for.
+// results; their arrival is what stage_barrier waits for.  Nothing looks into such a block for hazards: a vector instruction may have written
+// the base's scalar registers (readfirstlane) right in front of it, and a load may read those five wait states later.
 __device__ __forceinline__ uint32_t lds_addr(const void* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p; }
 __device__ __forceinline__ void tile64_to_lds(const bf16_t* base, int64_t ld, int row0, int row_max, const uint32_t (&voff)[2], bf16_t* s, int wave, int lane) {
   const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_addr(s)) + wave * 2048;
+  uint32_t m0;                                            // the compiler's own, given back
   if (row0 + 63 <= row_max) {
     const char* b = (const char*)uniform_ptr(base + (int64_t)row0 * ld);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\ts_add_u32 m0, %0, 1024\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3"
-                 :: "s"(dst), "v"(voff[0]), "v"(voff[1]), "s"(b) : "memory", "m0", "scc");
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %2, %4\n\ts_add_u32 m0, %1, 1024\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %4\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0) : "s"(dst), "v"(voff[0]), "v"(voff[1]), "s"(b) : "memory", "scc");
     return;
   }
   const bf16_t* src[2];                                   // the last tile of the stream: rows past the end repeat the last one
@@ -877,12 +879,14 @@ __device__ __forceinline__ void tile64_to_lds(const bf16_t* base, int64_t ld, in
     const int row = wave * 16 + i * 8 + (lane >> 3);
     src[i] = base + (int64_t)min(row0 + row, row_max) * ld + ((lane & 7) ^ swz64(row)) * 8;
   }
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_add_u32 m0, %0, 1024\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off"
-               :: "s"(dst), "v"(src[0]), "v"(src[1]) : "memory", "m0", "scc");
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\ts_add_u32 m0, %1, 1024\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, off\n\ts_mov_b32 m0, %0"
+               : "=&s"(m0) : "s"(dst), "v"(src[0]), "v"(src[1]) : "memory", "scc");
 }
 // 64 floats, one per lane
 __device__ __forceinline__ void floats64_to_lds(const float* src, bf16_t* s) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" :: "s"(__builtin_amdgcn_readfirstlane(lds_addr(s))), "v"(src) : "memory", "m0");
+  uint32_t m0;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %2, off\n\ts_mov_b32 m0, %0"
+               : "=&s"(m0) : "s"(__builtin_amdgcn_readfirstlane(lds_addr(s))), "v"(src) : "memory");
 }
 // row fragment: row 32 blk + lane % 32, columns 16 ks + 8 h .. + 7 (f(row) = f(lane % 32): 32 blk does not touch bits 1..3)
 __device__ __forceinline__ bf16x8 row64(const bf16_t* tile, int blk, int ks, int l31, int h, int f) {

@@ -434,3 +434,27 @@ def test_lora_grad_loop():
         n_mfma += op.startswith("v_mfma")
     assert n_mfma == 3 * 4 * 32
     assert _min_valu_to_mfma_distance(seq) >= 4
+
+
+def test_hand_written_loads_keep_their_distance():
+    """Inline assembly is not searched for hazards by the compiler.  A load may read a scalar register five wait states after a vector
+    instruction wrote it (readfirstlane, right in front of the block at worst) and m0 one after it was set; m0 is not the block's to
+    change, it is given back."""
+    seen = 0
+    for name in os.listdir(CSRC):
+        if not name.endswith(".hip"):
+            continue
+        for text, rest in re.findall(r'asm volatile\(("(?:[^"\\]|\\.)*")\s*(:[^;]*)?;', open(os.path.join(CSRC, name)).read()):
+            ins = text[1:-1].replace("\\t", "").split("\\n")
+            if not any(i.startswith("global_load_lds") for i in ins):
+                continue
+            seen += 1
+            assert '"m0"' not in rest and ins[0] == "s_mov_b32 %0, m0" and ins[-1] == "s_mov_b32 m0, %0", ins
+            states, since_m0 = 0, 99
+            for i in ins:
+                if i.startswith("global_load_lds"):
+                    assert since_m0 >= 1, ins
+                    assert i.endswith(", off") or states >= 5, ins
+                n = 1 + int(i.split()[1]) if i.startswith("s_nop") else 1
+                states, since_m0 = states + n, 0 if i.split(",")[0].endswith(" m0") else since_m0 + n
+    assert seen == 3
