@@ -4,8 +4,8 @@
 // inside the same accumulators instead of a second GEMM and an add.
 //
 // Kernels:
-//  * gemm_f32_kernel        -- float operands on the matrix cores, 16x16 and 32x32 results per workgroup: the fp32 tier's small products.
-//  * gemm_fma_kernel        -- any type, any shape; fp32 FMAs: the fp32 tier's large products, bf16 rows that are not 16-byte aligned.
+//  * gemm_f32_kernel        -- float operands on the matrix cores, 16x16 and 32x32 results per workgroup: the fp32 tier's small products (f32_pick).
+//  * gemm_fma_kernel        -- any type, any shape; fp32 FMAs: the fp32 tier's large products, bf16 rows that are not 16-byte aligned, variant 1.
 //  * gemm_mfma_rd_kernel    -- bf16, hand-scheduled 256x256 tiles, persistent: the large products; also with B, or A and B, given by rows of K.
 //  * gemm_mfma_ring_kernel  -- bf16, 128x128 and 64x64 tiles in a ring of LDS stages: few rows or narrow outputs.
 //  * gemm_mfma_dlds_kernel, gemm_mfma_kernel -- bf16: K that is no multiple of 64, rows counted on the device that the
@@ -13,6 +13,7 @@
 // In all of them workgroup ids are first de-interleaved over the 8 XCDs (ids are dealt round-robin to XCDs, each with a
 // private L2) and then walked in groups of row tiles, so that the tiles resident on one XCD share A and B panels.
 #include "common.h"
+#include <cmath>
 #include <type_traits>
 
 // ------------------------------------------------------------------ helpers
@@ -41,7 +42,7 @@ __device__ __forceinline__ void store_out(const GemmParams& p, int z, int row, i
 // ------------------------------------------------------------- plain kernel
 // float FMAs, every product of an output in ascending order of k.  Tiles of BT x BT with 16 x 16 threads, rows in LDS with k
 // contiguous, so that a thread reads four k of a row at a time; the next K step's elements are on their way from memory
-// while this one is multiplied.  64-wide steps and 32 x 32 tiles (bf16 only) while those do not fill the chip, 64 x 64 tiles beyond.
+// while this one is multiplied.  64-wide steps and 32 x 32 tiles while those do not fill the chip, 64 x 64 tiles beyond.
 template <typename T, int BT, int BK>
 __global__ __launch_bounds__(256) void gemm_fma_kernel(GemmParams p, int m_off) {
   constexpr int TT = BT / 16, LS = BK + 4, PER = BT * BK / 4 / 256;      // outputs per thread and side; groups of four elements a thread loads
@@ -121,8 +122,8 @@ __global__ __launch_bounds__(256) void gemm_fma_kernel(GemmParams p, int m_off) 
 // every NW-th 16-wide chunk of the contraction each, operands come from memory into the fragments without LDS (a lane loads four
 // consecutive k of its row, 16 bytes; the four k of one matrix instruction are then 4 apart, in both operands alike), the next four
 // chunks' loads are in flight behind the products of these, and one sum over the waves ends it.  Four waves up to 16
-// chunks, eight up to 32, else sixteen (T = 1): up to 64 chunks every load of the product is then under way at once.  T = 1 until its 16 x 16 tiles are
-// eight workgroups per CU, T = 2 beyond, as half the operand reads per product count then.
+// chunks, eight up to 32, else sixteen (T = 1): up to 64 chunks every load of the product is then under way at once.  T = 2, beyond two to four
+// 16 x 16 tiles per CU, reads half the operands per product; from two 64 x 64 tiles per CU on gemm_fma_kernel is ahead, which reads each once per tile (f32_pick).
 // NN: B is [K, N], rows of up to three matrices below one another (p.nn): the layout of a weight matrix in the product with its output
 // gradient, so that no matrix is transposed first.  A lane then loads its column of four rows, 4 bytes each.
 // 2-layer model of width 128, 478 tokens, a product: 9.4 us with 32x32 tiles through LDS and FMAs, 5.6 so (K 688 and 1024: 20 and 28, now 8).
@@ -1178,10 +1179,71 @@ static bool rd_ok(const GemmParams& p) {
 
 static bool rd_live(const GemmParams& p) { return p.m_dev || p.grp_off; }
 static int fma_tile(const GemmParams& p) { return cdiv(p.N, 64) * cdiv(p.M, 64) * p.splitk >= kCus ? 64 : 32; }
-// float products: 16 x 16 results per workgroup, 32 x 32 (gemm_f32_kernel), or 4: 64 x 64 (gemm_fma_kernel)
-static int f32_tile(const GemmParams& p) {
-  if (cdiv(p.N, 16) * cdiv(p.M, 16) * p.splitk <= 8 * kCus) return 1;
-  return p.nn || cdiv(p.N, 64) * cdiv(p.M, 64) * p.splitk < 4 * kCus ? 2 : 4;
+
+// Float products: gemm_f32_kernel with 16 x 16 or 32 x 32 results per workgroup, gemm_fma_kernel with 32 x 32 or 64 x 64; B by rows of K: the first
+// two only.  Which one: the time that a fit to measured ones expects (us): a launch, the chain of one tile's contraction, and the work of
+// n tiles per CU, the last two joined as max (16 x 16) or as hypotenuse; rows that are not whole 16-byte pieces, which gemm_f32_kernel loads
+// value by value, have a fit of their own.  Fitted to all four kernels, operands new to the L2s, on 41 pairs of N and K (8 x 16 to 32000 x
+// 2048, a fifth of them odd) and row counts from 16 to 200,000, 532 shapes, and held against 678 shapes on operands just used.  gemm_fma_kernel's
+// own choice of tile, which had these products alone, is given 8 % ahead: the pick is 1.5 times as fast as that one on average, 8 % slower at
+// worst and more than 2 % at four shapes; 1.3 % over the best of the four on average.  Of the small tiles the 16 x 16 ones are 5 % ahead: four
+// times the workgroups where operands come from further away than measured.  (us, kernels in the order below: 478 x 384 x 128 5.7, 5.8, 6.6,
+// 11.6; 1003 x 1024 x 128 15, 12, 10.5, 12.6; 478 x 1024 x 1024 40, 25, 33, 60; 8192 x 3072 x 1024 -, 901, 970, 717; 2048 x 452 x 654 111, 70, 52, 49.)
+enum { F32_16, F32_32, FMA_32, FMA_64 };
+static constexpr int kF32Shift[4] = {4, 5, 5, 6}, kF32Tile[4] = {16, 32, 32, 64};
+static bool f32_whole_rows(const GemmParams& p, bool nn) {
+  for (int s = 0; s < p.nseg; s++) {
+    const GemmSeg& g = p.seg[s];
+    if (g.K % 4 || g.lda % 4 || (uintptr_t)g.A % 16 || (!nn && (g.ldb % 4 || (uintptr_t)g.B % 16))) return false;
+  }
+  return true;
+}
+struct F32Shape { int64_t rows; bool whole; double K, parts; };
+static double f32_time(int kernel, int nn, const F32Shape& x, int N) {
+  struct Fit { double launch, step, base, tile_step, tile_base; };
+  static constexpr Fit nt_fit[2][4] = {{{3.11, 0.0101, 0.253, 0.01, 0.343}, {1.75, 0.0295, 1.61, 0.0222, 1.41}, {3.8, 0.0297, 0.073, 0.0147, 0.747}, {5.16, 0.0626, 0., 0.0339, 1.59}},
+                                       {{3.61, 0.00397, 0., 0.00425, 0.265}, {3.44, 0.0105, 0.174, 0.00835, 1.32}, {3.32, 0.023, 0., 0.0101, 0.474}, {3.99, 0.0533, 0., 0.029, 1.02}}};
+  static constexpr Fit nn_fit[2][2] = {{{3.02, 0.00667, 0.723, 0.00732, 0.522}, {1.1, 0.0208, 3.17, 0.0153, 1.8}}, {{3.65, 0.00382, 0., 0.0045, 0.271}, {2.04, 0.0117, 2.12, 0.00869, 1.46}}};
+  const Fit& f = nn ? nn_fit[x.whole][kernel] : nt_fit[x.whole][kernel];
+  const int s = kF32Shift[kernel], b1 = kF32Tile[kernel] - 1;
+  const double n = (double)((((int64_t)N + b1) >> s) * ((x.rows + b1) >> s)) * x.parts * (1. / kCus);     // (a step of a small model asks some hundred times: shifts, no hypot)
+  if (kernel == F32_16 && n > 16.) return 1e30;            // beyond what was measured
+  const double chain = f.base + f.step * x.K, work = (f.tile_base + f.tile_step * x.K) * n;
+  const double several = nn < 2 ? 1. : kernel == F32_16 ? 1.22 : 1.45;       // more than one matrix: a choice per element (1.06-1.34 and 1.13-1.63 measured)
+  return (f.launch + (kernel == F32_16 ? std::max(chain, work) : std::sqrt(chain * chain + work * work))) * several * (kernel == F32_32 ? 1.05 : 1.);
+}
+// column groups side by side in one launch: groups of whole tiles, or (gemm_f32_kernel) any if A is the same for all
+static bool f32_groups_fit(const GemmParams& p, int kernel) {
+  if (kernel <= F32_32 && p.nseg == 1) return true;
+  for (int g = 0; g < p.ncg; g++) if (p.cg_end[g] % kF32Tile[kernel]) return false;
+  return true;
+}
+struct F32Pick { int kernel; double time; };
+static F32Pick f32_pick(const GemmParams& p, int variant, bool nn) {
+  const int usual = fma_tile(p) == 64 ? FMA_64 : FMA_32;
+  if (variant == 1) return {usual, 0.};
+  // rows: those a group may expect; of rows counted on the device (targets) a quarter
+  const int64_t rows = p.grp_off && p.grp_rows > 0 ? std::max<int64_t>(1, (int64_t)p.grp_rows / std::max(1, p.grp_n)) : p.m_dev ? (p.M + 3) / 4 : p.M;
+  const F32Shape x = {rows, f32_whole_rows(p, nn), (double)(p.seg[0].K + (p.nseg > 1 ? p.seg[1].K : 0)) / p.splitk, (double)p.splitk};
+  F32Pick best{nn ? F32_32 : usual, 1e30};
+  for (int k = 0; k < (nn ? 2 : 4); k++) {
+    if (k != FMA_64 && (p.M - 1) >> kF32Shift[k] >= 65535) continue;  // rows of a grid
+    double t = 0.;
+    if (f32_groups_fit(p, k)) t = f32_time(k, nn ? p.nn : 0, x, p.N);
+    else for (int g = 0; g < p.ncg; g++) t += f32_time(k, 0, x, p.cg_end[g] - (g ? p.cg_end[g - 1] : 0));      // one launch each
+    if (!nn && k != usual) t *= 1.08;
+    if (t < best.time) best = {k, t};
+  }
+  return best;
+}
+static bool f32_nn_ok(int variant, const GemmParams& p) {
+  return variant == 0 && p.nn >= 1 && p.nn <= 3 && !p.ncg && (p.nseg < 2 || p.seg[1].ldb == p.seg[0].ldb) && (p.M - 1) >> 5 < 65535;
+}
+// B by rows of K, against a transposed copy of its matrices (at least 2.4 us each, 1.4 us per million elements) and the product with that one;
+// 10 % ahead for the copy, which was the only way: 1.7 times as fast on average over the shapes above, 7 % slower at worst
+static bool f32_nn_pays(const GemmParams& p) {
+  const double launches = 2.4 * p.nn, bytes = 1.4e-6 * p.seg[0].K * p.N, copy = std::sqrt(launches * launches + bytes * bytes);
+  return f32_pick(p, 0, true).time * 1.1 < copy + f32_pick(p, 0, false).time;
 }
 // rows counted on the device whose contraction is long enough (sixteen parts of eight steps) to be split by the live count
 static bool live_split_ok(const GemmParams& p) {
@@ -1351,7 +1413,7 @@ static GemmPick pick_cfg(const GemmParams& p) {
 }
 
 bool gemm_nn_applies(int mode, int variant, const GemmParams& p) {
-  if (mode == AS_FP32) return variant <= 1 && p.nn >= 1 && p.nn <= 3 && !p.ncg && (p.nseg < 2 || p.seg[1].ldb == p.seg[0].ldb);
+  if (mode == AS_FP32) return f32_nn_ok(variant, p) && f32_nn_pays(p);
   if (mode != AS_BF16 || (variant != 0 && variant != 2 && variant != 34) || !mfma_ok(p) || !rd_ok(p)) return false;
   if (p.nn < 1 || p.nn > 3 || p.ncg || p.epi != GEMM_EPI_NONE || p.seg[0].ldb > (1 << 22) || (p.nseg > 1 && p.seg[1].ldb != p.seg[0].ldb)) return false;
   int row = 0;
@@ -1380,7 +1442,7 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
   if (p.splitk > 1 && !p.partial) return as_fail(ctx, AS_ERR_WORKSPACE, "gemm: split-K needs a partial buffer");
   if (p.accumulate && !p.c_f32) return as_fail(ctx, AS_ERR_SHAPE, "gemm: accumulate needs float output");
   if (p.grp_off && p.splitk > 1) return as_fail(ctx, AS_ERR_SHAPE, "gemm: grouped rows and split-K do not combine");
-  if (p.nn && (!gemm_nn_applies(mode, variant, p) || (m_off && !p.m_dev))) return as_fail(ctx, AS_ERR_SHAPE, "gemm: B as [K, N] needs the hand-scheduled kernel or the float one");
+  if (p.nn && (!(mode == AS_FP32 ? f32_nn_ok(variant, p) : gemm_nn_applies(mode, variant, p)) || (m_off && !p.m_dev))) return as_fail(ctx, AS_ERR_SHAPE, "gemm: B as [K, N] needs the hand-scheduled kernel or the float one");
   if (p.tn) {
     if (!gemm_tn_applies(mode, variant, p) || m_off) return as_fail(ctx, AS_ERR_SHAPE, "gemm: only the hand-scheduled kernel reads A as [K, M]");
     prof_begin(ctx, st, p.k_dev ? AS_K_GEMM_DEVROWS : AS_K_GEMM_RS, p.k_dev ? 0.0 : 2.0 * p.M * p.N * p.seg[0].K);
@@ -1416,9 +1478,7 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
     bool fused = mode == AS_BF16 && variant != 1 && mfma_ok(p) && ((c == 24 && rd_ok(p)) || c == 25 || c == 26);
     for (int g = 0; g < p.ncg && fused; g++) fused = p.cg_end[g] % width == 0 && !((uintptr_t)p.cg_B1[g] % 16) && (p.nseg < 2 || !((uintptr_t)p.cg_B2[g] % 16));
     if (mode == AS_FP32) {
-      const int t = f32_tile(p);                         // the small kernel takes groups that end inside a tile if A is the same for all
-      fused = true;
-      for (int g = 0; g < p.ncg; g++) fused = fused && ((t < 4 && p.nseg == 1) || p.cg_end[g] % (16 * t) == 0);
+      fused = f32_groups_fit(p, f32_pick(p, variant, false).kernel);
     }
     if (!fused) {                                        // one launch per group
       const size_t esz = mode == AS_BF16 ? 2 : 4;
@@ -1467,19 +1527,20 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
     const bool big = bt == 64;
     dim3 grid((unsigned)cdiv(p.N, bt), (unsigned)cdiv(p.M, bt), (unsigned)p.splitk);
     if (mode == AS_FP32) {
-      const int t = f32_tile(p);
-      const dim3 g((unsigned)cdiv(p.N, 16 * t), (unsigned)cdiv(p.M, 16 * t), (unsigned)p.splitk);
+      const int k = f32_pick(p, variant, p.nn > 0).kernel, b = kF32Tile[k];
+      const dim3 g((unsigned)cdiv(p.N, b), (unsigned)cdiv(p.M, b), (unsigned)p.splitk);
       auto run = [&](auto nn) {
         constexpr bool NN = decltype(nn)::value;
         const int chunks = (int)(cdiv(p.seg[0].K, 16) + (p.nseg > 1 ? cdiv(p.seg[1].K, 16) : 0)) / p.splitk;
-        if (t == 2) gemm_f32_kernel<2, NN, 4><<<g, 256, 0, st>>>(p, m_off);
+        if (k == F32_32) gemm_f32_kernel<2, NN, 4><<<g, 256, 0, st>>>(p, m_off);
         else if (chunks <= 16) gemm_f32_kernel<1, NN, 4><<<g, 256, 0, st>>>(p, m_off);
         else if (chunks <= 32) gemm_f32_kernel<1, NN, 8><<<g, 512, 0, st>>>(p, m_off);
         else gemm_f32_kernel<1, NN, 16><<<g, 1024, 0, st>>>(p, m_off);
       };
-      if (t < 4 && p.nn) run(std::true_type{});
-      else if (t < 4) run(std::false_type{});
-      else gemm_fma_kernel<float, 64, 32><<<dim3((unsigned)cdiv(p.N, 64), (unsigned)cdiv(p.M, 64), (unsigned)p.splitk), 256, 0, st>>>(p, m_off);
+      if (p.nn) run(std::true_type{});
+      else if (k <= F32_32) run(std::false_type{});
+      else if (k == FMA_32) gemm_fma_kernel<float, 32, 64><<<g, 256, 0, st>>>(p, m_off);
+      else gemm_fma_kernel<float, 64, 32><<<g, 256, 0, st>>>(p, m_off);
     } else if (big) gemm_fma_kernel<bf16_t, 64, 32><<<grid, 256, 0, st>>>(p, m_off);
     else gemm_fma_kernel<bf16_t, 32, 64><<<grid, 256, 0, st>>>(p, m_off);
     AS_LAUNCH_CHECK(ctx);
