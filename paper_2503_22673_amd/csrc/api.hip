@@ -152,7 +152,8 @@ static int ensure_stage(as_ctx* ctx, size_t bytes) {
   if (bytes > ctx->h_stage_bytes) {
     if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
     ctx->h_stage = nullptr; ctx->h_stage_bytes = 0;
-    AS_HIP(ctx, hipHostMalloc(&ctx->h_stage, bytes, hipHostMallocDefault));
+    // coherent: the next call's kernel must not find this call's bytes in a cache
+    AS_HIP(ctx, hipHostMalloc(&ctx->h_stage, bytes, hipHostMallocCoherent));
     ctx->h_stage_bytes = bytes;
   }
   return AS_OK;

@@ -33,15 +33,15 @@ template <typename T> static bool vec_ok(const void* p, int64_t ld) {
 template <bool VEC>
 __global__ __launch_bounds__(256) void pack_kernel(const int32_t* __restrict__ h_tok, const int32_t* __restrict__ h_cu, const uint8_t* __restrict__ h_mask, int n_out, int n_cu,
                                                    int32_t* __restrict__ tok, int32_t* __restrict__ cu, uint8_t* __restrict__ mask) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
+  const int i = blockIdx.x * 256 + threadIdx.x;            // below 2^29: n_out is an int
   for (int k = i; k < n_cu; k += gridDim.x * 256) cu[k] = h_cu[k];
-  if (VEC && 4 * i + 4 <= n_out) {                         // i < 2^29: n_out is an int
+  if (VEC && i < n_out / 4) {
     const int4 t = reinterpret_cast<const int4*>(h_tok)[i];
     const uint32_t m = reinterpret_cast<const uint32_t*>(h_mask)[i];
     reinterpret_cast<int4*>(tok)[i] = t; reinterpret_cast<uint32_t*>(mask)[i] = m;
     return;
   }
-  for (int k = 4 * i; k < n_out && k < 4 * i + 4; k++) { tok[k] = h_tok[k]; mask[k] = h_mask[k]; }
+  for (int k = 4 * i, end = k + min(4, n_out - k); k < end; k++) { tok[k] = h_tok[k]; mask[k] = h_mask[k]; }      // 4 i + 4 may not be an int
 }
 
 int launch_pack(as_ctx* ctx, const int32_t* h_tokens, const int32_t* h_cu, const uint8_t* h_mask, int n_out, int n_cu, int32_t* d_tokens, int32_t* d_cu, uint8_t* d_mask, hipStream_t st) {

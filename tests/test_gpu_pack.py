@@ -69,6 +69,17 @@ def test_outputs_at_any_address(T, rows, shift):
     assert (tok[:shift] == -7).all() and (tok[shift + live:] == -7).all() and (msk[:shift] == 9).all() and (msk[shift + live:] == 9).all()
 
 
+@pytest.mark.parametrize("T,rows", [(64, 8), (4096, 16)])
+def test_every_batch_of_a_context_is_its_own(T, rows):
+    """The pinned buffer is written by the host and read by the device call after call, at the same addresses: nothing of an earlier batch"""
+    B, ctx = _ctx(1000)
+    lens = [T // 2, T // 2 - 1, 1, T, T // 3, T // 3, T // 4] * rows
+    for step in range(6):
+        g = synth.rng(step, 31)
+        trajs = [[(1, g.integers(0, 1000, size=n // 2).astype(np.int32)), (2, g.integers(0, 1000, size=n - n // 2).astype(np.int32))] for n in lens]
+        _same(B, ctx, trajs, T, rows, pad_id=step)
+
+
 # ------------------------------------------------- best fit decreasing (as_pack_policy)
 
 def _same_policy(B, ctx, trajs, T, rows, policy, pad_id=0, truncate=True):
