@@ -1352,17 +1352,17 @@ static bool mfma_ok(const GemmParams& p) {
 // 24 = the hand-scheduled persistent 256x256 kernel with 4 waves; 25, 26 = ring of stages, 128x128 and 64x64 tiles.
 struct GemmPick { int cfg, parts; };                     // parts: workgroups that share a tile's contraction
 
-// Plain rows in whole K steps: the kernel and the split that the measured step times say is fastest (us; every pair of
-// 14 projections of the 1B and 8B shapes and 9 row counts from 300 to 16,000, and the adapters' widths 64 to 192 from 300 to
-// 59,000 rows: 2 % over the best of all candidates on average, 20 % at worst):
-//   256x256 hand-scheduled  0.87 per K step and 14.4 per round of 256 workgroups (start-up and epilogue of a tile)
-//   128x128 ring            1.02 per step with two workgroups on every CU, 0.74 with one, 1.3 per round
-//   64x64 ring              0.46 and 0.24, 3.1 per launch
+// Plain rows in whole K steps: the kernel and the split that a time model (us) says is fastest:
+//   256x256 hand-scheduled  0.815 per K step and 14.4 per round of 256 workgroups (start-up and epilogue of a tile)
+//   128x128 ring            0.684 per step and 2.32 per round with two workgroups on every CU, 0.644 with one, 2.28 per launch
+//   64x64 ring              0.387 and 0.275, 4.36 per launch
 // and for a split the second launch, its partials written and read at about 4 TB/s, and its serial sum over the parts.
 // More than half a round of 256x256 tiles goes to the hand-scheduled kernel unsplit without looking further: from there on it
-// is at most 3 % behind and mostly 15-40 % ahead.  Constants fitted to every candidate of 12 projections of the 1B and 8B shapes at seven
-// row counts from 300 to 7000 and of the adapters' widths 64 and 192 from 300 to 30,000 rows: the pick is 0.3 % over the best on
-// average, 11 % at worst (with the constants of the register-staged 256x256 kernel 1.4 and 31 %).
+// is mostly 15-40 % ahead; behind only where few steps meet a second round of few tiles (822 x 18432 x 832, 288 tiles: 43 against 33).  Fitted to the choice itself, over every candidate (1 to 12 parts) of 19 pairs of N and K, those of
+// the 1B and 8B projections and adapters and narrow ones of 256 to 1280 columns, at ten row counts from 100 to 18,787, operands new to the
+// L2s: the pick is 0.4 % over the best on average, more than 10 % at two of 182 shapes, 19 % at worst (100 x 14336 x 4160); with 129 more,
+// from 2 rows and one step on, 0.7 %.  Constants fitted to the projections' widths alone were 3.7 % over it on average and 35 % at worst (588 x
+// 1024 x 4160: 23.7 where three parts take 18.3).
 // Examples (us): 1531 x 4096 x 14400: 64x64 ring 330, 128x128 218, 256x256 in two parts 158; 1003 x 2048 x 8256: 72, 49 (four parts), 51 (six);
 // 1003 x 2048 x 16512: 128x128 in four parts 86, 256x256 in eight 73.
 static GemmPick pick_plain(const GemmParams& p) {
@@ -1379,9 +1379,9 @@ static GemmPick pick_plain(const GemmParams& p) {
     const double per = (double)cdiv(steps, parts);
     if (rs) {
       const int64_t T = cdiv(p.M, 256) * (p.N / 256);      // at most half a round
-      if (parts == 1) offer(24, 1, per * 0.87 + 14.4);
+      if (parts == 1) offer(24, 1, per * 0.815 + 14.4);
       else if (T * parts <= kCus && steps / parts >= 3 && (steps - cdiv(steps, parts)) < (int64_t)(p.seg[0].K / 64))
-        offer(24, parts, per * 0.87 + 14.4 + 6.2 + 2. * parts + 0.208 * (parts + 0.5) * mb);
+        offer(24, parts, per * 0.815 + 14.4 + 5.47 + 0.237 * parts + 0.206 * (parts + 0.5) * mb);
     }
     if (p.tn || ((double)parts * p.M * p.N > (double)kGemmTailFloats && parts > 1)) continue;   // tn: the hand-scheduled kernel only
     auto ring = [&](int cfg, int b, double launch, double one, double two, double round, double f0, double f_part, double f_mb) {
@@ -1390,8 +1390,8 @@ static GemmPick pick_plain(const GemmParams& p) {
       if (parts > 1) t += f0 + f_part * parts + f_mb * (parts + 0.5) * mb;
       offer(cfg, parts, t);
     };
-    ring(25, 128, 0., 0.74, 1.02, 1.3, 2.2, 0.65, 0.248);
-    ring(26, 64, 3.1, 0.243, 0.455, 0., 0.8, 0.19, 0.53);
+    ring(25, 128, 2.28, 0.644, 0.684, 2.32, 3.16, 0.316, 0.25);
+    ring(26, 64, 4.36, 0.275, 0.387, 0., 1.43, 0.352, 0.281);
   }
   return best;
 }
@@ -1407,7 +1407,7 @@ static GemmPick pick_cfg(const GemmParams& p) {
   if (p.N <= 128 && p.M > 128) return {3, 1};
   if (p.M <= 128) return {2, 1};
   if ((int64_t)cdiv(p.M, 256) * cdiv(p.N, 256) * p.splitk < 128) return {3, 1};
-  // The hand-scheduled kernel is ahead on every large shape it covers (a fifth and more on the shapes of an 8B model)
+  // The hand-scheduled kernel is ahead on every large shape it covers (4096 and 16384 rows of an 8B model: 27 to 30 %)
   if (rd_ok(p)) return {24, 1};
   return {20, 1};                                        // direct-to-LDS tiles when K allows, else staged (0)
 }
