@@ -1185,7 +1185,7 @@ static int fma_tile(const GemmParams& p) { return cdiv(p.N, 64) * cdiv(p.M, 64) 
 // n tiles per CU, the last two joined as max (16 x 16) or as hypotenuse; rows that are not whole 16-byte pieces, which gemm_f32_kernel loads
 // value by value, have a fit of their own.  Fitted to all four kernels, operands new to the L2s, on 41 pairs of N and K (8 x 16 to 32000 x
 // 2048, a fifth of them odd) and row counts from 16 to 200,000, 532 shapes, and held against 678 shapes on operands just used.  gemm_fma_kernel's
-// own choice of tile, which had these products alone, is given 8 % ahead: the pick is 1.5 times as fast as that one on average, 8 % slower at
+// own choice of tile, which had these products alone, is given 8 % ahead (20 where rows are not whole pieces: the fit is worse there): the pick is 1.5 times as fast as that one on average, 8 % slower at
 // worst and more than 2 % at four shapes; 1.3 % over the best of the four on average.  Of the small tiles the 16 x 16 ones are 5 % ahead: four
 // times the workgroups where operands come from further away than measured.  (us, kernels in the order below: 478 x 384 x 128 5.7, 5.8, 6.6,
 // 11.6; 1003 x 1024 x 128 15, 12, 10.5, 12.6; 478 x 1024 x 1024 40, 25, 33, 60; 8192 x 3072 x 1024 -, 901, 970, 717; 2048 x 452 x 654 111, 70, 52, 49.)
@@ -1198,7 +1198,7 @@ static bool f32_whole_rows(const GemmParams& p, bool nn) {
   }
   return true;
 }
-struct F32Shape { int64_t rows; bool whole; double K, parts; };
+struct F32Shape { int64_t rows; bool whole; int K1, K2; double parts; };
 static double f32_time(int kernel, int nn, const F32Shape& x, int N) {
   struct Fit { double launch, step, base, tile_step, tile_base; };
   static constexpr Fit nt_fit[2][4] = {{{3.11, 0.0101, 0.253, 0.01, 0.343}, {1.75, 0.0295, 1.61, 0.0222, 1.41}, {3.8, 0.0297, 0.073, 0.0147, 0.747}, {5.16, 0.0626, 0., 0.0339, 1.59}},
@@ -1206,9 +1206,11 @@ static double f32_time(int kernel, int nn, const F32Shape& x, int N) {
   static constexpr Fit nn_fit[2][2] = {{{3.02, 0.00667, 0.723, 0.00732, 0.522}, {1.1, 0.0208, 3.17, 0.0153, 1.8}}, {{3.65, 0.00382, 0., 0.0045, 0.271}, {2.04, 0.0117, 2.12, 0.00869, 1.46}}};
   const Fit& f = nn ? nn_fit[x.whole][kernel] : nt_fit[x.whole][kernel];
   const int s = kF32Shift[kernel], b1 = kF32Tile[kernel] - 1;
+  static constexpr int step[4] = {16, 16, 64, 32};         // of the contraction: what a short second segment costs
+  const double K = (double)(x.K1 + (x.K2 + step[kernel] - 1) / step[kernel] * step[kernel]) / x.parts;
   const double n = (double)((((int64_t)N + b1) >> s) * ((x.rows + b1) >> s)) * x.parts * (1. / kCus);     // (a step of a small model asks some hundred times: shifts, no hypot)
   if (kernel == F32_16 && n > 16.) return 1e30;            // beyond what was measured
-  const double chain = f.base + f.step * x.K, work = (f.tile_base + f.tile_step * x.K) * n;
+  const double chain = f.base + f.step * K, work = (f.tile_base + f.tile_step * K) * n;
   const double several = nn < 2 ? 1. : kernel == F32_16 ? 1.22 : 1.45;       // more than one matrix: a choice per element (1.06-1.34 and 1.13-1.63 measured)
   return (f.launch + (kernel == F32_16 ? std::max(chain, work) : std::sqrt(chain * chain + work * work))) * several * (kernel == F32_32 ? 1.05 : 1.);
 }
@@ -1224,14 +1226,14 @@ static F32Pick f32_pick(const GemmParams& p, int variant, bool nn) {
   if (variant == 1) return {usual, 0.};
   // rows: those a group may expect; of rows counted on the device (targets) a quarter
   const int64_t rows = p.grp_off && p.grp_rows > 0 ? std::max<int64_t>(1, (int64_t)p.grp_rows / std::max(1, p.grp_n)) : p.m_dev ? (p.M + 3) / 4 : p.M;
-  const F32Shape x = {rows, f32_whole_rows(p, nn), (double)(p.seg[0].K + (p.nseg > 1 ? p.seg[1].K : 0)) / p.splitk, (double)p.splitk};
+  const F32Shape x = {rows, f32_whole_rows(p, nn), p.seg[0].K, p.nseg > 1 ? p.seg[1].K : 0, (double)p.splitk};
   F32Pick best{nn ? F32_32 : usual, 1e30};
   for (int k = 0; k < (nn ? 2 : 4); k++) {
     if (k != FMA_64 && (p.M - 1) >> kF32Shift[k] >= 65535) continue;  // rows of a grid
     double t = 0.;
     if (f32_groups_fit(p, k)) t = f32_time(k, nn ? p.nn : 0, x, p.N);
     else for (int g = 0; g < p.ncg; g++) t += f32_time(k, 0, x, p.cg_end[g] - (g ? p.cg_end[g - 1] : 0));      // one launch each
-    if (!nn && k != usual) t *= 1.08;
+    if (!nn && k != usual) t *= x.whole ? 1.08 : 1.2;
     if (t < best.time) best = {k, t};
   }
   return best;
