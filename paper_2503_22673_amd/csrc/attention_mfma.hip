@@ -57,7 +57,7 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& a, int sl) {
 //    behind a wave-uniform branch.  The two lanes of a query hold the same reference, so each tests its own
 //    half of the keys; halves are exchanged only in that branch, and the two partial sums at the end.  The
 //    exchange through LDS on every tile sat in the serial chain between the products (24576 tokens, longest
-//    16384, 32 heads of 128: 2087 -> 2044 us; 8191, 4096: 263 -> 258; 32 heads of 64: 153.7 -> 149.8).
+//    16384, 32 heads of 128: 2008 -> 1970 us; 8191, 4096: 278 -> 273; 1003, 700, 32 heads of 64: 17.5 -> 16.7).
 //    Head_dim 128 is held by the card's power (1.7 GHz in this kernel): 16x16x32 products (level), half of the
 //    waves one phase behind the other half (level; 6 % slower on short segments) bring nothing.
 template <int ROWBYTES> __device__ __forceinline__ int swz_row(int row) { return ROWBYTES == 256 ? (row & 15) : ((row >> 1) & 7); }
@@ -846,11 +846,18 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv3_mfma(AttnParams p, float sc
 // the same phase: behind the barrier all issue the next tiles' loads, then all multiply, then all exponentiate.  Workgroups of four waves, three (dK / dV) or four to a
 // CU by their registers, overlap their phases; reading fragments ahead into registers costs a workgroup per CU and was slower
 // (dK / dV: 230 registers, 575 against 545 us of backward).
-// The tiles' loads are issued from assembly (tile64_to_lds): known to the compiler they cost a wait for all of them in front of the
-// first transposing read of a step (forward) or half step (dQ, dK / dV).  Without it, and with priority for the wave that has products
-// to issue: forward 2 to 5 % faster, backward 3 %.  32 query heads on 8 KV heads, this and the eight-wave kernels with token-major
-// copies: forward 150 and 200 us (8191 tokens, longest segment 4096), 246 and 309 (30000, 2500), 22 and 26 (1003, 700); backward 500
-// and 694, 900 and 1217, 58 and 77 us.
+// 32 query heads on 8 KV heads, this and the eight-wave kernels with token-major copies, us, longest segment in brackets: forward 150 and
+// 200 (8191 [4096]), 246 and 309 (30000 [2500]); backward 500 and 694, 900 and 1217, 58 and 77 (1003 [700]).  Since then, measure by measure on one box:
+//                                                      forward 1003 [700], 6000 [3000], 30000 [2500]    backward 1003, 8191, 30000
+//   before                                             18.2, 85, 262                                    62, 511, 900
+//   loads issued from assembly (tile64_to_lds): known
+//   to the compiler they cost a wait for all of them
+//   in front of the first transposing read of a step
+//   (forward) or half step (dQ, dK / dV)               17.5, 82, 248                                    60, 505, 875
+//   lane halves meet only where the maximum is raised  16.7, 82, 247                                    -
+//   backward: priority for the wave that has products
+//   to issue (matrix_phase)                            -                                                60, 494, 870
+// Priority in the forward too: 9 to 12 % slower up to 1500 tokens, 1 to 7 % at most others, 22 of 28 sizes to 30000, faster by 7 % at best (8191 [4096]).
 __device__ __forceinline__ int swz64(int row) { return ((row & 2) << 1) | ((row >> 1) & 2) | ((row >> 3) & 1); }
 constexpr int T64_E = 64 * 64;                            // elements of a tile
 
@@ -862,15 +869,17 @@ __device__ __forceinline__ void tile64_offsets(int64_t ld, int wave, int lane, u
 // The loads are written in assembly: issued through the builtin they are LDS writes the compiler knows of, and as it cannot tell the
 // transposing reads from them it waits for all of them (vmcnt(0)) in front of the first such read of a step.  They have no register
 // results; their arrival is what stage_barrier waits for.  Nothing looks into such a block for hazards: a vector instruction may have written
-// the base's scalar registers (readfirstlane) right in front of it, and a load may read those five wait states later.
+// the base's scalar registers (readfirstlane) right in front of it, and a load may read those five wait states later.  So the block copies the
+// base with a scalar instruction, which the hardware makes wait, and loads from the copy (s_nop 3 instead cost 1 % of short forwards).
 __device__ __forceinline__ uint32_t lds_addr(const void* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p; }
 __device__ __forceinline__ void tile64_to_lds(const bf16_t* base, int64_t ld, int row0, int row_max, const uint32_t (&voff)[2], bf16_t* s, int wave, int lane) {
   const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_addr(s)) + wave * 2048;
   uint32_t m0;                                            // the compiler's own, given back
   if (row0 + 63 <= row_max) {
     const char* b = (const char*)uniform_ptr(base + (int64_t)row0 * ld);
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %2, %4\n\ts_add_u32 m0, %1, 1024\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %4\n\ts_mov_b32 m0, %0"
-                 : "=&s"(m0) : "s"(dst), "v"(voff[0]), "v"(voff[1]), "s"(b) : "memory", "scc");
+    const char* at;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_mov_b64 %1, %5\n\tglobal_load_lds_dwordx4 %3, %1\n\ts_add_u32 m0, %2, 1024\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %1\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0), "=&s"(at) : "s"(dst), "v"(voff[0]), "v"(voff[1]), "s"(b) : "memory", "scc");
     return;
   }
   const bf16_t* src[2];                                   // the last tile of the stream: rows past the end repeat the last one
@@ -918,8 +927,7 @@ __device__ __forceinline__ void stage_barrier() {
   __syncthreads();
 }
 
-// Of the waves of a SIMD the one with products to issue goes first (backward, 8191 to 30000 tokens: 1.5 to 2 % faster; forward 169 -> 160 us
-// at 8191 tokens, level at 30000; no gain for the eight-wave forward of head_dim 128).
+// Of the waves of a SIMD the one with products to issue goes first (backward; figures above).
 __device__ __forceinline__ void matrix_phase(bool on) { if (on) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0); }
 
 template <int HPW>
@@ -964,7 +972,6 @@ __global__ __launch_bounds__(256, 4) void attn_fwd64_mfma(AttnParams p, float sl
     const bf16_t* sK = sm + b * 2 * T64_E; const bf16_t* sV = sK + T64_E;
     f32x16 s[2];
     if (mine) {
-      matrix_phase(true);
 #pragma unroll
       for (int kb = 0; kb < 2; kb++) {
         s[kb] = zero16();
@@ -972,7 +979,6 @@ __global__ __launch_bounds__(256, 4) void attn_fwd64_mfma(AttnParams p, float sl
         for (int ks = 0; ks < KS; ks++) s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row64(sK, kb, ks, l31, h, f), qf[ks], s[kb], 0, 0, 0);
       }
     }
-    matrix_phase(false);
     if (kt < kv_last) stage_v(kt + 1, b ^ 1);
     if (!mine) continue;
     if (!((k0 + 63 <= t_base) && (k0 >= ss_hi))) {          // the tile touches the diagonal or a segment start
@@ -1012,12 +1018,10 @@ __global__ __launch_bounds__(256, 4) void attn_fwd64_mfma(AttnParams p, float sl
       pb[kb * 2] = pack8(s[kb], 0); pb[kb * 2 + 1] = pack8(s[kb], 1);
     }
     l += rs;
-    matrix_phase(true);
 #pragma unroll
     for (int x = 0; x < 4; x++)
 #pragma unroll
       for (int cb = 0; cb < CB; cb++) o[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col64(sV, cn, x, cb), pb[x], o[cb], 0, 0, 0);
-    matrix_phase(false);
   }
   l += __shfl_xor(l, 32, 64);                              // the halves of the keys
   if (tq >= n) return;

@@ -438,8 +438,8 @@ def test_lora_grad_loop():
 
 def test_hand_written_loads_keep_their_distance():
     """Inline assembly is not searched for hazards by the compiler.  A load may read a scalar register five wait states after a vector
-    instruction wrote it (readfirstlane, right in front of the block at worst) and m0 one after it was set; m0 is not the block's to
-    change, it is given back."""
+    instruction wrote it (readfirstlane, right in front of the block at worst), or any time after a scalar instruction did, which itself
+    waits for such a value; and m0 one state after it was set.  m0 is not the block's to change, it is given back."""
     seen = 0
     for name in os.listdir(CSRC):
         if not name.endswith(".hip"):
@@ -450,11 +450,14 @@ def test_hand_written_loads_keep_their_distance():
                 continue
             seen += 1
             assert '"m0"' not in rest and ins[0] == "s_mov_b32 %0, m0" and ins[-1] == "s_mov_b32 m0, %0", ins
-            states, since_m0 = 0, 99
+            states, since_m0, scalar = 0, 99, set()
             for i in ins:
+                t = [x.strip() for x in i.partition(" ")[2].split(",")]
                 if i.startswith("global_load_lds"):
                     assert since_m0 >= 1, ins
-                    assert i.endswith(", off") or states >= 5, ins
-                n = 1 + int(i.split()[1]) if i.startswith("s_nop") else 1
-                states, since_m0 = states + n, 0 if i.split(",")[0].endswith(" m0") else since_m0 + n
+                    assert t[-1] == "off" or t[-1] in scalar or states >= 5, ins
+                elif i.startswith("s_") and not i.startswith("s_nop"):
+                    scalar.add(t[0])
+                n = 1 + int(t[0]) if i.startswith("s_nop") else 1
+                states, since_m0 = states + n, 0 if t[0] == "m0" else since_m0 + n
     assert seen == 3
