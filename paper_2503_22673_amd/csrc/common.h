@@ -71,7 +71,7 @@ __device__ __forceinline__ float wave_max(float v) {
 // GemmParams, what one product is, lies in gemm_items.h
 // the hand-scheduled kernel would take this product (whole 256 x 256 tiles, K in 64-wide steps, alignment)
 bool gemm_rd_applies(int mode, const GemmParams& p);
-// the launch (p.nn set) would go to the hand-scheduled kernel, which alone reads B as [K, N]
+// the launch (p.nn set) would go to a kernel that reads B as [K, N]: the hand-scheduled one, or (float operands) gemm_f32_kernel where it pays
 bool gemm_nn_applies(int mode, int variant, const GemmParams& p);
 bool gemm_tn_applies(int mode, int variant, const GemmParams& p);
 // floats of scratch (GemmParams::tail_part given by the caller through `tail_ws`) that let the launcher split the last round
