@@ -846,8 +846,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv3_mfma(AttnParams p, float sc
 // the same phase: behind the barrier all issue the next tiles' loads, then all multiply, then all exponentiate.  Workgroups of four waves, three (dK / dV) or four to a
 // CU by their registers, overlap their phases; reading fragments ahead into registers costs a workgroup per CU and was slower
 // (dK / dV: 230 registers, 575 against 545 us of backward).
-// 32 query heads on 8 KV heads, this and the eight-wave kernels with token-major copies, us, longest segment in brackets: forward 150 and
-// 200 (8191 [4096]), 246 and 309 (30000 [2500]); backward 500 and 694, 900 and 1217, 58 and 77 (1003 [700]).  Since then, measure by measure on one box:
+// 32 query heads on 8 KV heads, us, longest segment in brackets, when these kernels came and the eight-wave ones with token-major copies:
+// forward 186 and 200 (8191 [4096]), 271 and 309 (30000 [2500]), 22 and 26 (1003 [700]); backward 523 and 694, 926 and 1217, 60 and 77.
+// Since then, measure by measure on one card:
 //                                                      forward 1003 [700], 6000 [3000], 30000 [2500]    backward 1003, 8191, 30000
 //   before                                             18.2, 85, 262                                    62, 511, 900
 //   loads issued from assembly (tile64_to_lds): known

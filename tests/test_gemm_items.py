@@ -64,24 +64,24 @@ class _Operands:
         self.cgs, self.groups = list(cgs), groups
         ends = self.first[1:] + [K1]
         self.stride = (ends[0] * self.ldb if layout == NN else N * self.ldb) if groups else 0
-        self.box = {"A": (A, self.lda, K1, M) if layout == TN else (A, self.lda, self.cap, K1), "A2": (A2, self.lda2, self.cap, K2 * max(1, len(cgs)))}
+        self.extent = {"A": (A, self.lda, K1, M) if layout == TN else (A, self.lda, self.cap, K1), "A2": (A2, self.lda2, self.cap, K2 * max(1, len(cgs)))}
         for i, (b, e) in enumerate(zip(self.first, ends)):
             r = e - b if layout != NT else N
-            self.box["B%d" % i] = (Bs[i], self.ldb, r * max(1, groups), N if layout != NT else K1)
-        self.box["Bx"] = (B2, self.ldb2, K2 if layout == NN else N, N if layout == NN else K2)
+            self.extent["B%d" % i] = (Bs[i], self.ldb, r * max(1, groups), N if layout != NT else K1)
+        self.extent["Bx"] = (B2, self.ldb2, K2 if layout == NN else N, N if layout == NN else K2)
         self.args = dict(layout=layout, M=M, N=N, K1=K1, K2=K2, A=A, A2=A2, B0=Bs[0], B1=Bs[1], B3=Bs[2], B2=B2, lda=self.lda, ldb=self.ldb, lda2=self.lda2, ldb2=self.ldb2,
                          nn=len(self.first) if layout == NN else 0, nb0=self.first[1] if len(self.first) > 1 else 0, nb1=self.first[2] if len(self.first) > 2 else 0,
                          rows_cap=cap, grp_b_stride=self.stride)
         if cgs:                                                        # column groups: a matrix each
             for i, end in enumerate(cgs):
                 w = end - (cgs[i - 1] if i else 0)
-                self.box["B%d" % i], self.box["Bx%d" % i] = ((10 + i) << 40, self.ldb, w, K1), ((20 + i) << 40, self.ldb2, w, K2)
+                self.extent["B%d" % i], self.extent["Bx%d" % i] = ((10 + i) << 40, self.ldb, w, K1), ((20 + i) << 40, self.ldb2, w, K2)
                 self.args.update({"cg_end%d" % i: end, "cg_B%d" % i: (10 + i) << 40, "cg_C%d" % i: (20 + i) << 40, "cg_a%d" % i: i * K2})
             self.args["ncg"] = len(cgs)
 
     def inside(self, byte, rows, cols, name):
         """[rows x cols] elements from a byte address lie inside the operand; returns row and column of the first"""
-        base, ld, R, C = self.box[name]
+        base, ld, R, C = self.extent[name]
         assert byte >= base and byte % 2 == 0, (name, byte)
         r, c = divmod((int(byte) - base) // 2, ld)
         assert r + rows <= R and c + cols <= C, "%s: rows %d + %d of %d, columns %d + %d of %d" % (name, r, rows, R, c, cols, C)
@@ -137,7 +137,7 @@ def _check(driver, ops, live=0, off=None, **kw):
                 s = min(t, it["lim"])
                 ops.inside(a("an") + s * (128 * ops.lda if ops.layout == TN else 128), *((16, 256) if ops.layout == TN else (64, 64)), "A")
                 b = a("bn") + s * (128 if ops.layout == NT else 128 * ops.ldb)
-                name = [n for n, (base, ld, R, C) in ops.box.items() if n[0] == "B" and base <= b < base + 2 * ld * R]
+                name = [n for n, (base, ld, R, C) in ops.extent.items() if n[0] == "B" and base <= b < base + 2 * ld * R]
                 assert len(name) == 1 and name[0][:2] != "Bx", "a load behind the last step lies outside of every matrix of segment 0: %#x" % b
                 ops.inside(b, *((64, 64) if ops.layout == NT else (16, 256)), name[0])
     assert g["nt"] == (ops.K1 + ops.K2) // 64 or "k_dev" in kw
@@ -225,7 +225,7 @@ class _Bounded(_Workgroup):
 
     def __init__(self, ops):
         super().__init__(_lines(NAMES[ops.layout]), NAMES[ops.layout])
-        self.ops, self.A, self.lda, self.ldb, self.lda2, self.ldb2 = ops, ops.box["A"][0], ops.lda, ops.ldb, ops.lda2, ops.ldb2
+        self.ops, self.A, self.lda, self.ldb, self.lda2, self.ldb2 = ops, ops.extent["A"][0], ops.lda, ops.ldb, ops.lda2, ops.ldb2
         base = _Workgroup(_lines(NAMES[ops.layout]), NAMES[ops.layout])
         for at, (old, new) in enumerate(((base.lda, ops.lda), (base.ldb, ops.ldb), (base.lda2, ops.lda2), (base.ldb2, ops.ldb2))):
             for o in range(2):                                         # lane offsets: rows of the old stride become rows of the new one
@@ -234,7 +234,7 @@ class _Bounded(_Workgroup):
     def load(self, t):
         src = (self.sget(t[1])[:, None] + self.addr[:, int(t[0][1:])]) // 2
         ok = np.zeros(src.shape, bool)
-        for base, ld, R, C in self.ops.box.values():
+        for base, ld, R, C in self.ops.extent.values():
             e = src - base // 2
             ok |= (e >= 0) & (e < ld * R) & (e % ld + 8 <= C)
         assert ok.all(), "a load outside of every operand"
