@@ -190,8 +190,9 @@ int launch_seq_logp(as_ctx* ctx, const float* loss_rows, const int32_t* tgt_idx,
                     const int32_t* kept_of, int n_seg, float* logp, hipStream_t st);
 int launch_dpo_pairs(as_ctx* ctx, const int32_t* pairs, int n_pairs, const float* logp, const float* ref, float beta, int n_seg,
                      const int32_t* kept_of, int n_kept, float* w_kept, float* stats, hipStream_t st);
+// again (may be NULL): the number of rows, or 0 if there are at most `held`
 int launch_dpo_row_weights(as_ctx* ctx, const int32_t* tgt_idx, const int32_t* count, const int32_t* cu, int n_kept,
-                           const float* w_kept, int n, float* row_w, hipStream_t st);
+                           const float* w_kept, int n, float* row_w, int held, int32_t* again, hipStream_t st);
 int launch_fill_float(as_ctx* ctx, float* p, int n, float v, hipStream_t st);
 // head without stored logits: z_lab[row] = hf[row] . W[labels[row]] for rows < *count; then per row the log-sum-exp from the
 // per-block statistics of the GEMM and loss = lse - z_lab
@@ -199,6 +200,8 @@ int launch_label_logit(as_ctx* ctx, const void* hf, const void* W, int d, const 
                        float* zlab, hipStream_t st);
 int launch_ce_finish(as_ctx* ctx, const float* part, int nblk, int row0, int rows_cap, const int32_t* count, const float* zlab,
                      float* lse, float* loss_rows, hipStream_t st);
+int launch_soft_finish(as_ctx* ctx, const float* part, int V, int row0, int rows_cap, const int32_t* count, const float* zlab, const int32_t* labels,
+                       float* inv, float* loss_rows, void* E, hipStream_t st);
 int launch_loss_finalize(as_ctx* ctx, const float* loss_rows, const int32_t* count, float* loss,
                          float* loss_sum, hipStream_t st);
 int launch_splitk_reduce(as_ctx* ctx, const float* partial, int splitk, int64_t mn, int N, float alpha,

@@ -82,8 +82,9 @@ __global__ __launch_bounds__(1024) void dpo_pairs_kernel(const int32_t* __restri
 // row_w[i] = w_kept[segment of target row i]
 __global__ void dpo_row_weights_kernel(const int32_t* __restrict__ tgt_idx, const int32_t* __restrict__ count,
                                        const int32_t* __restrict__ cu, int n_kept, const float* __restrict__ w_kept,
-                                       float* __restrict__ row_w) {
+                                       float* __restrict__ row_w, int held, int32_t* __restrict__ again) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0 && again) *again = *count > held ? *count : 0;
   if (i >= *count) return;
   const int t = tgt_idx[i];
   int lo = 0, hi = n_kept;                          // last k with cu[k] <= t
@@ -116,9 +117,9 @@ int launch_dpo_pairs(as_ctx* ctx, const int32_t* pairs, int n_pairs, const float
 }
 
 int launch_dpo_row_weights(as_ctx* ctx, const int32_t* tgt_idx, const int32_t* count, const int32_t* cu, int n_kept,
-                           const float* w_kept, int n, float* row_w, hipStream_t st) {
+                           const float* w_kept, int n, float* row_w, int held, int32_t* again, hipStream_t st) {
   if (n <= 0) return AS_OK;
-  dpo_row_weights_kernel<<<(n + 255) / 256, 256, 0, st>>>(tgt_idx, count, cu, n_kept, w_kept, row_w);
+  dpo_row_weights_kernel<<<(n + 255) / 256, 256, 0, st>>>(tgt_idx, count, cu, n_kept, w_kept, row_w, held, again);
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }

@@ -876,7 +876,9 @@ __device__ __forceinline__ void rd_rows(const GemmParams& p, const f32x16 (&t)[4
 // bf16 results through the wave's 8 KB of the free half stage, so that a store instruction writes four whole 256-byte row pieces; 16-byte
 // chunk c of row r lies at c ^ (r % 16).  A residual takes the same way in: loaded 16 bytes per lane, parked at the place of the result,
 // picked up by the lane that owns the element and rounded once with the sum.
-// PROB: the values are turned into w_row * (exp(value - lse_row) - [column is the row's label]) before they are rounded.
+// EPI PROB: the values are turned into w_row * (exp(value - lse_row) - [column is the row's label]) before they are rounded.
+// EPI ROWS: a row is multiplied by its row_scale * w_row.
+// EPI SOFT: exp(value) over a whole power of two, see GemmParams; per row and block the exponent and the sum of the unrounded elements go to epi_part.
 template <bool MASK>
 __device__ __forceinline__ void rd_load_residual(const GemmParams& p, u32x4 (&res)[8], const RdOut& o, int i, int lane) {
   const int r4 = lane >> 4, c16 = lane & 15;
@@ -892,7 +894,7 @@ __device__ __forceinline__ void rd_load_residual(const GemmParams& p, u32x4 (&re
 #pragma unroll
   for (int it = 0; it < 8; it++, src += step) res[it] = *reinterpret_cast<const u32x4*>(src + at);
 }
-template <bool MASK, bool PROB, bool RES>
+template <bool MASK, int EPI, bool RES>
 __device__ __forceinline__ void rd_staged(const GemmParams& p, f32x16 (&t)[4], u32x4 (&res)[8], unsigned char* my, const RdOut& o, int i, int lane) {
   const int l15 = lane & 15, q = lane >> 4, r4 = lane >> 4, c16 = lane & 15;
   unsigned char* mine = my + l15 * 256 + (q & 1) * 8;      // this lane's row of 16 and its half of a chunk
@@ -914,12 +916,23 @@ __device__ __forceinline__ void rd_staged(const GemmParams& p, f32x16 (&t)[4], u
   }
 #pragma unroll
   for (int a = 0; a < 2; a++) {
-    float neg_lse2 = 0.f, wrow = 0.f; int clab = -1;
-    if (PROB) {                                            // rows outside the live range compute with the last live row's values and are not written
-      const int rr = o.row0 + 32 * i + 16 * a + l15, r = MASK ? min(max(rr, o.row_lo), o.row_hi - 1) : rr;
-      neg_lse2 = -1.4426950408889634f * p.epi_lse[r];
-      wrow = p.epi_w ? p.epi_w[r] : 1.f / (float)*p.epi_cnt;
-      clab = p.epi_lab[r] - o.col0 - 4 * q;                // position of the label among this lane's columns of the block, if any
+    float neg_lse2 = 0.f, wrow = 0.f, neg_ref = 0.f, sum = 0.f; int clab = -1;
+    // rows outside the live range compute with the last live row's values and are not written
+    const int rr = o.row0 + 32 * i + 16 * a + l15, r = MASK ? min(max(rr, o.row_lo), o.row_hi - 1) : rr;
+    if (EPI == GEMM_EPI_PROB) neg_lse2 = -1.4426950408889634f * p.epi_lse[r];
+    if (EPI == GEMM_EPI_PROB || EPI == GEMM_EPI_ROWS) wrow = p.epi_w ? p.epi_w[r] : 1.f / (float)*p.epi_cnt;
+    if (EPI == GEMM_EPI_ROWS) wrow *= p.row_scale[r];
+    if (EPI == GEMM_EPI_PROB || EPI == GEMM_EPI_SOFT) clab = p.epi_lab[r] - o.col0 - 4 * q;   // position of the label among this lane's columns of the block, if any
+    if (EPI == GEMM_EPI_SOFT) {
+      float m = -INFINITY;
+#pragma unroll
+      for (int j = 0; j < 4; j++)
+#pragma unroll
+        for (int e = 0; e < 8; e++) m = fmaxf(m, t[j][8 * a + e]);
+      m = fmaxf(m, __shfl_xor(m, 32, 64));
+      m = fmaxf(m, __shfl_xor(m, 16, 64));
+      // whole numbers, so that blocks of one row differ by exact powers of two; a label logit that is no number or out of reach counts for nothing
+      neg_ref = -fmaxf(fminf(fmaxf(rintf(p.epi_zlab[r] * 1.4426950408889634f), -4e6f), 4e6f), ceilf(m * 1.4426950408889634f) - 40.f);
     }
 #pragma unroll
     for (int j = 0; j < 4; j++)
@@ -927,7 +940,17 @@ __device__ __forceinline__ void rd_staged(const GemmParams& p, f32x16 (&t)[4], u
       for (int b = 0; b < 2; b++) {
         bf16x4_t* at = reinterpret_cast<bf16x4_t*>(mine + a * 4096 + (ch ^ ((4 * j + 2 * b) * 16)));
         f32x4 v = quad(t[j], a, b, 1.f);
-        if (PROB) {
+        if (EPI == GEMM_EPI_ROWS) {
+#pragma unroll
+          for (int k = 0; k < 4; k++) v[k] *= wrow;
+        }
+        if (EPI == GEMM_EPI_SOFT) {
+#pragma unroll
+          for (int k = 0; k < 4; k++) { v[k] = __builtin_amdgcn_exp2f(fmaf(v[k], 1.4426950408889634f, neg_ref)); sum += v[k]; }
+          const int at_k = clab - (32 * j + 16 * b);       // one block in V / 128 holds a row's label
+          if (at_k >= 0 && at_k < 4 && (!MASK || r == rr)) p.epi_elab[r] = at_k == 0 ? v[0] : at_k == 1 ? v[1] : at_k == 2 ? v[2] : v[3];
+        }
+        if (EPI == GEMM_EPI_PROB) {
 #pragma unroll
           for (int k = 0; k < 4; k++)
             v[k] = wrow * (__builtin_amdgcn_exp2f(fmaf(v[k], 1.4426950408889634f, neg_lse2)) - (clab == 32 * j + 16 * b + k ? 1.f : 0.f));
@@ -940,6 +963,11 @@ __device__ __forceinline__ void rd_staged(const GemmParams& p, f32x16 (&t)[4], u
         for (int k = 0; k < 4; k++) w[k] = (bf16_t)v[k];
         *at = w;
       }
+    if (EPI == GEMM_EPI_SOFT) {
+      sum += __shfl_xor(sum, 32, 64);
+      sum += __shfl_xor(sum, 16, 64);
+      if (lane < 16 && (!MASK || r == rr)) *(reinterpret_cast<float2*>(p.epi_part) + (int64_t)r * (p.N / 128) + o.col0 / 128) = make_float2(-neg_ref, sum);
+    }
   }
   asm volatile("" ::: "memory");                           // LDS operations of a wave complete in order
   u32x4 out[8];
@@ -992,7 +1020,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_rd_kernel(GemmParams p, int m_o
   constexpr int BM = 256, BN = 256;
   constexpr bool NN = LAYOUT == RD_NN, AK = LAYOUT == RD_TN;      // B is [K, N]; A is [K, M] and B [K, N]
   extern __shared__ __align__(16) unsigned char smem[];
-  const RdLaunch g = rd_launch<LIVE, LAYOUT, EPI == GEMM_EPI_NONE>(p, m_off, tiles_m, tiles_n);
+  const RdLaunch g = rd_launch<LIVE, LAYOUT, EPI == GEMM_EPI_NONE || EPI == GEMM_EPI_ROWS>(p, m_off, tiles_m, tiles_n);
   const int items = g.items, first_split = g.first_split, parts = g.parts;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
@@ -1051,26 +1079,30 @@ __global__ __launch_bounds__(256) void gemm_mfma_rd_kernel(GemmParams p, int m_o
       unsigned char* my = smem + ((half + 4) % 5) * 32768 + wave * 8192;
       GemmParams q = p;
       RdOut o = {w.row0 + wm * 128, w.col0 + wn * 128, w.row_lo, w.row_hi};
-      const bool part = EPI == GEMM_EPI_NONE && w.kpart >= 0;
+      const bool part = (EPI == GEMM_EPI_NONE || EPI == GEMM_EPI_ROWS) && w.kpart >= 0;
       if (part) {                                          // raw float sums of this part into the tile's scratch
         q.C = p.tail_part + ((int64_t)(w.pid - first_split) * parts + w.kpart) * (BM * BN); q.ldc = BN; q.c_f32 = 1; q.alpha = 1.f; q.R = nullptr; q.accumulate = 0;
         o = {wm * 128, wn * 128, 0, BM};
       } else if (AK) q.C = row_group_base(p, w.row0);
-      const bool staged = EPI == GEMM_EPI_PROB || (!AK && EPI == GEMM_EPI_NONE && !q.c_f32 && !(q.ldc % 8) && (!q.R || (!(q.ldr % 8) && !((uintptr_t)q.R % 16))));
+      const bool staged = EPI == GEMM_EPI_PROB || EPI == GEMM_EPI_SOFT || (!AK && EPI == GEMM_EPI_NONE && !q.c_f32 && !(q.ldc % 8) && (!q.R || (!(q.ldr % 8) && !((uintptr_t)q.R % 16))));
       constexpr bool MASK = LIVE != 0;
       u32x4 res[8];
-      if (staged && q.R) rd_load_residual<MASK>(q, res, o, 0, lane);
+      if (EPI == GEMM_EPI_NONE && staged && q.R) rd_load_residual<MASK>(q, res, o, 0, lane);
 #pragma unroll
       for (int i = 0; i < 4; i++) {
         f32x16 t[4] = {acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
         int el = lane;                                     // the piece's per-lane addresses are formed here, not kept across the loop
         asm volatile("" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]), "+v"(el));
         if constexpr (EPI == GEMM_EPI_STATS) rd_stats<MASK>(q, t, o, i, el);
-        else if constexpr (EPI == GEMM_EPI_PROB) rd_staged<MASK, true, false>(q, t, res, my, o, i, el);
+        else if constexpr (EPI == GEMM_EPI_PROB) rd_staged<MASK, GEMM_EPI_PROB, false>(q, t, res, my, o, i, el);
+        else if constexpr (EPI == GEMM_EPI_SOFT) rd_staged<MASK, GEMM_EPI_SOFT, false>(q, t, res, my, o, i, el);
+        else if constexpr (EPI == GEMM_EPI_ROWS) {
+          if (part) rd_rows<MASK, true, false>(q, t, o, i, el); else rd_staged<MASK, GEMM_EPI_ROWS, false>(q, t, res, my, o, i, el);
+        }
         else if constexpr (AK) {
           if (q.accumulate) rd_rows<false, true, true>(q, t, o, i, el); else rd_rows<false, true, false>(q, t, o, i, el);
-        } else if (staged && q.R) rd_staged<MASK, false, true>(q, t, res, my, o, i, el);
-        else if (staged) rd_staged<MASK, false, false>(q, t, res, my, o, i, el);
+        } else if (staged && q.R) rd_staged<MASK, GEMM_EPI_NONE, true>(q, t, res, my, o, i, el);
+        else if (staged) rd_staged<MASK, GEMM_EPI_NONE, false>(q, t, res, my, o, i, el);
         else if (q.c_f32 && !q.R && !q.accumulate) rd_rows<MASK, true, false>(q, t, o, i, el);
         else if (q.c_f32) rd_rows<MASK, true, true>(q, t, o, i, el);
         else rd_rows<MASK, false, true>(q, t, o, i, el);
@@ -1145,8 +1177,10 @@ __global__ __launch_bounds__(256) void gemm_tail_fixup_kernel(GemmParams p, int 
     const int64_t row = (int64_t)row0 + r_first + (threadIdx.x >> 6) + 4 * i; const int col = tile_n * BN + c;
     if (row >= row_lo && row < row_hi) {
       f32x4 v = sum[i];
+      float f = p.alpha;
+      if (p.row_scale) f = p.row_scale[row] * (p.epi_w ? p.epi_w[row] : 1.f / (float)*p.epi_cnt);
 #pragma unroll
-      for (int k = 0; k < 4; k++) v[k] *= p.alpha;
+      for (int k = 0; k < 4; k++) v[k] *= f;
       if (p.R) { const bf16x4_t x = *reinterpret_cast<const bf16x4_t*>((const bf16_t*)p.R + row * p.ldr + col);
 #pragma unroll
         for (int k = 0; k < 4; k++) v[k] += (float)x[k]; }
@@ -1281,9 +1315,10 @@ static int launch_256(as_ctx* ctx, const GemmParams& p_in, int m_off, int parts,
     const int tm = p.grp_n > 0 ? (int)cdiv(p.rows_cap, 256) + p.grp_n : (int)cdiv(p.M, 256);
     if (p.epi == GEMM_EPI_STATS) return launch_tiles<1, RD_NT, GEMM_EPI_STATS>(ctx, p, m_off, tm * tn, tm, tn, st);
     if (p.epi == GEMM_EPI_PROB) return launch_tiles<1, RD_NT, GEMM_EPI_PROB>(ctx, p, m_off, tm * tn, tm, tn, st);
+    if (p.epi == GEMM_EPI_SOFT) return launch_tiles<1, RD_NT, GEMM_EPI_SOFT>(ctx, p, m_off, tm * tn, tm, tn, st);
     if (!live_split_ok(p)) p.tail_part = nullptr;
     const int wgs = p.tail_part ? std::max(tm * tn, kCus) : tm * tn;
-    rc = p.nn ? launch_tiles<1, RD_NN>(ctx, p, m_off, wgs, tm, tn, st) : launch_tiles<1, RD_NT>(ctx, p, m_off, wgs, tm, tn, st);
+    rc = p.row_scale ? launch_tiles<1, RD_NN, GEMM_EPI_ROWS>(ctx, p, m_off, wgs, tm, tn, st) : p.nn ? launch_tiles<1, RD_NN>(ctx, p, m_off, wgs, tm, tn, st) : launch_tiles<1, RD_NT>(ctx, p, m_off, wgs, tm, tn, st);
     if (!rc && p.tail_part) { gemm_tail_fixup_kernel<<<dim3(16 * std::min(tm * tn, 128)), 256, 0, st>>>(p, m_off, tm, tn); AS_LAUNCH_CHECK(ctx); }
     return rc;
   }
@@ -1472,6 +1507,10 @@ int launch_gemm_off(as_ctx* ctx, int mode, int variant, const GemmParams& p_in, 
     if (p.epi == GEMM_EPI_STATS && !p.epi_part) return as_fail(ctx, AS_ERR_NULL, "gemm: statistics epilogue without a buffer");
     if (p.epi == GEMM_EPI_PROB && (!p.epi_lse || !p.epi_lab || (!p.epi_w && !p.epi_cnt) || p.c_f32 || p.R || (p.ldc % 8))) return as_fail(ctx, AS_ERR_SHAPE, "gemm: probability epilogue needs lse, labels, a row factor and bf16 output");
   }
+  if (p.epi == GEMM_EPI_SOFT && (!p.epi_part || !p.epi_zlab || !p.epi_elab || !p.epi_lab || p.c_f32 || p.R || (p.ldc % 8) || p.alpha != 1.f))
+    return as_fail(ctx, AS_ERR_SHAPE, "gemm: softmax epilogue needs buffers, label logits and bf16 output");
+  if (p.row_scale && (!p.nn || !p.m_dev || p.grp_off || p.epi != GEMM_EPI_NONE || p.c_f32 || p.R || (p.ldc % 8) || p.alpha != 1.f || (!p.epi_w && !p.epi_cnt)))
+    return as_fail(ctx, AS_ERR_SHAPE, "gemm: row factors need the product of device-counted rows with a [K, N] matrix and bf16 output");
   if (p.ncg > 0) {
     if (p.ncg > 3 || p.grp_off || p.m_dev || p.splitk > 1 || p.cg_end[p.ncg - 1] != p.N) return as_fail(ctx, AS_ERR_SHAPE, "gemm: column groups need plain rows and ends that add up to N");
     // the hand-scheduled kernel and the ring kernels take all groups at once when every group is whole tiles wide

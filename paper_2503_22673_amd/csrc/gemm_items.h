@@ -43,6 +43,11 @@ struct GemmParams {
   //    the sum of exp(value - maximum) go to epi_part[(row * (N / 128) + block) * 2 + {0, 1}];
   //  epi == GEMM_EPI_PROB:  C = w_row * (exp(value - epi_lse[row]) - [column == epi_lab[row]]), w_row = epi_w[row] when
   //    given, else 1 / *epi_cnt: the gradient of the masked loss with respect to the logits, straight from the accumulators.
+  //  epi == GEMM_EPI_SOFT:  C = exp(value) / 2^R, R a whole number per row and 128-column block: the row's label logit epi_zlab in powers of
+  //    two, more only where a value lies 2^40 above it; R and the block's sum go to epi_part as above, the label's own element to
+  //    epi_elab[row] as a float.  Up to whole powers of two and the factor w_row / (sum over the row) this is the gradient, before the sum is known.
+  // row_scale (with epi_w or epi_cnt; the product of device-counted rows with a [K, N] matrix only): row r of the result times
+  //    row_scale[r] * w_row.
   // Split tiles (hand-scheduled kernel, plain rows): with tail_first >= 0 the tiles tail_first .. of the launch are each
   // computed by tail_parts workgroups, one per part of the contraction, as float partials in tail_part
   // [tile - tail_first][part][256 x 256]; a second small launch adds the parts in order and applies the epilogue.
@@ -57,8 +62,9 @@ struct GemmParams {
   // contraction ends with row *k_dev - k_off (rows up to the next multiple of 64 must be zero in both operands).
   int tn; const int* k_dev; int k_off; int nrg; void* rg_C[2]; int rg_row[2];
   int epi; const float* epi_lse; const int32_t* epi_lab; const float* epi_w; const int32_t* epi_cnt; float* epi_part;
+  const float* epi_zlab; float* epi_elab; const float* row_scale;
 };
-enum { GEMM_EPI_NONE = 0, GEMM_EPI_STATS = 1, GEMM_EPI_PROB = 2 };
+enum { GEMM_EPI_NONE = 0, GEMM_EPI_STATS = 1, GEMM_EPI_PROB = 2, GEMM_EPI_SOFT = 3, GEMM_EPI_ROWS = 4 };   // ROWS: what row_scale selects inside the kernel
 
 // ------------------------------------------------------------------ shape rules of the 256 x 256 kernel
 constexpr int kTile = 256, kStep = 64;                   // rows and columns of a tile; contraction of a step
