@@ -234,6 +234,7 @@ struct LoraSlot {       // prepared copies of one adapter (type T)
   void *At = nullptr;   // [din, group_cols] column block of the group transpose
   void *Bs = nullptr;   // [dout, rp]  = scale * B, zero padded
   void *Bst = nullptr;  // [rp, dout]
+  void *frag = nullptr; // gate, up: Bst, down: A, in the operand order of the SwiGLU kernels' products (or NULL)
   int slot = 0;         // position inside its group (qkv / o / gate-up / down)
 };
 
@@ -404,6 +405,7 @@ static void make_plan(const as_ctx* ctx, int64_t rows, int64_t row_len, Bump& w,
                          s.At = P.At_gu[l] ? (char*)P.At_gu[l] + (size_t)s.slot * rp * es : nullptr; }
       else { s.slot = 0; s.A = w.take(rp * s.din * es); s.At = w.take((size_t)s.din * rp * es); }
       s.Bs = w.take((size_t)s.dout * rp * es); s.Bst = w.take(rp * s.dout * es);
+      if ((t == AS_T_GATE || t == AS_T_UP || t == AS_T_DOWN) && swiglu_adapter_ok(c.mode, P.N, c.ffn, c.lora_rank, {})) s.frag = w.take((size_t)c.ffn * 16 * es);
       if (l == 0) {
         int r = c.lora_rank;
         part = std::max(part, (size_t)pick_splitk(c.mode, s.dout, r, P.N) * s.dout * r);
@@ -527,8 +529,8 @@ struct Step {
     const int r = c.lora_rank, rp = P.rp;
     auto launch = [&](const PrepBatch& b) { return launch_lora_prep_batch(ctx, mode, b, st); };
     BatchedLaunches<PrepBatch, kPrepBatch, decltype(launch)> batches(1 << 22, launch);
-    auto add = [&](const float* in, int rows, int cols, int rows_pad, int cols_pad, float scale, void* out, int64_t ldo, void* out_t, int64_t ldo_t) {
-      batches.add(PrepMatrix{in, out, out_t, ldo, ldo_t, rows, cols, rows_pad, cols_pad, scale, 0}, cdiv(rows_pad, 64) * cdiv(cols_pad, 64));
+    auto add = [&](const float* in, int rows, int cols, int rows_pad, int cols_pad, float scale, void* out, int64_t ldo, void* out_t, int64_t ldo_t, void* frag, int rank_rows) {
+      batches.add(PrepMatrix{in, out, out_t, ldo, ldo_t, rows, cols, rows_pad, cols_pad, scale, 0, frag, rank_rows}, cdiv(rows_pad, 64) * cdiv(cols_pad, 64));
     };
     for (int l = 0; l < c.n_layers; l++) {
       const as_layer_lora& Lr = lora->layers[l];
@@ -537,9 +539,9 @@ struct Step {
         if (!sl.on) continue;
         int64_t ld_at = (t <= AS_T_V) ? (int64_t)P.n_qkv * rp : (t == AS_T_GATE || t == AS_T_UP) ? (int64_t)P.n_gu * rp : rp;
         // A [r, din] -> A copy [rp, din] and its transpose block [din, rp] inside a [din, group] matrix
-        add(Lr.a[t], r, sl.din, rp, sl.din, 1.f, sl.A, sl.din, sl.At, ld_at);
+        add(Lr.a[t], r, sl.din, rp, sl.din, 1.f, sl.A, sl.din, sl.At, ld_at, t == AS_T_DOWN ? sl.frag : nullptr, 1);
         // B [dout, r] -> s*B [dout, rp] and transpose [rp, dout]
-        add(Lr.b[t], sl.dout, r, sl.dout, rp, s, sl.Bs, rp, sl.Bst, sl.dout);
+        add(Lr.b[t], sl.dout, r, sl.dout, rp, s, sl.Bs, rp, sl.Bst, sl.dout, t != AS_T_DOWN ? sl.frag : nullptr, 0);
       }
     }
     return batches.finish();
@@ -592,9 +594,10 @@ struct Step {
                 nullptr, 0, off(a.gu, (size_t)i * F), 2 * F);
       if (rc) return rc;
     }
-    if ((rc = launch_swiglu_fwd(ctx, mode, N, F, a.gu, a.m, st))) return rc;
     { LoraSlot& s = slot(l, AS_T_DOWN);
-      if (s.on && (rc = gemm(N, rp, a.m, F, s.A, F, F, nullptr, 0, nullptr, 0, 0, nullptr, 0, a.u_d, rp))) return rc;
+      const bool with_u = s.on && s.frag && swiglu_adapter_ok(mode, N, F, c.lora_rank, {a.gu, a.m});
+      if ((rc = with_u ? launch_swiglu_fwd_adapter(ctx, N, F, a.gu, a.m, s.frag, rp, a.u_d, st) : launch_swiglu_fwd(ctx, mode, N, F, a.gu, a.m, st))) return rc;
+      if (s.on && !with_u && (rc = gemm(N, rp, a.m, F, s.A, F, F, nullptr, 0, nullptr, 0, 0, nullptr, 0, a.u_d, rp))) return rc;
       rows_cap_once = P.cap;
       if ((rc = gemm(N, d, a.m, F, dense(w.wdown, w.adown, d, F), F, F, s.on ? a.u_d : nullptr, rp, s.Bs, rp, s.on ? rp : 0, a.h_mid, d, h_out, d))) return rc; }
     return AS_OK;
@@ -845,13 +848,18 @@ struct Step {
     if (c.n_experts) { if ((rc = backward_moe(l, a))) return rc; }
     else {
     // ---- down projection
+    bool with_du = false;                                  // du of gate and up came with the SwiGLU backward
     { LoraSlot& s = slot(l, AS_T_DOWN);
       if (s.on && (rc = gemm(N, rp, P.dh, d, s.Bst, d, d, nullptr, 0, nullptr, 0, 0, nullptr, 0, P.du_d, rp))) return rc;
       rows_cap_once = P.cap;
       if ((rc = gemm_dx(N, F, P.dh, d, {{w.wdown, w.adown, d}}, s.on ? P.du_d : nullptr, rp, s.A, s.At, rp, s.on ? rp : 0, P.dm, F))) return rc;
       // ---- SwiGLU (in recompute mode 2 it also rewrites the forward product, which the gradients below need)
       const bool rewrite_m = c.recompute == 2 && l != c.n_layers - 1 && (full || s.on);
-      if ((rc = launch_swiglu_bwd(ctx, mode, N, F, P.dm, a.gu, P.dgu, rewrite_m ? a.m : nullptr, st))) return rc;
+      LoraSlot &sg = slot(l, AS_T_GATE), &su = slot(l, AS_T_UP);
+      with_du = sg.on && su.on && sg.frag && su.frag && swiglu_adapter_ok(mode, N, F, c.lora_rank, {P.dm, a.gu, P.dgu, a.m});
+      if (with_du) rc = launch_swiglu_bwd_adapter(ctx, N, F, P.dm, a.gu, P.dgu, rewrite_m ? a.m : nullptr, sg.frag, su.frag, rp, P.du_gu, st);
+      else rc = launch_swiglu_bwd(ctx, mode, N, F, P.dm, a.gu, P.dgu, rewrite_m ? a.m : nullptr, st);
+      if (rc) return rc;
       if (s.on && !tn_path()) {
         if ((rc = transpose_tok(d, P.dh, d, P.dyT))) return rc;
         if ((rc = transpose_tok(F, a.m, F, P.xT))) return rc;
@@ -865,7 +873,7 @@ struct Step {
     { const int ldg = P.n_gu * rp;
       for (int i = 0; i < 2; i++) {
         LoraSlot& s = slot(l, AS_T_GATE + i);
-        if (s.on && (rc = gemm(N, rp, off(P.dgu, (size_t)i * F), 2 * F, s.Bst, F, F, nullptr, 0, nullptr, 0, 0, nullptr, 0,
+        if (s.on && !with_du && (rc = gemm(N, rp, off(P.dgu, (size_t)i * F), 2 * F, s.Bst, F, F, nullptr, 0, nullptr, 0, 0, nullptr, 0,
                                off(P.du_gu, (size_t)s.slot * rp), ldg))) return rc;
       }
       rows_cap_once = P.cap;

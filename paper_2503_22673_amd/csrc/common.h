@@ -9,6 +9,8 @@
 #include <vector>
 #include <algorithm>
 #include <atomic>
+#include <initializer_list>
+#include <type_traits>
 #include "actionstudio.h"
 #include "gemm_items.h"
 
@@ -162,6 +164,11 @@ int launch_moe_dlogit(as_ctx* ctx, int mode, const void* dy, const void* y, cons
                       int n, int d, int Epad, void* dlogit, hipStream_t st);
 int launch_swiglu_fwd(as_ctx* ctx, int mode, int64_t n, int F, const void* gu, void* m, hipStream_t st);
 int launch_swiglu_bwd(as_ctx* ctx, int mode, int64_t n, int F, const void* dm, const void* gu, void* dgu, void* m_out, hipStream_t st);
+// the same with the adapter products of what they write, rank up to 16, from 4096 tokens on: u [n, rp] = m A^T; du [n, 2 rp] = dgate Bg | dup Bu; the adapters as PrepMatrix::frag
+bool swiglu_adapter_ok(int mode, int n, int F, int r, std::initializer_list<const void*> ptrs);
+int launch_swiglu_fwd_adapter(as_ctx* ctx, int n, int F, const void* gu, void* m, const void* fragA, int rp, void* u, hipStream_t st);
+int launch_swiglu_bwd_adapter(as_ctx* ctx, int n, int F, const void* dm, const void* gu, void* dgu, void* m_out, const void* fragBg, const void* fragBu, int rp, void* du,
+                              hipStream_t st);
 // out[c, r] = in[r, c] for r < rows_pad, reading zero for r >= rows (and, with rows_dev, for rows at
 // or past *rows_dev - row_off)
 int launch_transpose(as_ctx* ctx, int mode, int rows, int rows_pad, int cols, const void* in, int64_t ldi, void* out,
@@ -172,9 +179,12 @@ int launch_transpose_qs(as_ctx* ctx, int mode, int rows, int rows_pad, int cols,
 int launch_transpose_pair(as_ctx* ctx, int mode, int rows, int rows_pad, int cols, const void* in, const void* in2, int64_t ldi,
                           void* out, void* out2, int64_t ldo, hipStream_t st);
 // out[rows_pad, cols_pad] (type T, row stride ldo) = scale * in[rows, cols] (float), zero in the
-// padding; out_t (row stride ldo_t) receives the transpose.
-struct PrepMatrix { const float* in; void *out, *out_t; int64_t ldo, ldo_t; int rows, cols, rows_pad, cols_pad; float scale; int first_tile; };
-constexpr int kPrepBatch = 48;                             // a batch is a kernel argument (3.1 KB)
+// padding; out_t (row stride ldo_t) receives the transpose.  frag (may be NULL; bf16, both padded sizes multiples of 64): the
+// first 16 of the rank, which is the row of `in` (frag_rank_rows) or its column, as operands of v_mfma_f32_16x16x32_bf16, 512 elements for every
+// 32 of the contraction.
+struct PrepMatrix { const float* in; void *out, *out_t; int64_t ldo, ldo_t; int rows, cols, rows_pad, cols_pad; float scale; int first_tile; void* frag; int frag_rank_rows; };
+constexpr int kPrepBatch = 48;                             // a batch is a kernel argument (3.8 KB)
+
 struct PrepBatch { PrepMatrix m[kPrepBatch]; int n, n_tiles; };
 int launch_lora_prep_batch(as_ctx* ctx, int mode, const PrepBatch& b, hipStream_t st);
 int launch_fill_zero(as_ctx* ctx, void* p, size_t bytes, hipStream_t st);

@@ -520,7 +520,15 @@ int launch_rmsnorm_bwd_gain(as_ctx* ctx, int mode, int n, int d, const void* dy,
 }
 
 // ------------------------------------------------------------------ SwiGLU
-// gu holds [gate | up] side by side, row length 2F.
+// gu holds [gate | up] side by side, row length 2F.  In bf16 the reciprocal is the instruction's (one unit of a float's last place off at
+// most, results are rounded to bf16), an exact division costs ten more.
+template <typename T> __device__ __forceinline__ float sigmoid(float a) {
+  const float e = 1.f + __expf(-a);
+  return sizeof(T) == 2 ? __builtin_amdgcn_rcpf(e) : 1.f / e;
+}
+template <typename T> __device__ __forceinline__ float silu_times(float a, float b) {
+  return sizeof(T) == 2 ? a * sigmoid<T>(a) * b : a / (1.f + __expf(-a)) * b;
+}
 template <typename T>
 __global__ void swiglu_fwd_kernel(int64_t n, int F, const T* __restrict__ gu, T* __restrict__ m, int vec) {
   constexpr int VN = Vec<T>::N;
@@ -532,11 +540,11 @@ __global__ void swiglu_fwd_kernel(int64_t n, int F, const T* __restrict__ gu, T*
   if (vec) {
     float a[VN], b[VN], o[VN]; load_vec<T>(gr + j, a); load_vec<T>(gr + F + j, b);
 #pragma unroll
-    for (int i = 0; i < VN; i++) o[i] = a[i] / (1.f + __expf(-a[i])) * b[i];
+    for (int i = 0; i < VN; i++) o[i] = silu_times<T>(a[i], b[i]);
     store_vec<T>(m + t * F + j, o);
   } else {
     float a = to_f<T>(gr[j]), b = to_f<T>(gr[F + j]);
-    m[t * F + j] = from_f<T>(a / (1.f + __expf(-a)) * b);
+    m[t * F + j] = from_f<T>(silu_times<T>(a, b));
   }
 }
 
@@ -555,7 +563,7 @@ __global__ void swiglu_bwd_kernel(int64_t n, int F, const T* __restrict__ dm, co
     load_vec<T>(gr + j, a); load_vec<T>(gr + F + j, b); load_vec<T>(dm + t * F + j, c);
 #pragma unroll
     for (int i = 0; i < VN; i++) {
-      float sg = 1.f / (1.f + __expf(-a[i]));
+      const float sg = sigmoid<T>(a[i]);
       og[i] = c[i] * b[i] * sg * (1.f + a[i] * (1.f - sg));
       ou[i] = c[i] * a[i] * sg;
     }
@@ -563,15 +571,15 @@ __global__ void swiglu_bwd_kernel(int64_t n, int F, const T* __restrict__ dm, co
     if (m_out) {                                       // the forward product again, in the forward kernel's arithmetic
       float o[VN];
 #pragma unroll
-      for (int i = 0; i < VN; i++) o[i] = a[i] / (1.f + __expf(-a[i])) * b[i];
+      for (int i = 0; i < VN; i++) o[i] = silu_times<T>(a[i], b[i]);
       store_vec<T>(m_out + t * F + j, o);
     }
   } else {
     float a = to_f<T>(gr[j]), b = to_f<T>(gr[F + j]), c = to_f<T>(dm[t * F + j]);
-    float sg = 1.f / (1.f + __expf(-a));
+    const float sg = sigmoid<T>(a);
     dr[j] = from_f<T>(c * b * sg * (1.f + a * (1.f - sg)));
     dr[F + j] = from_f<T>(c * a * sg);
-    if (m_out) m_out[t * F + j] = from_f<T>(a / (1.f + __expf(-a)) * b);
+    if (m_out) m_out[t * F + j] = from_f<T>(silu_times<T>(a, b));
   }
 }
 
@@ -595,6 +603,123 @@ int launch_swiglu_bwd(as_ctx* ctx, int mode, int64_t n, int F, const void* dm, c
   prof_end(ctx, st);
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
+}
+
+// SwiGLU and the adapter products that read its result, in one pass (bf16, rank up to 16): u = m A^T forward (down's adapter), du = dgate Bg
+// and dup Bu backward (gate's and up's).  A kernel of their own reads m, or dgate and dup, a second time.  16 tokens per workgroup, its eight
+// waves take every eighth 64 columns, the next step's operands on their way.  Loads and stores are eight lanes to 128 bytes of a row
+// (neighbouring lanes in different rows, the product's own operand layout, cost a clock a lane: 590 us where this takes 455); the
+// rounded result passes through 2 KB of the wave's LDS into that layout, the adapter comes from L2 in it (PrepMatrix::frag), the waves' sums meet at the end.
+// 24,710 tokens x 8192: forward 259 us, 307 as two kernels (5.2 TB/s of what has to move), backward 455 and 539 (4.9).  Of rank 64, on 14336
+// columns, it takes 270 + 524 us where the kernels one after the other take 262 + 515 (the adapter's rows are then four times the traffic from L2).
+// Under one workgroup per CU (sixteen waves each: 626 tokens, a step of two layers 1.420 ms, 1.412 with two kernels) the rows stay with two kernels.
+struct SwigluAdapter { const bf16_t* frag[2]; int rp; bf16_t* u; };        // frag: A of down forward; B of gate, of up backward
+constexpr int kSwigluRank = 16, kSwigluTokens = 16 * 256;
+template <bool BWD>
+__global__ __launch_bounds__(512) void swiglu_adapter_kernel(int n, int F, const bf16_t* __restrict__ dm, const bf16_t* __restrict__ gu, bf16_t* __restrict__ dgu,
+                                                                 bf16_t* __restrict__ m, const SwigluAdapter ad) {
+  constexpr int MT = BWD ? 2 : 1, NW = 8;                  // products, waves
+  __shared__ __align__(16) unsigned char smem[NW * MT * 2048];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, q = lane >> 4, r8 = lane >> 3, ch = lane & 7;
+  const int row0 = blockIdx.x * 16;
+  unsigned char* my = smem + wave * (MT * 2048);
+  f32x4 acc[MT] = {};
+  struct Operands { bf16x8 g[2], x[2], z[2]; };
+  auto load = [&](int c, Operands& v) {
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+      const int64_t row = min(row0 + 8 * h + r8, n - 1);
+      const bf16_t* gr = gu + row * 2 * F + c + ch * 8;
+      v.g[h] = *reinterpret_cast<const bf16x8*>(gr); v.x[h] = *reinterpret_cast<const bf16x8*>(gr + F);
+      if (BWD) v.z[h] = *reinterpret_cast<const bf16x8*>(dm + row * F + c + ch * 8);
+    }
+  };
+  auto step = [&](int c, const Operands& v) {
+    bf16x8 w[MT][2];
+#pragma unroll
+    for (int p = 0; p < MT; p++)
+#pragma unroll
+      for (int k = 0; k < 2; k++) w[p][k] = *reinterpret_cast<const bf16x8*>(ad.frag[p] + (int64_t)(c / 32 + k) * 512 + lane * 8);
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+      const int row = row0 + 8 * h + r8;
+      const bool mine = row < n;
+      bf16x8 y[MT], mo;
+#pragma unroll
+      for (int i = 0; i < 8; i++) {
+        const float a = (float)v.g[h][i], b = (float)v.x[h][i], sg = sigmoid<bf16_t>(a);
+        if (BWD) {
+          const float d = (float)v.z[h][i];
+          y[0][i] = (bf16_t)(d * b * sg * (1.f + a * (1.f - sg)));
+          y[MT - 1][i] = (bf16_t)(d * a * sg);
+          if (m) mo[i] = (bf16_t)(a * sg * b);             // the forward product again, in the forward kernel's arithmetic
+        } else y[0][i] = (bf16_t)(a * sg * b);
+      }
+      if (mine) {
+        if (BWD) {
+          bf16_t* o = dgu + (int64_t)row * 2 * F + c + ch * 8;
+          *reinterpret_cast<bf16x8*>(o) = y[0]; *reinterpret_cast<bf16x8*>(o + F) = y[MT - 1];
+          if (m) *reinterpret_cast<bf16x8*>(m + (int64_t)row * F + c + ch * 8) = mo;
+        } else *reinterpret_cast<bf16x8*>(m + (int64_t)row * F + c + ch * 8) = y[0];
+      }
+#pragma unroll
+      for (int p = 0; p < MT; p++) *reinterpret_cast<bf16x8*>(my + p * 2048 + (h * 8 + r8) * 128 + ((ch ^ r8) * 16)) = y[p];
+    }
+    asm volatile("" ::: "memory");                         // LDS operations of a wave complete in order
+#pragma unroll
+    for (int p = 0; p < MT; p++)
+#pragma unroll
+      for (int k = 0; k < 2; k++) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(my + p * 2048 + l15 * 128 + (((k * 4 + q) ^ (l15 & 7)) * 16));
+        acc[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, w[p][k], acc[p], 0, 0, 0);
+      }
+    asm volatile("" ::: "memory");
+  };
+  const int steps = F / 64;
+  int s = wave;
+  Operands v0, v1;
+  if (s < steps) load(s * 64, v0);
+  for (; s + NW < steps; s += 2 * NW) {
+    load((s + NW) * 64, v1);
+    step(s * 64, v0);
+    if (s + 2 * NW < steps) load((s + 2 * NW) * 64, v0);
+    step((s + NW) * 64, v1);
+  }
+  if (s < steps) step(s * 64, v0);
+  // the waves' sums in wave order to u [rows, MT rp]; columns past 16 are zero
+  f32x4 (*red)[MT][64] = reinterpret_cast<f32x4 (*)[MT][64]>(smem);
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < MT; p++) red[wave][p][lane] = acc[p];
+  __syncthreads();
+  for (int o = threadIdx.x; o < 16 * MT * ad.rp; o += 64 * NW) {           // token t is element t % 4 of lane 16 (t / 4) + rank index
+    const int t = o / (MT * ad.rp), p = o / ad.rp % MT, j = o % ad.rp;
+    float v = 0.f;
+    if (j < 16)
+      for (int w = 0; w < NW; w++) v += red[w][p][(t >> 2) * 16 + j][t & 3];
+    if (row0 + t < n) ad.u[(int64_t)(row0 + t) * (MT * ad.rp) + p * ad.rp + j] = (bf16_t)v;
+  }
+}
+bool swiglu_adapter_ok(int mode, int n, int F, int r, std::initializer_list<const void*> ptrs) {
+  uintptr_t x = 0;
+  for (const void* p : ptrs) x |= (uintptr_t)p;
+  return mode == AS_BF16 && n >= kSwigluTokens && F % 64 == 0 && r <= kSwigluRank && x % 16 == 0;
+}
+template <bool BWD>
+static int launch_swiglu_adapter(as_ctx* ctx, int n, int F, const void* dm, const void* gu, void* dgu, void* m, const SwigluAdapter& ad, hipStream_t st) {
+  if (n <= 0) return AS_OK;
+  prof_begin(ctx, st, AS_K_SWIGLU, 0.0);
+  swiglu_adapter_kernel<BWD><<<(unsigned)cdiv(n, 16), 512, 0, st>>>(n, F, (const bf16_t*)dm, (const bf16_t*)gu, (bf16_t*)dgu, (bf16_t*)m, ad);
+  prof_end(ctx, st);
+  AS_LAUNCH_CHECK(ctx);
+  return AS_OK;
+}
+int launch_swiglu_fwd_adapter(as_ctx* ctx, int n, int F, const void* gu, void* m, const void* fragA, int rp, void* u, hipStream_t st) {
+  return launch_swiglu_adapter<false>(ctx, n, F, nullptr, gu, nullptr, m, SwigluAdapter{{(const bf16_t*)fragA, nullptr}, rp, (bf16_t*)u}, st);
+}
+int launch_swiglu_bwd_adapter(as_ctx* ctx, int n, int F, const void* dm, const void* gu, void* dgu, void* m_out, const void* fragBg, const void* fragBu, int rp, void* du,
+                              hipStream_t st) {
+  return launch_swiglu_adapter<true>(ctx, n, F, dm, gu, dgu, m_out, SwigluAdapter{{(const bf16_t*)fragBg, (const bf16_t*)fragBu}, rp, (bf16_t*)du}, st);
 }
 
 // --------------------------------------------------------------- transpose
@@ -750,6 +875,13 @@ __global__ __launch_bounds__(256) void lora_prep_kernel(const PrepBatch b) {
   for (int i = 0; i < 16; i++) {
     const int c = c0 + ty + 4 * i, r = r0 + tx;
     if (r < m.rows_pad && c < m.cols_pad) out_t[(int64_t)c * m.ldo_t + r] = from_f<T>(tile[tx][ty + 4 * i]);
+  }
+  const bool by_row = m.frag_rank_rows;
+  if (m.frag && (by_row ? r0 : c0) == 0 && threadIdx.x < 128) {            // whole 64 x 64 tiles: two 32-wide chunks of the contraction
+    const int lane = threadIdx.x & 63, kc = threadIdx.x >> 6, j = lane & 15, k = kc * 32 + (lane >> 4) * 8;
+    T* o = (T*)m.frag + (int64_t)((by_row ? c0 : r0) / 32 + kc) * 512 + lane * 8;
+#pragma unroll
+    for (int x = 0; x < 8; x++) o[x] = from_f<T>(by_row ? tile[j][k + x] : tile[k + x][j]);
   }
 }
 
