@@ -701,12 +701,16 @@ struct Step {
     if ((rc = gemm_experts_dx(a.eoff, F, P.xbp, {{w.wdown, nullptr, d}}, P.dm))) return rc;
     if ((rc = launch_swiglu_bwd(ctx, mode, 2 * N, F, P.dm, a.gu, P.dgu, nullptr, st))) return rc;
     if ((rc = gemm_experts_dx(a.eoff, d, P.dgu, {{w.wgate, nullptr, F}, {w.wup, nullptr, F}}, P.xbp))) return rc;   // grouped gradient of the expert inputs
-    if ((rc = launch_moe_combine(ctx, mode, nullptr, P.xbp, a.pos, nullptr, N, d, P.da, st))) return rc;  // back to token order
-    // router: db = (expert part) + dlogit Wr + du_r A
+    // back to token order, and the router: db = (expert part) + dlogit Wr + du_r A
     LoraSlot& s = slot(l, AS_T_ROUTER);
-    if ((rc = transpose(E, d, w.wrouter, d, P.wrT, E))) return rc;                                        // [d, E]
     if (s.on && (rc = gemm(N, rp, P.dlogit, E, s.Bst, E, E, nullptr, 0, nullptr, 0, 0, nullptr, 0, P.du_r, rp))) return rc;
-    if ((rc = gemm(N, d, P.dlogit, E, P.wrT, E, E, s.on ? P.du_r : nullptr, rp, s.At, rp, s.on ? rp : 0, P.da, d, P.db, d))) return rc;
+    if (moe_combine_router_ok(mode, d, s.on ? c.lora_rank : 0, P.xbp, w.wrouter, s.A, P.db)) {
+      if ((rc = launch_moe_combine_router(ctx, mode, P.xbp, a.pos, a.sel, P.dlogit, E, w.wrouter, P.du_r, rp, s.A, s.on ? c.lora_rank : 0, N, d, P.db, st))) return rc;
+    } else {
+      if ((rc = launch_moe_combine(ctx, mode, nullptr, P.xbp, a.pos, nullptr, N, d, P.da, st))) return rc;
+      if ((rc = transpose(E, d, w.wrouter, d, P.wrT, E))) return rc;                                      // [d, E]
+      if ((rc = gemm(N, d, P.dlogit, E, P.wrT, E, E, s.on ? P.du_r : nullptr, rp, s.At, rp, s.on ? rp : 0, P.da, d, P.db, d))) return rc;
+    }
     if (s.on) {
       if (!tn_path()) {
         if ((rc = transpose_tok(E, P.dlogit, E, P.dyT))) return rc;

@@ -69,6 +69,29 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// 16 bytes of a row at a time
+template <typename T> struct Vec;
+template <> struct Vec<float> { static constexpr int N = 4; typedef f32x4 type; };
+template <> struct Vec<bf16_t> { static constexpr int N = 8; typedef bf16x8 type; };
+
+template <typename T> __device__ __forceinline__ void load_vec(const T* p, float* out) {
+  typename Vec<T>::type v = *reinterpret_cast<const typename Vec<T>::type*>(p);
+#pragma unroll
+  for (int i = 0; i < Vec<T>::N; i++) out[i] = to_f<T>(v[i]);
+}
+template <typename T> __device__ __forceinline__ void store_vec(T* p, const float* in) {
+  typename Vec<T>::type v;
+#pragma unroll
+  for (int i = 0; i < Vec<T>::N; i++) v[i] = from_f<T>(in[i]);
+  *reinterpret_cast<typename Vec<T>::type*>(p) = v;
+}
+template <typename T> static bool vec_ok(const void* p, int64_t ld) {
+  return ((uintptr_t)p % 16 == 0) && (ld % Vec<T>::N == 0);
+}
+
+#define DISPATCH_T(mode, ...) do { if ((mode) == AS_FP32) { typedef float T; __VA_ARGS__; } \
+  else { typedef bf16_t T; __VA_ARGS__; } } while (0)
+
 // ---- GEMM (gemm.hip) ------------------------------------------------------
 // GemmParams, what one product is, lies in gemm_items.h
 // the hand-scheduled kernel would take this product (whole 256 x 256 tiles, K in 64-wide steps, alignment)
@@ -160,6 +183,11 @@ int launch_moe_permute(as_ctx* ctx, const int32_t* sel, int n, int E, int32_t* e
 int launch_moe_gather(as_ctx* ctx, int mode, const void* src, const int32_t* perm, const float* w, int rows, int d, void* out, hipStream_t st);
 int launch_moe_combine(as_ctx* ctx, int mode, const void* res, const void* y, const int32_t* pos, const float* w, int n, int d,
                        void* out, hipStream_t st);
+// out[t] = y[pos[2t]] + y[pos[2t+1]] + dlogit[t] Wr + du[t] A: the gradient of a sparse layer's input from its experts' and its router's (adapter of
+// rank r, rows of du rp apart; r = 0: none), where moe_combine_router_ok
+bool moe_combine_router_ok(int mode, int d, int r, const void* y, const void* Wr, const void* A, const void* out);
+int launch_moe_combine_router(as_ctx* ctx, int mode, const void* y, const int32_t* pos, const int32_t* sel, const void* dlogit, int E, const void* Wr,
+                              const void* du, int rp, const void* A, int r, int n, int d, void* out, hipStream_t st);
 int launch_moe_dlogit(as_ctx* ctx, int mode, const void* dy, const void* y, const int32_t* pos, const int32_t* sel, const float* w,
                       int n, int d, int Epad, void* dlogit, hipStream_t st);
 int launch_swiglu_fwd(as_ctx* ctx, int mode, int64_t n, int F, const void* gu, void* m, hipStream_t st);

@@ -5,28 +5,6 @@
 // needed, so reductions are shuffles only; rows are read with 16-byte loads.
 #include "common.h"
 
-#define DISPATCH_T(mode, ...) do { if ((mode) == AS_FP32) { typedef float T; __VA_ARGS__; } \
-  else { typedef bf16_t T; __VA_ARGS__; } } while (0)
-
-template <typename T> struct Vec;
-template <> struct Vec<float> { static constexpr int N = 4; typedef f32x4 type; };
-template <> struct Vec<bf16_t> { static constexpr int N = 8; typedef bf16x8 type; };
-
-template <typename T> __device__ __forceinline__ void load_vec(const T* p, float* out) {
-  typename Vec<T>::type v = *reinterpret_cast<const typename Vec<T>::type*>(p);
-#pragma unroll
-  for (int i = 0; i < Vec<T>::N; i++) out[i] = to_f<T>(v[i]);
-}
-template <typename T> __device__ __forceinline__ void store_vec(T* p, const float* in) {
-  typename Vec<T>::type v;
-#pragma unroll
-  for (int i = 0; i < Vec<T>::N; i++) v[i] = from_f<T>(in[i]);
-  *reinterpret_cast<typename Vec<T>::type*>(p) = v;
-}
-template <typename T> static bool vec_ok(const void* p, int64_t ld) {
-  return ((uintptr_t)p % 16 == 0) && (ld % Vec<T>::N == 0);
-}
-
 // ------------------------------------------------------------------ pack
 // The packed stream lies in pinned host memory, put together there: one pass over the bus.  Four tokens a thread, so that a wave asks
 // for a kilobyte of tokens at a time and the whole stream is under way at once.

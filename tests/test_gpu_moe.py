@@ -135,3 +135,20 @@ def test_moe_expert_products_whose_last_round_is_split(row_len):
         for k in ("a", "b"):
             err = ((got["grads"][0][t][k].double() - g[k]).norm() / g[k].norm()).item()
             assert err <= 0.03, (t, k, err)                # the step's tolerance on its gradients
+
+
+@pytest.mark.parametrize("d, rank, targets, bf16", [
+    (64, 16, ("q", "router"), False), (64, 16, ("q", "router"), True),       # the highest rank that the token-order sum takes in
+    (2056, 5, ("q", "router"), False), (2056, 5, ("q", "router"), True),     # several column blocks, the last of few lanes
+    (64, 17, ("q", "router"), False), (64, 17, ("q", "router"), True),       # past it: the router's part as a product
+    (64, 4, ("q",), False), (64, 4, ("q",), True),                           # no router adapter
+    (66, 4, ("q", "router"), False),                                         # rows that are no whole 16-byte pieces
+])
+def test_moe_router_gradient_into_the_input(d, rank, targets, bf16):
+    """Whatever reaches a sparse layer's input, through experts and router, is in the first layer's adapter gradients."""
+    sh = synth.CONFIGS[1].replace(**dict(MOE, d_model=d, lora_rank=rank, lora_alpha=2.0 * rank, lora_targets=targets))
+    trajs = random_trajs(7, 5, sh.vocab, turn_lo=8, turn_hi=30, turns=(2, 5))
+    params, lora = structured_router_params(sh, 7), synth.lora_weights(sh, 7)
+    if d > 1000:
+        params["embed"] *= 8 * d ** 0.5          # else the attention's output, and not the token, decides the routing at this width
+    _compare(sh, params, lora, trajs, 1, 333, bf16, 0)
