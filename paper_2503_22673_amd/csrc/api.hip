@@ -568,7 +568,7 @@ struct Step {
                 nullptr, 0, off(a.qkv, coff[i]), QKV);
       if (rc) return rc;
     }
-    if ((rc = launch_rope(ctx, mode, N, c.n_q_heads + c.n_kv_heads, c.head_dim, a.qkv, QKV, P.seg_start, P.rope_cos, P.rope_sin, 0, st))) return rc;
+    if ((rc = launch_rope(ctx, mode, N, c.n_q_heads + c.n_kv_heads, c.head_dim, a.qkv, QKV, P.seg_start, P.rope_cos, P.rope_sin, st))) return rc;
     AttnParams ap; memset(&ap, 0, sizeof ap);
     ap.n = N; ap.Hq = c.n_q_heads; ap.Hkv = c.n_kv_heads; ap.dh = c.head_dim; ap.seg_start = P.seg_start; ap.seg_end = P.seg_end;
     ap.q = a.qkv; ap.k = off(a.qkv, D); ap.v = off(a.qkv, D + Dkv); ap.ldq = QKV; ap.ldkv = QKV; ap.o = a.o; ap.lse = a.lse; ap.max_seg = max_seg; ap.t_scratch = P.attT;
@@ -916,11 +916,8 @@ struct Step {
       ap.q = a.qkv; ap.k = off(a.qkv, D); ap.v = off(a.qkv, D + Dkv); ap.ldq = QKV; ap.ldkv = QKV; ap.o = a.o; ap.lse = a.lse;
       ap.d_o = P.d_o; ap.dq = P.dqkv; ap.dk = off(P.dqkv, D); ap.dv = off(P.dqkv, D + Dkv); ap.delta = P.delta; ap.max_seg = max_seg; ap.t_scratch = P.attT;
       ap.order_q = P.order_q; ap.order_k = P.order_k;
-      // the MFMA kernels rotate dq and dk back themselves (one rounding, no extra pass); else a pass of its own does
-      const bool fused_rope = attention_bwd_is_mfma(mode, av, ap);
-      if (fused_rope) { ap.rope_cos = P.rope_cos; ap.rope_sin = P.rope_sin; }
-      if ((rc = launch_attention_bwd(ctx, mode, av, ap, st))) return rc;
-      if (!fused_rope && (rc = launch_rope(ctx, mode, N, c.n_q_heads + c.n_kv_heads, c.head_dim, P.dqkv, QKV, P.seg_start, P.rope_cos, P.rope_sin, 1, st))) return rc; }
+      ap.rope_cos = P.rope_cos; ap.rope_sin = P.rope_sin;   // the kernels rotate dq and dk back themselves (one rounding, no extra pass)
+      if ((rc = launch_attention_bwd(ctx, mode, av, ap, st))) return rc; }
     // ---- q / k / v projections
     { const int ldu = P.n_qkv * rp;
       const int nout[3] = {D, Dkv, Dkv}; const int coff[3] = {0, D, D + Dkv};

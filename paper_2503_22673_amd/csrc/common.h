@@ -137,12 +137,10 @@ struct AttnParams {
   // optional launch orders (device arrays, longest workgroups first): order_q[i] = query tile of workgroup i
   // (tiles of attention_query_tile() tokens), order_k[i] = key block (256 keys) of workgroup i in the dK / dV launches
   const int32_t* order_q; const int32_t* order_k;
-  // backward, MFMA kernels only: when set, dq and dk leave the kernels already rotated back (the inverse of the rotary
+  // backward: when set, dq and dk leave the kernels already rotated back (the inverse of the rotary
   // embedding applied to q and k before attention): tables [position][dh / 2] of cos and sin, position = t - seg_start[t]
   const float* rope_cos; const float* rope_sin;
 };
-// the MFMA backward kernels will take this call (then the rotation above is available)
-bool attention_bwd_is_mfma(int mode, int variant, const AttnParams& p);
 int launch_attention_fwd(as_ctx* ctx, int mode, int variant, const AttnParams& p, hipStream_t st);
 int attention_query_tile(int n_q_heads, int n_kv_heads);   // tokens per workgroup of the forward and dQ MFMA kernels
 int launch_attention_bwd(as_ctx* ctx, int mode, int variant, const AttnParams& p, hipStream_t st);
@@ -166,7 +164,7 @@ int launch_rmsnorm_bwd(as_ctx* ctx, int mode, int n, int d, const void* dy, cons
 int launch_rmsnorm_bwd_gain(as_ctx* ctx, int mode, int n, int d, const void* dy, const int32_t* src_pos, const void* x, const void* g,
                             const float* rstd, const void* add, void* dx, float* partial, int n_part, float* dg, hipStream_t st);
 int launch_rope(as_ctx* ctx, int mode, int n, int n_heads, int dh, void* x, int64_t ldx,
-                const int32_t* seg_start, const float* cosb, const float* sinb, int inverse, hipStream_t st);
+                const int32_t* seg_start, const float* cosb, const float* sinb, hipStream_t st);
 // NF4 block quantisation (quant.hip)
 int launch_nf4_quantize(as_ctx* ctx, int mode, const void* w, int64_t numel, uint8_t* codes, float* absmax, hipStream_t st);
 int launch_nf4_dequantize(as_ctx* ctx, int mode, const uint8_t* codes, const float* absmax, int64_t numel, void* out, hipStream_t st);

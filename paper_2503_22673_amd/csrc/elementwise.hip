@@ -102,7 +102,7 @@ int launch_rope_table(as_ctx* ctx, int max_pos, int dh, float base, float* cosb,
 template <typename T>
 __global__ void rope_kernel(int n, int n_heads, int dh, T* __restrict__ x, int64_t ldx,
                             const int32_t* __restrict__ seg_start, const float* __restrict__ cosb,
-                            const float* __restrict__ sinb, float sign) {
+                            const float* __restrict__ sinb) {
   int half = dh >> 1;
   int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int64_t tot = (int64_t)n * n_heads * half;
@@ -112,7 +112,7 @@ __global__ void rope_kernel(int n, int n_heads, int dh, T* __restrict__ x, int64
   int hd = r % n_heads;
   int t = r / n_heads;
   int p = t - seg_start[t];
-  float c = cosb[(int64_t)p * half + i], s = sign * sinb[(int64_t)p * half + i];
+  float c = cosb[(int64_t)p * half + i], s = sinb[(int64_t)p * half + i];
   T* row = x + (int64_t)t * ldx + (int64_t)hd * dh;
   float x1 = to_f<T>(row[i]), x2 = to_f<T>(row[i + half]);
   row[i] = from_f<T>(x1 * c - x2 * s);
@@ -123,7 +123,7 @@ __global__ void rope_kernel(int n, int n_heads, int dh, T* __restrict__ x, int64
 template <typename T>
 __global__ void rope_vec_kernel(int n, int n_heads, int dh, T* __restrict__ x, int64_t ldx,
                                 const int32_t* __restrict__ seg_start, const float* __restrict__ cosb,
-                                const float* __restrict__ sinb, float sign) {
+                                const float* __restrict__ sinb) {
   constexpr int VN = Vec<T>::N;
   const int half = dh >> 1, per = half / VN;
   int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -141,25 +141,24 @@ __global__ void rope_vec_kernel(int n, int n_heads, int dh, T* __restrict__ x, i
     const f32x4 s = *reinterpret_cast<const f32x4*>(sinb + (int64_t)p * half + i + k);
 #pragma unroll
     for (int q = 0; q < 4; q++) {
-      const float sq = sign * s[q];
-      o1[k + q] = x1[k + q] * c[q] - x2[k + q] * sq;
-      o2[k + q] = x1[k + q] * sq + x2[k + q] * c[q];
+      o1[k + q] = x1[k + q] * c[q] - x2[k + q] * s[q];
+      o2[k + q] = x1[k + q] * s[q] + x2[k + q] * c[q];
     }
   }
   store_vec<T>(row + i, o1); store_vec<T>(row + i + half, o2);
 }
 
 int launch_rope(as_ctx* ctx, int mode, int n, int n_heads, int dh, void* x, int64_t ldx,
-                const int32_t* seg_start, const float* cosb, const float* sinb, int inverse, hipStream_t st) {
+                const int32_t* seg_start, const float* cosb, const float* sinb, hipStream_t st) {
   int64_t tot = (int64_t)n * n_heads * (dh / 2);
   if (tot <= 0) return AS_OK;
   prof_begin(ctx, st, AS_K_ROPE, 0.0);
   DISPATCH_T(mode, {
     constexpr int VN = Vec<T>::N;
     if ((dh / 2) % VN == 0 && vec_ok<T>(x, ldx) && ((uintptr_t)cosb % 16) == 0 && ((uintptr_t)sinb % 16) == 0)
-      rope_vec_kernel<T><<<cdiv(tot / VN, 256), 256, 0, st>>>(n, n_heads, dh, (T*)x, ldx, seg_start, cosb, sinb, inverse ? -1.f : 1.f);
+      rope_vec_kernel<T><<<cdiv(tot / VN, 256), 256, 0, st>>>(n, n_heads, dh, (T*)x, ldx, seg_start, cosb, sinb);
     else
-      rope_kernel<T><<<cdiv(tot, 256), 256, 0, st>>>(n, n_heads, dh, (T*)x, ldx, seg_start, cosb, sinb, inverse ? -1.f : 1.f); });
+      rope_kernel<T><<<cdiv(tot, 256), 256, 0, st>>>(n, n_heads, dh, (T*)x, ldx, seg_start, cosb, sinb); });
   prof_end(ctx, st);
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;

@@ -352,3 +352,37 @@ def test_plain_attention_around_one_wave_and_one_workgroup_of_rows(Hq, Hkv, dh, 
     got = G.to_np(dqkv)
     for x, r in zip((G.to_np(o), got[:, :D], got[:, D:D + Dkv], got[:, D + Dkv:]), refs):
         assert grad_norm_err(x, r.reshape(n, -1)) < tol
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("Hq,Hkv,dh", [(4, 2, 32), (2, 1, 64), (2, 2, 128)])
+def test_plain_attention_of_rows_at_any_address_and_beside_values_that_are_no_numbers(Hq, Hkv, dh, bf16):
+    """The same arithmetic whether a row comes in pieces of four values or one by one; no row that a token does not see reaches it."""
+    B, G, ctx, sh = _env(n_q_heads=Hq, n_kv_heads=Hkv, head_dim=dh)
+    dt, mode = (torch.bfloat16, B.AS_BF16) if bf16 else (torch.float32, B.AS_FP32)
+    lens = [70, 1, 130, 41]
+    g, cu, n = _attn_case(13, len(lens), Hq, Hkv, dh, lens)
+    W, D = (Hq + 2 * Hkv) * dh, Hq * dh
+    seg = om.segment_ids(cu, n)
+    s0, s1 = (torch.from_numpy(x.astype(np.int32)).cuda() for x in (cu[seg], cu[seg + 1]))
+    qkv, do = G.to_dev(g.standard_normal((n, W)), dt), G.to_dev(g.standard_normal((n, D)), dt)
+
+    def run(qkv, do, shift):
+        def at(x):                                         # a copy `shift` elements past an aligned address
+            flat = torch.empty(x.numel() + 8, dtype=dt, device="cuda")
+            flat[shift:shift + x.numel()] = x.reshape(-1)
+            return flat[shift:shift + x.numel()].view(x.shape)
+        o, lse = ctx.op_attention_fwd(at(qkv), s0, variant=1, mode=mode)
+        return o, lse, ctx.op_attention_bwd(at(qkv), s0, s1, at(o), lse, at(do), variant=1, mode=mode)
+
+    base = run(qkv, do, 0)
+    for a, b in zip(base, run(qkv, do, 1)):
+        assert torch.equal(a, b)
+    bad = qkv.clone(), do.clone()
+    for x in bad:
+        x[71:201] = float("nan")                           # the third segment
+    out = run(*bad, 0)
+    keep = torch.ones(n, dtype=torch.bool, device="cuda")
+    keep[71:201] = False
+    for a, b in zip(base, out):
+        assert torch.equal(a[keep], b[keep])
