@@ -523,6 +523,20 @@ struct Step {
     return launch_gemm_off(ctx, mode, gv, g, 0, st);
   }
 
+  // du = s dY B of the adapters among `tgt`, whose output gradients are columns coff[i] .. + nout[i] of dy: their columns of du side by side
+  int adapter_du(int l, const int* tgt, int nt, const void* dy, int64_t lddy, const int* coff, const int* nout, void* du, int64_t ldu) {
+    GemmParams g; memset(&g, 0, sizeof g);
+    for (int i = 0; i < nt; i++) {
+      const LoraSlot& s = slot(l, tgt[i]);
+      if (!s.on) continue;
+      const int k = g.nbat++;
+      g.bt_A[k] = off(dy, coff[i]); g.bt_B[k] = s.Bst; g.bt_K[k] = nout[i]; g.bt_C[k] = off(du, (size_t)s.slot * P.rp);
+    }
+    g.seg[0].lda = lddy; g.nseg = 1; g.M = P.N; g.N = P.rp; g.ldc = ldu; g.alpha = 1.f; g.splitk = 1;
+    g.tail_part = P.gemm_tail;
+    return launch_gemm_batch(ctx, mode, g, st);
+  }
+
   // type T copies of every adapter and their transposes, as many matrices per launch as a kernel argument holds
   int prep_lora() {
     const float s = c.lora_alpha / (float)c.lora_rank;
@@ -875,11 +889,8 @@ struct Step {
       if (full && (rc = weight_grads(P.dh, d, a.m, F, {{G->w_layers[l].wdown, d}}))) return rc; }
     // ---- gate / up projections
     { const int ldg = P.n_gu * rp;
-      for (int i = 0; i < 2; i++) {
-        LoraSlot& s = slot(l, AS_T_GATE + i);
-        if (s.on && !with_du && (rc = gemm(N, rp, off(P.dgu, (size_t)i * F), 2 * F, s.Bst, F, F, nullptr, 0, nullptr, 0, 0, nullptr, 0,
-                               off(P.du_gu, (size_t)s.slot * rp), ldg))) return rc;
-      }
+      const int tg[2] = {AS_T_GATE, AS_T_UP}, ng[2] = {F, F}, cg[2] = {0, F};
+      if (!with_du && (rc = adapter_du(l, tg, 2, P.dgu, 2 * F, cg, ng, P.du_gu, ldg))) return rc;
       rows_cap_once = P.cap;
       if ((rc = gemm_dx(N, d, P.dgu, 2 * F, {{w.wgate, w.agate, F}, {w.wup, w.aup, F}}, P.n_gu ? P.du_gu : nullptr, ldg, P.A_gu[l], P.At_gu[l], ldg, ldg, P.db, d))) return rc;
       if (P.n_gu && !tn_path()) {
@@ -923,11 +934,8 @@ struct Step {
       const int nout[3] = {D, Dkv, Dkv}; const int coff[3] = {0, D, D + Dkv};
       // with frozen embeddings nothing below the first layer's first norm takes a gradient
       const bool need_da = full || l > 0;
-      for (int i = 0; i < 3; i++) {
-        LoraSlot& s = slot(l, i);
-        if (s.on && (rc = gemm(N, rp, off(P.dqkv, coff[i]), QKV, s.Bst, nout[i], nout[i], nullptr, 0, nullptr, 0, 0, nullptr, 0,
-                               off(P.du_qkv, (size_t)s.slot * rp), ldu))) return rc;
-      }
+      const int tq[3] = {AS_T_Q, AS_T_K, AS_T_V};
+      if ((rc = adapter_du(l, tq, 3, P.dqkv, QKV, coff, nout, P.du_qkv, ldu))) return rc;
       rows_cap_once = P.cap;
       if (need_da && (rc = gemm_dx(N, d, P.dqkv, QKV, {{w.wq, w.aq, D}, {w.wk, w.ak, Dkv}, {w.wv, w.av, Dkv}}, P.n_qkv ? P.du_qkv : nullptr, ldu,
                                    P.A_qkv[l], P.At_qkv[l], ldu, ldu, P.da, d))) return rc;

@@ -61,6 +61,9 @@ struct GemmParams {
   // several matrices: from row rg_row[i] (a multiple of 256) on they go to rg_C[i], all with row stride ldc.  k_dev: the
   // contraction ends with row *k_dev - k_off (rows up to the next multiple of 64 must be zero in both operands).
   int tn; const int* k_dev; int k_off; int nrg; void* rg_C[2]; int rg_row[2];
+  // nbat > 0: up to three products of one shape M x N side by side in a launch (the adapters' du of q, k and v): product i has A bt_A[i] (row stride
+  // seg[0].lda), B bt_B[i] [N, bt_K[i]] (row stride bt_K[i]), result bt_C[i] (row stride ldc).  launch_gemm_batch only.
+  int nbat; const void* bt_A[3]; const void* bt_B[3]; void* bt_C[3]; int bt_K[3];
   int epi; const float* epi_lse; const int32_t* epi_lab; const float* epi_w; const int32_t* epi_cnt; float* epi_part;
   const float* epi_zlab; float* epi_elab; const float* row_scale;
 };

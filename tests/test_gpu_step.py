@@ -237,3 +237,21 @@ def test_adapter_gradients_of_a_group_in_one_launch(targets, rank, turns):
                                   lora_targets=targets, lora_rank=rank, lora_alpha=2.0 * rank)
     trajs = random_trajs(13, 3, sh.vocab, turn_lo=8, turn_hi=20, turns=turns)
     G.compare_step(sh, 8, trajs, 2, 640, bf16=True, loss_tol=2e-3, grad_tol=3e-2)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("targets, tokens, d, heads, kv, ffn", [
+    (("q", "k", "v"), 333, 512, 8, 2, 192),            # contractions of 512, 128, 128 side by side, split where one of them ends early
+    (("q", "v", "up"), 130, 128, 2, 1, 64),            # two of the three; one of two
+    (("k", "v"), 1100, 1024, 16, 4, 1088),             # without the longest
+    (synth.DENSE_TARGETS7, 70, 1024, 16, 2, 2112),     # one row tile, long contractions
+])
+def test_adapter_products_side_by_side(targets, tokens, d, heads, kv, ffn, bf16):
+    """du of q, k, v and of gate, up as one launch each."""
+    import gpu_util as G
+    sh = synth.CONFIGS[1].replace(n_layers=1, d_model=d, n_q_heads=heads, n_kv_heads=kv, head_dim=64, ffn=ffn, vocab=512, lora_rank=16, lora_alpha=32.0,
+                                  lora_targets=targets)
+    g = synth.rng(6, tokens)
+    cuts = [0, tokens // 3, tokens]
+    trajs = [[(1, g.integers(0, sh.vocab, size=3).astype(np.int32)), (2, g.integers(0, sh.vocab, size=e - b - 3).astype(np.int32))] for b, e in zip(cuts, cuts[1:])]
+    G.compare_step(sh, 2, trajs, 1, tokens, bf16=bf16, loss_tol=2e-3 if bf16 else 1e-4, grad_tol=3e-2 if bf16 else 1e-4)
