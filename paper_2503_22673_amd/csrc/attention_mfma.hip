@@ -613,7 +613,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv2_mfma(AttnParams p, float sc
 // per loop trip.  K and V tiles sit in LDS once, row major, three stages deep; dQ^T += K^T dS^T reads K through the
 // transposing LDS loads, so no token-major copy of K is needed.  Every wave issues eight loads per tile.
 #include "attn_dq_tile.inc"
-__global__ __launch_bounds__(256) void attn_bwd_dq3_mfma(AttnParams p, float scale, float sl2) {
+__device__ __forceinline__ void dq3_block(const AttnParams& p, float scale, float sl2, int block) {
   constexpr int DH = 128, KS = DH / 16, CB = DH / 32, QT = 64;
   constexpr int KT_B = BKEY * DH * 2, ST_B = 2 * KT_B;   // bytes of a tile, of a stage (K, V)
   extern __shared__ __align__(256) unsigned char dyn_smem256[];
@@ -624,7 +624,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq3_mfma(AttnParams p, float sca
   const int n = p.n, grp = p.Hq / p.Hkv;
   int hg, qi;
   const int nqt = (n + QT - 1) / QT;
-  xcd_group_map(blockIdx.x, nqt, p.Hq / 4, hg, qi);
+  xcd_group_map(block, nqt, p.Hq / 4, hg, qi);
   const int j = hg * 4 + wave, g = j / grp;
   const int t_wg = (p.order_q ? p.order_q[qi] : nqt - 1 - qi) * QT;   // long rows first
   const bf16_t* Q = (const bf16_t*)p.q; const bf16_t* K = (const bf16_t*)p.k; const bf16_t* V = (const bf16_t*)p.v;
@@ -726,7 +726,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq3_mfma(AttnParams p, float sca
 // Every wave issues nine loads per tile (four kilobytes of Q, four of dO, and the tile's lse values (even waves) or
 // delta values (odd waves); those of waves 2 and 3 land in spare space), so that one count serves all waves.
 #include "attn_dkv_tile.inc"
-__global__ __launch_bounds__(256) void attn_bwd_dkv3_mfma(AttnParams p, float scale, float sl2) {
+__device__ __forceinline__ void dkv3_block(const AttnParams& p, float scale, float sl2, int block) {
   constexpr int DH = 128, KS = DH / 16, CB = DH / 32, NWV = 4, KPB = 32 * NWV, NST = 3;
   constexpr int KT_B = BKEY * DH * 2;                     // bytes of a tile
   constexpr int ST_B = 2 * KT_B + 1024;                   // Q, dO, 64 lse, 64 delta floats, 512 spare bytes
@@ -738,7 +738,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv3_mfma(AttnParams p, float sc
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = p.n, grp = p.Hq / p.Hkv;
   int g, ki;
-  xcd_group_map(blockIdx.x, 2 * ((n + 255) / 256), p.Hkv, g, ki);
+  xcd_group_map(block, 2 * ((n + 255) / 256), p.Hkv, g, ki);
   const int u_wg = (p.order_k ? p.order_k[ki >> 1] * 2 + (ki & 1) : ki) * KPB, u_base = u_wg + wave * 32;
   if (u_wg >= n) return;                                        // the second half of a last, half-empty block of 256
   const bf16_t* Q = (const bf16_t*)p.q; const bf16_t* K = (const bf16_t*)p.k; const bf16_t* V = (const bf16_t*)p.v;
@@ -834,6 +834,14 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv3_mfma(AttnParams p, float sc
   const int pos = u - p.seg_start[u];
   store_grad_row<DH>(accK, scale, (bf16_t*)p.dk + (int64_t)u * p.ldkv + g * DH, h, p.rope_cos, p.rope_sin, pos);
   store_grad_row<DH>(accV, 1.f, (bf16_t*)p.dv + (int64_t)u * p.ldkv + g * DH, h, nullptr, p.rope_sin, pos);
+}
+
+// Workgroups of both kinds in one launch, those of dK / dV, which are the longest, first: neither kind waits for the other's last ones, and the few
+// of a short call run side by side.  As two launches (us, 32 heads over 8, then and so): 700 tokens 86 and 60, 3000 188 and 129, 6000 in segments up to 4096
+// 672 and 530, 12,000 608 and 547, 24,576 1397 and 1372.  The grid may end with dK / dV: then dQ is another kernel's.
+__global__ __launch_bounds__(256) void attn_bwd3_mfma(AttnParams p, float scale, float sl2, int dkv_blocks) {
+  if ((int)blockIdx.x < dkv_blocks) dkv3_block(p, scale, sl2, blockIdx.x);
+  else dq3_block(p, scale, sl2, (int)blockIdx.x - dkv_blocks);
 }
 
 // ------------------------------------------------------------------ head_dim 64
@@ -1041,7 +1049,7 @@ __global__ __launch_bounds__(256, 4) void attn_fwd64_mfma(AttnParams p, float sl
 }
 
 template <int HPW>
-__global__ __launch_bounds__(256, 4) void attn_bwd_dq64_mfma(AttnParams p, float scale, float sl2) {
+__device__ __forceinline__ void dq64_block(const AttnParams& p, float scale, float sl2, int block) {
   constexpr int DH = 64, KS = 4, CB = 2, QT = 32 * (4 / HPW);
   extern __shared__ __align__(256) unsigned char dyn_smem[];
   bf16_t* sm = (bf16_t*)dyn_smem;                         // [2 stages][K, V]
@@ -1050,7 +1058,7 @@ __global__ __launch_bounds__(256, 4) void attn_bwd_dq64_mfma(AttnParams p, float
   const int n = p.n, grp = p.Hq / p.Hkv;
   int hg, qi;
   const int nqt = (n + 2 * QT - 1) / (2 * QT) * 2;
-  xcd_group_map(blockIdx.x, nqt, p.Hq / HPW, hg, qi);
+  xcd_group_map(block, nqt, p.Hq / HPW, hg, qi);
   const int j = hg * HPW + (wave % HPW), g = j / grp;
   const int t_wg = (p.order_q ? p.order_q[qi >> 1] * 2 + 1 - (qi & 1) : nqt - 1 - qi) * QT;
   if (t_wg >= n) return;
@@ -1161,8 +1169,8 @@ __global__ __launch_bounds__(256) void attn_stat64_kernel(const bf16_t* __restri
 // head float partials [dK, dV][query head][token][dh], summed in head order by a second pass: a workgroup that takes the heads of a
 // group one after the other saves that pass (95 us of 555 at 15.5k tokens, 32 heads) but is four times as long, and the launch then
 // waits for its longest ones (600 against 460 + 95 us).
-__global__ __launch_bounds__(256, 3) void attn_bwd_dkv64_mfma(AttnParams p, float scale, float sl2, const float* __restrict__ nls, const float* __restrict__ nd, int n64,
-                                                              const int32_t* __restrict__ order, float* __restrict__ part) {
+__device__ __forceinline__ void dkv64_block(const AttnParams& p, float scale, float sl2, const float* __restrict__ nls, const float* __restrict__ nd, int n64,
+                                            const int32_t* __restrict__ order, float* __restrict__ part, int block) {
   constexpr int DH = 64, KS = 4, CB = 2, KPB = 128;
   constexpr int ST_E = 2 * T64_E + 256;                    // Q, dO, 64 -lse / scale and 64 -delta floats (2 elements each)
   extern __shared__ __align__(256) unsigned char dyn_smem[];
@@ -1171,7 +1179,7 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dkv64_mfma(AttnParams p, floa
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = p.n, grp = p.Hq / p.Hkv;
   int jj, ki;
-  xcd_group_map<true>(blockIdx.x, 2 * ((n + 255) / 256), p.Hq, jj, ki);
+  xcd_group_map<true>(block, 2 * ((n + 255) / 256), p.Hq, jj, ki);
   const int g = jj / grp;
   const int u_wg = (order ? order[ki >> 1] * 2 + (ki & 1) : ki) * KPB, u_base = u_wg + wave * 32;
   if (u_wg >= n) return;
@@ -1271,6 +1279,19 @@ __global__ __launch_bounds__(256, 3) void attn_bwd_dkv64_mfma(AttnParams p, floa
   store_grad_row<DH>(accV, 1.f, (bf16_t*)p.dv + (int64_t)u * p.ldkv + g * DH, h, nullptr, p.rope_sin, pos);
 }
 
+// A call's workgroups of both kinds in one launch, those of dK / dV, which are the longest, first: neither kind waits for the other's last ones
+// (bwd64: which calls).
+template <int HPW>
+__global__ __launch_bounds__(256, 3) void attn_bwd64_mfma(AttnParams p, float scale, float sl2, const float* __restrict__ nls, const float* __restrict__ nd, int n64,
+                                                          const int32_t* __restrict__ order, float* __restrict__ part, int dkv_blocks) {
+  if ((int)blockIdx.x < dkv_blocks) dkv64_block(p, scale, sl2, nls, nd, n64, order, part, blockIdx.x);
+  else dq64_block<HPW>(p, scale, sl2, (int)blockIdx.x - dkv_blocks);
+}
+template <int HPW>
+__global__ __launch_bounds__(256, 4) void attn_bwd_dq64_mfma(AttnParams p, float scale, float sl2) { dq64_block<HPW>(p, scale, sl2, blockIdx.x); }
+__global__ __launch_bounds__(256, 3) void attn_bwd_dkv64_mfma(AttnParams p, float scale, float sl2, const float* __restrict__ nls, const float* __restrict__ nd, int n64,
+                                                              const int32_t* __restrict__ order, float* __restrict__ part) { dkv64_block(p, scale, sl2, nls, nd, n64, order, part, blockIdx.x); }
+
 // dk[u, g, :] = scale * sum over the query heads of group g, in head order, of the dK partials; dv likewise (scale 1).
 // With rotary tables dk is rotated back by the token's position before its one rounding: a thread then owns 4 columns
 // i .. i + 3 of the lower half and their partners i + dh / 2.
@@ -1350,11 +1371,26 @@ int bwd64(as_ctx* ctx, const AttnParams& p, float scale, float sl2, int Np, floa
                                                                                                      sqrtf(64.f), p.delta, nls, nd, p.seg_end, order);
   AS_LAUNCH_CHECK(ctx);
   const int hpw = heads_per_wg(p);
+  const int32_t* ord = order ? order : p.order_k;
+  constexpr size_t smem = (size_t)2 * (2 * T64_E + 256) * sizeof(bf16_t);   // two stages of Q, dO, -lse / scale, -delta
+  static_assert(smem >= kSmem64, "the dQ blocks' two stages of K and V fit");
+  const int64_t dkv = 2 * cdiv(p.n, 256) * p.Hq, dq = cdiv(p.n, 64 * (4 / hpw)) * 2 * (p.Hq / hpw);
+  // Both kinds in one launch up to two rounds of dK / dV workgroups: their registers leave a CU three workgroups of dQ where it takes four alone, so
+  // many rounds are 1 % slower, but short calls run side by side (us, 32 heads over 8, apart and so): 512 tokens 42 and 28, 1003 64 and 44, 2100 122 and 94, 4100 171
+  // and 153, 6000 311 and 312, 12,000 346 and 350.
+  if (dkv <= 6 * kCus) {
+    auto go = [&](auto k) -> int {
+      AS_SET_SMEM(ctx, k, smem);
+      k<<<(unsigned)(dkv + dq), 256, smem, st>>>(p, scale, sl2, nls, nd, Np, ord, part, (int)dkv);
+      AS_LAUNCH_CHECK(ctx);
+      return AS_OK;
+    };
+    return hpw == 4 ? go(attn_bwd64_mfma<4>) : hpw == 2 ? go(attn_bwd64_mfma<2>) : go(attn_bwd64_mfma<1>);
+  }
   const int rc = hpw == 4 ? launch_dq64<4>(ctx, p, scale, sl2, st) : hpw == 2 ? launch_dq64<2>(ctx, p, scale, sl2, st) : launch_dq64<1>(ctx, p, scale, sl2, st);
   if (rc) return rc;
-  constexpr size_t smem = (size_t)2 * (2 * T64_E + 256) * sizeof(bf16_t);   // two stages of Q, dO, -lse / scale, -delta
   AS_SET_SMEM(ctx, attn_bwd_dkv64_mfma, smem);
-  attn_bwd_dkv64_mfma<<<(unsigned)(2 * cdiv(p.n, 256) * p.Hq), 256, smem, st>>>(p, scale, sl2, nls, nd, Np, order ? order : p.order_k, part);
+  attn_bwd_dkv64_mfma<<<(unsigned)dkv, 256, smem, st>>>(p, scale, sl2, nls, nd, Np, ord, part);
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }
@@ -1390,18 +1426,11 @@ int launch_dkv2(as_ctx* ctx, const AttnParams& p, float scale, float sl2, float*
   return AS_OK;
 }
 
-int launch_dq3(as_ctx* ctx, const AttnParams& p, float scale, float sl2, hipStream_t st) {
-  constexpr size_t smem = (size_t)3 * 2 * BKEY * 128 * sizeof(bf16_t);      // three stages of a K and a V tile
-  AS_SET_SMEM(ctx, attn_bwd_dq3_mfma, smem);
-  attn_bwd_dq3_mfma<<<(unsigned)(cdiv(p.n, 64) * (p.Hq / 4)), 256, smem, st>>>(p, scale, sl2);
-  AS_LAUNCH_CHECK(ctx);
-  return AS_OK;
-}
-
-int launch_dkv3(as_ctx* ctx, const AttnParams& p, float scale, float sl2, hipStream_t st) {
-  constexpr size_t smem = (size_t)3 * (2 * BKEY * 128 * sizeof(bf16_t) + 1024);   // three stages of a Q and a dO tile, lse, delta
-  AS_SET_SMEM(ctx, attn_bwd_dkv3_mfma, smem);
-  attn_bwd_dkv3_mfma<<<(unsigned)(2 * cdiv(p.n, 256) * p.Hkv), 256, smem, st>>>(p, scale, sl2);
+int launch_bwd3(as_ctx* ctx, const AttnParams& p, float scale, float sl2, bool with_dq, hipStream_t st) {
+  constexpr size_t smem = (size_t)3 * (2 * BKEY * 128 * sizeof(bf16_t) + 1024);   // three stages of a Q and a dO tile, lse, delta; dQ's K and V tiles need less
+  AS_SET_SMEM(ctx, attn_bwd3_mfma, smem);
+  const int64_t dkv = 2 * cdiv(p.n, 256) * p.Hkv;          // a head's dQ blocks keep to one XCD whatever the remainder by eight is
+  attn_bwd3_mfma<<<(unsigned)(dkv + (with_dq ? cdiv(p.n, 64) * (p.Hq / 4) : 0)), 256, smem, st>>>(p, scale, sl2, (int)dkv);
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }
@@ -1432,11 +1461,11 @@ int bwd_dh(as_ctx* ctx, const AttnParams& p_in, int variant, hipStream_t st) {
     }
     launch_delta<DH>(p, rows, st);
     AS_LAUNCH_CHECK(ctx);
-    if (dq_one_wave) rc = launch_dq3(ctx, p, scale, sl2, st);
-    else if (hpw == 4) rc = launch_dq2<DH, 4>(ctx, p, scale, sl2, st); else if (hpw == 2) rc = launch_dq2<DH, 2>(ctx, p, scale, sl2, st);
+    if (dq_one_wave) return launch_bwd3(ctx, p, scale, sl2, true, st);
+    if (hpw == 4) rc = launch_dq2<DH, 4>(ctx, p, scale, sl2, st); else if (hpw == 2) rc = launch_dq2<DH, 2>(ctx, p, scale, sl2, st);
     else rc = launch_dq2<DH, 1>(ctx, p, scale, sl2, st);
     if (rc) return rc;
-    if (one_pass) return launch_dkv3(ctx, p, scale, sl2, st);     // sums over the query heads itself
+    if (one_pass) return launch_bwd3(ctx, p, scale, sl2, false, st);     // sums over the query heads itself
     if ((rc = launch_dkv2<DH, 0>(ctx, p, scale, sl2, part, st)) || (rc = launch_dkv2<DH, 1>(ctx, p, scale, sl2, part, st))) return rc;
   }
   if (p.Hq > p.Hkv) {

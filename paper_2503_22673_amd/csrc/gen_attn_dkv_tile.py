@@ -1,5 +1,5 @@
 #!/usr/bin/env python3
-"""Writes attn_dkv_tile.inc: one (32 keys x 64 queries) tile step of attn_bwd_dkv3_mfma (attention_mfma.hip, head_dim
+"""Writes attn_dkv_tile.inc: one (32 keys x 64 queries) tile step of attn_bwd3_mfma (attention_mfma.hip, head_dim
 128) as one inline-asm block.  Run by hand after a change (python gen_attn_dkv_tile.py); the generated file is
 committed.
 
@@ -328,7 +328,7 @@ def main(out_path=None):
     lines.append("L_dkv_end_%=:")
     out = out_path or os.path.join(os.path.dirname(os.path.abspath(__file__)), "attn_dkv_tile.inc")
     with open(out, "w") as f:
-        f.write("// Generated by gen_attn_dkv_tile.py -- do not edit.  One tile step of attn_bwd_dkv3_mfma.\n")
+        f.write("// Generated by gen_attn_dkv_tile.py -- do not edit.  One tile step of attn_bwd3_mfma.\n")
         f.write("#define ATTN_DKV_TILE_ASM \\\n")
         for ln in lines:
             f.write('  "%s\\n" \\\n' % ln)

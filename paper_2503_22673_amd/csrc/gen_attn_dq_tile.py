@@ -1,5 +1,5 @@
 #!/usr/bin/env python3
-"""Writes attn_dq_tile.inc: one (64 queries x 64 keys) tile step of attn_bwd_dq3_mfma (attention_mfma.hip, head_dim
+"""Writes attn_dq_tile.inc: one (64 queries x 64 keys) tile step of attn_bwd3_mfma (attention_mfma.hip, head_dim
 128) as one inline-asm block.  Run by hand after a change (python gen_attn_dq_tile.py); the generated file is
 committed.  Same construction as gen_attn_dkv_tile.py (one wave per SIMD, everything behind the MFMAs, waits derived by
 replaying the sequence); what differs:
@@ -234,7 +234,7 @@ def main(out_path=None):
     lines.append("L_dq_end_%=:")
     out = out_path or os.path.join(os.path.dirname(os.path.abspath(__file__)), "attn_dq_tile.inc")
     with open(out, "w") as f:
-        f.write("// Generated by gen_attn_dq_tile.py -- do not edit.  One tile step of attn_bwd_dq3_mfma.\n")
+        f.write("// Generated by gen_attn_dq_tile.py -- do not edit.  One tile step of attn_bwd3_mfma.\n")
         f.write("#define ATTN_DQ_TILE_ASM \\\n")
         for ln in lines:
             f.write('  "%s\\n" \\\n' % ln)
