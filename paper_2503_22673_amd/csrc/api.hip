@@ -255,7 +255,7 @@ struct Plan {
   float *part, *zlab, *lse_rows;         // its per-block softmax statistics [Mc, V / 128, 2], label logits and log-sum-exps per target   // Np: token count rounded up to 64 (row length of token-major transposes)
   int cap;                               // token rows every activation buffer holds (rows * row_len of the plan)
   int n_qkv, n_gu;                       // adapters inside the q/k/v and gate/up groups
-  int32_t *seg_start, *seg_end, *tgt_idx, *tgt_pos, *labels, *count, *iscratch;
+  int32_t *seg_start, *seg_end, *block_targets, *tgt_idx, *tgt_pos, *labels, *count, *iscratch;
   int32_t* step_tab; size_t step_tab_ints;   // per-step host table: segment table, sources, attention launch orders, kept-segment map, pairs
   int32_t *tok_c; uint8_t* mask_c;       // tokens and mask with the skipped segments squeezed out
   const int32_t *order_q = nullptr, *order_k = nullptr;   // attention launch orders of this step (longest workgroups first)
@@ -315,6 +315,7 @@ static void make_plan(const as_ctx* ctx, int64_t rows, int64_t row_len, Bump& w,
   const size_t rp = (size_t)P.rp;
 
   P.seg_start = (int32_t*)w.take(N * 4); P.seg_end = (int32_t*)w.take(N * 4);
+  P.block_targets = (int32_t*)w.take((size_t)cdiv(P.N, kTargetBlock) * 4);
   P.tgt_idx = (int32_t*)w.take(N * 4); P.tgt_pos = (int32_t*)w.take(N * 4); P.labels = (int32_t*)w.take(N * 4);
   P.count = (int32_t*)w.take(256);
   P.step_tab_ints = 6 * N + 64;                           // (S+1) + S + N/32 + N/256 + S + 2 P with S, P <= N
@@ -1241,9 +1242,9 @@ static int run_step(as_ctx* ctx, const char* who, const as_weights* weights, con
     }
     return S.zero_outputs(d_loss, d_loss_sum, d_count);
   }
-  if ((rc = launch_segment_info(ctx, d_cu_eff, n_seg_eff, n, P.seg_start, P.seg_end, st))) return rc;
+  if ((rc = launch_segment_info(ctx, d_cu_eff, n_seg_eff, d_loss_mask, n, P.seg_start, P.seg_end, P.block_targets, st))) return rc;
   if ((rc = launch_rope_table(ctx, max_seg, c.head_dim, c.rope_base, P.rope_cos, P.rope_sin, st))) return rc;
-  if ((rc = launch_select_targets(ctx, P.seg_start, d_loss_mask, d_tokens, n, P.tgt_idx, P.tgt_pos, P.labels, d_count, st))) return rc;
+  if ((rc = launch_select_targets(ctx, P.seg_end, P.block_targets, d_loss_mask, d_tokens, n, P.tgt_idx, P.tgt_pos, P.labels, d_count, st))) return rc;
   P.count = d_count;
   if (!full && !adapters_off && (rc = S.prep_lora())) return rc;
   if ((rc = launch_embed(ctx, c.mode, d_tokens, n, c.d_model, weights->embed, P.h[0], st))) return rc;

@@ -49,6 +49,16 @@ int as_fail(as_ctx* ctx, int code, const char* fmt, ...);
     AS_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(bytes))); \
     done_.fetch_or(bit_, std::memory_order_relaxed); } } while (0)
 
+// The item of a launch's table that x lies in, first(k) being where item k begins: the begins are read side by side and counted.  A search
+// reads them one after the other, and each of those reads is a first touch of memory: 0.2 to 0.4 us of the
+// adapter gradients' launches, their sums' and the 4-bit unpacking.
+template <int MAX, typename X, typename F> __device__ __forceinline__ int table_item(int n, X x, F first) {
+  int it = 0;
+#pragma unroll
+  for (int k = 1; k < MAX; k++) it += k < n && x >= first(k) ? 1 : 0;
+  return it;
+}
+
 static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 template <typename T> __device__ __forceinline__ float to_f(T x);
@@ -152,8 +162,10 @@ int launch_pack(as_ctx* ctx, const int32_t* h_tokens, const int32_t* h_cu, const
 // tok_c[i], mask_c[i] = tok[src], mask[src] with src = src_start[s] + (i - cu_c[s]) for the kept segment s holding i
 int launch_compact(as_ctx* ctx, const int32_t* tok, const uint8_t* mask, const int32_t* cu_c, const int32_t* src_start,
                    int n_seg, int n, int32_t* tok_c, uint8_t* mask_c, hipStream_t st);
-int launch_segment_info(as_ctx* ctx, const int32_t* d_cu, int n_seg, int n, int32_t* seg_start,
-                        int32_t* seg_end, hipStream_t st);
+// and the number of targets among every kTargetBlock tokens (mask: tokens that bear loss; a target is predicted by the token before it)
+constexpr int kTargetBlock = 256;
+int launch_segment_info(as_ctx* ctx, const int32_t* d_cu, int n_seg, const uint8_t* mask, int n, int32_t* seg_start,
+                        int32_t* seg_end, int32_t* block_targets, hipStream_t st);
 int launch_rope_table(as_ctx* ctx, int max_pos, int dh, float base, float* cosb, float* sinb, hipStream_t st);
 int launch_embed(as_ctx* ctx, int mode, const int32_t* tok, int n, int d, const void* E, void* h, hipStream_t st);
 int launch_rmsnorm_fwd(as_ctx* ctx, int mode, int n, int d, const void* x, const int32_t* row_idx,
@@ -211,13 +223,13 @@ int launch_transpose_pair(as_ctx* ctx, int mode, int rows, int rows_pad, int col
 // first 16 of the rank, which is the row of `in` (frag_rank_rows) or its column, as operands of v_mfma_f32_16x16x32_bf16, 512 elements for every
 // 32 of the contraction.
 struct PrepMatrix { const float* in; void *out, *out_t; int64_t ldo, ldo_t; int rows, cols, rows_pad, cols_pad; float scale; int first_tile; void* frag; int frag_rank_rows; };
-constexpr int kPrepBatch = 48;                             // a batch is a kernel argument (3.8 KB)
+constexpr int kPrepBatch = 40;                             // a batch is a kernel argument (3.4 KB)
 
 struct PrepBatch { PrepMatrix m[kPrepBatch]; int n, n_tiles; };
 int launch_lora_prep_batch(as_ctx* ctx, int mode, const PrepBatch& b, hipStream_t st);
 int launch_fill_zero(as_ctx* ctx, void* p, size_t bytes, hipStream_t st);
 int launch_zero_tail_rows(as_ctx* ctx, int rows, const int* n_dev, int off, void* a, int64_t lda, int ca, void* b, int64_t ldb, int cb, hipStream_t st);
-int launch_select_targets(as_ctx* ctx, const int32_t* seg_start, const uint8_t* mask, const int32_t* tok,
+int launch_select_targets(as_ctx* ctx, const int32_t* seg_end, const int32_t* block_targets, const uint8_t* mask, const int32_t* tok,
                           int n, int32_t* tgt_idx, int32_t* tgt_pos, int32_t* labels, int32_t* count,
                           hipStream_t st);
 // one row of logits per target: loss_t, and P = (softmax - onehot) / count written as T

@@ -53,23 +53,32 @@ int launch_compact(as_ctx* ctx, const int32_t* tok, const uint8_t* mask, const i
   return AS_OK;
 }
 
-__global__ void segment_info_kernel(const int32_t* __restrict__ cu, int n_seg, int n,
-                                    int32_t* __restrict__ seg_start, int32_t* __restrict__ seg_end) {
-  int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n) return;
-  int lo = 0, hi = n_seg - 1;               // last s with cu[s] <= t
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (cu[mid] <= t) lo = mid; else hi = mid - 1;
+// token t predicts a target: the next token is of the same segment and bears loss
+__device__ __forceinline__ bool predicts_target(int t, int seg_end, const uint8_t* mask) { return t + 1 < seg_end && mask[t + 1]; }
+
+__global__ __launch_bounds__(kTargetBlock) void segment_info_kernel(const int32_t* __restrict__ cu, int n_seg, const uint8_t* __restrict__ mask, int n,
+                                                                    int32_t* __restrict__ seg_start, int32_t* __restrict__ seg_end, int32_t* __restrict__ block_targets) {
+  const int t = blockIdx.x * kTargetBlock + threadIdx.x;
+  bool is = false;
+  if (t < n) {
+    int lo = 0, hi = n_seg - 1;             // last s with cu[s] <= t
+    while (lo < hi) {
+      int mid = (lo + hi + 1) >> 1;
+      if (cu[mid] <= t) lo = mid; else hi = mid - 1;
+    }
+    const int e = cu[lo + 1];
+    seg_start[t] = cu[lo];
+    seg_end[t] = e;
+    is = predicts_target(t, e, mask);
   }
-  seg_start[t] = cu[lo];
-  seg_end[t] = cu[lo + 1];
+  const int c = __syncthreads_count(is);
+  if (threadIdx.x == 0) block_targets[blockIdx.x] = c;
 }
 
-int launch_segment_info(as_ctx* ctx, const int32_t* d_cu, int n_seg, int n, int32_t* seg_start,
-                        int32_t* seg_end, hipStream_t st) {
+int launch_segment_info(as_ctx* ctx, const int32_t* d_cu, int n_seg, const uint8_t* mask, int n, int32_t* seg_start,
+                        int32_t* seg_end, int32_t* block_targets, hipStream_t st) {
   if (n <= 0) return AS_OK;
-  segment_info_kernel<<<cdiv(n, 256), 256, 0, st>>>(d_cu, n_seg, n, seg_start, seg_end);
+  segment_info_kernel<<<cdiv(n, kTargetBlock), kTargetBlock, 0, st>>>(d_cu, n_seg, mask, n, seg_start, seg_end, block_targets);
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }
@@ -823,25 +832,24 @@ int launch_transpose_qs(as_ctx* ctx, int mode, int rows, int rows_pad, int cols,
 
 // ------------------------------------------------------ LoRA operand copies
 // out[rp, cp] = scale * in[r, c] inside, 0 in the padding; out_t is its transpose.  Up to kPrepBatch matrices per launch,
-// described in the kernel argument; a workgroup takes one 64 x 64 tile of one of them (found by bisection over the
-// matrices' first tiles), writes it and, through LDS, its transpose, both in whole row pieces.  One launch per matrix wrote the
+// described in the kernel argument; a workgroup takes one 64 x 64 tile of one of them, writes it and, through LDS, its transpose, both in whole row pieces.  One launch per matrix wrote the
 // transposes two bytes at a time and took 102 us
-// for the 28 matrices of two 1B layers; 17 us so.
+// for the 28 matrices of two 1B layers; 17.6 with its loads one after the other, 13.9 so.
+struct PrepArgs { PrepMatrix m[kPrepBatch]; int first[kPrepBatch]; };        // first: past the last matrix, past every tile
 template <typename T>
-__global__ __launch_bounds__(256) void lora_prep_kernel(const PrepBatch b) {
+__global__ __launch_bounds__(256) void lora_prep_kernel(const PrepArgs b) {
   __shared__ float tile[64][65];
-  int mi = 0, hi = b.n - 1;
-  while (mi < hi) { const int mid = (mi + hi + 1) >> 1; if ((int)blockIdx.x >= b.m[mid].first_tile) mi = mid; else hi = mid - 1; }
-  const PrepMatrix& m = b.m[mi];
+  const PrepMatrix& m = b.m[table_item<kPrepBatch>(kPrepBatch, (int)blockIdx.x, [&](int k) { return b.first[k]; })];
   const int tiles_c = (m.cols_pad + 63) / 64, t = (int)blockIdx.x - m.first_tile;
   const int r0 = (t / tiles_c) * 64, c0 = (t % tiles_c) * 64;
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   T* out = (T*)m.out; T* out_t = (T*)m.out_t;
+  // every load is made, inside the matrix, before the first value is used: a load under a condition of its own waits for the one before
+  float v[16];
 #pragma unroll
-  for (int i = 0; i < 16; i++) {
-    const int r = r0 + ty + 4 * i, c = c0 + tx;
-    tile[ty + 4 * i][tx] = (r < m.rows && c < m.cols) ? m.scale * m.in[(int64_t)r * m.cols + c] : 0.f;
-  }
+  for (int i = 0; i < 16; i++) v[i] = m.in[(int64_t)min(r0 + ty + 4 * i, m.rows - 1) * m.cols + min(c0 + tx, m.cols - 1)];
+#pragma unroll
+  for (int i = 0; i < 16; i++) tile[ty + 4 * i][tx] = r0 + ty + 4 * i < m.rows && c0 + tx < m.cols ? m.scale * v[i] : 0.f;
 #pragma unroll
   for (int i = 0; i < 16; i++) {
     const int r = r0 + ty + 4 * i, c = c0 + tx;
@@ -864,7 +872,9 @@ __global__ __launch_bounds__(256) void lora_prep_kernel(const PrepBatch b) {
 
 int launch_lora_prep_batch(as_ctx* ctx, int mode, const PrepBatch& b, hipStream_t st) {
   if (b.n <= 0 || b.n_tiles <= 0) return AS_OK;
-  DISPATCH_T(mode, (lora_prep_kernel<T><<<b.n_tiles, 256, 0, st>>>(b)));
+  PrepArgs a;
+  for (int k = 0; k < kPrepBatch; k++) { a.m[k] = b.m[k < b.n ? k : 0]; a.first[k] = k < b.n ? b.m[k].first_tile : INT32_MAX; }
+  DISPATCH_T(mode, (lora_prep_kernel<T><<<b.n_tiles, 256, 0, st>>>(a)));
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }
@@ -900,39 +910,39 @@ int launch_zero_tail_rows(as_ctx* ctx, int rows, const int* n_dev, int off, void
 }
 
 // ---------------------------------------------------------- target selection
-// Position t is a target when t+1 exists, starts no segment, and carries the
-// mask.  One block scans the whole stream so the order is fixed.
-__global__ void select_targets_kernel(const int32_t* __restrict__ seg_start, const uint8_t* __restrict__ mask,
-                                      const int32_t* __restrict__ tok, int n, int32_t* __restrict__ tgt_idx,
-                                      int32_t* __restrict__ tgt_pos, int32_t* __restrict__ labels,
-                                      int32_t* __restrict__ count) {
-  __shared__ int32_t sums[1024];
-  int tid = threadIdx.x;
-  int per = (n + 1023) / 1024;
-  int b = tid * per, e = min(n, b + per);
-  int c = 0;
-  for (int t = b; t < e; t++) c += (t + 1 < n && seg_start[t + 1] != t + 1 && mask[t + 1]) ? 1 : 0;
-  sums[tid] = c;
+// Stable compaction of the target rows.  A workgroup takes kTargetBlock tokens and adds up the counts of the blocks before it: 24,710 tokens 55 -> 4.7 us
+// (one workgroup with a slab of tokens a thread before).
+__global__ __launch_bounds__(kTargetBlock) void select_targets_kernel(const int32_t* __restrict__ seg_end, const int32_t* __restrict__ block_targets,
+                                                                      const uint8_t* __restrict__ mask, const int32_t* __restrict__ tok, int n,
+                                                                      int32_t* __restrict__ tgt_idx, int32_t* __restrict__ tgt_pos, int32_t* __restrict__ labels,
+                                                                      int32_t* __restrict__ count) {
+  constexpr int WAVES = kTargetBlock / AS_WAVE;
+  __shared__ int32_t before[WAVES], mine[WAVES];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, t = blockIdx.x * kTargetBlock + tid;
+  int sum = 0;
+  for (int b = tid; b < (int)blockIdx.x; b += kTargetBlock) sum += block_targets[b];
+  const bool is = t < n && predicts_target(t, seg_end[t], mask);
+  const uint64_t set = __ballot(is);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  if (lane == 0) { before[wave] = sum; mine[wave] = __popcll(set); }
   __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {          // inclusive scan
-    int v = tid >= off ? sums[tid - off] : 0;
-    __syncthreads();
-    sums[tid] += v;
-    __syncthreads();
+  int base = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < WAVES; w++) { base += before[w] + (w < wave ? mine[w] : 0); all += before[w] + mine[w]; }
+  if (t < n) {
+    const int at = base + __popcll(set & ((1ull << lane) - 1));
+    if (is) { tgt_idx[at] = t; labels[at] = tok[t + 1]; }
+    tgt_pos[t] = is ? at : -1;
   }
-  int base = sums[tid] - c;
-  for (int t = b; t < e; t++) {
-    bool is = (t + 1 < n && seg_start[t + 1] != t + 1 && mask[t + 1]);
-    if (is) { tgt_idx[base] = t; labels[base] = tok[t + 1]; tgt_pos[t] = base; base++; }
-    else tgt_pos[t] = -1;
-  }
-  if (tid == 1023) *count = sums[1023];
+  if (blockIdx.x == gridDim.x - 1 && tid == 0) *count = all;
 }
 
-int launch_select_targets(as_ctx* ctx, const int32_t* seg_start, const uint8_t* mask, const int32_t* tok,
+int launch_select_targets(as_ctx* ctx, const int32_t* seg_end, const int32_t* block_targets, const uint8_t* mask, const int32_t* tok,
                           int n, int32_t* tgt_idx, int32_t* tgt_pos, int32_t* labels, int32_t* count,
                           hipStream_t st) {
-  select_targets_kernel<<<1, 1024, 0, st>>>(seg_start, mask, tok, n, tgt_idx, tgt_pos, labels, count);
+  if (n <= 0) return AS_OK;
+  select_targets_kernel<<<(unsigned)cdiv(n, kTargetBlock), kTargetBlock, 0, st>>>(seg_end, block_targets, mask, tok, n, tgt_idx, tgt_pos, labels, count);
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }

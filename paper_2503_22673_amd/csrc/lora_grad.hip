@@ -28,8 +28,7 @@ struct TnParams {
 #include "lora_grad_loop.inc"
 template <int NB>
 __global__ __launch_bounds__(256) void lora_grad_tn_kernel(TnParams batch) {
-  int it = 0;
-  while (it + 1 < batch.b.n && (int)blockIdx.x >= batch.b.m[it + 1].first_block) it++;
+  const int it = table_item<6>(batch.b.n, (int)blockIdx.x, [&](int k) { return batch.b.m[k].first_block; });
   struct { const bf16_t* X; int64_t ldx; const bf16_t* UT; int64_t ldu; int n, M, r, steps_per_split, total_steps; float* partial; int64_t split_stride; } p;
   {
     const TnGrad& m = batch.b.m[it];
@@ -130,9 +129,7 @@ __global__ void tn_reduce_kernel(const TnGradBatch b, const float* __restrict__ 
   // a thread owns four consecutive elements (M is a multiple of 8) and adds the splits in order; eight loads in flight
   const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4, total = b.total;
   if (i >= total) return;
-  int it = 0;
-  while (it + 1 < b.n && i >= b.m[it + 1].first_out) it++;
-  const TnGrad& m = b.m[it];
+  const TnGrad& m = b.m[table_item<6>(b.n, i, [&](int k) { return b.m[k].first_out; })];
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   int s = 0;
   for (; s + 8 <= splits; s += 8) {
@@ -204,9 +201,7 @@ int launch_tn_grads(as_ctx* ctx, TnGradBatch b, int n, int r, float* partial, si
 constexpr int PG_WAVES = 16, PG_B = 16, PG_U = 8;
 __global__ __launch_bounds__(PG_WAVES * 64) void plain_grad_kernel(const PlainGradBatch b, int n, int r, int splits, float* __restrict__ partial) {
   __shared__ __align__(16) f32x4 sh[PG_WAVES][64];
-  int it = 0;
-  while (it + 1 < b.n && (int)blockIdx.x >= b.m[it + 1].first_block) it++;
-  const PlainGrad& m = b.m[it];
+  const PlainGrad& m = b.m[table_item<8>(b.n, (int)blockIdx.x, [&](int k) { return b.m[k].first_block; })];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, q = lane >> 4;
   const int nj = (r + PG_B - 1) / PG_B, blk = (int)blockIdx.x - m.first_block, col0 = (blk / nj) * PG_B, j0 = (blk % nj) * PG_B;
   const int per = (n + splits - 1) / splits, t_lo = blockIdx.y * per, t_hi = min(n, t_lo + per);
@@ -240,9 +235,7 @@ __global__ __launch_bounds__(PG_WAVES * 64) void plain_grad_kernel(const PlainGr
 __global__ __launch_bounds__(256) void plain_grad_sum_kernel(const PlainGradBatch b, int r, int splits, const float* __restrict__ partial) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= b.total) return;
-  int it = 0;
-  while (it + 1 < b.n && i >= b.m[it + 1].first_out) it++;
-  const PlainGrad& m = b.m[it];
+  const PlainGrad& m = b.m[table_item<8>(b.n, i, [&](int k) { return b.m[k].first_out; })];
   float s = 0.f;
 #pragma unroll 8
   for (int k = 0; k < splits; k++) s += partial[(int64_t)k * b.total + i];

@@ -46,11 +46,7 @@ __global__ void nf4_dequantize_kernel(const uint8_t* __restrict__ codes, const f
 }
 
 // the matrix of a batch that a block works on
-__device__ __forceinline__ int piece_of(const Nf4Batch& b, int block) {
-  int k = 0;
-  while (k + 1 < b.n && block >= b.m[k + 1].first) k++;
-  return k;
-}
+__device__ __forceinline__ int piece_of(const Nf4Batch& b, int block) { return table_item<3>(b.n, block, [&](int k) { return b.m[k].first; }); }
 
 // bf16, `out` 16-byte and `codes` 4-byte aligned, the matrices of one input group (q, k, v; gate, up) in one launch.
 // Memory bound: 0.5 bytes in, 2 out per weight.  A wave takes kVecRuns runs of 512 elements one after the other, so that a load reads 256 and a store
