@@ -358,16 +358,15 @@ int launch_rmsnorm_bwd(as_ctx* ctx, int mode, int n, int d, const void* dy, cons
 // The same with the gain gradient dg_j = sum_t dy[t,j] x[t,j] rstd[t] out of the same pass over dy and x (full fine-tuning):
 // up to 256 workgroups walk the rows, a lane adds up the columns it holds of every row it sees, the waves of a workgroup are
 // added in order through LDS into partial[workgroup, :], and a second launch adds the workgroups in order.  Bound by memory (dy, x,
-// add in, dx out), by more of it than that: 16 waves of a workgroup with KEEP = 4 (2048 16-bit columns), 8 with KEEP = 8,
-// leave too few registers for the 16-bit instances.  40 and 92 spill, and the column sums among them go through scratch memory for
-// every row: 48,564 rows of 2048, bf16: 204 us for 832 MB in and 464 MB out by the counters, where the operands are 597 and
-// 199 MB (3.9 TB/s of them; the backward pass without gains runs at 5.8).  15,700 rows: 77 us with the sum; as three launches
-// (backward, a second pass over dy and x, a sum of 256 slabs by one thread per column) 130 us.
+// add in, dx out).  8 waves with KEEP = 4 (2048 16-bit columns), 4 with KEEP = 8: the registers for a row's three operands and the column sums.
+// Twice as many waves spilled 40 and 92 registers, the column sums among them, to scratch memory for every row: 13,800 rows of 2048, bf16, 71 us
+// where this takes 43 (5.2 TB/s).  As three launches (backward, a second pass over dy and x, a sum of 256 slabs by one thread per column) it was
+// 130 us against 77 with the spills and the sum.
 template <typename T, int KEEP>
-__global__ __launch_bounds__(4096 / KEEP) void rmsnorm_bwd_gain_kernel(int n, int d, const T* __restrict__ dy, const int32_t* __restrict__ src_pos,
+__global__ __launch_bounds__(2048 / KEEP) void rmsnorm_bwd_gain_kernel(int n, int d, const T* __restrict__ dy, const int32_t* __restrict__ src_pos,
                                                                const T* __restrict__ x, const T* __restrict__ g, const float* __restrict__ rstd,
                                                                const T* __restrict__ add, T* __restrict__ dx, float* __restrict__ partial) {
-  constexpr int VN = Vec<T>::N, STEP = AS_WAVE * VN, NW = 64 / KEEP;
+  constexpr int VN = Vec<T>::N, STEP = AS_WAVE * VN, NW = 32 / KEEP;
   typedef typename Vec<T>::type VT;
   extern __shared__ __align__(16) float gsum[];          // [d]
   const int lane = threadIdx.x % AS_WAVE, wave = threadIdx.x / AS_WAVE;
@@ -490,9 +489,9 @@ int launch_rmsnorm_bwd_gain(as_ctx* ctx, int mode, int n, int d, const void* dy,
   if (fused) {
     DISPATCH_T(mode, {
       const bool small = d <= 4 * AS_WAVE * Vec<T>::N;
-      n_part = (int)std::min<int64_t>(n_part, cdiv(n, small ? 16 : 8));
-      if (small) rmsnorm_bwd_gain_kernel<T, 4><<<n_part, 1024, (size_t)d * 4, st>>>(n, d, (const T*)dy, src_pos, (const T*)x, (const T*)g, rstd, (const T*)add, (T*)dx, partial);
-      else rmsnorm_bwd_gain_kernel<T, 8><<<n_part, 512, (size_t)d * 4, st>>>(n, d, (const T*)dy, src_pos, (const T*)x, (const T*)g, rstd, (const T*)add, (T*)dx, partial); });
+      n_part = (int)std::min<int64_t>(n_part, cdiv(n, small ? 8 : 4));
+      if (small) rmsnorm_bwd_gain_kernel<T, 4><<<n_part, 512, (size_t)d * 4, st>>>(n, d, (const T*)dy, src_pos, (const T*)x, (const T*)g, rstd, (const T*)add, (T*)dx, partial);
+      else rmsnorm_bwd_gain_kernel<T, 8><<<n_part, 256, (size_t)d * 4, st>>>(n, d, (const T*)dy, src_pos, (const T*)x, (const T*)g, rstd, (const T*)add, (T*)dx, partial); });
   } else {
     int rc = launch_rmsnorm_bwd(ctx, mode, n, d, dy, src_pos, x, g, rstd, add, dx, st);
     if (rc) return rc;
