@@ -791,7 +791,7 @@ struct Step {
   bool tn_path() const { return mode == AS_FP32 || c.lora_rank <= 64; }
   // token-major copies of a group's u and du (bf16)
   int lora_tok(int cols, const void* u, const void* du) {
-    if (mode == AS_FP32) return AS_OK;
+    if (mode == AS_FP32 || tn_grads_take_rows(c.lora_rank)) return AS_OK;
     return launch_transpose_pair(ctx, mode, P.N, P.Np, cols, u, du, cols, P.uT, P.duT, P.Np, st);
   }
   PlainGradBatch pg{};
@@ -814,10 +814,11 @@ struct Step {
       pg.m[pg.n++] = {(const float*)x, (const float*)du + (size_t)s.slot * rp, ldx, ldu, g.a[t], 1, s.din, 0, s.din, 0, 1.f};
       return AS_OK;
     }
-    const void* uT = off(P.uT, (size_t)s.slot * rp * Np);
-    const void* duT = off(P.duT, (size_t)s.slot * rp * Np);
+    const bool rows = tn_grads_take_rows(r);
+    const void* uT = rows ? off(u, (size_t)s.slot * rp) : off(P.uT, (size_t)s.slot * rp * Np);
+    const void* duT = rows ? off(du, (size_t)s.slot * rp) : off(P.duT, (size_t)s.slot * rp * Np);
     if (tn_path()) {
-      tg.ldu = Np;
+      tg.ldu = rows ? ldu : Np;
       tg.m[tg.n++] = {dy, lddy, uT, s.dout, sc, g.b[t], r, 1, 0, 0};
       tg.m[tg.n++] = {x, ldx, duT, s.din, 1.f, g.a[t], 1, s.din, 0, 0};
       return AS_OK;

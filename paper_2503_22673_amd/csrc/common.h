@@ -121,7 +121,9 @@ int launch_feed_probe(as_ctx* ctx, int k, const void* buf, size_t span, int iter
 int launch_mfma_peak(as_ctx* ctx, int iters, int blocks, float* sink, hipStream_t st);
 
 // ---- adapter gradients (lora_grad.hip) ---------------------------------------
-// C[m*sm + j*sj] = alpha * sum_t X[t, m] * UT[j, t]  (bf16 X row-major, UT token-major, float C)
+// C[m*sm + j*sj] = alpha * sum_t X[t, m] * UT[j, t]  (bf16 X row-major, float C); UT is U token-major with rows of ldu tokens, or, where
+// tn_grads_take_rows(rank), U itself, rows of ldu columns of which 16 are read
+bool tn_grads_take_rows(int r);
 struct TnGrad { const void* X; int64_t ldx; const void* UT; int M; float alpha; float* C; int64_t sm, sj; int first_block; int64_t first_out; };
 struct TnGradBatch { TnGrad m[6]; int n; int64_t ldu, total; };
 size_t tn_grad_partial_floats(int n, const int* M, int items, int r);

@@ -8,7 +8,9 @@
 // 16 lanes and token) and transposes it in registers (v_perm), which yields the A operands of eight
 // v_mfma_f32_16x16x32_bf16 -- one per column of the block; MFMA row m then stands for column
 // c0 + 8 m + q of X.  U comes from its small token-major copy ([j][token]), one 16-byte load per
-// lane and 16-column block.  Token ranges (splits) go to a partial buffer reduced in split order.
+// lane and 16-column block; of rank 16 and less, as it is: 32 tokens of 16 columns are one 16-byte load a lane, pass through a kilobyte of the wave's LDS and
+// come back through the transposing reads
+// (copies of both for every input group, a launch of 4.5 us each at 626 tokens: a step of two 1B layers 1.334 -> 1.305 ms).  Token ranges (splits) go to a partial buffer reduced in split order.
 // The products of an input group (dB and dA of q, k, v) are one launch and one sum: each of them alone is a ramp of a few
 // microseconds around little work when tokens are few: steps of two 1B layers with seven adapters at 1003 tokens 1708 -> 1555 us,
 // at 32768 tokens 18.19 -> 17.68 ms.
@@ -43,6 +45,10 @@ __global__ __launch_bounds__(256) void lora_grad_tn_kernel(TnParams batch) {
   if (slab * 128 >= p.M) return;
   const int col = slab * 128 + 8 * lm;
   const bool col_ok = col < p.M;
+  // NB = 1: U [token][16 of its columns] as rows
+  constexpr bool ROWS = NB == 1;
+  __shared__ __align__(16) bf16_t turn[ROWS ? 4 * 512 : 8];
+  bf16_t* mine = turn + (ROWS ? wave * 512 : 0);
   f32x4 acc[8][NB];
 #pragma unroll
   for (int q = 0; q < 8; q++)
@@ -58,8 +64,26 @@ __global__ __launch_bounds__(256) void lora_grad_tn_kernel(TnParams batch) {
       const u32x4 v = *reinterpret_cast<const u32x4*>(p.X + (int64_t)(ok ? t : 0) * p.ldx + (ok ? col : 0));
       x[r] = ok ? v : (u32x4){0u, 0u, 0u, 0u};
     }
+    if constexpr (ROWS) {
+      const int t = step * 32 + (lane >> 1);
+      b[0] = *reinterpret_cast<const bf16x8*>(p.UT + (int64_t)min(t, p.n - 1) * p.ldu + (lane & 1) * 8);
+      if (t >= p.n) b[0] = __builtin_bit_cast(bf16x8, (u32x4){0u, 0u, 0u, 0u});
+    } else {
 #pragma unroll
-    for (int nb = 0; nb < NB; nb++) b[nb] = *reinterpret_cast<const bf16x8*>(p.UT + (int64_t)(nb * 16 + lm) * p.ldu + t0);
+      for (int nb = 0; nb < NB; nb++) b[nb] = *reinterpret_cast<const bf16x8*>(p.UT + (int64_t)(nb * 16 + lm) * p.ldu + t0);
+    }
+  };
+  // rows as they were loaded -> the operand: column lm of tokens 8 lg .. + 7 (LDS operations of a wave complete in order)
+  auto operand = [&](bf16x8& b) {
+    if constexpr (ROWS) {
+      *reinterpret_cast<bf16x8*>(mine + lane * 8) = b;
+      asm volatile("" ::: "memory");
+      const bf16_t* at = mine + (8 * lg + (lm >> 2)) * 16 + (lm & 3) * 4;
+      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4*)at);
+      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4*)(at + 64));
+      b = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      asm volatile("" ::: "memory");
+    }
   };
   auto compute = [&](const u32x4 (&x)[8], const bf16x8 (&b)[NB]) {
 #pragma unroll
@@ -105,9 +129,11 @@ __global__ __launch_bounds__(256) void lora_grad_tn_kernel(TnParams batch) {
   if (step < s_end) load(step, xa, ba);
   for (; step < s_end; step += 2) {
     if (step + 1 < s_end) load(step + 1, xb, bb);
+    operand(ba[0]);
     compute(xa, ba);
     if (step + 1 >= s_end) break;
     if (step + 2 < s_end) load(step + 2, xa, ba);
+    operand(bb[0]);
     compute(xb, bb);
   }
   // accumulator row 4*lg + i of MFMA q is column c0 + 8*(4*lg + i) + q; its column is j = nb*16 + lm
@@ -163,7 +189,8 @@ size_t tn_grad_partial_floats(int n, const int* M, int items, int r) {
   return items ? (size_t)tn_splits(n, blocks, items) * cols * r : 0;
 }
 
-// C[m * sm + j * sj] = alpha * sum_t X[t, m] * UT[j, t] for every product of the batch;  r <= 64, M a multiple of 8, ldx a multiple of 8.
+bool tn_grads_take_rows(int r) { return r <= 16; }
+// C[m * sm + j * sj] = alpha * sum_t X[t, m] * U[t, j] for every product of the batch, U as rows or token-major (tn_grads_take_rows);  r <= 64, M a multiple of 8, ldx a multiple of 8.
 int launch_tn_grads(as_ctx* ctx, TnGradBatch b, int n, int r, float* partial, size_t partial_floats, hipStream_t st) {
   if (n <= 0 || b.n <= 0 || r <= 0) return AS_OK;
   if (r > 64 || (b.ldu % 8) || ((uintptr_t)partial % 16)) return as_fail(ctx, AS_ERR_SHAPE, "lora_grad_tn: rank <= 64 and 8-element alignment needed");

@@ -255,3 +255,14 @@ def test_adapter_products_side_by_side(targets, tokens, d, heads, kv, ffn, bf16)
     cuts = [0, tokens // 3, tokens]
     trajs = [[(1, g.integers(0, sh.vocab, size=3).astype(np.int32)), (2, g.integers(0, sh.vocab, size=e - b - 3).astype(np.int32))] for b, e in zip(cuts, cuts[1:])]
     G.compare_step(sh, 2, trajs, 1, tokens, bf16=bf16, loss_tol=2e-3 if bf16 else 1e-4, grad_tol=3e-2 if bf16 else 1e-4)
+
+
+@pytest.mark.parametrize("tokens, rank", [(4, 16), (31, 1), (32, 16), (33, 15), (97, 16), (97, 17), (2049, 8)])
+def test_adapter_gradients_around_their_32_token_steps(tokens, rank):
+    """Up to rank 16 the kernel reads u and du as rows, past it as token-major copies; a last step may hold one token."""
+    import gpu_util as G
+    sh = synth.CONFIGS[1].replace(n_layers=1, d_model=128, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=192, vocab=256, lora_rank=rank, lora_alpha=2.0 * rank,
+                                  lora_targets=synth.DENSE_TARGETS7)
+    g = synth.rng(8, tokens)
+    trajs = [[(1, g.integers(0, sh.vocab, size=1).astype(np.int32)), (2, g.integers(0, sh.vocab, size=tokens - 1).astype(np.int32))]]
+    G.compare_step(sh, 3, trajs, 1, tokens, bf16=True, loss_tol=2e-3, grad_tol=3e-2)
