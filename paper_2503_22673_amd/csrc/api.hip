@@ -234,7 +234,7 @@ struct LoraSlot {       // prepared copies of one adapter (type T)
   void *At = nullptr;   // [din, group_cols] column block of the group transpose
   void *Bs = nullptr;   // [dout, rp]  = scale * B, zero padded
   void *Bst = nullptr;  // [rp, dout]
-  void *frag = nullptr; // gate, up: Bst, down: A, in the operand order of the SwiGLU kernels' products (or NULL)
+  void *fragA = nullptr, *fragB = nullptr;   // A (over din) and B (over dout) in the operand order of the row kernels, rank up to 16 (or NULL)
   int slot = 0;         // position inside its group (qkv / o / gate-up / down)
 };
 
@@ -406,7 +406,10 @@ static void make_plan(const as_ctx* ctx, int64_t rows, int64_t row_len, Bump& w,
                          s.At = P.At_gu[l] ? (char*)P.At_gu[l] + (size_t)s.slot * rp * es : nullptr; }
       else { s.slot = 0; s.A = w.take(rp * s.din * es); s.At = w.take((size_t)s.din * rp * es); }
       s.Bs = w.take((size_t)s.dout * rp * es); s.Bst = w.take(rp * s.dout * es);
-      if ((t == AS_T_GATE || t == AS_T_UP || t == AS_T_DOWN) && swiglu_adapter_ok(c.mode, P.N, c.ffn, c.lora_rank, {})) s.frag = w.take((size_t)c.ffn * 16 * es);
+      if (adapter_rows_ok(c.mode, c.lora_rank, 0, {})) {
+        if (s.din % 64 == 0) s.fragA = w.take((size_t)s.din * 16 * es);
+        if (s.dout % 64 == 0) s.fragB = w.take((size_t)s.dout * 16 * es);
+      }
       if (l == 0) {
         int r = c.lora_rank;
         part = std::max(part, (size_t)pick_splitk(c.mode, s.dout, r, P.N) * s.dout * r);
@@ -524,15 +527,35 @@ struct Step {
     return launch_gemm_off(ctx, mode, gv, g, 0, st);
   }
 
+  // u = x A^T of the adapters among `tgt`, their rp columns side by side in u; Acat: their A below one another
+  int adapter_u(int l, const int* tgt, int nt, const void* x, int din, const void* Acat, void* u, int64_t ldu) {
+    AdapterRows p{}; int k = 0;
+    bool rows = adapter_rows_ok(mode, c.lora_rank, din, {x});
+    for (int i = 0; i < nt; i++) {
+      const LoraSlot& s = slot(l, tgt[i]);
+      if (!s.on) continue;
+      rows = rows && s.fragA;
+      p.x[k] = x; p.frag[k] = s.fragA; p.K[k] = din; p.u[k++] = off(u, (size_t)s.slot * P.rp);
+    }
+    if (!k) return AS_OK;
+    if (rows) { p.ldx = din; p.ldu = ldu; p.n = P.N; p.rp = P.rp; return launch_adapter_rows(ctx, p, k, true, st); }
+    return gemm(P.N, k * P.rp, x, din, Acat, din, din, nullptr, 0, nullptr, 0, 0, nullptr, 0, u, ldu);
+  }
+
   // du = s dY B of the adapters among `tgt`, whose output gradients are columns coff[i] .. + nout[i] of dy: their columns of du side by side
   int adapter_du(int l, const int* tgt, int nt, const void* dy, int64_t lddy, const int* coff, const int* nout, void* du, int64_t ldu) {
     GemmParams g; memset(&g, 0, sizeof g);
+    AdapterRows p{};
+    bool rows = adapter_rows_ok(mode, c.lora_rank, lddy, {dy});
     for (int i = 0; i < nt; i++) {
       const LoraSlot& s = slot(l, tgt[i]);
       if (!s.on) continue;
       const int k = g.nbat++;
+      rows = rows && s.fragB && coff[i] % 8 == 0;
+      p.x[k] = off(dy, coff[i]); p.frag[k] = s.fragB; p.K[k] = nout[i]; p.u[k] = off(du, (size_t)s.slot * P.rp);
       g.bt_A[k] = off(dy, coff[i]); g.bt_B[k] = s.Bst; g.bt_K[k] = nout[i]; g.bt_C[k] = off(du, (size_t)s.slot * P.rp);
     }
+    if (rows) { p.ldx = lddy; p.ldu = ldu; p.n = P.N; p.rp = P.rp; return launch_adapter_rows(ctx, p, g.nbat, false, st); }
     g.seg[0].lda = lddy; g.nseg = 1; g.M = P.N; g.N = P.rp; g.ldc = ldu; g.alpha = 1.f; g.splitk = 1;
     g.tail_part = P.gemm_tail;
     return launch_gemm_batch(ctx, mode, g, st);
@@ -554,9 +577,9 @@ struct Step {
         if (!sl.on) continue;
         int64_t ld_at = (t <= AS_T_V) ? (int64_t)P.n_qkv * rp : (t == AS_T_GATE || t == AS_T_UP) ? (int64_t)P.n_gu * rp : rp;
         // A [r, din] -> A copy [rp, din] and its transpose block [din, rp] inside a [din, group] matrix
-        add(Lr.a[t], r, sl.din, rp, sl.din, 1.f, sl.A, sl.din, sl.At, ld_at, t == AS_T_DOWN ? sl.frag : nullptr, 1);
+        add(Lr.a[t], r, sl.din, rp, sl.din, 1.f, sl.A, sl.din, sl.At, ld_at, sl.fragA, 1);
         // B [dout, r] -> s*B [dout, rp] and transpose [rp, dout]
-        add(Lr.b[t], sl.dout, r, sl.dout, rp, s, sl.Bs, rp, sl.Bst, sl.dout, t != AS_T_DOWN ? sl.frag : nullptr, 0);
+        add(Lr.b[t], sl.dout, r, sl.dout, rp, s, sl.Bs, rp, sl.Bst, sl.dout, sl.fragB, 0);
       }
     }
     return batches.finish();
@@ -569,7 +592,8 @@ struct Step {
     int rc;
     if ((rc = launch_rmsnorm_fwd(ctx, mode, N, d, h_in, nullptr, nullptr, w.g1, c.rms_eps, a.a, a.rstd1, st))) return rc;
     const int ldu = P.n_qkv * rp;
-    if (P.n_qkv && (rc = gemm(N, ldu, a.a, d, P.A_qkv[l], d, d, nullptr, 0, nullptr, 0, 0, nullptr, 0, a.u_qkv, ldu))) return rc;
+    { const int tq[3] = {AS_T_Q, AS_T_K, AS_T_V};
+      if ((rc = adapter_u(l, tq, 3, a.a, d, P.A_qkv[l], a.u_qkv, ldu))) return rc; }
     const void* wq[3] = {w.wq, w.wk, w.wv}; const float* aq[3] = {w.aq, w.ak, w.av};
     const int nout[3] = {D, Dkv, Dkv}; const int coff[3] = {0, D, D + Dkv};
     const int tq[3] = {AS_T_Q, AS_T_K, AS_T_V};
@@ -590,13 +614,15 @@ struct Step {
     ap.order_q = P.order_q; ap.order_k = P.order_k;
     if ((rc = launch_attention_fwd(ctx, mode, av, ap, st))) return rc;
     { LoraSlot& s = slot(l, AS_T_O);
-      if (s.on && (rc = gemm(N, rp, a.o, D, s.A, D, D, nullptr, 0, nullptr, 0, 0, nullptr, 0, a.u_o, rp))) return rc;
+      const int to = AS_T_O;
+      if ((rc = adapter_u(l, &to, 1, a.o, D, s.A, a.u_o, rp))) return rc;
       rows_cap_once = P.cap;
       if ((rc = gemm(N, d, a.o, D, dense(w.wo, w.ao, d, D), D, D, s.on ? a.u_o : nullptr, rp, s.Bs, rp, s.on ? rp : 0, h_in, d, a.h_mid, d))) return rc; }
     if ((rc = launch_rmsnorm_fwd(ctx, mode, N, d, a.h_mid, nullptr, nullptr, w.g2, c.rms_eps, a.b, a.rstd2, st))) return rc;
     if (c.n_experts) return forward_moe(l, a);
     const int ldg = P.n_gu * rp;
-    if (P.n_gu && (rc = gemm(N, ldg, a.b, d, P.A_gu[l], d, d, nullptr, 0, nullptr, 0, 0, nullptr, 0, a.u_gu, ldg))) return rc;
+    { const int tu[2] = {AS_T_GATE, AS_T_UP};
+      if ((rc = adapter_u(l, tu, 2, a.b, d, P.A_gu[l], a.u_gu, ldg))) return rc; }
     const void* wg[2] = {w.wgate, w.wup}; const float* ag[2] = {w.agate, w.aup};
     const int tg[2] = {AS_T_GATE, AS_T_UP}; const int ng[2] = {F, F};
     if (side_by_side_ok(l, tg, 2)) {
@@ -610,9 +636,10 @@ struct Step {
       if (rc) return rc;
     }
     { LoraSlot& s = slot(l, AS_T_DOWN);
-      const bool with_u = s.on && s.frag && swiglu_adapter_ok(mode, N, F, c.lora_rank, {a.gu, a.m});
-      if ((rc = with_u ? launch_swiglu_fwd_adapter(ctx, N, F, a.gu, a.m, s.frag, rp, a.u_d, st) : launch_swiglu_fwd(ctx, mode, N, F, a.gu, a.m, st))) return rc;
-      if (s.on && !with_u && (rc = gemm(N, rp, a.m, F, s.A, F, F, nullptr, 0, nullptr, 0, 0, nullptr, 0, a.u_d, rp))) return rc;
+      const bool with_u = s.on && s.fragA && swiglu_adapter_ok(mode, N, F, c.lora_rank, {a.gu, a.m});
+      if ((rc = with_u ? launch_swiglu_fwd_adapter(ctx, N, F, a.gu, a.m, s.fragA, rp, a.u_d, st) : launch_swiglu_fwd(ctx, mode, N, F, a.gu, a.m, st))) return rc;
+      const int td = AS_T_DOWN;
+      if (!with_u && (rc = adapter_u(l, &td, 1, a.m, F, s.A, a.u_d, rp))) return rc;
       rows_cap_once = P.cap;
       if ((rc = gemm(N, d, a.m, F, dense(w.wdown, w.adown, d, F), F, F, s.on ? a.u_d : nullptr, rp, s.Bs, rp, s.on ? rp : 0, a.h_mid, d, h_out, d))) return rc; }
     return AS_OK;
@@ -693,7 +720,8 @@ struct Step {
     const int N = P.N, d = P.d, F = P.F, rp = P.rp, E = c.n_experts;
     int rc;
     LoraSlot& s = slot(l, AS_T_ROUTER);
-    if (s.on && (rc = gemm(N, rp, a.b, d, s.A, d, d, nullptr, 0, nullptr, 0, 0, nullptr, 0, a.u_r, rp))) return rc;
+    const int tr = AS_T_ROUTER;
+    if ((rc = adapter_u(l, &tr, 1, a.b, d, s.A, a.u_r, rp))) return rc;
     if ((rc = gemm(N, E, a.b, d, w.wrouter, d, d, s.on ? a.u_r : nullptr, rp, s.Bs, rp, s.on ? rp : 0, nullptr, 0, a.rl, E, 1))) return rc;
     if ((rc = launch_moe_route(ctx, a.rl, N, E, a.sel, a.wsel, st))) return rc;
     if ((rc = launch_moe_permute(ctx, a.sel, N, E, a.eoff, a.pos, a.perm, st))) return rc;
@@ -870,14 +898,15 @@ struct Step {
     // ---- down projection
     bool with_du = false;                                  // du of gate and up came with the SwiGLU backward
     { LoraSlot& s = slot(l, AS_T_DOWN);
-      if (s.on && (rc = gemm(N, rp, P.dh, d, s.Bst, d, d, nullptr, 0, nullptr, 0, 0, nullptr, 0, P.du_d, rp))) return rc;
+      const int td = AS_T_DOWN, zero = 0;
+      if ((rc = adapter_du(l, &td, 1, P.dh, d, &zero, &d, P.du_d, rp))) return rc;
       rows_cap_once = P.cap;
       if ((rc = gemm_dx(N, F, P.dh, d, {{w.wdown, w.adown, d}}, s.on ? P.du_d : nullptr, rp, s.A, s.At, rp, s.on ? rp : 0, P.dm, F))) return rc;
       // ---- SwiGLU (in recompute mode 2 it also rewrites the forward product, which the gradients below need)
       const bool rewrite_m = c.recompute == 2 && l != c.n_layers - 1 && (full || s.on);
       LoraSlot &sg = slot(l, AS_T_GATE), &su = slot(l, AS_T_UP);
-      with_du = sg.on && su.on && sg.frag && su.frag && swiglu_adapter_ok(mode, N, F, c.lora_rank, {P.dm, a.gu, P.dgu, a.m});
-      if (with_du) rc = launch_swiglu_bwd_adapter(ctx, N, F, P.dm, a.gu, P.dgu, rewrite_m ? a.m : nullptr, sg.frag, su.frag, rp, P.du_gu, st);
+      with_du = sg.on && su.on && sg.fragB && su.fragB && swiglu_adapter_ok(mode, N, F, c.lora_rank, {P.dm, a.gu, P.dgu, a.m});
+      if (with_du) rc = launch_swiglu_bwd_adapter(ctx, N, F, P.dm, a.gu, P.dgu, rewrite_m ? a.m : nullptr, sg.fragB, su.fragB, rp, P.du_gu, st);
       else rc = launch_swiglu_bwd(ctx, mode, N, F, P.dm, a.gu, P.dgu, rewrite_m ? a.m : nullptr, st);
       if (rc) return rc;
       if (s.on && !tn_path()) {
@@ -911,7 +940,8 @@ struct Step {
     if ((rc = norm_bwd(P.db, nullptr, a.h_mid, w.g2, a.rstd2, P.dh, P.dh2, full ? G->w_layers[l].g2 : nullptr))) return rc;
     // ---- output projection
     { LoraSlot& s = slot(l, AS_T_O);
-      if (s.on && (rc = gemm(N, rp, P.dh2, d, s.Bst, d, d, nullptr, 0, nullptr, 0, 0, nullptr, 0, P.du_o, rp))) return rc;
+      const int to = AS_T_O, zero = 0;
+      if ((rc = adapter_du(l, &to, 1, P.dh2, d, &zero, &d, P.du_o, rp))) return rc;
       rows_cap_once = P.cap;
       if ((rc = gemm_dx(N, D, P.dh2, d, {{w.wo, w.ao, d}}, s.on ? P.du_o : nullptr, rp, s.A, s.At, rp, s.on ? rp : 0, P.d_o, D))) return rc;
       if (s.on && !tn_path()) {

@@ -211,6 +211,11 @@ bool swiglu_adapter_ok(int mode, int n, int F, int r, std::initializer_list<cons
 int launch_swiglu_fwd_adapter(as_ctx* ctx, int n, int F, const void* gu, void* m, const void* fragA, int rp, void* u, hipStream_t st);
 int launch_swiglu_bwd_adapter(as_ctx* ctx, int n, int F, const void* dm, const void* gu, void* dgu, void* m_out, const void* fragBg, const void* fragBu, int rp, void* du,
                               hipStream_t st);
+// products of token rows with adapters of rank up to 16: u[i] [n, rp columns, rows of ldu] = x[i] [n, K[i], rows of ldx] times the adapter frag[i] (PrepMatrix::frag);
+// one_x: all on x[0].  K in multiples of 64
+struct AdapterRows { const void* x[3]; const void* frag[3]; void* u[3]; int K[3]; int64_t ldx, ldu; int n, rp; };
+bool adapter_rows_ok(int mode, int r, int64_t ldx, std::initializer_list<const void*> ptrs);
+int launch_adapter_rows(as_ctx* ctx, const AdapterRows& p, int items, bool one_x, hipStream_t st);
 // out[c, r] = in[r, c] for r < rows_pad, reading zero for r >= rows (and, with rows_dev, for rows at
 // or past *rows_dev - row_off)
 int launch_transpose(as_ctx* ctx, int mode, int rows, int rows_pad, int cols, const void* in, int64_t ldi, void* out,

@@ -688,6 +688,93 @@ __global__ __launch_bounds__(512) void swiglu_adapter_kernel(int n, int F, const
     if (row0 + t < n) ad.u[(int64_t)(row0 + t) * (MT * ad.rp) + p * ad.rp + j] = (bf16_t)v;
   }
 }
+// Products of token rows with adapters of rank up to 16, in the same manner: u = x A^T, du = dY B.  NB adapters on one x (q, k, v; gate, up), or (NB = 1) up
+// to three of their own, one per blockIdx.y.  Columns past 16 of an adapter's rp are written as zeros.
+// As narrow GEMMs through LDS tiles (64 columns computed for 16, the sum of a split contraction a second launch) the products of two 1B layers took 432 us at
+// 24,710 tokens and 206 at 626; 300 and 103 so (24,710 x 2048: 24 us, 4.3 TB/s of the rows).  Steps: 626 tokens 1.292 -> 1.215 ms, 24,710 15.25 -> 15.10.
+template <int NB, int NW>
+__global__ __launch_bounds__(64 * NW) void adapter_rows_kernel(const AdapterRows p) {
+  __shared__ __align__(16) unsigned char smem[NW * (NB > 2 ? NB * 1024 : 2048)];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, q = lane >> 4, r8 = lane >> 3, ch = lane & 7;
+  const int item = blockIdx.y, row0 = blockIdx.x * 16;
+  const bf16_t* x = (const bf16_t*)(item == 0 ? p.x[0] : item == 1 ? p.x[1] : p.x[2]);
+  const bf16_t* f0 = (const bf16_t*)(item == 0 ? p.frag[0] : item == 1 ? p.frag[1] : p.frag[2]);
+  const int steps = (item == 0 ? p.K[0] : item == 1 ? p.K[1] : p.K[2]) / 64;
+  const bf16_t* xr[2];
+#pragma unroll
+  for (int h = 0; h < 2; h++) xr[h] = x + (int64_t)min(row0 + 8 * h + r8, p.n - 1) * p.ldx + ch * 8;
+  unsigned char* my = smem + wave * 2048;
+  f32x4 acc[NB] = {};
+  constexpr int AHEAD = 2;                                 // steps whose operands are under way
+  struct Operands { bf16x8 x[2], w[NB][2]; };
+  auto load = [&](int s, Operands& v) {
+#pragma unroll
+    for (int h = 0; h < 2; h++) v.x[h] = *reinterpret_cast<const bf16x8*>(xr[h] + s * 64);
+#pragma unroll
+    for (int b = 0; b < NB; b++)
+#pragma unroll
+      for (int k = 0; k < 2; k++) v.w[b][k] = *reinterpret_cast<const bf16x8*>((b == 0 ? f0 : (const bf16_t*)p.frag[b]) + (int64_t)(2 * s + k) * 512 + lane * 8);
+  };
+  auto step = [&](const Operands& v) {
+#pragma unroll
+    for (int h = 0; h < 2; h++) *reinterpret_cast<bf16x8*>(my + (h * 8 + r8) * 128 + ((ch ^ r8) * 16)) = v.x[h];
+    asm volatile("" ::: "memory");                         // LDS operations of a wave complete in order
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+      const bf16x8 a = *reinterpret_cast<const bf16x8*>(my + l15 * 128 + (((k * 4 + q) ^ (l15 & 7)) * 16));
+#pragma unroll
+      for (int b = 0; b < NB; b++) acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, v.w[b][k], acc[b], 0, 0, 0);
+    }
+    asm volatile("" ::: "memory");
+  };
+  Operands v[AHEAD];
+  int s = wave;
+#pragma unroll
+  for (int i = 0; i < AHEAD; i++) if (s + i * NW < steps) load(s + i * NW, v[i]);
+  for (; s < steps; s += AHEAD * NW) {
+#pragma unroll
+    for (int i = 0; i < AHEAD; i++)
+      if (s + i * NW < steps) {
+        step(v[i]);
+        if (s + (i + AHEAD) * NW < steps) load(s + (i + AHEAD) * NW, v[i]);
+      }
+  }
+  // the waves' sums in wave order
+  f32x4 (*red)[NB][64] = reinterpret_cast<f32x4 (*)[NB][64]>(smem);
+  __syncthreads();
+#pragma unroll
+  for (int b = 0; b < NB; b++) red[wave][b][lane] = acc[b];
+  __syncthreads();
+  for (int o = threadIdx.x; o < 16 * NB * p.rp; o += 64 * NW) {             // token t is element t % 4 of lane 16 (t / 4) + rank index
+    const int t = o / (NB * p.rp), b = o / p.rp % NB, j = o % p.rp;
+    float sum = 0.f;
+    if (j < 16)
+      for (int w = 0; w < NW; w++) sum += red[w][b][(t >> 2) * 16 + j][t & 3];
+    bf16_t* u = (bf16_t*)(NB == 1 ? (item == 0 ? p.u[0] : item == 1 ? p.u[1] : p.u[2]) : b == 0 ? p.u[0] : b == 1 ? p.u[1] : p.u[2]);
+    if (row0 + t < p.n) u[(int64_t)(row0 + t) * p.ldu + j] = (bf16_t)sum;
+  }
+}
+bool adapter_rows_ok(int mode, int r, int64_t ldx, std::initializer_list<const void*> ptrs) {
+  uintptr_t x = 0;
+  for (const void* p : ptrs) x |= (uintptr_t)p;
+  return mode == AS_BF16 && r <= kSwigluRank && ldx % 8 == 0 && x % 16 == 0;
+}
+int launch_adapter_rows(as_ctx* ctx, const AdapterRows& p, int items, bool one_x, hipStream_t st) {
+  if (p.n <= 0 || items < 1) return AS_OK;
+  const dim3 g((unsigned)cdiv(p.n, 16), one_x ? 1 : items);
+  const bool wide = (int64_t)g.x * g.y < 512;              // under two workgroups of eight waves a CU: sixteen
+  double flops = 0;
+  for (int i = 0; i < items; i++) flops += 2.0 * p.n * 64 * p.K[one_x ? 0 : i];
+  auto go = [&](auto nb) { if (wide) adapter_rows_kernel<nb(), 16><<<g, 1024, 0, st>>>(p); else adapter_rows_kernel<nb(), 8><<<g, 512, 0, st>>>(p); };
+  prof_begin(ctx, st, AS_K_GEMM_MFMA_SKINNY, flops);
+  if (!one_x || items == 1) go(std::integral_constant<int, 1>());
+  else if (items == 2) go(std::integral_constant<int, 2>());
+  else go(std::integral_constant<int, 3>());
+  prof_end(ctx, st);
+  AS_LAUNCH_CHECK(ctx);
+  return AS_OK;
+}
+
 bool swiglu_adapter_ok(int mode, int n, int F, int r, std::initializer_list<const void*> ptrs) {
   uintptr_t x = 0;
   for (const void* p : ptrs) x |= (uintptr_t)p;

@@ -266,3 +266,21 @@ def test_adapter_gradients_around_their_32_token_steps(tokens, rank):
     g = synth.rng(8, tokens)
     trajs = [[(1, g.integers(0, sh.vocab, size=1).astype(np.int32)), (2, g.integers(0, sh.vocab, size=tokens - 1).astype(np.int32))]]
     G.compare_step(sh, 3, trajs, 1, tokens, bf16=True, loss_tol=2e-3, grad_tol=3e-2)
+
+
+@pytest.mark.parametrize("tokens, d, heads, kv, ffn, targets", [
+    (17, 64, 1, 1, 64, synth.DENSE_TARGETS7),              # one 64-wide step of the contraction, a workgroup of one token
+    (300, 1088, 17, 1, 2112, synth.DENSE_TARGETS7),        # more steps than waves, contractions of different lengths side by side
+    (8200, 128, 2, 1, 192, synth.DENSE_TARGETS7),          # eight waves
+    (300, 128, 2, 2, 200, synth.DENSE_TARGETS7),           # an FFN that is no multiple of 64: its adapters as narrow products
+    (300, 128, 2, 2, 192, ("q", "v", "up")),               # two of three, one of two
+])
+def test_adapter_products_from_rows(tokens, d, heads, kv, ffn, targets):
+    """u = x A^T and du = dY B of rank up to 16."""
+    import gpu_util as G
+    sh = synth.CONFIGS[1].replace(n_layers=2, d_model=d, n_q_heads=heads, n_kv_heads=kv, head_dim=64, ffn=ffn, vocab=512, lora_rank=13, lora_alpha=26.0,
+                                  lora_targets=targets)
+    g = synth.rng(9, tokens)
+    cuts = [tokens * i // 8 for i in range(9)]
+    trajs = [[(1, g.integers(0, sh.vocab, size=1).astype(np.int32)), (2, g.integers(0, sh.vocab, size=e - b - 1).astype(np.int32))] for b, e in zip(cuts, cuts[1:])]
+    G.compare_step(sh, 4, trajs, 1, tokens, bf16=True, loss_tol=2e-3, grad_tol=3e-2)
