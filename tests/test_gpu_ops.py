@@ -330,6 +330,31 @@ def test_attention_head_dim_64_at_tile_edges(Hq, Hkv, lens):
         assert grad_norm_err(x, r.reshape(n, -1)) < tol
 
 
+@pytest.mark.parametrize("Hkv", [64, 32, 16])
+def test_attention_backward_head_dim_64_in_one_launch_and_in_two(Hkv):
+    """64 heads: 3072 tokens are the last that dQ and dK / dV share a launch for (two rounds of dK / dV workgroups), 3073 the first of two launches.
+    The token more is a segment of its own, so the others' gradients must agree, and both with the oracle (tolerance as above)."""
+    Hq, dh, tol = 64, 64, 2.0 ** -6
+    B, G, ctx, sh = _env(n_q_heads=Hq, n_kv_heads=Hkv, head_dim=dh)
+    lens = [600, 65, 255, 1, 511, 640, 1000, 1]
+    g, cu, n = _attn_case(21, len(lens), Hq, Hkv, dh, lens)
+    assert n == 3073
+    q, k, v, do = (G.quantise(g.standard_normal((n, H, dh)), True) for H in (Hq, Hkv, Hkv, Hq))
+    o_ref, probs = om.attention(q, k, v, cu, Hq // Hkv)
+    refs = om.attention_bwd(do, q, k, v, o_ref, probs, cu, Hq // Hkv)
+    seg = om.segment_ids(cu, n)
+    D, Dkv, got = Hq * dh, Hkv * dh, []
+    for m in (n, n - 1):
+        seg_start, seg_end = (torch.from_numpy(cu[seg[:m] + e].astype(np.int32)).cuda() for e in (0, 1))
+        qkv_d = G.to_dev(np.concatenate([x[:m].reshape(m, -1) for x in (q, k, v)], axis=1), torch.bfloat16)
+        _, lse = ctx.op_attention_fwd(qkv_d, seg_start, variant=2, mode=B.AS_BF16)
+        o_in, do_in = (G.to_dev(x[:m].reshape(m, -1), torch.bfloat16) for x in (o_ref, do))
+        got.append(G.to_np(ctx.op_attention_bwd(qkv_d, seg_start, seg_end, o_in, lse, do_in, variant=2, mode=B.AS_BF16)))
+        for x, r in zip(np.split(got[-1], [D, D + Dkv], axis=1), refs):
+            assert grad_norm_err(x, r[:m].reshape(m, -1)) < tol
+    assert np.array_equal(got[0][:n - 1], got[1])
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("Hq,Hkv,dh", [(2, 2, 32), (8, 2, 32), (2, 1, 64), (4, 1, 128)])
 def test_plain_attention_around_one_wave_and_one_workgroup_of_rows(Hq, Hkv, dh, bf16):
