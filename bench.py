@@ -23,9 +23,9 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
 # HBM-side bytes per launch of the dominant kernel at config 3: FETCH_SIZE and WRITE_SIZE of two counter runs over one
 # bench step, each scaled by what the counter reads for a 1 GiB copy (profiles/bench_config3_counters.md).  The figure
 # belongs to the kernel sources those runs saw: the digest below names them, and the line reports null when they differ.
-TRAFFIC_BYTES_PER_LAUNCH = {(3, "gemm_mfma_rd_kernel<0, 0, *>"): 15.20e9}
+TRAFFIC_BYTES_PER_LAUNCH = {(3, "gemm_mfma_rd_kernel<0, 0, *>"): 15.23e9}
 TRAFFIC_SOURCES = ("gemm.hip", "gemm_items.h", "gemm_rd_loop.inc", "gemm_rd_nn_loop.inc", "common.h")
-TRAFFIC_SOURCE_DIGEST = "9b481c61f83fa2a1"
+TRAFFIC_SOURCE_DIGEST = "55094958fd72fdc9"
 DOMINANT_KERNEL = "gemm_mfma_rd_kernel<0, 0, *>"               # dense models; expert GEMMs: the same kernel with live-row limits, <1>
 GROUPED_KERNEL = "gemm_mfma_rd_kernel<1, 0, *>"
 
@@ -96,10 +96,10 @@ def algorithmic_flops(sh, seg_lens_nonpad, n_nonpad, n_targets, dpo=False):
     dims = synth.lora_dims(sh)
     lora = 6.0 * r * sum(sum(dims[t]) for t in sh.lora_targets) * L * n_nonpad
     head = (6.0 if sh.full_ft else 4.0) * d * V * n_targets
-    if dpo:     # forward of the frozen reference policy (no adapters), and the first of the two passes over the head
+    if dpo:     # forward of the frozen reference policy (no adapters)
         dense += 2.0 * L * p_layer * n_nonpad
         attn += 2.0 * D * L * float(sum(x * x for x in seg_lens_nonpad))
-        head += 2.0 * 2.0 * d * V * n_targets
+        head += 2.0 * d * V * n_targets
     recompute = 0.0
     if sh.recompute == 1:
         recompute = (2.0 * p_layer * n_nonpad + 2.0 * D * float(sum(x * x for x in seg_lens_nonpad)) +
