@@ -561,12 +561,23 @@ struct Step {
     return launch_gemm_batch(ctx, mode, g, st);
   }
 
-  // type T copies of every adapter and their transposes, as many matrices per launch as a kernel argument holds
-  int prep_lora() {
+  // What comes before the first layer: segments, rotary table, embedding, and type T copies of every adapter (adapters: there are any to copy) and
+  // their transposes, as many matrices per launch as a kernel argument holds, the first of them in the launch of all the rest
+  int begin(const StepBegin& sb, bool adapters) {
+    bool begun = false;
+    auto launch = [&](const PrepBatch& b) {
+      if (begun) return launch_lora_prep_batch(ctx, mode, b, st);
+      begun = true;
+      return launch_step_begin(ctx, mode, sb, b, st);
+    };
+    if (adapters) { const int rc = prep_lora(launch); if (rc || begun) return rc; }
+    PrepBatch none; memset(&none, 0, sizeof none);
+    return launch(none);
+  }
+  template <typename L> int prep_lora(const L& launch) {
     const float s = c.lora_alpha / (float)c.lora_rank;
     const int r = c.lora_rank, rp = P.rp;
-    auto launch = [&](const PrepBatch& b) { return launch_lora_prep_batch(ctx, mode, b, st); };
-    BatchedLaunches<PrepBatch, kPrepBatch, decltype(launch)> batches(1 << 22, launch);
+    BatchedLaunches<PrepBatch, kPrepBatch, L> batches(1 << 22, launch);
     auto add = [&](const float* in, int rows, int cols, int rows_pad, int cols_pad, float scale, void* out, int64_t ldo, void* out_t, int64_t ldo_t, void* frag, int rank_rows) {
       batches.add(PrepMatrix{in, out, out_t, ldo, ldo_t, rows, cols, rows_pad, cols_pad, scale, 0, frag, rank_rows}, cdiv(rows_pad, 64) * cdiv(cols_pad, 64));
     };
@@ -1273,12 +1284,11 @@ static int run_step(as_ctx* ctx, const char* who, const as_weights* weights, con
     }
     return S.zero_outputs(d_loss, d_loss_sum, d_count);
   }
-  if ((rc = launch_segment_info(ctx, d_cu_eff, n_seg_eff, d_loss_mask, n, P.seg_start, P.seg_end, P.block_targets, st))) return rc;
-  if ((rc = launch_rope_table(ctx, max_seg, c.head_dim, c.rope_base, P.rope_cos, P.rope_sin, st))) return rc;
+  const StepBegin sb{d_cu_eff, n_seg_eff, d_loss_mask, n, P.seg_start, P.seg_end, P.block_targets, max_seg, c.head_dim, c.rope_base, P.rope_cos, P.rope_sin,
+                     d_tokens, c.d_model, weights->embed, P.h[0], 0};
+  if ((rc = S.begin(sb, !full && !adapters_off))) return rc;
   if ((rc = launch_select_targets(ctx, P.seg_end, P.block_targets, d_loss_mask, d_tokens, n, P.tgt_idx, P.tgt_pos, P.labels, d_count, st))) return rc;
   P.count = d_count;
-  if (!full && !adapters_off && (rc = S.prep_lora())) return rc;
-  if ((rc = launch_embed(ctx, c.mode, d_tokens, n, c.d_model, weights->embed, P.h[0], st))) return rc;
   for (int l = 0; l < c.n_layers; l++)
     if ((rc = S.forward_layer(l, P.acts[c.recompute == 1 ? 0 : l]))) return rc;
   if ((rc = S.head_and_loss(d_loss, d_loss_sum))) return rc;

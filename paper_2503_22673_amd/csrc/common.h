@@ -164,12 +164,7 @@ int launch_pack(as_ctx* ctx, const int32_t* h_tokens, const int32_t* h_cu, const
 // tok_c[i], mask_c[i] = tok[src], mask[src] with src = src_start[s] + (i - cu_c[s]) for the kept segment s holding i
 int launch_compact(as_ctx* ctx, const int32_t* tok, const uint8_t* mask, const int32_t* cu_c, const int32_t* src_start,
                    int n_seg, int n, int32_t* tok_c, uint8_t* mask_c, hipStream_t st);
-// and the number of targets among every kTargetBlock tokens (mask: tokens that bear loss; a target is predicted by the token before it)
-constexpr int kTargetBlock = 256;
-int launch_segment_info(as_ctx* ctx, const int32_t* d_cu, int n_seg, const uint8_t* mask, int n, int32_t* seg_start,
-                        int32_t* seg_end, int32_t* block_targets, hipStream_t st);
-int launch_rope_table(as_ctx* ctx, int max_pos, int dh, float base, float* cosb, float* sinb, hipStream_t st);
-int launch_embed(as_ctx* ctx, int mode, const int32_t* tok, int n, int d, const void* E, void* h, hipStream_t st);
+constexpr int kTargetBlock = 256;                          // tokens of a block of StepBegin::block_targets
 int launch_rmsnorm_fwd(as_ctx* ctx, int mode, int n, int d, const void* x, const int32_t* row_idx,
                        const int* n_dev, const void* g, float eps, void* y, float* rstd, hipStream_t st);
 // dx[t] = vjp(dy[row_of(t)]) + add[t]; src_pos (optional) maps t -> row of dy or -1 (then dx = add or 0)
@@ -234,6 +229,14 @@ constexpr int kPrepBatch = 40;                             // a batch is a kerne
 
 struct PrepBatch { PrepMatrix m[kPrepBatch]; int n, n_tiles; };
 int launch_lora_prep_batch(as_ctx* ctx, int mode, const PrepBatch& b, hipStream_t st);
+// What a step needs before its first layer: a token's segment, the number of targets among every kTargetBlock tokens (mask: tokens that bear
+// loss; a target is predicted by the token before it), the rotary table, the embedded tokens, and a batch of adapters (b.n may be 0)
+struct StepBegin {
+  const int32_t* cu; int n_seg; const uint8_t* mask; int n; int32_t *seg_start, *seg_end, *block_targets;
+  int max_pos, dh; double rope_base; float *cosb, *sinb;
+  const int32_t* tok; int d; const void* embed; void* h; int vec;
+};
+int launch_step_begin(as_ctx* ctx, int mode, const StepBegin& s, const PrepBatch& b, hipStream_t st);
 int launch_fill_zero(as_ctx* ctx, void* p, size_t bytes, hipStream_t st);
 int launch_zero_tail_rows(as_ctx* ctx, int rows, const int* n_dev, int off, void* a, int64_t lda, int ca, void* b, int64_t ldb, int cb, hipStream_t st);
 int launch_select_targets(as_ctx* ctx, const int32_t* seg_end, const int32_t* block_targets, const uint8_t* mask, const int32_t* tok,

@@ -56,54 +56,35 @@ int launch_compact(as_ctx* ctx, const int32_t* tok, const uint8_t* mask, const i
 // token t predicts a target: the next token is of the same segment and bears loss
 __device__ __forceinline__ bool predicts_target(int t, int seg_end, const uint8_t* mask) { return t + 1 < seg_end && mask[t + 1]; }
 
-__global__ __launch_bounds__(kTargetBlock) void segment_info_kernel(const int32_t* __restrict__ cu, int n_seg, const uint8_t* __restrict__ mask, int n,
-                                                                    int32_t* __restrict__ seg_start, int32_t* __restrict__ seg_end, int32_t* __restrict__ block_targets) {
-  const int t = blockIdx.x * kTargetBlock + threadIdx.x;
+__device__ __forceinline__ void segment_info_block(const StepBegin& b, int block) {      // of kTargetBlock threads
+  const int t = block * kTargetBlock + threadIdx.x;
   bool is = false;
-  if (t < n) {
-    int lo = 0, hi = n_seg - 1;             // last s with cu[s] <= t
+  if (t < b.n) {
+    int lo = 0, hi = b.n_seg - 1;           // last s with cu[s] <= t
     while (lo < hi) {
       int mid = (lo + hi + 1) >> 1;
-      if (cu[mid] <= t) lo = mid; else hi = mid - 1;
+      if (b.cu[mid] <= t) lo = mid; else hi = mid - 1;
     }
-    const int e = cu[lo + 1];
-    seg_start[t] = cu[lo];
-    seg_end[t] = e;
-    is = predicts_target(t, e, mask);
+    const int e = b.cu[lo + 1];
+    b.seg_start[t] = b.cu[lo];
+    b.seg_end[t] = e;
+    is = predicts_target(t, e, b.mask);
   }
   const int c = __syncthreads_count(is);
-  if (threadIdx.x == 0) block_targets[blockIdx.x] = c;
-}
-
-int launch_segment_info(as_ctx* ctx, const int32_t* d_cu, int n_seg, const uint8_t* mask, int n, int32_t* seg_start,
-                        int32_t* seg_end, int32_t* block_targets, hipStream_t st) {
-  if (n <= 0) return AS_OK;
-  segment_info_kernel<<<cdiv(n, kTargetBlock), kTargetBlock, 0, st>>>(d_cu, n_seg, mask, n, seg_start, seg_end, block_targets);
-  AS_LAUNCH_CHECK(ctx);
-  return AS_OK;
+  if (threadIdx.x == 0) b.block_targets[block] = c;
 }
 
 // ------------------------------------------------------------------ RoPE
 // cos/sin of p * base^(-2i/dh), evaluated in double and rounded once.
-__global__ void rope_table_kernel(int max_pos, int half, int dh, double base, float* __restrict__ cosb,
-                                  float* __restrict__ sinb) {
-  int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= max_pos * half) return;
+__device__ __forceinline__ void rope_table_block(const StepBegin& b, int block) {
+  const int half = b.dh / 2, idx = block * 256 + threadIdx.x;
+  if (idx >= b.max_pos * half) return;
   int p = idx / half, i = idx % half;
-  double theta = pow(base, -2.0 * (double)i / (double)dh);
+  double theta = pow(b.rope_base, -2.0 * (double)i / (double)b.dh);
   double s, c;
   sincos((double)p * theta, &s, &c);
-  cosb[idx] = (float)c;
-  sinb[idx] = (float)s;
-}
-
-int launch_rope_table(as_ctx* ctx, int max_pos, int dh, float base, float* cosb, float* sinb, hipStream_t st) {
-  int half = dh / 2;
-  int64_t tot = (int64_t)max_pos * half;
-  if (tot <= 0) return AS_OK;
-  rope_table_kernel<<<cdiv(tot, 256), 256, 0, st>>>(max_pos, half, dh, (double)base, cosb, sinb);
-  AS_LAUNCH_CHECK(ctx);
-  return AS_OK;
+  b.cosb[idx] = (float)c;
+  b.sinb[idx] = (float)s;
 }
 
 // Rotates pairs (i, i + dh/2) of every head in place; the position of token t
@@ -175,26 +156,17 @@ int launch_rope(as_ctx* ctx, int mode, int n, int n_heads, int dh, void* x, int6
 
 // --------------------------------------------------------------- embedding
 template <typename T>
-__global__ void embed_kernel(const int32_t* __restrict__ tok, int n, int d, const T* __restrict__ E,
-                             T* __restrict__ h, int vec) {
-  int t = blockIdx.x;
-  const T* src = E + (int64_t)tok[t] * d;
-  T* dst = h + (int64_t)t * d;
-  if (vec) {
+__device__ __forceinline__ void embed_row(const StepBegin& b, int t) {
+  const int d = b.d;
+  const T* src = (const T*)b.embed + (int64_t)b.tok[t] * d;
+  T* dst = (T*)b.h + (int64_t)t * d;
+  if (b.vec) {
     constexpr int VN = Vec<T>::N;
-    for (int j = threadIdx.x * VN; j < d; j += blockDim.x * VN)
+    for (int j = threadIdx.x * VN; j < d; j += 256 * VN)
       *reinterpret_cast<typename Vec<T>::type*>(dst + j) = *reinterpret_cast<const typename Vec<T>::type*>(src + j);
   } else {
-    for (int j = threadIdx.x; j < d; j += blockDim.x) dst[j] = src[j];
+    for (int j = threadIdx.x; j < d; j += 256) dst[j] = src[j];
   }
-}
-
-int launch_embed(as_ctx* ctx, int mode, const int32_t* tok, int n, int d, const void* E, void* h, hipStream_t st) {
-  if (n <= 0) return AS_OK;
-  DISPATCH_T(mode, { int vec = vec_ok<T>(E, d) && vec_ok<T>(h, d);
-                     embed_kernel<T><<<n, 256, 0, st>>>(tok, n, d, (const T*)E, (T*)h, vec); });
-  AS_LAUNCH_CHECK(ctx);
-  return AS_OK;
 }
 
 // ----------------------------------------------------------------- RMSNorm
@@ -926,10 +898,9 @@ int launch_transpose_qs(as_ctx* ctx, int mode, int rows, int rows_pad, int cols,
 // for the 28 matrices of two 1B layers; 17.6 with its loads one after the other, 13.9 so.
 struct PrepArgs { PrepMatrix m[kPrepBatch]; int first[kPrepBatch]; };        // first: past the last matrix, past every tile
 template <typename T>
-__global__ __launch_bounds__(256) void lora_prep_kernel(const PrepArgs b) {
-  __shared__ float tile[64][65];
-  const PrepMatrix& m = b.m[table_item<kPrepBatch>(kPrepBatch, (int)blockIdx.x, [&](int k) { return b.first[k]; })];
-  const int tiles_c = (m.cols_pad + 63) / 64, t = (int)blockIdx.x - m.first_tile;
+__device__ __forceinline__ void lora_prep_tile(const PrepArgs& b, int item, float (&tile)[64][65]) {
+  const PrepMatrix& m = b.m[table_item<kPrepBatch>(kPrepBatch, item, [&](int k) { return b.first[k]; })];
+  const int tiles_c = (m.cols_pad + 63) / 64, t = item - m.first_tile;
   const int r0 = (t / tiles_c) * 64, c0 = (t % tiles_c) * 64;
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   T* out = (T*)m.out; T* out_t = (T*)m.out_t;
@@ -959,10 +930,45 @@ __global__ __launch_bounds__(256) void lora_prep_kernel(const PrepArgs b) {
   }
 }
 
-int launch_lora_prep_batch(as_ctx* ctx, int mode, const PrepBatch& b, hipStream_t st) {
-  if (b.n <= 0 || b.n_tiles <= 0) return AS_OK;
+template <typename T>
+__global__ __launch_bounds__(256) void lora_prep_kernel(const PrepArgs b) {
+  __shared__ float tile[64][65];
+  lora_prep_tile<T>(b, (int)blockIdx.x, tile);
+}
+// What a step needs before its first layer, in one launch: nothing in it reads what another part of it writes.  The tiles of the first batch of adapters
+// come first (the longest), then segments, rotary table and one workgroup per embedded row.
+// What bounds it is the latency of its longest chain: as four launches one after the other 15 us of a 478-token float step and 24 of 626 tokens of two 1B
+// layers; steps 267 -> 259 us and 1.169 -> 1.158 ms.
+template <typename T>
+__global__ __launch_bounds__(256) void step_begin_kernel(const StepBegin s, const PrepArgs b, int tiles, int seg_blocks, int rope_blocks) {
+  __shared__ float tile[64][65];
+  int block = (int)blockIdx.x;
+  if (block < tiles) { lora_prep_tile<T>(b, block, tile); return; }
+  block -= tiles;
+  if (block < seg_blocks) { segment_info_block(s, block); return; }
+  block -= seg_blocks;
+  if (block < rope_blocks) { rope_table_block(s, block); return; }
+  embed_row<T>(s, block - rope_blocks);
+}
+
+static PrepArgs prep_args(const PrepBatch& b) {
   PrepArgs a;
   for (int k = 0; k < kPrepBatch; k++) { a.m[k] = b.m[k < b.n ? k : 0]; a.first[k] = k < b.n ? b.m[k].first_tile : INT32_MAX; }
+  return a;
+}
+int launch_step_begin(as_ctx* ctx, int mode, const StepBegin& s_in, const PrepBatch& b, hipStream_t st) {
+  StepBegin s = s_in;
+  if (s.n <= 0) return AS_OK;
+  const int tiles = b.n > 0 ? b.n_tiles : 0, seg_blocks = (int)cdiv(s.n, kTargetBlock), rope_blocks = (int)cdiv((int64_t)s.max_pos * (s.dh / 2), 256);
+  const PrepArgs a = prep_args(b);
+  DISPATCH_T(mode, { s.vec = vec_ok<T>(s.embed, s.d) && vec_ok<T>(s.h, s.d);
+                     step_begin_kernel<T><<<(unsigned)(tiles + seg_blocks + rope_blocks + s.n), 256, 0, st>>>(s, a, tiles, seg_blocks, rope_blocks); });
+  AS_LAUNCH_CHECK(ctx);
+  return AS_OK;
+}
+int launch_lora_prep_batch(as_ctx* ctx, int mode, const PrepBatch& b, hipStream_t st) {
+  if (b.n <= 0 || b.n_tiles <= 0) return AS_OK;
+  const PrepArgs a = prep_args(b);
   DISPATCH_T(mode, (lora_prep_kernel<T><<<b.n_tiles, 256, 0, st>>>(a)));
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;

@@ -213,6 +213,19 @@ def test_more_adapter_matrices_than_one_preparation_launch(bf16):
     G.compare_step(sh, 8, trajs, 1, 256, bf16=bf16, loss_tol=2e-3 if bf16 else 1e-4, grad_tol=3e-2 if bf16 else 1e-4)
 
 
+@pytest.mark.parametrize("full", [False, True])
+@pytest.mark.parametrize("d_model,targets", [(66, ("q", "k", "v", "o", "up")), (72, ("q", "k", "v", "o", "up", "down")), (72, ("v",))])
+def test_what_precedes_the_first_layer_in_one_launch(d_model, targets, full):
+    """40 adapter matrices fill the launch that also makes segments, rotary table and embedding, 48 need a second, 8 and none leave room; rows of the
+    embedding that are no whole 16-byte pieces; 257 tokens are one past a block of the segment table.  The step's stated fp32 tolerances."""
+    import gpu_util as G
+    sh = synth.CONFIGS[1].replace(n_layers=4, n_q_heads=2, n_kv_heads=1, head_dim=32, d_model=d_model, ffn=136, vocab=128,
+                                  lora_targets=targets, lora_rank=4, lora_alpha=8.0)
+    g = synth.rng(5, 9)
+    trajs = [[(r, g.integers(0, sh.vocab, size=n).astype(np.int32)) for r, n in zip(synth.role_pattern(len(lens)), lens)] for lens in ([60, 70, 30, 1], [40, 56])]
+    G.compare_step(sh, 8, trajs, 1, 257, bf16=False, loss_tol=1e-4, grad_tol=1e-4, full=full)
+
+
 @pytest.mark.parametrize("row_len,ffn,targets,full", [(4352, 192, synth.DENSE_TARGETS7, False), (4300, 256, ("v", "gate"), False),
                                                       (4300, 192, ("down",), False), (4352, 256, (), True)])
 def test_input_gradients_from_matrices_as_they_are(row_len, ffn, targets, full):
