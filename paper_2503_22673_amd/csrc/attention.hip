@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256) void attn_fwd_plain(AttnParams p, float scale)
 #pragma unroll
     for (int i = 0; i < U; i++)
       if (base + grp + i * ROWS < len) {
-        const float e = expf(d[i] - mx);
+        const float e = d[i] == -INFINITY ? 0.f : expf(d[i] - mx);      // no -inf - -inf where a group has met nothing else yet
         sum += e;
 #pragma unroll
         for (int c = 0; c < 4; c++) acc[c] = fmaf(e, v[i][c], acc[c]);
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(256) void attn_fwd_plain(AttnParams p, float scale)
   sum = 0.f; acc = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int w = 0; w < 4; w++) {
-    const float fw = rmx[w] > -INFINITY ? expf(rmx[w] - all) : 0.f;
+    const float fw = expf(rmx[w] - all);                   // a wave without rows: 0; no finite score at all: no number, in o and lse
     sum += rsum[w] * fw;
 #pragma unroll
     for (int c = 0; c < 4; c++) acc[c] = fmaf(racc[w * LPR + lane][c], fw, acc[c]);

@@ -411,3 +411,33 @@ def test_plain_attention_of_rows_at_any_address_and_beside_values_that_are_no_nu
     keep[71:201] = False
     for a, b in zip(base, out):
         assert torch.equal(a[keep], b[keep])
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("Hq,Hkv,dh", [(4, 2, 32), (2, 1, 64), (2, 2, 128)])
+def test_plain_attention_with_scores_of_minus_infinity(Hq, Hkv, dh, bf16):
+    """A score that overflows to -inf weighs nothing as long as its query sees another, also where all that a row group has met so far are of that
+    kind (one key of a short segment, five groups' worth of rows, all rows of a group's first pass); a query that sees nothing else has no softmax."""
+    B, G, ctx, sh = _env(n_q_heads=Hq, n_kv_heads=Hkv, head_dim=dh)
+    dt, tol, mode = (torch.bfloat16, 2.0 ** -6, B.AS_BF16) if bf16 else (torch.float32, 1e-5, B.AS_FP32)
+    lens, gone = [40, 9, 300, 5], [range(3, 4), range(2, 7), range(1, 170), range(0)]
+    g, cu, n = _attn_case(17, len(lens), Hq, Hkv, dh, lens)
+    q, k, v, do = (G.quantise(g.standard_normal((n, h, dh)), bf16) for h in (Hq, Hkv, Hkv, Hq))
+    q[:, :, 0], k[:, :, 0] = 8.0, 0.0
+    lost = np.concatenate([cu[s] + np.asarray(list(r), dtype=np.int64) for s, r in enumerate(gone)])
+    k[lost, :, 0] = G.quantise(np.array(-3e38), bf16)        # 8 * -3e38 is -inf in float, and far below every other score in float64
+    o_ref, probs = om.attention(q, k, v, cu, Hq // Hkv)
+    refs = (o_ref,) + tuple(om.attention_bwd(do, q, k, v, o_ref, probs, cu, Hq // Hkv))
+    seg = om.segment_ids(cu, n)
+    s0, s1 = (torch.from_numpy(x.astype(np.int32)).cuda() for x in (cu[seg], cu[seg + 1]))
+    qkv_d = G.to_dev(np.concatenate([x.reshape(n, -1) for x in (q, k, v)], axis=1), dt)
+    o, lse = ctx.op_attention_fwd(qkv_d, s0, variant=1, mode=mode)
+    dqkv = ctx.op_attention_bwd(qkv_d, s0, s1, G.to_dev(o_ref.reshape(n, -1), dt), lse, G.to_dev(do.reshape(n, -1), dt), variant=1, mode=mode)
+    D, Dkv = Hq * dh, Hkv * dh
+    got = G.to_np(dqkv)
+    for x, r in zip((G.to_np(o), got[:, :D], got[:, D:D + Dkv], got[:, D + Dkv:]), refs):
+        assert grad_norm_err(x, r.reshape(n, -1)) < tol
+    first = torch.from_numpy(cu[:-1].astype(np.int64)).cuda()
+    qkv_d.view(n, -1, dh)[first, Hq:Hq + Hkv, 0] = float(k[lost[0], 0, 0])              # the first queries of the segments see themselves only
+    o, lse = ctx.op_attention_fwd(qkv_d, s0, variant=1, mode=mode)
+    assert torch.isnan(o[first]).all() and torch.isnan(lse[first]).all()
