@@ -480,15 +480,10 @@ int launch_rmsnorm_bwd_gain(as_ctx* ctx, int mode, int n, int d, const void* dy,
 }
 
 // ------------------------------------------------------------------ SwiGLU
-// gu holds [gate | up] side by side, row length 2F.  In bf16 the reciprocal is the instruction's (one unit of a float's last place off at
-// most, results are rounded to bf16), an exact division costs ten more.
-template <typename T> __device__ __forceinline__ float sigmoid(float a) {
-  const float e = 1.f + __expf(-a);
-  return sizeof(T) == 2 ? __builtin_amdgcn_rcpf(e) : 1.f / e;
-}
-template <typename T> __device__ __forceinline__ float silu_times(float a, float b) {
-  return sizeof(T) == 2 ? a * sigmoid<T>(a) * b : a / (1.f + __expf(-a)) * b;
-}
+// gu holds [gate | up] side by side, row length 2F.  The divisions are exact ones: the reciprocal instruction is a unit of the last place off and
+// loses gates under -87.3, where 1 + exp(-gate) passes 2^126, altogether.
+__device__ __forceinline__ float sigmoid(float a) { return 1.f / (1.f + __expf(-a)); }
+__device__ __forceinline__ float silu_times(float a, float b) { return a / (1.f + __expf(-a)) * b; }
 template <typename T>
 __global__ void swiglu_fwd_kernel(int64_t n, int F, const T* __restrict__ gu, T* __restrict__ m, int vec) {
   constexpr int VN = Vec<T>::N;
@@ -500,11 +495,11 @@ __global__ void swiglu_fwd_kernel(int64_t n, int F, const T* __restrict__ gu, T*
   if (vec) {
     float a[VN], b[VN], o[VN]; load_vec<T>(gr + j, a); load_vec<T>(gr + F + j, b);
 #pragma unroll
-    for (int i = 0; i < VN; i++) o[i] = silu_times<T>(a[i], b[i]);
+    for (int i = 0; i < VN; i++) o[i] = silu_times(a[i], b[i]);
     store_vec<T>(m + t * F + j, o);
   } else {
     float a = to_f<T>(gr[j]), b = to_f<T>(gr[F + j]);
-    m[t * F + j] = from_f<T>(silu_times<T>(a, b));
+    m[t * F + j] = from_f<T>(silu_times(a, b));
   }
 }
 
@@ -523,7 +518,7 @@ __global__ void swiglu_bwd_kernel(int64_t n, int F, const T* __restrict__ dm, co
     load_vec<T>(gr + j, a); load_vec<T>(gr + F + j, b); load_vec<T>(dm + t * F + j, c);
 #pragma unroll
     for (int i = 0; i < VN; i++) {
-      const float sg = sigmoid<T>(a[i]);
+      const float sg = sigmoid(a[i]);
       og[i] = c[i] * b[i] * sg * (1.f + a[i] * (1.f - sg));
       ou[i] = c[i] * a[i] * sg;
     }
@@ -531,15 +526,15 @@ __global__ void swiglu_bwd_kernel(int64_t n, int F, const T* __restrict__ dm, co
     if (m_out) {                                       // the forward product again, in the forward kernel's arithmetic
       float o[VN];
 #pragma unroll
-      for (int i = 0; i < VN; i++) o[i] = silu_times<T>(a[i], b[i]);
+      for (int i = 0; i < VN; i++) o[i] = silu_times(a[i], b[i]);
       store_vec<T>(m_out + t * F + j, o);
     }
   } else {
     float a = to_f<T>(gr[j]), b = to_f<T>(gr[F + j]), c = to_f<T>(dm[t * F + j]);
-    const float sg = sigmoid<T>(a);
+    const float sg = sigmoid(a);
     dr[j] = from_f<T>(c * b * sg * (1.f + a * (1.f - sg)));
     dr[F + j] = from_f<T>(c * a * sg);
-    if (m_out) m_out[t * F + j] = from_f<T>(silu_times<T>(a, b));
+    if (m_out) m_out[t * F + j] = from_f<T>(silu_times(a, b));
   }
 }
 
@@ -607,13 +602,13 @@ __global__ __launch_bounds__(512) void swiglu_adapter_kernel(int n, int F, const
       bf16x8 y[MT], mo;
 #pragma unroll
       for (int i = 0; i < 8; i++) {
-        const float a = (float)v.g[h][i], b = (float)v.x[h][i], sg = sigmoid<bf16_t>(a);
+        const float a = (float)v.g[h][i], b = (float)v.x[h][i];
         if (BWD) {
-          const float d = (float)v.z[h][i];
+          const float d = (float)v.z[h][i], sg = sigmoid(a);
           y[0][i] = (bf16_t)(d * b * sg * (1.f + a * (1.f - sg)));
           y[MT - 1][i] = (bf16_t)(d * a * sg);
-          if (m) mo[i] = (bf16_t)(a * sg * b);             // the forward product again, in the forward kernel's arithmetic
-        } else y[0][i] = (bf16_t)(a * sg * b);
+          if (m) mo[i] = (bf16_t)silu_times(a, b);         // the forward product again, in the forward kernel's arithmetic
+        } else y[0][i] = (bf16_t)silu_times(a, b);
       }
       if (mine) {
         if (BWD) {
