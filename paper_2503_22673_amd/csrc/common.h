@@ -79,6 +79,15 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// Softmax without the sum (GEMM_EPI_SOFT): the power of two that a row's block of logits is held against, whole numbers, so that blocks of one row differ
+// by exact powers of two, and what the exponentials against the block's maximum are multiplied by for it.  A label logit that is no number or
+// out of reach counts for nothing.
+constexpr float kLog2e = 1.4426950408889634f;
+__device__ __forceinline__ float soft_exponent(float label_logit, float block_max) {
+  return fmaxf(fminf(fmaxf(rintf(label_logit * kLog2e), -4e6f), 4e6f), ceilf(block_max * kLog2e) - 40.f);
+}
+__device__ __forceinline__ float soft_scale(float block_max, float exponent) { return __builtin_amdgcn_exp2f(fmaf(block_max, kLog2e, -exponent)); }
+
 // 16 bytes of a row at a time
 template <typename T> struct Vec;
 template <> struct Vec<float> { static constexpr int N = 4; typedef f32x4 type; };

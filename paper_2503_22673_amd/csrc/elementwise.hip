@@ -1133,9 +1133,10 @@ __global__ __launch_bounds__(256) void ce_finish_kernel(const float* __restrict_
   s = wave_sum(s);
   if (lane == 0) { const float lse = m + logf(s); lse_out[row] = lse; loss_rows[row] = lse - zlab[row]; }
 }
-// The same from the exponents and sums of GEMM_EPI_SOFT, whose elements E [rows, V] it completes: loss = ln(sum) - label logit; the label's
-// element loses the sum; 1 / sum goes to inv (which holds the label's element as a float when the kernel begins): inv * w_row * E is the
-// gradient of the logits.  Only a row with a logit 2^40 above its label's has blocks of different exponents; those are brought to one.
+// The same for GEMM_EPI_SOFT, loss and statistics in the same arithmetic (a policy has its reference's log-probabilities to the bit); the product's elements
+// E [rows, V] are completed: the label's loses the sum, and 1 / sum goes to inv (which holds the label's element as a float when the kernel
+// begins): inv * w_row * E is the gradient of the logits.  Only a row with a logit 2^40 above its label's has blocks of different exponents; those
+// are brought to one.
 __global__ __launch_bounds__(256) void soft_finish_kernel(const float* __restrict__ part, int V, int row0, const int32_t* __restrict__ count,
                                                           const float* __restrict__ zlab, const int32_t* __restrict__ labels, float* __restrict__ inv,
                                                           float* __restrict__ loss_rows, bf16_t* __restrict__ E) {
@@ -1143,19 +1144,20 @@ __global__ __launch_bounds__(256) void soft_finish_kernel(const float* __restric
   const int row = row0 + r;
   if (row >= *count) return;
   const float2* pr = reinterpret_cast<const float2*>(part) + (int64_t)r * nblk;
-  float hi = -INFINITY, lo = INFINITY;
-  for (int b = lane; b < nblk; b += 64) { const float x = pr[b].x; hi = fmaxf(hi, x); lo = fminf(lo, x); }
-  hi = wave_max(hi); lo = -wave_max(-lo);
-  float s = 0.f;
-  for (int b = lane; b < nblk; b += 64) { const float2 v = pr[b]; s += v.y * exp2f(v.x - hi); }
-  s = wave_sum(s);
+  const float zl = zlab[row];
+  float m = -INFINITY, hi = -INFINITY, lo = INFINITY;
+  for (int b = lane; b < nblk; b += 64) { const float x = pr[b].x, e = soft_exponent(zl, x); m = fmaxf(m, x); hi = fmaxf(hi, e); lo = fminf(lo, e); }
+  m = wave_max(m); hi = wave_max(hi); lo = -wave_max(-lo);
+  float s = 0.f, es = 0.f;
+  for (int b = lane; b < nblk; b += 64) { const float2 v = pr[b]; s += v.y * expf(v.x - m); es += v.y * soft_scale(v.x, hi); }
+  s = wave_sum(s); es = wave_sum(es);
   const int lab = labels[row];
-  const float rl = pr[lab / 128].x;
-  const bf16_t el = (bf16_t)(inv[row] * exp2f(rl - hi) - s);
+  const float rl = soft_exponent(zl, pr[lab / 128].x);
+  const bf16_t el = (bf16_t)(inv[row] * exp2f(rl - hi) - es);
   bf16_t* e = E + (int64_t)r * V;
   if (lo < hi)                                             // the same for the whole wave
     for (int b = 0; b < nblk; b++) {
-      const float f = exp2f(pr[b].x - hi);
+      const float f = exp2f(soft_exponent(zl, pr[b].x) - hi);
       if (f == 1.f) continue;
       const int c = b * 128 + 2 * lane;
       bf16x2 x = *reinterpret_cast<const bf16x2*>(e + c);
@@ -1165,8 +1167,9 @@ __global__ __launch_bounds__(256) void soft_finish_kernel(const float* __restric
     }
   if (lane == 0) {
     if (!(rl < hi)) e[lab] = el;
-    inv[row] = 1.f / s;
-    loss_rows[row] = hi * 0.6931471805599453f + logf(s) - zlab[row];
+    inv[row] = 1.f / es;
+    const float lse = m + logf(s);
+    loss_rows[row] = lse - zl;
   }
 }
 int launch_soft_finish(as_ctx* ctx, const float* part, int V, int row0, int rows_cap, const int32_t* count, const float* zlab, const int32_t* labels,

@@ -890,12 +890,33 @@ __device__ __forceinline__ void rd_rows(const GemmParams& p, const f32x16 (&t)[4
   }
 }
 
+// Softmax statistics of the rows 16 a + lane % 16 of a 128-column block: the maximum of alpha * value and the sum of exp(alpha * value - maximum), whose terms
+// take the values' place (a lane owns 32 of a row's columns, the others sit in lane ^ 16, lane ^ 32).  What a loss is made of, whichever epilogue wants it.
+__device__ __forceinline__ float2 row_stats(f32x16 (&t)[4], int a, float alpha) {
+  float m = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < 4; j++)
+#pragma unroll
+    for (int e = 0; e < 8; e++) m = fmaxf(m, alpha * t[j][8 * a + e]);
+  m = fmaxf(m, __shfl_xor(m, 32, 64));
+  m = fmaxf(m, __shfl_xor(m, 16, 64));
+  const float nm2 = -kLog2e * m;
+  float s = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; j++)
+#pragma unroll
+    for (int e = 0; e < 8; e++) { t[j][8 * a + e] = __builtin_amdgcn_exp2f(fmaf(alpha * t[j][8 * a + e], kLog2e, nm2)); s += t[j][8 * a + e]; }
+  s += __shfl_xor(s, 32, 64);
+  s += __shfl_xor(s, 16, 64);
+  return make_float2(m, s);
+}
+
 // bf16 results through the wave's 8 KB of the free half stage, so that a store instruction writes four whole 256-byte row pieces; 16-byte
 // chunk c of row r lies at c ^ (r % 16).  A residual takes the same way in: loaded 16 bytes per lane, parked at the place of the result,
 // picked up by the lane that owns the element and rounded once with the sum.
 // EPI PROB: the values are turned into w_row * (exp(value - lse_row) - [column is the row's label]) before they are rounded.
 // EPI ROWS: a row is multiplied by its row_scale * w_row.
-// EPI SOFT: exp(value) over a whole power of two, see GemmParams; per row and block the exponent and the sum of the unrounded elements go to epi_part.
+// EPI SOFT: exp(value) over a whole power of two, see GemmParams: the statistics' exponentials times one factor per row and block.
 template <bool MASK>
 __device__ __forceinline__ void rd_load_residual(const GemmParams& p, u32x4 (&res)[8], const RdOut& o, int i, int lane) {
   const int r4 = lane >> 4, c16 = lane & 15;
@@ -933,23 +954,17 @@ __device__ __forceinline__ void rd_staged(const GemmParams& p, f32x16 (&t)[4], u
   }
 #pragma unroll
   for (int a = 0; a < 2; a++) {
-    float neg_lse2 = 0.f, wrow = 0.f, neg_ref = 0.f, sum = 0.f; int clab = -1;
+    float neg_lse2 = 0.f, wrow = 0.f, sum_scale = 0.f; int clab = -1;
     // rows outside the live range compute with the last live row's values and are not written
     const int rr = o.row0 + 32 * i + 16 * a + l15, r = MASK ? min(max(rr, o.row_lo), o.row_hi - 1) : rr;
-    if (EPI == GEMM_EPI_PROB) neg_lse2 = -1.4426950408889634f * p.epi_lse[r];
+    if (EPI == GEMM_EPI_PROB) neg_lse2 = -kLog2e * p.epi_lse[r];
     if (EPI == GEMM_EPI_PROB || EPI == GEMM_EPI_ROWS) wrow = p.epi_w ? p.epi_w[r] : 1.f / (float)*p.epi_cnt;
     if (EPI == GEMM_EPI_ROWS) wrow *= p.row_scale[r];
     if (EPI == GEMM_EPI_PROB || EPI == GEMM_EPI_SOFT) clab = p.epi_lab[r] - o.col0 - 4 * q;   // position of the label among this lane's columns of the block, if any
     if (EPI == GEMM_EPI_SOFT) {
-      float m = -INFINITY;
-#pragma unroll
-      for (int j = 0; j < 4; j++)
-#pragma unroll
-        for (int e = 0; e < 8; e++) m = fmaxf(m, t[j][8 * a + e]);
-      m = fmaxf(m, __shfl_xor(m, 32, 64));
-      m = fmaxf(m, __shfl_xor(m, 16, 64));
-      // whole numbers, so that blocks of one row differ by exact powers of two; a label logit that is no number or out of reach counts for nothing
-      neg_ref = -fmaxf(fminf(fmaxf(rintf(p.epi_zlab[r] * 1.4426950408889634f), -4e6f), 4e6f), ceilf(m * 1.4426950408889634f) - 40.f);
+      const float2 st = row_stats(t, a, 1.f);              // t: the exponentials of the statistics from here on
+      sum_scale = soft_scale(st.x, soft_exponent(p.epi_zlab[r], st.x));
+      if (lane < 16 && (!MASK || r == rr)) *(reinterpret_cast<float2*>(p.epi_part) + (int64_t)r * (p.N / 128) + o.col0 / 128) = st;
     }
 #pragma unroll
     for (int j = 0; j < 4; j++)
@@ -963,14 +978,14 @@ __device__ __forceinline__ void rd_staged(const GemmParams& p, f32x16 (&t)[4], u
         }
         if (EPI == GEMM_EPI_SOFT) {
 #pragma unroll
-          for (int k = 0; k < 4; k++) { v[k] = __builtin_amdgcn_exp2f(fmaf(v[k], 1.4426950408889634f, neg_ref)); sum += v[k]; }
+          for (int k = 0; k < 4; k++) v[k] *= sum_scale;
           const int at_k = clab - (32 * j + 16 * b);       // one block in V / 128 holds a row's label
           if (at_k >= 0 && at_k < 4 && (!MASK || r == rr)) p.epi_elab[r] = at_k == 0 ? v[0] : at_k == 1 ? v[1] : at_k == 2 ? v[2] : v[3];
         }
         if (EPI == GEMM_EPI_PROB) {
 #pragma unroll
           for (int k = 0; k < 4; k++)
-            v[k] = wrow * (__builtin_amdgcn_exp2f(fmaf(v[k], 1.4426950408889634f, neg_lse2)) - (clab == 32 * j + 16 * b + k ? 1.f : 0.f));
+            v[k] = wrow * (__builtin_amdgcn_exp2f(fmaf(v[k], kLog2e, neg_lse2)) - (clab == 32 * j + 16 * b + k ? 1.f : 0.f));
         }
         if (RES) { const bf16x4_t x = *at;
 #pragma unroll
@@ -980,11 +995,6 @@ __device__ __forceinline__ void rd_staged(const GemmParams& p, f32x16 (&t)[4], u
         for (int k = 0; k < 4; k++) w[k] = (bf16_t)v[k];
         *at = w;
       }
-    if (EPI == GEMM_EPI_SOFT) {
-      sum += __shfl_xor(sum, 32, 64);
-      sum += __shfl_xor(sum, 16, 64);
-      if (lane < 16 && (!MASK || r == rr)) *(reinterpret_cast<float2*>(p.epi_part) + (int64_t)r * (p.N / 128) + o.col0 / 128) = make_float2(-neg_ref, sum);
-    }
   }
   asm volatile("" ::: "memory");                           // LDS operations of a wave complete in order
   u32x4 out[8];
@@ -1001,30 +1011,14 @@ __device__ __forceinline__ void rd_staged(const GemmParams& p, f32x16 (&t)[4], u
   asm volatile("" ::: "memory");
 }
 
-// Softmax statistics of the logits, nothing of which is written (a lane owns 32 of a row's 128 columns, the others sit in lane ^ 16,
-// lane ^ 32): per row the maximum and the sum of exp(value - maximum).
+// Softmax statistics of the logits, nothing of which is written.
 template <bool MASK>
-__device__ __forceinline__ void rd_stats(const GemmParams& p, const f32x16 (&t)[4], const RdOut& o, int i, int lane) {
-  const float alpha = p.alpha;
+__device__ __forceinline__ void rd_stats(const GemmParams& p, f32x16 (&t)[4], const RdOut& o, int i, int lane) {
 #pragma unroll
   for (int a = 0; a < 2; a++) {
-    float m = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < 4; j++)
-#pragma unroll
-      for (int e = 0; e < 8; e++) m = fmaxf(m, alpha * t[j][8 * a + e]);
-    m = fmaxf(m, __shfl_xor(m, 32, 64));
-    m = fmaxf(m, __shfl_xor(m, 16, 64));
-    const float nm2 = -1.4426950408889634f * m;
-    float s = 0.f;
-#pragma unroll
-    for (int j = 0; j < 4; j++)
-#pragma unroll
-      for (int e = 0; e < 8; e++) s += __builtin_amdgcn_exp2f(fmaf(alpha * t[j][8 * a + e], 1.4426950408889634f, nm2));
-    s += __shfl_xor(s, 32, 64);
-    s += __shfl_xor(s, 16, 64);
+    const float2 st = row_stats(t, a, p.alpha);
     const int r = o.row0 + 32 * i + 16 * a + (lane & 15);
-    if (lane < 16 && (!MASK || (r >= o.row_lo && r < o.row_hi))) *(reinterpret_cast<float2*>(p.epi_part) + (int64_t)r * (p.N / 128) + o.col0 / 128) = make_float2(m, s);
+    if (lane < 16 && (!MASK || (r >= o.row_lo && r < o.row_hi))) *(reinterpret_cast<float2*>(p.epi_part) + (int64_t)r * (p.N / 128) + o.col0 / 128) = st;
   }
 }
 

@@ -44,7 +44,7 @@ struct GemmParams {
   //  epi == GEMM_EPI_PROB:  C = w_row * (exp(value - epi_lse[row]) - [column == epi_lab[row]]), w_row = epi_w[row] when
   //    given, else 1 / *epi_cnt: the gradient of the masked loss with respect to the logits, straight from the accumulators.
   //  epi == GEMM_EPI_SOFT:  C = exp(value) / 2^R, R a whole number per row and 128-column block: the row's label logit epi_zlab in powers of
-  //    two, more only where a value lies 2^40 above it; R and the block's sum go to epi_part as above, the label's own element to
+  //    two, more only where a value lies 2^40 above it; the statistics go to epi_part as above, the label's own element to
   //    epi_elab[row] as a float.  Up to whole powers of two and the factor w_row / (sum over the row) this is the gradient, before the sum is known.
   // row_scale (with epi_w or epi_cnt; the product of device-counted rows with a [K, N] matrix only): row r of the result times
   //    row_scale[r] * w_row.

@@ -152,6 +152,35 @@ def test_policy_equal_to_reference_gives_ln2_and_half_beta_factors():
             assert not dA.any().item() and dB.any().item()                 # dA = s B^T(...) = 0, dB live
 
 
+@pytest.mark.parametrize("tokens, vocab", [(700, 8192), (700, 512), (9000, 8192)])
+def test_policy_equal_to_reference_has_the_references_bits_in_bf16(tokens, vocab):
+    """The same log-probabilities to the bit, whichever way the head takes for its gradient: one pass over a vocabulary of 8192, with the first 8192
+    targets' exponentials kept or all made again, two passes over one of 512."""
+    from paper_2503_22673_amd import binding as B
+    sh = synth.CONFIGS[1].replace(n_layers=1, d_model=256, n_q_heads=4, n_kv_heads=4, head_dim=64, ffn=256, vocab=vocab)
+    params, lora = synth.weights(sh, 0), synth.lora_weights(sh, 0, zero_b=True)
+    params["head"] *= 50.0                                   # logits of 16 in the mean, as a trained model has them
+    g = synth.rng(12, tokens)
+    cuts = [tokens * i // 8 for i in range(9)]
+    trajs = [[(1, g.integers(0, vocab, size=1).astype(np.int32)), (2, g.integers(0, vocab, size=e - b - 1).astype(np.int32))] for b, e in zip(cuts, cuts[1:])]
+    ctx = B.Context(B.make_config(sh, mode=B.AS_BF16))
+    pk = ctx.pack(*synth.flatten_trajectories(trajs), tokens, 1)
+    hcu = pk["cu_seqlens"].cpu().numpy()
+    model = B.DeviceModel(ctx, params, lora)
+    ws = torch.empty(ctx.workspace_bytes(1, tokens), dtype=torch.uint8, device="cuda")
+    args = (pk["tokens"], pk["cu_seqlens"], hcu, pk["loss_mask"], 1, tokens, ws)
+    ref = ctx.sequence_logps(model, *args, adapters=True)
+    ctx.profile(True)
+    out = ctx.dpo_step(model, *args, [(0, 1), (2, 3), (5, 4)], ref, 0.3)
+    torch.cuda.synchronize()
+    products = ctx.profile_read()["gemm_devrows"][0]         # over the targets: with logits or their exponentials, and dH, of every 8192 of them
+    ctx.profile(False)
+    assert products == (2 if tokens < 8192 else 6) + (vocab == 512)
+    assert torch.equal(out["logp"], ref)
+    st = out["stats"].cpu().numpy()
+    assert st[0] == pytest.approx(np.log(2.0), rel=1e-6) and st[1] == 0.0 and st[2] == 0.0
+
+
 def test_no_pair_and_invalid_arguments():
     import gpu_util as G
     from paper_2503_22673_amd import binding as B
