@@ -1362,6 +1362,16 @@ int launch_dq64(as_ctx* ctx, const AttnParams& p, float scale, float sl2, hipStr
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }
+constexpr size_t kSmemDkv64 = (size_t)2 * (2 * T64_E + 256) * sizeof(bf16_t);   // two stages of Q, dO, -lse / scale, -delta
+static_assert(kSmemDkv64 >= kSmem64, "the dQ blocks' two stages of K and V fit");
+template <int HPW>
+int launch_bwd64(as_ctx* ctx, const AttnParams& p, float scale, float sl2, const float* nls, const float* nd, int Np, const int32_t* order, float* part, int64_t dkv, int64_t dq,
+                 hipStream_t st) {
+  AS_SET_SMEM(ctx, attn_bwd64_mfma<HPW>, kSmemDkv64);
+  attn_bwd64_mfma<HPW><<<(unsigned)(dkv + dq), 256, kSmemDkv64, st>>>(p, scale, sl2, nls, nd, Np, order, part, (int)dkv);
+  AS_LAUNCH_CHECK(ctx);
+  return AS_OK;
+}
 
 // Scratch of t_scratch: -lse / scale, -delta and an order of the key blocks where the token-major copy of Q would be, partials behind it all.
 int bwd64(as_ctx* ctx, const AttnParams& p, float scale, float sl2, int Np, float* stat, float* part, hipStream_t st) {
@@ -1372,25 +1382,18 @@ int bwd64(as_ctx* ctx, const AttnParams& p, float scale, float sl2, int Np, floa
   AS_LAUNCH_CHECK(ctx);
   const int hpw = heads_per_wg(p);
   const int32_t* ord = order ? order : p.order_k;
-  constexpr size_t smem = (size_t)2 * (2 * T64_E + 256) * sizeof(bf16_t);   // two stages of Q, dO, -lse / scale, -delta
-  static_assert(smem >= kSmem64, "the dQ blocks' two stages of K and V fit");
   const int64_t dkv = 2 * cdiv(p.n, 256) * p.Hq, dq = cdiv(p.n, 64 * (4 / hpw)) * 2 * (p.Hq / hpw);
   // Both kinds in one launch up to two rounds of dK / dV workgroups: their registers leave a CU three workgroups of dQ where it takes four alone, so
   // many rounds are 1 % slower, but short calls run side by side (us, 32 heads over 8, apart and so): 512 tokens 42 and 28, 1003 64 and 44, 2100 122 and 94, 4100 171
   // and 153, 6000 311 and 312, 12,000 346 and 350.
   if (dkv <= 6 * kCus) {
-    auto go = [&](auto k) -> int {
-      AS_SET_SMEM(ctx, k, smem);
-      k<<<(unsigned)(dkv + dq), 256, smem, st>>>(p, scale, sl2, nls, nd, Np, ord, part, (int)dkv);
-      AS_LAUNCH_CHECK(ctx);
-      return AS_OK;
-    };
-    return hpw == 4 ? go(attn_bwd64_mfma<4>) : hpw == 2 ? go(attn_bwd64_mfma<2>) : go(attn_bwd64_mfma<1>);
+    auto go = [&](auto h) { return launch_bwd64<h()>(ctx, p, scale, sl2, nls, nd, Np, ord, part, dkv, dq, st); };
+    return hpw == 4 ? go(std::integral_constant<int, 4>()) : hpw == 2 ? go(std::integral_constant<int, 2>()) : go(std::integral_constant<int, 1>());
   }
   const int rc = hpw == 4 ? launch_dq64<4>(ctx, p, scale, sl2, st) : hpw == 2 ? launch_dq64<2>(ctx, p, scale, sl2, st) : launch_dq64<1>(ctx, p, scale, sl2, st);
   if (rc) return rc;
-  AS_SET_SMEM(ctx, attn_bwd_dkv64_mfma, smem);
-  attn_bwd_dkv64_mfma<<<(unsigned)dkv, 256, smem, st>>>(p, scale, sl2, nls, nd, Np, ord, part);
+  AS_SET_SMEM(ctx, attn_bwd_dkv64_mfma, kSmemDkv64);
+  attn_bwd_dkv64_mfma<<<(unsigned)dkv, 256, kSmemDkv64, st>>>(p, scale, sl2, nls, nd, Np, ord, part);
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }

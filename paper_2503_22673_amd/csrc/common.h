@@ -13,6 +13,7 @@
 #include <type_traits>
 #include "actionstudio.h"
 #include "gemm_items.h"
+#include "per_kernel.h"
 
 typedef __bf16 bf16_t;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -43,8 +44,9 @@ int as_fail(as_ctx* ctx, int code, const char* fmt, ...);
 #define AS_HIP(ctx, call) do { hipError_t e_ = (call); if (e_ != hipSuccess) \
   return as_fail((ctx), AS_ERR_HIP, "%s: %s", #call, hipGetErrorString(e_)); } while (0)
 #define AS_LAUNCH_CHECK(ctx) AS_HIP(ctx, hipGetLastError())
-// Raises a kernel's dynamic LDS limit once per device (the attribute belongs to the code object loaded on that device).
-#define AS_SET_SMEM(ctx, kern, bytes) do { static std::atomic<uint64_t> done_{0}; const uint64_t bit_ = 1ull << ((ctx)->device & 63); \
+// Raises a kernel's dynamic LDS limit once per device (the attribute belongs to the code object loaded on that device); kern: a constant expression,
+// and of one kernel always the same number of bytes.
+#define AS_SET_SMEM(ctx, kern, bytes) do { std::atomic<uint64_t>& done_ = smem_devices<kern>; const uint64_t bit_ = 1ull << ((ctx)->device & 63); \
   if (!(done_.load(std::memory_order_relaxed) & bit_)) { \
     AS_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(bytes))); \
     done_.fetch_or(bit_, std::memory_order_relaxed); } } while (0)

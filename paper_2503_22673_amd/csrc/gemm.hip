@@ -1126,7 +1126,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_rd_kernel(GemmParams p, int m_o
 template <int BM, int BN, int WM, int WN>
 static int launch_dlds_cfg(as_ctx* ctx, const GemmParams& p, int m_off, hipStream_t st) {
   size_t smem = (size_t)2 * (BM + BN) * 64 * sizeof(bf16_t);
-  auto k0 = gemm_mfma_dlds_kernel<BM, BN, WM, WN>;
+  constexpr auto k0 = gemm_mfma_dlds_kernel<BM, BN, WM, WN>;
   AS_SET_SMEM(ctx, k0, smem);
   int tm = (int)cdiv(p.M, BM), tn = (int)cdiv(p.N, BN);
   dim3 grid(tm * tn, p.splitk > 1 ? p.splitk : 1);
@@ -1373,8 +1373,8 @@ static int launch_mfma_cfg(as_ctx* ctx, const GemmParams& p, int m_off, hipStrea
   size_t smem = (size_t)2 * (BM + BN) * LS * sizeof(bf16_t);
   bool edge = false;
   for (int s = 0; s < p.nseg; s++) edge = edge || (p.seg[s].K % 64 != 0);
-  auto k0 = gemm_mfma_kernel<BM, BN, WM, WN, false>;
-  auto k1 = gemm_mfma_kernel<BM, BN, WM, WN, true>;
+  constexpr auto k0 = gemm_mfma_kernel<BM, BN, WM, WN, false>;
+  constexpr auto k1 = gemm_mfma_kernel<BM, BN, WM, WN, true>;
   AS_SET_SMEM(ctx, k0, smem);
   AS_SET_SMEM(ctx, k1, smem);
   int tm = (int)cdiv(p.M, BM), tn = (int)cdiv(p.N, BN);
