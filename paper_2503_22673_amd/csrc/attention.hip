@@ -140,7 +140,7 @@ template <int LPR> __device__ __forceinline__ f32x4 rotate_back(const AttnParams
   return r;
 }
 // Workgroups with blockIdx.y < Hkv: dk, dv of one (token, KV head), summed over the query heads of the group in head order and the later tokens
-// of the segment; the others: dq of one (token, head), and delta = sum_c dO O.
+// of the segment; the others: dq of one (token, head).
 template <typename T, int DH, bool VEC>
 __global__ __launch_bounds__(256, 8) void attn_bwd_plain(AttnParams p, float scale) {
   constexpr int LPR = DH / 4, G = 64 / LPR, ROWS = 4 * G, U = 2;
@@ -190,7 +190,6 @@ __global__ __launch_bounds__(256, 8) void attn_bwd_plain(AttnParams p, float sca
   const T* kb = (const T*)p.k + (int64_t)s0 * p.ldkv + g * DH + 4 * lc;
   const T* vb = (const T*)p.v + (int64_t)s0 * p.ldkv + g * DH + 4 * lc;
   const float lse = p.lse[(int64_t)t * p.Hq + j], dl = row_sum<LPR>(dot4(d, o));
-  if (tid == 0) p.delta[(int64_t)t * p.Hq + j] = dl;
   for (int base = 0; base < len; base += ROWS * U) {
     f32x4 k[U], v[U];
 #pragma unroll
@@ -216,10 +215,12 @@ __global__ __launch_bounds__(256, 8) void attn_bwd_plain(AttnParams p, float sca
   if (tid < LPR) put4<T>((T*)p.dq + (int64_t)t * p.ldq + j * DH + 4 * lc, a0);
 }
 
-// Segments as long as kernels with a score per row in LDS took (floats of it): the callers' limits stay where they were.
-static int check_plain(as_ctx* ctx, const AttnParams& p, int64_t floats) {
+// The plain kernels have no limit of their own: they answer for the segments that they have always answered for, up to 40,960 - head_dim
+// tokens forward and half as many backward.
+constexpr int kPlainTokens = 40960;
+static int check_plain(as_ctx* ctx, const AttnParams& p, int limit) {
   if (p.dh != 32 && p.dh != 64 && p.dh != 128) return as_fail(ctx, AS_ERR_SHAPE, "attention: head_dim 32, 64 or 128");
-  if (floats * 4 > 160 * 1024) return as_fail(ctx, AS_ERR_SHAPE, "attention (plain kernels): segment too long for LDS");
+  if (p.max_seg > limit) return as_fail(ctx, AS_ERR_SHAPE, "attention (plain kernels): segments of at most %d tokens", limit);
   return AS_OK;
 }
 
@@ -245,7 +246,7 @@ int launch_attention_fwd(as_ctx* ctx, int mode, int variant, const AttnParams& p
   bool mf = mode == AS_BF16 && variant != 1 && attention_mfma_ok(p);
   if (variant >= 2 && !mf) return as_fail(ctx, AS_ERR_SHAPE, "attention: MFMA kernel needs bf16, head_dim 64/128, aligned strides");
   if (mf) { prof_begin(ctx, st, AS_K_ATTN_FWD, 0.0); int r = launch_attention_fwd_mfma(ctx, p, variant, st); prof_end(ctx, st); return r; }
-  int rc = check_plain(ctx, p, (int64_t)p.dh + std::max(p.max_seg, kPlainThreads)); if (rc) return rc;
+  int rc = check_plain(ctx, p, kPlainTokens - p.dh); if (rc) return rc;
   plain_kernel(mode, p, plain_vec(mode, p, {p.q, p.k, p.v}), [&](auto t, auto dh, auto vec) {
     attn_fwd_plain<decltype(t), dh(), vec()><<<dim3(p.n, p.Hq), kPlainThreads, 0, st>>>(p, 1.f / sqrtf((float)p.dh)); });
   AS_LAUNCH_CHECK(ctx);
@@ -257,7 +258,7 @@ int launch_attention_bwd(as_ctx* ctx, int mode, int variant, const AttnParams& p
   bool mf = mode == AS_BF16 && variant != 1 && attention_mfma_ok(p);
   if (variant >= 2 && !mf) return as_fail(ctx, AS_ERR_SHAPE, "attention: MFMA kernel needs bf16, head_dim 64/128, aligned strides");
   if (mf) { prof_begin(ctx, st, AS_K_ATTN_BWD, 0.0); int r = launch_attention_bwd_mfma(ctx, p, variant, st); prof_end(ctx, st); return r; }
-  int rc = check_plain(ctx, p, 2 * ((int64_t)p.dh + std::max(p.max_seg, kPlainThreads))); if (rc) return rc;
+  int rc = check_plain(ctx, p, kPlainTokens / 2 - p.dh); if (rc) return rc;
   plain_kernel(mode, p, plain_vec(mode, p, {p.q, p.k, p.v, p.o, p.d_o}), [&](auto t, auto dh, auto vec) {
     attn_bwd_plain<decltype(t), dh(), vec()><<<dim3(p.n, p.Hkv + p.Hq), kPlainThreads, 0, st>>>(p, 1.f / sqrtf((float)p.dh)); });
   AS_LAUNCH_CHECK(ctx);

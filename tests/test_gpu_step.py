@@ -297,3 +297,21 @@ def test_adapter_products_from_rows(tokens, d, heads, kv, ffn, targets):
     cuts = [tokens * i // 8 for i in range(9)]
     trajs = [[(1, g.integers(0, sh.vocab, size=1).astype(np.int32)), (2, g.integers(0, sh.vocab, size=e - b - 1).astype(np.int32))] for b, e in zip(cuts, cuts[1:])]
     G.compare_step(sh, 4, trajs, 1, tokens, bf16=True, loss_tol=2e-3, grad_tol=3e-2)
+
+
+@pytest.mark.parametrize("dh", [32, 128])
+def test_fp32_steps_take_segments_of_so_many_tokens(dh):
+    """20,480 - head_dim in backward; the message of a longer one's refusal says so."""
+    import gpu_util as G
+    from paper_2503_22673_amd import binding as B
+    sh = synth.CONFIGS[1].replace(n_layers=1, d_model=32, n_q_heads=1, n_kv_heads=1, head_dim=dh, ffn=32, vocab=64, lora_rank=2, lora_alpha=4.0, lora_targets=("q",))
+    params, lora = synth.weights(sh, 1), synth.lora_weights(sh, 1)
+    limit = 20480 - dh
+    for n in (limit, limit + 1):
+        trajs = [[(1, np.full(2, 5, np.int32)), (2, np.full(n - 2, 6, np.int32))]]
+        if n > limit:
+            with pytest.raises(B.ASError, match="segments of at most %d tokens" % limit):
+                G.run_step(sh, params, lora, trajs, 1, n, mode=B.AS_FP32)
+        else:
+            res, model, _, _ = G.run_step(sh, params, lora, trajs, 1, n, mode=B.AS_FP32)
+            assert res["count"] == n - 2 and np.isfinite(res["loss"]) and all(torch.isfinite(x).all().item() for x in model.lora_grads[0]["q"])
