@@ -731,7 +731,7 @@ int launch_adapter_rows(as_ctx* ctx, const AdapterRows& p, int items, bool one_x
   const dim3 g((unsigned)cdiv(p.n, 16), one_x ? 1 : items);
   const bool wide = (int64_t)g.x * g.y < 512;              // under two workgroups of eight waves a CU: sixteen
   double flops = 0;
-  for (int i = 0; i < items; i++) flops += 2.0 * p.n * 64 * p.K[one_x ? 0 : i];
+  for (int i = 0; i < items; i++) flops += 2.0 * p.n * 16 * p.K[one_x ? 0 : i];
   auto go = [&](auto nb) { if (wide) adapter_rows_kernel<nb(), 16><<<g, 1024, 0, st>>>(p); else adapter_rows_kernel<nb(), 8><<<g, 512, 0, st>>>(p); };
   prof_begin(ctx, st, AS_K_GEMM_MFMA_SKINNY, flops);
   if (!one_x || items == 1) go(std::integral_constant<int, 1>());
@@ -1175,7 +1175,9 @@ __global__ __launch_bounds__(256) void soft_finish_kernel(const float* __restric
 int launch_soft_finish(as_ctx* ctx, const float* part, int V, int row0, int rows_cap, const int32_t* count, const float* zlab, const int32_t* labels,
                        float* inv, float* loss_rows, void* E, hipStream_t st) {
   if (rows_cap <= 0) return AS_OK;
+  prof_begin(ctx, st, AS_K_CE, 0.0);
   soft_finish_kernel<<<(unsigned)cdiv(rows_cap, 4), 256, 0, st>>>(part, V, row0, count, zlab, labels, inv, loss_rows, (bf16_t*)E);
+  prof_end(ctx, st);
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }

@@ -173,6 +173,28 @@ def test_per_kernel_timing_brackets_nested_launchers():
     assert {k: v[0] for k, v in again.items()} == {k: v[0] for k, v in prof.items()}
 
 
+def test_profile_of_adapter_products_and_of_the_one_pass_head():
+    """An adapter of rank 16 adds its 16 columns of u and the 64 columns of the second segment to a forward pass; label logits and the rows' end
+    are the head's two launches beside its products."""
+    import gpu_util as G
+    from paper_2503_22673_amd import binding as B
+    sh = synth.CONFIGS[1].replace(n_layers=1, d_model=256, n_q_heads=2, n_kv_heads=2, head_dim=64, ffn=256, vocab=8192, lora_rank=16, lora_alpha=16.0, lora_targets=("o",))
+    trajs, n = random_trajs(3, 4, sh.vocab, turn_lo=20, turn_hi=30, turns=(2, 4)), 512
+    _, model, pk, ctx = G.run_step(sh, synth.weights(sh, 2), synth.lora_weights(sh, 2), trajs, 1, n, mode=B.AS_BF16, skip=False)
+    hcu, ws = pk["cu_seqlens"].cpu().numpy(), torch.empty(ctx.workspace_bytes(1, n), dtype=torch.uint8, device="cuda")
+
+    def profile(call):
+        ctx.profile(True)
+        call()
+        prof = ctx.profile_read()
+        ctx.profile(False)
+        return prof
+    on, off = (profile(lambda: ctx.sequence_logps(model, pk["tokens"], pk["cu_seqlens"], hcu, pk["loss_mask"], 1, n, ws, adapters=a)) for a in (True, False))
+    assert sum(v[2] for v in on.values()) - sum(v[2] for v in off.values()) == 2.0 * n * (16 * 128 + 64 * 256)
+    step = profile(lambda: ctx.train_step(model, pk["tokens"], pk["cu_seqlens"], hcu, pk["loss_mask"], 1, n, ws))
+    assert (step["gemm_devrows"][0], step["ce"][0]) == (2, 2)
+
+
 @pytest.mark.parametrize("row_len", [384, 320])
 def test_wide_ffn_step_runs_the_hand_scheduled_gemm(row_len):
     """ffn = 11264 with 3 row tiles makes 132 tiles of 256 x 256: the gate | up projection (one launch over both matrices) and the input gradient of
@@ -205,7 +227,7 @@ def test_wide_ffn_step_runs_the_hand_scheduled_gemm(row_len):
 
 @pytest.mark.parametrize("bf16", [False, True])
 def test_more_adapter_matrices_than_one_preparation_launch(bf16):
-    """4 layers x 7 adapters are 56 matrices, prepared 48 per launch; widths that are no multiple of the 64 x 64 tiles."""
+    """4 layers x 7 adapters are 56 matrices, prepared 40 per launch; widths that are no multiple of the 64 x 64 tiles."""
     import gpu_util as G
     sh = synth.CONFIGS[1].replace(n_layers=4, n_q_heads=2, n_kv_heads=1, head_dim=32, d_model=72, ffn=136, vocab=128,
                                   lora_targets=synth.DENSE_TARGETS7, lora_rank=5, lora_alpha=10.0)
