@@ -274,22 +274,37 @@ def test_adapter_gradients_of_a_group_in_one_launch(targets, rank, turns):
     G.compare_step(sh, 8, trajs, 2, 640, bf16=True, loss_tol=2e-3, grad_tol=3e-2)
 
 
-@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("bf16, rank", [(False, 16), (True, 16), (True, 33), (True, 64)])
 @pytest.mark.parametrize("targets, tokens, d, heads, kv, ffn", [
-    (("q", "k", "v"), 333, 512, 8, 2, 192),            # contractions of 512, 128, 128 side by side, split where one of them ends early
+    (("q", "k", "v"), 333, 512, 8, 2, 192),            # contractions of 512, 128, 128 side by side
     (("q", "v", "up"), 130, 128, 2, 1, 64),            # two of the three; one of two
     (("k", "v"), 1100, 1024, 16, 4, 1088),             # without the longest
     (synth.DENSE_TARGETS7, 70, 1024, 16, 2, 2112),     # one row tile, long contractions
+    (("q", "k", "v"), 70, 256, 64, 1, 192),            # 4096, 64 and 64, split: parts in which k and v have no step
 ])
-def test_adapter_products_side_by_side(targets, tokens, d, heads, kv, ffn, bf16):
-    """du of q, k, v and of gate, up as one launch each."""
+def test_adapter_products_side_by_side(targets, tokens, d, heads, kv, ffn, bf16, rank):
+    """du of q, k, v and of gate, up as one launch each: in bf16 past rank 16 as batched GEMMs, up to it from rows."""
     import gpu_util as G
-    sh = synth.CONFIGS[1].replace(n_layers=1, d_model=d, n_q_heads=heads, n_kv_heads=kv, head_dim=64, ffn=ffn, vocab=512, lora_rank=16, lora_alpha=32.0,
+    from paper_2503_22673_amd import binding as B
+    sh = synth.CONFIGS[1].replace(n_layers=1, d_model=d, n_q_heads=heads, n_kv_heads=kv, head_dim=64, ffn=ffn, vocab=512, lora_rank=rank, lora_alpha=2.0 * rank,
                                   lora_targets=targets)
     g = synth.rng(6, tokens)
     cuts = [0, tokens // 3, tokens]
     trajs = [[(1, g.integers(0, sh.vocab, size=3).astype(np.int32)), (2, g.integers(0, sh.vocab, size=e - b - 3).astype(np.int32))] for b, e in zip(cuts, cuts[1:])]
     G.compare_step(sh, 2, trajs, 1, tokens, bf16=bf16, loss_tol=2e-3 if bf16 else 1e-4, grad_tol=3e-2 if bf16 else 1e-4)
+    if not bf16:
+        return
+    # beyond a forward pass: the input gradients of down, gate | up and o, and one launch of du for every group with an adapter
+    _, model, pk, ctx = G.run_step(sh, synth.weights(sh, 2), synth.lora_weights(sh, 2), trajs, 1, tokens, mode=B.AS_BF16)
+    args = (model, pk["tokens"], pk["cu_seqlens"], pk["cu_seqlens"].cpu().numpy(), pk["loss_mask"], 1, tokens,
+            torch.empty(ctx.workspace_bytes(1, tokens), dtype=torch.uint8, device="cuda"))
+    launches = []
+    for call in (ctx.sequence_logps, ctx.train_step):
+        ctx.profile(True)
+        call(*args)
+        launches.append(ctx.profile_read()["gemm_mfma_skinny"][0])
+        ctx.profile(False)
+    assert launches[1] - launches[0] == 3 + sum(any(t in targets for t in group) for group in (("q", "k", "v"), ("o",), ("gate", "up"), ("down",)))
 
 
 @pytest.mark.parametrize("tokens, rank", [(4, 16), (31, 1), (32, 16), (33, 15), (97, 16), (97, 17), (2049, 8)])
