@@ -613,106 +613,6 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv2_mfma(AttnParams p, float sc
 // per loop trip.  K and V tiles sit in LDS once, row major, three stages deep; dQ^T += K^T dS^T reads K through the
 // transposing LDS loads, so no token-major copy of K is needed.  Every wave issues eight loads per tile.
 #include "attn_dq_tile.inc"
-__device__ __forceinline__ void dq3_block(const AttnParams& p, float scale, float sl2, int block) {
-  constexpr int DH = 128, KS = DH / 16, CB = DH / 32, QT = 64;
-  constexpr int KT_B = BKEY * DH * 2, ST_B = 2 * KT_B;   // bytes of a tile, of a stage (K, V)
-  extern __shared__ __align__(256) unsigned char dyn_smem256[];
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)dyn_smem256;
-  if (lds0 & 255) return;                                       // never the case: the array is the kernel's only LDS
-  const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, h = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n = p.n, grp = p.Hq / p.Hkv;
-  int hg, qi;
-  const int nqt = (n + QT - 1) / QT;
-  xcd_group_map(block, nqt, p.Hq / 4, hg, qi);
-  const int j = hg * 4 + wave, g = j / grp;
-  const int t_wg = (p.order_q ? p.order_q[qi] : nqt - 1 - qi) * QT;   // long rows first
-  const bf16_t* Q = (const bf16_t*)p.q; const bf16_t* K = (const bf16_t*)p.k; const bf16_t* V = (const bf16_t*)p.v;
-  const bf16_t* dO = (const bf16_t*)p.d_o;
-  const int ss_hi = __builtin_amdgcn_readfirstlane(p.seg_start[min(t_wg + QT - 1, n - 1)]);
-  f32x16 dq[2][CB];
-#pragma unroll
-  for (int qb = 0; qb < 2; qb++)
-#pragma unroll
-    for (int cb = 0; cb < CB; cb++) dq[qb][cb] = zero16();
-  const int kv_first = __builtin_amdgcn_readfirstlane(p.seg_start[min(t_wg, n - 1)] / BKEY);
-  const int kv_last = min(t_wg + QT - 1, n - 1) / BKEY;
-  const int total = kv_last - kv_first + 1;
-  // LDS position of chunk c of row r: c ^ f(r), f = the low four row bits in the order (1, 0, 2, 3)
-  auto swz = [](int row) { return ((row & 3) << 2) | (((row >> 2) & 1) << 1) | ((row >> 3) & 1); };
-  const int l4 = lane >> 4, lc = lane & 15;
-  const uint32_t off0 = (uint32_t)((((int64_t)(wave * 16 + l4)) * p.ldkv + ((lc ^ swz(l4)) * 8)) * 2);
-  auto stage = [&](int it, int st) {                           // the loads of key tile kv_first + it, from here (first two tiles, ragged tiles)
-    const int k0 = (kv_first + it) * BKEY;
-    unsigned char* d = dyn_smem256 + st * ST_B;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int row = wave * 16 + 4 * i + l4, tok = min(k0 + row, n - 1), ch = (lc ^ swz(row)) * 8;
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(K + (int64_t)tok * p.ldkv + g * DH + ch),
-                                       (__attribute__((address_space(3))) void*)(d + (wave * 4 + i) * 1024), 16, 0, 0);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int row = wave * 16 + 4 * i + l4, tok = min(k0 + row, n - 1), ch = (lc ^ swz(row)) * 8;
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(V + (int64_t)tok * p.ldkv + g * DH + ch),
-                                       (__attribute__((address_space(3))) void*)(d + KT_B + (wave * 4 + i) * 1024), 16, 0, 0);
-    }
-  };
-  const int sl = lane & 15, mh = (lane >> 4) & 1, row0 = 4 * h + (sl >> 2);
-  const uint32_t aR0 = lds0 + l31 * 256 + ((h ^ swz(l31)) * 16);
-  const uint32_t aT0 = lds0 + row0 * 256 + (((2 * mh + ((sl & 3) >> 1)) ^ swz(row0)) * 16) + (sl & 1) * 8;
-  if (total > 0) stage(0, 0);                                  // the first tiles travel while the wave fetches its own rows
-  if (total > 1) stage(1, 1);
-  int tq[2], ss[2];
-  float nl2[2], dl[2];
-  bf16x8 qf[2][KS], dof[2][KS];
-#pragma unroll
-  for (int qb = 0; qb < 2; qb++) {
-    tq[qb] = t_wg + qb * 32 + l31;
-    const int tc = min(tq[qb], n - 1);
-    ss[qb] = p.seg_start[tc];
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) {
-      qf[qb][ks] = *reinterpret_cast<const bf16x8*>(Q + (int64_t)tc * p.ldq + j * DH + ks * 16 + h * 8);
-      dof[qb][ks] = *reinterpret_cast<const bf16x8*>(dO + ((int64_t)tc * p.Hq + j) * DH + ks * 16 + h * 8);
-    }
-    nl2[qb] = -p.lse[(int64_t)tc * p.Hq + j] * 1.4426950408889634f;
-    dl[qb] = p.delta[(int64_t)tc * p.Hq + j];
-  }
-  int st = 0;
-  for (int it = 0; it < total; it++) {
-    if (it + 1 < total) __builtin_amdgcn_s_waitcnt(0x0f78); else __builtin_amdgcn_s_waitcnt(0x0f70);   // all but the next tile's eight loads
-    __syncthreads();
-    const int k0 = (kv_first + it) * BKEY;
-    const int nx = it + 2, k0n = (kv_first + nx) * BKEY, stn = st == 0 ? 2 : st - 1;      // (it + 2) % 3
-    const bool has = nx < total, fast = has && k0n + BKEY - 1 <= n - 1;
-    if (has && !fast) stage(nx, stn);
-    // 1: every query of the wave sees every key of the tile; 2: the tile touches the diagonal or a segment start
-    const int kind = (k0 + 63 <= t_wg && k0 >= ss_hi) ? 1 : 2;
-    const int mode = kind | (fast ? 4 : 0);
-    const uint32_t sb = st * ST_B, sbn = stn * ST_B;
-    const uint32_t aR = aR0 + sb, aT = aT0 + sb;
-    const int tb0 = k0 + 4 * h - ss[0], tb1 = k0 + 4 * h - ss[1], lim0 = tq[0] - ss[0], lim1 = tq[1] - ss[1];
-    const int k0c = has ? k0n : 0;
-    const uint64_t gk = (uint64_t)(K + g * DH + (int64_t)k0c * p.ldkv), gv = (uint64_t)(V + g * DH + (int64_t)k0c * p.ldkv);
-    const uint32_t str = (uint32_t)(4 * p.ldkv * 2);
-    const uint32_t m0t = lds0 + sbn + wave * 4096;
-    asm volatile(ATTN_DQ_TILE_ASM
-                 : "+a"(dq[0][0]), "+a"(dq[0][1]), "+a"(dq[0][2]), "+a"(dq[0][3]), "+a"(dq[1][0]), "+a"(dq[1][1]), "+a"(dq[1][2]), "+a"(dq[1][3])
-                 : "a"(qf[0][0]), "a"(qf[0][1]), "a"(qf[0][2]), "a"(qf[0][3]), "a"(qf[0][4]), "a"(qf[0][5]), "a"(qf[0][6]), "a"(qf[0][7]),
-                   "a"(qf[1][0]), "a"(qf[1][1]), "a"(qf[1][2]), "a"(qf[1][3]), "a"(qf[1][4]), "a"(qf[1][5]), "a"(qf[1][6]), "a"(qf[1][7]),
-                   "a"(dof[0][0]), "a"(dof[0][1]), "a"(dof[0][2]), "a"(dof[0][3]), "a"(dof[0][4]), "a"(dof[0][5]), "a"(dof[0][6]), "a"(dof[0][7]),
-                   "a"(dof[1][0]), "a"(dof[1][1]), "a"(dof[1][2]), "a"(dof[1][3]), "a"(dof[1][4]), "a"(dof[1][5]), "a"(dof[1][6]), "a"(dof[1][7]),
-                   "v"(aR), "v"(aT), "s"(sl2), "v"(nl2[0]), "v"(nl2[1]), "v"(dl[0]), "v"(dl[1]), "v"(tb0), "v"(tb1), "v"(lim0), "v"(lim1), "s"(mode),
-                   "s"(gk), "s"(gv), "s"(str), "v"(off0), "s"(m0t)
-                 : ATTN_DQ_TILE_CLOBBERS);
-    st = st == 2 ? 0 : st + 1;
-  }
-  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");            // the accumulators are read next: wait states of the last MFMA
-#pragma unroll
-  for (int qb = 0; qb < 2; qb++)
-    if (tq[qb] < n) store_grad_row<DH>(dq[qb], scale, (bf16_t*)p.dq + (int64_t)tq[qb] * p.ldq + j * DH, h, p.rope_cos, p.rope_sin, tq[qb] - ss[qb]);
-}
 
 // dK and dV in ONE pass (head_dim 128): S, the exponentials and dP are computed once, and the query heads of a KV head
 // are taken one after the other into the same accumulators (head order, then tile order: a fixed summation order, no
@@ -726,122 +626,223 @@ __device__ __forceinline__ void dq3_block(const AttnParams& p, float scale, floa
 // Every wave issues nine loads per tile (four kilobytes of Q, four of dO, and the tile's lse values (even waves) or
 // delta values (odd waves); those of waves 2 and 3 land in spare space), so that one count serves all waves.
 #include "attn_dkv_tile.inc"
-__device__ __forceinline__ void dkv3_block(const AttnParams& p, float scale, float sl2, int block) {
-  constexpr int DH = 128, KS = DH / 16, CB = DH / 32, NWV = 4, KPB = 32 * NWV, NST = 3;
-  constexpr int KT_B = BKEY * DH * 2;                     // bytes of a tile
-  constexpr int ST_B = 2 * KT_B + 1024;                   // Q, dO, 64 lse, 64 delta floats, 512 spare bytes
-  static_assert(ST_B % 256 == 0, "slice and column-block addresses are formed by XOR on a 256-byte aligned row address");
-  extern __shared__ __align__(256) unsigned char dyn_smem256[];
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)dyn_smem256;
-  if (lds0 & 255) return;                                       // never the case: the array is the kernel's only LDS
-  const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, h = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n = p.n, grp = p.Hq / p.Hkv;
-  int g, ki;
-  xcd_group_map(block, 2 * ((n + 255) / 256), p.Hkv, g, ki);
-  const int u_wg = (p.order_k ? p.order_k[ki >> 1] * 2 + (ki & 1) : ki) * KPB, u_base = u_wg + wave * 32;
-  if (u_wg >= n) return;                                        // the second half of a last, half-empty block of 256
-  const bf16_t* Q = (const bf16_t*)p.q; const bf16_t* K = (const bf16_t*)p.k; const bf16_t* V = (const bf16_t*)p.v;
-  const bf16_t* dO = (const bf16_t*)p.d_o;
-  const int64_t ldo = (int64_t)p.Hq * DH;
-  const int u = u_base + l31, uc = min(u, n - 1);
-  const int uend = (u < n) ? p.seg_end[uc] : 0;                 // queries u <= t < uend see this key
-  const int vis = (u < n) ? uend - u : 0;
-  f32x16 accK[CB], accV[CB];                                    // dK^T and dV^T, [dh rows, key lane]
-#pragma unroll
-  for (int cb = 0; cb < CB; cb++) { accK[cb] = zero16(); accV[cb] = zero16(); }
-  const int q_first = u_wg / BKEY;
-  const int q_last = __builtin_amdgcn_readfirstlane((p.seg_end[min(u_wg + KPB - 1, n - 1)] - 1) / BKEY);
-  const int w_end = (u_base < n) ? __builtin_amdgcn_readfirstlane(p.seg_end[min(u_base + 31, n - 1)]) : 0;
-  const int w_end_min = (u_base < n) ? __builtin_amdgcn_readfirstlane(p.seg_end[min(u_base, n - 1)]) : 0;
-  const int total = q_last - q_first + 1;                       // query tiles per head
-  const int steps = total * grp;                                // the query heads of the group one after the other: step = (head, tile)
-  // LDS position of chunk c of row r: c ^ f(r), f = the low four row bits in the order (1, 0, 2, 3)
-  auto swz = [](int row) { return ((row & 3) << 2) | (((row >> 2) & 1) << 1) | ((row >> 3) & 1); };
-  // a load instruction of a wave fills one kilobyte = four rows; lane -> row lane / 16, position lane % 16
-  const int l4 = lane >> 4, lc = lane & 15;
-  const uint32_t offQ0 = (uint32_t)((((int64_t)(wave * 16 + l4)) * p.ldq + ((lc ^ swz(l4)) * 8)) * 2);
-  const uint32_t offD0 = (uint32_t)((((int64_t)(wave * 16 + l4)) * ldo + ((lc ^ swz(l4)) * 8)) * 2);
-  const float* stat = (wave & 1) ? p.delta : p.lse;             // this wave's ninth load
-  auto stat_ptr = [&](int jj, int t0) { return stat + (int64_t)min(t0 + lane, n - 1) * p.Hq + jj; };
-  auto stage = [&](int hh, int it, int st) {                   // the loads of tile `it` of head hh, from here (first two steps, ragged tiles)
-    const int t0 = (q_last - it) * BKEY, jj = g * grp + hh;
-    unsigned char* d = dyn_smem256 + st * ST_B;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int row = wave * 16 + 4 * i + l4, tok = min(t0 + row, n - 1), ch = (lc ^ swz(row)) * 8;
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Q + (int64_t)tok * p.ldq + jj * DH + ch),
-                                       (__attribute__((address_space(3))) void*)(d + (wave * 4 + i) * 1024), 16, 0, 0);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int row = wave * 16 + 4 * i + l4, tok = min(t0 + row, n - 1), ch = (lc ^ swz(row)) * 8;
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(dO + (int64_t)tok * ldo + jj * DH + ch),
-                                       (__attribute__((address_space(3))) void*)(d + KT_B + (wave * 4 + i) * 1024), 16, 0, 0);
-    }
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)stat_ptr(jj, t0),
-                                     (__attribute__((address_space(3))) void*)(d + 2 * KT_B + wave * 256), 4, 0, 0);
-  };
-  // this lane's row in a tile (256-byte rows, chunk h: slice ks is that address XOR 32 ks); its corner of the
-  // 4 row x 16 column patch of a transposing read (lanes 0..15 of a block: row s / 4, columns 4 (s % 4) ..; blocks:
-  // columns 16 (b & 1) .., rows 4 (b / 2) ..; the column block is an XOR of 64 cb, rows 8.. an XOR of 16 plus 2048);
-  // its four lse / delta values per eight queries
-  const int sl = lane & 15, mh = (lane >> 4) & 1, row0 = 4 * h + (sl >> 2);
-  const uint32_t aR0 = lds0 + l31 * 256 + ((h ^ swz(l31)) * 16);
-  const uint32_t aT0 = lds0 + row0 * 256 + (((2 * mh + ((sl & 3) >> 1)) ^ swz(row0)) * 16) + (sl & 1) * 8;
-  const uint32_t aL0 = lds0 + 2 * KT_B + 16 * h;
-  if (steps > 0) stage(0, 0, 0);                               // the first tiles travel while the wave fetches its own rows
-  if (steps > 1) { if (total > 1) stage(0, 1, 1); else stage(1, 0, 1); }
-  bf16x8 kf[KS], vf[KS];
-#pragma unroll
-  for (int ks = 0; ks < KS; ks++) {
-    kf[ks] = *reinterpret_cast<const bf16x8*>(K + (int64_t)uc * p.ldkv + g * DH + ks * 16 + h * 8);
-    vf[ks] = *reinterpret_cast<const bf16x8*>(V + (int64_t)uc * p.ldkv + g * DH + ks * 16 + h * 8);
-  }
-  int st = 0, it = 0, hn = total > 2 ? 0 : (total == 2 ? 1 : 2), itn = total > 2 ? 2 : 0;   // (head, tile) of this step; of the step after next
-  for (int step = 0; step < steps; step++) {
-    if (step + 1 < steps) __builtin_amdgcn_s_waitcnt(0x0f79); else __builtin_amdgcn_s_waitcnt(0x0f70);   // all but the next step's nine loads
-    __syncthreads();
-    const int t0 = (q_last - it) * BKEY;
-    const int t0n = (q_last - itn) * BKEY, stn = st == 0 ? 2 : st - 1;                     // stage (step + 2) % 3
-    const bool has = step + 2 < steps, fast = has && t0n + BKEY - 1 <= n - 1;
-    if (has && !fast) stage(hn, itn, stn);
-    // 0: no query of the tile sees a key of this wave; 1: every query sees every key; 2: the tile touches the diagonal or a segment end
-    const int kind = (t0 + 63 < u_base || t0 >= w_end) ? 0 : ((t0 >= u_base + 31) && (t0 + 63 < w_end_min)) ? 1 : 2;
-    const int mode = kind | (fast ? 4 : 0);
-    const uint32_t sb = st * ST_B, sbn = stn * ST_B;
-    const uint32_t aR = aR0 + sb, aT = aT0 + sb, aL = aL0 + sb;
-    const int tb = t0 + 4 * h - u;
-    const int t0c = has ? t0n : 0;
-    const int jn = g * grp + (has ? hn : 0);
-    const uint64_t gq = (uint64_t)(Q + jn * DH + (int64_t)t0c * p.ldq), gd = (uint64_t)(dO + jn * DH + (int64_t)t0c * ldo);
-    const uint32_t strq = (uint32_t)(4 * p.ldq * 2), strd = (uint32_t)(4 * ldo * 2);
-    const uint32_t m0t = lds0 + sbn + wave * 4096, m0l = lds0 + sbn + 2 * KT_B + wave * 256;
-    const uint64_t vl = (uint64_t)stat_ptr(jn, t0c);
-    asm volatile(ATTN_DKV_TILE_ASM
-                 : "+a"(accK[0]), "+a"(accK[1]), "+a"(accK[2]), "+a"(accK[3]), "+a"(accV[0]), "+a"(accV[1]), "+a"(accV[2]), "+a"(accV[3])
-                 : "a"(kf[0]), "a"(kf[1]), "a"(kf[2]), "a"(kf[3]), "a"(kf[4]), "a"(kf[5]), "a"(kf[6]), "a"(kf[7]),
-                   "a"(vf[0]), "a"(vf[1]), "a"(vf[2]), "a"(vf[3]), "a"(vf[4]), "a"(vf[5]), "a"(vf[6]), "a"(vf[7]),
-                   "v"(aR), "v"(aT), "v"(aL), "s"(sl2), "v"(tb), "v"(vis), "s"(mode),
-                   "s"(gq), "s"(gd), "s"(strq), "s"(strd), "v"(offQ0), "v"(offD0), "s"(m0t), "v"(vl), "s"(m0l)
-                 : ATTN_DKV_TILE_CLOBBERS);
-    st = st == 2 ? 0 : st + 1;
-    if (++it == total) it = 0;
-    if (++itn == total) { itn = 0; hn++; }
-  }
-  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");            // the accumulators are read next: wait states of the last MFMA
-  if (u >= n) return;
-  const int pos = u - p.seg_start[u];
-  store_grad_row<DH>(accK, scale, (bf16_t*)p.dk + (int64_t)u * p.ldkv + g * DH, h, p.rope_cos, p.rope_sin, pos);
-  store_grad_row<DH>(accV, 1.f, (bf16_t*)p.dv + (int64_t)u * p.ldkv + g * DH, h, nullptr, p.rope_sin, pos);
-}
 
-// Workgroups of both kinds in one launch, those of dK / dV, which are the longest, first: neither kind waits for the other's last ones, and the few
-// of a short call run side by side.  As two launches (us, 32 heads over 8, then and so): 700 tokens 86 and 60, 3000 188 and 129, 6000 in segments up to 4096
-// 672 and 530, 12,000 608 and 547, 24,576 1397 and 1372.  The grid may end with dK / dV: then dQ is another kernel's.
+// The two kinds of workgroups: each in a launch of its own, or both in one, those of dK / dV, which are the longest, first, so that neither kind waits for
+// the other's last ones and the few of a short call run side by side (bwd_dh: which calls).  The bodies stand in the kernel: as functions that it calls
+// they compile to other registers, and dK / dV of one segment of 65,536 tokens took 68.1 ms for 65.7.
+enum { BWD_DQ, BWD_DKV, BWD_BOTH };
+template <int KIND>
 __global__ __launch_bounds__(256) void attn_bwd3_mfma(AttnParams p, float scale, float sl2, int dkv_blocks) {
-  if ((int)blockIdx.x < dkv_blocks) dkv3_block(p, scale, sl2, blockIdx.x);
-  else dq3_block(p, scale, sl2, (int)blockIdx.x - dkv_blocks);
+  if (KIND == BWD_DKV || (KIND == BWD_BOTH && (int)blockIdx.x < dkv_blocks)) {
+    const int block = blockIdx.x;
+    constexpr int DH = 128, KS = DH / 16, CB = DH / 32, NWV = 4, KPB = 32 * NWV, NST = 3;
+    constexpr int KT_B = BKEY * DH * 2;                     // bytes of a tile
+    constexpr int ST_B = 2 * KT_B + 1024;                   // Q, dO, 64 lse, 64 delta floats, 512 spare bytes
+    static_assert(ST_B % 256 == 0, "slice and column-block addresses are formed by XOR on a 256-byte aligned row address");
+    extern __shared__ __align__(256) unsigned char dyn_smem256[];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)dyn_smem256;
+    if (lds0 & 255) return;                                       // never the case: the array is the kernel's only LDS
+    const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = p.n, grp = p.Hq / p.Hkv;
+    int g, ki;
+    xcd_group_map(block, 2 * ((n + 255) / 256), p.Hkv, g, ki);
+    const int u_wg = (p.order_k ? p.order_k[ki >> 1] * 2 + (ki & 1) : ki) * KPB, u_base = u_wg + wave * 32;
+    if (u_wg >= n) return;                                        // the second half of a last, half-empty block of 256
+    const bf16_t* Q = (const bf16_t*)p.q; const bf16_t* K = (const bf16_t*)p.k; const bf16_t* V = (const bf16_t*)p.v;
+    const bf16_t* dO = (const bf16_t*)p.d_o;
+    const int64_t ldo = (int64_t)p.Hq * DH;
+    const int u = u_base + l31, uc = min(u, n - 1);
+    const int uend = (u < n) ? p.seg_end[uc] : 0;                 // queries u <= t < uend see this key
+    const int vis = (u < n) ? uend - u : 0;
+    f32x16 accK[CB], accV[CB];                                    // dK^T and dV^T, [dh rows, key lane]
+#pragma unroll
+    for (int cb = 0; cb < CB; cb++) { accK[cb] = zero16(); accV[cb] = zero16(); }
+    const int q_first = u_wg / BKEY;
+    const int q_last = __builtin_amdgcn_readfirstlane((p.seg_end[min(u_wg + KPB - 1, n - 1)] - 1) / BKEY);
+    const int w_end = (u_base < n) ? __builtin_amdgcn_readfirstlane(p.seg_end[min(u_base + 31, n - 1)]) : 0;
+    const int w_end_min = (u_base < n) ? __builtin_amdgcn_readfirstlane(p.seg_end[min(u_base, n - 1)]) : 0;
+    const int total = q_last - q_first + 1;                       // query tiles per head
+    const int steps = total * grp;                                // the query heads of the group one after the other: step = (head, tile)
+    // LDS position of chunk c of row r: c ^ f(r), f = the low four row bits in the order (1, 0, 2, 3)
+    auto swz = [](int row) { return ((row & 3) << 2) | (((row >> 2) & 1) << 1) | ((row >> 3) & 1); };
+    // a load instruction of a wave fills one kilobyte = four rows; lane -> row lane / 16, position lane % 16
+    const int l4 = lane >> 4, lc = lane & 15;
+    const uint32_t offQ0 = (uint32_t)((((int64_t)(wave * 16 + l4)) * p.ldq + ((lc ^ swz(l4)) * 8)) * 2);
+    const uint32_t offD0 = (uint32_t)((((int64_t)(wave * 16 + l4)) * ldo + ((lc ^ swz(l4)) * 8)) * 2);
+    const float* stat = (wave & 1) ? p.delta : p.lse;             // this wave's ninth load
+    auto stat_ptr = [&](int jj, int t0) { return stat + (int64_t)min(t0 + lane, n - 1) * p.Hq + jj; };
+    auto stage = [&](int hh, int it, int st) {                   // the loads of tile `it` of head hh, from here (first two steps, ragged tiles)
+      const int t0 = (q_last - it) * BKEY, jj = g * grp + hh;
+      unsigned char* d = dyn_smem256 + st * ST_B;
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const int row = wave * 16 + 4 * i + l4, tok = min(t0 + row, n - 1), ch = (lc ^ swz(row)) * 8;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Q + (int64_t)tok * p.ldq + jj * DH + ch),
+                                         (__attribute__((address_space(3))) void*)(d + (wave * 4 + i) * 1024), 16, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const int row = wave * 16 + 4 * i + l4, tok = min(t0 + row, n - 1), ch = (lc ^ swz(row)) * 8;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(dO + (int64_t)tok * ldo + jj * DH + ch),
+                                         (__attribute__((address_space(3))) void*)(d + KT_B + (wave * 4 + i) * 1024), 16, 0, 0);
+      }
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)stat_ptr(jj, t0),
+                                       (__attribute__((address_space(3))) void*)(d + 2 * KT_B + wave * 256), 4, 0, 0);
+    };
+    // this lane's row in a tile (256-byte rows, chunk h: slice ks is that address XOR 32 ks); its corner of the
+    // 4 row x 16 column patch of a transposing read (lanes 0..15 of a block: row s / 4, columns 4 (s % 4) ..; blocks:
+    // columns 16 (b & 1) .., rows 4 (b / 2) ..; the column block is an XOR of 64 cb, rows 8.. an XOR of 16 plus 2048);
+    // its four lse / delta values per eight queries
+    const int sl = lane & 15, mh = (lane >> 4) & 1, row0 = 4 * h + (sl >> 2);
+    const uint32_t aR0 = lds0 + l31 * 256 + ((h ^ swz(l31)) * 16);
+    const uint32_t aT0 = lds0 + row0 * 256 + (((2 * mh + ((sl & 3) >> 1)) ^ swz(row0)) * 16) + (sl & 1) * 8;
+    const uint32_t aL0 = lds0 + 2 * KT_B + 16 * h;
+    if (steps > 0) stage(0, 0, 0);                               // the first tiles travel while the wave fetches its own rows
+    if (steps > 1) { if (total > 1) stage(0, 1, 1); else stage(1, 0, 1); }
+    bf16x8 kf[KS], vf[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) {
+      kf[ks] = *reinterpret_cast<const bf16x8*>(K + (int64_t)uc * p.ldkv + g * DH + ks * 16 + h * 8);
+      vf[ks] = *reinterpret_cast<const bf16x8*>(V + (int64_t)uc * p.ldkv + g * DH + ks * 16 + h * 8);
+    }
+    int st = 0, it = 0, hn = total > 2 ? 0 : (total == 2 ? 1 : 2), itn = total > 2 ? 2 : 0;   // (head, tile) of this step; of the step after next
+    for (int step = 0; step < steps; step++) {
+      if (step + 1 < steps) __builtin_amdgcn_s_waitcnt(0x0f79); else __builtin_amdgcn_s_waitcnt(0x0f70);   // all but the next step's nine loads
+      __syncthreads();
+      const int t0 = (q_last - it) * BKEY;
+      const int t0n = (q_last - itn) * BKEY, stn = st == 0 ? 2 : st - 1;                     // stage (step + 2) % 3
+      const bool has = step + 2 < steps, fast = has && t0n + BKEY - 1 <= n - 1;
+      if (has && !fast) stage(hn, itn, stn);
+      // 0: no query of the tile sees a key of this wave; 1: every query sees every key; 2: the tile touches the diagonal or a segment end
+      const int kind = (t0 + 63 < u_base || t0 >= w_end) ? 0 : ((t0 >= u_base + 31) && (t0 + 63 < w_end_min)) ? 1 : 2;
+      const int mode = kind | (fast ? 4 : 0);
+      const uint32_t sb = st * ST_B, sbn = stn * ST_B;
+      const uint32_t aR = aR0 + sb, aT = aT0 + sb, aL = aL0 + sb;
+      const int tb = t0 + 4 * h - u;
+      const int t0c = has ? t0n : 0;
+      const int jn = g * grp + (has ? hn : 0);
+      const uint64_t gq = (uint64_t)(Q + jn * DH + (int64_t)t0c * p.ldq), gd = (uint64_t)(dO + jn * DH + (int64_t)t0c * ldo);
+      const uint32_t strq = (uint32_t)(4 * p.ldq * 2), strd = (uint32_t)(4 * ldo * 2);
+      const uint32_t m0t = lds0 + sbn + wave * 4096, m0l = lds0 + sbn + 2 * KT_B + wave * 256;
+      const uint64_t vl = (uint64_t)stat_ptr(jn, t0c);
+      asm volatile(ATTN_DKV_TILE_ASM
+                   : "+a"(accK[0]), "+a"(accK[1]), "+a"(accK[2]), "+a"(accK[3]), "+a"(accV[0]), "+a"(accV[1]), "+a"(accV[2]), "+a"(accV[3])
+                   : "a"(kf[0]), "a"(kf[1]), "a"(kf[2]), "a"(kf[3]), "a"(kf[4]), "a"(kf[5]), "a"(kf[6]), "a"(kf[7]),
+                     "a"(vf[0]), "a"(vf[1]), "a"(vf[2]), "a"(vf[3]), "a"(vf[4]), "a"(vf[5]), "a"(vf[6]), "a"(vf[7]),
+                     "v"(aR), "v"(aT), "v"(aL), "s"(sl2), "v"(tb), "v"(vis), "s"(mode),
+                     "s"(gq), "s"(gd), "s"(strq), "s"(strd), "v"(offQ0), "v"(offD0), "s"(m0t), "v"(vl), "s"(m0l)
+                   : ATTN_DKV_TILE_CLOBBERS);
+      st = st == 2 ? 0 : st + 1;
+      if (++it == total) it = 0;
+      if (++itn == total) { itn = 0; hn++; }
+    }
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");            // the accumulators are read next: wait states of the last MFMA
+    if (u >= n) return;
+    const int pos = u - p.seg_start[u];
+    store_grad_row<DH>(accK, scale, (bf16_t*)p.dk + (int64_t)u * p.ldkv + g * DH, h, p.rope_cos, p.rope_sin, pos);
+    store_grad_row<DH>(accV, 1.f, (bf16_t*)p.dv + (int64_t)u * p.ldkv + g * DH, h, nullptr, p.rope_sin, pos);
+  } else {
+    const int block = KIND == BWD_BOTH ? (int)blockIdx.x - dkv_blocks : (int)blockIdx.x;
+    constexpr int DH = 128, KS = DH / 16, CB = DH / 32, QT = 64;
+    constexpr int KT_B = BKEY * DH * 2, ST_B = 2 * KT_B;   // bytes of a tile, of a stage (K, V)
+    extern __shared__ __align__(256) unsigned char dyn_smem256[];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)dyn_smem256;
+    if (lds0 & 255) return;                                       // never the case: the array is the kernel's only LDS
+    const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = p.n, grp = p.Hq / p.Hkv;
+    int hg, qi;
+    const int nqt = (n + QT - 1) / QT;
+    xcd_group_map(block, nqt, p.Hq / 4, hg, qi);
+    const int j = hg * 4 + wave, g = j / grp;
+    const int t_wg = (p.order_q ? p.order_q[qi] : nqt - 1 - qi) * QT;   // long rows first
+    const bf16_t* Q = (const bf16_t*)p.q; const bf16_t* K = (const bf16_t*)p.k; const bf16_t* V = (const bf16_t*)p.v;
+    const bf16_t* dO = (const bf16_t*)p.d_o;
+    const int ss_hi = __builtin_amdgcn_readfirstlane(p.seg_start[min(t_wg + QT - 1, n - 1)]);
+    f32x16 dq[2][CB];
+#pragma unroll
+    for (int qb = 0; qb < 2; qb++)
+#pragma unroll
+      for (int cb = 0; cb < CB; cb++) dq[qb][cb] = zero16();
+    const int kv_first = __builtin_amdgcn_readfirstlane(p.seg_start[min(t_wg, n - 1)] / BKEY);
+    const int kv_last = min(t_wg + QT - 1, n - 1) / BKEY;
+    const int total = kv_last - kv_first + 1;
+    // LDS position of chunk c of row r: c ^ f(r), f = the low four row bits in the order (1, 0, 2, 3)
+    auto swz = [](int row) { return ((row & 3) << 2) | (((row >> 2) & 1) << 1) | ((row >> 3) & 1); };
+    const int l4 = lane >> 4, lc = lane & 15;
+    const uint32_t off0 = (uint32_t)((((int64_t)(wave * 16 + l4)) * p.ldkv + ((lc ^ swz(l4)) * 8)) * 2);
+    auto stage = [&](int it, int st) {                           // the loads of key tile kv_first + it, from here (first two tiles, ragged tiles)
+      const int k0 = (kv_first + it) * BKEY;
+      unsigned char* d = dyn_smem256 + st * ST_B;
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const int row = wave * 16 + 4 * i + l4, tok = min(k0 + row, n - 1), ch = (lc ^ swz(row)) * 8;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(K + (int64_t)tok * p.ldkv + g * DH + ch),
+                                         (__attribute__((address_space(3))) void*)(d + (wave * 4 + i) * 1024), 16, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const int row = wave * 16 + 4 * i + l4, tok = min(k0 + row, n - 1), ch = (lc ^ swz(row)) * 8;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(V + (int64_t)tok * p.ldkv + g * DH + ch),
+                                         (__attribute__((address_space(3))) void*)(d + KT_B + (wave * 4 + i) * 1024), 16, 0, 0);
+      }
+    };
+    const int sl = lane & 15, mh = (lane >> 4) & 1, row0 = 4 * h + (sl >> 2);
+    const uint32_t aR0 = lds0 + l31 * 256 + ((h ^ swz(l31)) * 16);
+    const uint32_t aT0 = lds0 + row0 * 256 + (((2 * mh + ((sl & 3) >> 1)) ^ swz(row0)) * 16) + (sl & 1) * 8;
+    if (total > 0) stage(0, 0);                                  // the first tiles travel while the wave fetches its own rows
+    if (total > 1) stage(1, 1);
+    int tq[2], ss[2];
+    float nl2[2], dl[2];
+    bf16x8 qf[2][KS], dof[2][KS];
+#pragma unroll
+    for (int qb = 0; qb < 2; qb++) {
+      tq[qb] = t_wg + qb * 32 + l31;
+      const int tc = min(tq[qb], n - 1);
+      ss[qb] = p.seg_start[tc];
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++) {
+        qf[qb][ks] = *reinterpret_cast<const bf16x8*>(Q + (int64_t)tc * p.ldq + j * DH + ks * 16 + h * 8);
+        dof[qb][ks] = *reinterpret_cast<const bf16x8*>(dO + ((int64_t)tc * p.Hq + j) * DH + ks * 16 + h * 8);
+      }
+      nl2[qb] = -p.lse[(int64_t)tc * p.Hq + j] * 1.4426950408889634f;
+      dl[qb] = p.delta[(int64_t)tc * p.Hq + j];
+    }
+    int st = 0;
+    for (int it = 0; it < total; it++) {
+      if (it + 1 < total) __builtin_amdgcn_s_waitcnt(0x0f78); else __builtin_amdgcn_s_waitcnt(0x0f70);   // all but the next tile's eight loads
+      __syncthreads();
+      const int k0 = (kv_first + it) * BKEY;
+      const int nx = it + 2, k0n = (kv_first + nx) * BKEY, stn = st == 0 ? 2 : st - 1;      // (it + 2) % 3
+      const bool has = nx < total, fast = has && k0n + BKEY - 1 <= n - 1;
+      if (has && !fast) stage(nx, stn);
+      // 1: every query of the wave sees every key of the tile; 2: the tile touches the diagonal or a segment start
+      const int kind = (k0 + 63 <= t_wg && k0 >= ss_hi) ? 1 : 2;
+      const int mode = kind | (fast ? 4 : 0);
+      const uint32_t sb = st * ST_B, sbn = stn * ST_B;
+      const uint32_t aR = aR0 + sb, aT = aT0 + sb;
+      const int tb0 = k0 + 4 * h - ss[0], tb1 = k0 + 4 * h - ss[1], lim0 = tq[0] - ss[0], lim1 = tq[1] - ss[1];
+      const int k0c = has ? k0n : 0;
+      const uint64_t gk = (uint64_t)(K + g * DH + (int64_t)k0c * p.ldkv), gv = (uint64_t)(V + g * DH + (int64_t)k0c * p.ldkv);
+      const uint32_t str = (uint32_t)(4 * p.ldkv * 2);
+      const uint32_t m0t = lds0 + sbn + wave * 4096;
+      asm volatile(ATTN_DQ_TILE_ASM
+                   : "+a"(dq[0][0]), "+a"(dq[0][1]), "+a"(dq[0][2]), "+a"(dq[0][3]), "+a"(dq[1][0]), "+a"(dq[1][1]), "+a"(dq[1][2]), "+a"(dq[1][3])
+                   : "a"(qf[0][0]), "a"(qf[0][1]), "a"(qf[0][2]), "a"(qf[0][3]), "a"(qf[0][4]), "a"(qf[0][5]), "a"(qf[0][6]), "a"(qf[0][7]),
+                     "a"(qf[1][0]), "a"(qf[1][1]), "a"(qf[1][2]), "a"(qf[1][3]), "a"(qf[1][4]), "a"(qf[1][5]), "a"(qf[1][6]), "a"(qf[1][7]),
+                     "a"(dof[0][0]), "a"(dof[0][1]), "a"(dof[0][2]), "a"(dof[0][3]), "a"(dof[0][4]), "a"(dof[0][5]), "a"(dof[0][6]), "a"(dof[0][7]),
+                     "a"(dof[1][0]), "a"(dof[1][1]), "a"(dof[1][2]), "a"(dof[1][3]), "a"(dof[1][4]), "a"(dof[1][5]), "a"(dof[1][6]), "a"(dof[1][7]),
+                     "v"(aR), "v"(aT), "s"(sl2), "v"(nl2[0]), "v"(nl2[1]), "v"(dl[0]), "v"(dl[1]), "v"(tb0), "v"(tb1), "v"(lim0), "v"(lim1), "s"(mode),
+                     "s"(gk), "s"(gv), "s"(str), "v"(off0), "s"(m0t)
+                   : ATTN_DQ_TILE_CLOBBERS);
+      st = st == 2 ? 0 : st + 1;
+    }
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");            // the accumulators are read next: wait states of the last MFMA
+#pragma unroll
+    for (int qb = 0; qb < 2; qb++)
+      if (tq[qb] < n) store_grad_row<DH>(dq[qb], scale, (bf16_t*)p.dq + (int64_t)tq[qb] * p.ldq + j * DH, h, p.rope_cos, p.rope_sin, tq[qb] - ss[qb]);
+  }
 }
 
 // ------------------------------------------------------------------ head_dim 64
@@ -1429,11 +1430,24 @@ int launch_dkv2(as_ctx* ctx, const AttnParams& p, float scale, float sl2, float*
   return AS_OK;
 }
 
-int launch_bwd3(as_ctx* ctx, const AttnParams& p, float scale, float sl2, bool with_dq, hipStream_t st) {
-  constexpr size_t smem = (size_t)3 * (2 * BKEY * 128 * sizeof(bf16_t) + 1024);   // three stages of a Q and a dO tile, lse, delta; dQ's K and V tiles need less
-  AS_SET_SMEM(ctx, attn_bwd3_mfma, smem);
-  const int64_t dkv = 2 * cdiv(p.n, 256) * p.Hkv;          // a head's dQ blocks keep to one XCD whatever the remainder by eight is
-  attn_bwd3_mfma<<<(unsigned)(dkv + (with_dq ? cdiv(p.n, 64) * (p.Hq / 4) : 0)), 256, smem, st>>>(p, scale, sl2, (int)dkv);
+constexpr size_t kSmemDq3 = (size_t)3 * 2 * BKEY * 128 * sizeof(bf16_t);               // three stages of a K and a V tile
+constexpr size_t kSmemDkv3 = (size_t)3 * (2 * BKEY * 128 * sizeof(bf16_t) + 1024);      // three stages of a Q and a dO tile, lse, delta
+static_assert(kSmemDkv3 >= kSmemDq3, "the dQ blocks' stages fit");
+int launch_dq3(as_ctx* ctx, const AttnParams& p, float scale, float sl2, hipStream_t st) {
+  AS_SET_SMEM(ctx, attn_bwd3_mfma<BWD_DQ>, kSmemDq3);
+  attn_bwd3_mfma<BWD_DQ><<<(unsigned)(cdiv(p.n, 64) * (p.Hq / 4)), 256, kSmemDq3, st>>>(p, scale, sl2, 0);
+  AS_LAUNCH_CHECK(ctx);
+  return AS_OK;
+}
+int launch_dkv3(as_ctx* ctx, const AttnParams& p, float scale, float sl2, hipStream_t st) {
+  AS_SET_SMEM(ctx, attn_bwd3_mfma<BWD_DKV>, kSmemDkv3);
+  attn_bwd3_mfma<BWD_DKV><<<(unsigned)(2 * cdiv(p.n, 256) * p.Hkv), 256, kSmemDkv3, st>>>(p, scale, sl2, 0);
+  AS_LAUNCH_CHECK(ctx);
+  return AS_OK;
+}
+int launch_bwd3(as_ctx* ctx, const AttnParams& p, float scale, float sl2, int64_t dkv, hipStream_t st) {
+  AS_SET_SMEM(ctx, attn_bwd3_mfma<BWD_BOTH>, kSmemDkv3);
+  attn_bwd3_mfma<BWD_BOTH><<<(unsigned)(dkv + cdiv(p.n, 64) * (p.Hq / 4)), 256, kSmemDkv3, st>>>(p, scale, sl2, (int)dkv);      // a head's dQ blocks keep to one XCD whatever dkv's remainder by eight is
   AS_LAUNCH_CHECK(ctx);
   return AS_OK;
 }
@@ -1464,11 +1478,21 @@ int bwd_dh(as_ctx* ctx, const AttnParams& p_in, int variant, hipStream_t st) {
     }
     launch_delta<DH>(p, rows, st);
     AS_LAUNCH_CHECK(ctx);
-    if (dq_one_wave) return launch_bwd3(ctx, p, scale, sl2, true, st);
+    const int64_t dkv = 2 * cdiv(p.n, 256) * p.Hkv;
+    if (dq_one_wave) {
+      // Both kinds in one launch under four rounds of dK / dV workgroups (one a CU), twelve without a launch order: dQ fills the rounds' ends, which many
+      // rounds have little of where the longest workgroups come first, and the two kinds side by side find less of each other's tiles in L2.  Inside a
+      // step, apart -> together, per cent of both kernels' time: 0.6 rounds (2401 tokens, 8 KV heads) 21 less, 1.7: 17, 2.1: 11, 2.7: 5.5, 3.7: 3.3, 3.9: 2 less to 1 more (segments
+      // of 500); one segment of 16,384 (4.0) 2.3 more, 5 to 8: 0.6 less to 0.2 more, 10.8: 0.8 more, 14.4 (58,971 tokens) 1.1 more, 16 2.4 more.  Without an order (mixed
+      // segments): 14,000 tokens 10 less, 20,000 to 33,000 1 to 5, 45,000 2 less, 49,152 (12.0) 0.3 to 2 more, 58,971 1 less, 65,536 0 to 1.5 more.
+      if (dkv < (p.order_k ? 4 : 12) * kCus) return launch_bwd3(ctx, p, scale, sl2, dkv, st);
+      if ((rc = launch_dq3(ctx, p, scale, sl2, st))) return rc;
+      return launch_dkv3(ctx, p, scale, sl2, st);
+    }
     if (hpw == 4) rc = launch_dq2<DH, 4>(ctx, p, scale, sl2, st); else if (hpw == 2) rc = launch_dq2<DH, 2>(ctx, p, scale, sl2, st);
     else rc = launch_dq2<DH, 1>(ctx, p, scale, sl2, st);
     if (rc) return rc;
-    if (one_pass) return launch_bwd3(ctx, p, scale, sl2, false, st);     // sums over the query heads itself
+    if (one_pass) return launch_dkv3(ctx, p, scale, sl2, st);     // sums over the query heads itself
     if ((rc = launch_dkv2<DH, 0>(ctx, p, scale, sl2, part, st)) || (rc = launch_dkv2<DH, 1>(ctx, p, scale, sl2, part, st))) return rc;
   }
   if (p.Hq > p.Hkv) {

@@ -352,3 +352,16 @@ def test_fp32_steps_take_segments_of_so_many_tokens(dh):
         else:
             res, model, _, _ = G.run_step(sh, params, lora, trajs, 1, n, mode=B.AS_FP32)
             assert res["count"] == n - 2 and np.isfinite(res["loss"]) and all(torch.isfinite(x).all().item() for x in model.lora_grads[0]["q"])
+
+
+@pytest.mark.parametrize("tokens", [3840, 3841])
+def test_attention_backward_head_dim_128_in_one_launch_and_in_two(tokens):
+    """128 heads over 32: 3840 tokens are the last of a step that dQ and dK / dV share a launch for (under four rounds of dK / dV workgroups), 3841 the
+    first of two launches.  The bf16 tier's tolerances."""
+    import gpu_util as G
+    sh = synth.CONFIGS[1].replace(n_layers=1, d_model=64, n_q_heads=128, n_kv_heads=32, head_dim=128, ffn=64, vocab=256, lora_rank=8, lora_alpha=16.0,
+                                  lora_targets=("q", "k", "v"))
+    g = synth.rng(14, 0)
+    cuts = [0, 300, 301, 303, 559, 815] + list(range(900, 3800, 60)) + [tokens]
+    trajs = [[(2, g.integers(0, sh.vocab, size=e - b).astype(np.int32))] for b, e in zip(cuts, cuts[1:])]
+    G.compare_step(sh, 5, trajs, 1, tokens, bf16=True, loss_tol=2e-3, grad_tol=3e-2, skip=False)
