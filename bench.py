@@ -23,9 +23,9 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
 # HBM-side bytes per launch of the dominant kernel at config 3: FETCH_SIZE and WRITE_SIZE of two counter runs over one
 # bench step, each scaled by what the counter reads for a 1 GiB copy (profiles/bench_config3_counters.md).  The figure
 # belongs to the kernel sources those runs saw: the digest below names them, and the line reports null when they differ.
-TRAFFIC_BYTES_PER_LAUNCH = {(3, "gemm_mfma_rd_kernel<0, 0, *>"): 15.11e9}
+TRAFFIC_BYTES_PER_LAUNCH = {(3, "gemm_mfma_rd_kernel<0, 0, *>"): 15.04e9}
 TRAFFIC_SOURCES = ("gemm.hip", "gemm_items.h", "gemm_rd_loop.inc", "gemm_rd_nn_loop.inc", "common.h")
-TRAFFIC_SOURCE_DIGEST = "ed0a73f9426ccdcc"
+TRAFFIC_SOURCE_DIGEST = "786a4f49a2e4fae3"
 DOMINANT_KERNEL = "gemm_mfma_rd_kernel<0, 0, *>"               # dense models; expert GEMMs: the same kernel with live-row limits, <1>
 GROUPED_KERNEL = "gemm_mfma_rd_kernel<1, 0, *>"
 

@@ -290,9 +290,12 @@ int as_train_step(as_ctx* ctx, const as_weights* weights, const as_lora* lora,
  *  d_stats     [device] float[3]: loss, mean z_p ("reward margin"), fraction of pairs with z_p > 0.
  *  d_logp      [device] float [n_segments] or NULL: the policy's pi_s.
  *  Gradients are overwritten; with no pair they are exactly zero and the loss is 0.
- * All other arguments, the workspace size and the error behaviour are as_train_step's.  The
- * vocabulary head runs twice (per-target losses first, then the gradient rows, whose factor
- * depends on all sums); everything else runs once. */
+ * All other arguments, the workspace size and the error behaviour are as_train_step's.  The factor
+ * of a gradient row depends on all sums.  With adapters in AS_BF16 mode, where as_op_head_loss's
+ * conditions for one pass hold, the vocabulary product runs once as long as at most 8192 targets
+ * are kept (its exponentials are still there when the factors are known), and once more beyond
+ * that; otherwise it runs twice, for the losses and for the gradient rows.  Everything else runs
+ * once.  pi_s has the bits that as_sequence_logps gives for the same policy and batch. */
 int as_sequence_logps(as_ctx* ctx, const as_weights* weights, const as_lora* lora,
                       const int32_t* d_tokens, const int32_t* d_cu_seqlens,
                       const int32_t* h_cu_seqlens, int32_t n_segments, const uint8_t* h_seg_skip,
@@ -425,9 +428,12 @@ int as_op_attention_bwd(as_ctx* ctx, int mode, int variant, int64_t n, const int
  *  hf, dhf  [device] T [n_rows rounded up to a multiple of 256, d_model] (the products run over whole 256-row tiles);
  *  head     [device] T [vocab, d_model], 16-byte aligned; labels [device] int32 [n_rows]; row_w [device] float [n_rows] or NULL;
  *  loss_rows [device] float [n_rows].
- * In AS_BF16 mode with vocab a multiple of 256 and d_model a multiple of 64 no logits are stored: the product runs twice,
- * first with an epilogue that keeps per-block softmax statistics only, then with one that writes the gradient rows with
- * respect to the logits as bf16, 8192 target rows at a time.  Otherwise a float logits chunk of 4096 rows is used.
+ * In AS_BF16 mode with vocab a multiple of 256 and d_model a multiple of 64 no logits are stored, and 8192 target rows are done
+ * at a time.  The product runs once where the head is not trained and the product for dhf is large enough to read the head as
+ * it is (d_model a multiple of 256; 128 tiles of 256 x 256 in every chunk, or, inside a step, vocab of 8192 and more): its
+ * epilogue keeps per-block softmax statistics and writes the exponentials as bf16, and the row's sum and factor are applied
+ * to dhf.  Otherwise it runs twice, first with an epilogue that keeps the statistics only, then with one that writes
+ * the gradient rows with respect to the logits as bf16.  In AS_FP32 mode and at other sizes a float logits chunk of 4096 rows is used.
  * Workspace: as_op_head_loss_workspace bytes, 256-byte aligned.  d_model and vocab are the context's. */
 int as_op_head_loss_workspace(const as_ctx* ctx, int mode, int64_t n_rows, size_t* bytes);
 int as_op_head_loss(as_ctx* ctx, int mode, int64_t n_rows, const void* hf, const void* head, const int32_t* labels,

@@ -1,8 +1,9 @@
 // Preference learning (DPO; the paper's Sections 1 and 3.2 name it beside supervised fine-tuning, the
 // loss is the published DPO objective with a frozen reference policy): the small kernels between the
-// two passes over the vocabulary head.  Pass one yields -log p of every target; these kernels turn them
-// into per-segment sums pi_s, the pair loss and, per target row, the factor its (softmax - one-hot) row is
-// scaled with in pass two.  Every sum runs in a fixed order, in double.
+// losses of the vocabulary head and its gradient.  The head yields -log p of every target; these kernels turn them
+// into per-segment sums pi_s, the pair loss and, per target row, the factor of its (softmax - one-hot) row.  With one pass over
+// the head the factor is applied to the rows of dH, and the first 8192 targets' exponentials serve both; with two it
+// goes into the gradient rows of the second.  Every sum runs in a fixed order, in double.
 #include "common.h"
 
 // first target row whose token position is >= pos (rows are in token order)

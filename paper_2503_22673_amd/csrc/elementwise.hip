@@ -563,9 +563,9 @@ int launch_swiglu_bwd(as_ctx* ctx, int mode, int64_t n, int F, const void* dm, c
 // SwiGLU and the adapter products that read its result, in one pass (bf16, rank up to 16): u = m A^T forward (down's adapter), du = dgate Bg
 // and dup Bu backward (gate's and up's).  A kernel of their own reads m, or dgate and dup, a second time.  16 tokens per workgroup, its eight
 // waves take every eighth 64 columns, the next step's operands on their way.  Loads and stores are eight lanes to 128 bytes of a row
-// (neighbouring lanes in different rows, the product's own operand layout, cost a clock a lane: 590 us where this takes 455); the
+// (neighbouring lanes in different rows, the product's own operand layout, cost a clock a lane: 590 us where this takes 457); the
 // rounded result passes through 2 KB of the wave's LDS into that layout, the adapter comes from L2 in it (PrepMatrix::frag), the waves' sums meet at the end.
-// 24,710 tokens x 8192: forward 259 us, 307 as two kernels (5.2 TB/s of what has to move), backward 455 and 539 (4.9).  Of rank 64, on 14336
+// 24,710 tokens x 8192: forward 262 us, 307 as two kernels (5.2 TB/s of what has to move), backward 457 and 539 (4.9); the exact divisions are 2 and 7 of them.  Of rank 64, on 14336
 // columns, it takes 270 + 524 us where the kernels one after the other take 262 + 515 (the adapter's rows are then four times the traffic from L2).
 // Under one workgroup per CU (sixteen waves each: 626 tokens, a step of two layers 1.420 ms, 1.412 with two kernels) the rows stay with two kernels.
 struct SwigluAdapter { const bf16_t* frag[2]; int rp; bf16_t* u; };        // frag: A of down forward; B of gate, of up backward

@@ -786,6 +786,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(GemmParams p, int t
   }
 }
 
+// sum of the splits in order, then the epilogue
 __global__ __launch_bounds__(256) void gemm_splitk_finish_kernel(GemmParams p) {
   const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4, mn = (int64_t)p.M * p.N;
   if (idx >= mn) return;
@@ -954,7 +955,7 @@ __device__ __forceinline__ void rd_staged(const GemmParams& p, f32x16 (&t)[4], u
   }
 #pragma unroll
   for (int a = 0; a < 2; a++) {
-    float neg_lse2 = 0.f, wrow = 0.f, sum_scale = 0.f; int clab = -1;
+    float neg_lse2 = 0.f, wrow = 0.f, soft = 0.f; int clab = -1;
     // rows outside the live range compute with the last live row's values and are not written
     const int rr = o.row0 + 32 * i + 16 * a + l15, r = MASK ? min(max(rr, o.row_lo), o.row_hi - 1) : rr;
     if (EPI == GEMM_EPI_PROB) neg_lse2 = -kLog2e * p.epi_lse[r];
@@ -963,7 +964,7 @@ __device__ __forceinline__ void rd_staged(const GemmParams& p, f32x16 (&t)[4], u
     if (EPI == GEMM_EPI_PROB || EPI == GEMM_EPI_SOFT) clab = p.epi_lab[r] - o.col0 - 4 * q;   // position of the label among this lane's columns of the block, if any
     if (EPI == GEMM_EPI_SOFT) {
       const float2 st = row_stats(t, a, 1.f);              // t: the exponentials of the statistics from here on
-      sum_scale = soft_scale(st.x, soft_exponent(p.epi_zlab[r], st.x));
+      soft = soft_scale(st.x, soft_exponent(p.epi_zlab[r], st.x));
       if (lane < 16 && (!MASK || r == rr)) *(reinterpret_cast<float2*>(p.epi_part) + (int64_t)r * (p.N / 128) + o.col0 / 128) = st;
     }
 #pragma unroll
@@ -978,7 +979,7 @@ __device__ __forceinline__ void rd_staged(const GemmParams& p, f32x16 (&t)[4], u
         }
         if (EPI == GEMM_EPI_SOFT) {
 #pragma unroll
-          for (int k = 0; k < 4; k++) v[k] *= sum_scale;
+          for (int k = 0; k < 4; k++) v[k] *= soft;
           const int at_k = clab - (32 * j + 16 * b);       // one block in V / 128 holds a row's label
           if (at_k >= 0 && at_k < 4 && (!MASK || r == rr)) p.epi_elab[r] = at_k == 0 ? v[0] : at_k == 1 ? v[1] : at_k == 2 ? v[2] : v[3];
         }
